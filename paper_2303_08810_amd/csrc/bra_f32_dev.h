@@ -1,0 +1,438 @@
+// Device-side kernels of the float32 family: products on v_mfma_f32_16x16x4_f32 (internal).
+//
+// Lane 16 g + i of that instruction holds A[row i][k g], B[k g][col i] and D[rows 4 g + j][col i].
+// A lane that loads 4 consecutive values of the contraction axis feeds 4 such products: product e of
+// step s then contracts over {16 s + 4 g' + e}, any order being right as long as both operands use the
+// same one.  The float32 instruction runs at 64 flops per clock and SIMD, twice the vector unit without
+// packed float32, and takes its operands 16 bytes per lane and 4 products, where a vector FMA reads LDS
+// for every few flops: the vector kernels this replaces were bound by LDS reads and instruction issue.
+//
+// Every kernel takes float or bf16 tensors (template types) and any channel count; VEC selects 4-channel
+// loads, for channel counts that are multiples of 4.
+#pragma once
+
+#include "bra_mfma_dev.h"
+
+namespace bra {
+namespace f32 {
+
+using mfma::bf16_hi;
+using mfma::bf16_lo;
+using mfma::cross_row_max;
+using mfma::cross_row_sum;
+using mfma::f32x2;
+using mfma::f32x4;
+using mfma::kWave;
+using mfma::u32x2;
+
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// 4 consecutive elements as float32: p 16-byte (float) or 8-byte (bf16) aligned with VEC; without VEC
+// elements past `left` read as zero.
+template <bool VEC>
+__device__ __forceinline__ f32x4 load4(const float *p, int left)
+{
+    if (VEC) return *(const f32x4 *)p;
+    return f32x4{left > 0 ? p[0] : 0.f, left > 1 ? p[1] : 0.f, left > 2 ? p[2] : 0.f, left > 3 ? p[3] : 0.f};
+}
+template <bool VEC>
+__device__ __forceinline__ f32x4 load4(const bf16_t *p, int left)
+{
+    if (VEC) {
+        const u32x2 u = *(const u32x2 *)p;
+        return f32x4{bf16_lo(u[0]), bf16_hi(u[0]), bf16_lo(u[1]), bf16_hi(u[1])};
+    }
+    return f32x4{left > 0 ? bf16_to_f32(p[0]) : 0.f, left > 1 ? bf16_to_f32(p[1]) : 0.f,
+                 left > 2 ? bf16_to_f32(p[2]) : 0.f, left > 3 ? bf16_to_f32(p[3]) : 0.f};
+}
+template <bool VEC>
+__device__ __forceinline__ void store4(float *p, f32x4 v, int left)
+{
+    if (VEC) { *(f32x4 *)p = v; return; }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (e < left) p[e] = v[e];
+}
+template <bool VEC>
+__device__ __forceinline__ void store4(bf16_t *p, f32x4 v, int left)
+{
+    if (VEC) { *(u32x2 *)p = mfma::pack4(v); return; }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (e < left) p[e] = f32_to_bf16(v[e]);
+}
+
+// ---------------------------------------------------------------------------
+// Out[m][n] = act(sum_k A[m][k] B[k][n] + bias[n]) + res[m][n] in float32, for a tile of 64 rows x BN
+// columns per workgroup, the contraction in chunks of 32 staged in LDS (the next chunk is requested while
+// the current one is multiplied).  The four wavefronts split the tile 2 x 2; the product is formed
+// transposed (D[column 4 g + j][row i]), so that a lane stores 4 consecutive columns of one row.
+// BT: B is read transposed (B[k][n] = Bm[n * ldb + k]).
+// LDS pitches: 16-byte reads of 16 rows at 36 floats and 4-byte reads of 16 consecutive floats in 4 rows
+// 4 pitches apart (BN + 4) both touch every bank once.
+constexpr int kGemmBM = 64, kGemmBK = 32;
+
+template <typename TA, typename TB, typename TO>
+struct GemmJob {
+    const TA *A;
+    const TB *Bm;
+    TO *Out;
+    long M;
+    int lda, ldb, ldo, N, K;
+    const float *bias;
+    const TO *res;          // the layout of Out
+    int gelu;
+};
+
+template <bool BT, bool VEC, int BN, typename TA, typename TB, typename TO>
+__device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int block, float *smem)
+{
+    constexpr int BK = kGemmBK, PA = BK + 4, PB = BT ? BK + 4 : BN + 4, NT = BN / 32;
+    float *As = smem, *Bs = smem + kGemmBM * PA;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int ntiles = (J.N + BN - 1) / BN;
+    const long m0 = (long)(block / ntiles) * kGemmBM;
+    const int n0 = (block % ntiles) * BN;
+    constexpr int NA = kGemmBM * BK / 4 / 256, NB = BN * BK / 4 / 256;
+    f32x4 ra[NA], rb[NB];
+    // rows past the end repeat the last one (never stored); k past the end reads as zero on both sides
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < NA; ++u) {
+            const int idx = tid + 256 * u, k = k0 + 4 * (idx % (BK / 4));
+            const long m = min(m0 + idx / (BK / 4), J.M - 1);
+            ra[u] = load4<VEC>(J.A + m * J.lda + (VEC ? min(k, J.K - 4) : k), J.K - k);
+            if (VEC && k >= J.K) ra[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int idx = tid + 256 * u;
+            if (BT) {
+                const int k = k0 + 4 * (idx % (BK / 4)), n = min(n0 + idx / (BK / 4), J.N - 1);
+                rb[u] = load4<VEC>(J.Bm + (long)n * J.ldb + (VEC ? min(k, J.K - 4) : k), J.K - k);
+                if (VEC && k >= J.K) rb[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            } else {
+                const int k = k0 + idx / (BN / 4), n = n0 + 4 * (idx % (BN / 4));
+                const TB *row = J.Bm + (long)min(k, J.K - 1) * J.ldb;
+                rb[u] = load4<VEC>(row + (VEC ? min(n, J.N - 4) : n), J.N - n);
+                if (k >= J.K) rb[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+    };
+    const int wr = wave / 2, wc = wave % 2;
+    f32x4 acc[2][NT];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    fetch(0);
+    for (int k0 = 0; k0 < J.K; k0 += BK) {
+        if (k0) __syncthreads();                 // the previous chunk has been read
+#pragma unroll
+        for (int u = 0; u < NA; ++u) {
+            const int idx = tid + 256 * u;
+            *(f32x4 *)(As + (idx / (BK / 4)) * PA + 4 * (idx % (BK / 4))) = ra[u];
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int idx = tid + 256 * u;
+            if (BT) *(f32x4 *)(Bs + (idx / (BK / 4)) * PB + 4 * (idx % (BK / 4))) = rb[u];
+            else *(f32x4 *)(Bs + (idx / (BN / 4)) * PB + 4 * (idx % (BN / 4))) = rb[u];
+        }
+        __syncthreads();
+        if (k0 + BK < J.K) fetch(k0 + BK);
+#pragma unroll
+        for (int s = 0; s < BK / 16; ++s) {
+            f32x4 xb[2], wa[NT];
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) xb[rt] = *(const f32x4 *)(As + (32 * wr + 16 * rt + i) * PA + 16 * s + 4 * g);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int n = (BN / 2) * wc + 16 * t + i;
+                if (BT) wa[t] = *(const f32x4 *)(Bs + n * PB + 16 * s + 4 * g);
+                else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) wa[t][e] = Bs[(16 * s + 4 * g + e) * PB + n];
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int rt = 0; rt < 2; ++rt) acc[rt][t] = mfma_f32(wa[t][e], xb[rt][e], acc[rt][t]);
+        }
+    }
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+        const long m = m0 + 32 * wr + 16 * rt + i;
+        if (m >= J.M) continue;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int n = n0 + (BN / 2) * wc + 16 * t + 4 * g, left = J.N - n;
+            if (left <= 0) continue;
+            f32x4 v = acc[rt][t];
+            if (J.bias) v += load4<VEC>(J.bias + n, left);
+            if (J.gelu) v = f32x4{gelu_f32(v[0]), gelu_f32(v[1]), gelu_f32(v[2]), gelu_f32(v[3])};
+            if (J.res) v += load4<VEC>(J.res + m * J.ldo + n, left);
+            store4<VEC>(J.Out + m * J.ldo + n, v, left);
+        }
+    }
+}
+
+template <int BN, bool BT>
+constexpr size_t gemm_lds_floats() { return (size_t)kGemmBM * (kGemmBK + 4) + (BT ? BN * (kGemmBK + 4) : kGemmBK * (BN + 4)); }
+
+// Workgroups below blocks0 do job J0, the rest J1 (of the same B matrix type, A and Out float32): the
+// region-level projection of the routing rides in the token projection's launch.
+template <bool BT, bool VEC, int BN, typename TA, typename TB, typename TO>
+__global__ __launch_bounds__(256) void k_gemm(GemmJob<TA, TB, TO> J0, GemmJob<float, TB, float> J1, int blocks0)
+{
+    __shared__ __attribute__((aligned(16))) float smem[gemm_lds_floats<BN, BT>()];
+    if ((int)blockIdx.x < blocks0) gemm_tile<BT, VEC, BN>(J0, blockIdx.x, smem);
+    else gemm_tile<BT, VEC, BN>(J1, (int)blockIdx.x - blocks0, smem);
+}
+
+// ---------------------------------------------------------------------------
+// Xr[b, r, :] = mean over the n tokens of region r.  SUB (a power of two up to 64) consecutive lanes share
+// one (image, region, 4-channel chunk): lane s adds tokens s, s + SUB, .. of the region (row-major), then
+// the partial sums are combined pairwise in a fixed order.
+template <typename T, bool VEC>
+__global__ __launch_bounds__(256) void k_pool(const T *__restrict__ X, float *__restrict__ Xr, Dims D, int SUB)
+{
+    const int CH = (D.C + 3) / 4;
+    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+    const long total = (long)D.B * D.R * CH, item = min(idx / SUB, total - 1);
+    const int sub = (int)(idx % SUB);
+    const int cc = (int)(item % CH), r = (int)((item / CH) % D.R), b = (int)(item / ((long)CH * D.R));
+    const T *base = X + (((size_t)b * D.H + (r / D.S) * D.rh) * D.W + (r % D.S) * D.rw) * D.C + 4 * cc;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int slot = sub; slot < D.n; slot += SUB) {
+        const int y = slot / D.rw, x = slot - y * D.rw;
+        acc += load4<VEC>(base + ((size_t)y * D.W + x) * D.C, D.C - 4 * cc);
+    }
+    for (int off = 1; off < SUB; off *= 2)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], off);
+    if (idx / SUB < total && sub == 0) store4<VEC>(Xr + ((size_t)b * D.R + r) * D.C + 4 * cc, acc * (1.0f / (float)D.n), D.C - 4 * cc);
+}
+
+// ---------------------------------------------------------------------------
+// Routed attention (Eq. 6, Eq. 1) in float32 for heads of at most DP (32 or 64) channels; QKV is
+// [B, N, 3C] (q | k | v per token).  Workgroup (image, region, query tile, HPW heads): wavefront w has the
+// head w / (4 / HPW) of the group and 16 queries; regions of at most 16 tokens put four heads side by
+// side, larger ones 64 queries of one head.  The k n routed keys are taken KB at a time: their K and V rows
+// (found by index in the projected map; no gathered tensor) go to LDS, the next block being requested
+// meanwhile; S^T = K Q^T (a lane ends with 4 consecutive keys of one query), one online softmax over all
+// routed keys, O^T += V^T P^T with the weights straight from the registers they were formed in.
+// Head channels past d are zero on both sides.
+template <int DP, int HPW>
+struct AttnShape {
+    static constexpr int CW = DP * HPW, P = CW + 4, KB = CW <= 64 ? 64 : 32, TPH = 4 / HPW, QT = 16 * TPH;
+};
+
+// Rows of a token map -> registers: channels of the workgroup's HPW heads, 4 at a time; head h0 + hl owns
+// channels [(h0 + hl) d, (h0 + hl + 1) d).
+template <int DP, bool VEC>
+__device__ __forceinline__ f32x4 load_head_chunk(const float *row, int c4, int h0, const Dims &D)
+{
+    const int h = h0 + 4 * c4 / DP, ch = (4 * c4) % DP;
+    const int left = h < D.heads ? D.d - ch : 0;
+    if (VEC) {
+        const f32x4 v = *(const f32x4 *)(row + (left > 0 ? h * D.d + ch : 0));
+        return left > 0 ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    return load4<false>(row + (left > 0 ? h * D.d + ch : 0), left);
+}
+
+template <int DP, int HPW, bool VEC>
+__global__ __launch_bounds__(256) void k_attention(const float *__restrict__ QKV, const int32_t *__restrict__ Ir,
+                                                   float *__restrict__ O, Dims D, int hgroups, int qtiles)
+{
+    typedef AttnShape<DP, HPW> L;
+    constexpr int P = L::P, KB = L::KB, CW = L::CW, KT = KB / 16, NS = DP / 16;
+    __shared__ __attribute__((aligned(16))) float Ks[KB * P];
+    __shared__ __attribute__((aligned(16))) float Vs[KB * P];
+    const int hg = blockIdx.x % hgroups, qt = (blockIdx.x / hgroups) % qtiles;
+    const int reg = (blockIdx.x / (hgroups * qtiles)) % D.R, b = blockIdx.x / (hgroups * qtiles * D.R);
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int C3 = 3 * D.C, kn = D.kn, hl = wave / L::TPH, h = hg * HPW + hl;
+    const float *img = QKV + (size_t)b * D.N * C3;
+    const int32_t *irp = Ir + ((size_t)b * D.R + reg) * D.k;
+    auto region_token = [&](int r, int slot) {
+        return ((r / D.S) * D.rh + slot / D.rw) * D.W + (r % D.S) * D.rw + slot % D.rw;
+    };
+    const int slot = L::QT * qt + 16 * (wave % L::TPH) + i;
+    const int qtok = region_token(reg, min(slot, D.n - 1));
+    f32x4 qf[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        qf[s] = load_head_chunk<DP, VEC>(img + (size_t)qtok * C3, 4 * s + g, h, D);
+
+    constexpr int NL = KB * CW / 4 / 256;
+    f32x4 kr[NL], vr[NL];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int idx = tid + 256 * u, key = min(k0 + idx / (CW / 4), kn - 1);   // past the end: the last key, masked below
+            const int p = key / D.n;
+            const float *row = img + (size_t)region_token(region_index(irp[p], D.R), key - p * D.n) * C3;
+            kr[u] = load_head_chunk<DP, VEC>(row + D.C, idx % (CW / 4), hg * HPW, D);
+            vr[u] = load_head_chunk<DP, VEC>(row + 2 * D.C, idx % (CW / 4), hg * HPW, D);
+        }
+    };
+    float m = -INFINITY, l = 0.f;
+    f32x4 acc[NS];
+#pragma unroll
+    for (int dt = 0; dt < NS; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const float c_exp = D.scale * 1.4426950408889634f;
+    fetch(0);
+    for (int k0 = 0; k0 < kn; k0 += KB) {
+        if (k0) __syncthreads();                 // the previous block has been read
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int idx = tid + 256 * u;
+            *(f32x4 *)(Ks + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = kr[u];
+            *(f32x4 *)(Vs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = vr[u];
+        }
+        __syncthreads();
+        if (k0 + KB < kn) fetch(k0 + KB);
+        f32x4 st[KT];
+#pragma unroll
+        for (int t = 0; t < KT; ++t) st[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            f32x4 kf[KT];
+#pragma unroll
+            for (int t = 0; t < KT; ++t) kf[t] = *(const f32x4 *)(Ks + (16 * t + i) * P + DP * hl + 16 * s + 4 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < KT; ++t) st[t] = mfma_f32(kf[t][e], qf[s][e], st[t]);   // S^T[key 16 t + 4 g + j][query i]
+        }
+        const int left = kn - k0;
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) st[t][j] = 16 * t + 4 * g + j < left ? st[t][j] : -INFINITY;
+        float mx = st[0][0];
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) mx = fmaxf(mx, st[t][j]);
+        const float m_new = fmaxf(m, cross_row_max(mx));          // finite: the block's first key exists
+        const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c_exp);
+        m = m_new;
+        float ls = 0.f;
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                st[t][j] = __builtin_amdgcn_exp2f((st[t][j] - m_new) * c_exp);
+                ls += st[t][j];
+            }
+        l = fmaf(l, alpha, cross_row_sum(ls));
+#pragma unroll
+        for (int dt = 0; dt < NS; ++dt) acc[dt] *= alpha;
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int dt = 0; dt < NS; ++dt)
+                    acc[dt] = mfma_f32(Vs[(16 * t + 4 * g + e) * P + DP * hl + 16 * dt + i], st[t][e], acc[dt]);
+    }
+    if (slot < D.n && h < D.heads) {
+        const float inv = 1.0f / l;
+        float *orow = O + ((size_t)b * D.N + qtok) * D.C + h * D.d;
+#pragma unroll
+        for (int dt = 0; dt < NS; ++dt) {
+            const int ch = 16 * dt + 4 * g;
+            if (ch < D.d) store4<VEC>(orow + ch, acc[dt] * inv, D.d - ch);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Out[t][c] += sum_{ky,kx} w[c][ky][kx] In[t + (ky - 2, kx - 2)][c] over the H x W map (zero outside):
+// LCE (Eq. 7); FLIP reverses the taps (its transpose, for the backward pass).  Workgroup: 64 channels of
+// 256 VW / 64 column pieces; a thread walks down kLceRows rows of one column with VW (2 or 1) channels: an
+// input row of 5 columns is read once and goes into the output rows it belongs to.  The taps pass through
+// LDS once per workgroup: read per thread from the [C][25] tensor they would cost a cache line per lane.
+// Row pitches ldi, ldo.
+constexpr int kLceRows = 4;
+
+template <typename TW, int VW, bool FLIP>
+__global__ __launch_bounds__(256) void k_lce(const float *__restrict__ In, int ldi, const TW *__restrict__ Wlce,
+                                             float *__restrict__ Out, int ldo, Dims D, int cblocks)
+{
+    __shared__ float taps[25][64];
+    constexpr int CPW = 64 / VW, COLS = 256 / CPW;
+    const int cb = blockIdx.x % cblocks, c0 = 64 * cb, yb_n = (D.H + kLceRows - 1) / kLceRows;
+    for (int e = threadIdx.x; e < min(64, D.C - c0) * 25; e += 256)
+        taps[FLIP ? 24 - e % 25 : e % 25][e / 25] = load_f32(Wlce + (size_t)c0 * 25 + e);
+    __syncthreads();
+    const int cl = ((int)threadIdx.x % CPW) * VW, c = c0 + cl;
+    const long q = (long)(blockIdx.x / cblocks) * COLS + threadIdx.x / CPW;
+    if (q >= (long)D.B * yb_n * D.W || c >= D.C) return;
+    const int x = (int)(q % D.W), y0 = (int)((q / D.W) % yb_n) * kLceRows;
+    const size_t b = q / ((long)D.W * yb_n);
+    const float *img = In + b * D.N * ldi + c;
+    float w[VW][25];
+#pragma unroll
+    for (int t = 0; t < 25; ++t)
+#pragma unroll
+        for (int v = 0; v < VW; ++v) w[v][t] = taps[t][cl + v];
+    float acc[kLceRows][VW];
+#pragma unroll
+    for (int r = 0; r < kLceRows; ++r)
+#pragma unroll
+        for (int v = 0; v < VW; ++v) acc[r][v] = 0.f;
+#pragma unroll
+    for (int dy = 0; dy < kLceRows + 4; ++dy) {
+        const int y = y0 + dy - 2;
+        const bool row_in = (unsigned)y < (unsigned)D.H;
+        float in[5][VW];
+#pragma unroll
+        for (int kx = 0; kx < 5; ++kx) {
+            const int xx = x + kx - 2;
+            const bool ok = row_in && (unsigned)xx < (unsigned)D.W;
+            const float *p = img + (size_t)(ok ? y * D.W + xx : 0) * ldi;
+            if (VW == 2) {
+                const f32x2 v2 = *(const f32x2 *)p;
+                in[kx][0] = ok ? v2[0] : 0.f;
+                in[kx][VW - 1] = ok ? v2[1] : 0.f;
+            } else {
+                in[kx][0] = ok ? *p : 0.f;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kLceRows; ++r) {
+            const int ky = dy - r;
+            if (ky < 0 || ky > 4) continue;
+#pragma unroll
+            for (int kx = 0; kx < 5; ++kx)
+#pragma unroll
+                for (int v = 0; v < VW; ++v) acc[r][v] = fmaf(w[v][5 * ky + kx], in[kx][v], acc[r][v]);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kLceRows; ++r) {
+        if (y0 + r >= D.H) break;
+        float *o = Out + (b * D.N + (size_t)(y0 + r) * D.W + x) * ldo + c;
+        if (VW == 2) {
+            f32x2 v2 = *(f32x2 *)o;
+            v2[0] += acc[r][0];
+            v2[1] += acc[r][VW - 1];
+            *(f32x2 *)o = v2;
+        } else {
+            *o += acc[r][0];
+        }
+    }
+}
+
+}  // namespace f32
+}  // namespace bra

@@ -1,13 +1,15 @@
-// Generic kernel family: scalar (VALU) float32 arithmetic, any valid shape.
+// Float32 kernel family: float32 arithmetic, any valid shape.
 //
-// Used for float32 tensors and for shapes the matrix-core kernels are not built
+// Used for float32 tensors and for shapes the bf16 matrix-core kernels are not built
 // for.  All intermediates (Q, K, V, attention output) are kept in float32 in the
 // workspace, whatever the storage type of X and Y.  The steps follow Sec. 3.2:
 // projection (Eq. 3), region pooling + affinity (Eq. 4), top-k (Eq. 5), routed
 // attention straight from the index (Eq. 6-7, no gathered tensor), LCE, W^o (Eq. 2).
+// Products run on the float32 matrix-core instruction (bra_f32_dev.h); routing rows, heads wider
+// than 64 channels and the block's LayerNorms are scalar kernels.
 // Region pooling uses mean(X^r) W = mean(X^r W), which is exact in real arithmetic
 // (the mean is linear; same argument as Appendix A).
-#include "bra_common.h"
+#include "bra_f32_dev.h"
 #include <type_traits>
 
 #include <math.h>
@@ -21,119 +23,18 @@ constexpr int kTopkSlots = 16;      // affinity values per lane: R <= 64 * 16
 constexpr int kAttnChunk = 1024;    // keys per online-softmax chunk
 constexpr int kAttnMaxD = 256;      // head width limit of the generic attention kernel
 
-// ---------------------------------------------------------------------------
-// out[M, N] = A[M, K] * Bm[K, N]  (row-major with leading dimensions), float32 FMA,
-// k ascending.  64 x 64 tile per workgroup, 4 x 4 outputs per thread.
-// BT: B is read transposed (B[k][n] = Bm[n * ldb + k]).
-template <typename TA, typename TB, typename TO, bool BT = false>
-__global__ __launch_bounds__(256) void gen_gemm(const TA *__restrict__ A, int lda,
-                                                const TB *__restrict__ Bm, int ldb,
-                                                TO *__restrict__ Out, int ldo, int M, int N, int K,
-                                                const float *__restrict__ bias = nullptr,
-                                                const TO *__restrict__ res = nullptr, int gelu = 0)
-{
-    __shared__ float As[16][64 + 4];
-    __shared__ float Bs[16][64];
-    const int tid = threadIdx.x;
-    const int tx = tid % 16, ty = tid / 16;
-    const long m0 = (long)blockIdx.x * 64;
-    const int n0 = blockIdx.y * 64;
-    float acc[4][4];
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-
-    // the next 16-deep slice is requested while the current one is multiplied
-    float ra[4], rb[4];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int idx = tid + i * 256;
-            const int r = idx / 16, kk = idx % 16;
-            const long gm = m0 + r;
-            ra[i] = (gm < M && k0 + kk < K) ? load_f32(A + gm * lda + k0 + kk) : 0.f;
-            const int kb = idx / 64, nn = idx % 64;
-            rb[i] = (k0 + kb < K && n0 + nn < N)
-                        ? load_f32(BT ? Bm + (long)(n0 + nn) * ldb + k0 + kb : Bm + (long)(k0 + kb) * ldb + n0 + nn)
-                        : 0.f;
-        }
-    };
-    fetch(0);
-    for (int k0 = 0; k0 < K; k0 += 16) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int idx = tid + i * 256;
-            As[idx % 16][idx / 16] = ra[i];
-            Bs[idx / 64][idx % 64] = rb[i];
-        }
-        __syncthreads();
-        if (k0 + 16 < K) fetch(k0 + 16);
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-            for (int i = 0; i < 4; ++i)
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-    for (int i = 0; i < 4; ++i) {
-        long gm = m0 + ty * 4 + i;
-        if (gm >= M) continue;
-        for (int j = 0; j < 4; ++j) {
-            int gn = n0 + tx * 4 + j;
-            if (gn >= N) continue;
-            // optional epilogue: + bias[column], GELU, + res[row][column] (the layout of Out)
-            float v = acc[i][j];
-            if (bias) v += bias[gn];
-            if (gelu) v = gelu_f32(v);
-            if (res) v += load_f32(res + gm * ldo + gn);
-            store_from_f32(Out + gm * ldo + gn, v);
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Xr[b, r, c] = mean over the n tokens of region r of X[b, :, :, c]; tokens are
-// summed in row-major order inside the region; one workgroup per (b, r),
-// and Qr[b, r, :] = Xr[b, r, :] Wq, Kr[b, r, :] = Xr[b, r, :] Wk from the means in LDS (Sec. 3.2).
-template <typename T>
-__global__ void gen_pool_qk(const T *__restrict__ X, const T *__restrict__ Wqkv, float *__restrict__ Xr,
-                            float *__restrict__ Qr, float *__restrict__ Kr, Dims D)
-{
-    extern __shared__ float xs[];
-    const int b = blockIdx.x / D.R, r = blockIdx.x % D.R;
-    const size_t row = blockIdx.x;
-    const int y0 = (r / D.S) * D.rh, x0 = (r % D.S) * D.rw;
-    const T *img = X + (size_t)b * D.N * D.C;
-    for (int c = threadIdx.x; c < D.C; c += blockDim.x) {
-        float s = 0.f;
-        for (int ry = 0; ry < D.rh; ++ry)
-            for (int rx = 0; rx < D.rw; ++rx)
-                s += load_f32(img + ((size_t)(y0 + ry) * D.W + x0 + rx) * D.C + c);
-        xs[c] = s / (float)D.n;
-        Xr[row * D.C + c] = xs[c];
-    }
-    __syncthreads();
-    for (int o = threadIdx.x; o < 2 * D.C; o += blockDim.x) {
-        float acc = 0.f;
-        for (int c = 0; c < D.C; ++c) acc = fmaf(xs[c], load_f32(Wqkv + (size_t)c * 3 * D.C + o), acc);
-        if (o < D.C) Qr[row * D.C + o] = acc;
-        else Kr[row * D.C + o - D.C] = acc;
-    }
-}
-
 // One wavefront per (b, i): row i of A^r = Q^r (K^r)^T (Eq. 4), then k rounds of a
 // wave-wide arg-max (Eq. 5).  Order: larger value first, equal values by smaller
 // index; NaN counts as -inf so that the k indices are always distinct and valid.
 __global__ __launch_bounds__(kWave) void gen_affinity_topk(const float *__restrict__ Qr,
-                                                           const float *__restrict__ Kr,
+                                                           const float *__restrict__ Kr, int ld,
                                                            int32_t *__restrict__ Ir,
                                                            float *__restrict__ Ar_opt, Dims D)
 {
     extern __shared__ float qs[];
     const int b = blockIdx.x / D.R, i = blockIdx.x % D.R;
     const int lane = threadIdx.x;
-    for (int c = lane; c < D.C; c += kWave) qs[c] = Qr[((size_t)b * D.R + i) * D.C + c];
+    for (int c = lane; c < D.C; c += kWave) qs[c] = Qr[((size_t)b * D.R + i) * ld + c];
     __syncthreads();
     float vals[kTopkSlots];
 #pragma unroll
@@ -141,7 +42,7 @@ __global__ __launch_bounds__(kWave) void gen_affinity_topk(const float *__restri
         const int j = lane + t * kWave;
         float a = -INFINITY;
         if (j < D.R) {
-            const float *kr = Kr + ((size_t)b * D.R + j) * D.C;
+            const float *kr = Kr + ((size_t)b * D.R + j) * ld;
             a = 0.f;
             for (int c = 0; c < D.C; ++c) a = fmaf(qs[c], kr[c], a);
             if (Ar_opt) Ar_opt[((size_t)b * D.R + i) * D.R + j] = a;
@@ -168,93 +69,6 @@ __global__ __launch_bounds__(kWave) void gen_affinity_topk(const float *__restri
         }
         if (bi % kWave == lane) taken |= 1u << (bi / kWave);
         if (lane == 0) Ir[((size_t)b * D.R + i) * D.k + p] = bi;
-    }
-}
-
-// Routed attention (Eq. 6, Eq. 1) for heads of at most 64 channels, with the keys staged in
-// LDS; QKV is [B, N, 3C] float32 (q | k | v per token).
-// Workgroup (b, region, head) takes its queries 16 at a time (4 per wavefront) and, per pass,
-// the routed keys 64 at a time: K and V rows of the block are copied into LDS with
-// consecutive lanes on consecutive channels, then lane u scores key u against each of the
-// wavefront's queries (Eq. 1, scaled), the online softmax state of a query lives in
-// registers, and lane c accumulates channel c of P V.
-constexpr int kAttnLdsD = 64;
-
-__global__ __launch_bounds__(256) void gen_attention_lds(const float *__restrict__ QKV,
-                                                         const int32_t *__restrict__ Ir,
-                                                         float *__restrict__ O, Dims D, float scale)
-{
-    __shared__ float Ks[64][kAttnLdsD + 1];
-    __shared__ float Vs[64][kAttnLdsD + 1];
-    __shared__ float qs[16][kAttnLdsD];
-    __shared__ float sc[16][64];
-    const int hd = blockIdx.x % D.heads;
-    const int reg = (blockIdx.x / D.heads) % D.R;
-    const int b = blockIdx.x / (D.heads * D.R);
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const int C3 = 3 * D.C, d = D.d;
-    const float *img = QKV + (size_t)b * D.N * C3;
-    const int32_t *irp = Ir + ((size_t)b * D.R + reg) * D.k;
-    const int y0 = (reg / D.S) * D.rh, x0 = (reg % D.S) * D.rw;
-
-    for (int s0 = 0; s0 < D.n; s0 += 16) {
-        // the 16 queries of this pass (past the end: the last one again; never stored)
-        for (int e = tid; e < 16 * d; e += 256) {
-            const int s = min(s0 + e / d, D.n - 1);
-            const int qtok = (y0 + s / D.rw) * D.W + x0 + s % D.rw;
-            qs[e / d][e % d] = img[(size_t)qtok * C3 + hd * d + e % d];
-        }
-        float m[4], l[4], acc[4];
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-            m[qq] = -INFINITY;
-            l[qq] = 0.f;
-            acc[qq] = 0.f;
-        }
-        for (int k0 = 0; k0 < D.kn; k0 += 64) {
-            const int cn = min(64, D.kn - k0);
-            __syncthreads();               // queries staged; the previous block has been read
-            for (int e = tid; e < 64 * d; e += 256) {
-                const int u = e / d, c = e % d;
-                const int key = min(k0 + u, D.kn - 1);
-                const int j = region_index(irp[key / D.n], D.R), slot = key % D.n;
-                const int tok = ((j / D.S) * D.rh + slot / D.rw) * D.W + (j % D.S) * D.rw + slot % D.rw;
-                const float *row = img + (size_t)tok * C3 + hd * d + c;
-                Ks[u][c] = row[D.C];
-                Vs[u][c] = row[2 * D.C];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-                const float *q = qs[4 * wave + qq];
-                float a = 0.f;
-                for (int c = 0; c < d; ++c) a = fmaf(q[c], Ks[lane][c], a);
-                a = lane < cn ? a * scale : -INFINITY;
-                float mx = a;
-                for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
-                const float m_new = fmaxf(m[qq], mx);
-                const float corr = (m[qq] == -INFINITY) ? 0.f : expf(m[qq] - m_new);
-                const float pv = lane < cn ? expf(a - m_new) : 0.f;
-                float ls = pv;
-                for (int off = 32; off >= 1; off >>= 1) ls += __shfl_xor(ls, off, kWave);
-                l[qq] = l[qq] * corr + ls;
-                m[qq] = m_new;
-                sc[4 * wave + qq][lane] = pv;      // read back by this wavefront only
-                float o = acc[qq] * corr;
-                if (lane < d)
-                    for (int u = 0; u < cn; ++u) o = fmaf(sc[4 * wave + qq][u], Vs[u][lane], o);
-                acc[qq] = o;
-            }
-        }
-        __syncthreads();                   // the next pass replaces the queries
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-            const int s = s0 + 4 * wave + qq;
-            if (s < D.n && lane < d) {
-                const int qtok = (y0 + s / D.rw) * D.W + x0 + s % D.rw;
-                O[((size_t)b * D.N + qtok) * D.C + hd * d + lane] = acc[qq] / l[qq];
-            }
-        }
     }
 }
 
@@ -350,34 +164,8 @@ __global__ __launch_bounds__(256) void gen_attention(const float *__restrict__ Q
     }
 }
 
-// O[b, y, x, c] += sum_{ky,kx} Wlce[c, ky, kx] * V[b, y+ky-2, x+kx-2, c], V = 0 outside.
-template <typename T>
-__global__ void gen_lce_add(const float *__restrict__ QKV, const T *__restrict__ Wlce,
-                            float *__restrict__ O, Dims D)
-{
-    const size_t total = (size_t)D.B * D.N * D.C;
-    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total) return;
-    const int c = e % D.C;
-    const size_t t = e / D.C;
-    const int x = t % D.W, y = (t / D.W) % D.H;
-    const size_t b = t / D.N;
-    const float *img = QKV + b * D.N * 3 * D.C + 2 * D.C + c;
-    float acc = 0.f;
-    for (int ky = 0; ky < 5; ++ky) {
-        const int yy = y + ky - 2;
-        if (yy < 0 || yy >= D.H) continue;
-        for (int kx = 0; kx < 5; ++kx) {
-            const int xx = x + kx - 2;
-            if (xx < 0 || xx >= D.W) continue;
-            acc = fmaf(load_f32(Wlce + (c * 5 + ky) * 5 + kx), img[((size_t)yy * D.W + xx) * 3 * D.C], acc);
-        }
-    }
-    O[e] += acc;
-}
-
 struct GenericWs {
-    float *qkv, *o, *xr, *qr, *kr;
+    float *qkv, *o, *xr, *qk;        // qk: Q^r | K^r, interleaved rows of 2C
     int32_t *ir;
     size_t bytes;
 };
@@ -392,27 +180,130 @@ GenericWs carve(const Dims &D, void *ws)
     w.qkv = (float *)take(tok * 3 * D.C * sizeof(float));
     w.o = (float *)take(tok * D.C * sizeof(float));
     w.xr = (float *)take(reg * D.C * sizeof(float));
-    w.qr = (float *)take(reg * D.C * sizeof(float));
-    w.kr = (float *)take(reg * D.C * sizeof(float));
+    w.qk = (float *)take(reg * 2 * D.C * sizeof(float));
     w.ir = (int32_t *)take(reg * D.k * sizeof(int32_t));
     w.bytes = off;
     return w;
 }
 
-template <typename T>
-void launch_route(const Dims &D, const T *X, const T *Wqkv, int32_t *Ir, float *Ar_opt,
-                  const GenericWs &w, hipStream_t st)
+constexpr int kAttnF32MaxD = 64;    // head width up to which attention runs on the matrix cores
+
+bool launched() { return hipGetLastError() == hipSuccess; }
+
+// One or two products in one launch (J1: NULL for one).  64-column tiles where 128-column ones would leave
+// the chip under-filled or half empty, as for the bf16 product.
+template <bool BT, bool VEC, typename TA, typename TB, typename TO>
+int launch_gemm_vec(const f32::GemmJob<TA, TB, TO> &J0, const f32::GemmJob<float, TB, float> *J1, hipStream_t st)
 {
-    const int regs = D.B * D.R;
+    const long mt0 = (J0.M + f32::kGemmBM - 1) / f32::kGemmBM;
+    const bool narrow = J0.N <= 64 || mt0 * ((J0.N + 127) / 128) < 512;
+    const int bn = narrow ? 64 : 128;
+    auto blocks = [&](long M, int N) { return (M + f32::kGemmBM - 1) / f32::kGemmBM * ((N + bn - 1) / bn); };
+    const long b0 = blocks(J0.M, J0.N), b1 = J1 ? blocks(J1->M, J1->N) : 0;
+    if (b0 + b1 > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    const f32::GemmJob<float, TB, float> none = {};
+    const f32::GemmJob<float, TB, float> &j1 = J1 ? *J1 : none;
+    if (narrow)
+        hipLaunchKernelGGL((f32::k_gemm<BT, VEC, 64, TA, TB, TO>), dim3((unsigned)(b0 + b1)), dim3(256), 0, st, J0, j1, (int)b0);
+    else
+        hipLaunchKernelGGL((f32::k_gemm<BT, VEC, 128, TA, TB, TO>), dim3((unsigned)(b0 + b1)), dim3(256), 0, st, J0, j1, (int)b0);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+template <bool BT, typename TA, typename TB, typename TO>
+int launch_gemm(const f32::GemmJob<TA, TB, TO> &J0, const f32::GemmJob<float, TB, float> *J1, hipStream_t st)
+{
+    auto quads = [](int a, int b, int c, int d, int e) { return (a | b | c | d | e) % 4 == 0; };
+    const bool vec = quads(J0.lda, J0.ldb, J0.ldo, J0.N, J0.K) && (!J1 || quads(J1->lda, J1->ldb, J1->ldo, J1->N, J1->K));
+    return vec ? launch_gemm_vec<BT, true>(J0, J1, st) : launch_gemm_vec<BT, false>(J0, J1, st);
+}
+
+template <typename T>
+void launch_pool(const Dims &D, const T *X, float *Xr, hipStream_t st)
+{
+    int sub = 1;                                               // lanes per (region, 4-channel chunk)
+    while (sub < 16 && 4 * sub <= D.n) sub *= 2;
+    const long items = (long)D.B * D.R * ((D.C + 3) / 4) * sub;
+    const dim3 grid((unsigned)((items + 255) / 256));
+    ProfScope ps(st, K_GEN_POOL);
+    if (D.C % 4 == 0) hipLaunchKernelGGL((f32::k_pool<T, true>), grid, dim3(256), 0, st, X, Xr, D, sub);
+    else hipLaunchKernelGGL((f32::k_pool<T, false>), grid, dim3(256), 0, st, X, Xr, D, sub);
+}
+
+// Q^r | K^r = Xr [Wq | Wk]: columns 0 .. 2C - 1 of Wqkv, interleaved rows of 2C.
+template <typename T>
+f32::GemmJob<float, T, float> region_job(const Dims &D, const T *Wqkv, const GenericWs &w)
+{
+    return {w.xr, Wqkv, w.qk, (long)D.B * D.R, D.C, 3 * D.C, 2 * D.C, 2 * D.C, D.C, nullptr, nullptr, 0};
+}
+
+int launch_topk(const Dims &D, const float *Qr, const float *Kr, int ld, int32_t *Ir, float *Ar_opt, hipStream_t st)
+{
+    if (D.R <= kWave && D.C % 4 == 0) return route_rows(D, Qr, Kr, ld, Ir, Ar_opt, st);
+    ProfScope ps(st, K_GEN_TOPK);
+    hipLaunchKernelGGL(gen_affinity_topk, dim3(D.B * D.R), dim3(kWave), D.C * sizeof(float), st, Qr, Kr, ld, Ir, Ar_opt, D);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+// Routing on its own: region means, their projection, rows of A^r and top-k.  The arithmetic of every entry is that
+// of forward_t, so both give the same index.
+template <typename T>
+int launch_route(const Dims &D, const T *X, const T *Wqkv, int32_t *Ir, float *Ar_opt, const GenericWs &w, hipStream_t st)
+{
+    launch_pool<T>(D, X, w.xr, st);
     {
-        ProfScope ps(st, K_GEN_POOL);
-        hipLaunchKernelGGL(gen_pool_qk<T>, dim3(regs), dim3(256), D.C * sizeof(float), st, X, Wqkv, w.xr, w.qr, w.kr, D);
+        ProfScope ps(st, K_GEN_REGION_QK);
+        const int rc = launch_gemm<false>(region_job<T>(D, Wqkv, w), (const f32::GemmJob<float, T, float> *)nullptr, st);
+        if (rc != BRA_OK) return rc;
     }
-    {
-        ProfScope ps(st, K_GEN_TOPK);
-        hipLaunchKernelGGL(gen_affinity_topk, dim3(regs), dim3(kWave), D.C * sizeof(float), st, w.qr,
-                           w.kr, Ir, Ar_opt, D);
+    return launch_topk(D, w.qk, w.qk + D.C, 2 * D.C, Ir, Ar_opt, st);
+}
+
+template <int DP, int HPW, bool VEC>
+int launch_attention_t(const Dims &D, const float *qkv, const int32_t *Ir, float *o, hipStream_t st)
+{
+    const int hgroups = (D.heads + HPW - 1) / HPW, qt = f32::AttnShape<DP, HPW>::QT, qtiles = (D.n + qt - 1) / qt;
+    const long blocks = (long)D.B * D.R * hgroups * qtiles;
+    if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((f32::k_attention<DP, HPW, VEC>), dim3((unsigned)blocks), dim3(256), 0, st, qkv, Ir, o, D, hgroups,
+                       qtiles);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+int launch_attention(const Dims &D, const float *qkv, const int32_t *Ir, float *o, hipStream_t st)
+{
+    ProfScope ps(st, K_GEN_ATTENTION);
+    if (D.d > kAttnF32MaxD) {
+        hipLaunchKernelGGL(gen_attention, dim3(D.B * D.R * D.heads), dim3(256), D.k * sizeof(int), st, qkv, Ir, o, D,
+                           D.scale);
+        return launched() ? BRA_OK : BRA_ERR_LAUNCH;
     }
+    // heads side by side where a region's queries do not fill four 16-query tiles
+    const int want = D.n <= 16 ? 4 : (D.n <= 32 ? 2 : 1), hpw = D.heads >= want ? want : (D.heads >= 2 && want >= 2 ? 2 : 1);
+    const bool vec = D.d % 4 == 0;
+    if (D.d <= 32) {
+        if (hpw == 4) return vec ? launch_attention_t<32, 4, true>(D, qkv, Ir, o, st) : launch_attention_t<32, 4, false>(D, qkv, Ir, o, st);
+        if (hpw == 2) return vec ? launch_attention_t<32, 2, true>(D, qkv, Ir, o, st) : launch_attention_t<32, 2, false>(D, qkv, Ir, o, st);
+        return vec ? launch_attention_t<32, 1, true>(D, qkv, Ir, o, st) : launch_attention_t<32, 1, false>(D, qkv, Ir, o, st);
+    }
+    if (hpw >= 2) return vec ? launch_attention_t<64, 2, true>(D, qkv, Ir, o, st) : launch_attention_t<64, 2, false>(D, qkv, Ir, o, st);
+    return vec ? launch_attention_t<64, 1, true>(D, qkv, Ir, o, st) : launch_attention_t<64, 1, false>(D, qkv, Ir, o, st);
+}
+
+// Out += LCE(In) (FLIP: its transpose), row pitches ldi, ldo.
+template <bool FLIP, typename T>
+int launch_lce(const Dims &D, const float *In, int ldi, const T *Wlce, float *Out, int ldo, hipStream_t st)
+{
+    const int cblocks = (D.C + 63) / 64;
+    const long pieces = (long)D.B * ((D.H + f32::kLceRows - 1) / f32::kLceRows) * D.W;
+    const bool pairs = D.C % 2 == 0;
+    const int cols = pairs ? 8 : 4;
+    const long blocks = (pieces + cols - 1) / cols * cblocks;
+    if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    ProfScope ps(st, K_GEN_LCE);
+    if (pairs) hipLaunchKernelGGL((f32::k_lce<T, 2, FLIP>), dim3((unsigned)blocks), dim3(256), 0, st, In, ldi, Wlce, Out, ldo, D, cblocks);
+    else hipLaunchKernelGGL((f32::k_lce<T, 1, FLIP>), dim3((unsigned)blocks), dim3(256), 0, st, In, ldi, Wlce, Out, ldo, D, cblocks);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
 template <typename T>
@@ -422,47 +313,40 @@ int forward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *Wl
     GenericWs w = carve(D, ws);
     if constexpr (std::is_same<T, float>::value) {
         if (f32_small_ok(D))
-            return f32_small_forward(D, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, w.qkv, w.qr, w.kr, st);
+            return f32_small_forward(D, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, w.qkv, w.qk, w.qk + (size_t)D.B * D.R * D.C, st);
     }
     const long M = (long)D.B * D.N;
+    const int C = D.C;
+    const f32::GemmJob<T, T, float> qkv_job = {X, Wqkv, w.qkv, M, C, 3 * C, 3 * C, 3 * C, C, nullptr, nullptr, 0};
     const int32_t *Ir = Ir_in_opt;
+    int rc;
     if (!Ir_in_opt) {
         int32_t *dst = Ir_out_opt ? Ir_out_opt : w.ir;
-        launch_route<T>(D, X, Wqkv, dst, nullptr, w, st);
+        launch_pool<T>(D, X, w.xr, st);
+        const f32::GemmJob<float, T, float> rj = region_job<T>(D, Wqkv, w);
+        {
+            ProfScope ps(st, K_GEN_GEMM_QKV);
+            rc = launch_gemm<false>(qkv_job, &rj, st);
+        }
+        if (rc != BRA_OK) return rc;
+        rc = launch_topk(D, w.qk, w.qk + C, 2 * C, dst, nullptr, st);
+        if (rc != BRA_OK) return rc;
         Ir = dst;
-    } else if (Ir_out_opt) {
-        if (hipMemcpyAsync(Ir_out_opt, Ir_in_opt, sizeof(int32_t) * (size_t)D.B * D.R * D.k,
-                           hipMemcpyDeviceToDevice, st) != hipSuccess)
+    } else {
+        if (Ir_out_opt && hipMemcpyAsync(Ir_out_opt, Ir_in_opt, sizeof(int32_t) * (size_t)D.B * D.R * D.k,
+                                         hipMemcpyDeviceToDevice, st) != hipSuccess)
             return BRA_ERR_LAUNCH;
-    }
-    dim3 g1((unsigned)((M + 63) / 64), (unsigned)((3 * D.C + 63) / 64));
-    {
         ProfScope ps(st, K_GEN_GEMM_QKV);
-        hipLaunchKernelGGL((gen_gemm<T, T, float>), g1, dim3(256), 0, st, X, D.C, Wqkv, 3 * D.C, w.qkv,
-                           3 * D.C, (int)M, 3 * D.C, D.C);
+        rc = launch_gemm<false>(qkv_job, (const f32::GemmJob<float, T, float> *)nullptr, st);
+        if (rc != BRA_OK) return rc;
     }
-    {
-        ProfScope ps(st, K_GEN_ATTENTION);
-        if (D.d <= kAttnLdsD)
-            hipLaunchKernelGGL(gen_attention_lds, dim3(D.B * D.R * D.heads), dim3(256), 0, st, w.qkv, Ir, w.o, D,
-                               D.scale);
-        else
-            hipLaunchKernelGGL(gen_attention, dim3(D.B * D.R * D.heads), dim3(256), D.k * sizeof(int), st,
-                               w.qkv, Ir, w.o, D, D.scale);
-    }
-    const size_t total = (size_t)M * D.C;
-    {
-        ProfScope ps(st, K_GEN_LCE);
-        hipLaunchKernelGGL(gen_lce_add<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                           w.qkv, Wlce, w.o, D);
-    }
-    dim3 g2((unsigned)((M + 63) / 64), (unsigned)((D.C + 63) / 64));
-    {
-        ProfScope ps(st, K_GEN_GEMM_WO);
-        hipLaunchKernelGGL((gen_gemm<float, T, T>), g2, dim3(256), 0, st, w.o, D.C, Wo, D.C, Y, D.C,
-                           (int)M, D.C, D.C);
-    }
-    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+    rc = launch_attention(D, w.qkv, Ir, w.o, st);
+    if (rc != BRA_OK) return rc;
+    rc = launch_lce<false>(D, w.qkv + 2 * C, 3 * C, Wlce, w.o, C, st);
+    if (rc != BRA_OK) return rc;
+    ProfScope ps(st, K_GEN_GEMM_WO);
+    return launch_gemm<false>(f32::GemmJob<float, T, T>{w.o, Wo, Y, M, C, C, C, C, C, nullptr, nullptr, 0},
+                              (const f32::GemmJob<float, T, float> *)nullptr, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -567,19 +451,16 @@ int block_t(const Dims &D, int hidden, float eps, const T *X, const bra_block_pa
         hipLaunchKernelGGL((gen_token_ln<T, false>), dim3(tgrid), dim3(256), strip, st, x1, y, (const T *)nullptr,
                            (const float *)nullptr, p.ln2_gamma, p.ln2_beta, x1, xn, D.H, D.W, D.C, M, eps);
     }
+    const f32::GemmJob<float, T, float> *none = nullptr;
     {
         ProfScope ps(st, K_BLK_MLP_IN);
-        dim3 g((unsigned)((M + 63) / 64), (unsigned)((hidden + 63) / 64));
-        hipLaunchKernelGGL((gen_gemm<T, T, T>), g, dim3(256), 0, st, xn, D.C, (const T *)p.W1, hidden, hd, hidden,
-                           (int)M, hidden, D.C, p.b1, (const T *)nullptr, 1);
+        rc = launch_gemm<false>(f32::GemmJob<T, T, T>{xn, (const T *)p.W1, hd, M, D.C, hidden, hidden, hidden, D.C, p.b1,
+                                                      nullptr, 1}, none, st);
+        if (rc != BRA_OK) return rc;
     }
-    {
-        ProfScope ps(st, K_BLK_MLP_OUT);
-        dim3 g((unsigned)((M + 63) / 64), (unsigned)((D.C + 63) / 64));
-        hipLaunchKernelGGL((gen_gemm<T, T, T>), g, dim3(256), 0, st, hd, hidden, (const T *)p.W2, D.C, Xout, D.C,
-                           (int)M, D.C, hidden, p.b2, x1, 0);
-    }
-    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+    ProfScope ps(st, K_BLK_MLP_OUT);
+    return launch_gemm<false>(f32::GemmJob<T, T, T>{hd, (const T *)p.W2, Xout, M, hidden, D.C, D.C, D.C, hidden, p.b2, x1, 0},
+                              none, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -791,31 +672,6 @@ inline size_t attention_bwd_smem(int d)
     return (size_t)(2 * 64 * (d + 1) + 2 * 16 * d + 2 * 16 * 64) * sizeof(float);
 }
 
-// dV += LCE^T(dO): dV[y, x, c] += sum w[c, ky, kx] dO[y - ky + 2, x - kx + 2, c]   (after the attention part)
-template <typename T>
-__global__ void gen_lce_bwd_dv(const float *__restrict__ dO, const T *__restrict__ Wlce, float *__restrict__ dQKV,
-                               Dims D)
-{
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t total = (size_t)D.B * D.N * D.C;
-    if (idx >= total) return;
-    const int c = (int)(idx % D.C);
-    const size_t tok = idx / D.C;
-    const int x = (int)(tok % D.W), y = (int)((tok / D.W) % D.H);
-    const size_t b = tok / D.N;
-    float acc = 0.f;
-    for (int ky = 0; ky < 5; ++ky) {
-        const int yy = y - ky + 2;
-        if (yy < 0 || yy >= D.H) continue;
-        for (int kx = 0; kx < 5; ++kx) {
-            const int xx = x - kx + 2;
-            if (xx < 0 || xx >= D.W) continue;
-            acc = fmaf(load_f32(Wlce + (size_t)c * 25 + ky * 5 + kx), dO[((b * D.H + yy) * D.W + xx) * D.C + c], acc);
-        }
-    }
-    dQKV[tok * 3 * D.C + 2 * D.C + c] += acc;
-}
-
 // dWlce[c, ky, kx] += sum over this workgroup's tokens of dO[y, x, c] V[y + ky - 2, x + kx - 2, c]:
 // blockIdx.y = tap, a thread per channel, atomic adds into the zeroed gradient.
 __global__ __launch_bounds__(256) void gen_lce_bwd_dw(const float *__restrict__ dO, const float *__restrict__ QKV,
@@ -875,7 +731,6 @@ int backward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *W
     const BwdWs w = carve_bwd(D, ws);
     const long M = (long)D.B * D.N;
     const int C = D.C, C3 = 3 * D.C;
-    const size_t total = (size_t)M * C;
     if (attention_bwd_smem(D.d) > 64 * 1024) {
         static bool opted = false;
         if (!opted) {
@@ -887,11 +742,12 @@ int backward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *W
     }
     ProfScope ps(st, K_GEN_BACKWARD);
     // forward intermediates again: Q | K | V (the attention output comes out of the backward kernel)
-    hipLaunchKernelGGL((gen_gemm<T, T, float>), dim3((unsigned)((M + 63) / 64), (unsigned)((C3 + 63) / 64)), dim3(256), 0,
-                       st, X, C, Wqkv, C3, w.qkv, C3, (int)M, C3, C);
+    const f32::GemmJob<float, T, float> *none = nullptr;
+    int rc = launch_gemm<false>(f32::GemmJob<T, T, float>{X, Wqkv, w.qkv, M, C, C3, C3, C3, C, nullptr, nullptr, 0}, none, st);
+    if (rc != BRA_OK) return rc;
     // dO = dY Wo^T
-    hipLaunchKernelGGL((gen_gemm<T, T, float, true>), dim3((unsigned)((M + 63) / 64), (unsigned)((C + 63) / 64)), dim3(256),
-                       0, st, dY, C, Wo, C, w.dO, C, (int)M, C, C);
+    rc = launch_gemm<true>(f32::GemmJob<T, T, float>{dY, Wo, w.dO, M, C, C, C, C, C, nullptr, nullptr, 0}, none, st);
+    if (rc != BRA_OK) return rc;
     fill_zero(dWo, (size_t)C * C, st);
     fill_zero(dWqkv, (size_t)C * C3, st);
     fill_zero(dWlce, (size_t)C * 25, st);
@@ -900,20 +756,22 @@ int backward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *W
     hipLaunchKernelGGL(gen_attention_bwd, dim3((unsigned)((long)D.B * D.R * D.heads * ((D.n + 15) / 16))), dim3(256),
                        attention_bwd_smem(D.d), st, w.qkv, Ir,
                        w.o, w.dO, w.dqkv, D, D.scale);
-    hipLaunchKernelGGL(gen_lce_add<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, w.qkv, Wlce, w.o, D);
+    rc = launch_lce<false>(D, w.qkv + 2 * C, C3, Wlce, w.o, C, st);
+    if (rc != BRA_OK) return rc;
     long splits = (M + 255) / 256;                 // enough workgroups to fill the chip
     splits = splits > 4096 ? 4096 : splits;
     const long rows = ((M + splits - 1) / splits + 15) / 16 * 16;
     hipLaunchKernelGGL((gen_gemm_tn<float, T>), dim3((unsigned)((C + 63) / 64), (unsigned)((C + 63) / 64), (unsigned)splits),
                        dim3(256), 0, st, w.o, C, dY, C, dWo, C, M, C, C, rows);
     // the LCE parts
-    hipLaunchKernelGGL(gen_lce_bwd_dv<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, w.dO, Wlce, w.dqkv, D);
+    rc = launch_lce<true>(D, w.dO, C, Wlce, w.dqkv + 2 * C, C3, st);
+    if (rc != BRA_OK) return rc;
     const long tpw = 512;
     hipLaunchKernelGGL(gen_lce_bwd_dw, dim3((unsigned)((M + tpw - 1) / tpw), 25), dim3(256), 0, st, w.dO, w.qkv, dWlce, D,
                        tpw);
     // dX = [dQ | dK | dV] Wqkv^T, dWqkv = X^T [dQ | dK | dV]
-    hipLaunchKernelGGL((gen_gemm<float, T, T, true>), dim3((unsigned)((M + 63) / 64), (unsigned)((C + 63) / 64)), dim3(256),
-                       0, st, w.dqkv, C3, Wqkv, C3, dX, C, (int)M, C, C3);
+    rc = launch_gemm<true>(f32::GemmJob<float, T, T>{w.dqkv, Wqkv, dX, M, C3, C3, C, C, C3, nullptr, nullptr, 0}, none, st);
+    if (rc != BRA_OK) return rc;
     hipLaunchKernelGGL((gen_gemm_tn<T, float>), dim3((unsigned)((C + 63) / 64), (unsigned)((C3 + 63) / 64), (unsigned)splits),
                        dim3(256), 0, st, X, C, w.dqkv, C3, dWqkv, C3, M, C, C3, rows);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
@@ -975,12 +833,10 @@ int generic_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, f
 {
     GenericWs w = carve(D, ws);
     if (f32_small_ok(D))      // the kernels that bra_forward runs for this shape, so that both give the same index
-        return f32_small_route(D, (const float *)X, (const float *)Wqkv, Ir, Ar_opt, w.qkv, w.qr, w.kr, st);
+        return f32_small_route(D, (const float *)X, (const float *)Wqkv, Ir, Ar_opt, w.qkv, w.qk, w.qk + (size_t)D.B * D.R * D.C, st);
     if (D.dtype == BRA_F32)
-        launch_route<float>(D, (const float *)X, (const float *)Wqkv, Ir, Ar_opt, w, st);
-    else
-        launch_route<bf16_t>(D, (const bf16_t *)X, (const bf16_t *)Wqkv, Ir, Ar_opt, w, st);
-    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+        return launch_route<float>(D, (const float *)X, (const float *)Wqkv, Ir, Ar_opt, w, st);
+    return launch_route<bf16_t>(D, (const bf16_t *)X, (const bf16_t *)Wqkv, Ir, Ar_opt, w, st);
 }
 
 int generic_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
@@ -1008,10 +864,7 @@ size_t valu_route_scratch_bytes(const Dims &D)
 int valu_affinity_topk(const Dims &D, const float *Qr, const float *Kr, int32_t *Ir, float *Ar_opt,
                        hipStream_t st)
 {
-    ProfScope ps(st, K_GEN_TOPK);
-    hipLaunchKernelGGL(gen_affinity_topk, dim3(D.B * D.R), dim3(kWave), D.C * sizeof(float), st, Qr, Kr, Ir,
-                       Ar_opt, D);
-    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+    return launch_topk(D, Qr, Kr, D.C, Ir, Ar_opt, st);
 }
 
 int valu_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt,
@@ -1020,13 +873,10 @@ int valu_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, floa
     GenericWs w;
     const size_t each = align256((size_t)D.B * D.R * D.C * sizeof(float));
     w.xr = (float *)scratch;
-    w.qr = (float *)((char *)scratch + each);
-    w.kr = (float *)((char *)scratch + 2 * each);
+    w.qk = (float *)((char *)scratch + each);
     if (D.dtype == BRA_F32)
-        launch_route<float>(D, (const float *)X, (const float *)Wqkv, Ir, Ar_opt, w, st);
-    else
-        launch_route<bf16_t>(D, (const bf16_t *)X, (const bf16_t *)Wqkv, Ir, Ar_opt, w, st);
-    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+        return launch_route<float>(D, (const float *)X, (const float *)Wqkv, Ir, Ar_opt, w, st);
+    return launch_route<bf16_t>(D, (const bf16_t *)X, (const bf16_t *)Wqkv, Ir, Ar_opt, w, st);
 }
 
 }  // namespace bra

@@ -229,11 +229,12 @@ constexpr size_t gemm_smem(bool split, int cw = 4)
 // Rows of A^r = Q^r (K^r)^T (Eq. 4) in float32 and their top-k (Eq. 5) for workgroup
 // (image, 4 NR query regions), R <= 64: the channels pass through LDS 64 at a time (K^r of all
 // regions as [16][kQkRS][4]: channel group, region, channel; Q^r of the workgroup's rows),
-// wavefront w accumulates rows NR w .. NR w + NR - 1 with lane j holding entry j.
+// wavefront w accumulates rows NR w .. NR w + NR - 1 with lane j holding entry j.  Q^r, K^r have row
+// pitch ld; C is a multiple of 4 (a last chunk's missing channels read as zero).
 constexpr int kQkRS = 65;
 
 template <int NR>
-__global__ __launch_bounds__(256) void k_route_qk(const float *__restrict__ Qr, const float *__restrict__ Kr,
+__global__ __launch_bounds__(256) void k_route_qk(const float *__restrict__ Qr, const float *__restrict__ Kr, int ld,
                                                   int32_t *__restrict__ Ir, float *__restrict__ Ar, Dims D)
 {
     __shared__ __attribute__((aligned(16))) float Kt[16 * kQkRS * 4];
@@ -242,7 +243,7 @@ __global__ __launch_bounds__(256) void k_route_qk(const float *__restrict__ Qr, 
     const int groups = (D.R + QR - 1) / QR;
     const int b = blockIdx.x / groups, myrt = blockIdx.x % groups;
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const size_t img = (size_t)b * D.R * D.C;
+    const size_t img = (size_t)b * D.R * ld;
     float a[NR];
 #pragma unroll
     for (int rr = 0; rr < NR; ++rr) a[rr] = 0.f;
@@ -252,10 +253,14 @@ __global__ __launch_bounds__(256) void k_route_qk(const float *__restrict__ Qr, 
         for (int u = 0; u < 4; ++u) {
             const int idx = tid + 256 * u;               // (region, 4-channel group)
             const int r = min(idx / 16, D.R - 1);        // regions past R repeat the last; never used
-            kv[u] = *(const f32x4 *)(Kr + img + (size_t)r * D.C + c0 + (idx % 16) * 4);
+            const bool in = c0 + (idx % 16) * 4 < D.C;
+            kv[u] = *(const f32x4 *)(Kr + img + (size_t)r * ld + (in ? c0 + (idx % 16) * 4 : 0));
+            if (!in) kv[u] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
         const int r = min(QR * myrt + (tid / 16) % QR, D.R - 1);
-        qv = *(const f32x4 *)(Qr + img + (size_t)r * D.C + c0 + (tid % 16) * 4);
+        const bool in = c0 + (tid % 16) * 4 < D.C;
+        qv = *(const f32x4 *)(Qr + img + (size_t)r * ld + (in ? c0 + (tid % 16) * 4 : 0));
+        if (!in) qv = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     request(0);
     for (int c0 = 0; c0 < D.C; c0 += 64) {
@@ -505,16 +510,7 @@ int launch_gemm(const void *In, const bf16_t *W, int ldw, long M, int K, int Nou
 int affinity_steps(const Dims &D, const WideWs &w, int32_t *Ir, float *Ar_opt, hipStream_t st)
 {
     if (many_regions(D)) return valu_affinity_topk(D, w.qr, w.kr, Ir, Ar_opt, st);   // more than one entry per lane
-    ProfScope ps(st, K_MFMA_ROUTE_ROWS);
-    // 16 query regions per workgroup when that already fills the chip, else 8 or 4
-    const long wgs16 = (long)D.B * ((D.R + 15) / 16);
-    if (wgs16 >= 1024)
-        hipLaunchKernelGGL(k_route_qk<4>, dim3((unsigned)wgs16), dim3(256), 0, st, w.qr, w.kr, Ir, Ar_opt, D);
-    else if (2 * wgs16 >= 1024)
-        hipLaunchKernelGGL(k_route_qk<2>, dim3(D.B * ((D.R + 7) / 8)), dim3(256), 0, st, w.qr, w.kr, Ir, Ar_opt, D);
-    else
-        hipLaunchKernelGGL(k_route_qk<1>, dim3(D.B * ((D.R + 3) / 4)), dim3(256), 0, st, w.qr, w.kr, Ir, Ar_opt, D);
-    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+    return route_rows(D, w.qr, w.kr, D.C, Ir, Ar_opt, st);
 }
 
 // Pooling, region-level projections, A^r rows and top-k.
@@ -543,6 +539,20 @@ int route_steps(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideWs
 }
 
 }  // namespace
+
+int route_rows(const Dims &D, const float *Qr, const float *Kr, int ld, int32_t *Ir, float *Ar_opt, hipStream_t st)
+{
+    ProfScope ps(st, K_MFMA_ROUTE_ROWS);
+    // 16 query regions per workgroup when that already fills the chip, else 8 or 4
+    const long wgs16 = (long)D.B * ((D.R + 15) / 16);
+    if (wgs16 >= 1024)
+        hipLaunchKernelGGL(k_route_qk<4>, dim3((unsigned)wgs16), dim3(256), 0, st, Qr, Kr, ld, Ir, Ar_opt, D);
+    else if (2 * wgs16 >= 1024)
+        hipLaunchKernelGGL(k_route_qk<2>, dim3(D.B * ((D.R + 7) / 8)), dim3(256), 0, st, Qr, Kr, ld, Ir, Ar_opt, D);
+    else
+        hipLaunchKernelGGL(k_route_qk<1>, dim3(D.B * ((D.R + 3) / 4)), dim3(256), 0, st, Qr, Kr, ld, Ir, Ar_opt, D);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
 
 int gemm_bf16(const bf16_t *In, const bf16_t *W, long M, int K, int Nout, bf16_t *Out, const float *bias,
               const bf16_t *res, bool gelu, int kernel_id, hipStream_t st)
