@@ -278,7 +278,7 @@ def time_backward(cfg, steps, warmup):
     """bra_backward (fixed routing) at a named workload's shape, with the workspace allocated once
     and HIP events around the timed calls: context, never `value`.  bf16 workloads with heads of 32
     or 64 channels, C a multiple of 64 and at most 4096 routing entries per image run on the
-    matrix-core kernels, the others on the scalar float32 ones."""
+    matrix-core kernels, the others on the float32 ones."""
     import ctypes
 
     import torch
@@ -310,7 +310,7 @@ def time_backward(cfg, steps, warmup):
     return {"images_per_s": round(cfg.B / (ms / 1e3), 1), "ms_per_step": round(ms, 4),
             "achieved_tflops": round(3 * cfg.B * f["total"] / (ms / 1e3) / 1e12, 3),
             "kernels": "matrix-core (bf16 operands, float32 sums)" if mfma
-                       else "scalar float32 with atomic scatter-add",
+                       else "float32 matrix-core products",
             "note": "includes the binding's output allocations"}
 
 

@@ -53,7 +53,7 @@ enum { BRA_F32 = 0, BRA_BF16 = 1 };                 /* bra_shape.dtype */
 
 /* bra_shape.path: which kernel family runs.
  *   AUTO    the fastest family that supports the shape;
- *   GENERIC scalar (VALU) float32 kernels, any valid shape, float32 intermediates;
+ *   GENERIC float32 kernels, any valid shape, float32 intermediates;
  *   MFMA    bf16 matrix-core kernels: bf16 tensors, C a multiple of 64, heads of 32 or
  *           64 channels (specialised kernels for C = 64, 128, 256 with heads of 32
  *           and the region sizes of the paper's stages; a general pipeline for the
@@ -149,7 +149,7 @@ int bra_forward_padded(const bra_shape *shape, const void *X, const void *Wqkv, 
  *   Wpos [C,3,3] (channel, ky, kx), W1 [C, hidden], W2 [hidden, C], Wqkv, Wo, Wlce as above,
  *   all of shape->dtype; the vectors bpos, ln*_gamma, ln*_beta, b2 [C] and b1 [hidden] float32.
  * bf16 tensors with C and hidden multiples of 64 run on matrix-core kernels; float32 tensors and
- * all other sizes on scalar float32 kernels (C up to 4096).  The
+ * all other sizes on float32 kernels (C up to 4096).  The
  * BRA stage runs on the family that bra_forward would pick for `shape` (shape->path applies).
  * Intermediate tensors (X1, LayerNorm1's output, BRA's output, X2, the hidden layer) live in
  * `ws` in shape->dtype; arithmetic is float32.  Xout may be the same buffer as X.  Ir_out_opt /
@@ -192,8 +192,8 @@ int bra_block_forward(const bra_shape *shape, int32_t hidden, float eps, const v
  *                     region in registers, the weight gradients from per-workgroup partial sums in
  *                     a fixed order, so a repeat gives the same bits as long as no key region is
  *                     routed to by more than 256 index entries of one image.
- *   BRA_PATH_GENERIC  any dtype, heads up to 64 channels wide: scalar float32 kernels; sums over
- *                     tokens use float32 atomic adds, reproducible to rounding, not bit for bit.
+ *   BRA_PATH_GENERIC  any dtype, heads up to 64 channels wide: float32 kernels, float32 intermediates.
+ *                     No atomic adds either: repeats give the same bits.
  *   BRA_PATH_AUTO     the first where it applies, else the second.
  * Index values outside [0, S*S) are clamped.  Errors as bra_forward. */
 int bra_backward_workspace_bytes(const bra_shape *shape, size_t *out_bytes);

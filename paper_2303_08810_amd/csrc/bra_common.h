@@ -163,14 +163,14 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
                   const int32_t *Ir, const void *dY, void *dX, float *dWqkv, float *dWo, float *dWlce, void *ws,
                   hipStream_t st);
 
-// Backward pass with fixed routing, scalar float32 kernels (bra_generic.hip).
+// Backward pass with fixed routing, float32 kernels (bra_generic.hip).
 bool generic_backward_supported(const Dims &D);
 size_t generic_backward_workspace_bytes(const Dims &D);
 int generic_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo, const void *Wlce,
                      const int32_t *Ir, const void *dY, void *dX, float *dWqkv, float *dWo, float *dWlce, void *ws,
                      hipStream_t st);
 
-// Whole block with the scalar float32 kernels (bra_generic.hip): any dtype, C and hidden.
+// Whole block with the float32 kernels (bra_generic.hip): any dtype, C and hidden.
 size_t generic_block_workspace_bytes(const Dims &D, int hidden, size_t bra_bytes);
 int generic_block_forward(const Dims &D, int hidden, float eps, const void *X, const bra_block_params &p, void *Xout,
                           int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, size_t bra_bytes, int path,

@@ -11,7 +11,7 @@
 // loads, for channel counts that are multiples of 4.
 #pragma once
 
-#include "bra_mfma_dev.h"
+#include "bra_bwd_dev.h"
 
 namespace bra {
 namespace f32 {
@@ -234,6 +234,12 @@ struct AttnShape {
     static constexpr int CW = DP * HPW, P = CW + 4, KB = CW <= 64 ? 64 : 32, TPH = 4 / HPW, QT = 16 * TPH;
 };
 
+// Token (within the image) of slot `slot` of region r.
+__device__ __forceinline__ int region_token(const Dims &D, int r, int slot)
+{
+    return ((r / D.S) * D.rh + slot / D.rw) * D.W + (r % D.S) * D.rw + slot % D.rw;
+}
+
 // Rows of a token map -> registers: channels of the workgroup's HPW heads, 4 at a time; head h0 + hl owns
 // channels [(h0 + hl) d, (h0 + hl + 1) d).
 template <int DP, bool VEC>
@@ -262,11 +268,8 @@ __global__ __launch_bounds__(256) void k_attention(const float *__restrict__ QKV
     const int C3 = 3 * D.C, kn = D.kn, hl = wave / L::TPH, h = hg * HPW + hl;
     const float *img = QKV + (size_t)b * D.N * C3;
     const int32_t *irp = Ir + ((size_t)b * D.R + reg) * D.k;
-    auto region_token = [&](int r, int slot) {
-        return ((r / D.S) * D.rh + slot / D.rw) * D.W + (r % D.S) * D.rw + slot % D.rw;
-    };
     const int slot = L::QT * qt + 16 * (wave % L::TPH) + i;
-    const int qtok = region_token(reg, min(slot, D.n - 1));
+    const int qtok = region_token(D, reg, min(slot, D.n - 1));
     f32x4 qf[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s)
@@ -279,7 +282,7 @@ __global__ __launch_bounds__(256) void k_attention(const float *__restrict__ QKV
         for (int u = 0; u < NL; ++u) {
             const int idx = tid + 256 * u, key = min(k0 + idx / (CW / 4), kn - 1);   // past the end: the last key, masked below
             const int p = key / D.n;
-            const float *row = img + (size_t)region_token(region_index(irp[p], D.R), key - p * D.n) * C3;
+            const float *row = img + (size_t)region_token(D, region_index(irp[p], D.R), key - p * D.n) * C3;
             kr[u] = load_head_chunk<DP, VEC>(row + D.C, idx % (CW / 4), hg * HPW, D);
             vr[u] = load_head_chunk<DP, VEC>(row + 2 * D.C, idx % (CW / 4), hg * HPW, D);
         }
@@ -354,6 +357,363 @@ __global__ __launch_bounds__(256) void k_attention(const float *__restrict__ QKV
             if (ch < D.d) store4<VEC>(orow + ch, acc[dt] * inv, D.d - ch);
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// Query side of the attention backward (derivative of Eq. 6 with Eq. 1) in float32: the workgroup's queries
+// and head groups as in k_attention.  First sweep over the key blocks, with the online softmax's rescaling:
+// the maximum m, l = sum e, O~ = sum e V and D~ = sum e dP (dP^T = V dO^T); at its end O, D = D~ / l and
+// lse = log2(l) + scale log2(e) m are final.  Second sweep: P = exp2(scale log2(e) s - lse),
+// dS = P (dP - D), dQ^T += K^T dS^T.  A single key block (k n <= KB) is not taken twice.
+template <int DP, int HPW, bool VEC>
+__global__ __launch_bounds__(256) void k_attn_bwd_q(const float *__restrict__ QKV, const float *__restrict__ dO,
+                                                    const int32_t *__restrict__ Ir, float *__restrict__ O,
+                                                    float *__restrict__ dQKV, float *__restrict__ lse,
+                                                    float *__restrict__ dsum, Dims D, int hgroups, int qtiles)
+{
+    typedef AttnShape<DP, HPW> L;
+    constexpr int P = L::P, KB = L::KB, CW = L::CW, KT = KB / 16, NS = DP / 16;
+    __shared__ __attribute__((aligned(16))) float Ks[KB * P];
+    __shared__ __attribute__((aligned(16))) float Vs[KB * P];
+    const int hg = blockIdx.x % hgroups, qt = (blockIdx.x / hgroups) % qtiles;
+    const int reg = (blockIdx.x / (hgroups * qtiles)) % D.R, b = blockIdx.x / (hgroups * qtiles * D.R);
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int C3 = 3 * D.C, kn = D.kn, nblocks = (kn + KB - 1) / KB, hl = wave / L::TPH, h = hg * HPW + hl;
+    const size_t itok = (size_t)b * D.N;
+    const float *img = QKV + itok * C3;
+    const int32_t *irp = Ir + ((size_t)b * D.R + reg) * D.k;
+    const int slot = L::QT * qt + 16 * (wave % L::TPH) + i;
+    const int qtok = region_token(D, reg, min(slot, D.n - 1));
+    const bool live = slot < D.n && h < D.heads;
+    f32x4 qf[NS], gf[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        qf[s] = load_head_chunk<DP, VEC>(img + (size_t)qtok * C3, 4 * s + g, h, D);
+        gf[s] = load_head_chunk<DP, VEC>(dO + (itok + qtok) * D.C, 4 * s + g, h, D);
+    }
+    constexpr int NL = KB * CW / 4 / 256;
+    f32x4 kr[NL], vr[NL];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int idx = tid + 256 * u, key = min(k0 + idx / (CW / 4), kn - 1);   // past the end: the last key, masked below
+            const int p = key / D.n;
+            const float *row = img + (size_t)region_token(D, region_index(irp[p], D.R), key - p * D.n) * C3;
+            kr[u] = load_head_chunk<DP, VEC>(row + D.C, idx % (CW / 4), hg * HPW, D);
+            vr[u] = load_head_chunk<DP, VEC>(row + 2 * D.C, idx % (CW / 4), hg * HPW, D);
+        }
+    };
+    float m = -INFINITY, l = 0.f, dd = 0.f;
+    f32x4 acc[NS];
+#pragma unroll
+    for (int dt = 0; dt < NS; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const float c_exp = D.scale * 1.4426950408889634f;
+    // acc[dt] = T^T[channel 16 dt + 4 g + j][..] x weights of the block's keys
+    auto contract = [&](const float *T, const f32x4 (&wt)[KT]) {
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int dt = 0; dt < NS; ++dt)
+                    acc[dt] = mfma_f32(T[(16 * t + 4 * g + e) * P + DP * hl + 16 * dt + i], wt[t][e], acc[dt]);
+    };
+    fetch(0);
+    for (int step = 0; step < 2 * nblocks; ++step) {
+        const int sweep = step >= nblocks ? 1 : 0, k0 = KB * (step - sweep * nblocks);
+        if (step) __syncthreads();               // the previous block has been read
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int idx = tid + 256 * u;
+            *(f32x4 *)(Ks + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = kr[u];
+            *(f32x4 *)(Vs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = vr[u];
+        }
+        __syncthreads();
+        if (nblocks > 1 && step + 1 < 2 * nblocks) fetch(KB * ((step + 1) % nblocks));
+        f32x4 st[KT], dp[KT];
+#pragma unroll
+        for (int t = 0; t < KT; ++t) st[t] = dp[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+#pragma unroll
+            for (int t = 0; t < KT; ++t) {
+                const f32x4 kf = *(const f32x4 *)(Ks + (16 * t + i) * P + DP * hl + 16 * s + 4 * g);
+                const f32x4 vf = *(const f32x4 *)(Vs + (16 * t + i) * P + DP * hl + 16 * s + 4 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    st[t] = mfma_f32(kf[e], qf[s][e], st[t]);      // S^T[key 16 t + 4 g + j][query i]
+                    dp[t] = mfma_f32(vf[e], gf[s][e], dp[t]);      // dP^T, same layout
+                }
+            }
+        }
+        const int left = kn - k0;
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) st[t][j] = 16 * t + 4 * g + j < left ? st[t][j] : -INFINITY;
+        if (sweep == 0) {
+            float mx = st[0][0];
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) mx = fmaxf(mx, st[t][j]);
+            const float m_new = fmaxf(m, cross_row_max(mx));          // finite: the block's first key exists
+            const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c_exp);
+            m = m_new;
+            float ls = 0.f, ds = 0.f;
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    st[t][j] = __builtin_amdgcn_exp2f((st[t][j] - m_new) * c_exp);
+                    ls += st[t][j];
+                    ds = fmaf(st[t][j], dp[t][j], ds);
+                }
+            l = fmaf(l, alpha, cross_row_sum(ls));
+            dd = fmaf(dd, alpha, cross_row_sum(ds));
+#pragma unroll
+            for (int dt = 0; dt < NS; ++dt) acc[dt] *= alpha;
+            contract(Vs, st);
+            if (step + 1 < nblocks) continue;
+            // end of the sweep: O and the statistics
+            const float inv = 1.0f / l;
+            dd *= inv;
+            if (live) {
+                float *orow = O + (itok + qtok) * D.C + h * D.d;
+#pragma unroll
+                for (int dt = 0; dt < NS; ++dt)
+                    if (16 * dt + 4 * g < D.d) store4<VEC>(orow + 16 * dt + 4 * g, acc[dt] * inv, D.d - 16 * dt - 4 * g);
+                if (g == 0) {
+                    lse[(itok + qtok) * D.heads + h] = fmaf(m, c_exp, __builtin_amdgcn_logf(l));    // v_log_f32: log2
+                    dsum[(itok + qtok) * D.heads + h] = dd;
+                }
+            }
+#pragma unroll
+            for (int dt = 0; dt < NS; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (nblocks > 1) continue;
+        } else {
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) st[t][j] = __builtin_amdgcn_exp2f((st[t][j] - m) * c_exp);
+        }
+        // st: exp(s - m); dS = st / l (dP - D)
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) st[t][j] *= dp[t][j] - dd;
+        contract(Ks, st);
+        if (nblocks == 1) break;
+    }
+    if (live) {
+        const float f = D.scale / l;
+        float *qrow = dQKV + (itok + qtok) * C3 + h * D.d;
+#pragma unroll
+        for (int dt = 0; dt < NS; ++dt)
+            if (16 * dt + 4 * g < D.d) store4<VEC>(qrow + 16 * dt + 4 * g, acc[dt] * f, D.d - 16 * dt - 4 * g);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Key side for (image, key region, key tile, HPW heads): wavefront w has 16 keys of one head.  The queries of
+// all regions routed to this one (every routing entry that names it, in the order of the entries) form one
+// list of rows; their Q, dO rows and statistics pass through LDS QB at a time, the next block being requested
+// meanwhile:
+//     S = Q K^T and dP = dO V^T,  P = exp2(scale log2(e) S - lse),  dS = P (dP - D)      (registers)
+//     dV^T += dO^T P,  dK^T += Q^T dS                                                    (registers)
+// and dK, dV are stored once: no atomic adds, no zeroed buffers, the same bits on every run.  A region that no
+// query attends to gets zeros.
+template <int DP, int HPW, bool VEC>
+__global__ __launch_bounds__(256) void k_attn_bwd_kv(const float *__restrict__ QKV, const float *__restrict__ dO,
+                                                     const int32_t *__restrict__ Ir, const float *__restrict__ lse,
+                                                     const float *__restrict__ dsum, float *__restrict__ dQKV, Dims D,
+                                                     int hgroups, int ktiles)
+{
+    typedef AttnShape<DP, HPW> L;
+    constexpr int P = L::P, QB = L::KB, CW = L::CW, QTL = QB / 16, NS = DP / 16;
+    __shared__ __attribute__((aligned(16))) float Qs[QB * P];
+    __shared__ __attribute__((aligned(16))) float Gs[QB * P];
+    __shared__ __attribute__((aligned(16))) float lse_s[HPW * QB], dd_s[HPW * QB];
+    __shared__ int list[bwd::kListChunk], counts[16];
+    const int hg = blockIdx.x % hgroups, kt = (blockIdx.x / hgroups) % ktiles;
+    const int reg = (blockIdx.x / (hgroups * ktiles)) % D.R, b = blockIdx.x / (hgroups * ktiles * D.R);
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int C3 = 3 * D.C, hl = wave / L::TPH, h = hg * HPW + hl;
+    const size_t itok = (size_t)b * D.N;
+    const float *img = QKV + itok * C3;
+    const int slot = L::QT * kt + 16 * (wave % L::TPH) + i;
+    const int ktok = region_token(D, reg, min(slot, D.n - 1));
+    f32x4 kf[NS], vf[NS], ak[NS], av[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        kf[s] = load_head_chunk<DP, VEC>(img + (size_t)ktok * C3 + D.C, 4 * s + g, h, D);
+        vf[s] = load_head_chunk<DP, VEC>(img + (size_t)ktok * C3 + 2 * D.C, 4 * s + g, h, D);
+        ak[s] = av[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const float c_exp = D.scale * 1.4426950408889634f;
+    const int entries = D.R * D.k;
+    const int32_t *irb = Ir + (size_t)b * entries;
+    constexpr int NL = QB * CW / 4 / 256;
+    static_assert(HPW * QB <= 256, "one statistics entry per thread");
+    f32x4 qr[NL], gr[NL];
+    float next_lse = INFINITY, next_dd = 0.f;
+    for (int e0 = 0; e0 < entries; e0 += bwd::kListChunk) {
+        const int rows = bwd::collect_entries(irb, entries, e0, reg, D.R, list, counts) * D.n;
+        auto query_token = [&](int row) {
+            const int e = row / D.n;
+            return region_token(D, list[e] / D.k, row - e * D.n);
+        };
+        auto fetch = [&](int r0) {
+#pragma unroll
+            for (int u = 0; u < NL; ++u) {
+                const int idx = tid + 256 * u;
+                const int tok = query_token(min(r0 + idx / (CW / 4), rows - 1));      // past the end: weight zero, see below
+                qr[u] = load_head_chunk<DP, VEC>(img + (size_t)tok * C3, idx % (CW / 4), hg * HPW, D);
+                gr[u] = load_head_chunk<DP, VEC>(dO + (itok + tok) * D.C, idx % (CW / 4), hg * HPW, D);
+            }
+            if (tid < HPW * QB) {
+                const int row = r0 + tid % QB, hh = hg * HPW + tid / QB;
+                const bool ok = row < rows && hh < D.heads;
+                const size_t at = ok ? (itok + query_token(row)) * D.heads + hh : 0;
+                next_lse = ok ? lse[at] : INFINITY;                // a missing row: P = exp2(-inf) = 0
+                next_dd = ok ? dsum[at] : 0.f;
+            }
+        };
+        if (rows > 0) fetch(0);
+        for (int r0 = 0; r0 < rows; r0 += QB) {
+            __syncthreads();                     // the previous block has been read
+#pragma unroll
+            for (int u = 0; u < NL; ++u) {
+                const int idx = tid + 256 * u;
+                *(f32x4 *)(Qs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = qr[u];
+                *(f32x4 *)(Gs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = gr[u];
+            }
+            if (tid < HPW * QB) {
+                lse_s[tid] = next_lse;
+                dd_s[tid] = next_dd;
+            }
+            __syncthreads();
+            if (r0 + QB < rows) fetch(r0 + QB);
+            const int tiles = (min(QB, rows - r0) + 15) / 16;
+#pragma unroll
+            for (int t = 0; t < QTL; ++t) {
+                if (t >= tiles) break;
+                f32x4 st = {0.f, 0.f, 0.f, 0.f}, dp = st;
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    const f32x4 qv = *(const f32x4 *)(Qs + (16 * t + i) * P + DP * hl + 16 * s + 4 * g);
+                    const f32x4 gv = *(const f32x4 *)(Gs + (16 * t + i) * P + DP * hl + 16 * s + 4 * g);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        st = mfma_f32(qv[e], kf[s][e], st);       // S[query 16 t + 4 g + j][key i]
+                        dp = mfma_f32(gv[e], vf[s][e], dp);
+                    }
+                }
+                const f32x4 l4 = *(const f32x4 *)(lse_s + hl * QB + 16 * t + 4 * g);
+                const f32x4 d4 = *(const f32x4 *)(dd_s + hl * QB + 16 * t + 4 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float p = __builtin_amdgcn_exp2f(fmaf(st[e], c_exp, -l4[e])), ds = p * (dp[e] - d4[e]);
+#pragma unroll
+                    for (int dt = 0; dt < NS; ++dt) {
+                        const int at = (16 * t + 4 * g + e) * P + DP * hl + 16 * dt + i;
+                        av[dt] = mfma_f32(Gs[at], p, av[dt]);     // dV^T[channel 16 dt + 4 g + j][key i]
+                        ak[dt] = mfma_f32(Qs[at], ds, ak[dt]);
+                    }
+                }
+            }
+        }
+    }
+    if (slot < D.n && h < D.heads) {
+        float *row = dQKV + (itok + ktok) * C3 + h * D.d;
+#pragma unroll
+        for (int dt = 0; dt < NS; ++dt) {
+            const int ch = 16 * dt + 4 * g;
+            if (ch >= D.d) continue;
+            store4<VEC>(row + D.C + ch, ak[dt] * D.scale, D.d - ch);
+            store4<VEC>(row + 2 * D.C + ch, av[dt], D.d - ch);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Part[share][a][n] = sum over the share's tokens t of A[t][a] B[t][n]: the weight gradients, contractions over
+// all tokens.  A 64 x 64 block of the output per workgroup, both operands staged 32 tokens at a time (the next
+// 32 requested meanwhile) and read as 16 consecutive channels of 4 token rows; the wavefronts split the block
+// 2 x 2.  Two such products per launch.
+template <typename TA, typename TB>
+struct TnJob {
+    const TA *A;
+    const TB *Bm;
+    float *Part;
+    int lda, ldb, KA, N, blocks;
+};
+
+template <bool VEC, typename TA, typename TB>
+__device__ __forceinline__ void tn_tile(const TnJob<TA, TB> &J, int block, long M, int share_tokens, float *smem)
+{
+    constexpr int P = 64 + 4, TT = 32, NL = TT * 16 / 256;
+    float *As = smem, *Bs = smem + TT * P;
+    const int nb = (J.N + 63) / 64, ab = (J.KA + 63) / 64;
+    const int n0 = 64 * (block % nb), a0 = 64 * (block / nb % ab), share = block / (nb * ab);
+    const long t_begin = (long)share * share_tokens, t_end = min(M, t_begin + share_tokens);
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
+    f32x4 ra[NL], rb[NL], acc[2][2];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u / 2][u % 2] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto fetch = [&](long t0) {
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int idx = tid + 256 * u, c = 4 * (idx % 16);
+            const long t = t0 + idx / 16, tc = min(t, t_end - 1);
+            ra[u] = load4<VEC>(J.A + tc * J.lda + (VEC ? min(a0 + c, J.KA - 4) : a0 + c), J.KA - a0 - c);
+            rb[u] = load4<VEC>(J.Bm + tc * J.ldb + (VEC ? min(n0 + c, J.N - 4) : n0 + c), J.N - n0 - c);
+            if (t >= t_end) ra[u] = rb[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    fetch(t_begin);
+    for (long t0 = t_begin; t0 < t_end; t0 += TT) {
+        if (t0 > t_begin) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int idx = tid + 256 * u;
+            *(f32x4 *)(As + (idx / 16) * P + 4 * (idx % 16)) = ra[u];
+            *(f32x4 *)(Bs + (idx / 16) * P + 4 * (idx % 16)) = rb[u];
+        }
+        __syncthreads();
+        if (t0 + TT < t_end) fetch(t0 + TT);
+#pragma unroll
+        for (int s = 0; s < TT / 4; ++s) {
+            float a[2], bv[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                a[u] = As[(4 * s + g) * P + 32 * (wave / 2) + 16 * u + i];
+                bv[u] = Bs[(4 * s + g) * P + 32 * (wave % 2) + 16 * u + i];
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 2; ++v) acc[u][v] = mfma_f32(a[u], bv[v], acc[u][v]);
+        }
+    }
+    float *out = J.Part + (size_t)share * J.KA * J.N;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int a = a0 + 32 * (wave / 2) + 16 * u + 4 * g + j, n = n0 + 32 * (wave % 2) + 16 * v + i;
+                if (a < J.KA && n < J.N) out[(size_t)a * J.N + n] = acc[u][v][j];
+            }
+}
+
+template <bool VEC, typename TA0, typename TB0, typename TA1, typename TB1>
+__global__ __launch_bounds__(256) void k_gemm_tn(TnJob<TA0, TB0> J0, TnJob<TA1, TB1> J1, long M, int share_tokens)
+{
+    __shared__ __attribute__((aligned(16))) float smem[2 * 32 * (64 + 4)];
+    if ((int)blockIdx.x < J0.blocks) tn_tile<VEC>(J0, blockIdx.x, M, share_tokens, smem);
+    else tn_tile<VEC>(J1, (int)blockIdx.x - J0.blocks, M, share_tokens, smem);
 }
 
 // ---------------------------------------------------------------------------

@@ -270,6 +270,13 @@ int launch_attention_t(const Dims &D, const float *qkv, const int32_t *Ir, float
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
+// Heads side by side in a workgroup where a region's tokens do not fill four 16-row tiles.
+int heads_per_group(const Dims &D)
+{
+    const int want = D.n <= 16 ? 4 : (D.n <= 32 ? 2 : 1);
+    return D.heads > want / 2 ? want : (D.heads >= 2 ? 2 : 1);
+}
+
 int launch_attention(const Dims &D, const float *qkv, const int32_t *Ir, float *o, hipStream_t st)
 {
     ProfScope ps(st, K_GEN_ATTENTION);
@@ -278,8 +285,7 @@ int launch_attention(const Dims &D, const float *qkv, const int32_t *Ir, float *
                            D.scale);
         return launched() ? BRA_OK : BRA_ERR_LAUNCH;
     }
-    // heads side by side where a region's queries do not fill four 16-query tiles
-    const int want = D.n <= 16 ? 4 : (D.n <= 32 ? 2 : 1), hpw = D.heads >= want ? want : (D.heads >= 2 && want >= 2 ? 2 : 1);
+    const int hpw = heads_per_group(D);
     const bool vec = D.d % 4 == 0;
     if (D.d <= 32) {
         if (hpw == 4) return vec ? launch_attention_t<32, 4, true>(D, qkv, Ir, o, st) : launch_attention_t<32, 4, false>(D, qkv, Ir, o, st);
@@ -464,239 +470,30 @@ int block_t(const Dims &D, int hidden, float eps, const T *X, const bra_block_pa
 }
 
 // ---------------------------------------------------------------------------
-// Backward pass with fixed routing (the top-k of Eq. 5 has no derivative), scalar kernels.
+// Backward pass with fixed routing (the top-k of Eq. 5 has no derivative) in float32.
 // With dO = dY Wo^T and, per query token t of region i and head h, P = softmax over the keys G_i:
 //   dP_j = dO_h[t] . V_h[j],  dS_j = P_j (dP_j - sum_u P_u dP_u),
 //   dQ_h[t] = scale sum_j dS_j K_h[j],  dK_h[j] += scale dS_j Q_h[t],  dV_h[j] += P_j dO_h[t].
+// The weight gradients come from per-workgroup partial sums, added in a fixed order.
+constexpr int kBwdMaxD = kAttnF32MaxD;
 
-__global__ void gen_fill_zero(float *__restrict__ p, size_t n)
+// Token shares of the weight-gradient contractions: about 1024 workgroups over the 64 x 64 output blocks of
+// both products.
+struct SharePlan {
+    int shares, tokens;
+};
+
+SharePlan share_plan(long M, int C)
 {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.f;
+    const long blocks = (long)((C + 63) / 64) * ((3 * C + 63) / 64 + (C + 63) / 64), steps = (M + 31) / 32;
+    const long want = 1024 / blocks > 1 ? 1024 / blocks : 1, per = (steps + want - 1) / want;
+    return {(int)((steps + per - 1) / per), (int)(per * 32)};
 }
 
-// Out[i][j] += sum_m A[m][i] B[m][j] over this workgroup's slice of the rows m (atomic adds into
-// float32 Out [KA][N], zeroed beforehand): the weight gradients, a contraction over all tokens.
-template <typename TA, typename TB>
-__global__ __launch_bounds__(256) void gen_gemm_tn(const TA *__restrict__ A, int lda, const TB *__restrict__ Bm,
-                                                   int ldb, float *__restrict__ Out, int ldo, long M, int KA, int N,
-                                                   long rows_per_wg)
-{
-    __shared__ float As[16][64 + 4];
-    __shared__ float Bs[16][64];
-    const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-    const int i0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
-    const long m_begin = (long)blockIdx.z * rows_per_wg, m_end = min(M, m_begin + rows_per_wg);
-    float acc[4][4];
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-    for (long m0 = m_begin; m0 < m_end; m0 += 16) {
-        for (int u = 0; u < 4; ++u) {
-            const int idx = tid + u * 256;
-            const int mm = idx / 64, cc = idx % 64;
-            const long gm = m0 + mm;
-            As[mm][cc] = (gm < m_end && i0 + cc < KA) ? load_f32(A + gm * lda + i0 + cc) : 0.f;
-            Bs[mm][cc] = (gm < m_end && n0 + cc < N) ? load_f32(Bm + gm * ldb + n0 + cc) : 0.f;
-        }
-        __syncthreads();
-        for (int mm = 0; mm < 16; ++mm) {
-            float a[4], b[4];
-            for (int i = 0; i < 4; ++i) a[i] = As[mm][ty * 4 + i];
-            for (int j = 0; j < 4; ++j) b[j] = Bs[mm][tx * 4 + j];
-            for (int i = 0; i < 4; ++i)
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j) {
-            const int gi = i0 + ty * 4 + i, gn = n0 + tx * 4 + j;
-            if (gi < KA && gn < N) unsafeAtomicAdd(Out + (size_t)gi * ldo + gn, acc[i][j]);
-        }
-}
-
-// One workgroup per (image, region, head, pass of 16 queries: wavefront w owns 4 of them), the
-// routed keys in blocks of 64 staged in LDS.  Sweep 1 over the key blocks: the softmax maximum and
-// denominator of each query and, rescaled along with them, sum_j e_j dP_j, which gives
-// D_q = sum_j P_j dP_j.  The attention output itself (needed for dWo) falls out of sweep 2.  Sweep 2: per block, a lane per key forms P_j and dS_j
-// (kept in LDS for the pass's 16 queries), a lane per channel adds the query's share to dQ
-// (registers), then a thread per (key, channel) sums the 16 queries' shares of dK, dV and adds them
-// to memory with one atomic add each (other passes and regions route to the same keys).  LDS
-// atomics for that sum were measured at about one lane per clock: eight times slower.
-constexpr int kBwdMaxD = 64;
-
-__global__ __launch_bounds__(256) void gen_attention_bwd(const float *__restrict__ QKV,
-                                                         const int32_t *__restrict__ Ir,
-                                                         float *__restrict__ Oatt,
-                                                         const float *__restrict__ dO, float *__restrict__ dQKV,
-                                                         Dims D, float scale)
-{
-    extern __shared__ float lds[];
-    const int d = D.d, dp = d + 1;
-    float *Ks = lds, *Vs = Ks + 64 * dp;
-    float *qs = Vs + 64 * dp, *dos = qs + 16 * d, *Psc = dos + 16 * d, *dSsc = Psc + 16 * 64;
-    const int passes = (D.n + 15) / 16;
-    const int pass = blockIdx.x % passes, rest = blockIdx.x / passes;
-    const int hd = rest % D.heads;
-    const int reg = (rest / D.heads) % D.R;
-    const int b = rest / (D.heads * D.R);
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const int C3 = 3 * D.C;
-    const float *img = QKV + (size_t)b * D.N * C3;
-    float *dimg = dQKV + (size_t)b * D.N * C3;
-    const int32_t *irp = Ir + ((size_t)b * D.R + reg) * D.k;
-    const int y0 = (reg / D.S) * D.rh, x0 = (reg % D.S) * D.rw;
-    auto query_token = [&](int s) { return (y0 + s / D.rw) * D.W + x0 + s % D.rw; };
-    auto key_token = [&](int key) {
-        const int j = region_index(irp[key / D.n], D.R), slot = key % D.n;
-        return ((j / D.S) * D.rh + slot / D.rw) * D.W + (j % D.S) * D.rw + slot % D.rw;
-    };
-    auto stage_keys = [&](int k0, bool with_v) {
-        for (int e = tid; e < 64 * d; e += 256) {
-            const int u = e / d, c = e % d;
-            const float *row = img + (size_t)key_token(min(k0 + u, D.kn - 1)) * C3 + hd * d + c;
-            Ks[u * dp + c] = row[D.C];
-            if (with_v) Vs[u * dp + c] = row[2 * D.C];
-        }
-    };
-
-    {
-        const int s0 = 16 * pass;
-        for (int e = tid; e < 16 * d; e += 256) {
-            const int s = min(s0 + e / d, D.n - 1);      // past the end: the last query again; it adds nothing
-            const int qtok = query_token(s);
-            qs[e] = img[(size_t)qtok * C3 + hd * d + e % d];
-            dos[e] = dO[((size_t)b * D.N + qtok) * D.C + hd * d + e % d];
-        }
-        __syncthreads();
-        float m[4], l[4], Dq[4], dq[4], oa[4];
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-            m[qq] = -INFINITY;
-            l[qq] = 0.f;
-            Dq[qq] = 0.f;          // sum_j e_j dP_j until the end of sweep 1, then divided by l
-            dq[qq] = 0.f;
-            oa[qq] = 0.f;
-        }
-        for (int k0 = 0; k0 < D.kn; k0 += 64) {        // sweep 1: maximum, denominator and sum_j e_j dP_j
-            const int cn = min(64, D.kn - k0);
-            __syncthreads();
-            stage_keys(k0, true);
-            __syncthreads();
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-                const float *q = qs + (4 * wave + qq) * d, *dov = dos + (4 * wave + qq) * d;
-                float a = 0.f, gsum = 0.f;
-                for (int c = 0; c < d; ++c) {
-                    a = fmaf(q[c], Ks[lane * dp + c], a);
-                    gsum = fmaf(dov[c], Vs[lane * dp + c], gsum);
-                }
-                a = lane < cn ? a * scale : -INFINITY;
-                float mx = a;
-                for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
-                const float m_new = fmaxf(m[qq], mx);
-                float e = lane < cn ? expf(a - m_new) : 0.f;
-                float eg = e * gsum;
-                for (int off = 32; off >= 1; off >>= 1) {
-                    e += __shfl_xor(e, off, kWave);
-                    eg += __shfl_xor(eg, off, kWave);
-                }
-                const float corr = (m[qq] == -INFINITY) ? 0.f : expf(m[qq] - m_new);
-                l[qq] = l[qq] * corr + e;
-                Dq[qq] = Dq[qq] * corr + eg;
-                m[qq] = m_new;
-            }
-        }
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) Dq[qq] /= l[qq];
-        for (int k0 = 0; k0 < D.kn; k0 += 64) {        // sweep 2: gradients
-            const int cn = min(64, D.kn - k0);
-            if (D.kn > 64) {                           // a single block is still in LDS from sweep 1
-                __syncthreads();
-                stage_keys(k0, true);
-                __syncthreads();
-            }
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-                const bool live = s0 + 4 * wave + qq < D.n;      // uniform in the wavefront
-                const float *q = qs + (4 * wave + qq) * d, *dov = dos + (4 * wave + qq) * d;
-                float *Pw = Psc + (4 * wave + qq) * 64, *dSw = dSsc + (4 * wave + qq) * 64;
-                float a = 0.f, gsum = 0.f;
-                for (int c = 0; c < d; ++c) {
-                    a = fmaf(q[c], Ks[lane * dp + c], a);
-                    gsum = fmaf(dov[c], Vs[lane * dp + c], gsum);
-                }
-                const float pj = (live && lane < cn) ? expf(a * scale - m[qq]) / l[qq] : 0.f;
-                Pw[lane] = pj;
-                dSw[lane] = pj * (gsum - Dq[qq]) * scale;
-                if (live && lane < d) {
-                    float acc = dq[qq], o = oa[qq];
-                    for (int u = 0; u < cn; ++u) {               // this wavefront's rows only
-                        acc = fmaf(dSw[u], Ks[u * dp + lane], acc);
-                        o = fmaf(Pw[u], Vs[u * dp + lane], o);
-                    }
-                    dq[qq] = acc;
-                    oa[qq] = o;
-                }
-            }
-            __syncthreads();
-            // dK[u][c] += sum_q dS[q][u] Q[q][c], dV[u][c] += sum_q P[q][u] dO[q][c] over the pass's 16
-            // queries: a thread per (key, channel), then one atomic add each (other passes and other
-            // regions add to the same keys)
-            for (int e = tid; e < cn * d; e += 256) {
-                const int u = e / d, c = e % d;
-                float ak = 0.f, av = 0.f;
-#pragma unroll
-                for (int qi = 0; qi < 16; ++qi) {
-                    ak = fmaf(dSsc[qi * 64 + u], qs[qi * d + c], ak);
-                    av = fmaf(Psc[qi * 64 + u], dos[qi * d + c], av);
-                }
-                const size_t at = (size_t)key_token(k0 + u) * C3 + hd * d + c;
-                unsafeAtomicAdd(dimg + at + D.C, ak);
-                unsafeAtomicAdd(dimg + at + 2 * D.C, av);
-            }
-        }
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-            const int s = s0 + 4 * wave + qq;
-            if (s < D.n && lane < d) {                           // every query has one owner
-                dimg[(size_t)query_token(s) * C3 + hd * d + lane] = dq[qq];
-                Oatt[((size_t)b * D.N + query_token(s)) * D.C + hd * d + lane] = oa[qq];
-            }
-        }
-    }
-}
-
-inline size_t attention_bwd_smem(int d)
-{
-    return (size_t)(2 * 64 * (d + 1) + 2 * 16 * d + 2 * 16 * 64) * sizeof(float);
-}
-
-// dWlce[c, ky, kx] += sum over this workgroup's tokens of dO[y, x, c] V[y + ky - 2, x + kx - 2, c]:
-// blockIdx.y = tap, a thread per channel, atomic adds into the zeroed gradient.
-__global__ __launch_bounds__(256) void gen_lce_bwd_dw(const float *__restrict__ dO, const float *__restrict__ QKV,
-                                                      float *__restrict__ dW, Dims D, long tokens_per_wg)
-{
-    const int tap = blockIdx.y, ky = tap / 5, kx = tap % 5;
-    const long t_begin = (long)blockIdx.x * tokens_per_wg, t_end = min((long)D.B * D.N, t_begin + tokens_per_wg);
-    // 256 / C groups of threads share the workgroup's tokens when C < 256
-    const int cw = D.C < 256 ? D.C : 256, groups = 256 / cw, grp = threadIdx.x / cw;
-    if (grp >= groups) return;
-    for (int c = threadIdx.x % cw; c < D.C; c += cw) {
-        float acc = 0.f;
-        for (long tok = t_begin + grp; tok < t_end; tok += groups) {
-            const int x = (int)(tok % D.W), y = (int)((tok / D.W) % D.H);
-            const int yy = y + ky - 2, xx = x + kx - 2;
-            if (yy < 0 || yy >= D.H || xx < 0 || xx >= D.W) continue;
-            const long vt = tok + (long)(ky - 2) * D.W + (kx - 2);
-            acc = fmaf(dO[(size_t)tok * D.C + c], QKV[(size_t)vt * 3 * D.C + 2 * D.C + c], acc);
-        }
-        unsafeAtomicAdd(dW + (size_t)c * 25 + tap, acc);
-    }
-}
+bwd::LcePlan lce_grad_plan(const Dims &D) { return bwd::lce_plan(D, 768); }
 
 struct BwdWs {
-    float *qkv, *o, *dO, *dqkv;
+    float *qkv, *o, *dO, *dqkv, *lse, *dsum, *part_qkv, *part_o, *part_lce;
     size_t bytes;
 };
 
@@ -704,24 +501,51 @@ BwdWs carve_bwd(const Dims &D, void *ws)
 {
     char *base = (char *)ws;
     size_t off = 0;
-    auto take = [&](size_t bytes) {
+    auto take = [&](size_t count) {
         void *ptr = base ? base + off : nullptr;
-        off += align256(bytes);
-        return ptr;
+        off += align256(count * sizeof(float));
+        return (float *)ptr;
     };
-    const size_t tok = (size_t)D.B * D.N;
+    const size_t tok = (size_t)D.B * D.N, C = D.C;
+    const int shares = share_plan((long)tok, D.C).shares;
     BwdWs w;
-    w.qkv = (float *)take(tok * 3 * D.C * sizeof(float));
-    w.o = (float *)take(tok * D.C * sizeof(float));
-    w.dO = (float *)take(tok * D.C * sizeof(float));
-    w.dqkv = (float *)take(tok * 3 * D.C * sizeof(float));
+    w.qkv = take(tok * 3 * C);
+    w.o = take(tok * C);
+    w.dO = take(tok * C);
+    w.dqkv = take(tok * 3 * C);
+    w.lse = take(tok * D.heads);
+    w.dsum = take(tok * D.heads);
+    w.part_qkv = take((size_t)shares * 3 * C * C);
+    w.part_o = take((size_t)shares * C * C);
+    w.part_lce = take((size_t)lce_grad_plan(D).groups * 25 * C);
     w.bytes = off;
     return w;
 }
 
-void fill_zero(float *p, size_t n, hipStream_t st)
+template <int DP, int HPW, bool VEC>
+int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, hipStream_t st)
 {
-    hipLaunchKernelGGL(gen_fill_zero, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, n);
+    const int hgroups = (D.heads + HPW - 1) / HPW, qt = f32::AttnShape<DP, HPW>::QT, tiles = (D.n + qt - 1) / qt;
+    const long blocks = (long)D.B * D.R * hgroups * tiles;
+    if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((f32::k_attn_bwd_q<DP, HPW, VEC>), dim3((unsigned)blocks), dim3(256), 0, st, w.qkv, w.dO, Ir, w.o,
+                       w.dqkv, w.lse, w.dsum, D, hgroups, tiles);
+    hipLaunchKernelGGL((f32::k_attn_bwd_kv<DP, HPW, VEC>), dim3((unsigned)blocks), dim3(256), 0, st, w.qkv, w.dO, Ir, w.lse,
+                       w.dsum, w.dqkv, D, hgroups, tiles);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+int launch_attn_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, hipStream_t st)
+{
+    const int hpw = heads_per_group(D);
+    const bool vec = D.d % 4 == 0;
+    if (D.d <= 32) {
+        if (hpw == 4) return vec ? launch_attn_bwd_t<32, 4, true>(D, w, Ir, st) : launch_attn_bwd_t<32, 4, false>(D, w, Ir, st);
+        if (hpw == 2) return vec ? launch_attn_bwd_t<32, 2, true>(D, w, Ir, st) : launch_attn_bwd_t<32, 2, false>(D, w, Ir, st);
+        return vec ? launch_attn_bwd_t<32, 1, true>(D, w, Ir, st) : launch_attn_bwd_t<32, 1, false>(D, w, Ir, st);
+    }
+    if (hpw >= 2) return vec ? launch_attn_bwd_t<64, 2, true>(D, w, Ir, st) : launch_attn_bwd_t<64, 2, false>(D, w, Ir, st);
+    return vec ? launch_attn_bwd_t<64, 1, true>(D, w, Ir, st) : launch_attn_bwd_t<64, 1, false>(D, w, Ir, st);
 }
 
 template <typename T>
@@ -731,50 +555,42 @@ int backward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *W
     const BwdWs w = carve_bwd(D, ws);
     const long M = (long)D.B * D.N;
     const int C = D.C, C3 = 3 * D.C;
-    if (attention_bwd_smem(D.d) > 64 * 1024) {
-        static bool opted = false;
-        if (!opted) {
-            if (hipFuncSetAttribute((const void *)gen_attention_bwd, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)attention_bwd_smem(kBwdMaxD)) != hipSuccess)
-                return BRA_ERR_LAUNCH;
-            opted = true;
-        }
-    }
     ProfScope ps(st, K_GEN_BACKWARD);
-    // forward intermediates again: Q | K | V (the attention output comes out of the backward kernel)
     const f32::GemmJob<float, T, float> *none = nullptr;
+    // forward intermediates again: Q | K | V (the attention output comes out of the query side)
     int rc = launch_gemm<false>(f32::GemmJob<T, T, float>{X, Wqkv, w.qkv, M, C, C3, C3, C3, C, nullptr, nullptr, 0}, none, st);
     if (rc != BRA_OK) return rc;
     // dO = dY Wo^T
     rc = launch_gemm<true>(f32::GemmJob<T, T, float>{dY, Wo, w.dO, M, C, C, C, C, C, nullptr, nullptr, 0}, none, st);
     if (rc != BRA_OK) return rc;
-    fill_zero(dWo, (size_t)C * C, st);
-    fill_zero(dWqkv, (size_t)C * C3, st);
-    fill_zero(dWlce, (size_t)C * 25, st);
-    fill_zero(w.dqkv, (size_t)M * C3, st);
-    // attention: dQ, dK, dV and the attention output; then O = attention + LCE(V) for dWo
-    hipLaunchKernelGGL(gen_attention_bwd, dim3((unsigned)((long)D.B * D.R * D.heads * ((D.n + 15) / 16))), dim3(256),
-                       attention_bwd_smem(D.d), st, w.qkv, Ir,
-                       w.o, w.dO, w.dqkv, D, D.scale);
+    rc = launch_attn_bwd(D, w, Ir, st);
+    if (rc != BRA_OK) return rc;
+    // O = attention + LCE(V) for dWo; dV += LCE^T(dO) and the tap gradients
     rc = launch_lce<false>(D, w.qkv + 2 * C, C3, Wlce, w.o, C, st);
     if (rc != BRA_OK) return rc;
-    long splits = (M + 255) / 256;                 // enough workgroups to fill the chip
-    splits = splits > 4096 ? 4096 : splits;
-    const long rows = ((M + splits - 1) / splits + 15) / 16 * 16;
-    hipLaunchKernelGGL((gen_gemm_tn<float, T>), dim3((unsigned)((C + 63) / 64), (unsigned)((C + 63) / 64), (unsigned)splits),
-                       dim3(256), 0, st, w.o, C, dY, C, dWo, C, M, C, C, rows);
-    // the LCE parts
-    rc = launch_lce<true>(D, w.dO, C, Wlce, w.dqkv + 2 * C, C3, st);
-    if (rc != BRA_OK) return rc;
-    const long tpw = 512;
-    hipLaunchKernelGGL(gen_lce_bwd_dw, dim3((unsigned)((M + tpw - 1) / tpw), 25), dim3(256), 0, st, w.dO, w.qkv, dWlce, D,
-                       tpw);
-    // dX = [dQ | dK | dV] Wqkv^T, dWqkv = X^T [dQ | dK | dV]
+    const bwd::LcePlan lp = lce_grad_plan(D);
+    const dim3 lgrid((unsigned)(lp.groups * lp.cblocks));
+    if (C % 2 == 0)
+        hipLaunchKernelGGL((bwd::k_lce_grad<float, T, 2>), lgrid, dim3(256), 0, st, w.dO, w.qkv + 2 * C, C3, Wlce,
+                           w.dqkv + 2 * C, C3, w.part_lce, D, lp.cblocks, lp.strips, lp.strips_per_wg, lp.height);
+    else
+        hipLaunchKernelGGL((bwd::k_lce_grad<float, T, 1>), lgrid, dim3(256), 0, st, w.dO, w.qkv + 2 * C, C3, Wlce,
+                           w.dqkv + 2 * C, C3, w.part_lce, D, lp.cblocks, lp.strips, lp.strips_per_wg, lp.height);
+    // dX = [dQ | dK | dV] Wqkv^T
     rc = launch_gemm<true>(f32::GemmJob<float, T, T>{w.dqkv, Wqkv, dX, M, C3, C3, C, C, C3, nullptr, nullptr, 0}, none, st);
     if (rc != BRA_OK) return rc;
-    hipLaunchKernelGGL((gen_gemm_tn<T, float>), dim3((unsigned)((C + 63) / 64), (unsigned)((C3 + 63) / 64), (unsigned)splits),
-                       dim3(256), 0, st, X, C, w.dqkv, C3, dWqkv, C3, M, C, C3, rows);
-    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+    // dWqkv = X^T [dQ | dK | dV], dWo = O^T dY
+    const SharePlan sp = share_plan(M, C);
+    const int cb = (C + 63) / 64;
+    const f32::TnJob<T, float> jq = {X, w.dqkv, w.part_qkv, C, C3, C, C3, cb * ((C3 + 63) / 64) * sp.shares};
+    const f32::TnJob<float, T> jo = {w.o, dY, w.part_o, C, C, C, C, cb * cb * sp.shares};
+    const dim3 tgrid((unsigned)(jq.blocks + jo.blocks));
+    if (C % 4 == 0) hipLaunchKernelGGL((f32::k_gemm_tn<true, T, float, float, T>), tgrid, dim3(256), 0, st, jq, jo, M, sp.tokens);
+    else hipLaunchKernelGGL((f32::k_gemm_tn<false, T, float, float, T>), tgrid, dim3(256), 0, st, jq, jo, M, sp.tokens);
+    const bwd::ReduceJob r0 = bwd::reduce_job(w.part_qkv, dWqkv, sp.shares, C3 * C), r1 = bwd::reduce_job(w.part_o, dWo, sp.shares, C * C),
+                         r2 = bwd::reduce_job(w.part_lce, dWlce, lp.groups, 25 * C);
+    hipLaunchKernelGGL(bwd::k_reduce_parts, dim3(r0.blocks + r1.blocks + r2.blocks), dim3(1024), 0, st, r0, r1, r2);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
 }  // namespace

@@ -17,11 +17,14 @@
 // All products take bf16 operands and accumulate in float32; dQ, dK, dV and dO are rounded to
 // bf16 between the kernels (they are matrix-core operands of the next product).  The weight
 // gradients are summed from per-workgroup partial sums in a fixed order (k_reduce_parts).
-#include "bra_mfma_dev.h"
+#include "bra_bwd_dev.h"
 
 namespace bra {
 
 using namespace mfma;
+using bwd::k_reduce_parts;
+using bwd::reduce_job;
+using bwd::ReduceJob;
 
 namespace {
 
@@ -966,51 +969,6 @@ __global__ void k_bwd_transpose(const bf16_t *__restrict__ Wqkv, const bf16_t *_
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e < 3 * C * C) WT[e] = Wqkv[(size_t)(e % C) * 3 * C + e / C];
     else if (e < 4 * C * C) WoT[e - 3 * C * C] = Wo[(size_t)((e - 3 * C * C) % C) * C + (e - 3 * C * C) / C];
-}
-
-// out[e] = sum_p part[p][e], p in a fixed order, for up to three arrays in one launch.  A workgroup
-// of 1024 threads takes 1024 / slices elements x `slices` slices of p (a power of two up to 32, about
-// the number of partial arrays), the slices summed through LDS.
-struct ReduceJob {
-    const float *part;
-    float *out;
-    int nparts, count, slices, blocks;
-};
-
-ReduceJob reduce_job(const float *part, float *out, int nparts, int count)
-{
-    int slices = 1;
-    while (slices < 32 && slices < nparts) slices *= 2;
-    const int elems = 1024 / slices;
-    return ReduceJob{part, out, nparts, count, slices, (count + elems - 1) / elems};
-}
-
-__global__ __launch_bounds__(1024) void k_reduce_parts(ReduceJob j0, ReduceJob j1, ReduceJob j2)
-{
-    __shared__ float red[1024];
-    int bi = blockIdx.x;
-    ReduceJob job = j0;
-    if (bi >= j0.blocks) {
-        bi -= j0.blocks;
-        job = j1;
-        if (bi >= j1.blocks) {
-            bi -= j1.blocks;
-            job = j2;
-        }
-    }
-    const int elems = 1024 / job.slices;
-    const int x = threadIdx.x % elems, y = threadIdx.x / elems, e = bi * elems + x;
-    float sum = 0.f;
-    if (e < job.count)
-#pragma unroll 8
-        for (int p = y; p < job.nparts; p += job.slices) sum += job.part[(size_t)p * job.count + e];
-    red[y * elems + x] = sum;
-    __syncthreads();
-    if (y == 0 && e < job.count) {
-        float total = 0.f;
-        for (int u = 0; u < job.slices; ++u) total += red[u * elems + x];
-        job.out[e] = total;
-    }
 }
 
 // ---------------------------------------------------------------------------
