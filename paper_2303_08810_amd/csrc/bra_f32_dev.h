@@ -12,6 +12,7 @@
 #pragma once
 
 #include "bra_bwd_dev.h"
+#include "bra_lce_dev.h"
 
 namespace bra {
 namespace f32 {
@@ -98,14 +99,14 @@ __device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int bloc
     const int n0 = (block % ntiles) * BN;
     constexpr int NA = kGemmBM * BK / 4 / 256, NB = BN * BK / 4 / 256;
     f32x4 ra[NA], rb[NB];
-    // rows past the end repeat the last one (never stored); k past the end reads as zero on both sides
+    // Rows past the end repeat the last one (never stored).  k past the end is blanked where the values go to LDS:
+    // a select right behind the load would wait for it and take the prefetch away.
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
             const int idx = tid + 256 * u, k = k0 + 4 * (idx % (BK / 4));
             const long m = min(m0 + idx / (BK / 4), J.M - 1);
             ra[u] = load4<VEC>(J.A + m * J.lda + (VEC ? min(k, J.K - 4) : k), J.K - k);
-            if (VEC && k >= J.K) ra[u] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
@@ -113,12 +114,10 @@ __device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int bloc
             if (BT) {
                 const int k = k0 + 4 * (idx % (BK / 4)), n = min(n0 + idx / (BK / 4), J.N - 1);
                 rb[u] = load4<VEC>(J.Bm + (long)n * J.ldb + (VEC ? min(k, J.K - 4) : k), J.K - k);
-                if (VEC && k >= J.K) rb[u] = f32x4{0.f, 0.f, 0.f, 0.f};
             } else {
                 const int k = k0 + idx / (BN / 4), n = n0 + 4 * (idx % (BN / 4));
                 const TB *row = J.Bm + (long)min(k, J.K - 1) * J.ldb;
                 rb[u] = load4<VEC>(row + (VEC ? min(n, J.N - 4) : n), J.N - n);
-                if (k >= J.K) rb[u] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
         }
     };
@@ -131,6 +130,15 @@ __device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int bloc
     fetch(0);
     for (int k0 = 0; k0 < J.K; k0 += BK) {
         if (k0) __syncthreads();                 // the previous chunk has been read
+        if (k0 + BK > J.K) {
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < NA; ++u)
+                if (k0 + 4 * ((tid + 256 * u) % (BK / 4)) >= J.K) ra[u] = zero;
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                if (k0 + (BT ? 4 * ((tid + 256 * u) % (BK / 4)) : (tid + 256 * u) / (BN / 4)) >= J.K) rb[u] = zero;
+        }
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
             const int idx = tid + 256 * u;
@@ -242,16 +250,23 @@ __device__ __forceinline__ int region_token(const Dims &D, int r, int slot)
 
 // Rows of a token map -> registers: channels of the workgroup's HPW heads, 4 at a time; head h0 + hl owns
 // channels [(h0 + hl) d, (h0 + hl + 1) d).
+// With VEC a chunk past the end reads the row's first channels: blank it with head_chunk_ok where it is used, not
+// right behind the load (that would wait for it).
+template <int DP>
+__device__ __forceinline__ int head_chunk_left(int c4, int h0, const Dims &D)
+{
+    return h0 + 4 * c4 / DP < D.heads ? D.d - (4 * c4) % DP : 0;
+}
 template <int DP, bool VEC>
 __device__ __forceinline__ f32x4 load_head_chunk(const float *row, int c4, int h0, const Dims &D)
 {
-    const int h = h0 + 4 * c4 / DP, ch = (4 * c4) % DP;
-    const int left = h < D.heads ? D.d - ch : 0;
-    if (VEC) {
-        const f32x4 v = *(const f32x4 *)(row + (left > 0 ? h * D.d + ch : 0));
-        return left > 0 ? v : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    return load4<false>(row + (left > 0 ? h * D.d + ch : 0), left);
+    const int left = head_chunk_left<DP>(c4, h0, D);
+    return load4<VEC>(row + (left > 0 ? (h0 + 4 * c4 / DP) * D.d + (4 * c4) % DP : 0), left);
+}
+template <int DP, bool VEC>
+__device__ __forceinline__ f32x4 blank_head_chunk(f32x4 v, int c4, int h0, const Dims &D)
+{
+    return !VEC || head_chunk_left<DP>(c4, h0, D) > 0 ? v : f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 template <int DP, int HPW, bool VEC>
@@ -273,7 +288,7 @@ __global__ __launch_bounds__(256) void k_attention(const float *__restrict__ QKV
     f32x4 qf[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s)
-        qf[s] = load_head_chunk<DP, VEC>(img + (size_t)qtok * C3, 4 * s + g, h, D);
+        qf[s] = blank_head_chunk<DP, VEC>(load_head_chunk<DP, VEC>(img + (size_t)qtok * C3, 4 * s + g, h, D), 4 * s + g, h, D);
 
     constexpr int NL = KB * CW / 4 / 256;
     f32x4 kr[NL], vr[NL];
@@ -298,8 +313,8 @@ __global__ __launch_bounds__(256) void k_attention(const float *__restrict__ QKV
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
             const int idx = tid + 256 * u;
-            *(f32x4 *)(Ks + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = kr[u];
-            *(f32x4 *)(Vs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = vr[u];
+            *(f32x4 *)(Ks + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = blank_head_chunk<DP, VEC>(kr[u], idx % (CW / 4), hg * HPW, D);
+            *(f32x4 *)(Vs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = blank_head_chunk<DP, VEC>(vr[u], idx % (CW / 4), hg * HPW, D);
         }
         __syncthreads();
         if (k0 + KB < kn) fetch(k0 + KB);
@@ -388,8 +403,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q(const float *__restrict__ QK
     f32x4 qf[NS], gf[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        qf[s] = load_head_chunk<DP, VEC>(img + (size_t)qtok * C3, 4 * s + g, h, D);
-        gf[s] = load_head_chunk<DP, VEC>(dO + (itok + qtok) * D.C, 4 * s + g, h, D);
+        qf[s] = blank_head_chunk<DP, VEC>(load_head_chunk<DP, VEC>(img + (size_t)qtok * C3, 4 * s + g, h, D), 4 * s + g, h, D);
+        gf[s] = blank_head_chunk<DP, VEC>(load_head_chunk<DP, VEC>(dO + (itok + qtok) * D.C, 4 * s + g, h, D), 4 * s + g, h, D);
     }
     constexpr int NL = KB * CW / 4 / 256;
     f32x4 kr[NL], vr[NL];
@@ -425,8 +440,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q(const float *__restrict__ QK
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
             const int idx = tid + 256 * u;
-            *(f32x4 *)(Ks + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = kr[u];
-            *(f32x4 *)(Vs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = vr[u];
+            *(f32x4 *)(Ks + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = blank_head_chunk<DP, VEC>(kr[u], idx % (CW / 4), hg * HPW, D);
+            *(f32x4 *)(Vs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = blank_head_chunk<DP, VEC>(vr[u], idx % (CW / 4), hg * HPW, D);
         }
         __syncthreads();
         if (nblocks > 1 && step + 1 < 2 * nblocks) fetch(KB * ((step + 1) % nblocks));
@@ -546,8 +561,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const float *__restrict__ Q
     f32x4 kf[NS], vf[NS], ak[NS], av[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        kf[s] = load_head_chunk<DP, VEC>(img + (size_t)ktok * C3 + D.C, 4 * s + g, h, D);
-        vf[s] = load_head_chunk<DP, VEC>(img + (size_t)ktok * C3 + 2 * D.C, 4 * s + g, h, D);
+        kf[s] = blank_head_chunk<DP, VEC>(load_head_chunk<DP, VEC>(img + (size_t)ktok * C3 + D.C, 4 * s + g, h, D), 4 * s + g, h, D);
+        vf[s] = blank_head_chunk<DP, VEC>(load_head_chunk<DP, VEC>(img + (size_t)ktok * C3 + 2 * D.C, 4 * s + g, h, D), 4 * s + g, h, D);
         ak[s] = av[s] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     const float c_exp = D.scale * 1.4426950408889634f;
@@ -585,8 +600,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const float *__restrict__ Q
 #pragma unroll
             for (int u = 0; u < NL; ++u) {
                 const int idx = tid + 256 * u;
-                *(f32x4 *)(Qs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = qr[u];
-                *(f32x4 *)(Gs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = gr[u];
+                *(f32x4 *)(Qs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = blank_head_chunk<DP, VEC>(qr[u], idx % (CW / 4), hg * HPW, D);
+                *(f32x4 *)(Gs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = blank_head_chunk<DP, VEC>(gr[u], idx % (CW / 4), hg * HPW, D);
             }
             if (tid < HPW * QB) {
                 lse_s[tid] = next_lse;
@@ -665,15 +680,19 @@ __device__ __forceinline__ void tn_tile(const TnJob<TA, TB> &J, int block, long 
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
             const int idx = tid + 256 * u, c = 4 * (idx % 16);
-            const long t = t0 + idx / 16, tc = min(t, t_end - 1);
+            const long tc = min(t0 + idx / 16, t_end - 1);
             ra[u] = load4<VEC>(J.A + tc * J.lda + (VEC ? min(a0 + c, J.KA - 4) : a0 + c), J.KA - a0 - c);
             rb[u] = load4<VEC>(J.Bm + tc * J.ldb + (VEC ? min(n0 + c, J.N - 4) : n0 + c), J.N - n0 - c);
-            if (t >= t_end) ra[u] = rb[u] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     };
     fetch(t_begin);
     for (long t0 = t_begin; t0 < t_end; t0 += TT) {
         if (t0 > t_begin) __syncthreads();
+        if (t0 + TT > t_end) {               // blanked here, not behind the loads: the prefetch stays in flight
+#pragma unroll
+            for (int u = 0; u < NL; ++u)
+                if (t0 + (tid + 256 * u) / 16 >= t_end) ra[u] = rb[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
             const int idx = tid + 256 * u;
@@ -714,84 +733,6 @@ __global__ __launch_bounds__(256) void k_gemm_tn(TnJob<TA0, TB0> J0, TnJob<TA1, 
     __shared__ __attribute__((aligned(16))) float smem[2 * 32 * (64 + 4)];
     if ((int)blockIdx.x < J0.blocks) tn_tile<VEC>(J0, blockIdx.x, M, share_tokens, smem);
     else tn_tile<VEC>(J1, (int)blockIdx.x - J0.blocks, M, share_tokens, smem);
-}
-
-// ---------------------------------------------------------------------------
-// Out[t][c] += sum_{ky,kx} w[c][ky][kx] In[t + (ky - 2, kx - 2)][c] over the H x W map (zero outside):
-// LCE (Eq. 7); FLIP reverses the taps (its transpose, for the backward pass).  Workgroup: 64 channels of
-// 256 VW / 64 column pieces; a thread walks down kLceRows rows of one column with VW (2 or 1) channels: an
-// input row of 5 columns is read once and goes into the output rows it belongs to.  The taps pass through
-// LDS once per workgroup: read per thread from the [C][25] tensor they would cost a cache line per lane.
-// Row pitches ldi, ldo.
-constexpr int kLceRows = 4;
-
-template <typename TW, int VW, bool FLIP>
-__global__ __launch_bounds__(256) void k_lce(const float *__restrict__ In, int ldi, const TW *__restrict__ Wlce,
-                                             float *__restrict__ Out, int ldo, Dims D, int cblocks)
-{
-    __shared__ float taps[25][64];
-    constexpr int CPW = 64 / VW, COLS = 256 / CPW;
-    const int cb = blockIdx.x % cblocks, c0 = 64 * cb, yb_n = (D.H + kLceRows - 1) / kLceRows;
-    for (int e = threadIdx.x; e < min(64, D.C - c0) * 25; e += 256)
-        taps[FLIP ? 24 - e % 25 : e % 25][e / 25] = load_f32(Wlce + (size_t)c0 * 25 + e);
-    __syncthreads();
-    const int cl = ((int)threadIdx.x % CPW) * VW, c = c0 + cl;
-    const long q = (long)(blockIdx.x / cblocks) * COLS + threadIdx.x / CPW;
-    if (q >= (long)D.B * yb_n * D.W || c >= D.C) return;
-    const int x = (int)(q % D.W), y0 = (int)((q / D.W) % yb_n) * kLceRows;
-    const size_t b = q / ((long)D.W * yb_n);
-    const float *img = In + b * D.N * ldi + c;
-    float w[VW][25];
-#pragma unroll
-    for (int t = 0; t < 25; ++t)
-#pragma unroll
-        for (int v = 0; v < VW; ++v) w[v][t] = taps[t][cl + v];
-    float acc[kLceRows][VW];
-#pragma unroll
-    for (int r = 0; r < kLceRows; ++r)
-#pragma unroll
-        for (int v = 0; v < VW; ++v) acc[r][v] = 0.f;
-#pragma unroll
-    for (int dy = 0; dy < kLceRows + 4; ++dy) {
-        const int y = y0 + dy - 2;
-        const bool row_in = (unsigned)y < (unsigned)D.H;
-        float in[5][VW];
-#pragma unroll
-        for (int kx = 0; kx < 5; ++kx) {
-            const int xx = x + kx - 2;
-            const bool ok = row_in && (unsigned)xx < (unsigned)D.W;
-            const float *p = img + (size_t)(ok ? y * D.W + xx : 0) * ldi;
-            if (VW == 2) {
-                const f32x2 v2 = *(const f32x2 *)p;
-                in[kx][0] = ok ? v2[0] : 0.f;
-                in[kx][VW - 1] = ok ? v2[1] : 0.f;
-            } else {
-                in[kx][0] = ok ? *p : 0.f;
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < kLceRows; ++r) {
-            const int ky = dy - r;
-            if (ky < 0 || ky > 4) continue;
-#pragma unroll
-            for (int kx = 0; kx < 5; ++kx)
-#pragma unroll
-                for (int v = 0; v < VW; ++v) acc[r][v] = fmaf(w[v][5 * ky + kx], in[kx][v], acc[r][v]);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < kLceRows; ++r) {
-        if (y0 + r >= D.H) break;
-        float *o = Out + (b * D.N + (size_t)(y0 + r) * D.W + x) * ldo + c;
-        if (VW == 2) {
-            f32x2 v2 = *(f32x2 *)o;
-            v2[0] += acc[r][0];
-            v2[1] += acc[r][VW - 1];
-            *(f32x2 *)o = v2;
-        } else {
-            *o += acc[r][0];
-        }
-    }
 }
 
 }  // namespace f32

@@ -296,22 +296,6 @@ int launch_attention(const Dims &D, const float *qkv, const int32_t *Ir, float *
     return vec ? launch_attention_t<64, 1, true>(D, qkv, Ir, o, st) : launch_attention_t<64, 1, false>(D, qkv, Ir, o, st);
 }
 
-// Out += LCE(In) (FLIP: its transpose), row pitches ldi, ldo.
-template <bool FLIP, typename T>
-int launch_lce(const Dims &D, const float *In, int ldi, const T *Wlce, float *Out, int ldo, hipStream_t st)
-{
-    const int cblocks = (D.C + 63) / 64;
-    const long pieces = (long)D.B * ((D.H + f32::kLceRows - 1) / f32::kLceRows) * D.W;
-    const bool pairs = D.C % 2 == 0;
-    const int cols = pairs ? 8 : 4;
-    const long blocks = (pieces + cols - 1) / cols * cblocks;
-    if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    ProfScope ps(st, K_GEN_LCE);
-    if (pairs) hipLaunchKernelGGL((f32::k_lce<T, 2, FLIP>), dim3((unsigned)blocks), dim3(256), 0, st, In, ldi, Wlce, Out, ldo, D, cblocks);
-    else hipLaunchKernelGGL((f32::k_lce<T, 1, FLIP>), dim3((unsigned)blocks), dim3(256), 0, st, In, ldi, Wlce, Out, ldo, D, cblocks);
-    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
-}
-
 template <typename T>
 int forward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *Wlce, T *Y,
               int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st)
@@ -348,7 +332,7 @@ int forward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *Wl
     }
     rc = launch_attention(D, w.qkv, Ir, w.o, st);
     if (rc != BRA_OK) return rc;
-    rc = launch_lce<false>(D, w.qkv + 2 * C, 3 * C, Wlce, w.o, C, st);
+    rc = lce::launch_lce(D, w.qkv + 2 * C, 3 * C, Wlce, w.o, C, K_GEN_LCE, st);
     if (rc != BRA_OK) return rc;
     ProfScope ps(st, K_GEN_GEMM_WO);
     return launch_gemm<false>(f32::GemmJob<float, T, T>{w.o, Wo, Y, M, C, C, C, C, C, nullptr, nullptr, 0},
@@ -490,7 +474,7 @@ SharePlan share_plan(long M, int C)
     return {(int)((steps + per - 1) / per), (int)(per * 32)};
 }
 
-bwd::LcePlan lce_grad_plan(const Dims &D) { return bwd::lce_plan(D, 768); }
+lce::LcePlan lce_grad_plan(const Dims &D) { return lce::lce_plan(D, 768, D.C % 2 == 0 ? 8 : 4); }
 
 struct BwdWs {
     float *qkv, *o, *dO, *dqkv, *lse, *dsum, *part_qkv, *part_o, *part_lce;
@@ -566,16 +550,11 @@ int backward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *W
     rc = launch_attn_bwd(D, w, Ir, st);
     if (rc != BRA_OK) return rc;
     // O = attention + LCE(V) for dWo; dV += LCE^T(dO) and the tap gradients
-    rc = launch_lce<false>(D, w.qkv + 2 * C, C3, Wlce, w.o, C, st);
+    rc = lce::launch_lce(D, w.qkv + 2 * C, C3, Wlce, w.o, C, K_GEN_BACKWARD, st);
     if (rc != BRA_OK) return rc;
-    const bwd::LcePlan lp = lce_grad_plan(D);
-    const dim3 lgrid((unsigned)(lp.groups * lp.cblocks));
-    if (C % 2 == 0)
-        hipLaunchKernelGGL((bwd::k_lce_grad<float, T, 2>), lgrid, dim3(256), 0, st, w.dO, w.qkv + 2 * C, C3, Wlce,
-                           w.dqkv + 2 * C, C3, w.part_lce, D, lp.cblocks, lp.strips, lp.strips_per_wg, lp.height);
-    else
-        hipLaunchKernelGGL((bwd::k_lce_grad<float, T, 1>), lgrid, dim3(256), 0, st, w.dO, w.qkv + 2 * C, C3, Wlce,
-                           w.dqkv + 2 * C, C3, w.part_lce, D, lp.cblocks, lp.strips, lp.strips_per_wg, lp.height);
+    const lce::LcePlan lp = lce_grad_plan(D);
+    rc = lce::launch_lce_grad(D, lp, w.dO, w.qkv + 2 * C, C3, Wlce, w.dqkv + 2 * C, C3, w.part_lce, st);
+    if (rc != BRA_OK) return rc;
     // dX = [dQ | dK | dV] Wqkv^T
     rc = launch_gemm<true>(f32::GemmJob<float, T, T>{w.dqkv, Wqkv, dX, M, C3, C3, C, C, C3, nullptr, nullptr, 0}, none, st);
     if (rc != BRA_OK) return rc;

@@ -10,14 +10,16 @@
 //     dK = dS^T Q,  dV = P^T dO        k_attn_bwd_kv, one workgroup per KEY region: it finds the query
 //                                      regions routed to it in Ir, recomputes their P and dS from the
 //                                      statistics and sums in registers, so no atomic adds are needed
-//     O += LCE(V), dV += LCE^T(dO) (the correlation with the taps reversed) and
-//     dWlce[c][ky][kx] = sum_t dO[t][c] V[t + (ky - 2, kx - 2)][c]       k_lce_bwd
+//     O += LCE(V)                      k_lce
+//     dV += LCE^T(dO) (the correlation with the taps reversed) and
+//     dWlce[c][ky][kx] = sum_t dO[t][c] V[t + (ky - 2, kx - 2)][c]       k_lce_grad
 //     dX = [dQ | dK | dV] Wqkv^T,  dWqkv = X^T [dQ | dK | dV]      k_bwd_proj, one pass over the gradient map
 //     dWo = O^T dY                     k_gemm_tn (contraction over tokens)
 // All products take bf16 operands and accumulate in float32; dQ, dK, dV and dO are rounded to
 // bf16 between the kernels (they are matrix-core operands of the next product).  The weight
 // gradients are summed from per-workgroup partial sums in a fixed order (k_reduce_parts).
 #include "bra_bwd_dev.h"
+#include "bra_lce_dev.h"
 
 namespace bra {
 
@@ -98,7 +100,9 @@ __device__ __forceinline__ int region_token(const Dims &D, int region, int slot)
 }
 
 // Channels c0 .. c0 + CW - 1 of ROWS rows of two token maps (row pitch C) -> registers -> LDS tiles
-// of pitch CW + 8; tok(row) names the token of a tile row within the image (-1: a row of zeros).
+// of pitch CW + 8; tok(row) names the token of a tile row within the image.  Rows past the end of a list name an
+// existing token again: their weights are zero or their results are not stored.  The loads are unconditional: a
+// load under a condition makes the compiler wait for all outstanding ones and takes the prefetch away.
 template <int CW, int ROWS = 64>
 struct RowRegs {
     static constexpr int CHUNKS = ROWS * (CW / 8), NL = (CHUNKS + 255) / 256;
@@ -112,14 +116,10 @@ __device__ __forceinline__ void fetch_rows(RowRegs<CW, ROWS> &R, const bf16_t *_
     constexpr int CH8 = CW / 8;
 #pragma unroll
     for (int u = 0; u < RowRegs<CW, ROWS>::NL; ++u) {
-        const int idx = threadIdx.x + 256 * u, row = idx / CH8, c8 = idx % CH8;
-        const int t = idx < RowRegs<CW, ROWS>::CHUNKS ? tok(row) : -1;
-        R.r0[u] = u32x4{0u, 0u, 0u, 0u};
-        R.r1[u] = R.r0[u];
-        if (t >= 0) {
-            R.r0[u] = *(const u32x4 *)(M0 + (img + t) * C + c0 + c8 * 8);
-            R.r1[u] = *(const u32x4 *)(M1 + (img + t) * C + c0 + c8 * 8);
-        }
+        const int idx = threadIdx.x + 256 * u, row = min(idx / CH8, ROWS - 1), c8 = idx % CH8;
+        const size_t at = (img + tok(row)) * C + c0 + c8 * 8;
+        R.r0[u] = *(const u32x4 *)(M0 + at);
+        R.r1[u] = *(const u32x4 *)(M1 + at);
     }
 }
 
@@ -167,10 +167,10 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q(const bf16_t *__restrict__ Q
     const size_t img = (size_t)b * D.N;
     const int32_t *irow = Ir + ((size_t)b * D.R + r) * D.k;
     auto key_token = [&](int l) {          // key l of the gathered set (Eq. 6): slot l % n of routed region l / n
-        if (l >= kn) return -1;
+        l = min(l, kn - 1);
         return region_token(D, min(max(irow[l / D.n], 0), D.R - 1), l % D.n);
     };
-    auto query_token = [&](int l) { return l < nq ? region_token(D, r, 64 * qc + l) : -1; };
+    auto query_token = [&](int l) { return region_token(D, r, 64 * qc + min(l, nq - 1)); };
     {
         // the query rows do not wait for the routing index: ask for them first
         RowRegs<CW, QR> qr;
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q(const bf16_t *__restrict__ Q
             oacc[dt] *= inv;
             qacc[dt] *= inv * D.scale;
         }
-        if (my_qtok >= 0) {
+        if (q < nq) {
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) {
                 *(u32x2 *)(O + (img + my_qtok) * C + DH * h + 16 * dt + 4 * g) = pack4(oacc[dt]);
@@ -293,9 +293,10 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q_blocks(const bf16_t *__restr
     int *ir_s = (int *)(smem + L::q_bytes);
     for (int e = threadIdx.x; e < D.k; e += 256) ir_s[e] = min(max(Ir[((size_t)b * D.R + r) * D.k + e], 0), D.R - 1);
     auto key_token = [&](int l) {          // key l of the gathered set (Eq. 6): slot l % n of routed region l / n
-        return l < kn ? region_token(D, ir_s[l / D.n], l % D.n) : -1;
+        l = min(l, kn - 1);
+        return region_token(D, ir_s[l / D.n], l % D.n);
     };
-    auto query_token = [&](int l) { return l < nq ? region_token(D, r, 64 * qc + l) : -1; };
+    auto query_token = [&](int l) { return region_token(D, r, 64 * qc + min(l, nq - 1)); };
     // DEPTH blocks of K, V rows are in flight in registers.  One is enough: the sweeps are bound by
     // their vector work (about 200 instructions per pair and block), and with three blocks in flight
     // the kernel was slower (99 against 90 us on a 2 x 128 x 128 x 64 map with 1024 keys per query)
@@ -410,11 +411,12 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q_blocks(const bf16_t *__restr
                 if (task >= ntasks) continue;
                 const int qt = task % qtiles, h = h0 + task / qtiles;
                 const int tok = query_token(16 * qt + i);
+                const bool mine = 16 * qt + i < nq;
                 if (sweep == 0) {
                     const float inv = 1.0f / l[u];
                     const float lse2 = fmaf(m[u], c_exp, __builtin_amdgcn_logf(l[u]));      // v_log_f32: log2
                     const float dfin = dd[u] * inv;
-                    if (tok >= 0) {
+                    if (mine) {
 #pragma unroll
                         for (int dt = 0; dt < NDT; ++dt)
                             *(u32x2 *)(O + (img + tok) * C + DH * h + 16 * dt + 4 * g) = pack4(acc[u][dt] * inv);
@@ -427,7 +429,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q_blocks(const bf16_t *__restr
                     dd[u] = dfin;
 #pragma unroll
                     for (int dt = 0; dt < NDT; ++dt) acc[u][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-                } else if (tok >= 0) {
+                } else if (mine) {
 #pragma unroll
                     for (int dt = 0; dt < NDT; ++dt)
                         *(u32x2 *)(dQ + (img + tok) * (size_t)ldq + DH * h + 16 * dt + 4 * g) =
@@ -470,7 +472,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const bf16_t *__restrict__ 
     const int kc = bx % kchunks, jr = (bx / kchunks) % D.R, b = bx / (kchunks * D.R);
     const int nk = min(KR, D.n - 64 * kc);                  // KR = 16: regions of at most 16 tokens
     const size_t img = (size_t)b * D.N;
-    auto key_token = [&](int l) { return l < nk ? region_token(D, jr, 64 * kc + l) : -1; };
+    auto key_token = [&](int l) { return region_token(D, jr, 64 * kc + min(l, nk - 1)); };
     if (threadIdx.x == 0) *count = 0;
     __syncthreads();
     const int entries = D.R * D.k;
@@ -504,8 +506,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const bf16_t *__restrict__ 
     const int rows = m * D.n;
     // row r0 + l of the list of queries: slot .. % n of the query region of entry .. / n
     auto query_token = [&](int r0, int l) {
-        const int rho = r0 + l;
-        return rho < rows ? region_token(D, list[rho / D.n] / D.k, rho % D.n) : -1;
+        const int rho = min(r0 + l, rows - 1);
+        return region_token(D, list[rho / D.n] / D.k, rho % D.n);
     };
     // the next block's rows and statistics travel to registers while the current block is worked on
     RowRegs<CW, 64> next;
@@ -513,12 +515,9 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const bf16_t *__restrict__ 
     const int srow = threadIdx.x / HPW, sh = threadIdx.x % HPW;          // statistics: one (row, head) per thread
     auto fetch_block = [&](int r0) {
         fetch_rows<CW, 64>(next, Q, dO, img, C, DH * h0, [&](int l) { return query_token(r0, l); });
-        if ((int)threadIdx.x < 64 * HPW) {
-            const int t = query_token(r0, srow);
-            // a missing row: P = exp2(-inf) = 0 and dS = 0
-            next_lse = t >= 0 ? lse[(img + t) * HEADS + h0 + sh] : INFINITY;
-            next_dd = t >= 0 ? dsum[(img + t) * HEADS + h0 + sh] : 0.f;
-        }
+        const size_t at = (img + query_token(r0, srow % 64)) * HEADS + h0 + sh;
+        next_lse = lse[at];
+        next_dd = dsum[at];
     };
     __syncthreads();                      // the list is in place
     if (rows > 0) fetch_block(0);
@@ -526,8 +525,9 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const bf16_t *__restrict__ 
         if (r0 > 0) __syncthreads();      // the previous block's readers are done
         store_rows<CW, 64>(Qs, dOs, next);
         if ((int)threadIdx.x < 64 * HPW) {
-            lse_s[sh * 64 + srow] = next_lse;
-            dd_s[sh * 64 + srow] = next_dd;
+            // a missing row: P = exp2(-inf) = 0 and dS = 0
+            lse_s[sh * 64 + srow] = r0 + srow < rows ? next_lse : INFINITY;
+            dd_s[sh * 64 + srow] = r0 + srow < rows ? next_dd : 0.f;
         }
         __syncthreads();
         if (r0 + 64 < rows) fetch_block(r0 + 64);
@@ -589,8 +589,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const bf16_t *__restrict__ 
         const int task = w + 4 * u;
         if (task >= ntasks) continue;
         const int kt = task % ktiles, h = task / ktiles, col = DH * (h0 + h);
+        if (16 * kt + i >= nk) continue;
         const int t = key_token(16 * kt + i);
-        if (t < 0) continue;
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
             *(u32x2 *)(dKV + (img + t) * (size_t)ld + col + 16 * dt + 4 * g) = pack4(acc[u][NDT + dt] * D.scale);
@@ -623,16 +623,18 @@ __global__ __launch_bounds__(256) void k_gemm_tn(const bf16_t *__restrict__ A, i
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int idx = threadIdx.x + 256 * u, row = idx / 8, c8 = idx % 8;
-            ar[u] = u32x4{0u, 0u, 0u, 0u};
-            br[u] = ar[u];
-            if (t0 + row < t_end) {
-                ar[u] = *(const u32x4 *)(A + (size_t)(t0 + row) * lda + a0 + c8 * 8);
-                br[u] = *(const u32x4 *)(Bm + (size_t)(t0 + row) * ldb + b0 + c8 * 8);
-            }
+            const size_t t = min(t0 + row, t_end - 1);       // unconditional; rows past the end are blanked at the LDS write
+            ar[u] = *(const u32x4 *)(A + t * lda + a0 + c8 * 8);
+            br[u] = *(const u32x4 *)(Bm + t * ldb + b0 + c8 * 8);
         }
     };
     if (t_begin < t_end) fetch(t_begin);
     for (long t0 = t_begin; t0 < t_end; t0 += 64) {
+        if (t0 + 64 > t_end) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (t0 + (threadIdx.x + 256 * u) / 8 >= t_end) ar[u] = br[u] = u32x4{0u, 0u, 0u, 0u};
+        }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int idx = threadIdx.x + 256 * u, row = idx / 8, c8 = idx % 8;
@@ -698,22 +700,17 @@ __global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G
 #pragma unroll
         for (int u = 0; u < GL; ++u) {
             const int idx = threadIdx.x + NT * u;
-            const long t = tile * 64 + idx / GCH;
-            gr[u] = u32x4{0u, 0u, 0u, 0u};
-            if (t < M) gr[u] = *(const u32x4 *)(G + (size_t)t * 3 * C + (idx % GCH) * 8);
+            const size_t t = min(tile * 64 + idx / GCH, M - 1);
+            gr[u] = *(const u32x4 *)(G + t * 3 * C + (idx % GCH) * 8);
         }
 #pragma unroll
         for (int u = 0; u < XL; ++u) {
             const int idx = threadIdx.x + NT * u;
-            const long t = tile * 64 + idx / XCH;
-            xr[u] = u32x4{0u, 0u, 0u, 0u};
-            if (WO) orr[u] = yr[u] = xr[u];
-            if (t < M) {
-                xr[u] = *(const u32x4 *)(X + (size_t)t * C + (idx % XCH) * 8);
-                if (WO) {
-                    orr[u] = *(const u32x4 *)(O + (size_t)t * C + (idx % XCH) * 8);
-                    yr[u] = *(const u32x4 *)(dY + (size_t)t * C + (idx % XCH) * 8);
-                }
+            const size_t at = (size_t)min(tile * 64 + idx / XCH, M - 1) * C + (idx % XCH) * 8;
+            xr[u] = *(const u32x4 *)(X + at);
+            if (WO) {
+                orr[u] = *(const u32x4 *)(O + at);
+                yr[u] = *(const u32x4 *)(dY + at);
             }
         }
     };
@@ -721,6 +718,17 @@ __global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G
     if (first < last) fetch(first);
     for (int tile = first; tile < last; ++tile) {
         if (tile > first) __syncthreads();          // the previous tile's readers are done
+        if ((long)tile * 64 + 64 > M) {             // tokens past the end add nothing: blanked here, not behind the loads
+#pragma unroll
+            for (int u = 0; u < GL; ++u)
+                if ((long)tile * 64 + (threadIdx.x + NT * u) / GCH >= M) gr[u] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int u = 0; u < XL; ++u)
+                if ((long)tile * 64 + (threadIdx.x + NT * u) / XCH >= M) {
+                    xr[u] = u32x4{0u, 0u, 0u, 0u};
+                    if (WO) orr[u] = yr[u] = xr[u];
+                }
+        }
 #pragma unroll
         for (int u = 0; u < GL; ++u) {
             const int idx = threadIdx.x + NT * u;
@@ -774,193 +782,6 @@ __global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G
 }
 
 // ---------------------------------------------------------------------------
-// The three uses of the depth-wise 5x5 correlation (Eq. 7) in the backward pass, in one kernel.
-// A tile is kLbTH x kLbTW tokens of one image and 64 channels; a thread handles a pair of channels
-// and 4-token row segments.
-//   phase 1, V with a 2-token halo in LDS:   O += LCE(V)  (the forward's O, for dWo) and the tap
-//            gradients dWlce[c][ky][kx] = sum_t dO[t][c] V[t + (ky - 2, kx - 2)][c], 2 x 25 sums
-//            kept in registers across the workgroup's tiles (V is zero outside the image)
-//   phase 2, dO with its halo in the same LDS buffer:
-//            dV += LCE^T(dO), the correlation with the taps reversed; dV has row pitch ldv
-// Two workgroups per compute unit (the 50 tap sums, the unpacked weights and the halo rows in flight
-// take that register budget; fetching the next phase's halo into registers ahead of time was
-// measured slower, 92 against 68 us on a 64 x 56 x 56 x 64 map).  At the end the workgroup reduces its tap sums through
-// LDS and writes Part[tile group][C][25] for k_reduce_parts.
-constexpr int kLbTH = 4, kLbTW = 32, kLbHW = kLbTW + 4, kLbRows = (kLbTH + 4) * kLbHW, kLbPitch = 64 + 8;
-constexpr int kLbLoads = (kLbRows * 8 + 255) / 256;
-constexpr size_t kLbSmem = std::max((size_t)kLbRows * kLbPitch * 2, (size_t)4 * 32 * 50 * 4);
-
-__device__ __forceinline__ void halo_fetch(u32x4 (&h)[kLbLoads], const bf16_t *__restrict__ M, size_t img_off,
-                                           int y0, int x0, int c0, const Dims &D)
-{
-#pragma unroll
-    for (int u = 0; u < kLbLoads; ++u) {
-        const int idx = threadIdx.x + 256 * u, row = idx / 8, c8 = idx % 8;
-        const int y = y0 - 2 + row / kLbHW, x = x0 - 2 + row % kLbHW;
-        h[u] = u32x4{0u, 0u, 0u, 0u};
-        if (idx < kLbRows * 8 && y >= 0 && y < D.H && x >= 0 && x < D.W)
-            h[u] = *(const u32x4 *)(M + img_off + ((size_t)y * D.W + x) * D.C + c0 + c8 * 8);
-    }
-}
-
-__device__ __forceinline__ void halo_store(bf16_t *Hs, const u32x4 (&h)[kLbLoads])
-{
-#pragma unroll
-    for (int u = 0; u < kLbLoads; ++u) {
-        const int idx = threadIdx.x + 256 * u;
-        if (idx < kLbRows * 8) *(u32x4 *)(Hs + (idx / 8) * kLbPitch + (idx % 8) * 8) = h[u];
-    }
-}
-
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_lce_bwd(bf16_t *__restrict__ O, bf16_t *__restrict__ dVm, int ldv,
-                                                 const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
-                                                 const bf16_t *__restrict__ Wlce, float *__restrict__ Part, Dims D,
-                                                 int tiles_total, int tiles_per_wg)
-{
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    bf16_t *Hs = (bf16_t *)smem;
-    const int C = D.C, NCH = C / 64;
-    const int ytiles = (D.H + kLbTH - 1) / kLbTH, xtiles = (D.W + kLbTW - 1) / kLbTW;
-    const int cc = blockIdx.x % NCH, c0 = 64 * cc;
-    const int first_tile = (blockIdx.x / NCH) * tiles_per_wg;
-    const int last_tile = min(tiles_total, first_tile + tiles_per_wg);
-    const int cpair = threadIdx.x % 32, grp = threadIdx.x / 32;
-    unsigned wl[25];        // [W(c, 0..24) | W(c + 1, 0..24)] as 25 packed pairs
-#pragma unroll
-    for (int e = 0; e < 25; ++e) wl[e] = *(const unsigned *)(Wlce + (size_t)(c0 + 2 * cpair) * 25 + 2 * e);
-    auto tap = [&](int ch, int t) {   // weight of tap t of channel c + ch
-        const int e = 25 * ch + t;
-        return (e & 1) ? bf16_hi(wl[e / 2]) : bf16_lo(wl[e / 2]);
-    };
-    float g0[25], g1[25];
-#pragma unroll
-    for (int e = 0; e < 25; ++e) g0[e] = g1[e] = 0.f;
-
-    auto origin = [&](int tile, int &b, int &y0, int &x0) {
-        b = tile / (xtiles * ytiles);
-        y0 = ((tile / xtiles) % ytiles) * kLbTH;
-        x0 = (tile % xtiles) * kLbTW;
-    };
-    for (int tile = first_tile; tile < last_tile; ++tile) {
-        int b, y0, x0;
-        origin(tile, b, y0, x0);
-        const int th = min(kLbTH, D.H - y0), tw = min(kLbTW, D.W - x0);
-        const size_t img_off = (size_t)b * D.N * C, img_tok = (size_t)b * D.N;
-        __syncthreads();          // the previous tile's readers are done
-        {
-            u32x4 h[kLbLoads];
-            halo_fetch(h, V, img_off, y0, x0, c0, D);
-            halo_store(Hs, h);
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int task = grp; task < kLbTH * (kLbTW / 4); task += 8) {
-            const int seg = task % (kLbTW / 4), r = task / (kLbTW / 4);
-            if (r >= th || seg * 4 >= tw) continue;
-            const size_t tok = (size_t)(y0 + r) * D.W + x0 + seg * 4;
-            const unsigned *drow = (const unsigned *)(dO + img_off + tok * C + c0 + 2 * cpair);
-            unsigned *orow = (unsigned *)(O + img_off + tok * C + c0 + 2 * cpair);
-            unsigned o2[4];
-            float d0[4], d1[4], a0[4] = {0.f, 0.f, 0.f, 0.f}, a1[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const bool in = seg * 4 + x < tw;
-                const unsigned u = in ? drow[(size_t)x * (C / 2)] : 0u;
-                o2[x] = in ? orow[(size_t)x * (C / 2)] : 0u;
-                d0[x] = bf16_lo(u);
-                d1[x] = bf16_hi(u);
-            }
-#pragma unroll
-            for (int ky = 0; ky < 5; ++ky) {
-                float v0[8], v1[8];
-#pragma unroll
-                for (int x = 0; x < 8; ++x) {
-                    const unsigned u = *(const unsigned *)(Hs + ((r + ky) * kLbHW + seg * 4 + x) * kLbPitch + 2 * cpair);
-                    v0[x] = bf16_lo(u);
-                    v1[x] = bf16_hi(u);
-                }
-#pragma unroll
-                for (int kx = 0; kx < 5; ++kx) {
-                    const float w0 = tap(0, ky * 5 + kx), w1 = tap(1, ky * 5 + kx);
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        a0[x] = fmaf(w0, v0[x + kx], a0[x]);
-                        a1[x] = fmaf(w1, v1[x + kx], a1[x]);
-                        g0[ky * 5 + kx] = fmaf(d0[x], v0[x + kx], g0[ky * 5 + kx]);
-                        g1[ky * 5 + kx] = fmaf(d1[x], v1[x + kx], g1[ky * 5 + kx]);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);      // one halo row at a time: the tap sums fill the registers
-            }
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-                if (seg * 4 + x < tw)
-                    orow[(size_t)x * (C / 2)] = pack_bf16(bf16_lo(o2[x]) + a0[x], bf16_hi(o2[x]) + a1[x]);
-        }
-        __syncthreads();
-        {
-            u32x4 h[kLbLoads];
-            halo_fetch(h, dO, img_off, y0, x0, c0, D);
-            halo_store(Hs, h);
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int task = grp; task < kLbTH * (kLbTW / 4); task += 8) {
-            const int seg = task % (kLbTW / 4), r = task / (kLbTW / 4);
-            if (r >= th || seg * 4 >= tw) continue;
-            const size_t tok = img_tok + (size_t)(y0 + r) * D.W + x0 + seg * 4;
-            unsigned *vrow = (unsigned *)(dVm + tok * ldv + c0 + 2 * cpair);
-            unsigned o2[4];
-            float a0[4] = {0.f, 0.f, 0.f, 0.f}, a1[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int x = 0; x < 4; ++x) o2[x] = seg * 4 + x < tw ? vrow[(size_t)x * (ldv / 2)] : 0u;
-#pragma unroll
-            for (int ky = 0; ky < 5; ++ky) {
-                float v0[8], v1[8];
-#pragma unroll
-                for (int x = 0; x < 8; ++x) {
-                    const unsigned u = *(const unsigned *)(Hs + ((r + ky) * kLbHW + seg * 4 + x) * kLbPitch + 2 * cpair);
-                    v0[x] = bf16_lo(u);
-                    v1[x] = bf16_hi(u);
-                }
-#pragma unroll
-                for (int kx = 0; kx < 5; ++kx) {
-                    const float w0 = tap(0, 24 - (ky * 5 + kx)), w1 = tap(1, 24 - (ky * 5 + kx));
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        a0[x] = fmaf(w0, v0[x + kx], a0[x]);
-                        a1[x] = fmaf(w1, v1[x + kx], a1[x]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-                if (seg * 4 + x < tw)
-                    vrow[(size_t)x * (ldv / 2)] = pack_bf16(bf16_lo(o2[x]) + a0[x], bf16_hi(o2[x]) + a1[x]);
-        }
-    }
-    // lanes l and l + 32 of a wavefront hold the same channel pair; then the four wavefronts through LDS
-    __syncthreads();
-    float *Rs = (float *)smem;
-    const int wv = threadIdx.x / 64;
-#pragma unroll
-    for (int e = 0; e < 25; ++e) {
-        g0[e] += __shfl_xor(g0[e], 32);
-        g1[e] += __shfl_xor(g1[e], 32);
-        if (threadIdx.x % 64 < 32) {
-            Rs[(wv * 32 + cpair) * 50 + e] = g0[e];
-            Rs[(wv * 32 + cpair) * 50 + 25 + e] = g1[e];
-        }
-    }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < 32 * 50; idx += 256) {
-        const float v = Rs[idx] + Rs[32 * 50 + idx] + Rs[2 * 32 * 50 + idx] + Rs[3 * 32 * 50 + idx];
-        // idx = cpair * 50 + 25 * (channel of the pair) + tap
-        Part[((size_t)(blockIdx.x / NCH) * C + c0 + 2 * (idx / 50) + (idx % 50) / 25) * 25 + idx % 25] = v;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // WT[o][c] = Wqkv[c][o] ([3C][C]) and WoT[o][c] = Wo[c][o], for the channel counts whose projection
 // launch does not carry the rearrangement along.
 __global__ void k_bwd_transpose(const bf16_t *__restrict__ Wqkv, const bf16_t *__restrict__ Wo,
@@ -1000,22 +821,6 @@ ProjPlan proj_plan(long M, int C)
     return p;
 }
 
-struct TapPlan {
-    int tiles, per_wg, groups;
-};
-
-// Tiles of k_lce_bwd per workgroup: all workgroups resident at once (3 per compute unit).
-TapPlan tap_plan(const Dims &D)
-{
-    const int ytiles = (D.H + kLbTH - 1) / kLbTH, xtiles = (D.W + kLbTW - 1) / kLbTW;
-    const int slots = (int)experiment_value("BRA_LCE_SLOTS", 512) / (D.C / 64);
-    TapPlan t;
-    t.tiles = D.B * ytiles * xtiles;
-    t.per_wg = (t.tiles + slots - 1) / slots;
-    t.groups = (t.tiles + t.per_wg - 1) / t.per_wg;
-    return t;
-}
-
 // k_bwd_proj keeps 3C / 16 accumulators per wavefront: up to C = 128; wider layers take the plain
 // product for dX and k_gemm_tn for dWqkv.
 bool fused_projection(int C) { return C <= 128; }
@@ -1049,7 +854,7 @@ BwdWs carve_bwd(const Dims &D, void *ws)
     w.part_qkv = (float *)take((size_t)(fused_projection(D.C) ? proj_plan(M, D.C).groups : tn_plan(M, D.C, 3 * D.C).gx) *
                                3 * C * C * 4);
     w.part_o = (float *)take((size_t)std::max(tn_plan(M, D.C, D.C).gx, proj_plan(M, D.C).groups) * C * C * 4);
-    w.part_lce = (float *)take((size_t)tap_plan(D).groups * 25 * C * 4);
+    w.part_lce = (float *)take((size_t)lce::lce_grad_groups_bf16(D) * 25 * C * 4);
     w.wt = (bf16_t *)take(3 * C * C * 2);
     w.wot = (bf16_t *)take(C * C * 2);
     w.bytes = off;
@@ -1197,16 +1002,11 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
     if (rc != BRA_OK) return rc;
     rc = attn_bwd(D, w, Ir, st);                                              // O, dQ; then dK, dV
     if (rc != BRA_OK) return rc;
-    const TapPlan tp = tap_plan(D);
-    {
-        // O = attention + LCE(V) (Eq. 7), dV += LCE^T(dO), tap-gradient partial sums
-        static bool opted = false;
-        if (!opt_in(k_lce_bwd, opted)) return BRA_ERR_LAUNCH;
-        ProfScope ps(st, K_GEN_BACKWARD);
-        hipLaunchKernelGGL(k_lce_bwd, dim3(tp.groups * (C / 64)), dim3(256), kLbSmem, st, w.o, w.dqkv + 2 * C, 3 * C,
-                           w.v, w.dO, (const bf16_t *)Wlce, w.part_lce, D, tp.tiles, tp.per_wg);
-        if (!launched()) return BRA_ERR_LAUNCH;
-    }
+    // O = attention + LCE(V) (Eq. 7) for dWo; dV += LCE^T(dO) and the tap-gradient partial sums
+    rc = lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, C, K_GEN_BACKWARD, st);
+    if (rc != BRA_OK) return rc;
+    rc = lce::lce_grad_bf16(D, w.dO, w.v, (const bf16_t *)Wlce, w.dqkv + 2 * C, 3 * C, w.part_lce, K_GEN_BACKWARD, st);
+    if (rc != BRA_OK) return rc;
     const ProjPlan pp = proj_plan(M, C);
     const bool with_o = C == 64;          // dWo = O^T dY rides in the same pass where the registers allow it
     if (fused_projection(C)) {
@@ -1238,7 +1038,7 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
         const ReduceJob j0 = reduce_job(w.part_qkv, dWqkv, fused_projection(C) ? pp.groups : tn_plan(M, C, 3 * C).gx,
                                         3 * C * C);
         const ReduceJob j1 = reduce_job(w.part_o, dWo, with_o ? pp.groups : tn_plan(M, C, C).gx, C * C);
-        const ReduceJob j2 = reduce_job(w.part_lce, dWlce, tp.groups, 25 * C);
+        const ReduceJob j2 = reduce_job(w.part_lce, dWlce, lce::lce_grad_groups_bf16(D), 25 * C);
         ProfScope ps(st, K_GEN_BACKWARD);
         hipLaunchKernelGGL(k_reduce_parts, dim3(j0.blocks + j1.blocks + j2.blocks), dim3(1024), 0, st, j0, j1, j2);
         if (!launched()) return BRA_ERR_LAUNCH;

@@ -13,7 +13,7 @@
 // k_attn_map / k_attn_map4 (a head's Q, K, V of a whole image in LDS, the LCE added from the
 // same V slice), else k_attn_small (attention output to memory) and k_lce_add (adds the LCE
 // in place); then the projection kernel with W^o.
-#include "bra_mfma_dev.h"
+#include "bra_lce_dev.h"
 
 namespace bra {
 
@@ -642,99 +642,6 @@ __global__ __launch_bounds__(kMapThreads) void k_attn_map4(AttnArgs A, bf16_t *_
     }
 }
 
-// ---------------------------------------------------------------------------
-// O <- O_att + LCE(V) (Eq. 7) in place, for workgroup (image, tile of TH image rows x TW
-// columns (the full width on narrow maps), chunk of 64 channels).  LDS holds the V halo tile
-// of the chunk, [(TH + 4) x (TW + 4)] tokens x 64 channels; a thread keeps one channel pair for
-// all its (row, 4-token segment) tasks, so its 2 x 25 weights stay in registers.  W^o follows
-// as a plain projection.
-constexpr int kLceChunk = 64, kLcePitch = kLceChunk + 8;
-
-__global__ __launch_bounds__(256) void k_lce_add(bf16_t *__restrict__ O, const bf16_t *__restrict__ V,
-                                                 const bf16_t *__restrict__ Wlce, Dims D, int TH, int TW, int ldo)
-{
-    constexpr int CH8 = kLceChunk / 8, NBH = 6;
-    const int C = D.C, NCH = C / kLceChunk;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    bf16_t *Hs = (bf16_t *)smem;
-    const int tiles = (D.H + TH - 1) / TH, xtiles = (D.W + TW - 1) / TW;
-    const int cc = blockIdx.x % NCH, xt = (blockIdx.x / NCH) % xtiles;
-    const int tile = (blockIdx.x / (NCH * xtiles)) % tiles, b = blockIdx.x / (NCH * xtiles * tiles);
-    const int y0 = tile * TH, x0 = xt * TW;
-    const int th = min(TH, D.H - y0), tw = min(TW, D.W - x0);     // rows and columns of this tile
-    const size_t img_off = (size_t)b * D.N * C;
-    const int hw = tw + 4, hrows = (th + 4) * hw;
-    const float hw_inv = 1.0f / (float)hw;
-    const int c0 = cc * kLceChunk;
-
-    const int cpair = threadIdx.x % (kLceChunk / 2);
-    unsigned wl[25];        // [W(c, 0..24) | W(c + 1, 0..24)] as 25 packed pairs
-#pragma unroll
-    for (int e = 0; e < 25; ++e) wl[e] = *(const unsigned *)(Wlce + (size_t)(c0 + 2 * cpair) * 25 + 2 * e);
-    auto tap = [&](int ch, int t) {   // weight of tap t of channel c + ch
-        const int e = 25 * ch + t;
-        return (e & 1) ? bf16_hi(wl[e / 2]) : bf16_lo(wl[e / 2]);
-    };
-    for (int first = 0; first < hrows * CH8; first += 256 * NBH) {
-        u32x4 hreg[NBH];
-#pragma unroll
-        for (int u = 0; u < NBH; ++u) {
-            const int idx = first + (int)threadIdx.x + 256 * u;
-            const int row = idx / CH8, c8 = idx % CH8;
-            const int ry = fast_div(row, hw_inv);
-            const int y = y0 - 2 + ry, x = x0 + row - ry * hw - 2;
-            hreg[u] = u32x4{0u, 0u, 0u, 0u};
-            if (row < hrows && y >= 0 && y < D.H && x >= 0 && x < D.W)
-                hreg[u] = *(const u32x4 *)(V + img_off + ((size_t)y * D.W + x) * C + c0 + c8 * 8);
-        }
-#pragma unroll
-        for (int u = 0; u < NBH; ++u) {
-            const int idx = first + (int)threadIdx.x + 256 * u;
-            if (idx < hrows * CH8) *(u32x4 *)(Hs + (idx / CH8) * kLcePitch + (idx % CH8) * 8) = hreg[u];
-        }
-    }
-    __syncthreads();
-
-    const int cp_n = kLceChunk / 2, segs = (tw + 3) / 4;
-    const int tasks = th * segs * cp_n;
-    for (int task = threadIdx.x; task < tasks; task += 256) {
-        const int seg = (task / cp_n) % segs, r = task / (cp_n * segs);
-        float a0[4] = {0.f, 0.f, 0.f, 0.f}, a1[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ky = 0; ky < 5; ++ky) {
-            float v0[8], v1[8];
-#pragma unroll
-            for (int x = 0; x < 8; ++x) {
-                const int hx = min(seg * 4 + x, hw - 1);    // a ragged segment re-reads the last column; unused
-                const unsigned u = *(const unsigned *)(Hs + ((r + ky) * hw + hx) * kLcePitch + 2 * cpair);
-                v0[x] = bf16_lo(u);
-                v1[x] = bf16_hi(u);
-            }
-#pragma unroll
-            for (int kx = 0; kx < 5; ++kx) {
-                const float w0 = tap(0, ky * 5 + kx), w1 = tap(1, ky * 5 + kx);
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    a0[x] = fmaf(w0, v0[x + kx], a0[x]);
-                    a1[x] = fmaf(w1, v1[x + kx], a1[x]);
-                }
-            }
-        }
-        // rows of O are ldo elements apart (C for a map of its own, more for a slice of a wider map)
-        unsigned *orow = (unsigned *)(O + ((size_t)b * D.N + (size_t)(y0 + r) * D.W + x0 + seg * 4) * ldo + c0 + 2 * cpair);
-        unsigned o2[4];
-#pragma unroll
-        for (int x = 0; x < 4; ++x) o2[x] = seg * 4 + x < tw ? orow[(size_t)x * (ldo / 2)] : 0u;
-#pragma unroll
-        for (int x = 0; x < 4; ++x)
-            if (seg * 4 + x < tw) orow[(size_t)x * (ldo / 2)] = pack_bf16(bf16_lo(o2[x]) + a0[x], bf16_hi(o2[x]) + a1[x]);
-    }
-}
-
-// LCE tile: full-width rows on maps up to 64 columns, else 4 rows x 32 columns.
-int tile_cols(const Dims &D) { return D.W <= 64 ? D.W : 32; }
-int tile_rows(const Dims &D) { return D.W <= 64 ? 64 / D.W : 4; }
-
 int halo_rows_small(const Dims &D) { return (D.rh + 4) * (D.rw + 4); }
 
 template <int C>
@@ -748,8 +655,6 @@ static bool one_kernel(const Dims &D)
     if (D.n != 16) return false;
     return D.rh * ((D.rw + 3) / 4) * (D.C / 2) <= 256 * kMaxLceTasks;
 }
-
-static size_t lce_add_smem(const Dims &D) { return (size_t)(tile_rows(D) + 4) * (tile_cols(D) + 4) * kLcePitch * 2; }
 
 static size_t map_smem(const Dims &D, bool lce = false)
 {
@@ -786,12 +691,10 @@ bool small_supported(const Dims &D)
         smem = D.C == 64 ? small_smem<64>(D) : D.C == 128 ? small_smem<128>(D) : small_smem<256>(D);
     } else {
         if (D.W > 64) return false;
-        smem = lce_add_smem(D);
-        const size_t attn = map_attention(D) ? map_smem(D)
-                            : D.C == 64      ? SmallSmem<64>::kv_bytes
-                            : D.C == 128     ? SmallSmem<128>::kv_bytes
-                                             : SmallSmem<256>::kv_bytes;
-        if (attn > smem) smem = attn;
+        smem = map_attention(D) ? map_smem(D)
+               : D.C == 64      ? SmallSmem<64>::kv_bytes
+               : D.C == 128     ? SmallSmem<128>::kv_bytes
+                                : SmallSmem<256>::kv_bytes;
     }
     return smem <= (size_t)kMaxLds;
 }
@@ -837,23 +740,6 @@ static int launch_map(const Dims &D, AttnArgs A, bf16_t *O, int log2n, hipStream
     return BRA_OK;
 }
 
-// O += LCE(V) in place.
-static int launch_lce_add(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st, int ldo = 0,
-                          bool square_tiles = false)
-{
-    static bool opted = false;
-    if (!opt_in(k_lce_add, opted)) return BRA_ERR_LAUNCH;
-    // square_tiles: 4 rows x up to 32 columns, fewer halo rows per token than full-width rows
-    const int TH = square_tiles ? 4 : tile_rows(D), TW = square_tiles ? std::min(D.W, 32) : tile_cols(D);
-    const long blocks = (long)D.B * ((D.H + TH - 1) / TH) * ((D.W + TW - 1) / TW) * (D.C / kLceChunk);
-    if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    const size_t smem = (size_t)(TH + 4) * (TW + 4) * kLcePitch * 2;
-    ProfScope ps(st, K_MFMA_LCE_ADD);
-    hipLaunchKernelGGL(k_lce_add, dim3((unsigned)blocks), dim3(256), smem, st, O, A.V, A.Wlce, D, TH, TW,
-                       ldo ? ldo : D.C);
-    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
-}
-
 template <int C>
 static int launch_small_c(const Dims &D, const AttnArgs &A0, bf16_t *O, hipStream_t st)
 {
@@ -878,7 +764,7 @@ static int launch_small_c(const Dims &D, const AttnArgs &A0, bf16_t *O, hipStrea
         ProfScope ps(st, K_MFMA_ATTN_SMALL);
         hipLaunchKernelGGL(k_attn_small<C>, dim3(grid), dim3(256), SmallSmem<C>::kv_bytes, st, A, O, D, log2n);
     }
-    return launch_lce_add(D, A, O, st);
+    return lce::lce_add_bf16(D, A.V, A.Wlce, O, D.C, K_MFMA_LCE_ADD, st);
 }
 
 // Any C that is a multiple of 64: regions of fewer than 16 tokens on a map that fits the
@@ -887,13 +773,7 @@ bool map_tail_supported(const Dims &D)
 {
     if (D.C % 64 != 0 || D.d != 32) return false;
     if (D.n > 8 || (D.n & (D.n - 1)) != 0 || D.W > 64) return false;
-    return map_attention(D) && lce_add_smem(D) <= (size_t)kMaxLds;
-}
-
-// O += LCE(V) in place for any map (C a multiple of 64).
-int launch_lce_add_any(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st, int ldo, bool square_tiles)
-{
-    return launch_lce_add(D, A, O, st, ldo, square_tiles);
+    return map_attention(D);
 }
 
 int launch_map_tail(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
@@ -902,7 +782,7 @@ int launch_map_tail(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
     while ((1 << log2n) < D.n) ++log2n;
     const int rc = launch_map(D, A, O, log2n, st);
     if (rc != BRA_OK || map_adds_lce(D)) return rc;
-    return launch_lce_add(D, A, O, st);
+    return lce::lce_add_bf16(D, A.V, A.Wlce, O, D.C, K_MFMA_LCE_ADD, st);
 }
 
 int launch_small(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)

@@ -12,7 +12,7 @@
 //   image-resident attention (small maps, regions of up to 8 tokens; bra_mfma_small.hip) or
 //   k_attn_gen (everything else), then LCE added in place                       (Eq. 6, 7)
 //   k_gemm<false> Y = O Wo (Eq. 2)
-#include "bra_mfma_dev.h"
+#include "bra_lce_dev.h"
 
 #include <stdlib.h>
 
@@ -255,16 +255,20 @@ __global__ __launch_bounds__(256) void k_route_qk(const float *__restrict__ Qr, 
             const int r = min(idx / 16, D.R - 1);        // regions past R repeat the last; never used
             const bool in = c0 + (idx % 16) * 4 < D.C;
             kv[u] = *(const f32x4 *)(Kr + img + (size_t)r * ld + (in ? c0 + (idx % 16) * 4 : 0));
-            if (!in) kv[u] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
         const int r = min(QR * myrt + (tid / 16) % QR, D.R - 1);
         const bool in = c0 + (tid % 16) * 4 < D.C;
         qv = *(const f32x4 *)(Qr + img + (size_t)r * ld + (in ? c0 + (tid % 16) * 4 : 0));
-        if (!in) qv = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     request(0);
     for (int c0 = 0; c0 < D.C; c0 += 64) {
         if (c0) __syncthreads();
+        if (c0 + 64 > D.C) {              // blanked here, not behind the loads: the prefetch stays in flight
+            const bool in = c0 + (tid % 16) * 4 < D.C;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) kv[u] = in ? kv[u] : f32x4{0.f, 0.f, 0.f, 0.f};
+            qv = in ? qv : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int idx = tid + 256 * u;
@@ -627,7 +631,7 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
             if (D.d == 32) hipLaunchKernelGGL(k_attn_gen<32>, dim3(grid), dim3(256), 0, st, A, w.o, D);
             else hipLaunchKernelGGL(k_attn_gen<64>, dim3(grid), dim3(256), 0, st, A, w.o, D);
         }
-        rc = launch_lce_add_any(D, A, w.o, st);
+        rc = lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);
     }
     if (rc != BRA_OK) return rc;
     return launch_gemm<false>(w.o, (const bf16_t *)Wo, D.C, M, D.C, D.C, GemmOut{{Y, nullptr, nullptr}, D.C, {nullptr, nullptr}}, K_MFMA_WO, st);

@@ -1,0 +1,28 @@
+"""GPU parity of the depth-wise kernels on bf16 maps (general pipeline forward, backward) at the edges of their
+tiling: one and two columns, odd widths, fewer column pairs than a workgroup's slots (strips above each other), strip
+heights 5, 10 and 20 with ragged ends, several tiles per workgroup."""
+import pytest
+
+from synthetic_inputs import make_inputs
+from test_gpu_backward import compare_backward
+from test_gpu_parity import compare
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [  # (B, H, W, C, heads, S, k)
+    (1, 9, 1, 192, 6, 1, 1),
+    (2, 23, 2, 64, 1, 1, 1),
+    (1, 22, 5, 128, 2, 1, 1),
+    (3, 6, 21, 192, 3, 3, 4),
+    (1, 41, 17, 64, 1, 1, 1),
+    (40, 20, 36, 64, 1, 2, 1),
+]
+
+
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", EDGES)
+def test_lce_edges(B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=8000 + H * W + C, dtype="bf16")
+    compare(X, Wqkv, Wo, Wlce, "bf16", S, k, heads, "mfma", images=[0, B - 1])
+    compare_backward(X[:2], Wqkv, Wo, Wlce, "bf16", heads, S, k, path="mfma")
+    if B > 2:
+        compare_backward(X, Wqkv, Wo, Wlce, "bf16", heads, S, k, path="mfma")
