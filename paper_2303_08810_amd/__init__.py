@@ -1,8 +1,10 @@
 """Thin Python binding of libbra (BRA forward on MI355X): argument marshalling only.
 
 Every step of the path runs in the HIP kernels behind the C ABI declared in
-include/bra.h.  torch is used for device memory and the current stream.  There is
-no CPU fallback: if libbra.so has not been built, importing the entry points fails.
+include/bra.h.  torch is used for device memory and the current stream.  The entry points
+check and marshal their arguments in a CPython extension (csrc/bra_python.cpp, _native.so); the
+host-only queries and measurement aids go through ctypes.  There is no CPU fallback: if libbra.so
+or the extension has not been built, the entry points raise.
 """
 from __future__ import annotations
 
@@ -13,6 +15,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libbra.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 BRA_F32, BRA_BF16 = 0, 1
 PATH_AUTO, PATH_GENERIC, PATH_MFMA = 0, 1, 2
@@ -138,107 +141,55 @@ def _stream(device) -> ctypes.c_void_p:
     return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
 
 
-def _check_inputs(X, Wqkv, Wo=None, Wlce=None):
-    B, H, W, C = X.shape
-    for t in (X, Wqkv, Wo, Wlce):
-        if t is None:
-            continue
-        if not (t.is_cuda and t.is_contiguous() and t.dtype == X.dtype and t.device == X.device):
-            raise ValueError("tensors must be contiguous, on one GPU and of one dtype")
-    if tuple(Wqkv.shape) != (C, 3 * C):
-        raise ValueError("Wqkv must be [C, 3C]")
-    if Wo is not None and tuple(Wo.shape) != (C, C):
-        raise ValueError("Wo must be [C, C]")
-    if Wlce is not None and tuple(Wlce.shape) != (C, 5, 5):
-        raise ValueError("Wlce must be [C, 5, 5]")
-    return B, H, W, C
+_native_module = None
+
+
+def _load_native():
+    """The CPython extension (built by paper_2303_08810_amd/build.py) that checks and marshals the
+    arguments of the entry points below; raises if absent."""
+    global _native_module
+    if _native_module is None:
+        try:
+            from . import _native as module
+        except ImportError as e:
+            raise ImportError(f"{NATIVE_PATH} cannot be loaded ({e}): run `python -m paper_2303_08810_amd.build` "
+                              "(or __graft_entry__.build()) first; there is no fallback path") from e
+        module.init(BraError)
+        _native_module = module
+    return _native_module
 
 
 def bra_route(X, Wqkv, S, k, heads, *, want_Ar=False, path="auto", ws=None):
     """Routing index I^r [B, S*S, k] (int32) and, optionally, A^r [B, S*S, S*S] (float32)."""
-    B, H, W, C = _check_inputs(X, Wqkv)
-    shape = make_shape(B, H, W, C, heads, S, k, X.dtype, None, path)
-    if ws is None:
-        ws = alloc_workspace(shape, X.device)
-    Ir = torch.empty((B, S * S, k), dtype=torch.int32, device=X.device)
-    Ar = torch.empty((B, S * S, S * S), dtype=torch.float32, device=X.device) if want_Ar else None
-    _check(lib().bra_route(ctypes.byref(shape), _ptr(X), _ptr(Wqkv), _ptr(Ir), _ptr(Ar), _ptr(ws),
-                           ws.numel(), _stream(X.device)))
-    return (Ir, Ar) if want_Ar else Ir
+    return (_native_module or _load_native()).route(X, Wqkv, S, k, heads, want_Ar, _PATHS[path], ws)
 
 
 def bra_forward(X, Wqkv, Wo, Wlce, S, k, heads, *, scale=None, Ir_in=None, want_Ir=False,
                 path="auto", ws=None, out=None):
     """Y [B, H, W, C] = BRA(X); optionally also the routing index that was used."""
-    B, H, W, C = _check_inputs(X, Wqkv, Wo, Wlce)
-    shape = make_shape(B, H, W, C, heads, S, k, X.dtype, scale, path)
-    if ws is None:
-        ws = alloc_workspace(shape, X.device)
-    Y = out if out is not None else torch.empty_like(X)
-    Ir = torch.empty((B, S * S, k), dtype=torch.int32, device=X.device) if want_Ir else None
-    if Ir_in is not None:
-        if not (Ir_in.is_cuda and Ir_in.is_contiguous() and Ir_in.dtype == torch.int32
-                and tuple(Ir_in.shape) == (B, S * S, k)):
-            raise ValueError("Ir_in must be a contiguous int32 [B, S*S, k] device tensor")
-    _check(lib().bra_forward(ctypes.byref(shape), _ptr(X), _ptr(Wqkv), _ptr(Wo), _ptr(Wlce), _ptr(Y),
-                             _ptr(Ir), _ptr(Ir_in), _ptr(ws), ws.numel(), _stream(X.device)))
-    return (Y, Ir) if want_Ir else Y
+    return (_native_module or _load_native()).forward(X, Wqkv, Wo, Wlce, S, k, heads, scale, Ir_in, want_Ir, _PATHS[path],
+                                                 ws, out)
 
 
 def bra_forward_static(X, Wqkv, Wo, Wlce, S, k, heads, *, out, Ir_out=None, Ir_in=None, scale=None, path="auto"):
     """bra_forward on the library's built-in scratch buffer: nothing is allocated, here or in the
     library.  `out` [B, H, W, C] and, if wanted, `Ir_out` [B, S*S, k] (int32) are the caller's."""
-    B, H, W, C = _check_inputs(X, Wqkv, Wo, Wlce)
-    shape = make_shape(B, H, W, C, heads, S, k, X.dtype, scale, path)
-    for t, shp, dt in ((out, (B, H, W, C), X.dtype), (Ir_out, (B, S * S, k), torch.int32), (Ir_in, (B, S * S, k), torch.int32)):
-        if t is not None and not (t.is_cuda and t.is_contiguous() and t.dtype == dt and tuple(t.shape) == shp):
-            raise ValueError(f"expected a contiguous {dt} device tensor of shape {shp}")
-    _check(lib().bra_forward_static(ctypes.byref(shape), _ptr(X), _ptr(Wqkv), _ptr(Wo), _ptr(Wlce), _ptr(out),
-                                    _ptr(Ir_out), _ptr(Ir_in), _stream(X.device)))
-    return out
+    return (_native_module or _load_native()).forward_static(X, Wqkv, Wo, Wlce, S, k, heads, out, Ir_out, Ir_in, scale,
+                                                        _PATHS[path])
 
 
 def bra_forward_padded(X, Wqkv, Wo, Wlce, S, k, heads, *, scale=None, Ir_in=None, want_Ir=False, path="auto"):
     """BRA on a map whose sides S need not divide: zero tokens are appended at the bottom and right,
     Y is the top-left H x W part of the result (see include/bra.h)."""
-    B, H, W, C = _check_inputs(X, Wqkv, Wo, Wlce)
-    shape = make_shape(B, H, W, C, heads, S, k, X.dtype, scale, path)
-    need = ctypes.c_size_t(0)
-    _check(lib().bra_padded_workspace_bytes(ctypes.byref(shape), ctypes.byref(need)))
-    ws = torch.empty(max(need.value, 256), dtype=torch.uint8, device=X.device)
-    Y = torch.empty_like(X)
-    Ir = torch.empty((B, S * S, k), dtype=torch.int32, device=X.device) if want_Ir else None
-    if Ir_in is not None:
-        if not (Ir_in.is_cuda and Ir_in.is_contiguous() and Ir_in.dtype == torch.int32
-                and tuple(Ir_in.shape) == (B, S * S, k)):
-            raise ValueError("Ir_in must be a contiguous int32 [B, S*S, k] device tensor")
-    _check(lib().bra_forward_padded(ctypes.byref(shape), _ptr(X), _ptr(Wqkv), _ptr(Wo), _ptr(Wlce), _ptr(Y),
-                                    _ptr(Ir), _ptr(Ir_in), _ptr(ws), ws.numel(), _stream(X.device)))
-    return (Y, Ir) if want_Ir else Y
+    return (_native_module or _load_native()).forward_padded(X, Wqkv, Wo, Wlce, S, k, heads, scale, Ir_in, want_Ir,
+                                                        _PATHS[path])
 
 
 def bra_backward(X, Wqkv, Wo, Wlce, Ir, dY, S, heads, *, scale=None, path="auto", ws=None):
     """Gradients of the layer for fixed routing Ir [B, S*S, k] (see include/bra.h): returns
     (dX in X's dtype, dWqkv, dWo, dWlce in float32).  path: "auto", "generic" (float32
     kernels) or "mfma" (matrix-core kernels; raises if the shape is outside their range)."""
-    B, H, W, C = _check_inputs(X, Wqkv, Wo, Wlce)
-    k = int(Ir.shape[-1])
-    if not (Ir.is_cuda and Ir.is_contiguous() and Ir.dtype == torch.int32 and tuple(Ir.shape) == (B, S * S, k)):
-        raise ValueError("Ir must be a contiguous int32 [B, S*S, k] device tensor")
-    if not (dY.is_cuda and dY.is_contiguous() and dY.dtype == X.dtype and dY.shape == X.shape):
-        raise ValueError("dY must match X")
-    shape = make_shape(B, H, W, C, heads, S, k, X.dtype, scale, path)
-    if ws is None:
-        need = ctypes.c_size_t(0)
-        _check(lib().bra_backward_workspace_bytes(ctypes.byref(shape), ctypes.byref(need)))
-        ws = torch.empty(max(need.value, 256), dtype=torch.uint8, device=X.device)
-    dX = torch.empty_like(X)
-    dWqkv = torch.empty((C, 3 * C), dtype=torch.float32, device=X.device)
-    dWo = torch.empty((C, C), dtype=torch.float32, device=X.device)
-    dWlce = torch.empty((C, 5, 5), dtype=torch.float32, device=X.device)
-    _check(lib().bra_backward(ctypes.byref(shape), _ptr(X), _ptr(Wqkv), _ptr(Wo), _ptr(Wlce), _ptr(Ir), _ptr(dY),
-                              _ptr(dX), _ptr(dWqkv), _ptr(dWo), _ptr(dWlce), _ptr(ws), ws.numel(), _stream(X.device)))
-    return dX, dWqkv, dWo, dWlce
+    return (_native_module or _load_native()).backward(X, Wqkv, Wo, Wlce, Ir, dY, S, heads, scale, _PATHS[path], ws)
 
 
 def block_workspace_bytes(shape: BraShape, hidden: int) -> int:
@@ -252,33 +203,8 @@ def bra_block_forward(X, params, S, k, heads, *, eps=1e-6, scale=None, Ir_in=Non
     """One whole BiFormer block (position encoding, LayerNorm, BRA, LayerNorm, MLP with residual
     links; see include/bra.h).  `params`: dict of device tensors named as BraBlockParams.FIELDS;
     the matrices in X's dtype, the vectors float32."""
-    B, H, W, C = X.shape
-    hidden = int(params["W1"].shape[1])
-    want = {"Wpos": (C, 3, 3), "bpos": (C,), "ln1_g": (C,), "ln1_b": (C,), "Wqkv": (C, 3 * C), "Wo": (C, C),
-            "Wlce": (C, 5, 5), "ln2_g": (C,), "ln2_b": (C,), "W1": (C, hidden), "b1": (hidden,),
-            "W2": (hidden, C), "b2": (C,)}
-    if not (X.is_cuda and X.is_contiguous()):
-        raise ValueError("X must be a contiguous device tensor")
-    for name in BraBlockParams.FIELDS:
-        t = params[name]
-        dt = X.dtype if name in BraBlockParams.MATRICES else torch.float32
-        if not (t.is_cuda and t.is_contiguous() and t.device == X.device and t.dtype == dt
-                and tuple(t.shape) == want[name]):
-            raise ValueError(f"{name} must be a contiguous {dt} device tensor of shape {want[name]}")
-    shape = make_shape(B, H, W, C, heads, S, k, X.dtype, scale, path)
-    if ws is None:
-        ws = torch.empty(max(block_workspace_bytes(shape, hidden), 256), dtype=torch.uint8, device=X.device)
-        assert ws.data_ptr() % 256 == 0
-    Xout = out if out is not None else torch.empty_like(X)
-    Ir = torch.empty((B, S * S, k), dtype=torch.int32, device=X.device) if want_Ir else None
-    if Ir_in is not None:
-        if not (Ir_in.is_cuda and Ir_in.is_contiguous() and Ir_in.dtype == torch.int32
-                and tuple(Ir_in.shape) == (B, S * S, k)):
-            raise ValueError("Ir_in must be a contiguous int32 [B, S*S, k] device tensor")
-    P = BraBlockParams(*[params[name].data_ptr() for name in BraBlockParams.FIELDS])
-    _check(lib().bra_block_forward(ctypes.byref(shape), hidden, float(eps), _ptr(X), ctypes.byref(P), _ptr(Xout),
-                                   _ptr(Ir), _ptr(Ir_in), _ptr(ws), ws.numel(), _stream(X.device)))
-    return (Xout, Ir) if want_Ir else Xout
+    return (_native_module or _load_native()).block_forward(X, tuple(map(params.__getitem__, BraBlockParams.FIELDS)), S, k,
+                                                       heads, eps, scale, Ir_in, want_Ir, _PATHS[path], ws, out)
 
 
 def profile_begin(max_records: int) -> None:

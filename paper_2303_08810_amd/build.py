@@ -1,5 +1,5 @@
 """Builds libbra.so (HIP, gfx950 only) in-tree with hipcc: one compile per source file, in
-parallel, then one link."""
+parallel, then one link; and _native.so, the CPython extension of the binding (host code, g++)."""
 from __future__ import annotations
 
 import glob
@@ -10,6 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbra.so")
+NATIVE = os.path.join(HERE, "_native.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 HIPCC_FLAGS = [
@@ -44,6 +45,25 @@ def compile_objects(tag="product", defines=(), extra_flags=(), opt="-O3", verbos
         return list(pool.map(compile_one, sources()))
 
 
+def build_native(verbose: bool = False) -> str:
+    """Compiles csrc/bra_python.cpp against the installed torch and links it to libbra.so beside it."""
+    import sysconfig
+
+    import torch
+    troot = os.path.dirname(torch.__file__)
+    includes = [os.path.join(troot, "include"), os.path.join(troot, "include", "torch", "csrc", "api", "include"),
+                sysconfig.get_paths()["include"], "/opt/rocm/include"]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    cmd += [f"-I{d}" for d in includes] + [os.path.join(CSRC, "bra_python.cpp"), "-o", NATIVE, f"-L{HERE}", "-l:libbra.so",
+            f"-L{os.path.join(troot, 'lib')}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch", "-ltorch_python",
+            "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return NATIVE
+
+
 def build(verbose: bool = False, out: str = LIB, defines=(), jobs: int | None = None) -> str:
     """Always recompiles.  `defines`: extra -D names (BRA_EXPERIMENT makes the A/B switches of
     the kernels readable from the environment; the shipped library is built without it)."""
@@ -53,6 +73,8 @@ def build(verbose: bool = False, out: str = LIB, defines=(), jobs: int | None = 
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True, cwd=CSRC)
+    if out == LIB:
+        build_native(verbose)
     return out
 
 
