@@ -117,14 +117,11 @@ int f32_small_forward(const Dims &D, const float *X, const float *Wqkv, const fl
 int f32_small_route(const Dims &D, const float *X, const float *Wqkv, int32_t *Ir, float *Ar_opt, float *qkv,
                     float *pq, float *pk, hipStream_t st);
 
-// The same for at most 64 regions and C a multiple of 4 (bra_mfma_wide.hip); Q^r, K^r with row pitch ld.
+// Rows of A^r = Q^r (K^r)^T and their top-k from float32 Q^r, K^r [B, R, C] with row pitch ld (bra_route.hip; up to
+// 1024 regions).
 int route_rows(const Dims &D, const float *Qr, const float *Kr, int ld, int32_t *Ir, float *Ar_opt, hipStream_t st);
 
 size_t valu_route_scratch_bytes(const Dims &D);
-// Rows of A^r = Q^r (K^r)^T and their top-k from float32 Q^r, K^r [B, R, C] (any region count
-// that generic_supported accepts).
-int valu_affinity_topk(const Dims &D, const float *Qr, const float *Kr, int32_t *Ir, float *Ar_opt,
-                       hipStream_t st);
 int valu_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt,
                void *scratch, hipStream_t st);
 

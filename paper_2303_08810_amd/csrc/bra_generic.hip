@@ -5,7 +5,7 @@
 // workspace, whatever the storage type of X and Y.  The steps follow Sec. 3.2:
 // projection (Eq. 3), region pooling + affinity (Eq. 4), top-k (Eq. 5), routed
 // attention straight from the index (Eq. 6-7, no gathered tensor), LCE, W^o (Eq. 2).
-// Products run on the float32 matrix-core instruction (bra_f32_dev.h); routing rows, heads wider
+// Products run on the float32 matrix-core instruction (bra_f32_dev.h, bra_route.hip); heads wider
 // than 64 channels and the block's LayerNorms are scalar kernels.
 // Region pooling uses mean(X^r) W = mean(X^r W), which is exact in real arithmetic
 // (the mean is linear; same argument as Appendix A).
@@ -19,58 +19,9 @@ namespace bra {
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kTopkSlots = 16;      // affinity values per lane: R <= 64 * 16
+constexpr int kMaxRegions = 1024;   // what route_rows takes
 constexpr int kAttnChunk = 1024;    // keys per online-softmax chunk
 constexpr int kAttnMaxD = 256;      // head width limit of the generic attention kernel
-
-// One wavefront per (b, i): row i of A^r = Q^r (K^r)^T (Eq. 4), then k rounds of a
-// wave-wide arg-max (Eq. 5).  Order: larger value first, equal values by smaller
-// index; NaN counts as -inf so that the k indices are always distinct and valid.
-__global__ __launch_bounds__(kWave) void gen_affinity_topk(const float *__restrict__ Qr,
-                                                           const float *__restrict__ Kr, int ld,
-                                                           int32_t *__restrict__ Ir,
-                                                           float *__restrict__ Ar_opt, Dims D)
-{
-    extern __shared__ float qs[];
-    const int b = blockIdx.x / D.R, i = blockIdx.x % D.R;
-    const int lane = threadIdx.x;
-    for (int c = lane; c < D.C; c += kWave) qs[c] = Qr[((size_t)b * D.R + i) * ld + c];
-    __syncthreads();
-    float vals[kTopkSlots];
-#pragma unroll
-    for (int t = 0; t < kTopkSlots; ++t) {
-        const int j = lane + t * kWave;
-        float a = -INFINITY;
-        if (j < D.R) {
-            const float *kr = Kr + ((size_t)b * D.R + j) * ld;
-            a = 0.f;
-            for (int c = 0; c < D.C; ++c) a = fmaf(qs[c], kr[c], a);
-            if (Ar_opt) Ar_opt[((size_t)b * D.R + i) * D.R + j] = a;
-            if (!(a == a)) a = -INFINITY;
-        }
-        vals[t] = a;
-    }
-    unsigned taken = 0;  // bit t: slot t of this lane already selected
-    for (int p = 0; p < D.k; ++p) {
-        float bv = -INFINITY;
-        int bi = 0x7fffffff;
-#pragma unroll
-        for (int t = 0; t < kTopkSlots; ++t) {
-            const int j = lane + t * kWave;
-            if (j < D.R && !((taken >> t) & 1u)) {
-                if (bi == 0x7fffffff || vals[t] > bv) { bv = vals[t]; bi = j; }
-            }
-        }
-        for (int off = 32; off >= 1; off >>= 1) {
-            float ov = __shfl_xor(bv, off, kWave);
-            int oi = __shfl_xor(bi, off, kWave);
-            bool take = (oi != 0x7fffffff) && (bi == 0x7fffffff || ov > bv || (ov == bv && oi < bi));
-            if (take) { bv = ov; bi = oi; }
-        }
-        if (bi % kWave == lane) taken |= 1u << (bi / kWave);
-        if (lane == 0) Ir[((size_t)b * D.R + i) * D.k + p] = bi;
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Routed attention for wider heads, one workgroup (4 wavefronts) per (b, region i, head).  Each
@@ -237,14 +188,6 @@ f32::GemmJob<float, T, float> region_job(const Dims &D, const T *Wqkv, const Gen
     return {w.xr, Wqkv, w.qk, (long)D.B * D.R, D.C, 3 * D.C, 2 * D.C, 2 * D.C, D.C, nullptr, nullptr, 0};
 }
 
-int launch_topk(const Dims &D, const float *Qr, const float *Kr, int ld, int32_t *Ir, float *Ar_opt, hipStream_t st)
-{
-    if (D.R <= kWave && D.C % 4 == 0) return route_rows(D, Qr, Kr, ld, Ir, Ar_opt, st);
-    ProfScope ps(st, K_GEN_TOPK);
-    hipLaunchKernelGGL(gen_affinity_topk, dim3(D.B * D.R), dim3(kWave), D.C * sizeof(float), st, Qr, Kr, ld, Ir, Ar_opt, D);
-    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
-}
-
 // Routing on its own: region means, their projection, rows of A^r and top-k.  The arithmetic of every entry is that
 // of forward_t, so both give the same index.
 template <typename T>
@@ -256,7 +199,7 @@ int launch_route(const Dims &D, const T *X, const T *Wqkv, int32_t *Ir, float *A
         const int rc = launch_gemm<false>(region_job<T>(D, Wqkv, w), (const f32::GemmJob<float, T, float> *)nullptr, st);
         if (rc != BRA_OK) return rc;
     }
-    return launch_topk(D, w.qk, w.qk + D.C, 2 * D.C, Ir, Ar_opt, st);
+    return route_rows(D, w.qk, w.qk + D.C, 2 * D.C, Ir, Ar_opt, st);
 }
 
 template <int DP, int HPW, bool VEC>
@@ -319,7 +262,7 @@ int forward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *Wl
             rc = launch_gemm<false>(qkv_job, &rj, st);
         }
         if (rc != BRA_OK) return rc;
-        rc = launch_topk(D, w.qk, w.qk + C, 2 * C, dst, nullptr, st);
+        rc = route_rows(D, w.qk, w.qk + C, 2 * C, dst, nullptr, st);
         if (rc != BRA_OK) return rc;
         Ir = dst;
     } else {
@@ -613,7 +556,7 @@ bool generic_supported(const Dims &D)
     // grid sizes must fit 31 bits; head width and region count are bounded by the
     // static buffers of the attention and top-k kernels.
     if (D.d > kAttnMaxD) return false;
-    if (D.R > kWave * kTopkSlots) return false;
+    if (D.R > kMaxRegions) return false;
     if ((long)D.B * D.R * D.heads > 0x7fffffffL) return false;
     if (((long)D.B * D.N * D.C + 255) / 256 > 0x7fffffffL) return false;
     if ((size_t)D.k * sizeof(int) > 16 * 1024) return false;
@@ -654,12 +597,6 @@ namespace bra {
 size_t valu_route_scratch_bytes(const Dims &D)
 {
     return 3 * align256((size_t)D.B * D.R * D.C * sizeof(float));
-}
-
-int valu_affinity_topk(const Dims &D, const float *Qr, const float *Kr, int32_t *Ir, float *Ar_opt,
-                       hipStream_t st)
-{
-    return launch_topk(D, Qr, Kr, D.C, Ir, Ar_opt, st);
 }
 
 int valu_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt,

@@ -7,7 +7,7 @@
 //   k_pool_wide   Xr[b, r, :] = mean of the region's tokens, float32            (Sec. 3.2)
 //   k_gemm<true>  Q^r | K^r = Xr [Wq | Wk] in float32: the means are split exactly into three
 //                 bf16 terms, so the products are those of the float32 computation
-//   k_route_qk    rows of A^r = Q^r (K^r)^T (Eq. 4) and their top-k (Eq. 5)
+//   k_route_rows  rows of A^r = Q^r (K^r)^T (Eq. 4) and their top-k (Eq. 5)
 //   k_gemm<false> Q | K | V = X Wqkv (Eq. 3), bf16 out
 //   image-resident attention (small maps, regions of up to 8 tokens; bra_mfma_small.hip) or
 //   k_attn_gen (everything else), then LCE added in place                       (Eq. 6, 7)
@@ -226,81 +226,6 @@ constexpr size_t gemm_smem(bool split, int cw = 4)
 }
 
 // ---------------------------------------------------------------------------
-// Rows of A^r = Q^r (K^r)^T (Eq. 4) in float32 and their top-k (Eq. 5) for workgroup
-// (image, 4 NR query regions), R <= 64: the channels pass through LDS 64 at a time (K^r of all
-// regions as [16][kQkRS][4]: channel group, region, channel; Q^r of the workgroup's rows),
-// wavefront w accumulates rows NR w .. NR w + NR - 1 with lane j holding entry j.  Q^r, K^r have row
-// pitch ld; C is a multiple of 4 (a last chunk's missing channels read as zero).
-constexpr int kQkRS = 65;
-
-template <int NR>
-__global__ __launch_bounds__(256) void k_route_qk(const float *__restrict__ Qr, const float *__restrict__ Kr, int ld,
-                                                  int32_t *__restrict__ Ir, float *__restrict__ Ar, Dims D)
-{
-    __shared__ __attribute__((aligned(16))) float Kt[16 * kQkRS * 4];
-    __shared__ __attribute__((aligned(16))) float Qs[16 * 68];
-    constexpr int QR = 4 * NR;
-    const int groups = (D.R + QR - 1) / QR;
-    const int b = blockIdx.x / groups, myrt = blockIdx.x % groups;
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const size_t img = (size_t)b * D.R * ld;
-    float a[NR];
-#pragma unroll
-    for (int rr = 0; rr < NR; ++rr) a[rr] = 0.f;
-    f32x4 kv[4], qv;
-    auto request = [&](int c0) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int idx = tid + 256 * u;               // (region, 4-channel group)
-            const int r = min(idx / 16, D.R - 1);        // regions past R repeat the last; never used
-            const bool in = c0 + (idx % 16) * 4 < D.C;
-            kv[u] = *(const f32x4 *)(Kr + img + (size_t)r * ld + (in ? c0 + (idx % 16) * 4 : 0));
-        }
-        const int r = min(QR * myrt + (tid / 16) % QR, D.R - 1);
-        const bool in = c0 + (tid % 16) * 4 < D.C;
-        qv = *(const f32x4 *)(Qr + img + (size_t)r * ld + (in ? c0 + (tid % 16) * 4 : 0));
-    };
-    request(0);
-    for (int c0 = 0; c0 < D.C; c0 += 64) {
-        if (c0) __syncthreads();
-        if (c0 + 64 > D.C) {              // blanked here, not behind the loads: the prefetch stays in flight
-            const bool in = c0 + (tid % 16) * 4 < D.C;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) kv[u] = in ? kv[u] : f32x4{0.f, 0.f, 0.f, 0.f};
-            qv = in ? qv : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int idx = tid + 256 * u;
-            *(f32x4 *)(Kt + ((idx % 16) * kQkRS + idx / 16) * 4) = kv[u];
-        }
-        if (tid / 16 < QR) *(f32x4 *)(Qs + (tid / 16) * 68 + (tid % 16) * 4) = qv;
-        __syncthreads();
-        if (c0 + 64 < D.C) request(c0 + 64);      // the next chunk travels while this one is multiplied
-#pragma unroll 4
-        for (int c4 = 0; c4 < 16; ++c4) {
-            const f32x4 k4 = *(const f32x4 *)(Kt + (c4 * kQkRS + lane) * 4);
-#pragma unroll
-            for (int rr = 0; rr < NR; ++rr) {
-                const f32x4 q4 = *(const f32x4 *)(Qs + (NR * wave + rr) * 68 + 4 * c4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) a[rr] = fmaf(q4[e], k4[e], a[rr]);
-            }
-        }
-    }
-    const int r0 = QR * myrt + NR * wave;
-    if (r0 >= D.R) return;
-    const int nrows = min(NR, D.R - r0);
-    const size_t row0 = (size_t)b * D.R + r0;
-    if (Ar && lane < D.R) {
-#pragma unroll
-        for (int rr = 0; rr < NR; ++rr)
-            if (rr < nrows) Ar[(row0 + rr) * D.R + lane] = a[rr];
-    }
-    wave_topk_rows<NR>(a, nrows, lane, D.R, D.k, Ir + row0 * D.k);
-}
-
-// ---------------------------------------------------------------------------
 // Routed attention (Eq. 6, Eq. 1) for any region size and heads of 32 or 64 channels:
 // workgroup (image, region, tile of 64 queries of the region, group of 64 channels = 2 or
 // 1 heads), wavefront w with queries 16 w .. 16 w + 15 of the tile.  The k n routed keys are
@@ -513,7 +438,6 @@ int launch_gemm(const void *In, const bf16_t *W, int ldw, long M, int K, int Nou
 // A^r rows and top-k from the float32 Q^r, K^r in the workspace.
 int affinity_steps(const Dims &D, const WideWs &w, int32_t *Ir, float *Ar_opt, hipStream_t st)
 {
-    if (many_regions(D)) return valu_affinity_topk(D, w.qr, w.kr, Ir, Ar_opt, st);   // more than one entry per lane
     return route_rows(D, w.qr, w.kr, D.C, Ir, Ar_opt, st);
 }
 
@@ -543,20 +467,6 @@ int route_steps(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideWs
 }
 
 }  // namespace
-
-int route_rows(const Dims &D, const float *Qr, const float *Kr, int ld, int32_t *Ir, float *Ar_opt, hipStream_t st)
-{
-    ProfScope ps(st, K_MFMA_ROUTE_ROWS);
-    // 16 query regions per workgroup when that already fills the chip, else 8 or 4
-    const long wgs16 = (long)D.B * ((D.R + 15) / 16);
-    if (wgs16 >= 1024)
-        hipLaunchKernelGGL(k_route_qk<4>, dim3((unsigned)wgs16), dim3(256), 0, st, Qr, Kr, ld, Ir, Ar_opt, D);
-    else if (2 * wgs16 >= 1024)
-        hipLaunchKernelGGL(k_route_qk<2>, dim3(D.B * ((D.R + 7) / 8)), dim3(256), 0, st, Qr, Kr, ld, Ir, Ar_opt, D);
-    else
-        hipLaunchKernelGGL(k_route_qk<1>, dim3(D.B * ((D.R + 3) / 4)), dim3(256), 0, st, Qr, Kr, ld, Ir, Ar_opt, D);
-    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
-}
 
 int gemm_bf16(const bf16_t *In, const bf16_t *W, long M, int K, int Nout, bf16_t *Out, const float *bias,
               const bf16_t *res, bool gelu, int kernel_id, hipStream_t st)

@@ -28,3 +28,20 @@ def test_f32_family_edges(B, H, W, C, heads, S, k, dtype):
     X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=7000 + H * W + C + k, dtype=dtype)
     compare(X, Wqkv, Wo, Wlce, dtype, S, k, heads, "generic")
     compare_backward(X, Wqkv, Wo, Wlce, dtype, heads, S, k, path="generic")
+
+
+ROUTES = [  # (B, H, W, C, heads, S, k): region counts around the row tile and the key groups, channel slices 1 .. 8
+    (1, 5, 5, 16, 1, 5, 25),         # 25 regions, one channel step
+    (2, 9, 9, 24, 1, 9, 40),         # 81 regions: two key groups, k beyond the small ranking
+    (1, 16, 16, 192, 6, 16, 3),      # 256 regions, eight slices
+    (1, 17, 17, 33, 1, 17, 5),       # 289 regions, scalar loads
+    (1, 32, 32, 32, 1, 32, 2),       # 1024 regions
+    (3, 8, 8, 320, 10, 8, 64),       # k = all of 64 regions
+    (1, 1, 1, 64, 2, 1, 1),          # one region
+]
+
+
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", ROUTES)
+def test_routing_rows_edges(B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=7500 + S + C, dtype="f32")
+    compare(X, Wqkv, Wo, Wlce, "f32", S, k, heads, "generic")
