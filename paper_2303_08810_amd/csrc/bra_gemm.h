@@ -1,0 +1,40 @@
+// bf16 products of the general pipelines (bra_gemm.hip; internal).
+#pragma once
+
+#include "bra_mfma_dev.h"
+
+namespace bra {
+
+// Where a product goes: output column o to buffer o / cols (up to three buffers of `cols` columns each, e.g. Q, K, V),
+// column o % cols; cols is a multiple of 8.
+struct GemmOut {
+    void *buf[3];
+    int cols;
+    float *f32[2];      // optional float32 copies of the results that go to buf[0] and buf[1] (bf16 output only)
+    // bf16 output only, all optional: bias[o] is added, then GELU is applied, then res[m][o]
+    // (the layout of buf[0]) is added.
+    const float *bias;
+    const bf16_t *res;
+    int gelu;
+};
+
+// A second product with the same W and K whose input is float32 and enters as three exact bf16 terms, with float32
+// results: the region-level projection Q^r | K^r = Xr [Wq | Wk] in the launch of the token projection.
+struct GemmRegions {
+    const float *In;
+    long M;
+    int Nout;
+    float *buf[2];
+    int cols;
+};
+
+// Out = In W: In [M, K] bf16, W row-major [K][ldw]; K a multiple of 64, Nout of 8.
+int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, const GemmRegions *regions,
+         int kernel_id, hipStream_t st);
+// The same with float32 results (two buffers at most).
+int gemm_f32out(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, float *out0, float *out1, int cols,
+                int kernel_id, hipStream_t st);
+// The region-level product on its own.
+int gemm_regions(const GemmRegions &r, const bf16_t *W, int ldw, int K, int kernel_id, hipStream_t st);
+
+}  // namespace bra

@@ -1,0 +1,394 @@
+// bf16 products of the general pipelines.
+#include "bra_gemm.h"
+
+namespace bra {
+
+using namespace mfma;
+
+namespace {
+
+// ---------------------------------------------------------------------------
+// Out[m][o] = sum_k In[m][k] W[k][o] (W row-major with ldw columns, as the caller holds it)
+// for a tile of 64 rows m x 32 CW outputs o (128 or 64), the contraction in chunks of 64
+// staged in LDS (the next chunk is requested while the current one is multiplied).
+// The four wavefronts split the tile 2 x 2 (32 rows x 16 CW outputs each); the product is formed
+// transposed (D[output 16 t + 4 g + jj][row i]) so that a lane stores 4 consecutive outputs of one row;
+// its W operand (rows = outputs) comes out of the row-major chunk by the transposing LDS read.
+// Output column o goes to buffer o / cols (three buffers of `cols` columns each, e.g. Q, K,
+// V), column o % cols.
+// SPLIT: In is float32 and enters as three exact bf16 terms (smallest first); otherwise In is
+// bf16.  Out is float32.
+constexpr int kGemmPitch = 80;      // bf16 per LDS row of In: 64 + 16 (rows of 160 bytes); W: the tile's width + 16
+constexpr int kGemmGroupW = 64;     // W: 128 bytes more after every 8 rows: the neighbouring lane group of a
+                                    // transposing read (8 rows further on) then meets the other half of the banks
+
+// Ws: [64 k][32 CW + 16] and 8 group paddings, Xs[q]: [64][P].
+template <bool SPLIT, int CW>
+__device__ __forceinline__ void gemm64(const void *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int M, int K,
+                                       int Nout, const GemmOut &out, int block, bf16_t *Ws, bf16_t *const (&Xs)[SPLIT ? 3 : 1])
+{
+    constexpr int P = kGemmPitch, NT = SPLIT ? 3 : 1, COLS = 32 * CW, PW = COLS + 16;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int otiles = (Nout + COLS - 1) / COLS;
+    const int m0 = (block / otiles) * 64, o0 = (block % otiles) * COLS;
+
+    // this thread's pieces of a chunk: 4 x 16 bytes of W, and 2 x 16 bytes of bf16 In or
+    // 2 x 8 floats of float32 In
+    u32x4 wreg[CW], xreg[SPLIT ? 4 : 2];
+    auto request = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < CW; ++u) {
+            const int idx = tid + 256 * u;                       // (row k, 8 outputs)
+            const int o = min(o0 + (idx % (COLS / 8)) * 8, Nout - 8);    // columns past the end repeat the last; never stored
+            wreg[u] = *(const u32x4 *)(W + (size_t)(k0 + idx / (COLS / 8)) * ldw + o);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int idx = tid + 256 * u;
+            const int m = min(m0 + idx / 8, M - 1);
+            if (SPLIT) {
+                const float *src = (const float *)In + (size_t)m * K + k0 + (idx % 8) * 8;
+                xreg[2 * u] = *(const u32x4 *)src;
+                xreg[2 * u + 1] = *(const u32x4 *)(src + 4);
+            } else {
+                xreg[u] = *(const u32x4 *)((const bf16_t *)In + (size_t)m * K + k0 + (idx % 8) * 8);
+            }
+        }
+    };
+    auto park = [&]() {
+#pragma unroll
+        for (int u = 0; u < CW; ++u) {
+            const int idx = tid + 256 * u;
+            const int row = idx / (COLS / 8);
+            *(u32x4 *)(Ws + row * PW + (row / 8) * kGemmGroupW + (idx % (COLS / 8)) * 8) = wreg[u];
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int idx = tid + 256 * u;
+            const int at = (idx / 8) * P + (idx % 8) * 8;
+            if (SPLIT) {
+                const f32x4 lo = __builtin_bit_cast(f32x4, xreg[2 * u]), hi = __builtin_bit_cast(f32x4, xreg[2 * u + 1]);
+                const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                bf16x8 t[3];
+                split3(x, t);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) *(bf16x8 *)(Xs[q] + at) = t[q];
+            } else {
+                *(u32x4 *)(Xs[0] + at) = xreg[u];
+            }
+        }
+    };
+
+    // wavefront (wr, wc) owns rows 32 wr .. 32 wr + 31 (two 16-row tiles) and outputs 64 wc ..
+    // 64 wc + 63 (four tiles) of the workgroup's 64 x 128: a W fragment serves two row tiles
+    const int wr = wave / 2, wc = wave % 2;
+    f32x4 acc[2][CW];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int t = 0; t < CW; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    request(0);
+    for (int k0 = 0; k0 < K; k0 += 64) {
+        if (k0) __syncthreads();          // the previous chunk has been read
+        park();
+        __syncthreads();
+        if (k0 + 64 < K) request(k0 + 64);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            bf16x8 xb[2][NT];
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                for (int q = 0; q < NT; ++q)
+                    xb[rt][q] = *(const bf16x8 *)(Xs[q] + (32 * wr + 16 * rt + i) * P + 32 * ks + 8 * g);
+#pragma unroll
+            for (int t = 0; t < CW; ++t) {
+                const bf16_t *wp = Ws + (32 * ks + 8 * g + i / 4) * PW + (4 * ks + g) * kGemmGroupW + 16 * CW * wc + 16 * t +
+                                   4 * (i % 4);
+                const u32x2 w0 = __builtin_bit_cast(u32x2, lds_read_tr16(wp));
+                const u32x2 w1 = __builtin_bit_cast(u32x2, lds_read_tr16(wp + 4 * PW));
+                const bf16x8 wf = __builtin_bit_cast(bf16x8, u32x4{w0[0], w0[1], w1[0], w1[1]});
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                    for (int q = NT - 1; q >= 0; --q) acc[rt][t] = mfma16(wf, xb[rt][q], acc[rt][t]);
+            }
+        }
+    }
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+        const int m = m0 + 32 * wr + 16 * rt + i;
+        if (m >= M) continue;
+#pragma unroll
+        for (int t = 0; t < CW; ++t) {
+            const int o = o0 + 16 * CW * wc + 16 * t + 4 * g;
+            if (o >= Nout) break;
+            const int which = o / out.cols, col = o % out.cols;
+            *(f32x4 *)((float *)out.buf[which] + (size_t)m * out.cols + col) = acc[rt][t];
+        }
+    }
+}
+
+// 64 x 32 CW tiles for the float32 inputs and results of the routing.
+template <bool SPLIT, int CW>
+__global__ __launch_bounds__(256) void k_gemm(const void *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int M,
+                                              int K, int Nout, GemmOut out)
+{
+    constexpr int NT = SPLIT ? 3 : 1;
+    __shared__ __attribute__((aligned(16))) bf16_t Ws[64 * (32 * CW + 16) + 8 * kGemmGroupW];
+    __shared__ __attribute__((aligned(16))) bf16_t Xs[NT * 64 * kGemmPitch];
+    if constexpr (SPLIT) {
+        bf16_t *const planes[3] = {Xs, Xs + 64 * kGemmPitch, Xs + 2 * 64 * kGemmPitch};
+        gemm64<SPLIT, CW>(In, W, ldw, M, K, Nout, out, blockIdx.x, Ws, planes);
+    } else {
+        bf16_t *const planes[1] = {Xs};
+        gemm64<SPLIT, CW>(In, W, ldw, M, K, Nout, out, blockIdx.x, Ws, planes);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The large products: a BM x BN tile per workgroup on 32x32x16 products, a wavefront with a quarter of it (BM / 2 x BN / 2), the contraction in chunks of 64 that go from memory straight into LDS (16 bytes per lane, no registers in
+// between) into one of two buffers while the other is multiplied.
+// A chunk's rows lie unpadded, as the direct loads need; conflicts are avoided by exchanging 16-byte pieces: piece c of
+// row m of In sits at position c ^ (m % 8) (16-byte row reads of 8 rows then cover all banks), piece c of row k of W
+// at c ^ 4 (k % 4) (BN = 128) or c ^ 4 (k / 2 % 2) (BN = 64), so that the 4 rows of a transposing read, and the 2
+// column groups next to each other, meet different banks.
+// The product is formed transposed (rows = outputs) with W's columns taken in the order that leaves a lane with two
+// runs of 8 consecutive outputs of one row of In per 32 outputs (see the operand layouts in bra_mfma.hip).
+// What bounds it (8192 x 768 x 2304, 128 x 128 tiles): direct loads alone 24 us (18 TB/s out of the L2s), products with
+// their LDS reads alone 23, stores alone 9.5; they overlap to 47, with 2.25 workgroups per slot in three rounds.
+__device__ __forceinline__ void load_to_lds(const bf16_t *g, bf16_t *l)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) unsigned *)g,
+                                     (__attribute__((address_space(3))) unsigned *)l, 16, 0, 0);
+}
+
+template <int BM, int BN, bool REGIONS>
+__global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) void k_gemm_dma(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw,
+                                                  int M, int K, int Nout, GemmOut out, GemmRegions reg, int reg_blocks)
+{
+    constexpr int RegionElems = REGIONS ? 64 * kGemmPitch + 8 * kGemmGroupW : 0;     // what gemm64 needs of each array
+    constexpr int AE = BM * 64 > RegionElems ? BM * 64 : RegionElems, BE = BN * 64 > RegionElems ? BN * 64 : RegionElems;
+    __shared__ __attribute__((aligned(16))) bf16_t A0[AE];
+    __shared__ __attribute__((aligned(16))) bf16_t A1[AE];
+    __shared__ __attribute__((aligned(16))) bf16_t B0[BE];
+    __shared__ __attribute__((aligned(16))) bf16_t B1[BE];
+    if (REGIONS && (int)blockIdx.x < reg_blocks) {
+        const GemmOut ro = {{reg.buf[0], reg.buf[1], nullptr}, reg.cols, {nullptr, nullptr}, nullptr, nullptr, 0};
+        bf16_t *const planes[3] = {A0, A1, B1};
+        gemm64<true, 2>(reg.In, W, ldw, (int)reg.M, K, reg.Nout, ro, blockIdx.x, B0, planes);
+        return;
+    }
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, h = lane / 32, c = lane % 32;
+    const int otiles = (Nout + BN - 1) / BN;
+    // workgroups of an XCD take neighbouring tiles, the output tiles of the same rows one after the other
+    const int nb = (int)gridDim.x - reg_blocks, per_xcd = nb / 8, bi = (int)blockIdx.x - reg_blocks;
+    const int block = (bi % 8) * per_xcd + bi / 8;
+    const int m0 = (block / otiles) * BM, o0 = (block % otiles) * BN;
+    if (m0 >= M) return;                          // the grid is rounded up to a multiple of 8
+
+    constexpr int LA = BM / 32, LB = BN / 32;     // direct loads of a wavefront per chunk
+    const bf16_t *ap[LA], *bp[LB];
+#pragma unroll
+    for (int u = 0; u < LA; ++u) {
+        const int row = 8 * (wave * LA + u) + lane / 8, piece = (lane % 8) ^ (row % 8);
+        ap[u] = In + (size_t)min(m0 + row, M - 1) * K + 8 * piece;
+    }
+    constexpr int CH = BN / 8, RPI = 64 / CH;     // pieces of a row of W, rows per direct load
+#pragma unroll
+    for (int u = 0; u < LB; ++u) {
+        const int k = RPI * (wave * LB + u) + lane / CH;
+        const int piece = (lane % CH) ^ (BN == 128 ? 4 * (k % 4) : 4 * (k / 2 % 2));
+        bp[u] = W + (size_t)k * ldw + min(o0 + 8 * piece, Nout - 8);
+    }
+    auto request = [&](int k0, bf16_t *As, bf16_t *Bs) {
+#pragma unroll
+        for (int u = 0; u < LA; ++u) load_to_lds(ap[u] + k0, As + 512 * (wave * LA + u));
+#pragma unroll
+        for (int u = 0; u < LB; ++u) load_to_lds(bp[u] + (size_t)k0 * ldw, Bs + 512 * (wave * LB + u));
+    };
+    constexpr int MT = BM / 64, NT = BN / 64;     // 32 x 32 tiles of a wavefront
+    const int wm = (wave / 2) * (BM / 2), wn = (wave % 2) * (BN / 2);
+    f32x16 acc[NT][MT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[nt][mt][e] = 0.f;
+    // transposing read of W: lane s of a 16-lane group q gives the address of 4 columns of row k; with the two middle
+    // bits of the column exchanged (see above)
+    const int s = lane % 16, q = lane / 16, col4 = ((s % 4) % 2) * 2 + (s % 4) / 2;
+    auto fragments = [&](const bf16_t *As, const bf16_t *Bs, int ks, bf16x8 (&xf)[MT], bf16x8 (&wf)[NT]) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int row = wm + 32 * mt + c;
+            xf[mt] = *(const bf16x8 *)(As + row * 64 + 8 * ((2 * ks + h) ^ (row % 8)));
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            u32x2 r[2];
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const int k = 16 * ks + 8 * (q / 2) + 4 * half + s / 4;
+                const int o = wn + 32 * nt + 16 * (q % 2) + 4 * col4, piece = o / 8;
+                const int pos = piece ^ (BN == 128 ? 4 * (k % 4) : 4 * (k / 2 % 2));
+                r[half] = __builtin_bit_cast(u32x2, lds_read_tr16(Bs + k * BN + 8 * pos + o % 8));
+            }
+            wf[nt] = __builtin_bit_cast(bf16x8, u32x4{r[0][0], r[0][1], r[1][0], r[1][1]});
+        }
+    };
+    // the next step's operands are on their way while this step's products run
+    auto multiply = [&](const bf16_t *As, const bf16_t *Bs) {
+        bf16x8 xf[2][MT], wf[2][NT];
+        fragments(As, Bs, 0, xf[0], wf[0]);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            if (ks < 3) fragments(As, Bs, ks + 1, xf[(ks + 1) % 2], wf[(ks + 1) % 2]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = mfma32(wf[ks % 2][nt], xf[ks % 2][mt], acc[nt][mt]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    const int pairs = K / 128;
+    request(0, A0, B0);
+    for (int p = 0; p < pairs; ++p) {
+        __syncthreads();                          // the chunk has arrived; the other buffer has been read
+        request(128 * p + 64, A1, B1);
+        multiply(A0, B0);
+        __syncthreads();
+        request(min(128 * p + 128, K - 64), A0, B0);      // past the end: the last chunk again, not used
+        multiply(A1, B1);
+    }
+    __syncthreads();
+    if (K % 128) multiply(A0, B0);
+    const bool extras = out.bias || out.gelu || out.res;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        // a 32-output tile lies in one buffer (cols is a multiple of 32): looked up once per tile, for the whole wavefront
+        const int ot = __builtin_amdgcn_readfirstlane(o0 + wn + 32 * nt), which = ot / out.cols, ct = ot - which * out.cols;
+        bf16_t *buf = (bf16_t *)out.buf[which];
+        float *fbuf = which < 2 ? out.f32[which] : nullptr;
+        if (ot >= Nout) continue;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int m = m0 + wm + 32 * mt + c;
+            if (m >= M) continue;
+            const size_t row = (size_t)m * out.cols;
+#pragma unroll
+            for (int run = 0; run < 2; ++run) {
+                const int o = ot + 16 * run + 8 * h, col = ct + 16 * run + 8 * h;
+                if (o >= Nout) continue;
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = acc[nt][mt][8 * run + e];
+                if (fbuf) {
+                    *(f32x4 *)(fbuf + row + col) = f32x4{v[0], v[1], v[2], v[3]};
+                    *(f32x4 *)(fbuf + row + col + 4) = f32x4{v[4], v[5], v[6], v[7]};
+                }
+                if (extras) {
+                    if (out.bias) {
+                        const f32x4 b0 = *(const f32x4 *)(out.bias + o), b1 = *(const f32x4 *)(out.bias + o + 4);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { v[e] += b0[e]; v[4 + e] += b1[e]; }
+                    }
+                    if (out.gelu) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) v[e] = gelu_f32(v[e]);
+                    }
+                    if (out.res) {
+                        const u32x4 rv = *(const u32x4 *)(out.res + row + o);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { v[2 * e] += bf16_lo(rv[e]); v[2 * e + 1] += bf16_hi(rv[e]); }
+                    }
+                }
+                *(bf16x8 *)(buf + row + col) = pack8(v);
+            }
+        }
+    }
+}
+
+template <int BM, int BN, bool REGIONS>
+int launch_dma(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out,
+               const GemmRegions &reg, hipStream_t st)
+{
+    const long tiles = (M + BM - 1) / BM * ((Nout + BN - 1) / BN), blocks = (tiles + 7) / 8 * 8;
+    const long rb = REGIONS ? (reg.M + 63) / 64 * ((reg.Nout + 63) / 64) : 0;
+    if (blocks + rb > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((k_gemm_dma<BM, BN, REGIONS>), dim3((unsigned)(blocks + rb)), dim3(256), 0, st, In, W, ldw, (int)M, K,
+                       Nout, out, reg, (int)rb);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+template <bool REGIONS>
+int launch_big(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, const GemmRegions &reg,
+               hipStream_t st)
+{
+    // Wide tiles read less per product but need enough of them (about 1.5 per slot: 2 workgroups of 128 x 128, 3 of
+    // 64 x 128 per compute unit) and outputs that fill 128 columns.  Measured, 128 x 128 / 64 x 128 / 64 x 64 (us):
+    // 8192 x 768 x 2304: 47 / 52 / 58; 8192 x 768 x 768: 18.2 / 16.8 / 19.4; 12544 x 1152 x 384: 22.0 / 20.5 / 22.9;
+    // 3136 x 512 x 512: 7.7 / 7.2 / 6.8; 126464 x 64 x 192: 16.9 / 17.0 / 15.5 (a 64 x 128 tile staged through
+    // registers took 61, 22, 26, 8.9, 37).  256 x 128 with 8 wavefronts gained nothing (50 / 17.1 / 20.5).
+    const long c128 = (Nout + 127) / 128;
+    const bool fills = 128 * c128 * 100 <= 115L * Nout;
+    if (fills && (M + 127) / 128 * c128 >= 800) return launch_dma<128, 128, REGIONS>(In, W, ldw, M, K, Nout, out, reg, st);
+    if (fills && (M + 63) / 64 * c128 >= 512) return launch_dma<64, 128, REGIONS>(In, W, ldw, M, K, Nout, out, reg, st);
+    return launch_dma<64, 64, REGIONS>(In, W, ldw, M, K, Nout, out, reg, st);
+}
+
+template <bool SPLIT>
+int launch_f32out(const void *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, hipStream_t st)
+{
+    // 64 x 64 tiles (twice the workgroups, six wavefronts per SIMD instead of four) where 64 x 128
+    // tiles would leave the chip under-filled; measured: the narrow tile wins below a few hundred
+    // wide tiles and loses above about a thousand
+    // (and where the output is at most 64 columns wide: half of a wide tile would be idle)
+    const long mt = (M + 63) / 64;
+    if (Nout <= 64 || mt * ((Nout + 127) / 128) < 400)
+        hipLaunchKernelGGL((k_gemm<SPLIT, 2>), dim3((unsigned)(mt * ((Nout + 63) / 64))), dim3(256), 0, st, In, W, ldw,
+                           (int)M, K, Nout, out);
+    else
+        hipLaunchKernelGGL((k_gemm<SPLIT, 4>), dim3((unsigned)(mt * ((Nout + 127) / 128))), dim3(256), 0, st, In, W,
+                           ldw, (int)M, K, Nout, out);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+bool sizes_ok(long M, int K, int Nout) { return M >= 1 && M <= 0x7fffffffL && K >= 64 && K % 64 == 0 && Nout >= 8 && Nout % 8 == 0; }
+
+}  // namespace
+
+int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, const GemmRegions *regions,
+         int kernel_id, hipStream_t st)
+{
+    if (!sizes_ok(M, K, Nout) || (out.cols % 32 && out.cols != Nout)) return BRA_ERR_UNSUPPORTED;
+    ProfScope ps(st, kernel_id);
+    if (regions) return launch_big<true>(In, W, ldw, M, K, Nout, out, *regions, st);
+    return launch_big<false>(In, W, ldw, M, K, Nout, out, GemmRegions{}, st);
+}
+
+int gemm_f32out(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, float *out0, float *out1, int cols,
+                int kernel_id, hipStream_t st)
+{
+    if (!sizes_ok(M, K, Nout)) return BRA_ERR_UNSUPPORTED;
+    ProfScope ps(st, kernel_id);
+    return launch_f32out<false>(In, W, ldw, M, K, Nout, GemmOut{{out0, out1, nullptr}, cols, {nullptr, nullptr}}, st);
+}
+
+int gemm_regions(const GemmRegions &r, const bf16_t *W, int ldw, int K, int kernel_id, hipStream_t st)
+{
+    if (!sizes_ok(r.M, K, r.Nout)) return BRA_ERR_UNSUPPORTED;
+    ProfScope ps(st, kernel_id);
+    return launch_f32out<true>(r.In, W, ldw, r.M, K, r.Nout, GemmOut{{r.buf[0], r.buf[1], nullptr}, r.cols, {nullptr, nullptr}}, st);
+}
+
+int gemm_bf16(const bf16_t *In, const bf16_t *W, long M, int K, int Nout, bf16_t *Out, const float *bias,
+              const bf16_t *res, bool gelu, int kernel_id, hipStream_t st)
+{
+    return gemm(In, W, Nout, M, K, Nout, GemmOut{{Out, nullptr, nullptr}, Nout, {nullptr, nullptr}, bias, res, gelu ? 1 : 0},
+                nullptr, kernel_id, st);
+}
+
+}  // namespace bra

@@ -12,6 +12,7 @@
 //   image-resident attention (small maps, regions of up to 8 tokens; bra_mfma_small.hip) or
 //   k_attn_gen (everything else), then LCE added in place                       (Eq. 6, 7)
 //   k_gemm<false> Y = O Wo (Eq. 2)
+#include "bra_gemm.h"
 #include "bra_lce_dev.h"
 
 #include <stdlib.h>
@@ -56,173 +57,6 @@ __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X,
         *(f32x4 *)dst = f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
         *(f32x4 *)(dst + 4) = f32x4{acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv};
     }
-}
-
-// ---------------------------------------------------------------------------
-// Out[m][o] = sum_k In[m][k] W[k][o] (W row-major with ldw columns, as the caller holds it)
-// for a tile of 64 rows m x 32 CW outputs o (128 or 64) per workgroup, the contraction in chunks of 64
-// staged in LDS (the next chunk is requested while the current one is multiplied).
-// The four wavefronts split the tile 2 x 2 (32 rows x 16 CW outputs each); the product is formed
-// transposed (D[output 16 t + 4 g + jj][row i]) so that a lane stores 4 consecutive outputs of one row;
-// its W operand (rows = outputs) comes out of the row-major chunk by the transposing LDS read.
-// Output column o goes to buffer o / cols (three buffers of `cols` columns each, e.g. Q, K,
-// V), column o % cols.
-// SPLIT: In is float32 and enters as three exact bf16 terms (smallest first); otherwise In is
-// bf16.  F32OUT: Out is float32, else bf16.
-constexpr int kGemmPitch = 80;      // bf16 per LDS row of In: 64 + 16 (rows of 160 bytes); W: the tile's width + 16
-constexpr int kGemmGroupW = 64;     // W: 128 bytes more after every 8 rows: the neighbouring lane group of a
-                                    // transposing read (8 rows further on) then meets the other half of the banks
-
-struct GemmOut {
-    void *buf[3];
-    int cols;
-    float *f32[2];      // optional float32 copies of the results that go to buf[0] and buf[1] (bf16 output only)
-    // bf16 output only, all optional: bias[o] is added, then GELU is applied, then res[m][o]
-    // (the layout of buf[0]) is added.
-    const float *bias;
-    const bf16_t *res;
-    int gelu;
-};
-
-template <bool SPLIT, bool F32OUT = SPLIT, int CW = 4>
-__global__ __launch_bounds__(256) void k_gemm(const void *__restrict__ In, const bf16_t *__restrict__ W,
-                                              int ldw, int M, int K, int Nout, GemmOut out)
-{
-    constexpr int P = kGemmPitch, NT = SPLIT ? 3 : 1, COLS = 32 * CW, PW = COLS + 16;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    bf16_t *Ws = (bf16_t *)smem;                 // [64 k][PW]
-    bf16_t *Xs = Ws + 64 * PW + 8 * kGemmGroupW; // [NT][64][P]
-    float *bs = (float *)(Xs + NT * 64 * P);     // [128]: the tile's slice of the bias
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
-    const int otiles = (Nout + COLS - 1) / COLS;
-    const int m0 = (blockIdx.x / otiles) * 64, o0 = (blockIdx.x % otiles) * COLS;
-
-    // this thread's pieces of a chunk: 4 x 16 bytes of W, and 2 x 16 bytes of bf16 In or
-    // 2 x 8 floats of float32 In
-    u32x4 wreg[CW], xreg[SPLIT ? 4 : 2];
-    auto request = [&](int k0) {
-#pragma unroll
-        for (int u = 0; u < CW; ++u) {
-            const int idx = tid + 256 * u;                       // (row k, 8 outputs)
-            const int o = min(o0 + (idx % (COLS / 8)) * 8, Nout - 8);    // columns past the end repeat the last; never stored
-            wreg[u] = *(const u32x4 *)(W + (size_t)(k0 + idx / (COLS / 8)) * ldw + o);
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int idx = tid + 256 * u;
-            const int m = min(m0 + idx / 8, M - 1);
-            if (SPLIT) {
-                const float *src = (const float *)In + (size_t)m * K + k0 + (idx % 8) * 8;
-                xreg[2 * u] = *(const u32x4 *)src;
-                xreg[2 * u + 1] = *(const u32x4 *)(src + 4);
-            } else {
-                xreg[u] = *(const u32x4 *)((const bf16_t *)In + (size_t)m * K + k0 + (idx % 8) * 8);
-            }
-        }
-    };
-    auto park = [&]() {
-#pragma unroll
-        for (int u = 0; u < CW; ++u) {
-            const int idx = tid + 256 * u;
-            const int row = idx / (COLS / 8);
-            *(u32x4 *)(Ws + row * PW + (row / 8) * kGemmGroupW + (idx % (COLS / 8)) * 8) = wreg[u];
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int idx = tid + 256 * u;
-            bf16_t *dst = Xs + (idx / 8) * P + (idx % 8) * 8;
-            if (SPLIT) {
-                const f32x4 lo = __builtin_bit_cast(f32x4, xreg[2 * u]), hi = __builtin_bit_cast(f32x4, xreg[2 * u + 1]);
-                const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                bf16x8 t[3];
-                split3(x, t);
-#pragma unroll
-                for (int q = 0; q < 3; ++q) *(bf16x8 *)(dst + q * 64 * P) = t[q];
-            } else {
-                *(u32x4 *)dst = xreg[u];
-            }
-        }
-    };
-
-    // wavefront (wr, wc) owns rows 32 wr .. 32 wr + 31 (two 16-row tiles) and outputs 64 wc ..
-    // 64 wc + 63 (four tiles) of the workgroup's 64 x 128: a W fragment serves two row tiles
-    const int wr = wave / 2, wc = wave % 2;
-    f32x4 acc[2][CW];
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-        for (int t = 0; t < CW; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (!F32OUT && out.bias && tid < COLS) bs[tid] = out.bias[min(o0 + tid, Nout - 1)];   // read after the loop's barriers
-    request(0);
-    for (int k0 = 0; k0 < K; k0 += 64) {
-        if (k0) __syncthreads();          // the previous chunk has been read
-        park();
-        __syncthreads();
-        if (k0 + 64 < K) request(k0 + 64);
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 xb[2][NT];
-#pragma unroll
-            for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-                for (int q = 0; q < NT; ++q)
-                    xb[rt][q] = *(const bf16x8 *)(Xs + (q * 64 + 32 * wr + 16 * rt + i) * P + 32 * ks + 8 * g);
-#pragma unroll
-            for (int t = 0; t < CW; ++t) {
-                const bf16_t *wp = Ws + (32 * ks + 8 * g + i / 4) * PW + (4 * ks + g) * kGemmGroupW + 16 * CW * wc + 16 * t +
-                                   4 * (i % 4);
-                const u32x2 w0 = __builtin_bit_cast(u32x2, lds_read_tr16(wp));
-                const u32x2 w1 = __builtin_bit_cast(u32x2, lds_read_tr16(wp + 4 * PW));
-                const bf16x8 wf = __builtin_bit_cast(bf16x8, u32x4{w0[0], w0[1], w1[0], w1[1]});
-#pragma unroll
-                for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-                    for (int q = NT - 1; q >= 0; --q) acc[rt][t] = mfma16(wf, xb[rt][q], acc[rt][t]);
-            }
-        }
-    }
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-        const int m = m0 + 32 * wr + 16 * rt + i;
-        if (m >= M) continue;
-        // the residual's pieces are requested together, ahead of the arithmetic (one by one
-        // behind the loop's exit test their latencies would add up)
-        u32x2 rv[CW];
-        if (!F32OUT && out.res) {
-#pragma unroll
-            for (int t = 0; t < CW; ++t) {
-                const int o = min(o0 + 16 * CW * wc + 16 * t + 4 * g, Nout - 4);
-                rv[t] = *(const u32x2 *)(out.res + (size_t)m * out.cols + o);
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < CW; ++t) {
-            const int o = o0 + 16 * CW * wc + 16 * t + 4 * g;
-            if (o >= Nout) break;
-            const int which = o / out.cols, col = o % out.cols;
-            if (F32OUT) {
-                *(f32x4 *)((float *)out.buf[which] + (size_t)m * out.cols + col) = acc[rt][t];
-            } else {
-                f32x4 v = acc[rt][t];
-                if (out.bias) {
-                    const f32x4 bv = *(const f32x4 *)(bs + 16 * CW * wc + 16 * t + 4 * g);
-                    v = f32x4{v[0] + bv[0], v[1] + bv[1], v[2] + bv[2], v[3] + bv[3]};
-                }
-                if (out.gelu) v = f32x4{gelu_f32(v[0]), gelu_f32(v[1]), gelu_f32(v[2]), gelu_f32(v[3])};
-                if (out.res)
-                    v = f32x4{v[0] + bf16_lo(rv[t][0]), v[1] + bf16_hi(rv[t][0]), v[2] + bf16_lo(rv[t][1]),
-                              v[3] + bf16_hi(rv[t][1])};
-                *(u32x2 *)((bf16_t *)out.buf[which] + (size_t)m * out.cols + col) = pack4(v);
-                if (which < 2 && out.f32[which]) *(f32x4 *)(out.f32[which] + (size_t)m * out.cols + col) = acc[rt][t];
-            }
-        }
-    }
-}
-
-constexpr size_t gemm_smem(bool split, int cw = 4)
-{
-    return (size_t)(64 * (32 * cw + 16) + 8 * kGemmGroupW) * 2 + (size_t)(split ? 3 : 1) * 64 * kGemmPitch * 2 +
-           128 * sizeof(float);
 }
 
 // ---------------------------------------------------------------------------
@@ -403,78 +237,38 @@ WideWs carve(const Dims &D, void *ws)
     return w;
 }
 
-template <bool SPLIT, bool F32OUT, int CW>
-int launch_gemm_tile(const void *In, const bf16_t *W, int ldw, long M, int K, int Nout, GemmOut out, int kernel_id,
-                     hipStream_t st)
+void launch_pool(const Dims &D, const bf16_t *X, const WideWs &w, hipStream_t st)
 {
-    static bool opted = false;
-    if (!opted) {
-        if (hipFuncSetAttribute((const void *)k_gemm<SPLIT, F32OUT, CW>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)gemm_smem(SPLIT, CW)) != hipSuccess)
-            return BRA_ERR_LAUNCH;
-        opted = true;
-    }
-    const long grid = ((M + 63) / 64) * ((Nout + 32 * CW - 1) / (32 * CW));
-    ProfScope ps(st, kernel_id);
-    hipLaunchKernelGGL((k_gemm<SPLIT, F32OUT, CW>), dim3((unsigned)grid), dim3(256), gemm_smem(SPLIT, CW), st, In, W,
-                       ldw, (int)M, K, Nout, out);
-    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+    int sub = 1;                                           // lanes per (region, chunk)
+    while (sub < 8 && 2 * sub <= D.n) sub *= 2;
+    const long items = (long)D.B * D.R * (D.C / 8) * sub;
+    ProfScope ps(st, K_MFMA_POOL_QK);
+    hipLaunchKernelGGL(k_pool_wide, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, X, w.xr, D, sub);
 }
 
-template <bool SPLIT, bool F32OUT = SPLIT>
-int launch_gemm(const void *In, const bf16_t *W, int ldw, long M, int K, int Nout, GemmOut out, int kernel_id,
-                hipStream_t st)
+GemmRegions region_job(const Dims &D, const WideWs &w)
 {
-    // 64 x 64 tiles (twice the workgroups, six wavefronts per SIMD instead of four) where 64 x 128
-    // tiles would leave the chip under-filled; measured: the narrow tile wins below a few hundred
-    // wide tiles and loses above about a thousand
-    static const long narrow_below = experiment_value("BRA_GEMM_NARROW", 400);
-    // (and where the output is at most 64 columns wide: half of a wide tile would be idle)
-    if (Nout <= 64 || ((M + 63) / 64) * ((Nout + 127) / 128) < narrow_below)
-        return launch_gemm_tile<SPLIT, F32OUT, 2>(In, W, ldw, M, K, Nout, out, kernel_id, st);
-    return launch_gemm_tile<SPLIT, F32OUT, 4>(In, W, ldw, M, K, Nout, out, kernel_id, st);
+    return GemmRegions{w.xr, (long)D.B * D.R, 2 * D.C, {w.qr, w.kr}, D.C};
 }
 
-// A^r rows and top-k from the float32 Q^r, K^r in the workspace.
-int affinity_steps(const Dims &D, const WideWs &w, int32_t *Ir, float *Ar_opt, hipStream_t st)
-{
-    return route_rows(D, w.qr, w.kr, D.C, Ir, Ar_opt, st);
-}
-
-// Pooling, region-level projections, A^r rows and top-k.
+// Pooling, region-level projections, A^r rows and top-k on their own.
 int route_steps(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideWs &w, int32_t *Ir, float *Ar_opt,
                 hipStream_t st)
 {
+    int rc;
     if (D.n == 1) {
         // one token per region: the means are the (bf16) tokens themselves, so Q^r | K^r is the
         // plain projection of X with float32 results: no pooling, no split
-        const int rc = launch_gemm<false, true>(X, Wqkv, 3 * D.C, (long)D.B * D.R, D.C, 2 * D.C,
-                                                GemmOut{{w.qr, w.kr, nullptr}, D.C, {nullptr, nullptr}}, K_MFMA_ROUTE_ROWS, st);
-        if (rc != BRA_OK) return rc;
-        return affinity_steps(D, w, Ir, Ar_opt, st);
+        rc = gemm_f32out(X, Wqkv, 3 * D.C, (long)D.B * D.R, D.C, 2 * D.C, w.qr, w.kr, D.C, K_MFMA_ROUTE_ROWS, st);
+    } else {
+        launch_pool(D, X, w, st);
+        rc = gemm_regions(region_job(D, w), Wqkv, 3 * D.C, D.C, K_MFMA_ROUTE_ROWS, st);
     }
-    {
-        int sub = 1;                                           // lanes per (region, chunk)
-        while (sub < 8 && 2 * sub <= D.n) sub *= 2;
-        const long items = (long)D.B * D.R * (D.C / 8) * sub;
-        ProfScope ps(st, K_MFMA_POOL_QK);
-        hipLaunchKernelGGL(k_pool_wide, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, X, w.xr, D, sub);
-    }
-    const int rc = launch_gemm<true>(w.xr, Wqkv, 3 * D.C, (long)D.B * D.R, D.C, 2 * D.C, GemmOut{{w.qr, w.kr, nullptr}, D.C, {nullptr, nullptr}},
-                                     K_MFMA_ROUTE_ROWS, st);
     if (rc != BRA_OK) return rc;
-    return affinity_steps(D, w, Ir, Ar_opt, st);
+    return route_rows(D, w.qr, w.kr, D.C, Ir, Ar_opt, st);
 }
 
 }  // namespace
-
-int gemm_bf16(const bf16_t *In, const bf16_t *W, long M, int K, int Nout, bf16_t *Out, const float *bias,
-              const bf16_t *res, bool gelu, int kernel_id, hipStream_t st)
-{
-    if (M < 1 || M > 0x7fffffffL || K < 64 || K % 64 || Nout < 8 || Nout % 8) return BRA_ERR_UNSUPPORTED;
-    GemmOut out{{Out, nullptr, nullptr}, Nout, {nullptr, nullptr}, bias, res, gelu ? 1 : 0};
-    return launch_gemm<false>(In, W, Nout, M, K, Nout, out, kernel_id, st);
-}
 
 // Q, K, V = X Wqkv into three token maps (Eq. 3) for any C that is a multiple of 64: the projection of
 // the wide pipeline, for the backward pass.
@@ -482,8 +276,8 @@ int wide_project_qkv(const Dims &D, const void *X, const void *Wqkv, bf16_t *Q, 
 {
     const long M = (long)D.B * D.N;
     if (D.C % 64 || M > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    return launch_gemm<false>(X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C,
-                              GemmOut{{Q, K, V}, D.C, {nullptr, nullptr}}, K_MFMA_QKV, st);
+    return gemm((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, GemmOut{{Q, K, V}, D.C, {nullptr, nullptr}}, nullptr,
+                K_MFMA_QKV, st);
 }
 
 bool wide_supported(const Dims &D)
@@ -511,20 +305,19 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     const WideWs w = carve(D, ws);
     const int32_t *Ir_src = Ir_in_opt;
     int32_t *Ir_dst = Ir_out_opt ? Ir_out_opt : w.ir;
-    // one token per region: Q^r, K^r are Q, K before their rounding to bf16, which the token
-    // projection leaves as float32 copies; the routing then follows the projection
-    const bool route_after = !Ir_in_opt && D.n == 1;
-    if (!Ir_in_opt && !route_after) {
-        const int rc = route_steps(D, (const bf16_t *)X, (const bf16_t *)Wqkv, w, Ir_dst, nullptr, st);
-        if (rc != BRA_OK) return rc;
-        Ir_src = Ir_dst;
-    }
+    // Q^r | K^r: one token per region: Q, K before their rounding to bf16, which the token projection leaves as float32
+    // copies; else the projection of the region means, in the same launch as the tokens' (on its own it was a chain of
+    // 12 chunks on a few workgroups: 13.7 us at C = 768)
     const long M = (long)D.B * D.N;
-    float *fq = route_after ? w.qr : nullptr, *fk = route_after ? w.kr : nullptr;
-    int rc = launch_gemm<false>(X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, GemmOut{{w.q, w.k, w.v}, D.C, {fq, fk}}, K_MFMA_QKV, st);
+    const bool route = !Ir_in_opt, pooled = route && D.n > 1;
+    if (pooled) launch_pool(D, (const bf16_t *)X, w, st);
+    const GemmRegions rj = region_job(D, w);
+    float *fq = route && !pooled ? w.qr : nullptr, *fk = route && !pooled ? w.kr : nullptr;
+    int rc = gemm((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, GemmOut{{w.q, w.k, w.v}, D.C, {fq, fk}},
+                  pooled ? &rj : nullptr, K_MFMA_QKV, st);
     if (rc != BRA_OK) return rc;
-    if (route_after) {
-        rc = affinity_steps(D, w, Ir_dst, nullptr, st);
+    if (route) {
+        rc = route_rows(D, w.qr, w.kr, D.C, Ir_dst, nullptr, st);
         if (rc != BRA_OK) return rc;
         Ir_src = Ir_dst;
     }
@@ -544,7 +337,7 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
         rc = lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);
     }
     if (rc != BRA_OK) return rc;
-    return launch_gemm<false>(w.o, (const bf16_t *)Wo, D.C, M, D.C, D.C, GemmOut{{Y, nullptr, nullptr}, D.C, {nullptr, nullptr}}, K_MFMA_WO, st);
+    return gemm(w.o, (const bf16_t *)Wo, D.C, M, D.C, D.C, GemmOut{{Y, nullptr, nullptr}, D.C, {nullptr, nullptr}}, nullptr, K_MFMA_WO, st);
 }
 
 }  // namespace bra
