@@ -58,7 +58,7 @@ inline ReduceJob reduce_job(const float *part, float *out, int nparts, int count
     return ReduceJob{part, out, nparts, count, slices, (count + elems - 1) / elems};
 }
 
-static __global__ __launch_bounds__(1024) void k_reduce_parts(ReduceJob j0, ReduceJob j1, ReduceJob j2)
+[[maybe_unused]] static __global__ __launch_bounds__(1024) void k_reduce_parts(ReduceJob j0, ReduceJob j1, ReduceJob j2)
 {
     __shared__ float red[1024];
     int bi = blockIdx.x;

@@ -20,6 +20,7 @@
 // gradients are summed from per-workgroup partial sums in a fixed order (k_reduce_parts).
 #include "bra_bwd_dev.h"
 #include "bra_lce_dev.h"
+#include "bra_mfma_bwd_map.h"
 
 namespace bra {
 
@@ -935,6 +936,8 @@ int heads_per_workgroup(const Dims &D)
 
 int attn_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, hipStream_t st)
 {
+    if (attn_bwd_map_ok(D))
+        return launch_attn_bwd_map(D, w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, K_GEN_BACKWARD, st);
     const int hpw = heads_per_workgroup(D);
     if (D.d == 32) {
         if (hpw == 4) return attn_bwd_heads<32, 4>(D, w, Ir, st);

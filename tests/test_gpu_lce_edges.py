@@ -26,3 +26,18 @@ def test_lce_edges(B, H, W, C, heads, S, k):
     compare_backward(X[:2], Wqkv, Wo, Wlce, "bf16", heads, S, k, path="mfma")
     if B > 2:
         compare_backward(X, Wqkv, Wo, Wlce, "bf16", heads, S, k, path="mfma")
+
+
+MAPS = [  # (B, H, W, C, heads, S, k): image-resident attention backward: 1 .. 8 tokens per region, one and several key blocks
+    (2, 7, 7, 64, 2, 7, 49),         # one token per region, 49 keys
+    (1, 10, 5, 64, 2, 5, 7),         # 2 x 1 regions
+    (2, 9, 6, 64, 2, 3, 9),          # 3 x 2 regions, every region
+    (1, 28, 14, 64, 2, 7, 30),       # 8 tokens, 392 tokens per image (16 wavefronts, most of the LDS), 4 key blocks
+    (1, 16, 16, 96 + 32, 4, 8, 16),  # 64 keys exactly
+]
+
+
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", MAPS)
+def test_backward_image_resident(B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=8800 + H * W + C, dtype="bf16")
+    compare_backward(X, Wqkv, Wo, Wlce, "bf16", heads, S, k, path="mfma")
