@@ -156,7 +156,7 @@ __device__ __forceinline__ bool map_stage(MapWork &w, char *smem, const bf16_t *
 }
 
 template <int NW>
-__global__ __launch_bounds__(64 * NW) void k_attn_bwd_map(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
+__global__ __launch_bounds__(64 * NW, 4) void k_attn_bwd_map(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                           const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
                                                           const int32_t *__restrict__ Ir, bf16_t *__restrict__ O,
                                                           bf16_t *__restrict__ dQKV, Dims D, int total)
