@@ -41,26 +41,48 @@ __device__ __forceinline__ int collect_entries(const int32_t *__restrict__ irb, 
 }
 
 // ---------------------------------------------------------------------------
-// out[e] = sum_p part[p][e], p in a fixed order, for up to three arrays in one launch.  A workgroup
-// of 1024 threads takes 1024 / slices elements x `slices` slices of p (a power of two up to 32, about
-// the number of partial arrays), the slices summed through LDS.
+// out[e] = sum_p part[p][e], p in a fixed order, for up to three arrays in one launch.  A thread sums 4 elements (16
+// bytes) of one of `slices` slices of p (a power of two up to 64, about a quarter of the number of partial arrays), the
+// slices are summed through LDS.  Counts are multiples of 4 and arrays 16-byte aligned, else VEC = false: single elements.
 struct ReduceJob {
     const float *part;
     float *out;
     int nparts, count, slices, blocks;
+    int vec;
 };
 
 inline ReduceJob reduce_job(const float *part, float *out, int nparts, int count)
 {
     int slices = 1;
-    while (slices < 32 && slices < nparts) slices *= 2;
-    const int elems = 1024 / slices;
-    return ReduceJob{part, out, nparts, count, slices, (count + elems - 1) / elems};
+    while (slices < 64 && 4 * slices <= nparts) slices *= 2;
+    const int vec = count % 4 == 0 && (uintptr_t)part % 16 == 0 && (uintptr_t)out % 16 == 0;
+    const int elems = 256 / slices * (vec ? 4 : 1);
+    return ReduceJob{part, out, nparts, count, slices, (count + elems - 1) / elems, vec};
 }
 
-[[maybe_unused]] static __global__ __launch_bounds__(1024) void k_reduce_parts(ReduceJob j0, ReduceJob j1, ReduceJob j2)
+template <typename V>
+__device__ __forceinline__ void reduce_block(const ReduceJob &job, int bi, V *red)
 {
-    __shared__ float red[1024];
+    const int per = 256 / job.slices, x = threadIdx.x % per, y = threadIdx.x / per, n = job.count / (int)(sizeof(V) / 4);
+    const int e = bi * per + x;
+    const V *part = (const V *)job.part;
+    V sum = V{};
+    if (e < n) {
+#pragma unroll 4
+        for (int p = y; p < job.nparts; p += job.slices) sum += part[(size_t)p * n + e];
+    }
+    red[y * per + x] = sum;
+    __syncthreads();
+    if (y == 0 && e < n) {
+        V total = V{};
+        for (int u = 0; u < job.slices; ++u) total += red[u * per + x];
+        ((V *)job.out)[e] = total;
+    }
+}
+
+[[maybe_unused]] static __global__ __launch_bounds__(256) void k_reduce_parts(ReduceJob j0, ReduceJob j1, ReduceJob j2)
+{
+    __shared__ mfma::f32x4 red[256];
     int bi = blockIdx.x;
     ReduceJob job = j0;
     if (bi >= j0.blocks) {
@@ -71,19 +93,8 @@ inline ReduceJob reduce_job(const float *part, float *out, int nparts, int count
             job = j2;
         }
     }
-    const int elems = 1024 / job.slices;
-    const int x = threadIdx.x % elems, y = threadIdx.x / elems, e = bi * elems + x;
-    float sum = 0.f;
-    if (e < job.count)
-#pragma unroll 8
-        for (int p = y; p < job.nparts; p += job.slices) sum += job.part[(size_t)p * job.count + e];
-    red[y * elems + x] = sum;
-    __syncthreads();
-    if (y == 0 && e < job.count) {
-        float total = 0.f;
-        for (int u = 0; u < job.slices; ++u) total += red[u * elems + x];
-        job.out[e] = total;
-    }
+    if (job.vec) reduce_block<mfma::f32x4>(job, bi, red);
+    else reduce_block<float>(job, bi, (float *)red);
 }
 
 }  // namespace bwd

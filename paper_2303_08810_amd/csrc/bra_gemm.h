@@ -34,6 +34,19 @@ int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, co
 // The same with float32 results (two buffers at most).
 int gemm_f32out(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, float *out0, float *out1, int cols,
                 int kernel_id, hipStream_t st);
+// Out = In Wt^T: Wt [Nout][ldw], the contraction axis contiguous.
+int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout, bf16_t *Out, int kernel_id, hipStream_t st);
+
+// Contractions over all M tokens: Part[share][KA][N] = A^T B over the share's tokens, for two products in one launch with
+// gemm_tn_shares(M, ..) shares each (their sum, in a fixed order, is the product).  Sizes and pitches multiples of 8.
+struct GemmTn {
+    const bf16_t *A, *Bm;
+    float *Part;
+    int lda, ldb, KA, N;
+};
+int gemm_tn_shares(long M, int KA0, int N0, int KA1, int N1);
+int gemm_tn(const GemmTn &J0, const GemmTn &J1, long M, int kernel_id, hipStream_t st);
+
 // The region-level product on its own.
 int gemm_regions(const GemmRegions &r, const bf16_t *W, int ldw, int K, int kernel_id, hipStream_t st);
 

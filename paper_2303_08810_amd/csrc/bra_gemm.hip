@@ -163,7 +163,9 @@ __device__ __forceinline__ void load_to_lds(const bf16_t *g, bf16_t *l)
                                      (__attribute__((address_space(3))) unsigned *)l, 16, 0, 0);
 }
 
-template <int BM, int BN, bool REGIONS>
+// BT: W is given transposed, [Nout][ldw] with the contraction axis contiguous; its chunk then lies like In's and needs no
+// transposing reads.
+template <int BM, int BN, bool REGIONS, bool BT>
 __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) void k_gemm_dma(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw,
                                                   int M, int K, int Nout, GemmOut out, GemmRegions reg, int reg_blocks)
 {
@@ -197,6 +199,11 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
     constexpr int CH = BN / 8, RPI = 64 / CH;     // pieces of a row of W, rows per direct load
 #pragma unroll
     for (int u = 0; u < LB; ++u) {
+        if (BT) {
+            const int row = 8 * (wave * LB + u) + lane / 8, piece = (lane % 8) ^ (row % 8);
+            bp[u] = W + (size_t)min(o0 + row, Nout - 1) * ldw + 8 * piece;
+            continue;
+        }
         const int k = RPI * (wave * LB + u) + lane / CH;
         const int piece = (lane % CH) ^ (BN == 128 ? 4 * (k % 4) : 4 * (k / 2 % 2));
         bp[u] = W + (size_t)k * ldw + min(o0 + 8 * piece, Nout - 8);
@@ -205,7 +212,7 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
 #pragma unroll
         for (int u = 0; u < LA; ++u) load_to_lds(ap[u] + k0, As + 512 * (wave * LA + u));
 #pragma unroll
-        for (int u = 0; u < LB; ++u) load_to_lds(bp[u] + (size_t)k0 * ldw, Bs + 512 * (wave * LB + u));
+        for (int u = 0; u < LB; ++u) load_to_lds(bp[u] + (BT ? (size_t)k0 : (size_t)k0 * ldw), Bs + 512 * (wave * LB + u));
     };
     constexpr int MT = BM / 64, NT = BN / 64;     // 32 x 32 tiles of a wavefront
     const int wm = (wave / 2) * (BM / 2), wn = (wave % 2) * (BN / 2);
@@ -227,6 +234,12 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
         }
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
+            if (BT) {
+                // operand row c is output c with its two middle bits exchanged
+                const int row = wn + 32 * nt + (c & 0x13) + ((c & 4) << 1) + ((c & 8) >> 1);
+                wf[nt] = *(const bf16x8 *)(Bs + row * 64 + 8 * ((2 * ks + h) ^ (row % 8)));
+                continue;
+            }
             u32x2 r[2];
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
@@ -311,19 +324,19 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
     }
 }
 
-template <int BM, int BN, bool REGIONS>
+template <int BM, int BN, bool REGIONS, bool BT>
 int launch_dma(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out,
                const GemmRegions &reg, hipStream_t st)
 {
     const long tiles = (M + BM - 1) / BM * ((Nout + BN - 1) / BN), blocks = (tiles + 7) / 8 * 8;
     const long rb = REGIONS ? (reg.M + 63) / 64 * ((reg.Nout + 63) / 64) : 0;
     if (blocks + rb > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((k_gemm_dma<BM, BN, REGIONS>), dim3((unsigned)(blocks + rb)), dim3(256), 0, st, In, W, ldw, (int)M, K,
+    hipLaunchKernelGGL((k_gemm_dma<BM, BN, REGIONS, BT>), dim3((unsigned)(blocks + rb)), dim3(256), 0, st, In, W, ldw, (int)M, K,
                        Nout, out, reg, (int)rb);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
-template <bool REGIONS>
+template <bool REGIONS, bool BT = false>
 int launch_big(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, const GemmRegions &reg,
                hipStream_t st)
 {
@@ -334,9 +347,9 @@ int launch_big(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int No
     // registers took 61, 22, 26, 8.9, 37).  256 x 128 with 8 wavefronts gained nothing (50 / 17.1 / 20.5).
     const long c128 = (Nout + 127) / 128;
     const bool fills = 128 * c128 * 100 <= 115L * Nout;
-    if (fills && (M + 127) / 128 * c128 >= 800) return launch_dma<128, 128, REGIONS>(In, W, ldw, M, K, Nout, out, reg, st);
-    if (fills && (M + 63) / 64 * c128 >= 512) return launch_dma<64, 128, REGIONS>(In, W, ldw, M, K, Nout, out, reg, st);
-    return launch_dma<64, 64, REGIONS>(In, W, ldw, M, K, Nout, out, reg, st);
+    if (fills && (M + 127) / 128 * c128 >= 800) return launch_dma<128, 128, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
+    if (fills && (M + 63) / 64 * c128 >= 512) return launch_dma<64, 128, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
+    return launch_dma<64, 64, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
 }
 
 template <bool SPLIT>
@@ -356,6 +369,119 @@ int launch_f32out(const void *In, const bf16_t *W, int ldw, long M, int K, int N
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
+// ---------------------------------------------------------------------------
+// Part[share][a][n] = sum over the share's tokens t of A[t][a] B[t][n] (the weight gradients dWqkv = X^T dQKV and
+// dWo = O^T dY, both in one launch): a 128 x 128 block of the output per workgroup, 64 tokens at a time straight into one of
+// two LDS buffers; both operands by transposing reads (pieces exchanged as for W above).
+template <int UNUSED = 0>
+__device__ __forceinline__ void tn_block(const GemmTn &J, int block, long M, int share_tokens, bf16_t *A0, bf16_t *A1,
+                                         bf16_t *B0, bf16_t *B1)
+{
+    const int nb = (J.N + 127) / 128, ab = (J.KA + 127) / 128;
+    const int n0 = 128 * (block % nb), a0 = 128 * (block / nb % ab), share = block / (nb * ab);
+    const long t_begin = (long)share * share_tokens, t_end = min(M, t_begin + share_tokens);
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, h = lane / 32, c = lane % 32;
+    const int ldl = lane / 16;                                // row of a direct load (4 rows of 16 pieces)
+    const bf16_t *ap[4], *bp[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int k = 4 * (wave * 4 + u) + ldl, piece = (lane % 16) ^ (4 * (k % 4));
+        ap[u] = J.A + min(a0 + 8 * piece, J.KA - 8);
+        bp[u] = J.Bm + min(n0 + 8 * piece, J.N - 8);
+    }
+    auto request = [&](long t0, bf16_t *As, bf16_t *Bs) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const size_t t = min(t0 + 4 * (wave * 4 + u) + ldl, t_end - 1);
+            load_to_lds(ap[u] + t * J.lda, As + 512 * (wave * 4 + u));
+            load_to_lds(bp[u] + t * J.ldb, Bs + 512 * (wave * 4 + u));
+        }
+    };
+    const int wa = (wave / 2) * 64, wn = (wave % 2) * 64;
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
+    const int s = lane % 16, q = lane / 16;
+    auto operand = [&](const bf16_t *T, int col0, int ks) {
+        u32x2 r[2];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int k = 16 * ks + 8 * (q / 2) + 4 * half + s / 4, o = col0 + 16 * (q % 2) + 4 * (s % 4);
+            r[half] = __builtin_bit_cast(u32x2, lds_read_tr16(T + k * 128 + 8 * ((o / 8) ^ (4 * (k % 4))) + o % 8));
+        }
+        return __builtin_bit_cast(bf16x8, u32x4{r[0][0], r[0][1], r[1][0], r[1][1]});
+    };
+    auto multiply = [&](const bf16_t *As, const bf16_t *Bs) {
+        bf16x8 af[2][2], bf[2][2];
+        auto fragments = [&](int ks) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                af[ks % 2][x] = operand(As, wa + 32 * x, ks);
+                bf[ks % 2][x] = operand(Bs, wn + 32 * x, ks);
+            }
+        };
+        fragments(0);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            if (ks < 3) fragments(ks + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y) acc[x][y] = mfma32(af[ks % 2][x], bf[ks % 2][y], acc[x][y]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // tokens past the end add nothing: their rows of A are blanked once the chunk has arrived
+    auto blank = [&](long t0, bf16_t *As) {
+        if (t0 + 64 > t_end) {
+            for (int e = tid; e < 64 * 16; e += 256)
+                if (t0 + e / 16 >= t_end) *(u32x4 *)(As + 8 * e) = u32x4{0u, 0u, 0u, 0u};
+            __syncthreads();
+        }
+    };
+    request(t_begin, A0, B0);
+    for (long t0 = t_begin; t0 < t_end; t0 += 128) {
+        __syncthreads();
+        if (t0 + 64 < t_end) request(t0 + 64, A1, B1);
+        blank(t0, A0);
+        multiply(A0, B0);
+        __syncthreads();
+        if (t0 + 128 < t_end) request(t0 + 128, A0, B0);
+        if (t0 + 64 < t_end) {
+            blank(t0 + 64, A1);
+            multiply(A1, B1);
+        }
+    }
+    float *out = J.Part + (size_t)share * J.KA * J.N;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            const int n = n0 + wn + 32 * y + c;
+            if (n >= J.N) continue;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int a = a0 + wa + 32 * x + 8 * (e / 4) + 4 * h + e % 4;
+                if (a < J.KA) out[(size_t)a * J.N + n] = acc[x][y][e];
+            }
+        }
+}
+
+__global__ __launch_bounds__(256, 2) void k_gemm_tn(GemmTn J0, GemmTn J1, int blocks0, long M, int share_tokens)
+{
+    __shared__ __attribute__((aligned(16))) bf16_t A0[64 * 128];
+    __shared__ __attribute__((aligned(16))) bf16_t A1[64 * 128];
+    __shared__ __attribute__((aligned(16))) bf16_t B0[64 * 128];
+    __shared__ __attribute__((aligned(16))) bf16_t B1[64 * 128];
+    const bool second = (int)blockIdx.x >= blocks0;
+    tn_block(second ? J1 : J0, second ? (int)blockIdx.x - blocks0 : (int)blockIdx.x, M, share_tokens, A0, A1, B0, B1);
+}
+
 bool sizes_ok(long M, int K, int Nout) { return M >= 1 && M <= 0x7fffffffL && K >= 64 && K % 64 == 0 && Nout >= 8 && Nout % 8 == 0; }
 
 }  // namespace
@@ -369,12 +495,44 @@ int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, co
     return launch_big<false>(In, W, ldw, M, K, Nout, out, GemmRegions{}, st);
 }
 
+int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout, bf16_t *Out, int kernel_id, hipStream_t st)
+{
+    if (!sizes_ok(M, K, Nout)) return BRA_ERR_UNSUPPORTED;
+    ProfScope ps(st, kernel_id);
+    return launch_big<false, true>(In, Wt, ldw, M, K, Nout, GemmOut{{Out, nullptr, nullptr}, Nout, {nullptr, nullptr}, nullptr, nullptr, 0},
+                                   GemmRegions{}, st);
+}
+
 int gemm_f32out(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, float *out0, float *out1, int cols,
                 int kernel_id, hipStream_t st)
 {
     if (!sizes_ok(M, K, Nout)) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);
     return launch_f32out<false>(In, W, ldw, M, K, Nout, GemmOut{{out0, out1, nullptr}, cols, {nullptr, nullptr}}, st);
+}
+
+// Two workgroups per compute unit over the 128 x 128 blocks of both products.
+static int tn_share_tokens(long M, int KA0, int N0, int KA1, int N1)
+{
+    auto blocks = [](int a, int n) { return (long)((a + 127) / 128) * ((n + 127) / 128); };
+    const long want = std::max(1L, 512 / (blocks(KA0, N0) + blocks(KA1, N1))), chunks = (M + 63) / 64;
+    return (int)((chunks + want - 1) / want * 64);
+}
+
+int gemm_tn_shares(long M, int KA0, int N0, int KA1, int N1)
+{
+    const int t = tn_share_tokens(M, KA0, N0, KA1, N1);
+    return (int)((M + t - 1) / t);
+}
+
+int gemm_tn(const GemmTn &J0, const GemmTn &J1, long M, int kernel_id, hipStream_t st)
+{
+    if (M < 1 || (J0.KA | J0.N | J1.KA | J1.N | J0.lda | J0.ldb | J1.lda | J1.ldb) % 8) return BRA_ERR_UNSUPPORTED;
+    const int tokens = tn_share_tokens(M, J0.KA, J0.N, J1.KA, J1.N), shares = gemm_tn_shares(M, J0.KA, J0.N, J1.KA, J1.N);
+    auto blocks = [&](const GemmTn &J) { return (long)((J.KA + 127) / 128) * ((J.N + 127) / 128) * shares; };
+    ProfScope ps(st, kernel_id);
+    hipLaunchKernelGGL(k_gemm_tn, dim3((unsigned)(blocks(J0) + blocks(J1))), dim3(256), 0, st, J0, J1, (int)blocks(J0), M, tokens);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
 int gemm_regions(const GemmRegions &r, const bf16_t *W, int ldw, int K, int kernel_id, hipStream_t st)

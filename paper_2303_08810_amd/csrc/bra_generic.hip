@@ -511,7 +511,7 @@ int backward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *W
     else hipLaunchKernelGGL((f32::k_gemm_tn<false, T, float, float, T>), tgrid, dim3(256), 0, st, jq, jo, M, sp.tokens);
     const bwd::ReduceJob r0 = bwd::reduce_job(w.part_qkv, dWqkv, sp.shares, C3 * C), r1 = bwd::reduce_job(w.part_o, dWo, sp.shares, C * C),
                          r2 = bwd::reduce_job(w.part_lce, dWlce, lp.groups, 25 * C);
-    hipLaunchKernelGGL(bwd::k_reduce_parts, dim3(r0.blocks + r1.blocks + r2.blocks), dim3(1024), 0, st, r0, r1, r2);
+    hipLaunchKernelGGL(bwd::k_reduce_parts, dim3(r0.blocks + r1.blocks + r2.blocks), dim3(256), 0, st, r0, r1, r2);
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 

@@ -2,7 +2,7 @@
 // multiple of 64 up to 4096, at most 4096 routing entries per image), with the routing index held fixed.
 //
 // Chain rule through Eq. 6-7 and Eq. 1-2, with O = Attention(Q, K^g, V^g) + LCE(V), Y = O Wo:
-//     dO = dY Wo^T                     projection kernel with Wo^T as its matrix
+//     dO = dY Wo^T                     general product, Wo taken transposed as it lies
 //     P  = softmax(scale Q K^T)        recomputed per (region, head) from the re-projected Q, K
 //     dP = dO V^T,  dS = scale P o (dP - D),  D = rowsum(P o dP)
 //     dQ = dS K                        k_attn_bwd_q, one workgroup per query region; it also leaves the
@@ -19,6 +19,7 @@
 // bf16 between the kernels (they are matrix-core operands of the next product).  The weight
 // gradients are summed from per-workgroup partial sums in a fixed order (k_reduce_parts).
 #include "bra_bwd_dev.h"
+#include "bra_gemm.h"
 #include "bra_lce_dev.h"
 #include "bra_mfma_bwd_map.h"
 
@@ -601,65 +602,6 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const bf16_t *__restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Part[blockIdx.x][a][o] = sum_t A[t][a] Bm[t][o] over the workgroup's share of the M tokens (the
-// token contractions dWqkv = X^T dQKV and dWo = O^T dY): a 64 x 64 block (blockIdx.y, blockIdx.z)
-// of the [Ca][ldo] output per workgroup, both operands staged as [64 tokens][64 channels] LDS
-// tiles and read with transposing reads.  Wavefront w forms rows 16 w .. 16 w + 15 of the block.
-// k_reduce_parts then sums the partial matrices.
-__global__ __launch_bounds__(256) void k_gemm_tn(const bf16_t *__restrict__ A, int lda,
-                                                 const bf16_t *__restrict__ Bm, int ldb, float *__restrict__ Part,
-                                                 int ldo, long M, int tokens_per_wg)
-{
-    constexpr int TP = 64 + 16;
-    __shared__ __attribute__((aligned(16))) bf16_t As[64 * TP];
-    __shared__ __attribute__((aligned(16))) bf16_t Bs[64 * TP];
-    const int a0 = 64 * blockIdx.y, b0 = 64 * blockIdx.z;
-    const long t_begin = (long)blockIdx.x * tokens_per_wg, t_end = min(M, t_begin + tokens_per_wg);
-    const int w = threadIdx.x / 64, lane = threadIdx.x % 64, g = lane / 16, i = lane % 16;
-    f32x4 acc[4];
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    u32x4 ar[2], br[2];
-    auto fetch = [&](long t0) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int idx = threadIdx.x + 256 * u, row = idx / 8, c8 = idx % 8;
-            const size_t t = min(t0 + row, t_end - 1);       // unconditional; rows past the end are blanked at the LDS write
-            ar[u] = *(const u32x4 *)(A + t * lda + a0 + c8 * 8);
-            br[u] = *(const u32x4 *)(Bm + t * ldb + b0 + c8 * 8);
-        }
-    };
-    if (t_begin < t_end) fetch(t_begin);
-    for (long t0 = t_begin; t0 < t_end; t0 += 64) {
-        if (t0 + 64 > t_end) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (t0 + (threadIdx.x + 256 * u) / 8 >= t_end) ar[u] = br[u] = u32x4{0u, 0u, 0u, 0u};
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int idx = threadIdx.x + 256 * u, row = idx / 8, c8 = idx % 8;
-            *(u32x4 *)(As + row * TP + c8 * 8) = ar[u];
-            *(u32x4 *)(Bs + row * TP + c8 * 8) = br[u];
-        }
-        __syncthreads();
-        if (t0 + 64 < t_end) fetch(t0 + 64);
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const bf16x8 af = tr_operand(As, TP, 32 * ks, 16 * w, g, i);
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct) acc[ct] = mfma16(af, tr_operand(Bs, TP, 32 * ks, 16 * ct, g, i), acc[ct]);
-        }
-        __syncthreads();
-    }
-    float *out = Part + (size_t)blockIdx.x * (64 * gridDim.y) * ldo;
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) out[(size_t)(a0 + 16 * w + 4 * g + j) * ldo + b0 + 16 * ct + i] = acc[ct][j];
-}
-
-// ---------------------------------------------------------------------------
 // The two products that read the gradient map G = [dQ | dK | dV] ([M][3C]), in one pass over it:
 //     dX = G Wqkv^T                    (derivative of Eq. 3 with respect to X)
 //     dWqkv = X^T G                    (with respect to the weights; contraction over tokens)
@@ -782,31 +724,6 @@ __global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G
     }
 }
 
-// ---------------------------------------------------------------------------
-// WT[o][c] = Wqkv[c][o] ([3C][C]) and WoT[o][c] = Wo[c][o], for the channel counts whose projection
-// launch does not carry the rearrangement along.
-__global__ void k_bwd_transpose(const bf16_t *__restrict__ Wqkv, const bf16_t *__restrict__ Wo,
-                                bf16_t *__restrict__ WT, bf16_t *__restrict__ WoT, int C)
-{
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < 3 * C * C) WT[e] = Wqkv[(size_t)(e % C) * 3 * C + e / C];
-    else if (e < 4 * C * C) WoT[e - 3 * C * C] = Wo[(size_t)((e - 3 * C * C) % C) * C + (e - 3 * C * C) / C];
-}
-
-// ---------------------------------------------------------------------------
-// Token shares of k_gemm_tn: about 384 workgroups over the 64 x 64 output blocks.
-struct TnPlan {
-    int gx, tokens_per_wg;
-};
-
-TnPlan tn_plan(long M, int Ca, int Cb)
-{
-    const long steps = (M + 63) / 64;
-    const long want = std::max(1L, 384L / ((Ca / 64) * (Cb / 64)));
-    const long per_wg = (steps + want - 1) / want;
-    return TnPlan{(int)((steps + per_wg - 1) / per_wg), (int)(per_wg * 64)};
-}
-
 // Tiles of k_bwd_proj per workgroup: all workgroups resident at once.
 struct ProjPlan {
     int tiles, per_wg, groups;
@@ -826,8 +743,11 @@ ProjPlan proj_plan(long M, int C)
 // product for dX and k_gemm_tn for dWqkv.
 bool fused_projection(int C) { return C <= 128; }
 
+// Partial matrices of dWqkv (and of dWo, but for C = 128 where it is a launch of its own).
+int weight_parts(long M, int C) { return fused_projection(C) ? proj_plan(M, C).groups : gemm_tn_shares(M, C, 3 * C, C, C); }
+
 struct BwdWs {
-    bf16_t *q, *k, *v, *dO, *o, *dqkv, *wt, *wot;
+    bf16_t *q, *k, *v, *dO, *o, *dqkv;
     float *lse, *dsum, *part_qkv, *part_o, *part_lce;
     size_t bytes;
 };
@@ -852,12 +772,10 @@ BwdWs carve_bwd(const Dims &D, void *ws)
     w.dqkv = (bf16_t *)take(MC * 6);
     w.lse = (float *)take((size_t)M * D.heads * 4);
     w.dsum = (float *)take((size_t)M * D.heads * 4);
-    w.part_qkv = (float *)take((size_t)(fused_projection(D.C) ? proj_plan(M, D.C).groups : tn_plan(M, D.C, 3 * D.C).gx) *
-                               3 * C * C * 4);
-    w.part_o = (float *)take((size_t)std::max(tn_plan(M, D.C, D.C).gx, proj_plan(M, D.C).groups) * C * C * 4);
+    const int parts = weight_parts(M, D.C);
+    w.part_qkv = (float *)take((size_t)parts * 3 * C * C * 4);
+    w.part_o = (float *)take((size_t)(D.C == 128 ? gemm_tn_shares(M, D.C, D.C, 0, 0) : parts) * C * C * 4);
     w.part_lce = (float *)take((size_t)lce::lce_grad_groups_bf16(D) * 25 * C * 4);
-    w.wt = (bf16_t *)take(3 * C * C * 2);
-    w.wot = (bf16_t *)take(C * C * 2);
     w.bytes = off;
     return w;
 }
@@ -948,22 +866,10 @@ int attn_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, hipStream_t st)
     return attn_bwd_heads<64, 1>(D, w, Ir, st);
 }
 
-int gemm_tn(const bf16_t *A, int lda, int Ca, const bf16_t *Bm, int ldb, int Cb, float *Part, long M, hipStream_t st)
-{
-    const TnPlan t = tn_plan(M, Ca, Cb);
-    ProfScope ps(st, K_GEN_BACKWARD);
-    hipLaunchKernelGGL(k_gemm_tn, dim3(t.gx, Ca / 64, Cb / 64), dim3(256), 0, st, A, lda, Bm, ldb, Part, Cb, M,
-                       t.tokens_per_wg);
-    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
-}
-
 // The routing entries of an image must fit the key-side kernel's list in LDS.
 constexpr int kBwdMaxEntries = 4096;
 
 }  // namespace
-
-// The projection kernels specialised by channel count (they also carry the weight transposes along).
-static bool narrow_projection(int C) { return C == 64 || C == 128 || C == 256; }
 
 bool mfma_backward_supported(const Dims &D)
 {
@@ -984,24 +890,10 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
     const BwdWs w = carve_bwd(D, ws);
     const int C = D.C;
     const long M = (long)D.B * D.N;
-    int rc;
-    if (narrow_projection(C)) {
-        // Q, K, V once more (Eq. 3); the launch also leaves Wqkv^T and Wo^T (a launch of its own for Wo^T
-        // alone was measured 4 us slower)
-        rc = mfma_project_qkv(D, X, Wqkv, w.q, w.k, w.v, st, Wo, w.wt, w.wot);
-        if (rc != BRA_OK) return rc;
-        rc = mfma_project(D, dY, w.wot, w.dO, st);                            // dO = dY Wo^T
-    } else {
-        {
-            ProfScope ps(st, K_GEN_BACKWARD);
-            hipLaunchKernelGGL(k_bwd_transpose, dim3((4 * C * C + 255) / 256), dim3(256), 0, st, (const bf16_t *)Wqkv,
-                               (const bf16_t *)Wo, w.wt, w.wot, C);
-            if (!launched()) return BRA_ERR_LAUNCH;
-        }
-        rc = wide_project_qkv(D, X, Wqkv, w.q, w.k, w.v, st);
-        if (rc != BRA_OK) return rc;
-        rc = gemm_bf16((const bf16_t *)dY, w.wot, M, C, C, w.dO, nullptr, nullptr, false, K_GEN_BACKWARD, st);
-    }
+    // Q, K, V once more (Eq. 3); dO = dY Wo^T
+    int rc = wide_project_qkv(D, X, Wqkv, w.q, w.k, w.v, st);
+    if (rc != BRA_OK) return rc;
+    rc = gemm_bt((const bf16_t *)dY, (const bf16_t *)Wo, C, M, C, C, w.dO, K_GEN_BACKWARD, st);
     if (rc != BRA_OK) return rc;
     rc = attn_bwd(D, w, Ir, st);                                              // O, dQ; then dK, dV
     if (rc != BRA_OK) return rc;
@@ -1027,23 +919,25 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
                                w.dqkv, (const bf16_t *)X, (const bf16_t *)Wqkv, (bf16_t *)dX, w.part_qkv, nullptr,
                                nullptr, nullptr, M, pp.tiles, pp.per_wg);
         if (!launched()) return BRA_ERR_LAUNCH;
+        if (!with_o) {
+            const GemmTn none = {};
+            rc = gemm_tn(GemmTn{w.o, (const bf16_t *)dY, w.part_o, C, C, C, C}, none, M, K_GEN_BACKWARD, st);
+            if (rc != BRA_OK) return rc;
+        }
     } else {
-        rc = gemm_bf16(w.dqkv, w.wt, M, 3 * C, C, (bf16_t *)dX, nullptr, nullptr, false, K_GEN_BACKWARD, st);
+        rc = gemm_bt(w.dqkv, (const bf16_t *)Wqkv, 3 * C, M, 3 * C, C, (bf16_t *)dX, K_GEN_BACKWARD, st);
         if (rc != BRA_OK) return rc;
-        rc = gemm_tn((const bf16_t *)X, C, C, w.dqkv, 3 * C, 3 * C, w.part_qkv, M, st);
-        if (rc != BRA_OK) return rc;
-    }
-    if (!with_o) {
-        rc = gemm_tn(w.o, C, C, (const bf16_t *)dY, C, C, w.part_o, M, st);
+        rc = gemm_tn(GemmTn{(const bf16_t *)X, w.dqkv, w.part_qkv, C, 3 * C, C, 3 * C},
+                     GemmTn{w.o, (const bf16_t *)dY, w.part_o, C, C, C, C}, M, K_GEN_BACKWARD, st);
         if (rc != BRA_OK) return rc;
     }
     {
-        const ReduceJob j0 = reduce_job(w.part_qkv, dWqkv, fused_projection(C) ? pp.groups : tn_plan(M, C, 3 * C).gx,
-                                        3 * C * C);
-        const ReduceJob j1 = reduce_job(w.part_o, dWo, with_o ? pp.groups : tn_plan(M, C, C).gx, C * C);
+        const int parts = weight_parts(M, C);
+        const ReduceJob j0 = reduce_job(w.part_qkv, dWqkv, parts, 3 * C * C);
+        const ReduceJob j1 = reduce_job(w.part_o, dWo, C == 128 ? gemm_tn_shares(M, C, C, 0, 0) : parts, C * C);
         const ReduceJob j2 = reduce_job(w.part_lce, dWlce, lce::lce_grad_groups_bf16(D), 25 * C);
         ProfScope ps(st, K_GEN_BACKWARD);
-        hipLaunchKernelGGL(k_reduce_parts, dim3(j0.blocks + j1.blocks + j2.blocks), dim3(1024), 0, st, j0, j1, j2);
+        hipLaunchKernelGGL(k_reduce_parts, dim3(j0.blocks + j1.blocks + j2.blocks), dim3(256), 0, st, j0, j1, j2);
         if (!launched()) return BRA_ERR_LAUNCH;
     }
     return BRA_OK;
