@@ -209,6 +209,191 @@ __global__ __launch_bounds__(256) void k_attn_gen(AttnArgs A, bf16_t *__restrict
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same for regions of at most 32 tokens (16 NQ of them in NQ query tiles), where the tile of 64 queries above leaves
+// half or more of its wavefronts with copies: a wavefront works on its own, with all queries of a region and 64 channels
+// (2 or 1 heads).  It brings its K and V rows straight from memory into its own part of LDS, 32 keys at a time into one
+// of two buffers while the other is worked on; there is no barrier but the one behind the table of the region's routed
+// origins.  Rows of 128 bytes lie unpadded; 16-byte pieces are exchanged so that the row reads of K (piece c of row r at
+// c ^ r % 8) and the transposing reads of V (c ^ 4 (r / 2 % 2)) meet different banks.
+// The softmax reference moves only when a lane's own score exceeds it by 2^8 (checked without an exchange between
+// lanes); denominators are summed per lane and exchanged once at the end.
+// Bound by the gather out of the L2s: 302 MB for 8 images of 32 x 32 x 768 with 12 regions of 16 tokens each.
+// A direct load of 16 bytes per lane to 1024 consecutive bytes of LDS (l: the same for all lanes) that the compiler does
+// not count: it would wait for all outstanding ones before the next LDS read, those of the buffer in flight among them.
+// The caller waits (s_waitcnt vmcnt) before it reads the buffer.  M0 is the instruction's own here: nothing else in the
+// kernels that use this sets it.
+__device__ __forceinline__ void load_to_lds_untracked(const bf16_t *g, bf16_t *l)
+{
+    const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) bf16_t *)l);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(g) : "memory");
+}
+
+template <int HD, int NQ>
+__global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int groups, int total)
+{
+    constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16, KB = 32;
+    __shared__ __attribute__((aligned(16))) bf16_t S0[4 * 2 * KB * 64];      // [wavefront][K, V][32 keys][64]
+    __shared__ __attribute__((aligned(16))) bf16_t S1[4 * 2 * KB * 64];
+    extern __shared__ int origins[];             // [k]: first token of the routed regions
+    const int C = D.C, ncg = C / 64, n = D.n, kn = D.kn;
+    const int wid = swizzled_block();            // the workgroups of an image share an L2
+    if (wid >= total) return;
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, g = lane / 16, i = lane % 16;
+    const int cg = (wid % groups) * 4 + wave, reg = (wid / groups) % D.R, b = wid / (groups * D.R);
+    const float rw_inv = 1.0f / (float)D.rw, n_inv = 1.0f / (float)n, s_inv = 1.0f / (float)D.S;
+    auto region_origin = [&](int r) {
+        const int ry = fast_div(r, s_inv);
+        return ry * D.rh * D.W + (r - ry * D.S) * D.rw;
+    };
+    auto in_region = [&](int slot) {
+        const int sy = fast_div(slot, rw_inv);
+        return sy * D.W + slot - sy * D.rw;
+    };
+    const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
+    const bool report = A.Ir_out && A.Ir_out != A.Ir_src && wid % groups == 0;
+    for (int p = threadIdx.x; p < D.k; p += 256) {
+        const int j = irp[p];
+        origins[p] = region_origin(region_index(j, D.R));
+        if (report) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = j;
+    }
+    __syncthreads();
+    if (cg >= ncg) return;
+
+    const size_t img = (size_t)b * D.N * C + 64 * cg;
+    const int origin = region_origin(reg);
+    size_t qtok[NQ];
+    bf16x8 qf[NQ][HPW][KSD];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        qtok[q] = (size_t)origin + in_region(min(16 * q + i, n - 1));
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+            for (int ks = 0; ks < KSD; ++ks)
+                qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + HD * hh + 32 * ks + 8 * g);
+    }
+    // the operands have arrived before the loop: otherwise the compiler waits for them, and with them for the direct loads
+    // in flight, in every pass
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+            for (int ks = 0; ks < KSD; ++ks) asm volatile("" : "+v"(qf[q][hh][ks]));
+    // direct loads: 8 rows of 8 pieces each
+    auto request = [&](int k0, bf16_t *S) {
+        bf16_t *Ks = S + wave * 2 * KB * 64, *Vs = Ks + KB * 64;
+#pragma unroll
+        for (int u = 0; u < KB / 8; ++u) {
+            const int row = 8 * u + lane / 8, key = min(k0 + row, kn - 1), p = fast_div(key, n_inv);
+            const size_t at = img + (size_t)(origins[p] + in_region(key - p * n)) * C;
+            load_to_lds_untracked(A.K + at + 8 * ((lane % 8) ^ (row % 8)), Ks + 512 * u);
+            load_to_lds_untracked(A.V + at + 8 * ((lane % 8) ^ (4 * (row / 2 % 2))), Vs + 512 * u);
+        }
+    };
+    float m[NQ][HPW], l[NQ][HPW];
+    f32x4 acc[NQ][HPW][NDT];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh) {
+            m[q][hh] = -INFINITY;
+            l[q][hh] = 0.f;
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    const float lim = 8.0f / A.c_exp;
+    auto block = [&](int k0, const bf16_t *S) {
+        const bf16_t *Ks = S + wave * 2 * KB * 64, *Vs = Ks + KB * 64;
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh) {
+            bf16x8 kf[2][KSD], vf[NDT];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int ks = 0; ks < KSD; ++ks) {
+                    const int row = 16 * t + i, piece = HD / 8 * hh + 4 * ks + g;
+                    kf[t][ks] = *(const bf16x8 *)(Ks + row * 64 + 8 * (piece ^ (row % 8)));
+                }
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) {
+                u32x2 r[2];
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    const int row = 16 * half + 4 * g + i / 4, col = HD * hh + 16 * dt + 4 * (i % 4);
+                    r[half] = __builtin_bit_cast(u32x2, lds_read_tr16(Vs + row * 64 + 8 * ((col / 8) ^ (4 * (row / 2 % 2))) + col % 8));
+                }
+                vf[dt] = __builtin_bit_cast(bf16x8, u32x4{r[0][0], r[0][1], r[1][0], r[1][1]});
+            }
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                f32x4 s[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < KSD; ++ks) s[t] = mfma16(kf[t][ks], qf[q][hh][ks], s[t]);   // S^T[key 16 t + 4 g + j][query i]
+                }
+                if (k0 + KB > kn) {
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (k0 + 16 * t + 4 * g + j >= kn) s[t][j] = -INFINITY;
+                }
+                float mx = s[0][0];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) mx = fmaxf(mx, s[t][j]);
+                if (__builtin_amdgcn_ballot_w64(mx > m[q][hh] + lim) != 0) {
+                    const float m_new = fmaxf(m[q][hh], cross_row_max(mx));
+                    const float alpha = __builtin_amdgcn_exp2f((m[q][hh] - m_new) * A.c_exp);
+                    m[q][hh] = m_new;
+                    l[q][hh] *= alpha;
+#pragma unroll
+                    for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] *= alpha;
+                }
+                const float mc = m[q][hh] * A.c_exp;
+                float p[8];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        p[4 * t + j] = __builtin_amdgcn_exp2f(fmaf(s[t][j], A.c_exp, -mc));
+                        l[q][hh] += p[4 * t + j];
+                    }
+                const bf16x8 pb = pack8(p);
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = mfma16(vf[dt], pb, acc[q][hh][dt]);
+            }
+        }
+    };
+    const int last = kn - 1;
+    request(0, S0);
+    for (int k0 = 0; k0 < kn; k0 += 2 * KB) {
+        request(min(k0 + KB, last), S1);                      // past the end: not used
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");      // the 8 loads of the block before have arrived
+        block(k0, S0);
+        if (k0 + KB >= kn) break;
+        request(min(k0 + 2 * KB, last), S0);
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        block(k0 + KB, S1);
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        if (16 * q + i >= n) continue;
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh) {
+            const float inv = 1.0f / cross_row_sum(l[q][hh]);
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt)
+                *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(acc[q][hh][dt] * inv);
+        }
+    }
+}
+
 struct WideWs {
     bf16_t *q, *k, *v, *o;
     float *xr, *qr, *kr;
@@ -249,6 +434,17 @@ void launch_pool(const Dims &D, const bf16_t *X, const WideWs &w, hipStream_t st
 GemmRegions region_job(const Dims &D, const WideWs &w)
 {
     return GemmRegions{w.xr, (long)D.B * D.R, 2 * D.C, {w.qr, w.kr}, D.C};
+}
+
+void launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
+{
+    const int groups = (D.C / 64 + 3) / 4, total = D.B * D.R * groups;
+    const dim3 grid((unsigned)((total + 7) / 8 * 8)), block(256);
+    const size_t smem = (size_t)D.k * sizeof(int);
+    if (D.d == 32 && D.n <= 16) hipLaunchKernelGGL((k_attn_rows<32, 1>), grid, block, smem, st, A, O, D, groups, total);
+    else if (D.d == 32) hipLaunchKernelGGL((k_attn_rows<32, 2>), grid, block, smem, st, A, O, D, groups, total);
+    else if (D.n <= 16) hipLaunchKernelGGL((k_attn_rows<64, 1>), grid, block, smem, st, A, O, D, groups, total);
+    else hipLaunchKernelGGL((k_attn_rows<64, 2>), grid, block, smem, st, A, O, D, groups, total);
 }
 
 // Pooling, region-level projections, A^r rows and top-k on their own.
@@ -331,7 +527,8 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
         {
             const unsigned grid = (unsigned)((long)D.B * D.R * ((D.n + 63) / 64) * (D.C / 64));
             ProfScope ps(st, K_MFMA_ATTENTION);
-            if (D.d == 32) hipLaunchKernelGGL(k_attn_gen<32>, dim3(grid), dim3(256), 0, st, A, w.o, D);
+            if (D.n <= 32) launch_attn_rows(D, A, w.o, st);
+            else if (D.d == 32) hipLaunchKernelGGL(k_attn_gen<32>, dim3(grid), dim3(256), 0, st, A, w.o, D);
             else hipLaunchKernelGGL(k_attn_gen<64>, dim3(grid), dim3(256), 0, st, A, w.o, D);
         }
         rc = lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);

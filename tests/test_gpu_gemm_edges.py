@@ -22,3 +22,20 @@ EDGES = [  # (B, H, W, C, heads, S, k)
 def test_gemm_tiles(B, H, W, C, heads, S, k):
     X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=8500 + B + C, dtype="bf16")
     compare(X, Wqkv, Wo, Wlce, "bf16", S, k, heads, "mfma", images=[0, B - 1] if B > 1 else None)
+
+
+ROWS = [  # (B, H, W, C, heads, S, k): one wavefront per region and 64 channels: query tiles of 16 and 32, ragged key blocks,
+          # several 32-key blocks, idle wavefronts in the last group, two heads of 32 or one of 64 per wavefront
+    (2, 12, 12, 192, 3, 3, 2),       # n = 16, 32 keys: one block
+    (1, 15, 9, 320, 5, 3, 3),        # n = 15, 45 keys, five groups of 64 channels
+    (1, 12, 15, 384, 12, 3, 5),      # n = 20, 100 keys, heads of 32
+    (2, 8, 16, 64, 1, 2, 3),         # n = 32, 96 keys
+    (1, 22, 6, 192, 6, 2, 1),        # n = 33: the 64-query kernel
+    (1, 6, 6, 512, 8, 6, 36),        # n = 1, heads of 64, 36 keys
+]
+
+
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", ROWS)
+def test_attention_rows(B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=8700 + H * W + C, dtype="bf16")
+    compare(X, Wqkv, Wo, Wlce, "bf16", S, k, heads, "mfma")
