@@ -5,6 +5,11 @@
 
 namespace bra {
 
+// Rows are the tokens of Hp x Wp maps of which only the top-left H x W part exists in memory (Hp = 0: they all do).
+struct GemmRows {
+    int Hp = 0, Wp = 0, H = 0, W = 0;
+};
+
 // Where a product goes: output column o to buffer o / cols (up to three buffers of `cols` columns each, e.g. Q, K, V),
 // column o % cols; cols is a multiple of 8.
 struct GemmOut {
@@ -16,6 +21,8 @@ struct GemmOut {
     const float *bias;
     const bf16_t *res;
     int gelu;
+    float scale0 = 1.0f;        // bf16 output only: factor of what goes to buf[0] (not of its float32 copy)
+    GemmRows in_rows, out_rows; // bf16 output only: missing rows of In read as zeros, missing rows of the buffers are not written
 };
 
 // A second product with the same W and K whose input is float32 and enters as three exact bf16 terms, with float32

@@ -157,14 +157,17 @@ __global__ __launch_bounds__(256) void k_gemm(const void *__restrict__ In, const
 // runs of 8 consecutive outputs of one row of In per 32 outputs (see the operand layouts in bra_mfma.hip).
 // What bounds it (8192 x 768 x 2304, 128 x 128 tiles): direct loads alone 24 us (18 TB/s out of the L2s), products with
 // their LDS reads alone 23, stores alone 9.5; they overlap to 47, with 2.25 workgroups per slot in three rounds.
-__device__ __forceinline__ void load_to_lds(const bf16_t *g, bf16_t *l)
-{
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) unsigned *)g,
-                                     (__attribute__((address_space(3))) unsigned *)l, 16, 0, 0);
-}
-
 // BT: W is given transposed, [Nout][ldw] with the contraction axis contiguous; its chunk then lies like In's and needs no
 // transposing reads.
+__device__ bf16_t zero_row[4096];        // what missing rows of In read (never written)
+
+// Row of the map in memory that row m of the padded map is, or -1.
+__device__ __forceinline__ long stored_row(const GemmRows &r, int m)
+{
+    const int hw = r.Hp * r.Wp, b = m / hw, t = m - b * hw, y = t / r.Wp, x = t - y * r.Wp;
+    return y < r.H && x < r.W ? ((long)b * r.H + y) * r.W + x : -1;
+}
+
 template <int BM, int BN, bool REGIONS, bool BT>
 __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) void k_gemm_dma(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw,
                                                   int M, int K, int Nout, GemmOut out, GemmRegions reg, int reg_blocks)
@@ -195,6 +198,10 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
     for (int u = 0; u < LA; ++u) {
         const int row = 8 * (wave * LA + u) + lane / 8, piece = (lane % 8) ^ (row % 8);
         ap[u] = In + (size_t)min(m0 + row, M - 1) * K + 8 * piece;
+        if (out.in_rows.Hp) {
+            const long at = stored_row(out.in_rows, min(m0 + row, M - 1));
+            ap[u] = (at >= 0 ? In + (size_t)at * K : zero_row) + 8 * piece;
+        }
     }
     constexpr int CH = BN / 8, RPI = 64 / CH;     // pieces of a row of W, rows per direct load
 #pragma unroll
@@ -278,7 +285,7 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
     }
     __syncthreads();
     if (K % 128) multiply(A0, B0);
-    const bool extras = out.bias || out.gelu || out.res;
+    const bool extras = out.bias || out.gelu || out.res || out.scale0 != 1.0f;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         // a 32-output tile lies in one buffer (cols is a multiple of 32): looked up once per tile, for the whole wavefront
@@ -290,7 +297,12 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
         for (int mt = 0; mt < MT; ++mt) {
             const int m = m0 + wm + 32 * mt + c;
             if (m >= M) continue;
-            const size_t row = (size_t)m * out.cols;
+            size_t row = (size_t)m * out.cols;
+            if (out.out_rows.Hp) {
+                const long at = stored_row(out.out_rows, m);
+                if (at < 0) continue;
+                row = (size_t)at * out.cols;
+            }
 #pragma unroll
             for (int run = 0; run < 2; ++run) {
                 const int o = ot + 16 * run + 8 * h, col = ct + 16 * run + 8 * h;
@@ -303,6 +315,10 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
                     *(f32x4 *)(fbuf + row + col + 4) = f32x4{v[4], v[5], v[6], v[7]};
                 }
                 if (extras) {
+                    if (which == 0 && out.scale0 != 1.0f) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) v[e] *= out.scale0;
+                    }
                     if (out.bias) {
                         const f32x4 b0 = *(const f32x4 *)(out.bias + o), b1 = *(const f32x4 *)(out.bias + o + 4);
 #pragma unroll
@@ -489,7 +505,7 @@ bool sizes_ok(long M, int K, int Nout) { return M >= 1 && M <= 0x7fffffffL && K 
 int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, const GemmRegions *regions,
          int kernel_id, hipStream_t st)
 {
-    if (!sizes_ok(M, K, Nout) || (out.cols % 32 && out.cols != Nout)) return BRA_ERR_UNSUPPORTED;
+    if (!sizes_ok(M, K, Nout) || (out.cols % 32 && out.cols != Nout) || (out.in_rows.Hp && K > 4096)) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);
     if (regions) return launch_big<true>(In, W, ldw, M, K, Nout, out, *regions, st);
     return launch_big<false>(In, W, ldw, M, K, Nout, out, GemmRegions{}, st);

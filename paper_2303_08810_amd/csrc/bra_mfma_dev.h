@@ -104,6 +104,14 @@ __device__ __forceinline__ s16x4 lds_read_tr16(const bf16_t *p)
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)p);
 }
 
+// 16 bytes per lane straight from memory into 1024 consecutive bytes of LDS (l: the same for all lanes); a barrier waits
+// for the ones before it.
+__device__ __forceinline__ void load_to_lds(const bf16_t *g, bf16_t *l)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) unsigned *)g,
+                                     (__attribute__((address_space(3))) unsigned *)l, 16, 0, 0);
+}
+
 // A 16-byte store to global memory.  MODE 0: an ordinary store (the line stays dirty in this
 // XCD's L2 until it is evicted or the kernel ends); 1: with the streaming hint; 2: written through
 // to memory (system scope), so that the write-back does not wait for the end of the kernel.
@@ -644,6 +652,6 @@ size_t wide_workspace_bytes(const Dims &D);
 int wide_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *ws,
                hipStream_t st);
 int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo, const void *Wlce, void *Y,
-                 int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st);
+                 int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st, int H = 0, int W = 0);
 
 }  // namespace bra

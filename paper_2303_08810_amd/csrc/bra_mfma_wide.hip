@@ -23,11 +23,13 @@ using namespace mfma;
 
 namespace {
 
-// SUB (1, 2, 4 or 8) consecutive lanes share one (image, region, 8-channel chunk): lane s adds
+// SUB (a power of two up to 32) consecutive lanes share one (image, region, 8-channel chunk): lane s adds
 // tokens s, s + SUB, .. of the region (row-major), then the partial sums are combined pairwise
 // in a fixed order.
+// PAD: X is the caller's map of pad.H x pad.W tokens, zero beyond.
+template <bool PAD>
 __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X, float *__restrict__ Xr, Dims D,
-                                                   int SUB)
+                                                   int SUB, GemmRows pad)
 {
     const int CH = D.C / 8;
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
@@ -36,12 +38,15 @@ __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X,
     const bool valid = item < (long)D.B * D.R * CH;
     const long it = valid ? item : 0;
     const int cc = (int)(it % CH), r = (int)((it / CH) % D.R), b = (int)(it / ((long)CH * D.R));
-    const bf16_t *base = X + (((size_t)b * D.H + (r / D.S) * D.rh) * D.W + (r % D.S) * D.rw) * D.C + cc * 8;
+    const int H = PAD ? pad.H : D.H, W = PAD ? pad.W : D.W, y0 = (r / D.S) * D.rh, x0 = (r % D.S) * D.rw;
+    const bf16_t *base = X + (((size_t)b * H + y0) * W + x0) * D.C + cc * 8;
     const float rw_inv = 1.0f / (float)D.rw;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int slot = sub; slot < D.n; slot += SUB) {
         const int y = fast_div(slot, rw_inv), x = slot - y * D.rw;
-        const u32x4 v = *(const u32x4 *)(base + ((size_t)y * D.W + x) * D.C);
+        const bool in = !PAD || (y0 + y < H && x0 + x < W);
+        u32x4 v = *(const u32x4 *)(in ? base + ((size_t)y * W + x) * D.C : X);
+        if (PAD && !in) v = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             acc[2 * e] += bf16_lo(v[e]);
@@ -60,30 +65,72 @@ __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X,
 }
 
 // ---------------------------------------------------------------------------
-// Routed attention (Eq. 6, Eq. 1) for any region size and heads of 32 or 64 channels:
-// workgroup (image, region, tile of 64 queries of the region, group of 64 channels = 2 or
-// 1 heads), wavefront w with queries 16 w .. 16 w + 15 of the tile.  The k n routed keys are
-// taken 64 at a time: their K and V rows (the group's 128 bytes each, found by index in the
-// projected maps) are copied into LDS with coalesced loads, the next block being requested
-// while the current one is worked on; S^T = K Q^T, one softmax over all routed keys (lazy
-// reference, see softmax_pv_rows), O^T += V^T P^T by the transposing LDS read.  Queries past
-// the end of the region and keys past k n repeat the last one and are masked.
-template <int HD>
-__global__ __launch_bounds__(256) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D)
+// Routed attention (Eq. 6, Eq. 1) for any region size and heads of 32 or 64 channels.  Q comes multiplied by
+// scale * log2(e), so scores are exponents of 2.
+//
+// Softmax step shared by the two kernels below, for KT tiles of 16 keys x 16 queries of one head: scores
+// s[t][j] = S^T[key 16 t + 4 g + j][query i] relative to the reference m (which entered the product as its accumulator
+// input, so a score costs no subtraction), weights p = 2^s in the operand order of O^T += V^T P^T.  The reference moves,
+// and the sums are rescaled, only when a lane's own score exceeds it by 8 (weights stay below 2^8), which needs no exchange
+// between lanes; the quotient O / l does not depend on it.  FIRST: the reference is this block's maximum.
+template <bool FIRST, int KT, int NDT>
+__device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, f32x4 &l, f32x4 (&acc)[NDT], bf16x8 (&pb)[KT / 2])
 {
-    constexpr int HPW = 64 / HD;          // heads of this workgroup
-    constexpr int KSD = HD / 32;          // contraction steps of a score
-    constexpr int NDT = HD / 16;          // 16-channel tiles of a head's output
-    constexpr int XP = 64 + 16;
-    __shared__ __attribute__((aligned(16))) bf16_t Ks[64 * XP];
-    __shared__ __attribute__((aligned(16))) bf16_t Vs[64 * XP];
+    float mx = s[0][0];
+#pragma unroll
+    for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mx = fmaxf(mx, s[t][j]);
+    if (FIRST || __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0) {
+        const float up = FIRST ? cross_row_max(mx) : fmaxf(cross_row_max(mx), 0.f);
+        m += up;
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s[t][j] -= up;
+        if (!FIRST) {
+            const float alpha = __builtin_amdgcn_exp2f(-up);
+            l *= alpha;
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
+        }
+    }
+#pragma unroll
+    for (int tp = 0; tp < KT / 2; ++tp) {
+        float p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(s[2 * tp + e / 4][e % 4]);
+        pb[tp] = pack8(p);
+        // denominators of the same rounded weights, from a product with an all-ones operand
+        const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+        l = mfma16(__builtin_bit_cast(bf16x8, ones), pb[tp], l);
+    }
+}
+
+// Regions of more than 32 tokens: workgroup (image, region, tile of 64 NQ queries of the region, group of 64 channels = 2
+// or 1 heads), wavefront w with NQ query tiles of 16.  The k n routed keys are taken 64 at a time: their K and V rows (the
+// group's 128 bytes each, found by index in the projected maps) go straight from memory into one of two LDS buffers while
+// the other is worked on; 16-byte pieces are exchanged so that K's row reads (piece c of row r at c ^ r % 8) and V's
+// transposing reads (c ^ 4 (r / 2 % 2)) meet different banks.  Queries past the end of the region and keys past k n
+// repeat the last one and are masked.
+// Bound by vector issue, most of it the 2^x (a quarter-rate instruction per score); a score costs half a maximum, half a
+// conversion and no other vector instruction.  2 x 208 x 304 x 64, 16 x 16 regions, k = 4: 74 us with two query tiles per
+// wavefront and 256 registers, 81 with one and 170; with 170 registers for two tiles 91, with 128 160 (spills).
+template <int HD, int NQ>
+__global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles)
+{
+    constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16;
+    __shared__ __attribute__((aligned(16))) bf16_t K0[64 * 64];
+    __shared__ __attribute__((aligned(16))) bf16_t K1[64 * 64];
+    __shared__ __attribute__((aligned(16))) bf16_t V0[64 * 64];
+    __shared__ __attribute__((aligned(16))) bf16_t V1[64 * 64];
+    extern __shared__ int origins[];             // [k]: first token of the routed regions
     const int C = D.C, ncg = C / 64, n = D.n, kn = D.kn;
-    const int qtiles = (n + 63) / 64;
     const int cg = blockIdx.x % ncg, qt = (blockIdx.x / ncg) % qtiles;
     const int reg = (blockIdx.x / (ncg * qtiles)) % D.R, b = blockIdx.x / (ncg * qtiles * D.R);
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const float rw_inv = 1.0f / (float)D.rw, n_inv = 1.0f / (float)n, s_inv = 1.0f / (float)D.S;
-    const size_t img_off = (size_t)b * D.N * C + 64 * cg;
+    const size_t img = (size_t)b * D.N * C + 64 * cg;
     auto region_origin = [&](int r) {
         const int ry = fast_div(r, s_inv);
         return ry * D.rh * D.W + (r - ry * D.S) * D.rw;
@@ -93,118 +140,118 @@ __global__ __launch_bounds__(256) void k_attn_gen(AttnArgs A, bf16_t *__restrict
         return sy * D.W + slot - sy * D.rw;
     };
     const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
-    if (A.Ir_out && A.Ir_out != A.Ir_src && qt == 0 && cg == 0)
-        for (int p = tid; p < D.k; p += 256) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = irp[p];
-
-    const int slot = 64 * qt + 16 * wave + i;
-    const size_t qtok = (size_t)region_origin(reg) + in_region(min(slot, n - 1));
-    bf16x8 qf[HPW][KSD];
+    const bool report = A.Ir_out && A.Ir_out != A.Ir_src && qt == 0 && cg == 0;
+    for (int p = tid; p < D.k; p += 256) {
+        const int j = irp[p];
+        origins[p] = region_origin(region_index(j, D.R));
+        if (report) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = j;
+    }
+    size_t qtok[NQ];
+    bf16x8 qf[NQ][HPW][KSD];
 #pragma unroll
-    for (int hh = 0; hh < HPW; ++hh)
+    for (int q = 0; q < NQ; ++q) {
+        qtok[q] = (size_t)region_origin(reg) + in_region(min(64 * NQ * qt + 16 * (NQ * wave + q) + i, n - 1));
 #pragma unroll
-        for (int ks = 0; ks < KSD; ++ks)
-            qf[hh][ks] = *(const bf16x8 *)(A.Q + img_off + qtok * C + HD * hh + 32 * ks + 8 * g);
-
-    u32x4 kreg[2], vreg[2];
-    auto request = [&](int k0) {
+        for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+            for (int ks = 0; ks < KSD; ++ks)
+                qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + HD * hh + 32 * ks + 8 * g);
+    }
+    // direct loads: a wavefront brings rows 16 w .. 16 w + 15 of K and V, 8 rows of 8 pieces each
+    auto request = [&](int k0, bf16_t *Ks, bf16_t *Vs) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int idx = tid + 256 * u;                       // (key of the block, 16-byte piece)
-            const int key = min(k0 + idx / 8, kn - 1);
-            const int p = fast_div(key, n_inv);
-            const size_t tok = (size_t)region_origin(region_index(irp[p], D.R)) + in_region(key - p * n);
-            const size_t off = img_off + tok * C + (idx % 8) * 8;
-            kreg[u] = *(const u32x4 *)(A.K + off);
-            vreg[u] = *(const u32x4 *)(A.V + off);
+            const int row = 16 * wave + 8 * u + lane / 8, key = min(k0 + row, kn - 1), p = fast_div(key, n_inv);
+            const size_t at = img + (size_t)(origins[p] + in_region(key - p * n)) * C;
+            load_to_lds(A.K + at + 8 * ((lane % 8) ^ (row % 8)), Ks + 512 * (2 * wave + u));
+            load_to_lds(A.V + at + 8 * ((lane % 8) ^ (4 * (row / 2 % 2))), Vs + 512 * (2 * wave + u));
         }
     };
-    float m[HPW], l[HPW];
-    f32x4 acc[HPW][NDT];
+    float m[NQ][HPW];
+    f32x4 l[NQ][HPW], acc[NQ][HPW][NDT];
 #pragma unroll
-    for (int hh = 0; hh < HPW; ++hh) {
-        m[hh] = -INFINITY;
-        l[hh] = 0.f;
-#pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) acc[hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    const float lim = 8.0f / A.c_exp;
-    request(0);
-    for (int k0 = 0; k0 < kn; k0 += 64) {
-        if (k0) __syncthreads();              // the previous block has been read
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int idx = tid + 256 * u;
-            *(u32x4 *)(Ks + (idx / 8) * XP + (idx % 8) * 8) = kreg[u];
-            *(u32x4 *)(Vs + (idx / 8) * XP + (idx % 8) * 8) = vreg[u];
-        }
-        if (k0 + 64 < kn) request(k0 + 64);
-        __syncthreads();
+    for (int q = 0; q < NQ; ++q)
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            f32x4 s[4];
+            m[q][hh] = 0.f;
+            l[q][hh] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    auto block = [&](int k0, const bf16_t *Ks, const bf16_t *Vs, auto first) {
 #pragma unroll
-                for (int ks = 0; ks < KSD; ++ks) {
-                    const bf16x8 kf = *(const bf16x8 *)(Ks + (16 * t + i) * XP + HD * hh + 32 * ks + 8 * g);
-                    s[t] = mfma16(kf, qf[hh][ks], s[t]);        // S^T[key 16 t + 4 g + jj][query i]
-                }
-            }
-            if (k0 + 64 > kn) {
+        for (int hh = 0; hh < HPW; ++hh) {
+            bf16x8 pb[NQ][2];
+            {
+                bf16x8 kf[4][KSD];
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
-                    for (int jj = 0; jj < 4; ++jj)
-                        if (k0 + 16 * t + 4 * g + jj >= kn) s[t][jj] = -INFINITY;
-            }
-            float mx = s[0][0];
+                    for (int ks = 0; ks < KSD; ++ks) {
+                        const int row = 16 * t + i, piece = HD / 8 * hh + 4 * ks + g;
+                        kf[t][ks] = *(const bf16x8 *)(Ks + row * 64 + 8 * (piece ^ (row % 8)));
+                    }
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+                for (int q = 0; q < NQ; ++q) {
+                    f32x4 s[4];
+                    const float neg = -m[q][hh];
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj) mx = fmaxf(mx, s[t][jj]);
-            mx = cross_row_max(mx);
-            if (__builtin_amdgcn_ballot_w64(mx > m[hh] + lim) != 0) {
-                const float m_new = fmaxf(m[hh], mx);
-                const float alpha = __builtin_amdgcn_exp2f((m[hh] - m_new) * A.c_exp);
-                m[hh] = m_new;
-                l[hh] *= alpha;
+                    for (int t = 0; t < 4; ++t) {
+                        s[t] = f32x4{neg, neg, neg, neg};
 #pragma unroll
-                for (int dt = 0; dt < NDT; ++dt) acc[hh][dt] *= alpha;
-            }
-            const float mc = m[hh] * A.c_exp;
-            float p[4][4], ls = 0.f;
+                        for (int ks = 0; ks < KSD; ++ks) s[t] = mfma16(kf[t][ks], qf[q][hh][ks], s[t]);
+                    }
+                    if (k0 + 64 > kn) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+                        for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    p[t][jj] = __builtin_amdgcn_exp2f(fmaf(s[t][jj], A.c_exp, -mc));
-                    ls += p[t][jj];
+                            for (int j = 0; j < 4; ++j)
+                                if (k0 + 16 * t + 4 * g + j >= kn) s[t][j] = -INFINITY;
+                    }
+                    softmax_step<decltype(first)::value>(s, m[q][hh], l[q][hh], acc[q][hh], pb[q]);
+                    if (NQ > 1) __builtin_amdgcn_sched_barrier(0);
                 }
-            l[hh] += cross_row_sum(ls);
+            }
 #pragma unroll
-            for (int tp = 0; tp < 2; ++tp) {
-                const float pv[8] = {p[2 * tp][0], p[2 * tp][1], p[2 * tp][2], p[2 * tp][3],
-                                     p[2 * tp + 1][0], p[2 * tp + 1][1], p[2 * tp + 1][2], p[2 * tp + 1][3]};
-                const bf16x8 pb = pack8(pv);
-                const bf16_t *vp = Vs + (32 * tp + 4 * g + i / 4) * XP + HD * hh + 4 * (i % 4);
+            for (int tp = 0; tp < 2; ++tp)
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt) {
-                    const u32x2 v0 = __builtin_bit_cast(u32x2, lds_read_tr16(vp + 16 * dt));
-                    const u32x2 v1 = __builtin_bit_cast(u32x2, lds_read_tr16(vp + 16 * XP + 16 * dt));
-                    acc[hh][dt] = mfma16(__builtin_bit_cast(bf16x8, u32x4{v0[0], v0[1], v1[0], v1[1]}), pb,
-                                         acc[hh][dt]);
+                    u32x2 r[2];
+#pragma unroll
+                    for (int half = 0; half < 2; ++half) {
+                        const int row = 32 * tp + 16 * half + 4 * g + i / 4, col = HD * hh + 16 * dt + 4 * (i % 4);
+                        r[half] = __builtin_bit_cast(u32x2, lds_read_tr16(Vs + row * 64 + 8 * ((col / 8) ^ (4 * (row / 2 % 2))) + col % 8));
+                    }
+                    const bf16x8 vf = __builtin_bit_cast(bf16x8, u32x4{r[0][0], r[0][1], r[1][0], r[1][1]});
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) acc[q][hh][dt] = mfma16(vf, pb[q][tp], acc[q][hh][dt]);
                 }
-            }
+            __builtin_amdgcn_sched_barrier(0);    // one head at a time: interleaved, they take twice the registers
         }
+    };
+    __syncthreads();                              // the table is in place
+    request(0, K0, V0);
+    __syncthreads();                              // a barrier waits for the direct loads before it
+    if (64 < kn) request(64, K1, V1);
+    block(0, K0, V0, std::true_type{});
+    for (int k0 = 64; k0 < kn; k0 += 128) {
+        __syncthreads();
+        if (k0 + 64 < kn) request(k0 + 64, K0, V0);
+        block(k0, K1, V1, std::false_type{});
+        if (k0 + 64 >= kn) break;
+        __syncthreads();
+        if (k0 + 128 < kn) request(k0 + 128, K1, V1);
+        block(k0 + 64, K0, V0, std::false_type{});
     }
-    if (slot < n) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        if (64 * NQ * qt + 16 * (NQ * wave + q) + i >= n) continue;
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            const float inv = 1.0f / l[hh];
+            const float inv = 1.0f / l[q][hh][0];
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt)
-                *(u32x2 *)(O + img_off + qtok * C + HD * hh + 16 * dt + 4 * g) = pack4(acc[hh][dt] * inv);
+                *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(acc[q][hh][dt] * inv);
         }
     }
 }
@@ -216,8 +263,6 @@ __global__ __launch_bounds__(256) void k_attn_gen(AttnArgs A, bf16_t *__restrict
 // of two buffers while the other is worked on; there is no barrier but the one behind the table of the region's routed
 // origins.  Rows of 128 bytes lie unpadded; 16-byte pieces are exchanged so that the row reads of K (piece c of row r at
 // c ^ r % 8) and the transposing reads of V (c ^ 4 (r / 2 % 2)) meet different banks.
-// The softmax reference moves only when a lane's own score exceeds it by 2^8 (checked without an exchange between
-// lanes); denominators are summed per lane and exchanged once at the end.
 // Bound by the gather out of the L2s: 302 MB for 8 images of 32 x 32 x 768 with 12 regions of 16 tokens each.
 // A direct load of 16 bytes per lane to 1024 consecutive bytes of LDS (l: the same for all lanes) that the compiler does
 // not count: it would wait for all outstanding ones before the next LDS read, those of the buffer in flight among them.
@@ -292,19 +337,18 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
             load_to_lds_untracked(A.V + at + 8 * ((lane % 8) ^ (4 * (row / 2 % 2))), Vs + 512 * u);
         }
     };
-    float m[NQ][HPW], l[NQ][HPW];
-    f32x4 acc[NQ][HPW][NDT];
+    float m[NQ][HPW];
+    f32x4 l[NQ][HPW], acc[NQ][HPW][NDT];
 #pragma unroll
     for (int q = 0; q < NQ; ++q)
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            m[q][hh] = -INFINITY;
-            l[q][hh] = 0.f;
+            m[q][hh] = 0.f;
+            l[q][hh] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-    const float lim = 8.0f / A.c_exp;
-    auto block = [&](int k0, const bf16_t *S) {
+    auto block = [&](int k0, const bf16_t *S, auto first) {
         const bf16_t *Ks = S + wave * 2 * KB * 64, *Vs = Ks + KB * 64;
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
@@ -329,9 +373,10 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 f32x4 s[2];
+                const float neg = -m[q][hh];
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
-                    s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    s[t] = f32x4{neg, neg, neg, neg};
 #pragma unroll
                     for (int ks = 0; ks < KSD; ++ks) s[t] = mfma16(kf[t][ks], qf[q][hh][ks], s[t]);   // S^T[key 16 t + 4 g + j][query i]
                 }
@@ -342,51 +387,33 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
                         for (int j = 0; j < 4; ++j)
                             if (k0 + 16 * t + 4 * g + j >= kn) s[t][j] = -INFINITY;
                 }
-                float mx = s[0][0];
+                bf16x8 pb[1];
+                softmax_step<decltype(first)::value>(s, m[q][hh], l[q][hh], acc[q][hh], pb);
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) mx = fmaxf(mx, s[t][j]);
-                if (__builtin_amdgcn_ballot_w64(mx > m[q][hh] + lim) != 0) {
-                    const float m_new = fmaxf(m[q][hh], cross_row_max(mx));
-                    const float alpha = __builtin_amdgcn_exp2f((m[q][hh] - m_new) * A.c_exp);
-                    m[q][hh] = m_new;
-                    l[q][hh] *= alpha;
-#pragma unroll
-                    for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] *= alpha;
-                }
-                const float mc = m[q][hh] * A.c_exp;
-                float p[8];
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        p[4 * t + j] = __builtin_amdgcn_exp2f(fmaf(s[t][j], A.c_exp, -mc));
-                        l[q][hh] += p[4 * t + j];
-                    }
-                const bf16x8 pb = pack8(p);
-#pragma unroll
-                for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = mfma16(vf[dt], pb, acc[q][hh][dt]);
+                for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = mfma16(vf[dt], pb[0], acc[q][hh][dt]);
             }
         }
     };
     const int last = kn - 1;
     request(0, S0);
-    for (int k0 = 0; k0 < kn; k0 += 2 * KB) {
-        request(min(k0 + KB, last), S1);                      // past the end: not used
-        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");      // the 8 loads of the block before have arrived
-        block(k0, S0);
-        if (k0 + KB >= kn) break;
-        request(min(k0 + 2 * KB, last), S0);
+    request(min(KB, last), S1);                               // past the end: not used
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");          // the 8 loads of the block before have arrived
+    block(0, S0, std::true_type{});
+    for (int k0 = KB; k0 < kn; k0 += 2 * KB) {
+        request(min(k0 + KB, last), S0);
         asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        block(k0 + KB, S1);
+        block(k0, S1, std::false_type{});
+        if (k0 + KB >= kn) break;
+        request(min(k0 + 2 * KB, last), S1);
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        block(k0 + KB, S0, std::false_type{});
     }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         if (16 * q + i >= n) continue;
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            const float inv = 1.0f / cross_row_sum(l[q][hh]);
+            const float inv = 1.0f / l[q][hh][0];
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt)
                 *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(acc[q][hh][dt] * inv);
@@ -422,13 +449,17 @@ WideWs carve(const Dims &D, void *ws)
     return w;
 }
 
-void launch_pool(const Dims &D, const bf16_t *X, const WideWs &w, hipStream_t st)
+void launch_pool(const Dims &D, const bf16_t *X, const WideWs &w, const GemmRows &pad, hipStream_t st)
 {
-    int sub = 1;                                           // lanes per (region, chunk)
-    while (sub < 8 && 2 * sub <= D.n) sub *= 2;
+    // lanes per (region, chunk): up to 8 with two tokens each, beyond that with eight each (247 tokens per region, 8 lanes:
+    // 14 us on a 2 x 208 x 304 x 64 map, a chain of 31 loads)
+    int sub = 1;
+    while ((sub < 8 && 2 * sub <= D.n) || (sub < 32 && 8 * sub <= D.n)) sub *= 2;
     const long items = (long)D.B * D.R * (D.C / 8) * sub;
     ProfScope ps(st, K_MFMA_POOL_QK);
-    hipLaunchKernelGGL(k_pool_wide, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, X, w.xr, D, sub);
+    const dim3 grid((unsigned)((items + 255) / 256));
+    if (pad.Hp) hipLaunchKernelGGL(k_pool_wide<true>, grid, dim3(256), 0, st, X, w.xr, D, sub, pad);
+    else hipLaunchKernelGGL(k_pool_wide<false>, grid, dim3(256), 0, st, X, w.xr, D, sub, pad);
 }
 
 GemmRegions region_job(const Dims &D, const WideWs &w)
@@ -447,6 +478,25 @@ void launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t s
     else hipLaunchKernelGGL((k_attn_rows<64, 2>), grid, block, smem, st, A, O, D, groups, total);
 }
 
+template <int NQ>
+void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
+{
+    const int qtiles = (D.n + 64 * NQ - 1) / (64 * NQ);
+    const dim3 grid((unsigned)((long)D.B * D.R * qtiles * (D.C / 64)));
+    const size_t smem = (size_t)D.k * sizeof(int);
+    if (D.d == 32) hipLaunchKernelGGL((k_attn_gen<32, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles);
+    else hipLaunchKernelGGL((k_attn_gen<64, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles);
+}
+
+void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
+{
+    // two query tiles per wavefront (every K and V operand read serves both) where the wider tile leaves no more than an
+    // eighth of its queries empty beyond the narrow one and there are workgroups enough
+    const int t64 = (D.n + 63) / 64, t128 = (D.n + 127) / 128;
+    if (t128 * 128 * 8 <= t64 * 64 * 9 && (long)D.B * D.R * t128 * (D.C / 64) >= 512) launch_attn_gen_t<2>(D, A, O, st);
+    else launch_attn_gen_t<1>(D, A, O, st);
+}
+
 // Pooling, region-level projections, A^r rows and top-k on their own.
 int route_steps(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideWs &w, int32_t *Ir, float *Ar_opt,
                 hipStream_t st)
@@ -457,7 +507,7 @@ int route_steps(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideWs
         // plain projection of X with float32 results: no pooling, no split
         rc = gemm_f32out(X, Wqkv, 3 * D.C, (long)D.B * D.R, D.C, 2 * D.C, w.qr, w.kr, D.C, K_MFMA_ROUTE_ROWS, st);
     } else {
-        launch_pool(D, X, w, st);
+        launch_pool(D, X, w, GemmRows{}, st);
         rc = gemm_regions(region_job(D, w), Wqkv, 3 * D.C, D.C, K_MFMA_ROUTE_ROWS, st);
     }
     if (rc != BRA_OK) return rc;
@@ -495,9 +545,12 @@ int wide_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, floa
     return route_steps(D, (const bf16_t *)X, (const bf16_t *)Wqkv, w, Ir, Ar_opt, st);
 }
 
+// H, W: the caller's map where D describes a zero-padded one (0: it does not): the products and the pooling read tokens
+// beyond it as zeros and do not write them; nothing is copied.
 int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo, const void *Wlce, void *Y,
-                 int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st)
+                 int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st, int H, int W)
 {
+    const GemmRows pad = H ? GemmRows{D.H, D.W, H, W} : GemmRows{};
     const WideWs w = carve(D, ws);
     const int32_t *Ir_src = Ir_in_opt;
     int32_t *Ir_dst = Ir_out_opt ? Ir_out_opt : w.ir;
@@ -506,10 +559,12 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     // 12 chunks on a few workgroups: 13.7 us at C = 768)
     const long M = (long)D.B * D.N;
     const bool route = !Ir_in_opt, pooled = route && D.n > 1;
-    if (pooled) launch_pool(D, (const bf16_t *)X, w, st);
+    if (pooled) launch_pool(D, (const bf16_t *)X, w, pad, st);
     const GemmRegions rj = region_job(D, w);
+    const float c_exp = D.scale * 1.4426950408889634f;
+    const float q_scale = map_tail_supported(D) ? 1.0f : c_exp;     // k_attn_rows, k_attn_gen take scores in units of log2
     float *fq = route && !pooled ? w.qr : nullptr, *fk = route && !pooled ? w.kr : nullptr;
-    int rc = gemm((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, GemmOut{{w.q, w.k, w.v}, D.C, {fq, fk}},
+    int rc = gemm((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, GemmOut{{w.q, w.k, w.v}, D.C, {fq, fk}, nullptr, nullptr, 0, q_scale, pad, GemmRows{}},
                   pooled ? &rj : nullptr, K_MFMA_QKV, st);
     if (rc != BRA_OK) return rc;
     if (route) {
@@ -520,21 +575,20 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     AttnArgs A = {};
     A.X = (const bf16_t *)X; A.Q = w.q; A.K = w.k; A.V = w.v;
     A.Ir_src = Ir_src; A.Ir_out = Ir_out_opt; A.Wlce = (const bf16_t *)Wlce; A.Y = (bf16_t *)Y;
-    A.c_exp = D.scale * 1.4426950408889634f;
+    A.c_exp = c_exp;
     if (map_tail_supported(D)) {
         rc = launch_map_tail(D, A, w.o, st);
     } else {
         {
-            const unsigned grid = (unsigned)((long)D.B * D.R * ((D.n + 63) / 64) * (D.C / 64));
             ProfScope ps(st, K_MFMA_ATTENTION);
             if (D.n <= 32) launch_attn_rows(D, A, w.o, st);
-            else if (D.d == 32) hipLaunchKernelGGL(k_attn_gen<32>, dim3(grid), dim3(256), 0, st, A, w.o, D);
-            else hipLaunchKernelGGL(k_attn_gen<64>, dim3(grid), dim3(256), 0, st, A, w.o, D);
+            else launch_attn_gen(D, A, w.o, st);
         }
         rc = lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);
     }
     if (rc != BRA_OK) return rc;
-    return gemm(w.o, (const bf16_t *)Wo, D.C, M, D.C, D.C, GemmOut{{Y, nullptr, nullptr}, D.C, {nullptr, nullptr}}, nullptr, K_MFMA_WO, st);
+    return gemm(w.o, (const bf16_t *)Wo, D.C, M, D.C, D.C,
+                GemmOut{{Y, nullptr, nullptr}, D.C, {nullptr, nullptr}, nullptr, nullptr, 0, 1.0f, GemmRows{}, pad}, nullptr, K_MFMA_WO, st);
 }
 
 }  // namespace bra

@@ -1,7 +1,8 @@
 // BRA on maps whose sides S does not divide: zero tokens are appended at the bottom and right,
 // the layer runs on the padded map, the top-left H x W part of its output is returned
 // (the appendix on the choice of S and k: S is a divisor of the training size so that no padding
-// is needed; at other sizes the map is padded).
+// is needed; at other sizes the map is padded).  The general matrix-core pipeline reads and writes the caller's map with
+// the padding as address arithmetic; the copies are for the other pipelines.
 #include "bra_common.h"
 
 namespace bra {
@@ -65,6 +66,8 @@ int padded_forward(const Dims &Dp, int H, int W, const void *X, const void *Wqkv
 {
     const int esize = Dp.dtype == BRA_BF16 ? 2 : 4;
     char *Xp = (char *)ws, *Yp = Xp + map_bytes(Dp), *inner = Yp + map_bytes(Dp);
+    if (path == BRA_PATH_MFMA && mfma_reads_padded(Dp))
+        return mfma_forward_padded(Dp, H, W, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, inner, st);
     int rc = resize_map(Xp, X, Dp.B, Dp.H, Dp.W, H, W, Dp.C, esize, st);
     if (rc != BRA_OK) return rc;
     rc = (path == BRA_PATH_MFMA) ? mfma_forward(Dp, Xp, Wqkv, Wo, Wlce, Yp, Ir_out_opt, Ir_in_opt, inner, st)

@@ -39,3 +39,22 @@ ROWS = [  # (B, H, W, C, heads, S, k): one wavefront per region and 64 channels:
 def test_attention_rows(B, H, W, C, heads, S, k):
     X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=8700 + H * W + C, dtype="bf16")
     compare(X, Wqkv, Wo, Wlce, "bf16", S, k, heads, "mfma")
+
+
+TILES = [  # the kernel for larger regions: one and two query tiles per wavefront, ragged query tiles and key blocks, growing
+           # scores (the softmax reference has to move after the first block)
+    (1, 20, 20, 192, 6, 4, 3),       # n = 25: the small-region kernel, for comparison
+    (1, 24, 28, 192, 6, 4, 5),       # n = 42, 210 keys
+    (2, 16, 64, 64, 1, 2, 3),        # n = 256, heads of 64
+    (64, 26, 38, 64, 2, 2, 4),       # n = 247: 128-query tiles, 988 keys (images 0 and 63 compared)
+    (1, 104, 152, 64, 2, 8, 4),      # n = 247: 256 of 256 queries in two 128-query tiles, 988 keys
+]
+
+
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", TILES)
+def test_attention_large_regions(B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=8600 + H * W + C, dtype="bf16")
+    images = [0, B - 1] if B > 2 else None
+    compare(X, Wqkv, Wo, Wlce, "bf16", S, k, heads, "mfma", images=images)
+    if B <= 2:
+        compare(X, Wqkv, Wo, Wlce, "bf16", S, k, heads, "mfma", scale=0.5)
