@@ -168,7 +168,8 @@ __device__ __forceinline__ long stored_row(const GemmRows &r, int m)
     return y < r.H && x < r.W ? ((long)b * r.H + y) * r.W + x : -1;
 }
 
-template <int BM, int BN, bool REGIONS, bool BT>
+// EXT: bias, GELU, residual or rows that are not in memory (GemmRows).
+template <int BM, int BN, bool REGIONS, bool BT, bool EXT>
 __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) void k_gemm_dma(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw,
                                                   int M, int K, int Nout, GemmOut out, GemmRegions reg, int reg_blocks)
 {
@@ -198,7 +199,7 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
     for (int u = 0; u < LA; ++u) {
         const int row = 8 * (wave * LA + u) + lane / 8, piece = (lane % 8) ^ (row % 8);
         ap[u] = In + (size_t)min(m0 + row, M - 1) * K + 8 * piece;
-        if (out.in_rows.Hp) {
+        if (EXT && out.in_rows.Hp) {
             const long at = stored_row(out.in_rows, min(m0 + row, M - 1));
             ap[u] = (at >= 0 ? In + (size_t)at * K : zero_row) + 8 * piece;
         }
@@ -285,20 +286,20 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
     }
     __syncthreads();
     if (K % 128) multiply(A0, B0);
-    const bool extras = out.bias || out.gelu || out.res || out.scale0 != 1.0f;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         // a 32-output tile lies in one buffer (cols is a multiple of 32): looked up once per tile, for the whole wavefront
         const int ot = __builtin_amdgcn_readfirstlane(o0 + wn + 32 * nt), which = ot / out.cols, ct = ot - which * out.cols;
         bf16_t *buf = (bf16_t *)out.buf[which];
         float *fbuf = which < 2 ? out.f32[which] : nullptr;
+        const float scale = which == 0 ? out.scale0 : 1.0f;
         if (ot >= Nout) continue;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const int m = m0 + wm + 32 * mt + c;
             if (m >= M) continue;
             size_t row = (size_t)m * out.cols;
-            if (out.out_rows.Hp) {
+            if (EXT && out.out_rows.Hp) {
                 const long at = stored_row(out.out_rows, m);
                 if (at < 0) continue;
                 row = (size_t)at * out.cols;
@@ -314,11 +315,9 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
                     *(f32x4 *)(fbuf + row + col) = f32x4{v[0], v[1], v[2], v[3]};
                     *(f32x4 *)(fbuf + row + col + 4) = f32x4{v[4], v[5], v[6], v[7]};
                 }
-                if (extras) {
-                    if (which == 0 && out.scale0 != 1.0f) {
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) v[e] *= out.scale0;
-                    }
+                for (int e = 0; e < 8; ++e) v[e] *= scale;
+                if (EXT) {
                     if (out.bias) {
                         const f32x4 b0 = *(const f32x4 *)(out.bias + o), b1 = *(const f32x4 *)(out.bias + o + 4);
 #pragma unroll
@@ -340,16 +339,27 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
     }
 }
 
-template <int BM, int BN, bool REGIONS, bool BT>
-int launch_dma(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out,
+template <int BM, int BN, bool REGIONS, bool BT, bool EXT>
+int launch_dma_t(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out,
                const GemmRegions &reg, hipStream_t st)
 {
     const long tiles = (M + BM - 1) / BM * ((Nout + BN - 1) / BN), blocks = (tiles + 7) / 8 * 8;
     const long rb = REGIONS ? (reg.M + 63) / 64 * ((reg.Nout + 63) / 64) : 0;
     if (blocks + rb > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((k_gemm_dma<BM, BN, REGIONS, BT>), dim3((unsigned)(blocks + rb)), dim3(256), 0, st, In, W, ldw, (int)M, K,
+    hipLaunchKernelGGL((k_gemm_dma<BM, BN, REGIONS, BT, EXT>), dim3((unsigned)(blocks + rb)), dim3(256), 0, st, In, W, ldw, (int)M, K,
                        Nout, out, reg, (int)rb);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+template <int BM, int BN, bool REGIONS, bool BT>
+int launch_dma(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out,
+               const GemmRegions &reg, hipStream_t st)
+{
+    if constexpr (!BT) {
+        if (out.bias || out.gelu || out.res || out.in_rows.Hp || out.out_rows.Hp)
+            return launch_dma_t<BM, BN, REGIONS, false, true>(In, W, ldw, M, K, Nout, out, reg, st);
+    }
+    return launch_dma_t<BM, BN, REGIONS, BT, false>(In, W, ldw, M, K, Nout, out, reg, st);
 }
 
 template <bool REGIONS, bool BT = false>
