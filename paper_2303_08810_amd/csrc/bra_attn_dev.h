@@ -1,0 +1,68 @@
+// Device-side pieces of the routed attention kernels that stream rows straight into LDS (internal).
+#pragma once
+
+#include "bra_mfma_dev.h"
+
+#include <type_traits>
+
+namespace bra {
+namespace mfma {
+
+// Softmax step for KT tiles of 16 keys x 16 queries of one head: scores
+// s[t][j] = S^T[key 16 t + 4 g + j][query i] relative to the reference m (which entered the product as its accumulator
+// input, so a score costs no subtraction), weights p = 2^s in the operand order of O^T += V^T P^T.  The reference moves,
+// and the sums are rescaled, only when a lane's own score exceeds it by 8 (weights stay below 2^8), which needs no exchange
+// between lanes; the quotient O / l does not depend on it.  FIRST: the reference is this block's maximum.
+template <bool FIRST, int KT, int NDT>
+__device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, f32x4 &l, f32x4 (&acc)[NDT], bf16x8 (&pb)[KT / 2])
+{
+    float mx = s[0][0];
+#pragma unroll
+    for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mx = fmaxf(mx, s[t][j]);
+    if (FIRST || __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0) {
+        const float up = FIRST ? cross_row_max(mx) : fmaxf(cross_row_max(mx), 0.f);
+        m += up;
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s[t][j] -= up;
+        if (!FIRST) {
+            const float alpha = __builtin_amdgcn_exp2f(-up);
+            l *= alpha;
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
+        }
+    }
+#pragma unroll
+    for (int tp = 0; tp < KT / 2; ++tp) {
+        float p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(s[2 * tp + e / 4][e % 4]);
+        pb[tp] = pack8(p);
+        // denominators of the same rounded weights, from a product with an all-ones operand
+        const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+        l = mfma16(__builtin_bit_cast(bf16x8, ones), pb[tp], l);
+    }
+}
+
+// A direct load of 16 bytes per lane to 1024 consecutive bytes of LDS (l: the same for all lanes) that the compiler does
+// not count: it would wait for all outstanding ones before the next LDS read, those of the buffer in flight among them.
+// The caller waits (s_waitcnt vmcnt) before it reads the buffer.  M0 is the instruction's own here: nothing else in the
+// kernels that use this sets it.
+__device__ __forceinline__ void load_to_lds_untracked(const bf16_t *g, bf16_t *l)
+{
+    const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) bf16_t *)l);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(g) : "memory");
+}
+
+// Four bytes per lane to 256 consecutive bytes of LDS, likewise.
+__device__ __forceinline__ void load4_to_lds_untracked(const float *g, float *l)
+{
+    const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) float *)l);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(at), "v"(g) : "memory");
+}
+
+}  // namespace mfma
+}  // namespace bra

@@ -149,7 +149,7 @@ int padded_forward(const Dims &Dp, int H, int W, const void *X, const void *Wqkv
                    void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, int path, hipStream_t st);
 
 // Q, K, V = X Wqkv into three token maps for any C that is a multiple of 64 (bra_mfma_wide.hip).
-int wide_project_qkv(const Dims &D, const void *X, const void *Wqkv, bf16_t *Q, bf16_t *K, bf16_t *V, hipStream_t st);
+int wide_project_qkv(const Dims &D, const void *X, const void *Wqkv, bf16_t *Q, bf16_t *K, bf16_t *V, float q_scale, hipStream_t st);
 
 // Backward pass with fixed routing on the matrix cores (bra_mfma_bwd.hip).
 bool mfma_backward_supported(const Dims &D);

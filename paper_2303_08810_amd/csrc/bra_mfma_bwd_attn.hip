@@ -1,0 +1,725 @@
+// Attention backward for regions of any size (bf16, heads of 32 or 64 channels, C a multiple of 64): two kernels with the
+// layout of the forward's k_attn_gen and k_attn_rows (bra_mfma_wide.hip).
+//
+// With P = 2^(S - lse), S = Q K^T in units of log2 (Q comes multiplied by scale log2(e)), the row statistics enter the
+// products as their accumulator inputs: S - lse and dP - D, D = rowsum(dO o O), leave the matrix cores ready for
+//     dS = 2^(S - lse) (dP - D)                        an exponential, a multiplication and half a conversion per score
+// with dP = dO V^T, dQ = scale dS K, dV = P^T dO, dK = scale dS^T Q.
+//
+// kShared: a workgroup takes 64 N tokens of one region (16 N per wavefront) and 64 channels (2 or 1 heads); blocks of 64
+// rows of the other side are shared by its wavefronts.  kWaves (regions of at most 32 tokens): a wavefront takes all
+// tokens of a region and 64 channels by itself, with blocks of 32 rows in its own part of LDS and no barriers.  kSplit
+// (small calls): the wavefronts of a workgroup take every fourth block for the same 16 N tokens and add up at the end.  Rows
+// (128 bytes of each of two maps) go straight from memory into one of two buffers while the other is worked on; their
+// 16-byte pieces are exchanged (piece c of row r at c ^ r % 8), so that row reads and transposing reads meet different banks.
+//
+// Measured, query side + key side (us; before: kernels that staged rows through registers and formed S and dP without
+// their statistics): 11 x 42 x 42 x 256, k = 6 (36 tokens per region): 77 + 66 -> 50 + 46; 25 x 8 x 16 x 768 with heads
+// of 64, k = 36 (2 tokens): 215 + 172 -> 66 + 89; 12 x 112 x 120 x 64, k = 1 (210 tokens): 112 + 105 -> 68 + 78;
+// 64 x 56 x 56 x 64, k = 1: 36 + 49 -> 37 + 41, there bound by memory (150 MB per kernel).
+#include "bra_attn_dev.h"
+#include "bra_mfma_bwd_attn.h"
+
+namespace bra {
+
+using namespace mfma;
+
+namespace {
+
+enum Mode { kWaves, kShared, kSplit };
+
+template <Mode MODE>
+struct Rows {
+    static constexpr bool SHARED = MODE == kShared;
+    static constexpr int KB = SHARED ? 64 : 32;                // rows of a block
+    static constexpr int per_wave = SHARED ? 16 : 32;          // rows that a wavefront brings
+    static constexpr int buf = 2 * KB * 64;                    // elements of a buffer: two maps
+    static constexpr int bufs = 2 * (SHARED ? 1 : 4);          // two per workgroup or wavefront
+};
+
+// a / n for any non-negative a whose quotient is below 2^20: fast_div is off by one at most.
+__device__ __forceinline__ int divide(int a, int n, float n_inv)
+{
+    const int p = fast_div(a, n_inv), rest = a - p * n;
+    return rest < 0 ? p - 1 : rest >= n ? p + 1 : p;
+}
+
+// Where regions and their slots lie within an image (Sec. 3.2: regions tile the map row-major).
+struct Places {
+    float rw_inv, s_inv;
+    int S, rh, rw, W;
+    __device__ __forceinline__ Places(const Dims &D)
+        : rw_inv(1.0f / (float)D.rw), s_inv(1.0f / (float)D.S), S(D.S), rh(D.rh), rw(D.rw), W(D.W) {}
+    __device__ __forceinline__ int origin(int r) const
+    {
+        const int ry = fast_div(r, s_inv);
+        return ry * rh * W + (r - ry * S) * rw;
+    }
+    __device__ __forceinline__ int slot(int s) const
+    {
+        const int sy = divide(s, rw, rw_inv);
+        return sy * W + s - sy * rw;
+    }
+};
+
+// Rows 16 t + i of a buffer's map as operands: piece p.
+__device__ __forceinline__ bf16x8 row_operand(const bf16_t *T, int row, int piece)
+{
+    return *(const bf16x8 *)(T + row * 64 + 8 * (piece ^ (row % 8)));
+}
+
+// Columns col0 + i of rows row0 .. row0 + 31 (contraction slots in the accumulator order: 4 g .. 4 g + 3, then 16 further).
+__device__ __forceinline__ bf16x8 column_operand(const bf16_t *T, int row0, int col0, int g, int i)
+{
+    u32x2 r[2];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        const int row = row0 + 16 * half + 4 * g + i / 4, piece = col0 / 8 + (i % 4) / 2;
+        r[half] = __builtin_bit_cast(u32x2, lds_read_tr16(T + row * 64 + 8 * (piece ^ (row % 8)) + 4 * (i % 2)));
+    }
+    return __builtin_bit_cast(bf16x8, u32x4{r[0][0], r[0][1], r[1][0], r[1][1]});
+}
+
+// The workgroup's or wavefront's place in the grid: (image, region, tile of tokens, group of 64 channels); false: none.
+template <Mode MODE>
+__device__ __forceinline__ bool place(const Dims &D, int tiles, int items, int wave, int &b, int &reg, int &tile, int &cg)
+{
+    const int ncg = D.C / 64, wid = swizzled_block();          // those of an image share an L2
+    const int item = MODE != kWaves ? wid : __builtin_amdgcn_readfirstlane(4 * wid + wave);
+    if (item >= items) return false;
+    cg = item % ncg;
+    tile = (item / ncg) % tiles;
+    reg = (item / (ncg * tiles)) % D.R;
+    b = item / (ncg * tiles * D.R);
+    return true;
+}
+
+// ---------------------------------------------------------------------------
+// Query side: attention output O, row statistics lse and D, and dQ, in two sweeps over the region's k n routed keys.  The
+// first is the forward's attention; D = dO . O needs no dP there.  The second goes over the blocks backwards, so that the
+// last two are still in LDS (up to 128 or 64 routed keys: nothing is read twice).
+template <int HD, int NQ, Mode MODE>
+__global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_attn_bwd_q(AttnBwdArgs A, Dims D, int tiles, int items)
+{
+    using R = Rows<MODE>;
+    constexpr bool SHARED = R::SHARED, SPLIT = MODE == kSplit;
+    constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16, KB = R::KB, KT = KB / 16;
+    __shared__ __attribute__((aligned(16))) bf16_t lds[R::bufs * R::buf];
+    constexpr int kPart = 64 * (2 + 4 * NDT);    // SPLIT: m, l and the sums of a wavefront, one query tile and head
+    __shared__ __attribute__((aligned(16))) float sums[SPLIT ? NQ * HPW * 4 * kPart : 4];
+    extern __shared__ int origin_tables[];       // [k] or [4][k]: first token of the routed regions
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int C = D.C, n = D.n, kn = D.kn;
+    int b, reg, tile, cg;
+    if (!place<MODE>(D, tiles, items, wave, b, reg, tile, cg)) return;
+    const Places at(D);
+    const float n_inv = 1.0f / (float)n;
+    const size_t img = (size_t)b * D.N * C + 64 * cg;
+    bf16_t *mine = lds + (SHARED ? 0 : wave * 2 * R::buf);
+    int *origins = origin_tables + (SHARED ? 0 : wave * D.k);
+    for (int p = SHARED ? tid : lane; p < D.k; p += SHARED ? 256 : kWave)
+        origins[p] = at.origin(region_index(A.Ir[((size_t)b * D.R + reg) * D.k + p], D.R));
+    const int q0 = SHARED ? 64 * NQ * tile + 16 * NQ * wave : 16 * NQ * tile;
+    const bool idle = SHARED && q0 >= n;         // a wavefront without queries only brings its rows
+    int tok[NQ];
+    bf16x8 qf[NQ][HPW][KSD], gf[NQ][HPW][KSD];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        tok[q] = at.origin(reg) + at.slot(min(q0 + 16 * q + i, n - 1));
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+            for (int ks = 0; ks < KSD; ++ks) {
+                const size_t e = img + (size_t)tok[q] * C + HD * hh + 32 * ks + 8 * g;
+                qf[q][hh][ks] = *(const bf16x8 *)(A.Q + e);
+                gf[q][hh][ks] = *(const bf16x8 *)(A.dO + e);
+            }
+    }
+    // the operands have arrived before the sweeps: otherwise the compiler waits for them there, and with them for the
+    // direct loads in flight
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+            for (int ks = 0; ks < KSD; ++ks) asm volatile("" : "+v"(qf[q][hh][ks]), "+v"(gf[q][hh][ks]));
+    if (SHARED) __syncthreads();
+    else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // the table is read by other lanes
+
+    // blocks of this wavefront: local block s is block STEP s + start
+    constexpr int STEP = SPLIT ? 4 : 1;
+    const int start = SPLIT ? wave : 0, nb = ((kn + KB - 1) / KB - start + STEP - 1) / STEP;
+    auto request = [&](int local) {
+        const int blk = STEP * local + start;
+        bf16_t *Ks = mine + (local % 2) * R::buf, *Vs = Ks + KB * 64;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // the buffer's last reads are done
+#pragma unroll
+        for (int u = 0; u < R::per_wave / 8; ++u) {
+            const int row = (SHARED ? 16 * wave : 0) + 8 * u + lane / 8, key = min(KB * blk + row, kn - 1), p = divide(key, n, n_inv);
+            const size_t e = img + (size_t)(origins[p] + at.slot(key - p * n)) * C + 8 * ((lane % 8) ^ (lane / 8));
+            load_to_lds_untracked(A.K + e, Ks + (row - lane / 8) * 64);
+            load_to_lds_untracked(A.V + e, Vs + (row - lane / 8) * 64);
+        }
+    };
+    // Step s works on block s of the first sweep, then backwards; the first two blocks of the second sweep are in place.
+    // On return the block of step s is in LDS and that of step s + 1 requested.
+    auto block_of = [&](int s) { return s < nb ? s : 2 * nb - 1 - s; };
+    auto advance = [&](int s) {
+        const bool more = s + 1 < 2 * nb && (s + 1 < nb || s + 1 > nb + 1);
+        if (SHARED) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (more) request(block_of(s + 1));
+        } else if (more) {
+            request(block_of(s + 1));
+            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        } else {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+    };
+    float m[NQ][HPW];
+    f32x4 l[NQ][HPW], acc[NQ][HPW][NDT];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh) {
+            m[q][hh] = 0.f;
+            l[q][hh] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    auto mask = [&](f32x4 (&s)[KT], int left) {              // keys past the end get no weight
+        if (left < KB) {
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (16 * t + 4 * g + j >= left) s[t][j] = -INFINITY;
+        }
+    };
+    auto forward = [&](int s, auto first) {
+        const bf16_t *Ks = mine + (s % 2) * R::buf, *Vs = Ks + KB * 64;
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh) {
+            bf16x8 pb[NQ][KT / 2];
+            {
+                bf16x8 kf[KT][KSD];
+#pragma unroll
+                for (int t = 0; t < KT; ++t)
+#pragma unroll
+                    for (int ks = 0; ks < KSD; ++ks) kf[t][ks] = row_operand(Ks, 16 * t + i, HD / 8 * hh + 4 * ks + g);
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    f32x4 sc[KT];
+                    const float neg = -m[q][hh];
+#pragma unroll
+                    for (int t = 0; t < KT; ++t) {
+                        sc[t] = f32x4{neg, neg, neg, neg};
+#pragma unroll
+                        for (int ks = 0; ks < KSD; ++ks) sc[t] = mfma16(kf[t][ks], qf[q][hh][ks], sc[t]);   // S^T[key 16 t + 4 g + j][query i]
+                    }
+                    mask(sc, kn - KB * (STEP * s + start));
+                    softmax_step<decltype(first)::value>(sc, m[q][hh], l[q][hh], acc[q][hh], pb[q]);
+                    if (SHARED && NQ > 1) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+#pragma unroll
+            for (int tp = 0; tp < KT / 2; ++tp)
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) {
+                    const bf16x8 vf = column_operand(Vs, 32 * tp, HD * hh + 16 * dt, g, i);
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) acc[q][hh][dt] = mfma16(vf, pb[q][tp], acc[q][hh][dt]);
+                }
+            if (SHARED) __builtin_amdgcn_sched_barrier(0);    // one head at a time: interleaved, they take twice the registers
+        }
+    };
+    if (!SPLIT || nb > 0) {
+        request(0);
+        advance(0);
+        if (!idle) forward(0, std::true_type{});
+    }
+#pragma unroll 1
+    for (int s = 1; s < nb; ++s) {
+        advance(s);
+        if (!idle) forward(s, std::false_type{});
+    }
+    if constexpr (SPLIT) {
+        // the four wavefronts' sums on a common reference
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int hh = 0; hh < HPW; ++hh) {
+                if (nb == 0) m[q][hh] = -INFINITY;
+                float *part = sums + (q * HPW + hh) * 4 * kPart + lane;
+                part[wave * kPart] = m[q][hh];
+                part[wave * kPart + 64] = l[q][hh][0];
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) part[wave * kPart + 64 * (2 + 4 * dt + j)] = acc[q][hh][dt][j];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int hh = 0; hh < HPW; ++hh) {
+                const float *part = sums + (q * HPW + hh) * 4 * kPart + lane;
+                const float top = fmaxf(fmaxf(part[0], part[kPart]), fmaxf(part[2 * kPart], part[3 * kPart]));
+                float f[4], sum = 0.f;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    f[w] = __builtin_amdgcn_exp2f(part[w * kPart] - top);
+                    sum += f[w] * part[w * kPart + 64];
+                }
+                m[q][hh] = top;
+                l[q][hh][0] = sum;
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        float a = 0.f;
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) a += f[w] * part[w * kPart + 64 * (2 + 4 * dt + j)];
+                        acc[q][hh][dt][j] = a;
+                    }
+            }
+    }
+    float neg_lse[NQ][HPW], neg_d[NQ][HPW];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const bool store = q0 + 16 * q + i < n && (!SPLIT || wave == 0);
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh) {
+            const float inv = 1.0f / l[q][hh][0];
+            float d = 0.f;
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) {
+                const size_t e = img + (size_t)tok[q] * C + HD * hh + 16 * dt + 4 * g;
+                const u32x2 go = *(const u32x2 *)(A.dO + e);
+                const f32x4 o = acc[q][hh][dt] * inv;
+                d += o[0] * bf16_lo(go[0]) + o[1] * bf16_hi(go[0]) + o[2] * bf16_lo(go[1]) + o[3] * bf16_hi(go[1]);
+                if (store) *(u32x2 *)(A.O + e) = pack4(o);
+                acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            d = cross_row_sum(d);
+            const float lse = m[q][hh] + __builtin_amdgcn_logf(l[q][hh][0]);       // v_log_f32: log2
+            neg_lse[q][hh] = -lse;
+            neg_d[q][hh] = -d;
+            if (store && g == 0) {
+                const size_t e = ((size_t)b * D.heads + HPW * cg + hh) * D.N + tok[q];
+                A.lse[e] = lse;
+                A.dsum[e] = d;
+            }
+        }
+    }
+#pragma unroll 1
+    for (int s = nb; s < 2 * nb; ++s) {
+        advance(s);
+        if (idle) continue;
+        const int local = block_of(s), blk = STEP * local + start;
+        const bf16_t *Ks = mine + (local % 2) * R::buf, *Vs = Ks + KB * 64;
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh) {
+            bf16x8 db[NQ][KT / 2];
+#pragma unroll
+            for (int tp = 0; tp < KT / 2; ++tp) {
+                f32x4 sc[NQ][2], dp[NQ][2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    bf16x8 kf[KSD], vf[KSD];
+#pragma unroll
+                    for (int ks = 0; ks < KSD; ++ks) {
+                        kf[ks] = row_operand(Ks, 32 * tp + 16 * t + i, HD / 8 * hh + 4 * ks + g);
+                        vf[ks] = row_operand(Vs, 32 * tp + 16 * t + i, HD / 8 * hh + 4 * ks + g);
+                    }
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) {
+                        const float a = neg_lse[q][hh], c = neg_d[q][hh];
+                        sc[q][t] = f32x4{a, a, a, a};
+                        dp[q][t] = f32x4{c, c, c, c};
+#pragma unroll
+                        for (int ks = 0; ks < KSD; ++ks) {
+                            sc[q][t] = mfma16(kf[ks], qf[q][hh][ks], sc[q][t]);
+                            dp[q][t] = mfma16(vf[ks], gf[q][hh][ks], dp[q][t]);
+                        }
+                    }
+                }
+                const int left = kn - KB * blk - 32 * tp;
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    if (left < 32) {
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+                                if (16 * t + 4 * g + j >= left) sc[q][t][j] = -INFINITY;
+                    }
+                    float ds[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) ds[e] = __builtin_amdgcn_exp2f(sc[q][e / 4][e % 4]) * dp[q][e / 4][e % 4];
+                    db[q][tp] = pack8(ds);
+                }
+            }
+#pragma unroll
+            for (int tp = 0; tp < KT / 2; ++tp)
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) {
+                    const bf16x8 kc = column_operand(Ks, 32 * tp, HD * hh + 16 * dt, g, i);
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) acc[q][hh][dt] = mfma16(kc, db[q][tp], acc[q][hh][dt]);
+                }
+            if (SHARED) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if constexpr (SPLIT) {
+        // wavefront w adds up and stores channels 16 w .. 16 w + 15
+        __syncthreads();                          // the sums have been read
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) *(f32x4 *)(sums + ((q * 4 + a) * 4 + wave) * 256 + 4 * lane) = acc[q][a / NDT][a % NDT];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            if (q0 + 16 * q + i >= n) continue;
+            const float *part = sums + (q * 4 + wave) * 1024 + 4 * lane;
+            const f32x4 sum = (*(const f32x4 *)part + *(const f32x4 *)(part + 256)) + (*(const f32x4 *)(part + 512) + *(const f32x4 *)(part + 768));
+            *(u32x2 *)(A.dQKV + ((size_t)b * D.N + tok[q]) * 3 * C + 64 * cg + 16 * wave + 4 * g) = pack4(sum * D.scale);
+        }
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        if (q0 + 16 * q + i >= n) continue;
+        bf16_t *row = A.dQKV + ((size_t)b * D.N + tok[q]) * 3 * C + 64 * cg + 4 * g;
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) *(u32x2 *)(row + HD * hh + 16 * dt) = pack4(acc[q][hh][dt] * D.scale);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Key side: dK and dV of a region's tokens, summed in registers over the queries of all regions routed to it (every entry
+// of Ir that names it, in the order of the entries, so the result is the same every time).
+constexpr float kLn2 = 0.6931471805599453f;             // dK = scale dS^T Q, and Q came with scale log2(e)
+constexpr int kListShared = 1024, kListWave = 512;      // entries listed at a time
+
+// Query regions whose entries e0, e0 + 1, .. name region j, as first tokens, up to a full list; e0 moves behind the
+// entries looked at.  A wavefront on its own.
+__device__ __forceinline__ int list_of_wave(const int32_t *__restrict__ irb, int entries, int &e0, int j, int R, float k_inv,
+                                            const Places &at, int *list)
+{
+    const int lane = threadIdx.x % kWave;
+    int count = 0;
+    for (; e0 < entries && count + 4 * kWave <= kListWave; e0 += 4 * kWave) {
+        int r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) r[u] = irb[min(e0 + kWave * u + lane, entries - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + kWave * u + lane;
+            const bool named = e < entries && region_index(r[u], R) == j;
+            const unsigned long long votes = __ballot(named);
+            if (named) list[count + __popcll(votes & ((1ull << lane) - 1))] = at.origin(fast_div(e, k_inv));
+            count += __popcll(votes);
+        }
+    }
+    return count;
+}
+
+// The same for the whole workgroup, one range of kListShared entries at a time; barriers around it are the caller's.
+__device__ __forceinline__ int list_of_group(const int32_t *__restrict__ irb, int entries, int e0, int j, int R, float k_inv,
+                                             const Places &at, int *list, int *counts)
+{
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    unsigned long long votes[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int e = e0 + 256 * u + (int)threadIdx.x;
+        votes[u] = __ballot(e < entries && region_index(irb[min(e, entries - 1)], R) == j);
+        if (lane == 0) counts[4 * u + wave] = __popcll(votes[u]);
+    }
+    __syncthreads();
+    int total = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if (w == wave && (votes[u] >> lane & 1))
+                list[total + __popcll(votes[u] & ((1ull << lane) - 1))] = at.origin(fast_div(e0 + 256 * u + (int)threadIdx.x, k_inv));
+            total += counts[4 * u + w];
+        }
+    return __builtin_amdgcn_readfirstlane(total);
+}
+
+template <int HD, int NK, Mode MODE>
+__global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_attn_bwd_kv(AttnBwdArgs A, Dims D, int tiles, int items)
+{
+    using R = Rows<MODE>;
+    constexpr bool SHARED = R::SHARED, SPLIT = MODE == kSplit;
+    constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16, KB = R::KB;
+    constexpr int kStats = HPW * 2 * KB;         // per buffer: [head][lse, D][row]
+    __shared__ __attribute__((aligned(16))) bf16_t lds[R::bufs * R::buf];
+    __shared__ __attribute__((aligned(16))) float stats[R::bufs * kStats];
+    __shared__ __attribute__((aligned(16))) float sums[SPLIT ? NK * 4 * 2048 : 4];
+    __shared__ int lists[SHARED ? kListShared : 4 * kListWave];
+    __shared__ int counts[16];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int C = D.C, n = D.n;
+    int b, reg, tile, cg;
+    if (!place<MODE>(D, tiles, items, wave, b, reg, tile, cg)) return;
+    const Places at(D);
+    const float n_inv = 1.0f / (float)n, k_inv = 1.0f / (float)D.k;
+    const size_t img = (size_t)b * D.N * C + 64 * cg;
+    const size_t stat0 = ((size_t)b * D.heads + HPW * cg) * D.N;
+    bf16_t *mine = lds + (SHARED ? 0 : wave * 2 * R::buf);
+    float *my_stats = stats + (SHARED ? 0 : wave * 2 * kStats);
+    int *list = lists + (SHARED ? 0 : wave * kListWave);
+
+    const int q0 = SHARED ? 64 * NK * tile + 16 * NK * wave : 16 * NK * tile;
+    const bool idle = SHARED && q0 >= n;         // a wavefront without keys only brings its rows
+    int tok[NK];
+    bf16x8 kf[NK][HPW][KSD], vf[NK][HPW][KSD];
+#pragma unroll
+    for (int q = 0; q < NK; ++q) {
+        tok[q] = at.origin(reg) + at.slot(min(q0 + 16 * q + i, n - 1));
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+            for (int ks = 0; ks < KSD; ++ks) {
+                const size_t e = img + (size_t)tok[q] * C + HD * hh + 32 * ks + 8 * g;
+                kf[q][hh][ks] = *(const bf16x8 *)(A.K + e);
+                vf[q][hh][ks] = *(const bf16x8 *)(A.V + e);
+            }
+    }
+    f32x4 dk[NK][HPW][NDT], dv[NK][HPW][NDT];
+#pragma unroll
+    for (int q = 0; q < NK; ++q)
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) dk[q][hh][dt] = dv[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    int rows = 0;
+    constexpr int STEP = SPLIT ? 4 : 1;          // as above
+    const int start = SPLIT ? wave : 0;
+    auto request = [&](int local) {
+        const int blk = STEP * local + start;
+        bf16_t *Qs = mine + (local % 2) * R::buf, *Gs = Qs + KB * 64;
+        float *st = my_stats + (local % 2) * kStats;
+        auto token = [&](int row) {
+            const int r = min(KB * blk + row, rows - 1), p = divide(r, n, n_inv);
+            return list[p] + at.slot(r - p * n);
+        };
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // the buffer's last reads are done
+#pragma unroll
+        for (int u = 0; u < R::per_wave / 8; ++u) {
+            const int row = (SHARED ? 16 * wave : 0) + 8 * u + lane / 8;
+            const size_t e = img + (size_t)token(row) * C + 8 * ((lane % 8) ^ (lane / 8));
+            load_to_lds_untracked(A.Q + e, Qs + (row - lane / 8) * 64);
+            load_to_lds_untracked(A.dO + e, Gs + (row - lane / 8) * 64);
+        }
+        // statistics: 64 floats per load, (head, lse or D) by wavefront or (lse | D) of one head
+        const int t = token(lane % KB);
+        if (SHARED) {
+            if (wave < 2 * HPW)
+                load4_to_lds_untracked((wave % 2 ? A.dsum : A.lse) + stat0 + (size_t)(wave / 2) * D.N + t, st + wave * KB);
+        } else {
+#pragma unroll
+            for (int hh = 0; hh < HPW; ++hh)
+                load4_to_lds_untracked((lane >= KB ? A.dsum : A.lse) + stat0 + (size_t)hh * D.N + t, st + 2 * hh * KB);
+        }
+    };
+    auto block = [&](int local) {
+        const int blk = STEP * local + start;
+        const bf16_t *Qs = mine + (local % 2) * R::buf, *Gs = Qs + KB * 64;
+        const float *st = my_stats + (local % 2) * kStats;
+#pragma unroll
+        for (int tp = 0; tp < KB / 32; ++tp) {
+            const int left = rows - KB * blk - 32 * tp;
+            if (tp && left <= 0) break;
+#pragma unroll
+            for (int hh = 0; hh < HPW; ++hh) {
+                f32x4 s[NK][2], dp[NK][2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int row = 32 * tp + 16 * t;
+                    const f32x4 l4 = *(const f32x4 *)(st + 2 * hh * KB + row + 4 * g);
+                    const f32x4 d4 = *(const f32x4 *)(st + (2 * hh + 1) * KB + row + 4 * g);
+                    bf16x8 qf[KSD], gf[KSD];
+#pragma unroll
+                    for (int ks = 0; ks < KSD; ++ks) {
+                        qf[ks] = row_operand(Qs, row + i, HD / 8 * hh + 4 * ks + g);
+                        gf[ks] = row_operand(Gs, row + i, HD / 8 * hh + 4 * ks + g);
+                    }
+#pragma unroll
+                    for (int q = 0; q < NK; ++q) {
+                        s[q][t] = -l4;
+                        dp[q][t] = -d4;
+#pragma unroll
+                        for (int ks = 0; ks < KSD; ++ks) {
+                            s[q][t] = mfma16(qf[ks], kf[q][hh][ks], s[q][t]);       // S[query 16 t + 4 g + j][key i]
+                            dp[q][t] = mfma16(gf[ks], vf[q][hh][ks], dp[q][t]);
+                        }
+                    }
+                }
+                bf16x8 pb[NK], db[NK];
+#pragma unroll
+                for (int q = 0; q < NK; ++q) {
+                    if (left < 32) {
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+                                if (16 * t + 4 * g + j >= left) s[q][t][j] = -INFINITY;
+                    }
+                    float p[8], ds[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        p[e] = __builtin_amdgcn_exp2f(s[q][e / 4][e % 4]);
+                        ds[e] = p[e] * dp[q][e / 4][e % 4];
+                    }
+                    pb[q] = pack8(p);
+                    db[q] = pack8(ds);
+                }
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) {
+                    const bf16x8 gc = column_operand(Gs, 32 * tp, HD * hh + 16 * dt, g, i);
+                    const bf16x8 qc = column_operand(Qs, 32 * tp, HD * hh + 16 * dt, g, i);
+#pragma unroll
+                    for (int q = 0; q < NK; ++q) {
+                        dv[q][hh][dt] = mfma16(gc, pb[q], dv[q][hh][dt]);
+                        dk[q][hh][dt] = mfma16(qc, db[q], dk[q][hh][dt]);
+                    }
+                }
+                if (SHARED) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    const int entries = D.R * D.k;
+    const int32_t *irb = A.Ir + (size_t)b * entries;
+    for (int e0 = 0; e0 < entries;) {
+        int named;
+        if (SHARED) {
+            __syncthreads();                      // the list and the buffers have been read
+            named = list_of_group(irb, entries, e0, reg, D.R, k_inv, at, list, counts);
+            e0 += kListShared;
+            __syncthreads();
+        } else {
+            named = list_of_wave(irb, entries, e0, reg, D.R, k_inv, at, list);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        }
+        rows = named * n;
+        const int nb = ((rows + KB - 1) / KB - start + STEP - 1) / STEP;
+        if (nb <= 0) continue;
+        // the operands have arrived: see above
+#pragma unroll
+        for (int q = 0; q < NK; ++q)
+#pragma unroll
+            for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+                for (int ks = 0; ks < KSD; ++ks) asm volatile("" : "+v"(kf[q][hh][ks]), "+v"(vf[q][hh][ks]));
+        request(0);
+#pragma unroll 1
+        for (int s = 0; s < nb; ++s) {
+            const bool more = s + 1 < nb;
+            if (SHARED) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                if (more) request(s + 1);
+            } else if (more) {
+                request(s + 1);
+                if (HPW == 2) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
+            } else {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            if (!idle) block(s);
+        }
+    }
+    if constexpr (SPLIT) {
+        // wavefront w adds up and stores channels 16 w .. 16 w + 15 of both
+#pragma unroll
+        for (int q = 0; q < NK; ++q)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                float *part = sums + ((q * 4 + a) * 8 + wave) * 256 + 4 * lane;
+                *(f32x4 *)part = dk[q][a / NDT][a % NDT];
+                *(f32x4 *)(part + 1024) = dv[q][a / NDT][a % NDT];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NK; ++q) {
+            if (q0 + 16 * q + i >= n) continue;
+            const float *part = sums + (q * 4 + wave) * 2048 + 4 * lane;
+            bf16_t *dst = A.dQKV + ((size_t)b * D.N + tok[q]) * 3 * C + C + 64 * cg + 16 * wave + 4 * g;
+            f32x4 sum[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u, part += 1024)
+                sum[u] = (*(const f32x4 *)part + *(const f32x4 *)(part + 256)) + (*(const f32x4 *)(part + 512) + *(const f32x4 *)(part + 768));
+            *(u32x2 *)dst = pack4(sum[0] * kLn2);
+            *(u32x2 *)(dst + C) = pack4(sum[1]);
+        }
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < NK; ++q) {
+        if (q0 + 16 * q + i >= n) continue;
+        bf16_t *row = A.dQKV + ((size_t)b * D.N + tok[q]) * 3 * C + C + 64 * cg + 4 * g;
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) {
+                *(u32x2 *)(row + HD * hh + 16 * dt) = pack4(dk[q][hh][dt] * kLn2);
+                *(u32x2 *)(row + C + HD * hh + 16 * dt) = pack4(dv[q][hh][dt]);
+            }
+    }
+}
+
+template <int HD, int N, Mode MODE>
+int launch_t(const Dims &D, const AttnBwdArgs &A, int kernel_id, hipStream_t st)
+{
+    const int per_tile = (MODE == kShared ? 64 : 16) * N, tiles = (D.n + per_tile - 1) / per_tile;
+    const long items = (long)D.B * D.R * tiles * (D.C / 64), blocks = ((MODE == kWaves ? (items + 3) / 4 : items) + 7) / 8 * 8;
+    if (blocks > 0x7fffffffL / 4) return BRA_ERR_UNSUPPORTED;
+    {
+        ProfScope ps(st, kernel_id);
+        hipLaunchKernelGGL((k_attn_bwd_q<HD, N, MODE>), dim3((unsigned)blocks), dim3(256), (size_t)(MODE == kShared ? 1 : 4) * D.k * sizeof(int), st,
+                           A, D, tiles, (int)items);
+    }
+    if (hipGetLastError() != hipSuccess) return BRA_ERR_LAUNCH;
+    ProfScope ps(st, kernel_id);
+    hipLaunchKernelGGL((k_attn_bwd_kv<HD, N, MODE>), dim3((unsigned)blocks), dim3(256), 0, st, A, D, tiles, (int)items);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+template <int HD>
+int launch_hd(const Dims &D, const AttnBwdArgs &A, int kernel_id, hipStream_t st)
+{
+    const long regions = (long)D.B * D.R * (D.C / 64), t64 = (D.n + 63) / 64, t128 = (D.n + 127) / 128;
+    const long waves = regions * (D.n <= 32 ? 1 : 4 * t64);
+    // Too few wavefronts for the 1024 SIMDs: four share the rows of a tile, where a row list has at least two blocks
+    // (us for the whole gradient: 3 x 14 x 49 x 64, k = 20: 66 -> 50; 28 x 28 x 64, k = 4, 64 routed keys: 45 -> 42; but
+    // 392 wavefronts and 80 keys: 66 -> 69, 196 and 4 keys: 49 -> 60).
+    if (waves <= 256 && D.kn >= 64) {
+        if (D.n <= 16) return launch_t<HD, 1, kSplit>(D, A, kernel_id, st);
+        return launch_t<HD, 2, kSplit>(D, A, kernel_id, st);
+    }
+    if (D.n <= 16) return launch_t<HD, 1, kWaves>(D, A, kernel_id, st);
+    if (D.n <= 32) return launch_t<HD, 2, kWaves>(D, A, kernel_id, st);
+    // two token tiles per wavefront (every operand read serves both) where they leave no more than an eighth of their
+    // tokens empty beyond the narrow ones and there are workgroups enough
+    if (t128 * 128 * 8 <= t64 * 64 * 9 && regions * t128 >= 512) return launch_t<HD, 2, kShared>(D, A, kernel_id, st);
+    return launch_t<HD, 1, kShared>(D, A, kernel_id, st);
+}
+
+}  // namespace
+
+int launch_attn_bwd(const Dims &D, const AttnBwdArgs &A, int kernel_id, hipStream_t st)
+{
+    return D.d == 32 ? launch_hd<32>(D, A, kernel_id, st) : launch_hd<64>(D, A, kernel_id, st);
+}
+
+}  // namespace bra

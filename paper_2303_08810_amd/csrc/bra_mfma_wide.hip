@@ -12,6 +12,7 @@
 //   image-resident attention (small maps, regions of up to 8 tokens; bra_mfma_small.hip) or
 //   k_attn_gen (everything else), then LCE added in place                       (Eq. 6, 7)
 //   k_gemm<false> Y = O Wo (Eq. 2)
+#include "bra_attn_dev.h"
 #include "bra_gemm.h"
 #include "bra_lce_dev.h"
 
@@ -68,45 +69,6 @@ __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X,
 // Routed attention (Eq. 6, Eq. 1) for any region size and heads of 32 or 64 channels.  Q comes multiplied by
 // scale * log2(e), so scores are exponents of 2.
 //
-// Softmax step shared by the two kernels below, for KT tiles of 16 keys x 16 queries of one head: scores
-// s[t][j] = S^T[key 16 t + 4 g + j][query i] relative to the reference m (which entered the product as its accumulator
-// input, so a score costs no subtraction), weights p = 2^s in the operand order of O^T += V^T P^T.  The reference moves,
-// and the sums are rescaled, only when a lane's own score exceeds it by 8 (weights stay below 2^8), which needs no exchange
-// between lanes; the quotient O / l does not depend on it.  FIRST: the reference is this block's maximum.
-template <bool FIRST, int KT, int NDT>
-__device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, f32x4 &l, f32x4 (&acc)[NDT], bf16x8 (&pb)[KT / 2])
-{
-    float mx = s[0][0];
-#pragma unroll
-    for (int t = 0; t < KT; ++t)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) mx = fmaxf(mx, s[t][j]);
-    if (FIRST || __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0) {
-        const float up = FIRST ? cross_row_max(mx) : fmaxf(cross_row_max(mx), 0.f);
-        m += up;
-#pragma unroll
-        for (int t = 0; t < KT; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) s[t][j] -= up;
-        if (!FIRST) {
-            const float alpha = __builtin_amdgcn_exp2f(-up);
-            l *= alpha;
-#pragma unroll
-            for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
-        }
-    }
-#pragma unroll
-    for (int tp = 0; tp < KT / 2; ++tp) {
-        float p[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(s[2 * tp + e / 4][e % 4]);
-        pb[tp] = pack8(p);
-        // denominators of the same rounded weights, from a product with an all-ones operand
-        const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
-        l = mfma16(__builtin_bit_cast(bf16x8, ones), pb[tp], l);
-    }
-}
-
 // Regions of more than 32 tokens: workgroup (image, region, tile of 64 NQ queries of the region, group of 64 channels = 2
 // or 1 heads), wavefront w with NQ query tiles of 16.  The k n routed keys are taken 64 at a time: their K and V rows (the
 // group's 128 bytes each, found by index in the projected maps) go straight from memory into one of two LDS buffers while
@@ -128,7 +90,7 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
     const int C = D.C, ncg = C / 64, n = D.n, kn = D.kn;
     const int cg = blockIdx.x % ncg, qt = (blockIdx.x / ncg) % qtiles;
     const int reg = (blockIdx.x / (ncg * qtiles)) % D.R, b = blockIdx.x / (ncg * qtiles * D.R);
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
     const float rw_inv = 1.0f / (float)D.rw, n_inv = 1.0f / (float)n, s_inv = 1.0f / (float)D.S;
     const size_t img = (size_t)b * D.N * C + 64 * cg;
     auto region_origin = [&](int r) {
@@ -229,19 +191,20 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
             __builtin_amdgcn_sched_barrier(0);    // one head at a time: interleaved, they take twice the registers
         }
     };
+    const bool idle = 64 * NQ * qt + 16 * NQ * wave >= n;      // a wavefront without queries only brings its rows
     __syncthreads();                              // the table is in place
     request(0, K0, V0);
     __syncthreads();                              // a barrier waits for the direct loads before it
     if (64 < kn) request(64, K1, V1);
-    block(0, K0, V0, std::true_type{});
+    if (!idle) block(0, K0, V0, std::true_type{});
     for (int k0 = 64; k0 < kn; k0 += 128) {
         __syncthreads();
         if (k0 + 64 < kn) request(k0 + 64, K0, V0);
-        block(k0, K1, V1, std::false_type{});
+        if (!idle) block(k0, K1, V1, std::false_type{});
         if (k0 + 64 >= kn) break;
         __syncthreads();
         if (k0 + 128 < kn) request(k0 + 128, K1, V1);
-        block(k0 + 64, K0, V0, std::false_type{});
+        if (!idle) block(k0 + 64, K0, V0, std::false_type{});
     }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -259,33 +222,23 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
 // ---------------------------------------------------------------------------
 // The same for regions of at most 32 tokens (16 NQ of them in NQ query tiles), where the tile of 64 queries above leaves
 // half or more of its wavefronts with copies: a wavefront works on its own, with all queries of a region and 64 channels
-// (2 or 1 heads).  It brings its K and V rows straight from memory into its own part of LDS, 32 keys at a time into one
-// of two buffers while the other is worked on; there is no barrier but the one behind the table of the region's routed
-// origins.  Rows of 128 bytes lie unpadded; 16-byte pieces are exchanged so that the row reads of K (piece c of row r at
+// (2 or 1 heads), any four of them in a workgroup.  It brings its K and V rows straight from memory into its own part of LDS, 32 keys at a time into one
+// of two buffers while the other is worked on; there is no barrier.  Rows of 128 bytes lie unpadded; 16-byte pieces are exchanged so that the row reads of K (piece c of row r at
 // c ^ r % 8) and the transposing reads of V (c ^ 4 (r / 2 % 2)) meet different banks.
 // Bound by the gather out of the L2s: 302 MB for 8 images of 32 x 32 x 768 with 12 regions of 16 tokens each.
-// A direct load of 16 bytes per lane to 1024 consecutive bytes of LDS (l: the same for all lanes) that the compiler does
-// not count: it would wait for all outstanding ones before the next LDS read, those of the buffer in flight among them.
-// The caller waits (s_waitcnt vmcnt) before it reads the buffer.  M0 is the instruction's own here: nothing else in the
-// kernels that use this sets it.
-__device__ __forceinline__ void load_to_lds_untracked(const bf16_t *g, bf16_t *l)
-{
-    const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) bf16_t *)l);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(g) : "memory");
-}
-
 template <int HD, int NQ>
-__global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int groups, int total)
+__global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int items)
 {
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16, KB = 32;
     __shared__ __attribute__((aligned(16))) bf16_t S0[4 * 2 * KB * 64];      // [wavefront][K, V][32 keys][64]
     __shared__ __attribute__((aligned(16))) bf16_t S1[4 * 2 * KB * 64];
-    extern __shared__ int origins[];             // [k]: first token of the routed regions
+    extern __shared__ int origin_tables[];       // [4][k]: first token of the routed regions
     const int C = D.C, ncg = C / 64, n = D.n, kn = D.kn;
-    const int wid = swizzled_block();            // the workgroups of an image share an L2
-    if (wid >= total) return;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, g = lane / 16, i = lane % 16;
-    const int cg = (wid % groups) * 4 + wave, reg = (wid / groups) % D.R, b = wid / (groups * D.R);
+    const int item = __builtin_amdgcn_readfirstlane(4 * swizzled_block() + wave);      // those of an image share an L2
+    if (item >= items) return;
+    const int cg = item % ncg, reg = (item / ncg) % D.R, b = item / (ncg * D.R);
+    int *origins = origin_tables + wave * D.k;
     const float rw_inv = 1.0f / (float)D.rw, n_inv = 1.0f / (float)n, s_inv = 1.0f / (float)D.S;
     auto region_origin = [&](int r) {
         const int ry = fast_div(r, s_inv);
@@ -296,14 +249,13 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
         return sy * D.W + slot - sy * D.rw;
     };
     const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
-    const bool report = A.Ir_out && A.Ir_out != A.Ir_src && wid % groups == 0;
-    for (int p = threadIdx.x; p < D.k; p += 256) {
+    const bool report = A.Ir_out && A.Ir_out != A.Ir_src && cg == 0;
+    for (int p = lane; p < D.k; p += kWave) {
         const int j = irp[p];
         origins[p] = region_origin(region_index(j, D.R));
         if (report) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = j;
     }
-    __syncthreads();
-    if (cg >= ncg) return;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // the table is read by other lanes
 
     const size_t img = (size_t)b * D.N * C + 64 * cg;
     const int origin = region_origin(reg);
@@ -394,18 +346,23 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
             }
         }
     };
-    const int last = kn - 1;
+    // requests the keys from k0 on, if there are any, and waits for the 8 loads of the block before
+    auto advance = [&](int k0, bf16_t *S) {
+        if (k0 < kn) {
+            request(k0, S);
+            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        } else {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+    };
     request(0, S0);
-    request(min(KB, last), S1);                               // past the end: not used
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");          // the 8 loads of the block before have arrived
+    advance(KB, S1);
     block(0, S0, std::true_type{});
     for (int k0 = KB; k0 < kn; k0 += 2 * KB) {
-        request(min(k0 + KB, last), S0);
-        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        advance(k0 + KB, S0);
         block(k0, S1, std::false_type{});
         if (k0 + KB >= kn) break;
-        request(min(k0 + 2 * KB, last), S1);
-        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        advance(k0 + 2 * KB, S1);
         block(k0 + KB, S0, std::false_type{});
     }
 #pragma unroll
@@ -469,13 +426,13 @@ GemmRegions region_job(const Dims &D, const WideWs &w)
 
 void launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
 {
-    const int groups = (D.C / 64 + 3) / 4, total = D.B * D.R * groups;
-    const dim3 grid((unsigned)((total + 7) / 8 * 8)), block(256);
-    const size_t smem = (size_t)D.k * sizeof(int);
-    if (D.d == 32 && D.n <= 16) hipLaunchKernelGGL((k_attn_rows<32, 1>), grid, block, smem, st, A, O, D, groups, total);
-    else if (D.d == 32) hipLaunchKernelGGL((k_attn_rows<32, 2>), grid, block, smem, st, A, O, D, groups, total);
-    else if (D.n <= 16) hipLaunchKernelGGL((k_attn_rows<64, 1>), grid, block, smem, st, A, O, D, groups, total);
-    else hipLaunchKernelGGL((k_attn_rows<64, 2>), grid, block, smem, st, A, O, D, groups, total);
+    const int items = D.B * D.R * (D.C / 64), blocks = (items + 3) / 4;
+    const dim3 grid((unsigned)((blocks + 7) / 8 * 8)), block(256);
+    const size_t smem = (size_t)4 * D.k * sizeof(int);
+    if (D.d == 32 && D.n <= 16) hipLaunchKernelGGL((k_attn_rows<32, 1>), grid, block, smem, st, A, O, D, items);
+    else if (D.d == 32) hipLaunchKernelGGL((k_attn_rows<32, 2>), grid, block, smem, st, A, O, D, items);
+    else if (D.n <= 16) hipLaunchKernelGGL((k_attn_rows<64, 1>), grid, block, smem, st, A, O, D, items);
+    else hipLaunchKernelGGL((k_attn_rows<64, 2>), grid, block, smem, st, A, O, D, items);
 }
 
 template <int NQ>
@@ -518,11 +475,11 @@ int route_steps(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideWs
 
 // Q, K, V = X Wqkv into three token maps (Eq. 3) for any C that is a multiple of 64: the projection of
 // the wide pipeline, for the backward pass.
-int wide_project_qkv(const Dims &D, const void *X, const void *Wqkv, bf16_t *Q, bf16_t *K, bf16_t *V, hipStream_t st)
+int wide_project_qkv(const Dims &D, const void *X, const void *Wqkv, bf16_t *Q, bf16_t *K, bf16_t *V, float q_scale, hipStream_t st)
 {
     const long M = (long)D.B * D.N;
     if (D.C % 64 || M > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    return gemm((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, GemmOut{{Q, K, V}, D.C, {nullptr, nullptr}}, nullptr,
+    return gemm((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, GemmOut{{Q, K, V}, D.C, {nullptr, nullptr}, nullptr, nullptr, 0, q_scale}, nullptr,
                 K_MFMA_QKV, st);
 }
 
@@ -581,7 +538,7 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     } else {
         {
             ProfScope ps(st, K_MFMA_ATTENTION);
-            if (D.n <= 32) launch_attn_rows(D, A, w.o, st);
+            if (D.n <= 32 && D.k <= 1024) launch_attn_rows(D, A, w.o, st);      // its tables fit in LDS
             else launch_attn_gen(D, A, w.o, st);
         }
         rc = lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);

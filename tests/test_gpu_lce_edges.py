@@ -29,15 +29,40 @@ def test_lce_edges(B, H, W, C, heads, S, k):
 
 
 MAPS = [  # (B, H, W, C, heads, S, k): image-resident attention backward: 1 .. 8 tokens per region, one and several key blocks
-    (2, 7, 7, 64, 2, 7, 49),         # one token per region, 49 keys
-    (1, 10, 5, 64, 2, 5, 7),         # 2 x 1 regions
-    (2, 9, 6, 64, 2, 3, 9),          # 3 x 2 regions, every region
-    (1, 28, 14, 64, 2, 7, 30),       # 8 tokens, 392 tokens per image (16 wavefronts, most of the LDS), 4 key blocks
-    (1, 16, 16, 96 + 32, 4, 8, 16),  # 64 keys exactly
+    (64, 7, 7, 64, 2, 7, 49),        # one token per region, 49 keys
+    (64, 10, 5, 64, 2, 5, 7),        # 2 x 1 regions
+    (64, 9, 6, 64, 2, 3, 9),         # 3 x 2 regions, every region
+    (64, 28, 14, 64, 2, 7, 30),      # 8 tokens, 392 tokens per image (16 wavefronts, most of the LDS), 4 key blocks
+    (32, 16, 16, 96 + 32, 4, 8, 16), # 64 keys exactly
 ]
 
 
 @pytest.mark.parametrize("B,H,W,C,heads,S,k", MAPS)
 def test_backward_image_resident(B, H, W, C, heads, S, k):
     X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=8800 + H * W + C, dtype="bf16")
+    compare_backward(X, Wqkv, Wo, Wlce, "bf16", heads, S, k, path="mfma")
+
+
+REGIONS = [  # (B, H, W, C, heads, S, k): attention backward region by region
+    # a wavefront per region: 1, 16, 17 and 32 tokens; one block of keys, ragged blocks, more entries than one list holds
+    (2, 7, 7, 64, 1, 7, 33),
+    (6, 28, 28, 64, 2, 7, 3),
+    (2, 119, 7, 64, 2, 7, 3),
+    (2, 32, 64, 192, 6, 8, 16),
+    (5, 28, 21, 128, 4, 7, 7),
+    # four wavefronts per tile: two blocks, ragged tiles of 32 tokens, five
+    (1, 28, 28, 64, 2, 7, 4),
+    (2, 10, 14, 64, 1, 2, 3),
+    (1, 35, 28, 128, 2, 7, 20),
+    # four tiles of a region per workgroup: idle wavefronts, whole tiles, two tiles per wavefront
+    (4, 42, 42, 128, 4, 7, 3),
+    (3, 56, 56, 128, 2, 7, 1),
+    (9, 88, 80, 64, 2, 8, 2),
+    (5, 70, 77, 128, 2, 7, 3),
+]
+
+
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", REGIONS)
+def test_backward_regions(B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=9200 + H * W + C, dtype="bf16")
     compare_backward(X, Wqkv, Wo, Wlce, "bf16", heads, S, k, path="mfma")
