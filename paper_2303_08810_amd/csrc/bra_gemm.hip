@@ -277,14 +277,14 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
     const int pairs = K / 128;
     request(0, A0, B0);
     for (int p = 0; p < pairs; ++p) {
-        __syncthreads();                          // the chunk has arrived; the other buffer has been read
+        arrive_barrier();                          // the chunk has arrived; the other buffer has been read
         request(128 * p + 64, A1, B1);
         multiply(A0, B0);
-        __syncthreads();
+        arrive_barrier();
         request(min(128 * p + 128, K - 64), A0, B0);      // past the end: the last chunk again, not used
         multiply(A1, B1);
     }
-    __syncthreads();
+    arrive_barrier();
     if (K % 128) multiply(A0, B0);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -472,11 +472,11 @@ __device__ __forceinline__ void tn_block(const GemmTn &J, int block, long M, int
     };
     request(t_begin, A0, B0);
     for (long t0 = t_begin; t0 < t_end; t0 += 128) {
-        __syncthreads();
+        arrive_barrier();
         if (t0 + 64 < t_end) request(t0 + 64, A1, B1);
         blank(t0, A0);
         multiply(A0, B0);
-        __syncthreads();
+        arrive_barrier();
         if (t0 + 128 < t_end) request(t0 + 128, A0, B0);
         if (t0 + 64 < t_end) {
             blank(t0 + 64, A1);

@@ -167,8 +167,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
     auto advance = [&](int s) {
         const bool more = s + 1 < 2 * nb && (s + 1 < nb || s + 1 > nb + 1);
         if (SHARED) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
+            arrive_barrier();
             if (more) request(block_of(s + 1));
         } else if (more) {
             request(block_of(s + 1));
@@ -626,8 +625,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
         for (int s = 0; s < nb; ++s) {
             const bool more = s + 1 < nb;
             if (SHARED) {
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();
+                arrive_barrier();
                 if (more) request(s + 1);
             } else if (more) {
                 request(s + 1);

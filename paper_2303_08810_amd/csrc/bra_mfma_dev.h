@@ -104,12 +104,19 @@ __device__ __forceinline__ s16x4 lds_read_tr16(const bf16_t *p)
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)p);
 }
 
-// 16 bytes per lane straight from memory into 1024 consecutive bytes of LDS (l: the same for all lanes); a barrier waits
-// for the ones before it.
+// 16 bytes per lane straight from memory into 1024 consecutive bytes of LDS (l: the same for all lanes).  Other wavefronts
+// may read them behind arrive_barrier(): a plain barrier does not wait for such loads on every path.
 __device__ __forceinline__ void load_to_lds(const bf16_t *g, bf16_t *l)
 {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) unsigned *)g,
                                      (__attribute__((address_space(3))) unsigned *)l, 16, 0, 0);
+}
+
+// Barrier behind which the direct loads that any wavefront issued before it have arrived.
+__device__ __forceinline__ void arrive_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
 }
 
 // A 16-byte store to global memory.  MODE 0: an ordinary store (the line stays dirty in this

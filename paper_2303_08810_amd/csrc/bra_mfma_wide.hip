@@ -194,15 +194,15 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
     const bool idle = 64 * NQ * qt + 16 * NQ * wave >= n;      // a wavefront without queries only brings its rows
     __syncthreads();                              // the table is in place
     request(0, K0, V0);
-    __syncthreads();                              // a barrier waits for the direct loads before it
+    arrive_barrier();
     if (64 < kn) request(64, K1, V1);
     if (!idle) block(0, K0, V0, std::true_type{});
     for (int k0 = 64; k0 < kn; k0 += 128) {
-        __syncthreads();
+        arrive_barrier();
         if (k0 + 64 < kn) request(k0 + 64, K0, V0);
         if (!idle) block(k0, K1, V1, std::false_type{});
         if (k0 + 64 >= kn) break;
-        __syncthreads();
+        arrive_barrier();
         if (k0 + 128 < kn) request(k0 + 128, K1, V1);
         if (!idle) block(k0 + 64, K0, V0, std::false_type{});
     }
