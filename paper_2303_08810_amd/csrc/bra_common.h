@@ -41,25 +41,18 @@ __device__ inline float load_f32(const bf16_t *p) { return bf16_to_f32(*p); }
 __device__ inline void store_from_f32(float *p, float v) { *p = v; }
 __device__ inline void store_from_f32(bf16_t *p, float v) { *p = f32_to_bf16(v); }
 
-// GELU(t) = t Phi(t) = t / 2 + |t| (1 - erfc(|t| / sqrt 2)) / 2.  erfc by the approximation of
-// Abramowitz & Stegun 7.1.28, erfc(x) = (1 + a1 x + .. + a6 x^6)^-16 (absolute error below
-// 3e-7, far inside what a bf16 result resolves; one reciprocal is its only slow instruction);
-// the coefficients below are a_k / 2^(k/2), so that the polynomial takes |t| itself.
+// GELU(t) = t Phi(t) = max(t, 0) - a Phi(-a), a = |t|, with log2 Phi(-a) as a polynomial of degree 5 (least maximum error
+// of a Phi(-a) over a <= 6, found by linear programming; it falls ever faster beyond).  Absolute error below 7e-7, that of
+// the float32 arithmetic included; one exponential is its only slow instruction.  Past 16 the product is 0.
 __device__ __forceinline__ float gelu_f32(float t)
 {
-    const float a = fabsf(t);
-    float p = fmaf(5.382975000e-06f, a, 4.889063564e-05f);
-    p = fmaf(p, a, 3.800357500e-05f);
-    p = fmaf(p, a, 3.277626324e-03f);
-    p = fmaf(p, a, 2.114100615e-02f);
-    p = fmaf(p, a, 4.986734697e-02f);
-    p = fmaf(p, a, 1.0f);
-    p *= p;
-    p *= p;
-    p *= p;
-    p *= p;                                                  // overflows to infinity for large |t|: erfc = 0
-    const float q = fmaf(__builtin_amdgcn_rcpf(p), -0.5f, 0.5f);
-    return fmaf(a, q, 0.5f * t);
+    const float a = fminf(fabsf(t), 16.0f);
+    float p = fmaf(-4.732939124e-04f, a, 7.084460463e-03f);
+    p = fmaf(p, a, -5.182716623e-02f);
+    p = fmaf(p, a, -4.599926472e-01f);
+    p = fmaf(p, a, -1.150787711e+00f);
+    p = fmaf(p, a, -1.000037670e+00f);
+    return fmaf(-a, __builtin_amdgcn_exp2f(p), fmaxf(t, 0.f));
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
