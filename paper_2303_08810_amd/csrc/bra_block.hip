@@ -1,6 +1,7 @@
 // One whole BiFormer block around BRA (Sec. 3.4), bf16 tensors, float32 arithmetic:
 //
-//   k_token_ln<POS>   X1 = X + DWConv3x3(X) + bpos,  Xn = LayerNorm1(X1)      one pass over X
+//   k_pos_ln          X1 = X + DWConv3x3(X) + bpos,  Xn = LayerNorm1(X1)      one pass over X
+//   (k_token_ln<POS> for channel counts with several chunks of 8 per lane)
 //   BRA               Y  = BRA(Xn)                   (Eq. 2-7; the kernel family picked for the shape)
 //   C <= 256:  k_mlp_fused64 (C = 64, weights resident in LDS) or k_mlp_stream (weights streamed):
 //                     Xout = X2 + MLP(LayerNorm2(X2)), X2 = X1 + Y, in one kernel
@@ -204,6 +205,146 @@ __global__ __launch_bounds__(256) void k_token_ln(const bf16_t *A, const bf16_t 
 #pragma unroll
                 for (int e = 0; e < 8; ++e) o[e] = fmaf((v[e] - mean) * rstd, gm[e], bt[e]);
                 if (valid) *(bf16x8 *)(Norm + (size_t)tok * C + c0) = pack8(o);
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_token_ln<POS> for the channel counts at which a lane owns one chunk of 8 channels and G = 8 .. 64 lanes share a token:
+// X1 = X + DWConv3x3(X) + bpos and Xn = LayerNorm1(X1), walking down columns.  A lane keeps the window's three rows of its
+// token's column and the two beside it, so a step reads three new tokens instead of nine, requested a step ahead; the
+// products run on v_dot2_f32_bf16, taps (0, 1) of a row as pairs of columns (one byte permute per channel), tap 2 on the
+// column as loaded, with zero in the other channel's half of its weight.
+// 50176 tokens, C = 128: 13.1 us (nine loads per token and float32 multiply-adds: 19.4; 38 MB in and out are 8 us);
+// 12.5 to 14.0 with strips of 14 down to 2 rows.
+template <int G>
+__device__ __forceinline__ float lanes_sum(float x)
+{
+    x = dpp_fadd<0xB1>(x);                  // quad_perm [1,0,3,2]
+    x = dpp_fadd<0x4E>(x);                  // [2,3,0,1]
+    x = dpp_fadd<0x141>(x);                 // row_half_mirror
+    if (G >= 16) x = dpp_fadd<0x140>(x);    // row_mirror
+    if (G >= 32) {
+        const int xi = __builtin_bit_cast(int, x);
+        const auto a = __builtin_amdgcn_permlane16_swap(xi, xi, false, false);
+        x = __builtin_bit_cast(float, (int)a[0]) + __builtin_bit_cast(float, (int)a[1]);
+    }
+    if (G >= 64) {
+        const int xi = __builtin_bit_cast(int, x);
+        const auto a = __builtin_amdgcn_permlane32_swap(xi, xi, false, false);
+        x = __builtin_bit_cast(float, (int)a[0]) + __builtin_bit_cast(float, (int)a[1]);
+    }
+    return x;
+}
+
+template <int G>
+__global__ __launch_bounds__(256) void k_pos_ln(const bf16_t *__restrict__ X, const bf16_t *__restrict__ Wpos,
+                                                const float *__restrict__ bpos, const float *__restrict__ gamma,
+                                                const float *__restrict__ beta, bf16_t *__restrict__ Sum,
+                                                bf16_t *__restrict__ Norm, int H, int W, int C, int strips, int height,
+                                                int columns, float eps)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    float *bias_s = (float *)smem, *gamma_s = bias_s + C, *beta_s = gamma_s + C;
+    const int tid = threadIdx.x, sub = tid % G, slot = tid / G, CH = C / 8;
+    for (int q = tid; q < C; q += 256) { bias_s[q] = bpos[q]; gamma_s[q] = gamma[q]; beta_s[q] = beta[q]; }
+    // lanes beyond the last chunk stand on it, add nothing to the sums and store nothing
+    const bool lane_on = sub < CH;
+    const int c0 = 8 * min(sub, CH - 1);
+    const float c_inv = 1.0f / (float)C;
+    unsigned pair_w[3][8], one_w[3][8];
+    {
+        unsigned raw[36];                   // 72 consecutive bf16: channel-major, (ky, kx) inside
+        const u32x4 *src = (const u32x4 *)(Wpos + (size_t)c0 * 9);
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            const u32x4 v = src[q];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) raw[4 * q + e] = v[e];
+        }
+        auto weight = [&](int e, int t) { return (9 * e + t) % 2 ? raw[(9 * e + t) / 2] >> 16 : raw[(9 * e + t) / 2] & 0xffffu; };
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                pair_w[ky][e] = weight(e, 3 * ky) | weight(e, 3 * ky + 1) << 16;
+                one_w[ky][e] = e % 2 ? weight(e, 3 * ky + 2) << 16 : weight(e, 3 * ky + 2);
+            }
+    }
+    __syncthreads();
+    // columns of all strips of all images one after the other; workgroups of an XCD take neighbouring ones
+    const int col = swizzled_block() * (256 / G) + slot, cc = min(col, columns - 1);
+    const int x = cc % W, r = cc / W, y0 = (r % strips) * height, y1 = col < columns ? min(y0 + height, H) : y0;
+    const size_t base = ((size_t)(r / strips) * H * W + x) * C + c0, pitch = (size_t)W * C;
+    const bool left = x > 0, right = x + 1 < W;
+    const int to_left = left ? -C : 0, to_right = right ? C : 0;
+    struct Row {
+        unsigned pair[8], one[4];
+    };
+    u32x4 next[3];
+    auto request = [&](int y) {
+        const bf16_t *at = X + base + (size_t)min(max(y, 0), H - 1) * pitch;
+        next[0] = *(const u32x4 *)(at + to_left);
+        next[1] = *(const u32x4 *)at;
+        next[2] = *(const u32x4 *)(at + to_right);
+    };
+    auto pack_row = [&](int y) {            // zero padding: what was read in its place is blanked
+        const bool in = (unsigned)y < (unsigned)H;
+        Row R;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned l = in && left ? next[0][e] : 0u, m = in ? next[1][e] : 0u;
+            R.pair[2 * e] = pair_lo(l, m);
+            R.pair[2 * e + 1] = pair_hi(l, m);
+            R.one[e] = in && right ? next[2][e] : 0u;
+        }
+        return R;
+    };
+    Row win[3];
+    request(y0 - 1);
+    win[0] = pack_row(y0 - 1);
+    request(y0);
+    win[1] = pack_row(y0);
+    request(y0 + 1);
+    for (int yb = y0; yb < y1; yb += 3) {
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            const int y = yb + u;
+            if (y >= y1) break;
+            win[(u + 2) % 3] = pack_row(y + 1);
+            request(y + 2);
+            const Row &mid = win[(u + 1) % 3];
+            float v[8], s = 0.f;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const f32x4 b4 = *(const f32x4 *)(bias_s + c0 + 4 * q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * q + e] = bf16_hi(mid.pair[4 * q + e]) + b4[e];
+            }
+#pragma unroll
+            for (int ky = 0; ky < 3; ++ky) {
+                const Row &R = win[(u + ky) % 3];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = dot2(one_w[ky][e], R.one[e / 2], dot2(pair_w[ky][e], R.pair[e], v[e]));
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s += v[e];
+            const float mean = lanes_sum<G>(lane_on ? s : 0.f) * c_inv;
+            float q2 = 0.f, o[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { o[e] = v[e] - mean; q2 = fmaf(o[e], o[e], q2); }
+            const float rstd = __builtin_amdgcn_rsqf(lanes_sum<G>(lane_on ? q2 : 0.f) * c_inv + eps);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const f32x4 g4 = *(const f32x4 *)(gamma_s + c0 + 4 * q), t4 = *(const f32x4 *)(beta_s + c0 + 4 * q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[4 * q + e] = fmaf(o[4 * q + e] * rstd, g4[e], t4[e]);
+            }
+            if (lane_on) {
+                const size_t at = base + (size_t)y * pitch;
+                *(bf16x8 *)(Sum + at) = pack8(v);
+                *(bf16x8 *)(Norm + at) = pack8(o);
             }
         }
     }
@@ -651,6 +792,36 @@ int launch_token_ln(const Dims &D, const bf16_t *A, const bf16_t *Badd, const br
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
+template <int G>
+int launch_pos_ln_t(const Dims &D, const bf16_t *X, const bra_block_params &p, bf16_t *Sum, bf16_t *Norm, float eps,
+                    hipStream_t st)
+{
+    // Strips as long as leaves about two wavefronts per SIMD: a strip reads two rows beside its own.
+    int height = 16;
+    while (height > 2 && (long)D.B * D.W * ((D.H + height - 1) / height) * G < 2048 * 64L) height /= 2;
+    const int strips = (D.H + height - 1) / height;
+    const long columns = (long)D.B * D.W * strips, blocks = ((columns * G + 255) / 256 + 7) / 8 * 8;
+    if (blocks > 0x7fffffffL / (256 / G)) return BRA_ERR_UNSUPPORTED;
+    ProfScope ps(st, K_BLK_POS_LN);
+    hipLaunchKernelGGL(k_pos_ln<G>, dim3((unsigned)blocks), dim3(256), (size_t)3 * D.C * sizeof(float), st, X,
+                       (const bf16_t *)p.Wpos, p.bpos, p.ln1_gamma, p.ln1_beta, Sum, Norm, D.H, D.W, D.C, strips, height,
+                       (int)columns, eps);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+int launch_pos_ln(const Dims &D, const bf16_t *X, const bra_block_params &p, bf16_t *Sum, bf16_t *Norm, float eps,
+                  hipStream_t st)
+{
+    const int g_one = lanes_one_chunk(D.C), G = g_one ? g_one : lanes_per_token(D.C);
+    if (D.C / 8 <= G) {
+        if (G == 8) return launch_pos_ln_t<8>(D, X, p, Sum, Norm, eps, st);
+        if (G == 16) return launch_pos_ln_t<16>(D, X, p, Sum, Norm, eps, st);
+        if (G == 32) return launch_pos_ln_t<32>(D, X, p, Sum, Norm, eps, st);
+        if (G == 64) return launch_pos_ln_t<64>(D, X, p, Sum, Norm, eps, st);
+    }
+    return launch_token_ln<kPos>(D, X, nullptr, p, p.ln1_gamma, p.ln1_beta, Sum, Norm, eps, st);
+}
+
 struct BlockWs {
     bf16_t *x1, *xn, *y, *hd;
     void *inner;
@@ -706,7 +877,7 @@ int block_forward(const Dims &D, int hidden, float eps, const void *X, const bra
         return generic_block_forward(D, hidden, eps, X, p, Xout, Ir_out_opt, Ir_in_opt, ws, bra_bytes, path, st);
     const BlockWs w = carve_block(D, hidden, bra_bytes, ws);
     const long M = (long)D.B * D.N;
-    int rc = launch_token_ln<kPos>(D, (const bf16_t *)X, nullptr, p, p.ln1_gamma, p.ln1_beta, w.x1, w.xn, eps, st);
+    int rc = launch_pos_ln(D, (const bf16_t *)X, p, w.x1, w.xn, eps, st);
     if (rc != BRA_OK) return rc;
     rc = (path == BRA_PATH_MFMA)
              ? mfma_forward(D, w.xn, p.Wqkv, p.Wo, p.Wlce, w.y, Ir_out_opt, Ir_in_opt, w.inner, st)

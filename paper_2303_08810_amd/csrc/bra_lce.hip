@@ -16,16 +16,7 @@ namespace lce {
 
 namespace {
 
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-using mfma::u32x2;
-
-__device__ __forceinline__ float dot2(unsigned a, unsigned b, float c)
-{
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), c, false);
-}
-// (lower halves of a, b) and (upper halves of a, b) as pairs: channel c and c + 1 of two tokens
-__device__ __forceinline__ unsigned pair_lo(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
-__device__ __forceinline__ unsigned pair_hi(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+using namespace mfma;
 
 // A window row: pairs of columns (0,1), (2,3) | (1,2), (3,4) per channel, and columns 4, 5 as loaded.
 struct Row {

@@ -64,6 +64,15 @@ __device__ __forceinline__ u32x2 pack4(f32x4 v)
 __device__ __forceinline__ float bf16_lo(unsigned u) { return __builtin_bit_cast(float, u << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned u) { return __builtin_bit_cast(float, u & 0xffff0000u); }
 
+// Two multiply-adds on bf16 pairs with a float32 sum (v_dot2_f32_bf16).
+__device__ __forceinline__ float dot2(unsigned a, unsigned b, float c)
+{
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), c, false);
+}
+// (lower halves of a, b) and (upper halves of a, b) as pairs: channel c and c + 1 of two tokens
+__device__ __forceinline__ unsigned pair_lo(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+__device__ __forceinline__ unsigned pair_hi(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
 // row / width without an integer division; exact for the small non-negative values
 // that occur here (row < 2^20).
 __device__ __forceinline__ int fast_div(int row, float width_inv)
