@@ -32,7 +32,9 @@ constexpr int kMaxLceTasks = 2;   // (row, 4-token segment, channel pair) tasks 
 // oacc[hh][dt] = normalised O^T[channel 32 h + 16 dt + 4 g + jj][query i], h = w + 4 hh.
 // Ks, Vs: [64][C + 16] bf16 each.  Ends with all wavefronts past their last LDS read only
 // after the caller's next barrier.
-template <int C>
+// N16: regions of 16 tokens.  A thread's rows of a block then have one or two slots, and its wavefront one region per
+// chunk: the address is a scalar base and an offset formed once.
+template <int C, bool N16>
 __device__ __forceinline__ void small_attention(const AttnArgs &A, const Dims &D, int log2n,
                                                 size_t img_off, const int32_t *irp, size_t qtok,
                                                 bf16_t *Ks, bf16_t *Vs,
@@ -53,20 +55,37 @@ __device__ __forceinline__ void small_attention(const AttnArgs &A, const Dims &D
     }
     SoftmaxState<HPW> st;
     st.init();
-    for (int k0 = 0; k0 < kn; k0 += 64) {
-        u32x4 kr[NLD], vr[NLD];
+    constexpr int ROWS = 256 / CH, SLOTS = ROWS >= 16 ? 1 : 16 / ROWS;      // rows between a thread's chunks; slots they fall on
+    unsigned slot_off[SLOTS];
+    if (N16) {
+#pragma unroll
+        for (int u = 0; u < SLOTS; ++u) {
+            const int slot = ((int)threadIdx.x / CH + ROWS * u) % 16, sy = fast_div(slot, rw_inv);
+            slot_off[u] = (unsigned)((sy * D.W + slot - sy * D.rw) * C + ((int)threadIdx.x % CH) * 8);
+        }
+    }
+    u32x4 kr[NLD], vr[NLD];
+    auto request = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < NLD; ++u) {
-            const int idx = threadIdx.x + 256 * u;
-            int key = k0 + idx / CH;
-            if (key >= kn) key = kn - 1;           // rows past the end repeat the last key; masked below
-            const int j = region_index(irp[key >> log2n], D.R), slot = key & (n - 1);
-            const int sy = fast_div(slot, rw_inv), jy = fast_div(j, s_inv);
-            const size_t tok = (size_t)(jy * D.rh + sy) * D.W + (j - jy * D.S) * D.rw + slot - sy * D.rw;
-            const size_t off = img_off + tok * C + (idx % CH) * 8;
+            size_t off;
+            if (N16) {
+                const int row = wave * (kWave / CH) + ROWS * u;             // of the wavefront's first chunk; 16 divides kn
+                const int p = __builtin_amdgcn_readfirstlane(min((k0 + row) / 16, kn / 16 - 1));
+                const int j = region_index(irp[p], D.R), jy = fast_div(j, s_inv);
+                off = img_off + (size_t)__builtin_amdgcn_readfirstlane((jy * D.rh * D.W + (j - jy * D.S) * D.rw) * C) + slot_off[u % SLOTS];
+            } else {
+                const int idx = threadIdx.x + 256 * u, key = min(k0 + idx / CH, kn - 1);      // rows past the end repeat the last key; masked below
+                const int j = region_index(irp[key >> log2n], D.R), slot = key & (n - 1);
+                const int sy = fast_div(slot, rw_inv), jy = fast_div(j, s_inv);
+                off = img_off + ((size_t)(jy * D.rh + sy) * D.W + (j - jy * D.S) * D.rw + slot - sy * D.rw) * C + (idx % CH) * 8;
+            }
             kr[u] = *(const u32x4 *)(A.K + off);
             vr[u] = *(const u32x4 *)(A.V + off);
         }
+    };
+    for (int k0 = 0; k0 < kn; k0 += 64) {
+        request(k0);
         if (k0) __syncthreads();                   // the previous block has been read
 #pragma unroll
         for (int u = 0; u < NLD; ++u) {
@@ -121,6 +140,8 @@ struct SmallSmem {
     }
 };
 
+// Bound by vector issue.  64 x 28 x 28 x 128, k = 4: 28.2 us (LCE on float32 multiply-adds and a token address formed per
+// row: 30.9; requesting the next key block ahead changed nothing).
 template <int C>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 128 ? 4 : 2, 4)))
 void k_small(AttnArgs A, Dims D, int log2n)
@@ -174,11 +195,11 @@ void k_small(AttnArgs A, Dims D, int log2n)
     const int cpair = threadIdx.x % cp_n;
     unsigned wl[25];        // tap t of channels (c, c + 1) as a packed pair, from the tap-major table
 #pragma unroll
-    for (int t = 0; t < 25; ++t) wl[t] = *(const unsigned *)(A.WlT + (size_t)t * C + 2 * cpair);
+    for (int t = 0; t < 25; ++t) wl[t] = *(const unsigned *)(A.WlT + (unsigned)(t * C + 2 * cpair));
 
     f32x4 oacc[HPW][2];     // normalised attention output of this wavefront's heads
     BRA_TRACE(1);
-    small_attention<C>(A, D, log2n, img_off, irp, qtok, Ks, Vs, oacc);
+    small_attention<C, true>(A, D, log2n, img_off, irp, qtok, Ks, Vs, oacc);
     BRA_TRACE(2);
     __builtin_amdgcn_s_setprio(2);      // late phases first: the workgroup's LDS is freed sooner
     __syncthreads();        // the key blocks have been read: the halo tile takes their place
@@ -189,8 +210,19 @@ void k_small(AttnArgs A, Dims D, int log2n)
         tile_store<C, CS, NBH>(Hs, hreg, hrows, first);
     }
 
-    // LCE (Eq. 7) of the region's tokens
-    auto tap = [&](int ch, int t) { return ch ? bf16_hi(wl[t]) : bf16_lo(wl[t]); };
+    // LCE (Eq. 7) of the region's tokens on the two-element dot product: taps (0,1), (2,3) of a row per channel against
+    // pairs of columns, tap 4 against the column as loaded with zero in the other channel's half
+    unsigned w01[5][2], w23[5][2], w4[5][2];
+#pragma unroll
+    for (int ky = 0; ky < 5; ++ky) {
+        const unsigned *w = wl + 5 * ky;
+        w01[ky][0] = pair_lo(w[0], w[1]);
+        w01[ky][1] = pair_hi(w[0], w[1]);
+        w23[ky][0] = pair_lo(w[2], w[3]);
+        w23[ky][1] = pair_hi(w[2], w[3]);
+        w4[ky][0] = w[4] & 0xffffu;
+        w4[ky][1] = w[4] & 0xffff0000u;
+    }
     float lce[kMaxLceTasks][2][4];
     __syncthreads();        // the halo tile is complete
     BRA_TRACE(4);
@@ -201,25 +233,29 @@ void k_small(AttnArgs A, Dims D, int log2n)
         for (int x = 0; x < 4; ++x) lce[tk][0][x] = lce[tk][1][x] = 0.f;
         if (task < tasks) {
             const int seg = (task / cp_n) % segs, r = task / (cp_n * segs);
+            const bf16_t *row = Hs + (r * hw + seg * 4) * CS + 2 * cpair;
 #pragma unroll
-            for (int ky = 0; ky < 5; ++ky) {
-                float v0[8], v1[8];
+            for (int ky = 0; ky < 5; ++ky, row += hw * CS) {
+                // a ragged segment reads on behind its row, for results that are not kept
+                unsigned v[8], even[3][2], odd[3][2];
 #pragma unroll
-                for (int x = 0; x < 8; ++x) {
-                    const int hx = min(seg * 4 + x, hw - 1);    // a ragged segment re-reads the last column; unused
-                    const unsigned u = *(const unsigned *)(Hs + ((r + ky) * hw + hx) * CS + 2 * cpair);
-                    v0[x] = bf16_lo(u);
-                    v1[x] = bf16_hi(u);
+                for (int x = 0; x < 8; ++x) v[x] = *(const unsigned *)(row + x * CS);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    even[p][0] = pair_lo(v[2 * p], v[2 * p + 1]);
+                    even[p][1] = pair_hi(v[2 * p], v[2 * p + 1]);
+                    odd[p][0] = pair_lo(v[2 * p + 1], v[2 * p + 2]);
+                    odd[p][1] = pair_hi(v[2 * p + 1], v[2 * p + 2]);
                 }
 #pragma unroll
-                for (int kx = 0; kx < 5; ++kx) {
-                    const float w0 = tap(0, ky * 5 + kx), w1 = tap(1, ky * 5 + kx);
+                for (int ch = 0; ch < 2; ++ch)
 #pragma unroll
                     for (int x = 0; x < 4; ++x) {
-                        lce[tk][0][x] = fmaf(w0, v0[x + kx], lce[tk][0][x]);
-                        lce[tk][1][x] = fmaf(w1, v1[x + kx], lce[tk][1][x]);
+                        float s = lce[tk][ch][x];
+                        s = dot2(w01[ky][ch], x % 2 ? odd[x / 2][ch] : even[x / 2][ch], s);
+                        s = dot2(w23[ky][ch], x % 2 ? odd[x / 2 + 1][ch] : even[x / 2 + 1][ch], s);
+                        lce[tk][ch][x] = dot2(w4[ky][ch], v[x + 4], s);
                     }
-                }
             }
         }
     }
@@ -316,7 +352,7 @@ __global__ __launch_bounds__(256) void k_attn_small(AttnArgs A, bf16_t *__restri
     const size_t qtok = (size_t)(regy * D.rh + qy) * D.W + (reg - regy * D.S) * D.rw + qs - qy * D.rw;
 
     f32x4 oacc[HPW][2];
-    small_attention<C>(A, D, log2n, img_off, irp, qtok, Ks, Vs, oacc);
+    small_attention<C, false>(A, D, log2n, img_off, irp, qtok, Ks, Vs, oacc);
     if (i < n) {
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
