@@ -1905,6 +1905,12 @@ static bool specialised(const Dims &D)
     if (D.dtype != BRA_BF16 || D.d != 32) return false;
     if (D.C != 64 && D.C != 128 && D.C != 256) return false;
     if ((long)D.B * D.R * (D.n / 64 + 1) + 8 > 0x7fffffffL) return false;
+    // Regions of fewer than 16 tokens, where both pipelines use the same attention: the general one's smaller launches win
+    // for one token per region (4 x 7 x 7 x 64: 20.5 against 16.3 us), for more than 64 regions, whose routing is not part
+    // of the projection's launch (4 x 32 x 32 x 64, S = 16: 39 against 29), for C = 64, and for C = 128 up to 8192 tokens
+    // (16 x 16 x 32, k = 12: 42.8 against 38.4; 48 x 16 x 32: 65 against 72).
+    if (D.n < 16 && (D.n == 1 || !fast_route_ok(D) || D.C == 64 || (D.C == 128 && (long)D.B * D.N <= 8192)) && wide_supported(D))
+        return false;
     if (!fast_route_ok(D) && !generic_supported(D)) return false;   // fallback routing kernels
     return attn_big_ok(D) || small_supported(D);
 }
