@@ -24,6 +24,8 @@ using mfma::cross_row_sum;
 using mfma::f32x2;
 using mfma::f32x4;
 using mfma::kWave;
+using mfma::divide;
+using mfma::Places;
 using mfma::u32x2;
 
 __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c)
@@ -217,9 +219,10 @@ __global__ __launch_bounds__(256) void k_pool(const T *__restrict__ X, float *__
     const int sub = (int)(idx % SUB);
     const int cc = (int)(item % CH), r = (int)((item / CH) % D.R), b = (int)(item / ((long)CH * D.R));
     const T *base = X + (((size_t)b * D.H + (r / D.S) * D.rh) * D.W + (r % D.S) * D.rw) * D.C + 4 * cc;
+    const float rw_inv = 1.0f / (float)D.rw;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     for (int slot = sub; slot < D.n; slot += SUB) {
-        const int y = slot / D.rw, x = slot - y * D.rw;
+        const int y = D.rh < (1 << 20) ? divide(slot, D.rw, rw_inv) : slot / D.rw, x = slot - y * D.rw;
         acc += load4<VEC>(base + ((size_t)y * D.W + x) * D.C, D.C - 4 * cc);
     }
     for (int off = 1; off < SUB; off *= 2)
@@ -242,12 +245,6 @@ struct AttnShape {
     static constexpr int CW = DP * HPW, P = CW + 4, KB = CW <= 64 ? 64 : 32, TPH = 4 / HPW, QT = 16 * TPH;
 };
 
-// Token (within the image) of slot `slot` of region r.
-__device__ __forceinline__ int region_token(const Dims &D, int r, int slot)
-{
-    return ((r / D.S) * D.rh + slot / D.rw) * D.W + (r % D.S) * D.rw + slot % D.rw;
-}
-
 // Rows of a token map -> registers: channels of the workgroup's HPW heads, 4 at a time; head h0 + hl owns
 // channels [(h0 + hl) d, (h0 + hl + 1) d).
 // With VEC a chunk past the end reads the row's first channels: blank it with head_chunk_ok where it is used, not
@@ -269,8 +266,34 @@ __device__ __forceinline__ f32x4 blank_head_chunk(f32x4 v, int c4, int h0, const
     return !VEC || head_chunk_left<DP>(c4, h0, D) > 0 ? v : f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
+// acc[dt] += T^T x w: T's rows 16 t + 4 g + e (T points at row 4 g, column i) against the weights w[t][e], columns 16 dt + i.
+// The operands of the next 16 rows are on their way while this tile's products run.
+template <int KT, int NS>
+__device__ __forceinline__ void rows_product(const float *T, int P, const f32x4 (&w)[KT], f32x4 (&acc)[NS])
+{
+    float v[2][4][NS];
+    auto load = [&](int t) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int dt = 0; dt < NS; ++dt) v[t % 2][e][dt] = T[(16 * t + e) * P + 16 * dt];
+    };
+    load(0);
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+        if (t + 1 < KT) load(t + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int dt = 0; dt < NS; ++dt) acc[dt] = mfma_f32(v[t % 2][e][dt], w[t][e], acc[dt]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// HPW = 1: as many wavefronts as the region's query tiles of 16 fill (3 to 8; more tiles are dealt out evenly).
 template <int DP, int HPW, bool VEC>
-__global__ __launch_bounds__(256) void k_attention(const float *__restrict__ QKV, const int32_t *__restrict__ Ir,
+__global__ __launch_bounds__(HPW == 1 ? 512 : 256, DP == 32 ? 4 : 2) void k_attention(const float *__restrict__ QKV, const int32_t *__restrict__ Ir,
                                                    float *__restrict__ O, Dims D, int hgroups, int qtiles)
 {
     typedef AttnShape<DP, HPW> L;
@@ -279,48 +302,58 @@ __global__ __launch_bounds__(256) void k_attention(const float *__restrict__ QKV
     __shared__ __attribute__((aligned(16))) float Vs[KB * P];
     const int hg = blockIdx.x % hgroups, qt = (blockIdx.x / hgroups) % qtiles;
     const int reg = (blockIdx.x / (hgroups * qtiles)) % D.R, b = blockIdx.x / (hgroups * qtiles * D.R);
+    const int T = HPW == 1 ? (int)blockDim.x : 256, tph = HPW == 1 ? T / kWave : L::TPH;      // query tiles
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
-    const int C3 = 3 * D.C, kn = D.kn, hl = wave / L::TPH, h = hg * HPW + hl;
+    const int C3 = 3 * D.C, kn = D.kn, hl = HPW == 1 ? 0 : wave / L::TPH, h = hg * HPW + hl;
     const float *img = QKV + (size_t)b * D.N * C3;
     const int32_t *irp = Ir + ((size_t)b * D.R + reg) * D.k;
-    const int slot = L::QT * qt + 16 * (wave % L::TPH) + i;
-    const int qtok = region_token(D, reg, min(slot, D.n - 1));
+    const int slot0 = 16 * (tph * qt + (HPW == 1 ? wave : wave % L::TPH)), slot = slot0 + i;
+    const Places<true> at(D);
+    const float n_inv = 1.0f / (float)D.n;
+    const int qtok = at.origin(reg) + at.slot(min(slot, D.n - 1));
     f32x4 qf[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s)
         qf[s] = blank_head_chunk<DP, VEC>(load_head_chunk<DP, VEC>(img + (size_t)qtok * C3, 4 * s + g, h, D), 4 * s + g, h, D);
 
-    constexpr int NL = KB * CW / 4 / 256;
+    constexpr int CHUNKS = KB * CW / 4, NL = HPW == 1 ? (CHUNKS + 191) / 192 : CHUNKS / 256;
     f32x4 kr[NL], vr[NL];
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
-            const int idx = tid + 256 * u, key = min(k0 + idx / (CW / 4), kn - 1);   // past the end: the last key, masked below
-            const int p = key / D.n;
-            const float *row = img + (size_t)region_token(D, region_index(irp[p], D.R), key - p * D.n) * C3;
+            if (HPW == 1 && u && T * u >= CHUNKS) break;
+            const int idx = HPW == 1 ? min(tid + T * u, CHUNKS - 1) : tid + T * u;
+            const int key = min(k0 + idx / (CW / 4), kn - 1);   // past the end: the last key, masked below
+            const int p = divide(key, D.n, n_inv);
+            const float *row = img + (size_t)(at.origin(region_index(irp[p], D.R)) + at.slot(key - p * D.n)) * C3;
             kr[u] = load_head_chunk<DP, VEC>(row + D.C, idx % (CW / 4), hg * HPW, D);
             vr[u] = load_head_chunk<DP, VEC>(row + 2 * D.C, idx % (CW / 4), hg * HPW, D);
         }
     };
-    float m = -INFINITY, l = 0.f;
+    float m = 0.f, l[4] = {0.f, 0.f, 0.f, 0.f};      // reference score; this lane's part of the denominator
     f32x4 acc[NS];
 #pragma unroll
     for (int dt = 0; dt < NS; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float c_exp = D.scale * 1.4426950408889634f;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) qf[s] *= c_exp;     // scores as exponents of 2
+    const bool idle = slot0 >= D.n || h >= D.heads;
     fetch(0);
     for (int k0 = 0; k0 < kn; k0 += KB) {
         if (k0) __syncthreads();                 // the previous block has been read
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
-            const int idx = tid + 256 * u;
+            const int idx = tid + T * u;
+            if (HPW == 1 && idx >= CHUNKS) break;
             *(f32x4 *)(Ks + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = blank_head_chunk<DP, VEC>(kr[u], idx % (CW / 4), hg * HPW, D);
             *(f32x4 *)(Vs + (idx / (CW / 4)) * P + 4 * (idx % (CW / 4))) = blank_head_chunk<DP, VEC>(vr[u], idx % (CW / 4), hg * HPW, D);
         }
         __syncthreads();
         if (k0 + KB < kn) fetch(k0 + KB);
+        if (idle) continue;                      // no queries: the wavefront only brings its rows
         f32x4 st[KT];
 #pragma unroll
-        for (int t = 0; t < KT; ++t) st[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < KT; ++t) st[t] = f32x4{-m, -m, -m, -m};
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             f32x4 kf[KT];
@@ -329,42 +362,48 @@ __global__ __launch_bounds__(256) void k_attention(const float *__restrict__ QKV
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int t = 0; t < KT; ++t) st[t] = mfma_f32(kf[t][e], qf[s][e], st[t]);   // S^T[key 16 t + 4 g + j][query i]
+                for (int t = 0; t < KT; ++t) st[t] = mfma_f32(kf[t][e], qf[s][e], st[t]);   // S^T[key 16 t + 4 g + j][query i] - m
         }
         const int left = kn - k0;
+        if (left < KB) {
 #pragma unroll
-        for (int t = 0; t < KT; ++t)
+            for (int t = 0; t < KT; ++t)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) st[t][j] = 16 * t + 4 * g + j < left ? st[t][j] : -INFINITY;
+                for (int j = 0; j < 4; ++j) st[t][j] = 16 * t + 4 * g + j < left ? st[t][j] : -INFINITY;
+        }
         float mx = st[0][0];
 #pragma unroll
         for (int t = 0; t < KT; ++t)
 #pragma unroll
             for (int j = 0; j < 4; ++j) mx = fmaxf(mx, st[t][j]);
-        const float m_new = fmaxf(m, cross_row_max(mx));          // finite: the block's first key exists
-        const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c_exp);
-        m = m_new;
-        float ls = 0.f;
+        // the reference follows the maximum when a lane's own score exceeds it by 2^8; the quotient does not depend on it
+        if (k0 == 0 || __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0) {
+            const float up = k0 == 0 ? cross_row_max(mx) : fmaxf(cross_row_max(mx), 0.f);
+            m += up;
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) st[t][j] -= up;
+            if (k0) {
+                const float alpha = __builtin_amdgcn_exp2f(-up);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) l[j] *= alpha;
+#pragma unroll
+                for (int dt = 0; dt < NS; ++dt) acc[dt] *= alpha;
+            }
+        }
 #pragma unroll
         for (int t = 0; t < KT; ++t)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                st[t][j] = __builtin_amdgcn_exp2f((st[t][j] - m_new) * c_exp);
-                ls += st[t][j];
+                st[t][j] = __builtin_amdgcn_exp2f(st[t][j]);
+                l[j] += st[t][j];
             }
-        l = fmaf(l, alpha, cross_row_sum(ls));
-#pragma unroll
-        for (int dt = 0; dt < NS; ++dt) acc[dt] *= alpha;
-#pragma unroll
-        for (int t = 0; t < KT; ++t)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int dt = 0; dt < NS; ++dt)
-                    acc[dt] = mfma_f32(Vs[(16 * t + 4 * g + e) * P + DP * hl + 16 * dt + i], st[t][e], acc[dt]);
+        rows_product<KT, NS>(Vs + 4 * g * P + DP * hl + i, P, st, acc);
     }
+    const float denominator = cross_row_sum((l[0] + l[1]) + (l[2] + l[3]));
     if (slot < D.n && h < D.heads) {
-        const float inv = 1.0f / l;
+        const float inv = 1.0f / denominator;
         float *orow = O + ((size_t)b * D.N + qtok) * D.C + h * D.d;
 #pragma unroll
         for (int dt = 0; dt < NS; ++dt) {
@@ -398,7 +437,9 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q(const float *__restrict__ QK
     const float *img = QKV + itok * C3;
     const int32_t *irp = Ir + ((size_t)b * D.R + reg) * D.k;
     const int slot = L::QT * qt + 16 * (wave % L::TPH) + i;
-    const int qtok = region_token(D, reg, min(slot, D.n - 1));
+    const Places<true> at(D);
+    const float n_inv = 1.0f / (float)D.n;
+    const int qtok = at.origin(reg) + at.slot(min(slot, D.n - 1));
     const bool live = slot < D.n && h < D.heads;
     f32x4 qf[NS], gf[NS];
 #pragma unroll
@@ -412,8 +453,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q(const float *__restrict__ QK
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
             const int idx = tid + 256 * u, key = min(k0 + idx / (CW / 4), kn - 1);   // past the end: the last key, masked below
-            const int p = key / D.n;
-            const float *row = img + (size_t)region_token(D, region_index(irp[p], D.R), key - p * D.n) * C3;
+            const int p = divide(key, D.n, n_inv);
+            const float *row = img + (size_t)(at.origin(region_index(irp[p], D.R)) + at.slot(key - p * D.n)) * C3;
             kr[u] = load_head_chunk<DP, VEC>(row + D.C, idx % (CW / 4), hg * HPW, D);
             vr[u] = load_head_chunk<DP, VEC>(row + 2 * D.C, idx % (CW / 4), hg * HPW, D);
         }
@@ -557,7 +598,9 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const float *__restrict__ Q
     const size_t itok = (size_t)b * D.N;
     const float *img = QKV + itok * C3;
     const int slot = L::QT * kt + 16 * (wave % L::TPH) + i;
-    const int ktok = region_token(D, reg, min(slot, D.n - 1));
+    const Places<true> at(D);
+    const float n_inv = 1.0f / (float)D.n, k_inv = 1.0f / (float)D.k;
+    const int ktok = at.origin(reg) + at.slot(min(slot, D.n - 1));
     f32x4 kf[NS], vf[NS], ak[NS], av[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -575,8 +618,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const float *__restrict__ Q
     for (int e0 = 0; e0 < entries; e0 += bwd::kListChunk) {
         const int rows = bwd::collect_entries(irb, entries, e0, reg, D.R, list, counts) * D.n;
         auto query_token = [&](int row) {
-            const int e = row / D.n;
-            return region_token(D, list[e] / D.k, row - e * D.n);
+            const int e = divide(row, D.n, n_inv);
+            return at.origin(divide(list[e], D.k, k_inv)) + at.slot(row - e * D.n);
         };
         auto fetch = [&](int r0) {
 #pragma unroll

@@ -10,6 +10,8 @@
 // Region pooling uses mean(X^r) W = mean(X^r W), which is exact in real arithmetic
 // (the mean is linear; same argument as Appendix A).
 #include "bra_f32_dev.h"
+
+#include <algorithm>
 #include <type_traits>
 
 #include <math.h>
@@ -205,10 +207,25 @@ int launch_route(const Dims &D, const T *X, const T *Wqkv, int32_t *Ir, float *A
 template <int DP, int HPW, bool VEC>
 int launch_attention_t(const Dims &D, const float *qkv, const int32_t *Ir, float *o, hipStream_t st)
 {
-    const int hgroups = (D.heads + HPW - 1) / HPW, qt = f32::AttnShape<DP, HPW>::QT, qtiles = (D.n + qt - 1) / qt;
+    const int hgroups = (D.heads + HPW - 1) / HPW, tiles = (D.n + 15) / 16;
+    int waves = 4, qtiles = 1;
+    if (HPW == 1) {
+        // four query tiles per workgroup, or up to eight in one or more equal ones where that leaves a fifth fewer
+        // wavefronts (5 tiles: with four a second workgroup for the last one holds its place as long as the first;
+        // 17 x 49 x 70 x 96, k = 13: 441 -> 373 us)
+        qtiles = (tiles + 3) / 4;
+        const int groups = (tiles + 7) / 8, even = std::max(3, (tiles + groups - 1) / groups);
+        if (5 * groups * even <= 4 * 4 * qtiles) {
+            qtiles = groups;
+            waves = even;
+        }
+    } else {
+        const int qt = f32::AttnShape<DP, HPW>::QT;
+        qtiles = (D.n + qt - 1) / qt;
+    }
     const long blocks = (long)D.B * D.R * hgroups * qtiles;
     if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((f32::k_attention<DP, HPW, VEC>), dim3((unsigned)blocks), dim3(256), 0, st, qkv, Ir, o, D, hgroups,
+    hipLaunchKernelGGL((f32::k_attention<DP, HPW, VEC>), dim3((unsigned)blocks), dim3(64 * waves), 0, st, qkv, Ir, o, D, hgroups,
                        qtiles);
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }

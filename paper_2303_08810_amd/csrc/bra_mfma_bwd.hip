@@ -255,7 +255,7 @@ bool mfma_backward_supported(const Dims &D)
 {
     static const bool off = experiment_flag("BRA_NO_MFMA_BACKWARD");
     if (off || D.dtype != BRA_BF16 || (D.d != 32 && D.d != 64) || D.C % 64 != 0 || D.C > 4096) return false;
-    if ((long)D.R * D.k > kBwdMaxEntries) return false;
+    if ((long)D.R * D.k > kBwdMaxEntries || D.rh >= (1 << 20)) return false;
     const long M = (long)D.B * D.N;
     return M * 3 * D.C < (1L << 40) && (long)D.B * D.R * ((D.n + 63) / 64) * D.heads <= 0x7fffffffL &&
            M <= 0x7fffffffL;

@@ -37,31 +37,6 @@ struct Rows {
     static constexpr int bufs = 2 * (SHARED ? 1 : 4);          // two per workgroup or wavefront
 };
 
-// a / n for any non-negative a whose quotient is below 2^20: fast_div is off by one at most.
-__device__ __forceinline__ int divide(int a, int n, float n_inv)
-{
-    const int p = fast_div(a, n_inv), rest = a - p * n;
-    return rest < 0 ? p - 1 : rest >= n ? p + 1 : p;
-}
-
-// Where regions and their slots lie within an image (Sec. 3.2: regions tile the map row-major).
-struct Places {
-    float rw_inv, s_inv;
-    int S, rh, rw, W;
-    __device__ __forceinline__ Places(const Dims &D)
-        : rw_inv(1.0f / (float)D.rw), s_inv(1.0f / (float)D.S), S(D.S), rh(D.rh), rw(D.rw), W(D.W) {}
-    __device__ __forceinline__ int origin(int r) const
-    {
-        const int ry = fast_div(r, s_inv);
-        return ry * rh * W + (r - ry * S) * rw;
-    }
-    __device__ __forceinline__ int slot(int s) const
-    {
-        const int sy = divide(s, rw, rw_inv);
-        return sy * W + s - sy * rw;
-    }
-};
-
 // Rows 16 t + i of a buffer's map as operands: piece p.
 __device__ __forceinline__ bf16x8 row_operand(const bf16_t *T, int row, int piece)
 {
@@ -112,7 +87,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
     const int C = D.C, n = D.n, kn = D.kn;
     int b, reg, tile, cg;
     if (!place<MODE>(D, tiles, items, wave, b, reg, tile, cg)) return;
-    const Places at(D);
+    const Places<false> at(D);
     const float n_inv = 1.0f / (float)n;
     const size_t img = (size_t)b * D.N * C + 64 * cg;
     bf16_t *mine = lds + (SHARED ? 0 : wave * 2 * R::buf);
@@ -408,7 +383,7 @@ constexpr int kListShared = 1024, kListWave = 512;      // entries listed at a t
 // Query regions whose entries e0, e0 + 1, .. name region j, as first tokens, up to a full list; e0 moves behind the
 // entries looked at.  A wavefront on its own.
 __device__ __forceinline__ int list_of_wave(const int32_t *__restrict__ irb, int entries, int &e0, int j, int R, float k_inv,
-                                            const Places &at, int *list)
+                                            const Places<false> &at, int *list)
 {
     const int lane = threadIdx.x % kWave;
     int count = 0;
@@ -430,7 +405,7 @@ __device__ __forceinline__ int list_of_wave(const int32_t *__restrict__ irb, int
 
 // The same for the whole workgroup, one range of kListShared entries at a time; barriers around it are the caller's.
 __device__ __forceinline__ int list_of_group(const int32_t *__restrict__ irb, int entries, int e0, int j, int R, float k_inv,
-                                             const Places &at, int *list, int *counts)
+                                             const Places<false> &at, int *list, int *counts)
 {
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     unsigned long long votes[4];
@@ -469,7 +444,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
     const int C = D.C, n = D.n;
     int b, reg, tile, cg;
     if (!place<MODE>(D, tiles, items, wave, b, reg, tile, cg)) return;
-    const Places at(D);
+    const Places<false> at(D);
     const float n_inv = 1.0f / (float)n, k_inv = 1.0f / (float)D.k;
     const size_t img = (size_t)b * D.N * C + 64 * cg;
     const size_t stat0 = ((size_t)b * D.heads + HPW * cg) * D.N;

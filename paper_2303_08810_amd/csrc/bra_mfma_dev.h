@@ -80,6 +80,33 @@ __device__ __forceinline__ int fast_div(int row, float width_inv)
     return (int)(((float)row + 0.5f) * width_inv);
 }
 
+// a / n for any non-negative a whose quotient is below 2^20: fast_div is off by one at most.
+__device__ __forceinline__ int divide(int a, int n, float n_inv)
+{
+    const int p = fast_div(a, n_inv), rest = a - p * n;
+    return rest < 0 ? p - 1 : rest >= n ? p + 1 : p;
+}
+
+// Where regions and their slots lie within an image (Sec. 3.2: regions tile the map row-major).  ANY: regions of 2^20 rows
+// and more too.
+template <bool ANY>
+struct Places {
+    float rw_inv, s_inv;
+    int S, rh, rw, W;
+    __device__ __forceinline__ Places(const Dims &D)
+        : rw_inv(1.0f / (float)D.rw), s_inv(1.0f / (float)D.S), S(D.S), rh(D.rh), rw(D.rw), W(D.W) {}
+    __device__ __forceinline__ int origin(int r) const
+    {
+        const int ry = fast_div(r, s_inv);
+        return ry * rh * W + (r - ry * S) * rw;
+    }
+    __device__ __forceinline__ int slot(int s) const
+    {
+        const int sy = !ANY || rh < (1 << 20) ? divide(s, rw, rw_inv) : s / rw;
+        return sy * W + s - sy * rw;
+    }
+};
+
 // Exact split of 8 float32 values into three bf16 terms each (x = hi + mid + lo: 3 x 8
 // mantissa bits), as MFMA operands.
 __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3])

@@ -18,6 +18,8 @@ EDGES = [  # (B, H, W, C, heads, S, k)
     (3, 9, 12, 64, 1, 3, 5),         # one head of 64, n = 12
     (1, 16, 32, 40, 2, 16, 5),       # 1280 routing entries per image: two list chunks
     (1, 26, 8, 128, 2, 2, 4),        # n = 52, heads of 64, 208 keys
+    (1, 14, 20, 40, 2, 2, 3),        # n = 70: five query tiles in one workgroup
+    (1, 18, 20, 128, 2, 2, 2),       # n = 90, heads of 64: six
     (1, 5, 7, 4, 1, 1, 1),           # C = 4: one 4-channel chunk
 ]
 
