@@ -1,6 +1,8 @@
 // bf16 products of the general pipelines.
 #include "bra_gemm.h"
 
+#include <algorithm>
+
 namespace bra {
 
 using namespace mfma;
@@ -396,6 +398,123 @@ int launch_f32out(const void *In, const bf16_t *W, int ldw, long M, int K, int N
 }
 
 // ---------------------------------------------------------------------------
+// Products with a short contraction (K = 64 or 128) over many rows, into bf16 buffers of K columns each (N = K or 3 K): Q, K,
+// V, dO and Y of the first stages.  A tile of k_gemm_dma has one or two chunks to load before it stores, and its loads and
+// stores do not overlap with those of the one or two workgroups beside it (150528 x 128 x 384: 52 us, of which 30 without
+// the stores and 22 without the loads).  Here a workgroup per compute unit keeps all of W in LDS and its wavefronts walk
+// over tiles of 16 rows on their own: a row of In is an operand as it lies (16 bytes per lane, the next tile's on their way),
+// and there is no barrier behind the staging of W.
+// Two 16-output tiles make 32 outputs of which a lane holds 8 consecutive ones (output 8 i / 4 + 4 half + i % 4 for row i of
+// tile `half`).  W's columns lie in LDS in that order, so that a transposing read takes 32 bytes of each of 4 rows; rows are
+// 32 bytes longer than their columns and groups of 8 rows 128 bytes apart: the 8 rows of 32 lanes then cover all banks.
+// BT: W is given transposed ([N][ldw]) and read as it lies.
+template <int K, int N, bool BT>
+struct ProjLds {
+    static constexpr int pitch = BT ? K + 8 : N + 16;
+    static constexpr size_t bytes = BT ? (size_t)N * pitch * 2 : (size_t)(K * pitch + K / 8 * 64) * 2;
+};
+
+template <int K, int N, bool BT>
+__global__ __launch_bounds__(1024) void k_proj(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw, long M,
+                                               int per_group, GemmOut out)
+{
+    typedef ProjLds<K, N, BT> L;
+    constexpr int P = L::pitch, KS = K / 32, TP = N / 32;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    bf16_t *Ws = (bf16_t *)smem;
+    const int T = blockDim.x, tid = threadIdx.x, waves = T / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const long tiles = (M + 15) / 16, first = (long)blockIdx.x * per_group, last = min(tiles, first + per_group);
+    bf16x8 x[2][KS];
+    auto fetch = [&](long tile, bf16x8 (&r)[KS]) {
+        const bf16_t *row = In + min(min(tile, tiles - 1) * 16 + i, M - 1) * K + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) r[ks] = *(const bf16x8 *)(row + 32 * ks);
+    };
+    fetch(first + wave, x[0]);
+    if (BT) {
+        for (int e = tid; e < N * (K / 8); e += T) {
+            const int o = e / (K / 8), k8 = e % (K / 8);
+            *(u32x4 *)(Ws + o * P + 8 * k8) = *(const u32x4 *)(W + (size_t)o * ldw + 8 * k8);
+        }
+    } else {
+        for (int e = tid; e < K * (N / 8); e += T) {
+            const int k = e / (N / 8), o8 = e % (N / 8);              // columns 8 q .. 8 q + 7 of a group of 32
+            const u32x4 v = *(const u32x4 *)(W + (size_t)k * ldw + 8 * o8);
+            bf16_t *dst = Ws + k * P + (k / 8) * 64 + 32 * (o8 / 4) + 4 * (o8 % 4);
+            *(u32x2 *)dst = u32x2{v[0], v[1]};
+            *(u32x2 *)(dst + 16) = u32x2{v[2], v[3]};
+        }
+    }
+    __syncthreads();
+    int again = 0;      // set anew for every tile: the operands are not kept in registers across tiles
+    auto operand = [&](int tp, int half, int ks) {
+        if (BT) return *(const bf16x8 *)(Ws + again + (32 * tp + 8 * (i / 4) + 4 * half + i % 4) * P + 32 * ks + 8 * g);
+        const bf16_t *p = Ws + (32 * ks + 8 * g + i / 4) * P + (4 * ks + g) * 64 + 32 * tp + 16 * half + 4 * (i % 4);
+        const u32x2 r0 = __builtin_bit_cast(u32x2, lds_read_tr16(p)), r1 = __builtin_bit_cast(u32x2, lds_read_tr16(p + 4 * P));
+        return __builtin_bit_cast(bf16x8, u32x4{r0[0], r0[1], r1[0], r1[1]});
+    };
+    auto tile = [&](long t, const bf16x8 (&xf)[KS]) {
+        asm volatile("" : "+s"(again));
+        const long m = t * 16 + i;
+        const size_t at = (size_t)min(m, M - 1) * K + 8 * g;
+#pragma unroll
+        for (int tp = 0; tp < TP; ++tp) {
+            f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int half = 0; half < 2; ++half) acc[half] = mfma16(operand(tp, half, ks), xf[ks], acc[half]);
+            const float scale = 32 * tp < K ? out.scale0 : 1.0f;
+            const float v[8] = {acc[0][0] * scale, acc[0][1] * scale, acc[0][2] * scale, acc[0][3] * scale,
+                                acc[1][0] * scale, acc[1][1] * scale, acc[1][2] * scale, acc[1][3] * scale};
+            if (m < M) *(bf16x8 *)((bf16_t *)out.buf[32 * tp / K] + at + 32 * tp % K) = pack8(v);
+        }
+    };
+    for (long t = first + wave; t < last; t += 2 * waves) {
+        fetch(t + waves, x[1]);
+        tile(t, x[0]);
+        if (t + waves >= last) break;
+        fetch(t + 2 * waves, x[0]);
+        tile(t + waves, x[1]);
+    }
+}
+
+template <int K, int N, bool BT>
+int launch_proj_t(const bf16_t *In, const bf16_t *W, int ldw, long M, const GemmOut &out, hipStream_t st)
+{
+    static bool opted = false;
+    if (!opted) {
+        if (hipFuncSetAttribute((const void *)k_proj<K, N, BT>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess)
+            return BRA_ERR_LAUNCH;
+        opted = true;
+    }
+    // as many wavefronts as deal out a compute unit's share of the tiles in even rounds
+    const long tiles = (M + 15) / 16, per = (tiles + 255) / 256, rounds = (per + 15) / 16;
+    const int waves = (int)std::max(4L, (per + rounds - 1) / rounds);
+    hipLaunchKernelGGL((k_proj<K, N, BT>), dim3((unsigned)((tiles + per - 1) / per)), dim3(64 * waves), (ProjLds<K, N, BT>::bytes), st,
+                       In, W, ldw, M, (int)per, out);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+// Measured against the tiles (us): 50176 x 64 x 192 8.0 for 8.8, 200704 x 64 x 192 27 for 31; 25088 x 128 x 384 11.9 for 10.8,
+// 50176 x 128 x 384 16.7 for 21.2, 150528 x 128 x 384 38.8 for 55.1; 50176 x 128 x 128 9.1 for 10.1; 64 x 64 no difference.
+// The region-level product takes a launch of its own then, which K = 64 does not win back and K = 128 from about 100000 rows
+// on (whole forward, 58800 rows: 79.8 -> 82.9; 283392 rows: 316 -> 298).
+bool proj_ok(long M, int K, int N, const GemmOut &out, bool regions)
+{
+    const bool shape = K == 128 ? N == K || N == 3 * K : K == 64 && N == 3 * K && !regions;
+    return shape && out.cols == K && M >= (regions ? 100000 : 40000) && !out.bias && !out.gelu && !out.res && !out.f32[0] && !out.f32[1] &&
+           !out.in_rows.Hp && !out.out_rows.Hp;
+}
+
+int launch_proj(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int N, const GemmOut &out, hipStream_t st)
+{
+    if (K == 64) return launch_proj_t<64, 192, false>(In, W, ldw, M, out, st);
+    return N == K ? launch_proj_t<128, 128, false>(In, W, ldw, M, out, st) : launch_proj_t<128, 384, false>(In, W, ldw, M, out, st);
+}
+
+// ---------------------------------------------------------------------------
 // Part[share][a][n] = sum over the share's tokens t of A[t][a] B[t][n] (the weight gradients dWqkv = X^T dQKV and
 // dWo = O^T dY, both in one launch): a 128 x 128 block of the output per workgroup, 64 tokens at a time straight into one of
 // two LDS buffers; both operands by transposing reads (pieces exchanged as for W above).
@@ -516,6 +635,14 @@ int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, co
          int kernel_id, hipStream_t st)
 {
     if (!sizes_ok(M, K, Nout) || (out.cols % 32 && out.cols != Nout) || (out.in_rows.Hp && K > 4096)) return BRA_ERR_UNSUPPORTED;
+    if (proj_ok(M, K, Nout, out, regions != nullptr)) {
+        if (regions) {
+            const int rc = gemm_regions(*regions, W, ldw, K, kernel_id, st);
+            if (rc != BRA_OK) return rc;
+        }
+        ProfScope ps(st, kernel_id);
+        return launch_proj(In, W, ldw, M, K, Nout, out, st);
+    }
     ProfScope ps(st, kernel_id);
     if (regions) return launch_big<true>(In, W, ldw, M, K, Nout, out, *regions, st);
     return launch_big<false>(In, W, ldw, M, K, Nout, out, GemmRegions{}, st);
@@ -524,9 +651,10 @@ int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, co
 int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout, bf16_t *Out, int kernel_id, hipStream_t st)
 {
     if (!sizes_ok(M, K, Nout)) return BRA_ERR_UNSUPPORTED;
+    const GemmOut out = {{Out, nullptr, nullptr}, Nout, {nullptr, nullptr}, nullptr, nullptr, 0};
     ProfScope ps(st, kernel_id);
-    return launch_big<false, true>(In, Wt, ldw, M, K, Nout, GemmOut{{Out, nullptr, nullptr}, Nout, {nullptr, nullptr}, nullptr, nullptr, 0},
-                                   GemmRegions{}, st);
+    if (K == Nout && proj_ok(M, K, Nout, out, false)) return launch_proj_t<128, 128, true>(In, Wt, ldw, M, out, st);
+    return launch_big<false, true>(In, Wt, ldw, M, K, Nout, out, GemmRegions{}, st);
 }
 
 int gemm_f32out(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, float *out0, float *out1, int cols,

@@ -4,6 +4,7 @@ region-level projection in the same launch."""
 import pytest
 
 from synthetic_inputs import make_inputs
+from test_gpu_backward import compare_backward
 from test_gpu_parity import compare
 
 pytestmark = pytest.mark.gpu
@@ -58,3 +59,13 @@ def test_attention_large_regions(B, H, W, C, heads, S, k):
     compare(X, Wqkv, Wo, Wlce, "bf16", S, k, heads, "mfma", images=images)
     if B <= 2:
         compare(X, Wqkv, Wo, Wlce, "bf16", S, k, heads, "mfma", scale=0.5)
+
+
+@pytest.mark.parametrize("C", [64, 128])
+def test_many_rows(C):
+    # W in LDS, wavefronts walking over row tiles: 40817 and 100842 rows (the last tile with 1 and 10), Q | K | V, the region
+    # rows in a launch of their own, dO by the transposed product
+    X, Wqkv, Wo, Wlce = make_inputs(42, 49, 49, C, seed=9800 + C, dtype="bf16")
+    compare(X, Wqkv, Wo, Wlce, "bf16", 7, 2, C // 32, "mfma", images=[0, 41])
+    X = X[:17]
+    compare_backward(X, Wqkv, Wo, Wlce, "bf16", C // 32, 7, 1, path="mfma")
