@@ -14,6 +14,8 @@
 #include "bra_bwd_dev.h"
 #include "bra_lce_dev.h"
 
+#include <type_traits>
+
 namespace bra {
 namespace f32 {
 
@@ -89,6 +91,27 @@ struct GemmJob {
     const TO *res;          // the layout of Out
     int gelu;
 };
+
+// A wavefront's 32 rows from m0 on x BN / 2 columns from n0 on, with bias, GELU and residual.
+template <bool VEC, int BN, typename TA, typename TB, typename TO>
+__device__ __forceinline__ void gemm_store(const GemmJob<TA, TB, TO> &J, const f32x4 (&acc)[2][BN / 32], long m0, int n0, int g, int i)
+{
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+        const long m = m0 + 16 * rt + i;
+        if (m >= J.M) continue;
+#pragma unroll
+        for (int t = 0; t < BN / 32; ++t) {
+            const int n = n0 + 16 * t + 4 * g, left = J.N - n;
+            if (left <= 0) continue;
+            f32x4 v = acc[rt][t];
+            if (J.bias) v += load4<VEC>(J.bias + n, left);
+            if (J.gelu) v = f32x4{gelu_f32(v[0]), gelu_f32(v[1]), gelu_f32(v[2]), gelu_f32(v[3])};
+            if (J.res) v += load4<VEC>(J.res + m * J.ldo + n, left);
+            store4<VEC>(J.Out + m * J.ldo + n, v, left);
+        }
+    }
+}
 
 template <bool BT, bool VEC, int BN, typename TA, typename TB, typename TO>
 __device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int block, float *smem)
@@ -176,21 +199,93 @@ __device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int bloc
                     for (int rt = 0; rt < 2; ++rt) acc[rt][t] = mfma_f32(wa[t][e], xb[rt][e], acc[rt][t]);
         }
     }
+    gemm_store<VEC, BN>(J, acc, m0 + 32 * wr, n0 + (BN / 2) * wc, g, i);
+}
+
+// The same tile for bf16 operands, whose products are exact: on v_mfma_f32_16x16x32_bf16, one step per chunk (the float32
+// instruction spent 16 times as long on them).  Both operands lie in LDS as they came; B's rows (not BT) become an operand by the
+// transposing read, 128 bytes more after every 8 of them keep its lane groups on different banks.  Channel counts are
+// multiples of 4.  58310 x 96 x 288 with float32 results: GEMMTIME us (47.6 on the float32 instruction; 78 MB).
+template <bool BT, int BN, typename TO>
+__device__ __forceinline__ void gemm_tile_bf16(const GemmJob<bf16_t, bf16_t, TO> &J, int block, bf16_t *smem)
+{
+    using mfma::bf16x8;
+    using mfma::u32x4;
+    constexpr int BK = kGemmBK, PA = BK + 8, PB = BT ? BK + 8 : BN + 16, NT = BN / 32, NA = kGemmBM * BK / 4 / 256, NB = BN * BK / 4 / 256;
+    bf16_t *As = smem, *Bs = smem + kGemmBM * PA;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int ntiles = (J.N + BN - 1) / BN;
+    const long m0 = (long)(block / ntiles) * kGemmBM;
+    const int n0 = (block % ntiles) * BN;
+    u32x2 ra[NA], rb[NB];
+    auto fetch = [&](int k0) {               // past the end: as in gemm_tile
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-        const long m = m0 + 32 * wr + 16 * rt + i;
-        if (m >= J.M) continue;
+        for (int u = 0; u < NA; ++u) {
+            const int idx = tid + 256 * u, k = k0 + 4 * (idx % (BK / 4));
+            ra[u] = *(const u32x2 *)(J.A + min(m0 + idx / (BK / 4), J.M - 1) * J.lda + min(k, J.K - 4));
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int idx = tid + 256 * u;
+            if (BT) {
+                const int k = k0 + 4 * (idx % (BK / 4)), n = min(n0 + idx / (BK / 4), J.N - 1);
+                rb[u] = *(const u32x2 *)(J.Bm + (long)n * J.ldb + min(k, J.K - 4));
+            } else {
+                const int k = k0 + idx / (BN / 4), n = n0 + 4 * (idx % (BN / 4));
+                rb[u] = *(const u32x2 *)(J.Bm + (long)min(k, J.K - 1) * J.ldb + min(n, J.N - 4));
+            }
+        }
+    };
+    const int wr = wave / 2, wc = wave % 2;
+    f32x4 acc[2][NT];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    fetch(0);
+    for (int k0 = 0; k0 < J.K; k0 += BK) {
+        if (k0) __syncthreads();                 // the previous chunk has been read
+        if (k0 + BK > J.K) {
+            const u32x2 zero = {0u, 0u};
+#pragma unroll
+            for (int u = 0; u < NA; ++u)
+                if (k0 + 4 * ((tid + 256 * u) % (BK / 4)) >= J.K) ra[u] = zero;
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                if (k0 + (BT ? 4 * ((tid + 256 * u) % (BK / 4)) : (tid + 256 * u) / (BN / 4)) >= J.K) rb[u] = zero;
+        }
+#pragma unroll
+        for (int u = 0; u < NA; ++u) {
+            const int idx = tid + 256 * u;
+            *(u32x2 *)(As + (idx / (BK / 4)) * PA + 4 * (idx % (BK / 4))) = ra[u];
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int idx = tid + 256 * u;
+            if (BT) *(u32x2 *)(Bs + (idx / (BK / 4)) * PB + 4 * (idx % (BK / 4))) = rb[u];
+            else *(u32x2 *)(Bs + (idx / (BN / 4)) * PB + idx / (BN / 4) / 8 * 64 + 4 * (idx % (BN / 4))) = rb[u];
+        }
+        __syncthreads();
+        if (k0 + BK < J.K) fetch(k0 + BK);
+        bf16x8 xb[2];
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) xb[rt] = *(const bf16x8 *)(As + (32 * wr + 16 * rt + i) * PA + 8 * g);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            const int n = n0 + (BN / 2) * wc + 16 * t + 4 * g, left = J.N - n;
-            if (left <= 0) continue;
-            f32x4 v = acc[rt][t];
-            if (J.bias) v += load4<VEC>(J.bias + n, left);
-            if (J.gelu) v = f32x4{gelu_f32(v[0]), gelu_f32(v[1]), gelu_f32(v[2]), gelu_f32(v[3])};
-            if (J.res) v += load4<VEC>(J.res + m * J.ldo + n, left);
-            store4<VEC>(J.Out + m * J.ldo + n, v, left);
+            const int n = (BN / 2) * wc + 16 * t;
+            bf16x8 wf;
+            if (BT) {
+                wf = *(const bf16x8 *)(Bs + (n + i) * PB + 8 * g);
+            } else {
+                const bf16_t *wp = Bs + (8 * g + i / 4) * PB + g * 64 + n + 4 * (i % 4);
+                const u32x2 w0 = __builtin_bit_cast(u32x2, mfma::lds_read_tr16(wp)), w1 = __builtin_bit_cast(u32x2, mfma::lds_read_tr16(wp + 4 * PB));
+                wf = __builtin_bit_cast(bf16x8, u32x4{w0[0], w0[1], w1[0], w1[1]});
+            }
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) acc[rt][t] = mfma::mfma16(wf, xb[rt], acc[rt][t]);
         }
     }
+    gemm_store<true, BN>(J, acc, m0 + 32 * wr, n0 + (BN / 2) * wc, g, i);
 }
 
 template <int BN, bool BT>
@@ -202,7 +297,11 @@ template <bool BT, bool VEC, int BN, typename TA, typename TB, typename TO>
 __global__ __launch_bounds__(256) void k_gemm(GemmJob<TA, TB, TO> J0, GemmJob<float, TB, float> J1, int blocks0)
 {
     __shared__ __attribute__((aligned(16))) float smem[gemm_lds_floats<BN, BT>()];
-    if ((int)blockIdx.x < blocks0) gemm_tile<BT, VEC, BN>(J0, blockIdx.x, smem);
+    if ((int)blockIdx.x < blocks0) {
+        if constexpr (VEC && std::is_same<TA, bf16_t>::value && std::is_same<TB, bf16_t>::value)
+            gemm_tile_bf16<BT, BN>(J0, blockIdx.x, (bf16_t *)smem);
+        else gemm_tile<BT, VEC, BN>(J0, blockIdx.x, smem);
+    }
     else gemm_tile<BT, VEC, BN>(J1, (int)blockIdx.x - blocks0, smem);
 }
 
