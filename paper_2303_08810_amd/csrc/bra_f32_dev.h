@@ -202,27 +202,32 @@ __device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int bloc
     gemm_store<VEC, BN>(J, acc, m0 + 32 * wr, n0 + (BN / 2) * wc, g, i);
 }
 
-// The same tile for bf16 operands, whose products are exact: on v_mfma_f32_16x16x32_bf16, one step per chunk (the float32
-// instruction spent 16 times as long on them).  Both operands lie in LDS as they came; B's rows (not BT) become an operand by the
+// The same tile for a bf16 B, on v_mfma_f32_16x16x32_bf16, one step per chunk (the float32 instruction takes 16 times as
+// long).  The products are those of the float32 numbers: a bf16 A enters as it is, a float32 A as three bf16 terms that
+// add up to it exactly, smallest first.  Both operands lie in LDS as they came; B's rows (not BT) become an operand by the
 // transposing read, 128 bytes more after every 8 of them keep its lane groups on different banks.  Channel counts are
-// multiples of 4.  58310 x 96 x 288 with float32 results: GEMMTIME us (47.6 on the float32 instruction; 78 MB).
-template <bool BT, int BN, typename TO>
-__device__ __forceinline__ void gemm_tile_bf16(const GemmJob<bf16_t, bf16_t, TO> &J, int block, bf16_t *smem)
+// multiples of 4.  58310 x 96 x 288 with float32 results: 26 us (48 on the float32 instruction; 78 MB).
+// 58310 x 96 x 96 with a float32 A 10.5 us (19.4).
+template <bool BT, int BN, typename TA, typename TO>
+__device__ __forceinline__ void gemm_tile_bf16(const GemmJob<TA, bf16_t, TO> &J, int block, bf16_t *smem)
 {
     using mfma::bf16x8;
     using mfma::u32x4;
     constexpr int BK = kGemmBK, PA = BK + 8, PB = BT ? BK + 8 : BN + 16, NT = BN / 32, NA = kGemmBM * BK / 4 / 256, NB = BN * BK / 4 / 256;
-    bf16_t *As = smem, *Bs = smem + kGemmBM * PA;
+    constexpr bool SPLIT = std::is_same<TA, float>::value;
+    constexpr int TERMS = SPLIT ? 3 : 1, plane = kGemmBM * PA;
+    bf16_t *As = smem, *Bs = smem + TERMS * plane;
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int ntiles = (J.N + BN - 1) / BN;
     const long m0 = (long)(block / ntiles) * kGemmBM;
     const int n0 = (block % ntiles) * BN;
-    u32x2 ra[NA], rb[NB];
+    typename std::conditional<SPLIT, f32x4, u32x2>::type ra[NA];
+    u32x2 rb[NB];
     auto fetch = [&](int k0) {               // past the end: as in gemm_tile
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
             const int idx = tid + 256 * u, k = k0 + 4 * (idx % (BK / 4));
-            ra[u] = *(const u32x2 *)(J.A + min(m0 + idx / (BK / 4), J.M - 1) * J.lda + min(k, J.K - 4));
+            ra[u] = *(const decltype(&ra[0]))(J.A + min(m0 + idx / (BK / 4), J.M - 1) * J.lda + min(k, J.K - 4));
         }
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
@@ -249,7 +254,7 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmJob<bf16_t, bf16_t, TO>
             const u32x2 zero = {0u, 0u};
 #pragma unroll
             for (int u = 0; u < NA; ++u)
-                if (k0 + 4 * ((tid + 256 * u) % (BK / 4)) >= J.K) ra[u] = zero;
+                if (k0 + 4 * ((tid + 256 * u) % (BK / 4)) >= J.K) ra[u] = {};
 #pragma unroll
             for (int u = 0; u < NB; ++u)
                 if (k0 + (BT ? 4 * ((tid + 256 * u) % (BK / 4)) : (tid + 256 * u) / (BN / 4)) >= J.K) rb[u] = zero;
@@ -257,7 +262,18 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmJob<bf16_t, bf16_t, TO>
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
             const int idx = tid + 256 * u;
-            *(u32x2 *)(As + (idx / (BK / 4)) * PA + 4 * (idx % (BK / 4))) = ra[u];
+            bf16_t *dst = As + (idx / (BK / 4)) * PA + 4 * (idx % (BK / 4));
+            if constexpr (SPLIT) {
+                f32x4 rest = ra[u];
+#pragma unroll
+                for (int q = 0; q < TERMS; ++q) {
+                    const u32x2 term = mfma::pack4(rest);
+                    *(u32x2 *)(dst + q * plane) = term;
+                    rest -= f32x4{bf16_lo(term[0]), bf16_hi(term[0]), bf16_lo(term[1]), bf16_hi(term[1])};
+                }
+            } else {
+                *(u32x2 *)dst = ra[u];
+            }
         }
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
@@ -267,9 +283,11 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmJob<bf16_t, bf16_t, TO>
         }
         __syncthreads();
         if (k0 + BK < J.K) fetch(k0 + BK);
-        bf16x8 xb[2];
+        bf16x8 xb[2][TERMS];
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt) xb[rt] = *(const bf16x8 *)(As + (32 * wr + 16 * rt + i) * PA + 8 * g);
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int q = 0; q < TERMS; ++q) xb[rt][q] = *(const bf16x8 *)(As + q * plane + (32 * wr + 16 * rt + i) * PA + 8 * g);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int n = (BN / 2) * wc + 16 * t;
@@ -282,14 +300,21 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmJob<bf16_t, bf16_t, TO>
                 wf = __builtin_bit_cast(bf16x8, u32x4{w0[0], w0[1], w1[0], w1[1]});
             }
 #pragma unroll
-            for (int rt = 0; rt < 2; ++rt) acc[rt][t] = mfma::mfma16(wf, xb[rt], acc[rt][t]);
+            for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                for (int q = TERMS - 1; q >= 0; --q) acc[rt][t] = mfma::mfma16(wf, xb[rt][q], acc[rt][t]);
         }
     }
     gemm_store<true, BN>(J, acc, m0 + 32 * wr, n0 + (BN / 2) * wc, g, i);
 }
 
 template <int BN, bool BT>
-constexpr size_t gemm_lds_floats() { return (size_t)kGemmBM * (kGemmBK + 4) + (BT ? BN * (kGemmBK + 4) : kGemmBK * (BN + 4)); }
+constexpr size_t gemm_lds_floats()
+{
+    constexpr size_t f32 = (size_t)kGemmBM * (kGemmBK + 4) + (BT ? BN * (kGemmBK + 4) : kGemmBK * (BN + 4));
+    constexpr size_t terms = (3 * (size_t)kGemmBM * (kGemmBK + 8) + (BT ? BN * (kGemmBK + 8) : kGemmBK * (BN + 16) + kGemmBK / 8 * 64)) / 2;
+    return f32 > terms ? f32 : terms;
+}
 
 // Workgroups below blocks0 do job J0, the rest J1 (of the same B matrix type, A and Out float32): the
 // region-level projection of the routing rides in the token projection's launch.
@@ -298,10 +323,11 @@ __global__ __launch_bounds__(256) void k_gemm(GemmJob<TA, TB, TO> J0, GemmJob<fl
 {
     __shared__ __attribute__((aligned(16))) float smem[gemm_lds_floats<BN, BT>()];
     if ((int)blockIdx.x < blocks0) {
-        if constexpr (VEC && std::is_same<TA, bf16_t>::value && std::is_same<TB, bf16_t>::value)
-            gemm_tile_bf16<BT, BN>(J0, blockIdx.x, (bf16_t *)smem);
+        if constexpr (VEC && std::is_same<TB, bf16_t>::value) gemm_tile_bf16<BT, BN>(J0, blockIdx.x, (bf16_t *)smem);
         else gemm_tile<BT, VEC, BN>(J0, blockIdx.x, smem);
+        return;
     }
+    if constexpr (VEC && std::is_same<TB, bf16_t>::value) gemm_tile_bf16<BT, BN>(J1, (int)blockIdx.x - blocks0, (bf16_t *)smem);
     else gemm_tile<BT, VEC, BN>(J1, (int)blockIdx.x - blocks0, smem);
 }
 
