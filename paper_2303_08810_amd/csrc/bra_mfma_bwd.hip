@@ -74,8 +74,10 @@ struct ProjSmem {
     static constexpr size_t bytes = (size_t)64 * (GS + (WO ? 3 : 1) * XS) * 2;
 };
 
-template <int C, bool WO>
-__global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G, const bf16_t *__restrict__ X,
+// H = 2: two such groups of wavefronts in one workgroup, tile by tile in turn, add their sums through LDS at the end:
+// half as many partial matrices to write and to read again, which bound the end of the call.
+template <int C, bool WO, int H>
+__global__ __launch_bounds__(4 * C * H) void k_bwd_proj(const bf16_t *__restrict__ G, const bf16_t *__restrict__ X,
                                                     const bf16_t *__restrict__ Wqkv, bf16_t *__restrict__ dX,
                                                     float *__restrict__ Part, const bf16_t *__restrict__ O,
                                                     const bf16_t *__restrict__ dY, float *__restrict__ PartO, long M,
@@ -84,8 +86,9 @@ __global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G
     constexpr int NT = 4 * C, GS = ProjSmem<C, WO>::GS, XS = ProjSmem<C, WO>::XS, KS = 3 * C / 32, CT = 3 * C / 16;
     constexpr int GCH = 3 * C / 8, XCH = C / 8, GL = 64 * GCH / NT, XL = 64 * XCH / NT, OT = WO ? C / 16 : 1;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    bf16_t *Gs = (bf16_t *)smem, *Xs = Gs + 64 * GS, *Os = Xs + 64 * XS, *Ys = Os + 64 * XS;
-    const int w = threadIdx.x / 64, lane = threadIdx.x % 64, g = lane / 16, i = lane % 16;
+    const int half = H == 1 ? 0 : (int)threadIdx.x / NT, tid = threadIdx.x % NT;
+    bf16_t *Gs = (bf16_t *)(smem + half * ProjSmem<C, WO>::bytes), *Xs = Gs + 64 * GS, *Os = Xs + 64 * XS, *Ys = Os + 64 * XS;
+    const int w = tid / 64, lane = tid % 64, g = lane / 16, i = lane % 16;
     bf16x8 wf[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) wf[ks] = *(const bf16x8 *)(Wqkv + (size_t)(16 * w + i) * 3 * C + 32 * ks + 8 * g);
@@ -98,13 +101,13 @@ __global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G
     auto fetch = [&](long tile) {
 #pragma unroll
         for (int u = 0; u < GL; ++u) {
-            const int idx = threadIdx.x + NT * u;
+            const int idx = tid + NT * u;
             const size_t t = min(tile * 64 + idx / GCH, M - 1);
             gr[u] = *(const u32x4 *)(G + t * 3 * C + (idx % GCH) * 8);
         }
 #pragma unroll
         for (int u = 0; u < XL; ++u) {
-            const int idx = threadIdx.x + NT * u;
+            const int idx = tid + NT * u;
             const size_t at = (size_t)min(tile * 64 + idx / XCH, M - 1) * C + (idx % XCH) * 8;
             xr[u] = *(const u32x4 *)(X + at);
             if (WO) {
@@ -114,28 +117,30 @@ __global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G
         }
     };
     const int first = blockIdx.x * tiles_per_wg, last = min(tiles, first + tiles_per_wg);
-    if (first < last) fetch(first);
-    for (int tile = first; tile < last; ++tile) {
-        if (tile > first) __syncthreads();          // the previous tile's readers are done
-        if ((long)tile * 64 + 64 > M) {             // tokens past the end add nothing: blanked here, not behind the loads
+    if (first < last) fetch(first + half);
+    for (int t0 = first; t0 < last; t0 += H) {
+        const int tile = t0 + half;
+        const long rows = H == 1 || tile < last ? M : 0;    // the second group has no tile left: it adds nothing
+        if (t0 > first) __syncthreads();            // the previous tile's readers are done
+        if ((long)tile * 64 + 64 > rows) {          // tokens past the end add nothing: blanked here, not behind the loads
 #pragma unroll
             for (int u = 0; u < GL; ++u)
-                if ((long)tile * 64 + (threadIdx.x + NT * u) / GCH >= M) gr[u] = u32x4{0u, 0u, 0u, 0u};
+                if ((long)tile * 64 + (tid + NT * u) / GCH >= rows) gr[u] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int u = 0; u < XL; ++u)
-                if ((long)tile * 64 + (threadIdx.x + NT * u) / XCH >= M) {
+                if ((long)tile * 64 + (tid + NT * u) / XCH >= rows) {
                     xr[u] = u32x4{0u, 0u, 0u, 0u};
                     if (WO) orr[u] = yr[u] = xr[u];
                 }
         }
 #pragma unroll
         for (int u = 0; u < GL; ++u) {
-            const int idx = threadIdx.x + NT * u;
+            const int idx = tid + NT * u;
             *(u32x4 *)(Gs + (idx / GCH) * GS + (idx % GCH) * 8) = gr[u];
         }
 #pragma unroll
         for (int u = 0; u < XL; ++u) {
-            const int idx = threadIdx.x + NT * u;
+            const int idx = tid + NT * u;
             *(u32x4 *)(Xs + (idx / XCH) * XS + (idx % XCH) * 8) = xr[u];
             if (WO) {
                 *(u32x4 *)(Os + (idx / XCH) * XS + (idx % XCH) * 8) = orr[u];
@@ -143,7 +148,7 @@ __global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G
             }
         }
         __syncthreads();
-        if (tile + 1 < last) fetch(tile + 1);
+        if (t0 + H < last) fetch(tile + H);
 #pragma unroll
         for (int rt = 0; rt < 4; ++rt) {
             f32x4 a = {0.f, 0.f, 0.f, 0.f};
@@ -151,7 +156,7 @@ __global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G
             for (int ks = 0; ks < KS; ++ks)
                 a = mfma16(wf[ks], *(const bf16x8 *)(Gs + (16 * rt + i) * GS + 32 * ks + 8 * g), a);
             const long t = (long)tile * 64 + 16 * rt + i;       // a[j] = dX[token t][channel 16 w + 4 g + j]
-            if (t < M) *(u32x2 *)(dX + (size_t)t * C + 16 * w + 4 * g) = pack4(a);
+            if (t < rows) *(u32x2 *)(dX + (size_t)t * C + 16 * w + 4 * g) = pack4(a);
         }
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
@@ -165,6 +170,22 @@ __global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G
                     acco[ct] = mfma16(oa, tr_operand(Ys, XS, 32 * ks, 16 * ct, g, i), acco[ct]);
             }
         }
+    }
+    if (H == 2) {
+        f32x4 *sums = (f32x4 *)smem;
+        __syncthreads();
+        if (half == 1) {
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) sums[ct * NT + tid] = acc[ct];
+#pragma unroll
+            for (int ct = 0; ct < OT; ++ct) sums[(CT + ct) * NT + tid] = acco[ct];
+        }
+        __syncthreads();
+        if (half == 1) return;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[ct] += sums[ct * NT + tid];
+#pragma unroll
+        for (int ct = 0; ct < OT; ++ct) acco[ct] += sums[(CT + ct) * NT + tid];
     }
     float *out = Part + (size_t)blockIdx.x * C * 3 * C;
 #pragma unroll
@@ -180,9 +201,10 @@ __global__ __launch_bounds__(4 * C) void k_bwd_proj(const bf16_t *__restrict__ G
     }
 }
 
-// Tiles of k_bwd_proj per workgroup: all workgroups resident at once.
+// Tiles of k_bwd_proj per workgroup: all workgroups resident at once.  At C = 64 two groups of wavefronts share a
+// workgroup (`halves`) once each has more than one tile; before that the chip is not full and a tile each is best.
 struct ProjPlan {
-    int tiles, per_wg, groups;
+    int tiles, per_wg, groups, halves;
 };
 
 ProjPlan proj_plan(long M, int C)
@@ -191,6 +213,8 @@ ProjPlan proj_plan(long M, int C)
     p.tiles = (int)((M + 63) / 64);
     const int slots = C == 64 ? 512 : 256;
     p.per_wg = (p.tiles + slots - 1) / slots;
+    p.halves = C == 64 && p.per_wg > 1 ? 2 : 1;
+    p.per_wg *= p.halves;
     p.groups = (p.tiles + p.per_wg - 1) / p.per_wg;
     return p;
 }
@@ -286,16 +310,21 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
     const bool with_o = C == 64;          // dWo = O^T dY rides in the same pass where the registers allow it
     if (fused_projection(C)) {
         // dX = [dQ | dK | dV] Wqkv^T and the partial sums of dWqkv = X^T [dQ | dK | dV] (and of dWo)
-        static bool opted[2] = {false, false};
-        if (!(C == 64 ? opt_in(k_bwd_proj<64, true>, opted[0]) : opt_in(k_bwd_proj<128, false>, opted[1])))
+        static bool opted[3] = {false, false, false};
+        if (!(C == 128 ? opt_in(k_bwd_proj<128, false, 1>, opted[2])
+                       : pp.halves == 2 ? opt_in(k_bwd_proj<64, true, 2>, opted[1]) : opt_in(k_bwd_proj<64, true, 1>, opted[0])))
             return BRA_ERR_LAUNCH;
         ProfScope ps(st, K_GEN_BACKWARD);
-        if (C == 64)
-            hipLaunchKernelGGL((k_bwd_proj<64, true>), dim3(pp.groups), dim3(256), (ProjSmem<64, true>::bytes), st,
+        if (pp.halves == 2)
+            hipLaunchKernelGGL((k_bwd_proj<64, true, 2>), dim3(pp.groups), dim3(512), (2 * ProjSmem<64, true>::bytes), st,
+                               w.dqkv, (const bf16_t *)X, (const bf16_t *)Wqkv, (bf16_t *)dX, w.part_qkv, w.o,
+                               (const bf16_t *)dY, w.part_o, M, pp.tiles, pp.per_wg);
+        else if (C == 64)
+            hipLaunchKernelGGL((k_bwd_proj<64, true, 1>), dim3(pp.groups), dim3(256), (ProjSmem<64, true>::bytes), st,
                                w.dqkv, (const bf16_t *)X, (const bf16_t *)Wqkv, (bf16_t *)dX, w.part_qkv, w.o,
                                (const bf16_t *)dY, w.part_o, M, pp.tiles, pp.per_wg);
         else
-            hipLaunchKernelGGL((k_bwd_proj<128, false>), dim3(pp.groups), dim3(512), (ProjSmem<128, false>::bytes), st,
+            hipLaunchKernelGGL((k_bwd_proj<128, false, 1>), dim3(pp.groups), dim3(512), (ProjSmem<128, false>::bytes), st,
                                w.dqkv, (const bf16_t *)X, (const bf16_t *)Wqkv, (bf16_t *)dX, w.part_qkv, nullptr,
                                nullptr, nullptr, M, pp.tiles, pp.per_wg);
         if (!launched()) return BRA_ERR_LAUNCH;

@@ -78,6 +78,13 @@ def test_backward_matrix_cores(dtype, B, H, W, C, heads, S, k):
     test_backward(dtype, B, H, W, C, heads, S, k, path="mfma")
 
 
+# Token counts where two groups of wavefronts share a workgroup of the gradient-map pass (more than 512 tiles of 64
+# tokens): one tile in the last workgroup, and three, the last of them ragged
+@pytest.mark.parametrize("B,H,W,S", [(18, 38, 48, 2), (9, 63, 63, 7)])
+def test_backward_paired_groups(B, H, W, S):
+    test_backward("bf16", B, H, W, 64, 2, S, 1, path="mfma")
+
+
 def compare_backward(Xn, Wqkvn, Won, Wlcen, dtype, heads, S, k, path="auto"):
     B, H, W, C = Xn.shape
     print(f"backward case dtype={dtype} shape={(B, H, W, C)} heads={heads} S={S} k={k} path={path}", flush=True)
