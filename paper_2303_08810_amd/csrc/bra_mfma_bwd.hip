@@ -213,7 +213,7 @@ ProjPlan proj_plan(long M, int C)
     p.tiles = (int)((M + 63) / 64);
     const int slots = C == 64 ? 512 : 256;
     p.per_wg = (p.tiles + slots - 1) / slots;
-    p.halves = C == 64 && p.per_wg > 1 ? 2 : 1;
+    p.halves = C == 64 && p.tiles > 256 ? 2 : 1;
     p.per_wg *= p.halves;
     p.groups = (p.tiles + p.per_wg - 1) / p.per_wg;
     return p;
