@@ -43,7 +43,8 @@ __device__ inline void store_from_f32(bf16_t *p, float v) { *p = f32_to_bf16(v);
 
 // GELU(t) = t Phi(t) = max(t, 0) - a Phi(-a), a = |t|, with log2 Phi(-a) as a polynomial of degree 5 (least maximum error
 // of a Phi(-a) over a <= 6, found by linear programming; it falls ever faster beyond).  Absolute error below 7e-7, that of
-// the float32 arithmetic included; one exponential is its only slow instruction.  Past 16 the product is 0.
+// the float32 arithmetic included; one exponential is its only slow instruction.  Past 16 the product is 0.  A NaN goes
+// through: the minimum drops it, the maximum (v_maximum3_f32 on gfx950, no dearer than v_max_f32) does not.
 __device__ __forceinline__ float gelu_f32(float t)
 {
     const float a = fminf(fabsf(t), 16.0f);
@@ -52,7 +53,7 @@ __device__ __forceinline__ float gelu_f32(float t)
     p = fmaf(p, a, -4.599926472e-01f);
     p = fmaf(p, a, -1.150787711e+00f);
     p = fmaf(p, a, -1.000037670e+00f);
-    return fmaf(-a, __builtin_amdgcn_exp2f(p), fmaxf(t, 0.f));
+    return fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_elementwise_maximum(t, 0.f));
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
