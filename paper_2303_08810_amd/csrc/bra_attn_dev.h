@@ -10,41 +10,52 @@ namespace mfma {
 
 // Softmax step for KT tiles of 16 keys x 16 queries of one head: scores
 // s[t][j] = S^T[key 16 t + 4 g + j][query i] relative to the reference m (which entered the product as its accumulator
-// input, so a score costs no subtraction), weights p = 2^s in the operand order of O^T += V^T P^T.  The reference moves,
-// and the sums are rescaled, only when a lane's own score exceeds it by 8 (weights stay below 2^8), which needs no exchange
-// between lanes; the quotient O / l does not depend on it.  FIRST: the reference is this block's maximum.
+// input, so a score costs no subtraction), weights p = 2^s in the operand order of O^T += V^T P^T.  l: the lane's share of
+// the denominator, a sum of the float32 weights (over its keys: the caller adds up the four lane groups at the end).
+// That sum also decides when the reference has to move: only when a lane's weights of a block exceed 2^8 together, which
+// needs no maximum and no exchange between lanes; the quotient O / l does not depend on it.  FIRST: the reference is this
+// block's maximum.
 template <bool FIRST, int KT, int NDT>
-__device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, f32x4 &l, f32x4 (&acc)[NDT], bf16x8 (&pb)[KT / 2])
+__device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, float &l, f32x4 (&acc)[NDT], bf16x8 (&pb)[KT / 2])
 {
-    float mx = s[0][0];
+    auto raise = [&](bool keep) {               // moves the reference to the largest score; returns by how much
+        float mx = s[0][0];
 #pragma unroll
-    for (int t = 0; t < KT; ++t)
+        for (int t = 0; t < KT; ++t)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) mx = fmaxf(mx, s[t][j]);
-    if (FIRST || __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0) {
-        const float up = FIRST ? cross_row_max(mx) : fmaxf(cross_row_max(mx), 0.f);
+            for (int j = 0; j < 4; ++j) mx = fmaxf(mx, s[t][j]);
+        const float up = keep ? fmaxf(cross_row_max(mx), 0.f) : cross_row_max(mx);
         m += up;
 #pragma unroll
         for (int t = 0; t < KT; ++t)
 #pragma unroll
             for (int j = 0; j < 4; ++j) s[t][j] -= up;
-        if (!FIRST) {
-            const float alpha = __builtin_amdgcn_exp2f(-up);
-            l *= alpha;
+        return up;
+    };
+    auto weights = [&]() {
+        float sum[2];
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
+        for (int tp = 0; tp < KT / 2; ++tp) {
+            float p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                p[e] = __builtin_amdgcn_exp2f(s[2 * tp + e / 4][e % 4]);
+                sum[e % 2] = tp == 0 && e < 2 ? p[e] : sum[e % 2] + p[e];
+            }
+            pb[tp] = pack8(p);
         }
-    }
+        return sum[0] + sum[1];
+    };
+    if (FIRST) raise(false);
+    float sum = weights();
+    if (!FIRST && __builtin_amdgcn_ballot_w64(sum > 256.0f) != 0) {
+        const float alpha = __builtin_amdgcn_exp2f(-raise(true));
+        l *= alpha;
 #pragma unroll
-    for (int tp = 0; tp < KT / 2; ++tp) {
-        float p[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(s[2 * tp + e / 4][e % 4]);
-        pb[tp] = pack8(p);
-        // denominators of the same rounded weights, from a product with an all-ones operand
-        const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
-        l = mfma16(__builtin_bit_cast(bf16x8, ones), pb[tp], l);
+        for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
+        sum = weights();
     }
+    l += sum;
 }
 
 // A direct load of 16 bytes per lane to 1024 consecutive bytes of LDS (l: the same for all lanes) that the compiler does

@@ -151,14 +151,13 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
     };
-    float m[NQ][HPW];
-    f32x4 l[NQ][HPW], acc[NQ][HPW][NDT];
+    float m[NQ][HPW], l[NQ][HPW];
+    f32x4 acc[NQ][HPW][NDT];
 #pragma unroll
     for (int q = 0; q < NQ; ++q)
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            m[q][hh] = 0.f;
-            l[q][hh] = f32x4{0.f, 0.f, 0.f, 0.f};
+            m[q][hh] = l[q][hh] = 0.f;
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
@@ -227,7 +226,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
                 if (nb == 0) m[q][hh] = -INFINITY;
                 float *part = sums + (q * HPW + hh) * 4 * kPart + lane;
                 part[wave * kPart] = m[q][hh];
-                part[wave * kPart + 64] = l[q][hh][0];
+                part[wave * kPart + 64] = l[q][hh];
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
@@ -247,7 +246,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
                     sum += f[w] * part[w * kPart + 64];
                 }
                 m[q][hh] = top;
-                l[q][hh][0] = sum;
+                l[q][hh] = sum;
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
@@ -265,7 +264,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
         const bool store = q0 + 16 * q + i < n && (!SPLIT || wave == 0);
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            const float inv = 1.0f / l[q][hh][0];
+            const float total = cross_row_sum(l[q][hh]), inv = 1.0f / total;
             float d = 0.f;
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) {
@@ -277,7 +276,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
                 acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
             d = cross_row_sum(d);
-            const float lse = m[q][hh] + __builtin_amdgcn_logf(l[q][hh][0]);       // v_log_f32: log2
+            const float lse = m[q][hh] + __builtin_amdgcn_logf(total);       // v_log_f32: log2
             neg_lse[q][hh] = -lse;
             neg_d[q][hh] = -d;
             if (store && g == 0) {

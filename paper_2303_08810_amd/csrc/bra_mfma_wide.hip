@@ -75,9 +75,8 @@ __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X,
 // the other is worked on; 16-byte pieces are exchanged so that K's row reads (piece c of row r at c ^ r % 8) and V's
 // transposing reads (c ^ 4 (r / 2 % 2)) meet different banks.  Queries past the end of the region and keys past k n
 // repeat the last one and are masked.
-// Bound by vector issue, most of it the 2^x (a quarter-rate instruction per score); a score costs half a maximum, half a
-// conversion and no other vector instruction.  2 x 208 x 304 x 64, 16 x 16 regions, k = 4: 74 us with two query tiles per
-// wavefront and 256 registers, 81 with one and 170; with 170 registers for two tiles 91, with 128 160 (spills).
+// A score costs a 2^x (quarter rate), an addition and half a conversion in vector instructions.  2 x 208 x 304 x 64,
+// 16 x 16 regions, k = 4: two query tiles per wavefront (152 registers) for regions that fill them, else one.
 template <int HD, int NQ>
 __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles)
 {
@@ -129,14 +128,13 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
             load_to_lds(A.V + at + 8 * ((lane % 8) ^ (4 * (row / 2 % 2))), Vs + 512 * (2 * wave + u));
         }
     };
-    float m[NQ][HPW];
-    f32x4 l[NQ][HPW], acc[NQ][HPW][NDT];
+    float m[NQ][HPW], l[NQ][HPW];
+    f32x4 acc[NQ][HPW][NDT];
 #pragma unroll
     for (int q = 0; q < NQ; ++q)
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            m[q][hh] = 0.f;
-            l[q][hh] = f32x4{0.f, 0.f, 0.f, 0.f};
+            m[q][hh] = l[q][hh] = 0.f;
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
@@ -208,10 +206,11 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
     }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        if (64 * NQ * qt + 16 * (NQ * wave + q) + i >= n) continue;
+        const bool store = 64 * NQ * qt + 16 * (NQ * wave + q) + i < n;
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            const float inv = 1.0f / l[q][hh][0];
+            const float inv = 1.0f / cross_row_sum(l[q][hh]);
+            if (!store) continue;
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt)
                 *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(acc[q][hh][dt] * inv);
@@ -289,14 +288,13 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
             load_to_lds_untracked(A.V + at + 8 * ((lane % 8) ^ (4 * (row / 2 % 2))), Vs + 512 * u);
         }
     };
-    float m[NQ][HPW];
-    f32x4 l[NQ][HPW], acc[NQ][HPW][NDT];
+    float m[NQ][HPW], l[NQ][HPW];
+    f32x4 acc[NQ][HPW][NDT];
 #pragma unroll
     for (int q = 0; q < NQ; ++q)
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            m[q][hh] = 0.f;
-            l[q][hh] = f32x4{0.f, 0.f, 0.f, 0.f};
+            m[q][hh] = l[q][hh] = 0.f;
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
@@ -367,10 +365,11 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
     }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        if (16 * q + i >= n) continue;
+        const bool store = 16 * q + i < n;
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            const float inv = 1.0f / l[q][hh][0];
+            const float inv = 1.0f / cross_row_sum(l[q][hh]);
+            if (!store) continue;
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt)
                 *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(acc[q][hh][dt] * inv);

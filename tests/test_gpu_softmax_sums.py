@@ -1,0 +1,63 @@
+"""The softmax denominators and the row statistics of the backward are sums of float32 weights, also where the weights
+enter their product as bf16: one key of weight 1 and 769 of weight 1 / 255, which bf16 rounds up by 0.4 %.  In exact
+arithmetic the probabilities are 255 / 1024 and 1 / 1024, and every stored number that is checked here is a bf16 number."""
+import math
+
+import pytest
+import torch
+
+import paper_2303_08810_amd as bra
+
+pytestmark = pytest.mark.gpu
+
+KEYS = 770
+
+
+def layer(B, rh, rw, S, C, heads, values):
+    """X, Wqkv, Wo, Wlce, routing: all queries attend the tokens of the first k regions, Q K^T is 0 for the image's first
+    token and -log2(255) for the others (with scale ln 2 the exponent of 2), V is 1 on the first token or on the others."""
+    H, W, k, d = S * rh, S * rw, KEYS // (rh * rw), C // heads
+    assert k * rh * rw == KEYS and k <= S * S
+    X = torch.zeros(B, H, W, C, device="cuda")
+    X[..., 0] = 1.0
+    X[:, 0, 0, 0] = 0.0
+    X[..., 1] = 1.0
+    X[:, 0, 0, 2] = 1.0
+    Wqkv = torch.zeros(C, 3 * C, device="cuda")
+    Wqkv[1, 0:C:d] = Wqkv[1, 1:C:d] = 1.0
+    Wqkv[0, C:2 * C:d] = -8.0
+    Wqkv[0, C + 1:2 * C:d] = 8.0 - math.log2(255.0)          # its bf16 rounding is off by 1e-6
+    Wqkv[2 if values == "first" else 0, 2 * C:] = 1.0
+    bf = [t.bfloat16() for t in (X, Wqkv, torch.eye(C, device="cuda"), torch.zeros(C, 5, 5, device="cuda"))]
+    Ir = torch.arange(k, dtype=torch.int32, device="cuda").expand(B, S * S, k).contiguous()
+    return bf, Ir, k
+
+
+# (B, rh, rw, S, C, heads): 16, 32, 64 and 128 queries at a time
+@pytest.mark.parametrize("B,rh,rw,S,C,heads", [(1, 2, 7, 8, 192, 6), (2, 2, 11, 7, 192, 3), (1, 7, 11, 4, 192, 6),
+                                               (19, 10, 11, 3, 192, 3), (19, 10, 11, 3, 192, 6)])
+def test_forward_denominators(B, rh, rw, S, C, heads):
+    (X, Wqkv, Wo, Wlce), Ir, k = layer(B, rh, rw, S, C, heads, "first")
+    Y = bra.bra_forward(X, Wqkv, Wo, Wlce, S, k, heads, Ir_in=Ir, scale=math.log(2.0), path="mfma")
+    assert torch.equal(Y.float(), torch.full_like(Y.float(), 255 / 1024))
+
+
+# a wavefront per region (16 and 32 tokens), four wavefronts per tile, 64 and 128 tokens per workgroup
+BACKWARD = [(6, 2, 7, 8, 64, 1), (6, 2, 11, 7, 64, 2), (1, 2, 7, 8, 64, 2), (1, 2, 11, 7, 64, 1), (3, 7, 11, 4, 64, 2),
+            (57, 10, 11, 3, 64, 1), (57, 10, 11, 3, 64, 2)]
+
+
+def gradients(B, rh, rw, S, C, heads, values):
+    (X, Wqkv, Wo, Wlce), Ir, k = layer(B, rh, rw, S, C, heads, values)
+    dY = torch.zeros_like(X)
+    dY.view(B, -1, C)[:, :512] = 1.0
+    dWqkv = bra.bra_backward(X, Wqkv, Wo, Wlce, Ir, dY, S, heads, scale=math.log(2.0), path="mfma")[1]
+    return dWqkv.view(C, 3, C)
+
+
+@pytest.mark.parametrize("B,rh,rw,S,C,heads", BACKWARD)
+def test_backward_denominators(B, rh, rw, S, C, heads):
+    # dV = P^T dO over 512 queries: 512 / 1024 for each of 769 keys, 512 * 255 / 1024 for the first
+    dW = gradients(B, rh, rw, S, C, heads, "first")
+    assert torch.allclose(dW[0, 2], torch.full((C,), B * 769 * 0.5, device="cuda"), rtol=1e-5)
+    assert torch.allclose(dW[2, 2], torch.full((C,), B * 127.5, device="cuda"), rtol=1e-5)
