@@ -14,9 +14,10 @@ namespace mfma {
 // the denominator, a sum of the float32 weights (over its keys: the caller adds up the four lane groups at the end).
 // That sum also decides when the reference has to move: only when a lane's weights of a block exceed 2^8 together, which
 // needs no maximum and no exchange between lanes; the quotient O / l does not depend on it.  FIRST: the reference is this
-// block's maximum.
+// block's maximum.  With dp (scores of the gradient in the same layout) also d: the lane's share of sum p dp.
 template <bool FIRST, int KT, int NDT>
-__device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, float &l, f32x4 (&acc)[NDT], bf16x8 (&pb)[KT / 2])
+__device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, float &l, f32x4 (&acc)[NDT], bf16x8 (&pb)[KT / 2],
+                                             const f32x4 *dp = nullptr, float *d = nullptr)
 {
     auto raise = [&](bool keep) {               // moves the reference to the largest score; returns by how much
         float mx = s[0][0];
@@ -32,8 +33,10 @@ __device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, float &l,
             for (int j = 0; j < 4; ++j) s[t][j] -= up;
         return up;
     };
+    float dsum = 0.f;
     auto weights = [&]() {
         float sum[2];
+        dsum = 0.f;
 #pragma unroll
         for (int tp = 0; tp < KT / 2; ++tp) {
             float p[8];
@@ -41,6 +44,7 @@ __device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, float &l,
             for (int e = 0; e < 8; ++e) {
                 p[e] = __builtin_amdgcn_exp2f(s[2 * tp + e / 4][e % 4]);
                 sum[e % 2] = tp == 0 && e < 2 ? p[e] : sum[e % 2] + p[e];
+                if (dp) dsum = fmaf(p[e], dp[2 * tp + e / 4][e % 4], dsum);
             }
             pb[tp] = pack8(p);
         }
@@ -51,11 +55,13 @@ __device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, float &l,
     if (!FIRST && __builtin_amdgcn_ballot_w64(sum > 256.0f) != 0) {
         const float alpha = __builtin_amdgcn_exp2f(-raise(true));
         l *= alpha;
+        if (dp) *d *= alpha;
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
         sum = weights();
     }
     l += sum;
+    if (dp) *d += dsum;
 }
 
 // A direct load of 16 bytes per lane to 1024 consecutive bytes of LDS (l: the same for all lanes) that the compiler does

@@ -71,7 +71,8 @@ __device__ __forceinline__ bool place(const Dims &D, int tiles, int items, int w
 
 // ---------------------------------------------------------------------------
 // Query side: attention output O, row statistics lse and D, and dQ, in two sweeps over the region's k n routed keys.  The
-// first is the forward's attention; D = dO . O needs no dP there.  The second goes over the blocks backwards, so that the
+// first is the forward's attention and sums D = sum P dP beside it, from the float32 weights (dO . O has the rounding of
+// the weights that entered O).  The second goes over the blocks backwards, so that the
 // last two are still in LDS (up to 128 or 64 routed keys: nothing is read twice).
 template <int HD, int NQ, Mode MODE>
 __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_attn_bwd_q(AttnBwdArgs A, Dims D, int tiles, int items)
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
     constexpr bool SHARED = R::SHARED, SPLIT = MODE == kSplit;
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16, KB = R::KB, KT = KB / 16;
     __shared__ __attribute__((aligned(16))) bf16_t lds[R::bufs * R::buf];
-    constexpr int kPart = 64 * (2 + 4 * NDT);    // SPLIT: m, l and the sums of a wavefront, one query tile and head
+    constexpr int kPart = 64 * (3 + 4 * NDT);    // SPLIT: m, l, D and the sums of a wavefront, one query tile and head
     __shared__ __attribute__((aligned(16))) float sums[SPLIT ? NQ * HPW * 4 * kPart : 4];
     extern __shared__ int origin_tables[];       // [k] or [4][k]: first token of the routed regions
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
@@ -151,13 +152,13 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
     };
-    float m[NQ][HPW], l[NQ][HPW];
+    float m[NQ][HPW], l[NQ][HPW], dd[NQ][HPW];
     f32x4 acc[NQ][HPW][NDT];
 #pragma unroll
     for (int q = 0; q < NQ; ++q)
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            m[q][hh] = l[q][hh] = 0.f;
+            m[q][hh] = l[q][hh] = dd[q][hh] = 0.f;
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
@@ -176,23 +177,30 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
         for (int hh = 0; hh < HPW; ++hh) {
             bf16x8 pb[NQ][KT / 2];
             {
-                bf16x8 kf[KT][KSD];
+                bf16x8 kf[KT][KSD], vr[KT][KSD];
 #pragma unroll
                 for (int t = 0; t < KT; ++t)
 #pragma unroll
-                    for (int ks = 0; ks < KSD; ++ks) kf[t][ks] = row_operand(Ks, 16 * t + i, HD / 8 * hh + 4 * ks + g);
+                    for (int ks = 0; ks < KSD; ++ks) {
+                        kf[t][ks] = row_operand(Ks, 16 * t + i, HD / 8 * hh + 4 * ks + g);
+                        vr[t][ks] = row_operand(Vs, 16 * t + i, HD / 8 * hh + 4 * ks + g);
+                    }
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
-                    f32x4 sc[KT];
+                    f32x4 sc[KT], dp[KT];
                     const float neg = -m[q][hh];
 #pragma unroll
                     for (int t = 0; t < KT; ++t) {
                         sc[t] = f32x4{neg, neg, neg, neg};
+                        dp[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int ks = 0; ks < KSD; ++ks) sc[t] = mfma16(kf[t][ks], qf[q][hh][ks], sc[t]);   // S^T[key 16 t + 4 g + j][query i]
+                        for (int ks = 0; ks < KSD; ++ks) {
+                            sc[t] = mfma16(kf[t][ks], qf[q][hh][ks], sc[t]);   // S^T[key 16 t + 4 g + j][query i]
+                            dp[t] = mfma16(vr[t][ks], gf[q][hh][ks], dp[t]);
+                        }
                     }
                     mask(sc, kn - KB * (STEP * s + start));
-                    softmax_step<decltype(first)::value>(sc, m[q][hh], l[q][hh], acc[q][hh], pb[q]);
+                    softmax_step<decltype(first)::value>(sc, m[q][hh], l[q][hh], acc[q][hh], pb[q], dp, &dd[q][hh]);
                     if (SHARED && NQ > 1) __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -227,10 +235,11 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
                 float *part = sums + (q * HPW + hh) * 4 * kPart + lane;
                 part[wave * kPart] = m[q][hh];
                 part[wave * kPart + 64] = l[q][hh];
+                part[wave * kPart + 128] = dd[q][hh];
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) part[wave * kPart + 64 * (2 + 4 * dt + j)] = acc[q][hh][dt][j];
+                    for (int j = 0; j < 4; ++j) part[wave * kPart + 64 * (3 + 4 * dt + j)] = acc[q][hh][dt][j];
             }
         __syncthreads();
 #pragma unroll
@@ -239,21 +248,23 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
             for (int hh = 0; hh < HPW; ++hh) {
                 const float *part = sums + (q * HPW + hh) * 4 * kPart + lane;
                 const float top = fmaxf(fmaxf(part[0], part[kPart]), fmaxf(part[2 * kPart], part[3 * kPart]));
-                float f[4], sum = 0.f;
+                float f[4], sum = 0.f, dsum = 0.f;
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
                     f[w] = __builtin_amdgcn_exp2f(part[w * kPart] - top);
                     sum += f[w] * part[w * kPart + 64];
+                    dsum += f[w] * part[w * kPart + 128];
                 }
                 m[q][hh] = top;
                 l[q][hh] = sum;
+                dd[q][hh] = dsum;
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         float a = 0.f;
 #pragma unroll
-                        for (int w = 0; w < 4; ++w) a += f[w] * part[w * kPart + 64 * (2 + 4 * dt + j)];
+                        for (int w = 0; w < 4; ++w) a += f[w] * part[w * kPart + 64 * (3 + 4 * dt + j)];
                         acc[q][hh][dt][j] = a;
                     }
             }
@@ -264,18 +275,12 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
         const bool store = q0 + 16 * q + i < n && (!SPLIT || wave == 0);
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
-            const float total = cross_row_sum(l[q][hh]), inv = 1.0f / total;
-            float d = 0.f;
+            const float total = cross_row_sum(l[q][hh]), inv = 1.0f / total, d = cross_row_sum(dd[q][hh]) * inv;
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) {
-                const size_t e = img + (size_t)tok[q] * C + HD * hh + 16 * dt + 4 * g;
-                const u32x2 go = *(const u32x2 *)(A.dO + e);
-                const f32x4 o = acc[q][hh][dt] * inv;
-                d += o[0] * bf16_lo(go[0]) + o[1] * bf16_hi(go[0]) + o[2] * bf16_lo(go[1]) + o[3] * bf16_hi(go[1]);
-                if (store) *(u32x2 *)(A.O + e) = pack4(o);
+                if (store) *(u32x2 *)(A.O + img + (size_t)tok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(acc[q][hh][dt] * inv);
                 acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
-            d = cross_row_sum(d);
             const float lse = m[q][hh] + __builtin_amdgcn_logf(total);       // v_log_f32: log2
             neg_lse[q][hh] = -lse;
             neg_d[q][hh] = -d;

@@ -61,3 +61,14 @@ def test_backward_denominators(B, rh, rw, S, C, heads):
     dW = gradients(B, rh, rw, S, C, heads, "first")
     assert torch.allclose(dW[0, 2], torch.full((C,), B * 769 * 0.5, device="cuda"), rtol=1e-5)
     assert torch.allclose(dW[2, 2], torch.full((C,), B * 127.5, device="cuda"), rtol=1e-5)
+
+
+@pytest.mark.parametrize("B,rh,rw,S,C,heads", BACKWARD)
+def test_backward_row_sums(B, rh, rw, S, C, heads):
+    # V is 1 on the others: with d channels per head D = d 769 / 1024, dS = d 255 / 1024 / 1024 for each of them and, K being
+    # -8 there in channel 0 of a head, dQ = ln 2 * 769 dS * -8 at each of the 512 queries.  dS is a bf16 number; the bound
+    # is one rounding to bf16 of dQ, 2^-9, and the float32 sums
+    dW = gradients(B, rh, rw, S, C, heads, "others")
+    d = C // heads
+    dQ = -8.0 * math.log(2.0) * 769 * d * 255 / 1024 / 1024
+    assert torch.allclose(dW[1, 0, ::d], torch.full((heads,), B * 512 * dQ, device="cuda"), rtol=2.1e-3)
