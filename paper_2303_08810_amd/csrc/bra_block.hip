@@ -215,7 +215,8 @@ __global__ __launch_bounds__(256) void k_token_ln(const bf16_t *A, const bf16_t 
 // X1 = X + DWConv3x3(X) + bpos and Xn = LayerNorm1(X1), walking down columns.  A lane keeps the window's three rows of its
 // token's column and the two beside it, so a step reads three new tokens instead of nine, requested a step ahead; the
 // products run on v_dot2_f32_bf16, taps (0, 1) of a row as pairs of columns (one byte permute per channel), tap 2 on the
-// column as loaded, with zero in the other channel's half of its weight.
+// column as loaded, with zero in the other channel's half of its weight (an infinity makes NaN of the neighbour channel
+// too; the LayerNorm over the token's channels, and the attention output added to X1 after it, do so with all of them).
 // 50176 tokens, C = 128: 13.1 us (nine loads per token and float32 multiply-adds: 19.4; 38 MB in and out are 8 us);
 // 12.5 to 14.0 with strips of 14 down to 2 rows.
 template <int G>

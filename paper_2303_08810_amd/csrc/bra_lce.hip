@@ -3,9 +3,11 @@
 //
 // A thread has 2 channels (one 32-bit load per token) of 2 neighbouring columns and walks down a strip of rows with
 // the window of 5 rows x 6 columns in registers.  Per channel and row the left output takes the column pairs (0,1),
-// (2,3) and column 4 against (w0,w1), (w2,w3), w4; the right one the pairs (1,2), (3,4) and column 5 against the same
-// taps.  A pair costs one byte permute; columns 4 and 5 are used as loaded (both channels), with w4 in the half of its
-// channel and zero in the other.  The next row is requested a step ahead and nothing is staged through LDS.
+// (2,3), (3,4) against (w0,w1), (w2,w3), (0,w4); the right one the pairs (1,2), (3,4), (4,5) against the same taps.  A
+// pair costs one byte permute.  The zero meets a column that the output takes anyway, in the same channel: an infinity
+// may leave an output as NaN, but nothing reaches another channel or an output further away (columns as loaded, both
+// channels in one operand with w4 in one half, did that: 0 times infinity in the neighbour).
+// The next row is requested a step ahead and nothing is staged through LDS.
 // What bounds it: the dot products and permutes (about 0.4 of the time by instruction count) and, at 3 to 4 wavefronts
 // per SIMD, the latency they do not cover; an LDS-tiled version on float32 multiply-adds took 69 us for all three
 // correlations of a 64 x 56 x 56 x 64 map.
@@ -18,9 +20,9 @@ namespace {
 
 using namespace mfma;
 
-// A window row: pairs of columns (0,1), (2,3) | (1,2), (3,4) per channel, and columns 4, 5 as loaded.
+// A window row: pairs of columns (0,1), (2,3), (4,5) | (1,2), (3,4) per channel.
 struct Row {
-    unsigned even[2][2], odd[2][2], c4, c5;
+    unsigned even[2][3], odd[2][2];
 };
 
 // How a workgroup's 8 column-pair slots lie on a map: `pairs` of them side by side, `subs` strips above each other
@@ -40,7 +42,7 @@ __global__ __launch_bounds__(256) void k_lce_pairs(const bf16_t *__restrict__ In
                                                    int tiles_per_wg)
 {
     __shared__ __attribute__((aligned(16))) float red[GRAD ? 25 * 256 : 15 * 64];
-    unsigned (*table)[3][64] = (unsigned (*)[3][64])red;      // [ky][(w0,w1) | (w2,w3) | w4][channel]
+    unsigned (*table)[3][64] = (unsigned (*)[3][64])red;      // [ky][(w0,w1) | (w2,w3) | (0,w4)][channel]
     const int block = mfma::swizzled_block(), cb = block % cblocks, c0 = 64 * cb, grp = block / cblocks;
     const long first = (long)grp * tiles_per_wg, last = min(tiles, first + tiles_per_wg);
     if (first >= tiles) return;
@@ -55,7 +57,7 @@ __global__ __launch_bounds__(256) void k_lce_pairs(const bf16_t *__restrict__ In
         }
         table[ky][0][ch] = t[0] | t[1] << 16;
         table[ky][1][ch] = t[2] | t[3] << 16;
-        table[ky][2][ch] = ch % 2 ? t[4] << 16 : t[4];
+        table[ky][2][ch] = t[4] << 16;
     }
     __syncthreads();
     const bool live = c0 + 2 * cp < D.C;
@@ -105,14 +107,13 @@ __global__ __launch_bounds__(256) void k_lce_pairs(const bf16_t *__restrict__ In
             }
             Row R;
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < 3; ++t) {
                 R.even[0][t] = pair_lo(raw[2 * t], raw[2 * t + 1]);
                 R.even[1][t] = pair_hi(raw[2 * t], raw[2 * t + 1]);
+                if (t == 2) break;
                 R.odd[0][t] = pair_lo(raw[2 * t + 1], raw[2 * t + 2]);
                 R.odd[1][t] = pair_hi(raw[2 * t + 1], raw[2 * t + 2]);
             }
-            R.c4 = raw[4];
-            R.c5 = raw[5];
             return R;
         };
         unsigned next[6], nv[2], nd[2];
@@ -158,15 +159,15 @@ __global__ __launch_bounds__(256) void k_lce_pairs(const bf16_t *__restrict__ In
                             o[0][v] = dot2(w[r][t][v], R.even[v][t], o[0][v]);
                             o[1][v] = dot2(w[r][t][v], R.odd[v][t], o[1][v]);
                         }
-                        o[0][v] = dot2(w[r][2][v], R.c4, o[0][v]);
-                        o[1][v] = dot2(w[r][2][v], R.c5, o[1][v]);
+                        o[0][v] = dot2(w[r][2][v], R.odd[v][1], o[0][v]);
+                        o[1][v] = dot2(w[r][2][v], R.even[v][2], o[1][v]);
                         if (GRAD) {
 #pragma unroll
                             for (int t = 0; t < 2; ++t) {
                                 acc[5 * r + 2 * t][v] = dot2(vp[v], R.even[v][t], acc[5 * r + 2 * t][v]);
                                 acc[5 * r + 2 * t + 1][v] = dot2(vp[v], R.odd[v][t], acc[5 * r + 2 * t + 1][v]);
                             }
-                            acc[5 * r + 4][v] = dot2(vp[v], v ? pair_hi(R.c4, R.c5) : pair_lo(R.c4, R.c5), acc[5 * r + 4][v]);
+                            acc[5 * r + 4][v] = dot2(vp[v], R.even[v][2], acc[5 * r + 4][v]);
                         }
                     }
                 }

@@ -211,7 +211,8 @@ void k_small(AttnArgs A, Dims D, int log2n)
     }
 
     // LCE (Eq. 7) of the region's tokens on the two-element dot product: taps (0,1), (2,3) of a row per channel against
-    // pairs of columns, tap 4 against the column as loaded with zero in the other channel's half
+    // pairs of columns, tap 4 against the column as loaded with zero in the other channel's half (an infinity makes NaN of
+    // the neighbour channel too; W^o, which follows in this kernel, puts it into every channel of these tokens anyway)
     unsigned w01[5][2], w23[5][2], w4[5][2];
 #pragma unroll
     for (int ky = 0; ky < 5; ++ky) {

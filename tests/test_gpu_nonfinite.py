@@ -5,6 +5,7 @@ import torch
 
 import paper_2303_08810_amd as bra
 from parity_util import to_device
+from synthetic_inputs import make_inputs
 from test_gpu_block import device_params, inputs
 
 pytestmark = pytest.mark.gpu
@@ -25,3 +26,35 @@ def test_gelu_keeps_nan(dtype, C, heads, e):
         assert bool(torch.isfinite(out).all()) if finite else not bool(torch.isfinite(out).any()), value
         if np.isnan(value):
             assert bool(torch.isnan(out).all())
+
+
+# O += LCE(V) and dV += LCE^T(dO) on bf16 maps: even and odd widths, one column, several strips
+@pytest.mark.parametrize("H,W,C,heads,S", [(14, 14, 64, 2, 7), (21, 7, 128, 2, 7), (40, 1, 64, 1, 1), (24, 50, 192, 6, 2)])
+@pytest.mark.parametrize("channel", [2, 5])
+def test_depthwise_channels_independent(H, W, C, heads, S, channel):
+    X, Wqkv, Wo, Wlce = make_inputs(1, H, W, C, seed=9950 + H + C, dtype="bf16")
+    rng = np.random.Generator(np.random.PCG64(9951))
+    dY = np.asarray(X) * np.float32(0.5)
+    Ir = np.stack([rng.permutation(S * S)[:1] for _ in range(S * S)])[None].astype(np.int32)
+    y, x = H // 2, W // 2
+    other = np.arange(C) != channel
+
+    def gradients(X, Wqkv, Wo, dY):
+        args = [to_device(a, "bf16") for a in (X, Wqkv, Wo, Wlce)]
+        out = bra.bra_backward(*args, torch.from_numpy(Ir).cuda(), to_device(dY, "bf16"), S, heads, path="mfma")
+        return [g.float().cpu().numpy() for g in out]
+
+    # V overflows in one channel of one token: dWo = O^T dY is finite in every other row
+    Xi, Wi = X.copy(), Wqkv.copy()
+    Xi[0, y, x, 7] = 2.0 ** 100
+    Wi[7] = 0
+    Wi[7, 2 * C + channel] = 2.0 ** 40
+    dWo = gradients(Xi, Wi, Wo, dY)[2]
+    assert np.isfinite(dWo[other]).all() and not np.isfinite(dWo[channel]).any()
+    # dO overflows there: dV and its columns of dWqkv = X^T dV are finite in every other channel
+    dYi, Woi = dY.copy(), Wo.copy()
+    dYi[0, y, x, 9] = 2.0 ** 100
+    Woi[:, 9] = 0
+    Woi[channel, 9] = 2.0 ** 40
+    dW = gradients(X, Wqkv, Woi, dYi)[1][:, 2 * C:]
+    assert np.isfinite(dW[:, other]).all() and not np.isfinite(dW[:, channel]).any()
