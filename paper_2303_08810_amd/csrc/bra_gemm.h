@@ -38,9 +38,6 @@ struct GemmRegions {
 // Out = In W: In [M, K] bf16, W row-major [K][ldw]; K a multiple of 64, Nout of 8.
 int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, const GemmRegions *regions,
          int kernel_id, hipStream_t st);
-// The same with float32 results (two buffers at most).
-int gemm_f32out(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, float *out0, float *out1, int cols,
-                int kernel_id, hipStream_t st);
 // Out = In Wt^T: Wt [Nout][ldw], the contraction axis contiguous.
 int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout, bf16_t *Out, int kernel_id, hipStream_t st);
 

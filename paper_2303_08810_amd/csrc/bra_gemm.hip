@@ -10,33 +10,31 @@ using namespace mfma;
 namespace {
 
 // ---------------------------------------------------------------------------
-// Out[m][o] = sum_k In[m][k] W[k][o] (W row-major with ldw columns, as the caller holds it)
+// Out[m][o] = sum_k In[m][k] W[k][o] (W row-major with ldw columns, as the caller holds it), float32 In and Out,
 // for a tile of 64 rows m x 32 CW outputs o (128 or 64), the contraction in chunks of 64
 // staged in LDS (the next chunk is requested while the current one is multiplied).
 // The four wavefronts split the tile 2 x 2 (32 rows x 16 CW outputs each); the product is formed
 // transposed (D[output 16 t + 4 g + jj][row i]) so that a lane stores 4 consecutive outputs of one row;
 // its W operand (rows = outputs) comes out of the row-major chunk by the transposing LDS read.
-// Output column o goes to buffer o / cols (three buffers of `cols` columns each, e.g. Q, K,
-// V), column o % cols.
-// SPLIT: In is float32 and enters as three exact bf16 terms (smallest first); otherwise In is
-// bf16.  Out is float32.
+// Output column o goes to buffer o / cols (buffers of `cols` columns each, e.g. Q^r, K^r), column o % cols.
+// In enters as three exact bf16 terms (smallest first).
 constexpr int kGemmPitch = 80;      // bf16 per LDS row of In: 64 + 16 (rows of 160 bytes); W: the tile's width + 16
 constexpr int kGemmGroupW = 64;     // W: 128 bytes more after every 8 rows: the neighbouring lane group of a
                                     // transposing read (8 rows further on) then meets the other half of the banks
 
 // Ws: [64 k][32 CW + 16] and 8 group paddings, Xs[q]: [64][P].
-template <bool SPLIT, int CW>
-__device__ __forceinline__ void gemm64(const void *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int M, int K,
-                                       int Nout, const GemmOut &out, int block, bf16_t *Ws, bf16_t *const (&Xs)[SPLIT ? 3 : 1])
+template <int CW>
+__device__ __forceinline__ void gemm64(const GemmRegions &J, const bf16_t *__restrict__ W, int ldw, int K, int block,
+                                       bf16_t *Ws, bf16_t *const (&Xs)[3])
 {
-    constexpr int P = kGemmPitch, NT = SPLIT ? 3 : 1, COLS = 32 * CW, PW = COLS + 16;
+    const int M = (int)J.M, Nout = J.Nout;
+    constexpr int P = kGemmPitch, NT = 3, COLS = 32 * CW, PW = COLS + 16;
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int otiles = (Nout + COLS - 1) / COLS;
     const int m0 = (block / otiles) * 64, o0 = (block % otiles) * COLS;
 
-    // this thread's pieces of a chunk: 4 x 16 bytes of W, and 2 x 16 bytes of bf16 In or
-    // 2 x 8 floats of float32 In
-    u32x4 wreg[CW], xreg[SPLIT ? 4 : 2];
+    // this thread's pieces of a chunk: 4 x 16 bytes of W and 2 x 8 floats of In
+    u32x4 wreg[CW], xreg[4];
     auto request = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < CW; ++u) {
@@ -47,14 +45,9 @@ __device__ __forceinline__ void gemm64(const void *__restrict__ In, const bf16_t
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int idx = tid + 256 * u;
-            const int m = min(m0 + idx / 8, M - 1);
-            if (SPLIT) {
-                const float *src = (const float *)In + (size_t)m * K + k0 + (idx % 8) * 8;
-                xreg[2 * u] = *(const u32x4 *)src;
-                xreg[2 * u + 1] = *(const u32x4 *)(src + 4);
-            } else {
-                xreg[u] = *(const u32x4 *)((const bf16_t *)In + (size_t)m * K + k0 + (idx % 8) * 8);
-            }
+            const float *src = J.In + (size_t)min(m0 + idx / 8, M - 1) * K + k0 + (idx % 8) * 8;
+            xreg[2 * u] = *(const u32x4 *)src;
+            xreg[2 * u + 1] = *(const u32x4 *)(src + 4);
         }
     };
     auto park = [&]() {
@@ -68,16 +61,12 @@ __device__ __forceinline__ void gemm64(const void *__restrict__ In, const bf16_t
         for (int u = 0; u < 2; ++u) {
             const int idx = tid + 256 * u;
             const int at = (idx / 8) * P + (idx % 8) * 8;
-            if (SPLIT) {
-                const f32x4 lo = __builtin_bit_cast(f32x4, xreg[2 * u]), hi = __builtin_bit_cast(f32x4, xreg[2 * u + 1]);
-                const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                bf16x8 t[3];
-                split3(x, t);
+            const f32x4 lo = __builtin_bit_cast(f32x4, xreg[2 * u]), hi = __builtin_bit_cast(f32x4, xreg[2 * u + 1]);
+            const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            bf16x8 t[3];
+            split3(x, t);
 #pragma unroll
-                for (int q = 0; q < 3; ++q) *(bf16x8 *)(Xs[q] + at) = t[q];
-            } else {
-                *(u32x4 *)(Xs[0] + at) = xreg[u];
-            }
+            for (int q = 0; q < 3; ++q) *(bf16x8 *)(Xs[q] + at) = t[q];
         }
     };
 
@@ -125,27 +114,20 @@ __device__ __forceinline__ void gemm64(const void *__restrict__ In, const bf16_t
         for (int t = 0; t < CW; ++t) {
             const int o = o0 + 16 * CW * wc + 16 * t + 4 * g;
             if (o >= Nout) break;
-            const int which = o / out.cols, col = o % out.cols;
-            *(f32x4 *)((float *)out.buf[which] + (size_t)m * out.cols + col) = acc[rt][t];
+            const int which = o / J.cols, col = o % J.cols;
+            *(f32x4 *)(J.buf[which] + (size_t)m * J.cols + col) = acc[rt][t];
         }
     }
 }
 
-// 64 x 32 CW tiles for the float32 inputs and results of the routing.
-template <bool SPLIT, int CW>
-__global__ __launch_bounds__(256) void k_gemm(const void *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int M,
-                                              int K, int Nout, GemmOut out)
+// The region-level product on its own.
+template <int CW>
+__global__ __launch_bounds__(256) void k_gemm(GemmRegions J, const bf16_t *__restrict__ W, int ldw, int K)
 {
-    constexpr int NT = SPLIT ? 3 : 1;
     __shared__ __attribute__((aligned(16))) bf16_t Ws[64 * (32 * CW + 16) + 8 * kGemmGroupW];
-    __shared__ __attribute__((aligned(16))) bf16_t Xs[NT * 64 * kGemmPitch];
-    if constexpr (SPLIT) {
-        bf16_t *const planes[3] = {Xs, Xs + 64 * kGemmPitch, Xs + 2 * 64 * kGemmPitch};
-        gemm64<SPLIT, CW>(In, W, ldw, M, K, Nout, out, blockIdx.x, Ws, planes);
-    } else {
-        bf16_t *const planes[1] = {Xs};
-        gemm64<SPLIT, CW>(In, W, ldw, M, K, Nout, out, blockIdx.x, Ws, planes);
-    }
+    __shared__ __attribute__((aligned(16))) bf16_t Xs[3 * 64 * kGemmPitch];
+    bf16_t *const planes[3] = {Xs, Xs + 64 * kGemmPitch, Xs + 2 * 64 * kGemmPitch};
+    gemm64<CW>(J, W, ldw, K, blockIdx.x, Ws, planes);
 }
 
 // ---------------------------------------------------------------------------
@@ -182,9 +164,8 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
     __shared__ __attribute__((aligned(16))) bf16_t B0[BE];
     __shared__ __attribute__((aligned(16))) bf16_t B1[BE];
     if (REGIONS && (int)blockIdx.x < reg_blocks) {
-        const GemmOut ro = {{reg.buf[0], reg.buf[1], nullptr}, reg.cols, {nullptr, nullptr}, nullptr, nullptr, 0};
         bf16_t *const planes[3] = {A0, A1, B1};
-        gemm64<true, 2>(reg.In, W, ldw, (int)reg.M, K, reg.Nout, ro, blockIdx.x, B0, planes);
+        gemm64<2>(reg, W, ldw, K, blockIdx.x, B0, planes);
         return;
     }
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, h = lane / 32, c = lane % 32;
@@ -380,23 +361,6 @@ int launch_big(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int No
     return launch_dma<64, 64, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
 }
 
-template <bool SPLIT>
-int launch_f32out(const void *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, hipStream_t st)
-{
-    // 64 x 64 tiles (twice the workgroups, six wavefronts per SIMD instead of four) where 64 x 128
-    // tiles would leave the chip under-filled; measured: the narrow tile wins below a few hundred
-    // wide tiles and loses above about a thousand
-    // (and where the output is at most 64 columns wide: half of a wide tile would be idle)
-    const long mt = (M + 63) / 64;
-    if (Nout <= 64 || mt * ((Nout + 127) / 128) < 400)
-        hipLaunchKernelGGL((k_gemm<SPLIT, 2>), dim3((unsigned)(mt * ((Nout + 63) / 64))), dim3(256), 0, st, In, W, ldw,
-                           (int)M, K, Nout, out);
-    else
-        hipLaunchKernelGGL((k_gemm<SPLIT, 4>), dim3((unsigned)(mt * ((Nout + 127) / 128))), dim3(256), 0, st, In, W,
-                           ldw, (int)M, K, Nout, out);
-    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
-}
-
 // ---------------------------------------------------------------------------
 // Products with a short contraction (K = 64 or 128) over many rows, into bf16 buffers of K columns each (N = K or 3 K): Q, K,
 // V, dO and Y of the first stages.  A tile of k_gemm_dma has one or two chunks to load before it stores, and its loads and
@@ -518,7 +482,6 @@ int launch_proj(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int N
 // Part[share][a][n] = sum over the share's tokens t of A[t][a] B[t][n] (the weight gradients dWqkv = X^T dQKV and
 // dWo = O^T dY, both in one launch): a 128 x 128 block of the output per workgroup, 64 tokens at a time straight into one of
 // two LDS buffers; both operands by transposing reads (pieces exchanged as for W above).
-template <int UNUSED = 0>
 __device__ __forceinline__ void tn_block(const GemmTn &J, int block, long M, int share_tokens, bf16_t *A0, bf16_t *A1,
                                          bf16_t *B0, bf16_t *B1)
 {
@@ -657,14 +620,6 @@ int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout
     return launch_big<false, true>(In, Wt, ldw, M, K, Nout, out, GemmRegions{}, st);
 }
 
-int gemm_f32out(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, float *out0, float *out1, int cols,
-                int kernel_id, hipStream_t st)
-{
-    if (!sizes_ok(M, K, Nout)) return BRA_ERR_UNSUPPORTED;
-    ProfScope ps(st, kernel_id);
-    return launch_f32out<false>(In, W, ldw, M, K, Nout, GemmOut{{out0, out1, nullptr}, cols, {nullptr, nullptr}}, st);
-}
-
 // Two workgroups per compute unit over the 128 x 128 blocks of both products.
 static int tn_share_tokens(long M, int KA0, int N0, int KA1, int N1)
 {
@@ -693,7 +648,16 @@ int gemm_regions(const GemmRegions &r, const bf16_t *W, int ldw, int K, int kern
 {
     if (!sizes_ok(r.M, K, r.Nout)) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);
-    return launch_f32out<true>(r.In, W, ldw, r.M, K, r.Nout, GemmOut{{r.buf[0], r.buf[1], nullptr}, r.cols, {nullptr, nullptr}}, st);
+    // 64 x 64 tiles (twice the workgroups, six wavefronts per SIMD instead of four) where 64 x 128
+    // tiles would leave the chip under-filled; measured: the narrow tile wins below a few hundred
+    // wide tiles and loses above about a thousand
+    // (and where the output is at most 64 columns wide: half of a wide tile would be idle)
+    const long mt = (r.M + 63) / 64;
+    if (r.Nout <= 64 || mt * ((r.Nout + 127) / 128) < 400)
+        hipLaunchKernelGGL(k_gemm<2>, dim3((unsigned)(mt * ((r.Nout + 63) / 64))), dim3(256), 0, st, r, W, ldw, K);
+    else
+        hipLaunchKernelGGL(k_gemm<4>, dim3((unsigned)(mt * ((r.Nout + 127) / 128))), dim3(256), 0, st, r, W, ldw, K);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
 int gemm_bf16(const bf16_t *In, const bf16_t *W, long M, int K, int Nout, bf16_t *Out, const float *bias,

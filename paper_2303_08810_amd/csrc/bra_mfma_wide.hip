@@ -5,13 +5,13 @@
 // appendix (32x32 map, S = 8, k = 12, 12 heads of 64 channels).
 //
 //   k_pool_wide   Xr[b, r, :] = mean of the region's tokens, float32            (Sec. 3.2)
-//   k_gemm<true>  Q^r | K^r = Xr [Wq | Wk] in float32: the means are split exactly into three
-//                 bf16 terms, so the products are those of the float32 computation
+//   k_gemm_dma    Q | K | V = X Wqkv (Eq. 3), bf16 out; in the same launch Q^r | K^r = Xr [Wq | Wk] in float32: the
+//                 means are split exactly into three bf16 terms, so the products are those of the float32 computation
+//                 (one token per region: no means, the token projection leaves float32 copies of Q and K instead)
 //   k_route_rows  rows of A^r = Q^r (K^r)^T (Eq. 4) and their top-k (Eq. 5)
-//   k_gemm<false> Q | K | V = X Wqkv (Eq. 3), bf16 out
-//   image-resident attention (small maps, regions of up to 8 tokens; bra_mfma_small.hip) or
-//   k_attn_gen (everything else), then LCE added in place                       (Eq. 6, 7)
-//   k_gemm<false> Y = O Wo (Eq. 2)
+//   image-resident attention (small maps, regions of up to 8 tokens; bra_mfma_small.hip), k_attn_rows (regions of up to
+//   32 tokens) or k_attn_gen, then k_lce_pairs adds the LCE in place            (Eq. 6, 7)
+//   k_gemm_dma    Y = O Wo (Eq. 2)
 #include "bra_attn_dev.h"
 #include "bra_gemm.h"
 #include "bra_lce_dev.h"
@@ -459,9 +459,11 @@ int route_steps(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideWs
 {
     int rc;
     if (D.n == 1) {
-        // one token per region: the means are the (bf16) tokens themselves, so Q^r | K^r is the
-        // plain projection of X with float32 results: no pooling, no split
-        rc = gemm_f32out(X, Wqkv, 3 * D.C, (long)D.B * D.R, D.C, 2 * D.C, w.qr, w.kr, D.C, K_MFMA_ROUTE_ROWS, st);
+        // one token per region: the means are the (bf16) tokens themselves, so Q^r | K^r is the plain projection of X
+        // with float32 results: no pooling, no split.  The same product as in wide_forward (a sum's order does not
+        // depend on the tile), so that both decide on the same bits
+        rc = gemm(X, Wqkv, 3 * D.C, (long)D.B * D.R, D.C, 2 * D.C, GemmOut{{w.q, w.k, nullptr}, D.C, {w.qr, w.kr}, nullptr, nullptr, 0}, nullptr,
+                  K_MFMA_ROUTE_ROWS, st);
     } else {
         launch_pool(D, X, w, GemmRows{}, st);
         rc = gemm_regions(region_job(D, w), Wqkv, 3 * D.C, D.C, K_MFMA_ROUTE_ROWS, st);
