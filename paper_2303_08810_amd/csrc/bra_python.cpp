@@ -51,29 +51,28 @@ const at::Tensor &need(PyObject *o)
     return *t;
 }
 
+// ints and what converts to one without loss (numpy integers, anything with __index__); no floats, no strings
 int integer(PyObject *o)
 {
-    const long v = PyLong_AsLong(o);
-    if (v == -1 && PyErr_Occurred()) {
-        // numpy integers and other objects with __index__ / __int__
-        PyErr_Clear();
-        PyObject *i = PyNumber_Long(o);
-        if (!i) throw Raised{};
-        const long w = PyLong_AsLong(i);
-        Py_DECREF(i);
-        if (w == -1 && PyErr_Occurred()) throw Raised{};
-        return (int)w;
-    }
+    PyObject *i = PyNumber_Index(o);
+    if (!i) throw Raised{};
+    const long v = PyLong_AsLong(i);
+    Py_DECREF(i);
+    if (v == -1 && PyErr_Occurred()) throw Raised{};
     return (int)v;
 }
 
-float scale_of(PyObject *o)
+// what float() takes
+double real(PyObject *o)
 {
-    if (o == Py_None) return 0.f;
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw Raised{};
-    return (float)v;
+    PyObject *f = PyNumber_Float(o);
+    if (!f) throw Raised{};
+    const double v = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
+    return v;
 }
+
+float scale_of(PyObject *o) { return o == Py_None ? 0.f : (float)real(o); }
 
 int dtype_of(const at::Tensor &X)
 {
@@ -95,6 +94,7 @@ void same_kind(const at::Tensor &t, const at::Tensor &X)
 bra_shape layer_shape(const at::Tensor &X, const at::Tensor &Wqkv, const at::Tensor *Wo, const at::Tensor *Wlce, int S,
                       int k, int heads, PyObject *scale, PyObject *path)
 {
+    const float scale_value = scale_of(scale);
     if (X.dim() != 4) value_error("X must be [B, H, W, C]");
     const int64_t C = X.size(3);
     same_kind(X, X);
@@ -107,7 +107,7 @@ bra_shape layer_shape(const at::Tensor &X, const at::Tensor &Wqkv, const at::Ten
     for (int d = 0; d < 4; ++d)
         if (X.size(d) > INT32_MAX) value_error("X is too large");
     return bra_shape{(int32_t)X.size(0), (int32_t)X.size(1), (int32_t)X.size(2), (int32_t)C, heads, S, k, dtype_of(X),
-                     scale_of(scale), integer(path)};
+                     scale_value, integer(path)};
 }
 
 void check_index(const at::Tensor *Ir, const bra_shape &s, const char *text)
@@ -354,8 +354,7 @@ PyObject *py_block_forward(PyObject *, PyObject *const *a, Py_ssize_t n)
             if (X.size(d) > INT32_MAX) value_error("X is too large");
         const bra_shape s = {(int32_t)X.size(0), (int32_t)X.size(1), (int32_t)X.size(2), (int32_t)C, integer(a[4]), integer(a[2]),
                              integer(a[3]), dtype_of(X), scale_of(a[6]), integer(a[9])};
-        const double eps = PyFloat_AsDouble(a[5]);
-        if (eps == -1.0 && PyErr_Occurred()) throw Raised{};
+        const double eps = real(a[5]);
         at::Tensor own, Xout, Ir;
         const at::Tensor *Ir_in = tensor(a[7]), *ws = tensor(a[10]), *out = tensor(a[11]);
         if (!ws) {

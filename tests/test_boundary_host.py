@@ -5,7 +5,9 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
+import torch
 
 import paper_2303_08810_amd as bra
 
@@ -168,6 +170,30 @@ def test_backward_workspace_query_and_error_codes():
     assert L.bra_backward(ctypes.byref(shape), *args, 16, None) == -5          # workspace too small
     args[4] = None                                                              # Ir missing
     assert L.bra_backward(ctypes.byref(shape), *args, 1 << 30, None) == -1
+
+
+@pytest.mark.parametrize("place", ["S", "k", "heads"])
+def test_binding_takes_integers_only(place):
+    """Sizes are ints or convert to one by __index__; the tensors (not on a GPU here) are refused after that."""
+    X, Wqkv = torch.zeros(1, 14, 14, 64), torch.zeros(64, 192)
+    Wo, Wlce = torch.zeros(64, 64), torch.zeros(64, 5, 5)
+    calls = (lambda **kw: bra.bra_forward(X, Wqkv, Wo, Wlce, **kw), lambda **kw: bra.bra_route(X, Wqkv, **kw),
+             lambda **kw: bra.bra_forward_padded(X, Wqkv, Wo, Wlce, **kw))
+    for call in calls:
+        for bad in (7.9, 7.0, "7", None, np.float32(7)):
+            with pytest.raises(TypeError):
+                call(**{**dict(S=7, k=4, heads=2), place: bad})
+        for good in (7, np.int32(7), np.array(7), torch.tensor(7)):
+            with pytest.raises(ValueError):
+                call(**{**dict(S=7, k=4, heads=2), place: good})
+
+
+def test_binding_takes_what_float_takes():
+    X, Wqkv, Wo, Wlce = torch.zeros(1, 14, 14, 64), torch.zeros(64, 192), torch.zeros(64, 64), torch.zeros(64, 5, 5)
+    for scale, error in ((0.5, ValueError), (1, ValueError), ("0.5", ValueError), (torch.tensor(0.5), ValueError),
+                         ([0.5], TypeError)):
+        with pytest.raises(error, match="float|one GPU"):
+            bra.bra_forward(X, Wqkv, Wo, Wlce, 7, 4, 2, scale=scale)
 
 
 def test_missing_library_fails_loudly(monkeypatch, tmp_path):
