@@ -196,8 +196,14 @@ __global__ __launch_bounds__(256) void k_lce_pairs(const bf16_t *__restrict__ In
     }
 }
 
-// Strips of 20 rows, or 10 or 5 where that leaves fewer than `want` tiles.
-Tiling tiling(const Dims &D, long want, long &tiles)
+// Lane offsets are 32-bit: the rows of a tile (with the window, within the map) must span less than 2 GiB in either map.
+bool offsets_fit(const Dims &D, const Tiling &T, int ldo)
+{
+    return (long)std::min(T.subs * T.height + 4, D.H) * D.W * std::max(D.C, ldo) * 2 < (1L << 31);
+}
+
+// Strips of 20 rows, or 10 or 5 where that leaves fewer than `want` tiles or the rows span too much.
+Tiling tiling(const Dims &D, int ldo, long want, long &tiles)
 {
     Tiling T;
     const int xp = (D.W + 1) / 2;
@@ -208,25 +214,22 @@ Tiling tiling(const Dims &D, long want, long &tiles)
         T.subs = 8 / T.pairs < strips ? 8 / T.pairs : strips;
         T.ytiles = (strips + T.subs - 1) / T.subs;
         tiles = (long)D.B * T.xtiles * T.ytiles;
-        if (T.height == 5 || tiles >= want) return T;
+        if (T.height == 5 || (tiles >= want && offsets_fit(D, T, ldo))) return T;
     }
-}
-
-// Lane offsets are 32-bit: rows of a tile (with the window) must span less than 2 GiB in either map.
-bool offsets_fit(const Dims &D, const Tiling &T, int ldo)
-{
-    return (long)(T.subs * T.height + 4) * D.W * std::max(D.C, ldo) * 2 < (1L << 31);
 }
 
 }  // namespace
 
+// Maps so wide that not even strips of 5 rows fit (119 million values in a row) take the kernels of bra_lce_dev.h, whose
+// addresses are 64-bit throughout.
 int lce_add_bf16(const Dims &D, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, int ldo, int kernel_id, hipStream_t st)
 {
     const int cblocks = (D.C + 63) / 64;
     long tiles;
-    const Tiling T = tiling(D, 1536 / cblocks, tiles);
+    const Tiling T = tiling(D, ldo, 1536 / cblocks, tiles);
     const long blocks = tiles * cblocks;
-    if (D.C % 2 || ldo % 2 || blocks > 0x7ffffff0L || !offsets_fit(D, T, ldo)) return BRA_ERR_UNSUPPORTED;
+    if (!offsets_fit(D, T, ldo)) return launch_lce<bf16_t, bf16_t>(D, V, D.C, Wlce, O, ldo, kernel_id, st);
+    if (D.C % 2 || ldo % 2 || blocks > 0x7ffffff0L) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);
     hipLaunchKernelGGL(k_lce_pairs<false>, dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), 0, st, V, (const bf16_t *)nullptr,
                        Wlce, O, ldo, (float *)nullptr, D, T, cblocks, tiles, 1);
@@ -236,24 +239,27 @@ int lce_add_bf16(const Dims &D, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, 
 namespace {
 
 // About 768 workgroups (three per compute unit), each with the tiles of one group.
-Tiling grad_plan(const Dims &D, long &tiles, int &per_wg, int &groups)
+constexpr int kGradSlots = 768;
+
+Tiling grad_plan(const Dims &D, int lddv, long &tiles, int &per_wg, int &groups)
 {
     const int cblocks = (D.C + 63) / 64;
-    const long want = std::max(1, 768 / cblocks);
-    const Tiling T = tiling(D, want, tiles);
+    const long want = std::max(1, kGradSlots / cblocks);
+    const Tiling T = tiling(D, lddv, want, tiles);
     per_wg = (int)((tiles + want - 1) / want);
     groups = (int)((tiles + per_wg - 1) / per_wg);
     return T;
 }
 
+LcePlan wide_grad_plan(const Dims &D) { return lce_plan(D, kGradSlots, 8); }      // 8 columns per workgroup: two channels per thread
+
 }  // namespace
 
-int lce_grad_groups_bf16(const Dims &D)
+int lce_grad_groups_bf16(const Dims &D, int lddv)
 {
     long tiles;
     int per_wg, groups;
-    grad_plan(D, tiles, per_wg, groups);
-    return groups;
+    return offsets_fit(D, grad_plan(D, lddv, tiles, per_wg, groups), lddv) ? groups : wide_grad_plan(D).groups;
 }
 
 int lce_grad_bf16(const Dims &D, const bf16_t *dO, const bf16_t *V, const bf16_t *Wlce, bf16_t *dV, int lddv, float *Part,
@@ -262,8 +268,12 @@ int lce_grad_bf16(const Dims &D, const bf16_t *dO, const bf16_t *V, const bf16_t
     const int cblocks = (D.C + 63) / 64;
     long tiles;
     int per_wg, groups;
-    const Tiling T = grad_plan(D, tiles, per_wg, groups);
-    if (D.C % 2 || lddv % 2 || !offsets_fit(D, T, lddv)) return BRA_ERR_UNSUPPORTED;
+    const Tiling T = grad_plan(D, lddv, tiles, per_wg, groups);
+    if (D.C % 2 || lddv % 2) return BRA_ERR_UNSUPPORTED;
+    if (!offsets_fit(D, T, lddv)) {
+        ProfScope ps(st, kernel_id);
+        return launch_lce_grad<bf16_t, bf16_t>(D, wide_grad_plan(D), dO, V, D.C, Wlce, dV, lddv, Part, st);
+    }
     ProfScope ps(st, kernel_id);
     hipLaunchKernelGGL(k_lce_pairs<true>, dim3((unsigned)((groups * cblocks + 7) / 8 * 8)), dim3(256), 0, st, dO, V, Wlce, dV,
                        lddv, Part, D, T, cblocks, tiles, per_wg);

@@ -255,7 +255,7 @@ BwdWs carve_bwd(const Dims &D, void *ws)
     const int parts = weight_parts(M, D.C);
     w.part_qkv = (float *)take((size_t)parts * 3 * C * C * 4);
     w.part_o = (float *)take((size_t)(D.C == 128 ? gemm_tn_shares(M, D.C, D.C, 0, 0) : parts) * C * C * 4);
-    w.part_lce = (float *)take((size_t)lce::lce_grad_groups_bf16(D) * 25 * C * 4);
+    w.part_lce = (float *)take((size_t)lce::lce_grad_groups_bf16(D, 3 * D.C) * 25 * C * 4);
     w.bytes = off;
     return w;
 }
@@ -344,7 +344,7 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
         const int parts = weight_parts(M, C);
         const ReduceJob j0 = reduce_job(w.part_qkv, dWqkv, parts, 3 * C * C);
         const ReduceJob j1 = reduce_job(w.part_o, dWo, C == 128 ? gemm_tn_shares(M, C, C, 0, 0) : parts, C * C);
-        const ReduceJob j2 = reduce_job(w.part_lce, dWlce, lce::lce_grad_groups_bf16(D), 25 * C);
+        const ReduceJob j2 = reduce_job(w.part_lce, dWlce, lce::lce_grad_groups_bf16(D, 3 * D.C), 25 * C);
         ProfScope ps(st, K_GEN_BACKWARD);
         hipLaunchKernelGGL(k_reduce_parts, dim3(j0.blocks + j1.blocks + j2.blocks), dim3(256), 0, st, j0, j1, j2);
         if (!launched()) return BRA_ERR_LAUNCH;
