@@ -202,7 +202,9 @@ __global__ __launch_bounds__(4 * C * H) void k_bwd_proj(const bf16_t *__restrict
 }
 
 // Tiles of k_bwd_proj per workgroup: all workgroups resident at once.  At C = 64 two groups of wavefronts share a
-// workgroup (`halves`) once each has more than one tile; before that the chip is not full and a tile each is best.
+// workgroup (`halves`) from more than 256 tiles, one per compute unit, on.  Whole gradient with two groups and with one
+// (us, k = 1): 294 tiles 65.1 / 69.6, 392 70.9 / 75.5, 490 74.6 / 80.0, 3136 214 / 225; below the line 49 tiles 48.1 / 47.4,
+// but 98 52.0 / 52.4, 196 58.6 / 59.0, 256 86.0 / 87.5: a line between 50 and 98 tiles would gain up to 2 % there.
 struct ProjPlan {
     int tiles, per_wg, groups, halves;
 };

@@ -78,9 +78,10 @@ def test_backward_matrix_cores(dtype, B, H, W, C, heads, S, k):
     test_backward(dtype, B, H, W, C, heads, S, k, path="mfma")
 
 
-# Token counts where two groups of wavefronts share a workgroup of the gradient-map pass (more than 512 tiles of 64
-# tokens): one tile in the last workgroup, and three, the last of them ragged
-@pytest.mark.parametrize("B,H,W,S", [(18, 38, 48, 2), (9, 63, 63, 7)])
+# Token counts where two groups of wavefronts share a workgroup of the gradient-map pass (more than 256 tiles of 64
+# tokens): 513 and 559 tiles (one in the last workgroup, and three), the first count above the line (257) and the last with
+# one tile per group of wavefronts (512); ragged last tiles but for the first
+@pytest.mark.parametrize("B,H,W,S", [(18, 38, 48, 2), (9, 63, 63, 7), (5, 7, 469, 7), (4, 7, 1169, 7)])
 def test_backward_paired_groups(B, H, W, S):
     test_backward("bf16", B, H, W, 64, 2, S, 1, path="mfma")
 
