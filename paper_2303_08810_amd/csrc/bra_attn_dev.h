@@ -66,20 +66,29 @@ __device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, float &l,
 
 // A direct load of 16 bytes per lane to 1024 consecutive bytes of LDS (l: the same for all lanes) that the compiler does
 // not count: it would wait for all outstanding ones before the next LDS read, those of the buffer in flight among them.
-// The caller waits (s_waitcnt vmcnt) before it reads the buffer.  M0 is the instruction's own here: nothing else in the
-// kernels that use this sets it.
+// The caller waits (s_waitcnt vmcnt) before it reads the buffer, and calls lds_reads_done() before it refills one.
+// M0 is declared as overwritten, so that the compiler keeps no value of its own there across the load (it warns that it does
+// not restore the register, and need not).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds_untracked(const bf16_t *g, bf16_t *l)
 {
     const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) bf16_t *)l);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(g) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(g) : "memory", "m0");
 }
 
 // Four bytes per lane to 256 consecutive bytes of LDS, likewise.
 __device__ __forceinline__ void load4_to_lds_untracked(const float *g, float *l)
 {
     const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) float *)l);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(at), "v"(g) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(at), "v"(g) : "memory", "m0");
 }
+
+#pragma clang diagnostic pop
+
+// The wavefront's own reads of LDS have arrived in its registers: the compiler places the waits for them by their uses, and
+// does not know that a direct load is about to overwrite what they read.
+__device__ __forceinline__ void lds_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 }  // namespace mfma
 }  // namespace bra

@@ -128,7 +128,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
     auto request = [&](int local) {
         const int blk = STEP * local + start;
         bf16_t *Ks = mine + (local % 2) * R::buf, *Vs = Ks + KB * 64;
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // the buffer's last reads are done
+        lds_reads_done();
 #pragma unroll
         for (int u = 0; u < R::per_wave / 8; ++u) {
             const int row = (SHARED ? 16 * wave : 0) + 8 * u + lane / 8, key = min(KB * blk + row, kn - 1), p = divide(key, n, n_inv);
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
             const int r = min(KB * blk + row, rows - 1), p = divide(r, n, n_inv);
             return list[p] + at.slot(r - p * n);
         };
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // the buffer's last reads are done
+        lds_reads_done();
 #pragma unroll
         for (int u = 0; u < R::per_wave / 8; ++u) {
             const int row = (SHARED ? 16 * wave : 0) + 8 * u + lane / 8;

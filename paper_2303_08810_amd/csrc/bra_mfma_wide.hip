@@ -280,6 +280,7 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
     // direct loads: 8 rows of 8 pieces each
     auto request = [&](int k0, bf16_t *S) {
         bf16_t *Ks = S + wave * 2 * KB * 64, *Vs = Ks + KB * 64;
+        lds_reads_done();
 #pragma unroll
         for (int u = 0; u < KB / 8; ++u) {
             const int row = 8 * u + lane / 8, key = min(k0 + row, kn - 1), p = fast_div(key, n_inv);
