@@ -189,9 +189,9 @@ int bra_block_forward(const bra_shape *shape, int32_t hidden, float eps, const v
  *                     S*S*k <= 4096 routing entries per image: matrix-core kernels with bf16
  *                     operands and float32 sums; Q, K, V, dO, P, dS, dQ, dK, dV are rounded to
  *                     bf16 between the products.  No atomic adds: dK, dV are summed per key
- *                     region in registers, the weight gradients from per-workgroup partial sums in
- *                     a fixed order, so a repeat gives the same bits as long as no key region is
- *                     routed to by more than 256 index entries of one image.
+ *                     region in registers in the order of the index entries, the weight gradients
+ *                     from per-workgroup partial sums in a fixed order, so a repeat gives the
+ *                     same bits.
  *   BRA_PATH_GENERIC  any dtype, heads up to 64 channels wide: float32 kernels, float32 intermediates.
  *                     No atomic adds either: repeats give the same bits.
  *   BRA_PATH_AUTO     the first where it applies, else the second.

@@ -14,9 +14,10 @@
 // 16-byte pieces are exchanged (piece c of row r at c ^ r % 8), so that row reads and transposing reads meet different banks.
 //
 // Measured, query side + key side (us; before: kernels that staged rows through registers and formed S and dP without
-// their statistics): 11 x 42 x 42 x 256, k = 6 (36 tokens per region): 77 + 66 -> 50 + 46; 25 x 8 x 16 x 768 with heads
-// of 64, k = 36 (2 tokens): 215 + 172 -> 66 + 89; 12 x 112 x 120 x 64, k = 1 (210 tokens): 112 + 105 -> 68 + 78;
-// 64 x 56 x 56 x 64, k = 1: 36 + 49 -> 37 + 41, there bound by memory (150 MB per kernel).
+// their statistics): 11 x 42 x 42 x 256, k = 6 (36 tokens per region): 77 + 66 -> 54 + 44; 25 x 8 x 16 x 768 with heads
+// of 64, k = 36 (2 tokens): 215 + 172 -> 65 + 88; 12 x 112 x 120 x 64, k = 1 (210 tokens): 112 + 105 -> 68 + 75;
+// 64 x 56 x 56 x 64, k = 1: 36 + 49 -> 39 + 41, there bound by memory (150 MB per kernel).  D = dO . O instead of the sum
+// over the keys took 47, 65, 68 and 37 us on the query side, with the rounding of the bf16 weights in D.
 #include "bra_attn_dev.h"
 #include "bra_mfma_bwd_attn.h"
 

@@ -75,8 +75,10 @@ __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X,
 // the other is worked on; 16-byte pieces are exchanged so that K's row reads (piece c of row r at c ^ r % 8) and V's
 // transposing reads (c ^ 4 (r / 2 % 2)) meet different banks.  Queries past the end of the region and keys past k n
 // repeat the last one and are masked.
-// A score costs a 2^x (quarter rate), an addition and half a conversion in vector instructions.  2 x 208 x 304 x 64,
-// 16 x 16 regions, k = 4: two query tiles per wavefront (152 registers) for regions that fill them, else one.
+// Bound by vector issue: 2 x 208 x 304 x 64, 16 x 16 regions, k = 4 (250 M scores) takes 66 us, in which the vector ALUs
+// issue in 73 % of the cycles and the matrix cores work in 25 %.  Of 5.2 vector instructions per score 2.5 are its 2^x,
+// its addition to the denominator and half a conversion; with maxima instead of additions and denominators from a product
+// it took 68 us.  One query tile per wavefront instead of two: 74 us (4 x 64 x 64 x 384, heads of 64, k = 4: 45 for 39).
 template <int HD, int NQ>
 __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles)
 {
@@ -447,8 +449,8 @@ void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t 
 
 void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
 {
-    // two query tiles per wavefront (every K and V operand read serves both) where the wider tile leaves no more than an
-    // eighth of its queries empty beyond the narrow one and there are workgroups enough
+    // two query tiles per wavefront (every K and V operand read serves both; measured above) where the wider tile leaves no
+    // more than an eighth of its queries empty beyond the narrow one and there are workgroups enough
     const int t64 = (D.n + 63) / 64, t128 = (D.n + 127) / 128;
     if (t128 * 128 * 8 <= t64 * 64 * 9 && (long)D.B * D.R * t128 * (D.C / 64) >= 512) launch_attn_gen_t<2>(D, A, O, st);
     else launch_attn_gen_t<1>(D, A, O, st);
