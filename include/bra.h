@@ -2,7 +2,7 @@
  * libbra -- forward pass of Bi-Level Routing Attention (BRA) on AMD MI355X (gfx950).
  *
  * C ABI.  Every data pointer is CALLER-OWNED DEVICE memory (dense, row-major, no
- * strides); `shape` and `out_bytes` are host pointers.  The compute entry points never
+ * strides, 16-byte aligned: not checked); `shape` and `out_bytes` are host pointers.  The compute entry points never
  * allocate, free or synchronise: scratch memory comes from `ws` (size from
  * bra_workspace_bytes, 256-byte aligned) and all work is enqueued on `hip_stream`
  * (a hipStream_t passed as void*; NULL = the default stream).  Outputs are valid

@@ -72,3 +72,66 @@ def test_backward_row_sums(B, rh, rw, S, C, heads):
     d = C // heads
     dQ = -8.0 * math.log(2.0) * 769 * d * 255 / 1024 / 1024
     assert torch.allclose(dW[1, 0, ::d], torch.full((heads,), B * 512 * dQ, device="cuda"), rtol=2.1e-3)
+
+
+# The reference of the exponentials has to move from block to block: every 16 keys the scores go up by `step` powers of two
+# (beyond the range of float32 for 200), down again, or up and down.  All weights are powers of two, so nothing but the
+# result is rounded.
+def steps(B, rh, rw, S, k, C, heads, step, order):
+    n, R = rh * rw, S * S
+    g = torch.Generator(device="cuda").manual_seed(9990 + n)
+    T = torch.randint(-3, 4, (B, R, n, C), generator=g, device="cuda").float()      # tokens by region
+    T[..., 0], T[..., 1] = 0.0, 1.0
+    group = torch.arange(k * n, device="cuda") // 16
+    top = int(group[-1])
+    rank = {"up": group, "down": top - group, "zigzag": torch.where(group % 2 == 0, group, top - group)}[order]
+    T[:, :k, :, 0] = rank.view(k, n).float()
+    X = T.view(B, S, S, rh, rw, C).permute(0, 1, 3, 2, 4, 5).reshape(B, S * rh, S * rw, C).contiguous()
+    d = C // heads
+    Wqkv = torch.zeros(C, 3 * C, device="cuda")
+    Wqkv[1, 0:C:d] = 1.0
+    Wqkv[0, C:2 * C:d] = step
+    channel = torch.arange(C, device="cuda")
+    Wqkv[2 + channel % (C - 2), 2 * C + channel] = 1.0
+    Ir = torch.arange(k, dtype=torch.int32, device="cuda").expand(B, R, k).contiguous()
+    args = [t.bfloat16() for t in (X, Wqkv, torch.eye(C, device="cuda"), torch.zeros(C, 5, 5, device="cuda"))]
+    V = T[:, :k].reshape(B, k * n, C)[..., 2 + channel % (C - 2)].double()
+    P = torch.exp2((rank - rank.max()).double() * step)
+    return args, Ir, V, P / P.sum()
+
+
+@pytest.mark.parametrize("order", ["up", "down", "zigzag"])
+@pytest.mark.parametrize("step", [4, 10, 200])
+@pytest.mark.parametrize("B,rh,rw,S,k,C,heads", [(1, 2, 7, 7, 20, 192, 6), (2, 5, 5, 5, 11, 192, 3), (1, 8, 8, 4, 7, 192, 3),
+                                                 (19, 10, 11, 3, 7, 192, 6)])
+def test_moving_reference(B, rh, rw, S, k, C, heads, step, order):
+    (X, Wqkv, Wo, Wlce), Ir, V, P = steps(B, rh, rw, S, k, C, heads, step, order)
+    Y = bra.bra_forward(X, Wqkv, Wo, Wlce, S, k, heads, Ir_in=Ir, scale=math.log(2.0), path="mfma")
+    ref = (P[None, :, None] * V).sum(1)
+    err = (Y.double().view(B, -1, C) - ref[:, None]).abs() / (ref[:, None].abs() + 2.0 ** -12)
+    assert float(err.max()) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("order", ["up", "zigzag"])
+@pytest.mark.parametrize("step", [4, 10, 200])
+@pytest.mark.parametrize("B,rh,rw,S,C,heads", [(6, 2, 7, 7, 64, 2), (6, 5, 5, 5, 64, 1), (1, 5, 5, 5, 64, 2), (3, 8, 8, 4, 128, 4),
+                                               (57, 10, 11, 3, 64, 2)])
+def test_moving_reference_backward(B, rh, rw, S, C, heads, step, order):
+    k = min(7, S * S)
+    (X, Wqkv, Wo, Wlce), Ir, V, P = steps(B, rh, rw, S, k, C, heads, step, order)
+    dY = torch.randint(-2, 3, X.shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(9991)).bfloat16()
+    dW = bra.bra_backward(X, Wqkv, Wo, Wlce, Ir, dY, S, heads, scale=math.log(2.0), path="mfma")[1].double()
+    # every query has the same probabilities: dV = P^T dO; dS = P (dP - sum P dP), dK is its sum in channel 0 of each head
+    d, n = C // heads, rh * rw
+    g = dY.double().view(B, -1, heads, d).sum(1)                                    # dO summed over the queries
+    dP = torch.einsum("bhd,bkhd->bkh", g, V.view(B, -1, heads, d))
+    dS = P[None, :, None] * (dP - torch.einsum("k,bkh->bh", P, dP)[:, None])
+    keys = X.view(B, S, rh, S, rw, C).permute(0, 1, 3, 2, 4, 5).reshape(B, S * S, n, C)[:, :k].reshape(B, k * n, C).double()
+    want_k = math.log(2.0) * torch.einsum("bkc,bkh->ch", keys, dS)
+    want_v = torch.einsum("bkc,k,bhd->chd", keys, P, g).reshape(C, C)
+    # Rows 0 and 1 (the group's number, up to 48, and the constant) are left out for dK: sum_t dK[t] is 0 and only the
+    # roundings of dK, times the number, are left of it.  Else as in test_gpu_backward.py, 1e-2 of the largest element of a
+    # block: an element is a sum over the keys of products that carry four bf16 roundings
+    want_k, got_k, got_v = want_k[2:], dW[2:, C:2 * C:d], dW[:, 2 * C:]
+    assert float((got_v - want_v).abs().max()) <= 1e-2 * float(want_v.abs().max())
+    assert float((got_k - want_k).abs().max()) <= 1e-2 * float(want_k.abs().max())
