@@ -64,23 +64,52 @@ __device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, float &l,
     if (dp) *d += dsum;
 }
 
-// A direct load of 16 bytes per lane to 1024 consecutive bytes of LDS (l: the same for all lanes) that the compiler does
+// Rows 16 t + i of a buffer's map as operands: piece p (rows of 64 elements; their 16-byte pieces lie exchanged, piece c of
+// row r at c ^ r % 8).
+__device__ __forceinline__ bf16x8 row_operand(const bf16_t *T, int row, int piece)
+{
+    return *(const bf16x8 *)(T + row * 64 + 8 * (piece ^ (row % 8)));
+}
+
+// Columns col0 + i of rows row0 .. row0 + 31 (contraction slots in the accumulator order: 4 g .. 4 g + 3, then 16 further).
+__device__ __forceinline__ bf16x8 column_operand(const bf16_t *T, int row0, int col0, int g, int i)
+{
+    u32x2 r[2];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        const int row = row0 + 16 * half + 4 * g + i / 4, piece = col0 / 8 + (i % 4) / 2;
+        r[half] = __builtin_bit_cast(u32x2, lds_read_tr16(T + row * 64 + 8 * (piece ^ (row % 8)) + 4 * (i % 2)));
+    }
+    return __builtin_bit_cast(bf16x8, u32x4{r[0][0], r[0][1], r[1][0], r[1][1]});
+}
+
+// Address in LDS, as the direct loads take it; the same for all lanes.
+__device__ __forceinline__ unsigned lds_address(const void *l)
+{
+    return __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(const __attribute__((address_space(3))) char *)l);
+}
+
+// A direct load of 16 bytes per lane to the 1024 consecutive bytes from LDS address `at` on that the compiler does
 // not count: it would wait for all outstanding ones before the next LDS read, those of the buffer in flight among them.
 // The caller waits (s_waitcnt vmcnt) before it reads the buffer, and calls lds_reads_done() before it refills one.
 // M0 is declared as overwritten, so that the compiler keeps no value of its own there across the load (it warns that it does
 // not restore the register, and need not).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void load_to_lds_untracked(const bf16_t *g, bf16_t *l)
+__device__ __forceinline__ void load_to_lds_untracked(const bf16_t *g, unsigned at)
 {
-    const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) bf16_t *)l);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(g) : "memory", "m0");
 }
 
-// Four bytes per lane to 256 consecutive bytes of LDS, likewise.
-__device__ __forceinline__ void load4_to_lds_untracked(const float *g, float *l)
+// The same from `offset` bytes behind a base that is the same for all lanes.
+__device__ __forceinline__ void load_to_lds_untracked(const bf16_t *base, unsigned offset, unsigned at)
 {
-    const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) float *)l);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(at), "v"(offset), "s"(base) : "memory", "m0");
+}
+
+// Four bytes per lane to 256 consecutive bytes of LDS, likewise.
+__device__ __forceinline__ void load4_to_lds_untracked(const float *g, unsigned at)
+{
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(at), "v"(g) : "memory", "m0");
 }
 
@@ -89,6 +118,60 @@ __device__ __forceinline__ void load4_to_lds_untracked(const float *g, float *l)
 // The wavefront's own reads of LDS have arrived in its registers: the compiler places the waits for them by their uses, and
 // does not know that a direct load is about to overwrite what they read.
 __device__ __forceinline__ void lds_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Rows of a list of regions (origin by origin, n slots each), as a thread meets them: U rows `apart` from each other, all of
+// them `step` further on with every advance().  The region and the slot are kept and carried along, and two tables in LDS
+// give the token: divisions by n and by the region's width for every row were half of the vector instructions of
+// k_attn_rows, and a fifth of k_attn_gen's (8 x 32 x 32 x 768, 12 regions of 16 tokens: whole layer 111.6 -> 109.4 us; gradients
+// 25 x 8 x 16 x 768, k = 36: 267 -> 258 us, 11 x 42 x 42 x 256, k = 6: 212 -> 209, 12 x 112 x 120 x 64, k = 1: 272 -> 267).
+// Rows past the end of the list meet its last region.
+template <int U>
+struct RowWalk {
+    int p[U], s[U], n, step_p, step_s;
+    __device__ __forceinline__ void start(int row, int apart, int step, int n_, float n_inv)
+    {
+        n = n_;
+        step_p = divide(step, n, n_inv);
+        step_s = step - step_p * n;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            p[u] = divide(row + apart * u, n, n_inv);
+            s[u] = row + apart * u - p[u] * n;
+        }
+    }
+    __device__ __forceinline__ void advance()
+    {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int up = s[u] + step_s, wrapped = up - n;
+            p[u] += step_p + (wrapped >= 0 ? 1 : 0);
+            s[u] = (int)min((unsigned)up, (unsigned)wrapped);
+        }
+    }
+    __device__ __forceinline__ void retreat()
+    {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int down = s[u] - step_s, wrapped = down + n;
+            p[u] -= step_p + (down < 0 ? 1 : 0);
+            s[u] = (int)min((unsigned)down, (unsigned)wrapped);
+        }
+    }
+    __device__ __forceinline__ int token(int u, const int *origins, int last, const int *slots) const
+    {
+        return origins[min(p[u], last)] + slots[s[u]];
+    }
+};
+
+// What the walk takes: a slot table of 4 KB at most, token numbers of 24 bits and byte offsets of 32 within an image.
+constexpr int kWalkMaxSlots = 1024;
+inline bool walk_ok(const Dims &D)
+{
+    return D.n <= kWalkMaxSlots && D.N < (1 << 24) && (long)D.N * D.C * 2 < (1L << 32);
+}
+
+// Byte offset of a token's row, `lane_bytes` within it.
+__device__ __forceinline__ unsigned row_offset(int token, int C, unsigned lane_bytes) { return __umul24((unsigned)token, 2u * (unsigned)C) + lane_bytes; }
 
 }  // namespace mfma
 }  // namespace bra

@@ -38,24 +38,6 @@ struct Rows {
     static constexpr int bufs = 2 * (SHARED ? 1 : 4);          // two per workgroup or wavefront
 };
 
-// Rows 16 t + i of a buffer's map as operands: piece p.
-__device__ __forceinline__ bf16x8 row_operand(const bf16_t *T, int row, int piece)
-{
-    return *(const bf16x8 *)(T + row * 64 + 8 * (piece ^ (row % 8)));
-}
-
-// Columns col0 + i of rows row0 .. row0 + 31 (contraction slots in the accumulator order: 4 g .. 4 g + 3, then 16 further).
-__device__ __forceinline__ bf16x8 column_operand(const bf16_t *T, int row0, int col0, int g, int i)
-{
-    u32x2 r[2];
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        const int row = row0 + 16 * half + 4 * g + i / 4, piece = col0 / 8 + (i % 4) / 2;
-        r[half] = __builtin_bit_cast(u32x2, lds_read_tr16(T + row * 64 + 8 * (piece ^ (row % 8)) + 4 * (i % 2)));
-    }
-    return __builtin_bit_cast(bf16x8, u32x4{r[0][0], r[0][1], r[1][0], r[1][1]});
-}
-
 // The workgroup's or wavefront's place in the grid: (image, region, tile of tokens, group of 64 channels); false: none.
 template <Mode MODE>
 __device__ __forceinline__ bool place(const Dims &D, int tiles, int items, int wave, int &b, int &reg, int &tile, int &cg)
@@ -76,7 +58,7 @@ __device__ __forceinline__ bool place(const Dims &D, int tiles, int items, int w
 // the weights that entered O).  The second goes over the blocks backwards, so that the
 // last two are still in LDS (up to 128 or 64 routed keys: nothing is read twice).
 template <int HD, int NQ, Mode MODE>
-__global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_attn_bwd_q(AttnBwdArgs A, Dims D, int tiles, int items)
+__global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_attn_bwd_q(AttnBwdArgs A, Dims D, int tiles, int items, int walks)
 {
     using R = Rows<MODE>;
     constexpr bool SHARED = R::SHARED, SPLIT = MODE == kSplit;
@@ -84,7 +66,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
     __shared__ __attribute__((aligned(16))) bf16_t lds[R::bufs * R::buf];
     constexpr int kPart = 64 * (3 + 4 * NDT);    // SPLIT: m, l, D and the sums of a wavefront, one query tile and head
     __shared__ __attribute__((aligned(16))) float sums[SPLIT ? NQ * HPW * 4 * kPart : 4];
-    extern __shared__ int origin_tables[];       // [k] or [4][k]: first token of the routed regions
+    extern __shared__ int origin_tables[];       // [k] or [4][k]: first token of the routed regions; with `walks` [n] or [4][n]: tokens of a region's slots
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C = D.C, n = D.n, kn = D.kn;
     int b, reg, tile, cg;
@@ -93,7 +75,9 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
     const float n_inv = 1.0f / (float)n;
     const size_t img = (size_t)b * D.N * C + 64 * cg;
     bf16_t *mine = lds + (SHARED ? 0 : wave * 2 * R::buf);
-    int *origins = origin_tables + (SHARED ? 0 : wave * D.k);
+    int *origins = origin_tables + (SHARED ? 0 : wave * D.k), *slots = origin_tables + (SHARED ? D.k : 4 * D.k + wave * n);
+    if (walks)
+        for (int t = SHARED ? tid : lane; t < n; t += SHARED ? 256 : kWave) slots[t] = at.slot(t);
     for (int p = SHARED ? tid : lane; p < D.k; p += SHARED ? 256 : kWave)
         origins[p] = at.origin(region_index(A.Ir[((size_t)b * D.R + reg) * D.k + p], D.R));
     const int q0 = SHARED ? 64 * NQ * tile + 16 * NQ * wave : 16 * NQ * tile;
@@ -126,28 +110,44 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
     // blocks of this wavefront: local block s is block STEP s + start
     constexpr int STEP = SPLIT ? 4 : 1;
     const int start = SPLIT ? wave : 0, nb = ((kn + KB - 1) / KB - start + STEP - 1) / STEP;
-    auto request = [&](int local) {
-        const int blk = STEP * local + start;
-        bf16_t *Ks = mine + (local % 2) * R::buf, *Vs = Ks + KB * 64;
+    // The walk stands at the block to be requested next: upwards in the first sweep, back in the second.
+    constexpr int LOADS = R::per_wave / 8;
+    RowWalk<LOADS> walk;
+    walk.start(KB * start + (SHARED ? 16 * wave : 0) + lane / 8, 8, KB * STEP, n, n_inv);
+    const unsigned piece = 16 * ((lane % 8) ^ (lane / 8)), my_lds = lds_address(mine) + (SHARED ? 2048 * wave : 0);
+    auto request = [&](int local, bool back) {
+        const unsigned to = my_lds + (local % 2) * (2 * R::buf);
         lds_reads_done();
+        if (back) walk.retreat();
 #pragma unroll
-        for (int u = 0; u < R::per_wave / 8; ++u) {
-            const int row = (SHARED ? 16 * wave : 0) + 8 * u + lane / 8, key = min(KB * blk + row, kn - 1), p = divide(key, n, n_inv);
-            const size_t e = img + (size_t)(origins[p] + at.slot(key - p * n)) * C + 8 * ((lane % 8) ^ (lane / 8));
-            load_to_lds_untracked(A.K + e, Ks + (row - lane / 8) * 64);
-            load_to_lds_untracked(A.V + e, Vs + (row - lane / 8) * 64);
+        for (int u = 0; u < LOADS; ++u) {
+            if (MODE == kWaves || walks) {
+                const unsigned off = row_offset(walk.token(u, origins, D.k - 1, slots), C, piece);
+                load_to_lds_untracked(A.K + img, off, to + 1024 * u);
+                load_to_lds_untracked(A.V + img, off, to + KB * 128 + 1024 * u);
+            } else {
+                const int row = (SHARED ? 16 * wave : 0) + 8 * u + lane / 8, key = min(KB * (STEP * local + start) + row, kn - 1), p = divide(key, n, n_inv);
+                const size_t e = img + (size_t)(origins[p] + at.slot(key - p * n)) * C + piece / 2;
+                load_to_lds_untracked(A.K + e, to + 1024 * u);
+                load_to_lds_untracked(A.V + e, to + KB * 128 + 1024 * u);
+            }
         }
+        if (!back) walk.advance();
     };
     // Step s works on block s of the first sweep, then backwards; the first two blocks of the second sweep are in place.
     // On return the block of step s is in LDS and that of step s + 1 requested.
     auto block_of = [&](int s) { return s < nb ? s : 2 * nb - 1 - s; };
     auto advance = [&](int s) {
         const bool more = s + 1 < 2 * nb && (s + 1 < nb || s + 1 > nb + 1);
+        if (s + 1 == nb + 2) {                   // from behind the last block to the one before the two that are in place
+            walk.retreat();
+            walk.retreat();
+        }
         if (SHARED) {
             arrive_barrier();
-            if (more) request(block_of(s + 1));
+            if (more) request(block_of(s + 1), s >= nb);
         } else if (more) {
-            request(block_of(s + 1));
+            request(block_of(s + 1), s >= nb);
             asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
         } else {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
         }
     };
     if (!SPLIT || nb > 0) {
-        request(0);
+        request(0, false);
         advance(0);
         if (!idle) forward(0, std::true_type{});
     }
@@ -434,7 +434,7 @@ __device__ __forceinline__ int list_of_group(const int32_t *__restrict__ irb, in
 }
 
 template <int HD, int NK, Mode MODE>
-__global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_attn_bwd_kv(AttnBwdArgs A, Dims D, int tiles, int items)
+__global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_attn_bwd_kv(AttnBwdArgs A, Dims D, int tiles, int items, int walks)
 {
     using R = Rows<MODE>;
     constexpr bool SHARED = R::SHARED, SPLIT = MODE == kSplit;
@@ -445,6 +445,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
     __shared__ __attribute__((aligned(16))) float sums[SPLIT ? NK * 4 * 2048 : 4];
     __shared__ int lists[SHARED ? kListShared : 4 * kListWave];
     __shared__ int counts[16];
+    extern __shared__ int slot_tables[];         // with `walks` [n] or [4][n]: tokens of a region's slots
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C = D.C, n = D.n;
     int b, reg, tile, cg;
@@ -455,7 +456,9 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
     const size_t stat0 = ((size_t)b * D.heads + HPW * cg) * D.N;
     bf16_t *mine = lds + (SHARED ? 0 : wave * 2 * R::buf);
     float *my_stats = stats + (SHARED ? 0 : wave * 2 * kStats);
-    int *list = lists + (SHARED ? 0 : wave * kListWave);
+    int *list = lists + (SHARED ? 0 : wave * kListWave), *slots = slot_tables + (SHARED ? 0 : wave * n);
+    if (walks)
+        for (int t = SHARED ? tid : lane; t < n; t += SHARED ? 256 : kWave) slots[t] = at.slot(t);
 
     const int q0 = SHARED ? 64 * NK * tile + 16 * NK * wave : 16 * NK * tile;
     const bool idle = SHARED && q0 >= n;         // a wavefront without keys only brings its rows
@@ -484,32 +487,48 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
     int rows = 0;
     constexpr int STEP = SPLIT ? 4 : 1;          // as above
     const int start = SPLIT ? wave : 0;
+    constexpr int LOADS = R::per_wave / 8;
+    RowWalk<LOADS> walk;                         // rows that this lane brings
+    RowWalk<1> stat_walk;                        // row whose statistics it brings
+    int last = 0;                                // of the list
+    auto rewind = [&]() {
+        walk.start(KB * start + (SHARED ? 16 * wave : 0) + lane / 8, 8, KB * STEP, n, n_inv);
+        stat_walk.start(KB * start + lane % KB, 0, KB * STEP, n, n_inv);
+    };
+    const unsigned piece = 16 * ((lane % 8) ^ (lane / 8)), my_lds = lds_address(mine) + (SHARED ? 2048 * wave : 0), my_stat_lds = lds_address(my_stats);
     auto request = [&](int local) {
         const int blk = STEP * local + start;
-        bf16_t *Qs = mine + (local % 2) * R::buf, *Gs = Qs + KB * 64;
-        float *st = my_stats + (local % 2) * kStats;
+        const unsigned to = my_lds + (local % 2) * (2 * R::buf), st = my_stat_lds + (local % 2) * (4 * kStats);
         auto token = [&](int row) {
             const int r = min(KB * blk + row, rows - 1), p = divide(r, n, n_inv);
             return list[p] + at.slot(r - p * n);
         };
+        const bool tables = MODE == kWaves || walks;
         lds_reads_done();
 #pragma unroll
-        for (int u = 0; u < R::per_wave / 8; ++u) {
-            const int row = (SHARED ? 16 * wave : 0) + 8 * u + lane / 8;
-            const size_t e = img + (size_t)token(row) * C + 8 * ((lane % 8) ^ (lane / 8));
-            load_to_lds_untracked(A.Q + e, Qs + (row - lane / 8) * 64);
-            load_to_lds_untracked(A.dO + e, Gs + (row - lane / 8) * 64);
+        for (int u = 0; u < LOADS; ++u) {
+            if (tables) {
+                const unsigned off = row_offset(walk.token(u, list, last, slots), C, piece);
+                load_to_lds_untracked(A.Q + img, off, to + 1024 * u);
+                load_to_lds_untracked(A.dO + img, off, to + KB * 128 + 1024 * u);
+            } else {
+                const size_t e = img + (size_t)token((SHARED ? 16 * wave : 0) + 8 * u + lane / 8) * C + piece / 2;
+                load_to_lds_untracked(A.Q + e, to + 1024 * u);
+                load_to_lds_untracked(A.dO + e, to + KB * 128 + 1024 * u);
+            }
         }
         // statistics: 64 floats per load, (head, lse or D) by wavefront or (lse | D) of one head
-        const int t = token(lane % KB);
+        const int t = tables ? stat_walk.token(0, list, last, slots) : token(lane % KB);
         if (SHARED) {
             if (wave < 2 * HPW)
-                load4_to_lds_untracked((wave % 2 ? A.dsum : A.lse) + stat0 + (size_t)(wave / 2) * D.N + t, st + wave * KB);
+                load4_to_lds_untracked((wave % 2 ? A.dsum : A.lse) + stat0 + (size_t)(wave / 2) * D.N + t, st + 4 * wave * KB);
         } else {
 #pragma unroll
             for (int hh = 0; hh < HPW; ++hh)
-                load4_to_lds_untracked((lane >= KB ? A.dsum : A.lse) + stat0 + (size_t)hh * D.N + t, st + 2 * hh * KB);
+                load4_to_lds_untracked((lane >= KB ? A.dsum : A.lse) + stat0 + (size_t)hh * D.N + t, st + 8 * hh * KB);
         }
+        walk.advance();
+        stat_walk.advance();
     };
     auto block = [&](int local) {
         const int blk = STEP * local + start;
@@ -591,6 +610,8 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         }
         rows = named * n;
+        last = named - 1;
+        rewind();
         const int nb = ((rows + KB - 1) / KB - start + STEP - 1) / STEP;
         if (nb <= 0) continue;
         // the operands have arrived: see above
@@ -662,14 +683,18 @@ int launch_t(const Dims &D, const AttnBwdArgs &A, int kernel_id, hipStream_t st)
     const int per_tile = (MODE == kShared ? 64 : 16) * N, tiles = (D.n + per_tile - 1) / per_tile;
     const long items = (long)D.B * D.R * tiles * (D.C / 64), blocks = ((MODE == kWaves ? (items + 3) / 4 : items) + 7) / 8 * 8;
     if (blocks > 0x7fffffffL / 4) return BRA_ERR_UNSUPPORTED;
+    // kWaves has at most 32 tokens per region and always walks (up to 4096 regions)
+    const size_t tables = MODE == kShared ? 1 : 4;
+    const int walks = MODE == kSplit ? walk_ok(D) && D.n <= 256 : walk_ok(D);
     {
         ProfScope ps(st, kernel_id);
-        hipLaunchKernelGGL((k_attn_bwd_q<HD, N, MODE>), dim3((unsigned)blocks), dim3(256), (size_t)(MODE == kShared ? 1 : 4) * D.k * sizeof(int), st,
-                           A, D, tiles, (int)items);
+        hipLaunchKernelGGL((k_attn_bwd_q<HD, N, MODE>), dim3((unsigned)blocks), dim3(256), tables * (D.k + (walks ? D.n : 0)) * sizeof(int), st,
+                           A, D, tiles, (int)items, walks);
     }
     if (hipGetLastError() != hipSuccess) return BRA_ERR_LAUNCH;
     ProfScope ps(st, kernel_id);
-    hipLaunchKernelGGL((k_attn_bwd_kv<HD, N, MODE>), dim3((unsigned)blocks), dim3(256), 0, st, A, D, tiles, (int)items);
+    hipLaunchKernelGGL((k_attn_bwd_kv<HD, N, MODE>), dim3((unsigned)blocks), dim3(256), tables * (walks ? D.n : 0) * sizeof(int), st, A, D, tiles,
+                       (int)items, walks);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 

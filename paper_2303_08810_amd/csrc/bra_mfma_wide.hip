@@ -72,22 +72,22 @@ __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X,
 // Regions of more than 32 tokens: workgroup (image, region, tile of 64 NQ queries of the region, group of 64 channels = 2
 // or 1 heads), wavefront w with NQ query tiles of 16.  The k n routed keys are taken 64 at a time: their K and V rows (the
 // group's 128 bytes each, found by index in the projected maps) go straight from memory into one of two LDS buffers while
-// the other is worked on; 16-byte pieces are exchanged so that K's row reads (piece c of row r at c ^ r % 8) and V's
-// transposing reads (c ^ 4 (r / 2 % 2)) meet different banks.  Queries past the end of the region and keys past k n
+// the other is worked on; 16-byte pieces are exchanged (piece c of row r at c ^ r % 8), so that K's row reads and V's
+// transposing reads meet different banks.  Queries past the end of the region and keys past k n
 // repeat the last one and are masked.
 // Bound by vector issue: 2 x 208 x 304 x 64, 16 x 16 regions, k = 4 (250 M scores) takes 66 us, in which the vector ALUs
 // issue in 73 % of the cycles and the matrix cores work in 25 %.  Of 5.2 vector instructions per score 2.5 are its 2^x,
 // its addition to the denominator and half a conversion; with maxima instead of additions and denominators from a product
 // it took 68 us.  One query tile per wavefront instead of two: 74 us (4 x 64 x 64 x 384, heads of 64, k = 4: 45 for 39).
 template <int HD, int NQ>
-__global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles)
+__global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, int walks)
 {
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16;
     __shared__ __attribute__((aligned(16))) bf16_t K0[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t K1[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t V0[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t V1[64 * 64];
-    extern __shared__ int origins[];             // [k]: first token of the routed regions
+    extern __shared__ int origins[];             // [k]: first token of the routed regions; with `walks` [n]: tokens of a region's slots
     const int C = D.C, ncg = C / 64, n = D.n, kn = D.kn;
     const int cg = blockIdx.x % ncg, qt = (blockIdx.x / ncg) % qtiles;
     const int reg = (blockIdx.x / (ncg * qtiles)) % D.R, b = blockIdx.x / (ncg * qtiles * D.R);
@@ -109,6 +109,9 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
         origins[p] = region_origin(region_index(j, D.R));
         if (report) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = j;
     }
+    int *slots = origins + D.k;
+    if (walks)
+        for (int t = tid; t < n; t += 256) slots[t] = in_region(t);
     size_t qtok[NQ];
     bf16x8 qf[NQ][HPW][KSD];
 #pragma unroll
@@ -120,15 +123,35 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
             for (int ks = 0; ks < KSD; ++ks)
                 qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + HD * hh + 32 * ks + 8 * g);
     }
-    // direct loads: a wavefront brings rows 16 w .. 16 w + 15 of K and V, 8 rows of 8 pieces each
-    auto request = [&](int k0, bf16_t *Ks, bf16_t *Vs) {
+    // the operands have arrived before the loop: otherwise the compiler waits for them, and with them for the direct loads
+    // in flight, in every pass
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+            for (int ks = 0; ks < KSD; ++ks) asm volatile("" : "+v"(qf[q][hh][ks]));
+    // direct loads: a wavefront brings rows 16 w .. 16 w + 15 of K and V, 8 rows of 8 pieces each, block after block
+    RowWalk<2> walk;
+    walk.start(16 * wave + lane / 8, 8, 64, n, n_inv);
+    const unsigned piece = 16 * ((lane % 8) ^ (lane / 8));
+    auto request = [&](int k0, unsigned Ks, unsigned Vs) {
+        lds_reads_done();
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int row = 16 * wave + 8 * u + lane / 8, key = min(k0 + row, kn - 1), p = fast_div(key, n_inv);
-            const size_t at = img + (size_t)(origins[p] + in_region(key - p * n)) * C;
-            load_to_lds(A.K + at + 8 * ((lane % 8) ^ (row % 8)), Ks + 512 * (2 * wave + u));
-            load_to_lds(A.V + at + 8 * ((lane % 8) ^ (4 * (row / 2 % 2))), Vs + 512 * (2 * wave + u));
+            const unsigned at = 1024 * (2 * wave + u);
+            if (walks) {
+                const unsigned off = row_offset(walk.token(u, origins, D.k - 1, slots), C, piece);
+                load_to_lds_untracked(A.K + img, off, Ks + at);
+                load_to_lds_untracked(A.V + img, off, Vs + at);
+            } else {
+                const int key = min(k0 + 16 * wave + 8 * u + lane / 8, kn - 1), p = fast_div(key, n_inv);
+                const size_t e = img + (size_t)(origins[p] + in_region(key - p * n)) * C + piece / 2;
+                load_to_lds_untracked(A.K + e, Ks + at);
+                load_to_lds_untracked(A.V + e, Vs + at);
+            }
         }
+        walk.advance();
     };
     float m[NQ][HPW], l[NQ][HPW];
     f32x4 acc[NQ][HPW][NDT];
@@ -149,10 +172,7 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
-                    for (int ks = 0; ks < KSD; ++ks) {
-                        const int row = 16 * t + i, piece = HD / 8 * hh + 4 * ks + g;
-                        kf[t][ks] = *(const bf16x8 *)(Ks + row * 64 + 8 * (piece ^ (row % 8)));
-                    }
+                    for (int ks = 0; ks < KSD; ++ks) kf[t][ks] = row_operand(Ks, 16 * t + i, HD / 8 * hh + 4 * ks + g);
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
                     f32x4 s[4];
@@ -178,13 +198,7 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
             for (int tp = 0; tp < 2; ++tp)
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt) {
-                    u32x2 r[2];
-#pragma unroll
-                    for (int half = 0; half < 2; ++half) {
-                        const int row = 32 * tp + 16 * half + 4 * g + i / 4, col = HD * hh + 16 * dt + 4 * (i % 4);
-                        r[half] = __builtin_bit_cast(u32x2, lds_read_tr16(Vs + row * 64 + 8 * ((col / 8) ^ (4 * (row / 2 % 2))) + col % 8));
-                    }
-                    const bf16x8 vf = __builtin_bit_cast(bf16x8, u32x4{r[0][0], r[0][1], r[1][0], r[1][1]});
+                    const bf16x8 vf = column_operand(Vs, 32 * tp, HD * hh + 16 * dt, g, i);
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) acc[q][hh][dt] = mfma16(vf, pb[q][tp], acc[q][hh][dt]);
                 }
@@ -193,17 +207,18 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
     };
     const bool idle = 64 * NQ * qt + 16 * NQ * wave >= n;      // a wavefront without queries only brings its rows
     __syncthreads();                              // the table is in place
-    request(0, K0, V0);
+    const unsigned kv[2][2] = {{lds_address(K0), lds_address(V0)}, {lds_address(K1), lds_address(V1)}};
+    request(0, kv[0][0], kv[0][1]);
     arrive_barrier();
-    if (64 < kn) request(64, K1, V1);
+    if (64 < kn) request(64, kv[1][0], kv[1][1]);
     if (!idle) block(0, K0, V0, std::true_type{});
     for (int k0 = 64; k0 < kn; k0 += 128) {
         arrive_barrier();
-        if (k0 + 64 < kn) request(k0 + 64, K0, V0);
+        if (k0 + 64 < kn) request(k0 + 64, kv[0][0], kv[0][1]);
         if (!idle) block(k0, K1, V1, std::false_type{});
         if (k0 + 64 >= kn) break;
         arrive_barrier();
-        if (k0 + 128 < kn) request(k0 + 128, K1, V1);
+        if (k0 + 128 < kn) request(k0 + 128, kv[1][0], kv[1][1]);
         if (!idle) block(k0 + 64, K0, V0, std::false_type{});
     }
 #pragma unroll
@@ -224,22 +239,22 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
 // The same for regions of at most 32 tokens (16 NQ of them in NQ query tiles), where the tile of 64 queries above leaves
 // half or more of its wavefronts with copies: a wavefront works on its own, with all queries of a region and 64 channels
 // (2 or 1 heads), any four of them in a workgroup.  It brings its K and V rows straight from memory into its own part of LDS, 32 keys at a time into one
-// of two buffers while the other is worked on; there is no barrier.  Rows of 128 bytes lie unpadded; 16-byte pieces are exchanged so that the row reads of K (piece c of row r at
-// c ^ r % 8) and the transposing reads of V (c ^ 4 (r / 2 % 2)) meet different banks.
+// of two buffers while the other is worked on; there is no barrier.  Rows of 128 bytes lie unpadded, their pieces
+// exchanged as above.
 // Bound by the gather out of the L2s: 302 MB for 8 images of 32 x 32 x 768 with 12 regions of 16 tokens each.
 template <int HD, int NQ>
-__global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int items)
+__global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int items)
 {
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16, KB = 32;
     __shared__ __attribute__((aligned(16))) bf16_t S0[4 * 2 * KB * 64];      // [wavefront][K, V][32 keys][64]
     __shared__ __attribute__((aligned(16))) bf16_t S1[4 * 2 * KB * 64];
-    extern __shared__ int origin_tables[];       // [4][k]: first token of the routed regions
+    extern __shared__ int origin_tables[];       // [4][k]: first token of the routed regions; [4][32]: tokens of a region's slots
     const int C = D.C, ncg = C / 64, n = D.n, kn = D.kn;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, g = lane / 16, i = lane % 16;
     const int item = __builtin_amdgcn_readfirstlane(4 * swizzled_block() + wave);      // those of an image share an L2
     if (item >= items) return;
     const int cg = item % ncg, reg = (item / ncg) % D.R, b = item / (ncg * D.R);
-    int *origins = origin_tables + wave * D.k;
+    int *origins = origin_tables + wave * D.k, *slots = origin_tables + 4 * D.k + 32 * wave;
     const float rw_inv = 1.0f / (float)D.rw, n_inv = 1.0f / (float)n, s_inv = 1.0f / (float)D.S;
     auto region_origin = [&](int r) {
         const int ry = fast_div(r, s_inv);
@@ -256,7 +271,8 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
         origins[p] = region_origin(region_index(j, D.R));
         if (report) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = j;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // the table is read by other lanes
+    if (lane < n) slots[lane] = in_region(lane);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // the tables are read by other lanes
 
     const size_t img = (size_t)b * D.N * C + 64 * cg;
     const int origin = region_origin(reg);
@@ -279,17 +295,19 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
         for (int hh = 0; hh < HPW; ++hh)
 #pragma unroll
             for (int ks = 0; ks < KSD; ++ks) asm volatile("" : "+v"(qf[q][hh][ks]));
-    // direct loads: 8 rows of 8 pieces each
-    auto request = [&](int k0, bf16_t *S) {
-        bf16_t *Ks = S + wave * 2 * KB * 64, *Vs = Ks + KB * 64;
+    // direct loads: 8 rows of 8 pieces each, block after block
+    RowWalk<KB / 8> walk;
+    walk.start(lane / 8, 8, KB, n, n_inv);
+    const unsigned piece = 16 * ((lane % 8) ^ (lane / 8)), mine[2] = {lds_address(S0 + wave * 2 * KB * 64), lds_address(S1 + wave * 2 * KB * 64)};
+    auto request = [&](unsigned at) {
         lds_reads_done();
 #pragma unroll
         for (int u = 0; u < KB / 8; ++u) {
-            const int row = 8 * u + lane / 8, key = min(k0 + row, kn - 1), p = fast_div(key, n_inv);
-            const size_t at = img + (size_t)(origins[p] + in_region(key - p * n)) * C;
-            load_to_lds_untracked(A.K + at + 8 * ((lane % 8) ^ (row % 8)), Ks + 512 * u);
-            load_to_lds_untracked(A.V + at + 8 * ((lane % 8) ^ (4 * (row / 2 % 2))), Vs + 512 * u);
+            const unsigned off = row_offset(walk.token(u, origins, D.k - 1, slots), C, piece);
+            load_to_lds_untracked(A.K + img, off, at + 1024 * u);
+            load_to_lds_untracked(A.V + img, off, at + KB * 128 + 1024 * u);
         }
+        walk.advance();
     };
     float m[NQ][HPW], l[NQ][HPW];
     f32x4 acc[NQ][HPW][NDT];
@@ -309,20 +327,9 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int ks = 0; ks < KSD; ++ks) {
-                    const int row = 16 * t + i, piece = HD / 8 * hh + 4 * ks + g;
-                    kf[t][ks] = *(const bf16x8 *)(Ks + row * 64 + 8 * (piece ^ (row % 8)));
-                }
+                for (int ks = 0; ks < KSD; ++ks) kf[t][ks] = row_operand(Ks, 16 * t + i, HD / 8 * hh + 4 * ks + g);
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt) {
-                u32x2 r[2];
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const int row = 16 * half + 4 * g + i / 4, col = HD * hh + 16 * dt + 4 * (i % 4);
-                    r[half] = __builtin_bit_cast(u32x2, lds_read_tr16(Vs + row * 64 + 8 * ((col / 8) ^ (4 * (row / 2 % 2))) + col % 8));
-                }
-                vf[dt] = __builtin_bit_cast(bf16x8, u32x4{r[0][0], r[0][1], r[1][0], r[1][1]});
-            }
+            for (int dt = 0; dt < NDT; ++dt) vf[dt] = column_operand(Vs, 0, HD * hh + 16 * dt, g, i);
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 f32x4 s[2];
@@ -348,22 +355,22 @@ __global__ __launch_bounds__(256) void k_attn_rows(AttnArgs A, bf16_t *__restric
         }
     };
     // requests the keys from k0 on, if there are any, and waits for the 8 loads of the block before
-    auto advance = [&](int k0, bf16_t *S) {
+    auto advance = [&](int k0, unsigned at) {
         if (k0 < kn) {
-            request(k0, S);
+            request(at);
             asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
         } else {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
     };
-    request(0, S0);
-    advance(KB, S1);
+    request(mine[0]);
+    advance(KB, mine[1]);
     block(0, S0, std::true_type{});
     for (int k0 = KB; k0 < kn; k0 += 2 * KB) {
-        advance(k0 + KB, S0);
+        advance(k0 + KB, mine[0]);
         block(k0, S1, std::false_type{});
         if (k0 + KB >= kn) break;
-        advance(k0 + 2 * KB, S1);
+        advance(k0 + 2 * KB, mine[1]);
         block(k0 + KB, S0, std::false_type{});
     }
 #pragma unroll
@@ -430,7 +437,7 @@ void launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t s
 {
     const int items = D.B * D.R * (D.C / 64), blocks = (items + 3) / 4;
     const dim3 grid((unsigned)((blocks + 7) / 8 * 8)), block(256);
-    const size_t smem = (size_t)4 * D.k * sizeof(int);
+    const size_t smem = (size_t)4 * (D.k + 32) * sizeof(int);
     if (D.d == 32 && D.n <= 16) hipLaunchKernelGGL((k_attn_rows<32, 1>), grid, block, smem, st, A, O, D, items);
     else if (D.d == 32) hipLaunchKernelGGL((k_attn_rows<32, 2>), grid, block, smem, st, A, O, D, items);
     else if (D.n <= 16) hipLaunchKernelGGL((k_attn_rows<64, 1>), grid, block, smem, st, A, O, D, items);
@@ -442,9 +449,10 @@ void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t 
 {
     const int qtiles = (D.n + 64 * NQ - 1) / (64 * NQ);
     const dim3 grid((unsigned)((long)D.B * D.R * qtiles * (D.C / 64)));
-    const size_t smem = (size_t)D.k * sizeof(int);
-    if (D.d == 32) hipLaunchKernelGGL((k_attn_gen<32, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles);
-    else hipLaunchKernelGGL((k_attn_gen<64, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles);
+    const int walks = walk_ok(D);
+    const size_t smem = (size_t)(D.k + (walks ? D.n : 0)) * sizeof(int);
+    if (D.d == 32) hipLaunchKernelGGL((k_attn_gen<32, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks);
+    else hipLaunchKernelGGL((k_attn_gen<64, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks);
 }
 
 void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
