@@ -1,4 +1,5 @@
 // bf16 products of the general pipelines.
+#include "bra_attn_dev.h"
 #include "bra_gemm.h"
 
 #include <algorithm>
@@ -9,12 +10,22 @@ using namespace mfma;
 
 namespace {
 
+// The wait between the last 32x32x16 products and the first use of their results, spelled out: where a branch lies between
+// them the compiler has left it short.
+__device__ __forceinline__ void products_done()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // ---------------------------------------------------------------------------
 // Out[m][o] = sum_k In[m][k] W[k][o] (W row-major with ldw columns, as the caller holds it), float32 In and Out,
 // for a tile of 64 rows m x 32 CW outputs o (128 or 64), the contraction in chunks of 64
 // staged in LDS (the next chunk is requested while the current one is multiplied).
 // The four wavefronts split the tile 2 x 2 (32 rows x 16 CW outputs each); the product is formed
-// transposed (D[output 16 t + 4 g + jj][row i]) so that a lane stores 4 consecutive outputs of one row;
+// transposed on 32x32x16 products (16x16x32 ones, at 27 clocks for half the work of 32, took 5 us more of 8 x 32 x 32 x 768's
+// projection launch), with W's columns taken as in k_gemm_dma, so that a lane stores 8 consecutive outputs of one row;
 // its W operand (rows = outputs) comes out of the row-major chunk by the transposing LDS read.
 // Output column o goes to buffer o / cols (buffers of `cols` columns each, e.g. Q^r, K^r), column o % cols.
 // In enters as three exact bf16 terms (smallest first).
@@ -23,13 +34,15 @@ constexpr int kGemmGroupW = 64;     // W: 128 bytes more after every 8 rows: the
                                     // transposing read (8 rows further on) then meets the other half of the banks
 
 // Ws: [64 k][32 CW + 16] and 8 group paddings, Xs[q]: [64][P].
+constexpr size_t kGemm64Bytes = (size_t)(3 * 64 * kGemmPitch + 64 * (64 + 16) + 8 * kGemmGroupW) * 2;     // CW = 2
+
 template <int CW>
 __device__ __forceinline__ void gemm64(const GemmRegions &J, const bf16_t *__restrict__ W, int ldw, int K, int block,
                                        bf16_t *Ws, bf16_t *const (&Xs)[3])
 {
     const int M = (int)J.M, Nout = J.Nout;
     constexpr int P = kGemmPitch, NT = 3, COLS = 32 * CW, PW = COLS + 16;
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     const int otiles = (Nout + COLS - 1) / COLS;
     const int m0 = (block / otiles) * 64, o0 = (block % otiles) * COLS;
 
@@ -70,14 +83,14 @@ __device__ __forceinline__ void gemm64(const GemmRegions &J, const bf16_t *__res
         }
     };
 
-    // wavefront (wr, wc) owns rows 32 wr .. 32 wr + 31 (two 16-row tiles) and outputs 64 wc ..
-    // 64 wc + 63 (four tiles) of the workgroup's 64 x 128: a W fragment serves two row tiles
-    const int wr = wave / 2, wc = wave % 2;
-    f32x4 acc[2][CW];
+    // wavefront (wr, wc) owns rows 32 wr .. 32 wr + 31 and outputs 16 CW wc .. + 16 CW - 1 of the workgroup's tile
+    const int wr = wave / 2, wc = wave % 2, h = lane / 32, c = lane % 32;
+    const int s = lane % 16, q = lane / 16, col4 = (s % 2) * 2 + s % 4 / 2;       // see k_gemm_dma
+    f32x16 acc[CW / 2];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int t = 0; t < CW / 2; ++t)
 #pragma unroll
-        for (int t = 0; t < CW; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
     request(0);
     for (int k0 = 0; k0 < K; k0 += 64) {
         if (k0) __syncthreads();          // the previous chunk has been read
@@ -85,39 +98,38 @@ __device__ __forceinline__ void gemm64(const GemmRegions &J, const bf16_t *__res
         __syncthreads();
         if (k0 + 64 < K) request(k0 + 64);
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 xb[2][NT];
+        for (int ks = 0; ks < 4; ++ks) {
+            bf16x8 xb[NT];
 #pragma unroll
-            for (int rt = 0; rt < 2; ++rt)
+            for (int u = 0; u < NT; ++u) xb[u] = *(const bf16x8 *)(Xs[u] + (32 * wr + c) * P + 16 * ks + 8 * h);
 #pragma unroll
-                for (int q = 0; q < NT; ++q)
-                    xb[rt][q] = *(const bf16x8 *)(Xs[q] + (32 * wr + 16 * rt + i) * P + 32 * ks + 8 * g);
+            for (int t = 0; t < CW / 2; ++t) {
+                u32x2 r[2];
 #pragma unroll
-            for (int t = 0; t < CW; ++t) {
-                const bf16_t *wp = Ws + (32 * ks + 8 * g + i / 4) * PW + (4 * ks + g) * kGemmGroupW + 16 * CW * wc + 16 * t +
-                                   4 * (i % 4);
-                const u32x2 w0 = __builtin_bit_cast(u32x2, lds_read_tr16(wp));
-                const u32x2 w1 = __builtin_bit_cast(u32x2, lds_read_tr16(wp + 4 * PW));
-                const bf16x8 wf = __builtin_bit_cast(bf16x8, u32x4{w0[0], w0[1], w1[0], w1[1]});
+                for (int half = 0; half < 2; ++half) {
+                    const int k = 16 * ks + 8 * (q / 2) + 4 * half + s / 4;
+                    r[half] = __builtin_bit_cast(u32x2, lds_read_tr16(Ws + k * PW + (k / 8) * kGemmGroupW + 16 * CW * wc + 32 * t + 16 * (q % 2) + 4 * col4));
+                }
+                const bf16x8 wf = __builtin_bit_cast(bf16x8, u32x4{r[0][0], r[0][1], r[1][0], r[1][1]});
 #pragma unroll
-                for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-                    for (int q = NT - 1; q >= 0; --q) acc[rt][t] = mfma16(wf, xb[rt][q], acc[rt][t]);
+                for (int u = NT - 1; u >= 0; --u) acc[t] = mfma32(wf, xb[u], acc[t]);
             }
         }
     }
+    products_done();
+    const int m = m0 + 32 * wr + c;
+    if (m >= M) return;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-        const int m = m0 + 32 * wr + 16 * rt + i;
-        if (m >= M) continue;
+    for (int t = 0; t < CW / 2; ++t)
 #pragma unroll
-        for (int t = 0; t < CW; ++t) {
-            const int o = o0 + 16 * CW * wc + 16 * t + 4 * g;
-            if (o >= Nout) break;
+        for (int run = 0; run < 2; ++run) {
+            const int o = o0 + 16 * CW * wc + 32 * t + 16 * run + 8 * h;
+            if (o >= Nout) continue;
             const int which = o / J.cols, col = o % J.cols;
-            *(f32x4 *)(J.buf[which] + (size_t)m * J.cols + col) = acc[rt][t];
+            float *dst = J.buf[which] + (size_t)m * J.cols + col;
+            *(f32x4 *)dst = f32x4{acc[t][8 * run], acc[t][8 * run + 1], acc[t][8 * run + 2], acc[t][8 * run + 3]};
+            *(f32x4 *)(dst + 4) = f32x4{acc[t][8 * run + 4], acc[t][8 * run + 5], acc[t][8 * run + 6], acc[t][8 * run + 7]};
         }
-    }
 }
 
 // The region-level product on its own.
@@ -140,7 +152,8 @@ __global__ __launch_bounds__(256) void k_gemm(GemmRegions J, const bf16_t *__res
 // The product is formed transposed (rows = outputs) with W's columns taken in the order that leaves a lane with two
 // runs of 8 consecutive outputs of one row of In per 32 outputs (see the operand layouts in bra_mfma.hip).
 // What bounds it (8192 x 768 x 2304, 128 x 128 tiles): direct loads alone 24 us (18 TB/s out of the L2s), products with
-// their LDS reads alone 23, stores alone 9.5; they overlap to 47, with 2.25 workgroups per slot in three rounds.
+// their LDS reads alone 23, stores alone 9.5; they overlap to 37 (43.7 where the compiler counted the direct loads and a
+// chunk past the end was loaded once more).
 // BT: W is given transposed, [Nout][ldw] with the contraction axis contiguous; its chunk then lies like In's and needs no
 // transposing reads.
 __device__ bf16_t zero_row[4096];        // what missing rows of In read (never written)
@@ -152,23 +165,20 @@ __device__ __forceinline__ long stored_row(const GemmRows &r, int m)
     return y < r.H && x < r.W ? ((long)b * r.H + y) * r.W + x : -1;
 }
 
-// EXT: bias, GELU, residual or rows that are not in memory (GemmRows).
-template <int BM, int BN, bool REGIONS, bool BT, bool EXT>
-__global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) void k_gemm_dma(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw,
+// EXT: bias, GELU, residual or rows that are not in memory (GemmRows).  NB: buffers, 1 for K = 64, else 2.
+template <int BM, int BN, int NB, bool REGIONS, bool BT, bool EXT>
+__global__ __launch_bounds__(256, BM == 64 && BN == 64 ? 3 : 2) void k_gemm_dma(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw,
                                                   int M, int K, int Nout, GemmOut out, GemmRegions reg, int reg_blocks)
 {
-    constexpr int RegionElems = REGIONS ? 64 * kGemmPitch + 8 * kGemmGroupW : 0;     // what gemm64 needs of each array
-    constexpr int AE = BM * 64 > RegionElems ? BM * 64 : RegionElems, BE = BN * 64 > RegionElems ? BN * 64 : RegionElems;
-    __shared__ __attribute__((aligned(16))) bf16_t A0[AE];
-    __shared__ __attribute__((aligned(16))) bf16_t A1[AE];
-    __shared__ __attribute__((aligned(16))) bf16_t B0[BE];
-    __shared__ __attribute__((aligned(16))) bf16_t B1[BE];
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    constexpr int AE = BM * 64, BE = BN * 64;     // elements of a chunk
+    bf16_t *lds = (bf16_t *)smem;                 // buffers of a chunk of In, then W, each
     if (REGIONS && (int)blockIdx.x < reg_blocks) {
-        bf16_t *const planes[3] = {A0, A1, B1};
-        gemm64<2>(reg, W, ldw, K, blockIdx.x, B0, planes);
+        bf16_t *const planes[3] = {lds, lds + 64 * kGemmPitch, lds + 2 * 64 * kGemmPitch};
+        gemm64<2>(reg, W, ldw, K, blockIdx.x, lds + 3 * 64 * kGemmPitch, planes);
         return;
     }
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, h = lane / 32, c = lane % 32;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, h = lane / 32, c = lane % 32;
     const int otiles = (Nout + BN - 1) / BN;
     // workgroups of an XCD take neighbouring tiles, the output tiles of the same rows one after the other
     const int nb = (int)gridDim.x - reg_blocks, per_xcd = nb / 8, bi = (int)blockIdx.x - reg_blocks;
@@ -199,11 +209,15 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
         const int piece = (lane % CH) ^ (BN == 128 ? 4 * (k % 4) : 4 * (k / 2 % 2));
         bp[u] = W + (size_t)k * ldw + min(o0 + 8 * piece, Nout - 8);
     }
-    auto request = [&](int k0, bf16_t *As, bf16_t *Bs) {
+    const unsigned base = lds_address(lds);
+    auto request = [&](int chunk, int buffer) {
+        const int k0 = 64 * chunk;
+        const unsigned at = base + buffer * (AE + BE) * 2;
+        lds_reads_done();
 #pragma unroll
-        for (int u = 0; u < LA; ++u) load_to_lds(ap[u] + k0, As + 512 * (wave * LA + u));
+        for (int u = 0; u < LA; ++u) load_to_lds_untracked(ap[u] + k0, at + 1024 * (wave * LA + u));
 #pragma unroll
-        for (int u = 0; u < LB; ++u) load_to_lds(bp[u] + (BT ? (size_t)k0 : (size_t)k0 * ldw), Bs + 512 * (wave * LB + u));
+        for (int u = 0; u < LB; ++u) load_to_lds_untracked(bp[u] + (BT ? (size_t)k0 : (size_t)k0 * ldw), at + AE * 2 + 1024 * (wave * LB + u));
     };
     constexpr int MT = BM / 64, NT = BN / 64;     // 32 x 32 tiles of a wavefront
     const int wm = (wave / 2) * (BM / 2), wn = (wave % 2) * (BN / 2);
@@ -257,18 +271,18 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    const int pairs = K / 128;
-    request(0, A0, B0);
-    for (int p = 0; p < pairs; ++p) {
-        arrive_barrier();                          // the chunk has arrived; the other buffer has been read
-        request(128 * p + 64, A1, B1);
-        multiply(A0, B0);
-        arrive_barrier();
-        request(min(128 * p + 128, K - 64), A0, B0);      // past the end: the last chunk again, not used
-        multiply(A1, B1);
+    const int chunks = NB == 1 ? 1 : K / 64;
+    request(0, 0);
+    for (int c0 = 0; c0 < chunks; c0 += NB) {
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            if (c0 + u >= chunks) break;
+            arrive_barrier();                      // the chunk has arrived; the other buffer has been read
+            if (NB > 1 && c0 + u + 1 < chunks) request(c0 + u + 1, 1 - u);
+            multiply(lds + u * (AE + BE), lds + u * (AE + BE) + AE);
+        }
     }
-    arrive_barrier();
-    if (K % 128) multiply(A0, B0);
+    products_done();
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         // a 32-output tile lies in one buffer (cols is a multiple of 32): looked up once per tile, for the whole wavefront
@@ -322,43 +336,59 @@ __global__ __launch_bounds__(256, BM == 64 && !(REGIONS && BN == 128) ? 3 : 2) v
     }
 }
 
-template <int BM, int BN, bool REGIONS, bool BT, bool EXT>
+template <int BM, int BN, int NB, bool REGIONS, bool BT, bool EXT>
 int launch_dma_t(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out,
                const GemmRegions &reg, hipStream_t st)
 {
+    static bool opted = false;
+    if (!opted) {
+        if (hipFuncSetAttribute((const void *)k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess)
+            return BRA_ERR_LAUNCH;
+        opted = true;
+    }
     const long tiles = (M + BM - 1) / BM * ((Nout + BN - 1) / BN), blocks = (tiles + 7) / 8 * 8;
     const long rb = REGIONS ? (reg.M + 63) / 64 * ((reg.Nout + 63) / 64) : 0;
     if (blocks + rb > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((k_gemm_dma<BM, BN, REGIONS, BT, EXT>), dim3((unsigned)(blocks + rb)), dim3(256), 0, st, In, W, ldw, (int)M, K,
-                       Nout, out, reg, (int)rb);
+    // a single chunk: four workgroups per compute unit (with eight, 200704 x 64 x 64 takes 13.7 us instead of 12.9)
+    const size_t ring = NB == 1 ? 40 * 1024 : (size_t)NB * (BM + BN) * 64 * 2, region = REGIONS ? kGemm64Bytes : 0;
+    hipLaunchKernelGGL((k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT>), dim3((unsigned)(blocks + rb)), dim3(256), std::max(ring, region), st, In, W, ldw,
+                       (int)M, K, Nout, out, reg, (int)rb);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
-template <int BM, int BN, bool REGIONS, bool BT>
+template <int BM, int BN, int NB, bool REGIONS, bool BT>
 int launch_dma(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out,
                const GemmRegions &reg, hipStream_t st)
 {
     if constexpr (!BT) {
         if (out.bias || out.gelu || out.res || out.in_rows.Hp || out.out_rows.Hp)
-            return launch_dma_t<BM, BN, REGIONS, false, true>(In, W, ldw, M, K, Nout, out, reg, st);
+            return launch_dma_t<BM, BN, NB, REGIONS, false, true>(In, W, ldw, M, K, Nout, out, reg, st);
     }
-    return launch_dma_t<BM, BN, REGIONS, BT, false>(In, W, ldw, M, K, Nout, out, reg, st);
+    return launch_dma_t<BM, BN, NB, REGIONS, BT, false>(In, W, ldw, M, K, Nout, out, reg, st);
 }
 
 template <bool REGIONS, bool BT = false>
 int launch_big(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, const GemmRegions &reg,
                hipStream_t st)
 {
-    // Wide tiles read less per product but need enough of them (about 1.5 per slot: 2 workgroups of 128 x 128, 3 of
-    // 64 x 128 per compute unit) and outputs that fill 128 columns.  Measured, 128 x 128 / 64 x 128 / 64 x 64 (us):
-    // 8192 x 768 x 2304: 47 / 52 / 58; 8192 x 768 x 768: 18.2 / 16.8 / 19.4; 12544 x 1152 x 384: 22.0 / 20.5 / 22.9;
-    // 3136 x 512 x 512: 7.7 / 7.2 / 6.8; 126464 x 64 x 192: 16.9 / 17.0 / 15.5 (a 64 x 128 tile staged through
-    // registers took 61, 22, 26, 8.9, 37).  256 x 128 with 8 wavefronts gained nothing (50 / 17.1 / 20.5).
-    const long c128 = (Nout + 127) / 128;
-    const bool fills = 128 * c128 * 100 <= 115L * Nout;
-    if (fills && (M + 127) / 128 * c128 >= 800) return launch_dma<128, 128, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
-    if (fills && (M + 63) / 64 * c128 >= 512) return launch_dma<64, 128, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
-    return launch_dma<64, 64, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
+    // One chunk: no tile reads anything twice, small ones overlap their loads and stores best (126464 x 64 x 192: 14.0 us, 14.8
+    // with 64 x 128, 15.6 with 128 x 128).
+    if (K == 64) return launch_dma<64, 64, 1, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
+    // Wide tiles read less per product, narrow ones deal out more evenly over the 256 compute units.  Time is that of the
+    // compute unit with the most tiles: 744, 433 or 260 for one of 128 x 128, 64 x 128 or 64 x 64 (12544 x 768 x 2304:
+    // 52.1, 60.7 and 71.1 us for 7, 14 and 28 tiles), three tenths more where it has a single one and nothing to overlap it
+    // with.  Measured, 128 x 128 / 64 x 128 / 64 x 64 (us): 8192 x 768 x 2304: 37.2 / 38.9 / 47.1; 8192 x 768 x 768: 15.9 / 14.6 /
+    // 17.1; 12544 x 1152 x 384: 20.8 / 19.3 / 21.9; 12544 x 512 x 512: 12.4 / 14.0 / 12.7; 3136 x 768 x 768: 9.9 / 9.3 / 8.3;
+    // 12544 x 256 x 768: 12.2 / 11.2 / 12.0; 1568 x 384 x 1152: 6.6 / 5.2 / 4.8.  A third buffer, 256 x 128 tiles with 8 wavefronts
+    // and chunks of 32 gained nothing.
+    auto cost = [&](int bm, int bn, long tile) {
+        const long rounds = ((M + bm - 1) / bm * ((Nout + bn - 1) / bn) + 255) / 256;
+        return tile * rounds * (rounds == 1 ? 13 : 10);
+    };
+    const long wide = cost(128, 128, 744), mid = cost(64, 128, 433), narrow = cost(64, 64, 260);
+    if (wide <= mid && wide <= narrow) return launch_dma<128, 128, 2, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
+    if (mid <= narrow) return launch_dma<64, 128, 2, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
+    return launch_dma<64, 64, 2, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
 }
 
 // ---------------------------------------------------------------------------
