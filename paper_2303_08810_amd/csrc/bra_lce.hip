@@ -1,184 +1,36 @@
-// LCE (Eq. 7: depth-wise 5 x 5 correlation, stride 1, zero padding 2) and its gradients on bf16 maps, on the
-// two-element dot product v_dot2_f32_bf16 (two multiply-adds with a float32 sum per lane and instruction).
-//
-// A thread has 2 channels (one 32-bit load per token) of 2 neighbouring columns and walks down a strip of rows with
-// the window of 5 rows x 6 columns in registers.  Per channel and row the left output takes the column pairs (0,1),
-// (2,3), (3,4) against (w0,w1), (w2,w3), (0,w4); the right one the pairs (1,2), (3,4), (4,5) against the same taps.  A
-// pair costs one byte permute.  The zero meets a column that the output takes anyway, in the same channel: an infinity
-// may leave an output as NaN, but nothing reaches another channel or an output further away (columns as loaded, both
-// channels in one operand with w4 in one half, did that: 0 times infinity in the neighbour).
-// The next row is requested a step ahead and nothing is staged through LDS.
-// What bounds it: the dot products and permutes (about 0.4 of the time by instruction count) and, at 3 to 4 wavefronts
-// per SIMD, the latency they do not cover; an LDS-tiled version on float32 multiply-adds took 69 us for all three
-// correlations of a 64 x 56 x 56 x 64 map.
-#include "bra_lce_dev.h"
+// Depth-wise convolution passes on bf16 maps (walk_tile in bra_lce_pairs.h).
+#include "bra_lce_pairs.h"
+#include "bra_route_dev.h"
 
 namespace bra {
 namespace lce {
 
 namespace {
 
-using namespace mfma;
-
-// A window row: pairs of columns (0,1), (2,3), (4,5) | (1,2), (3,4) per channel.
-struct Row {
-    unsigned even[2][3], odd[2][2];
-};
-
-// How a workgroup's 8 column-pair slots lie on a map: `pairs` of them side by side, `subs` strips above each other
-// (narrow maps).
-struct Tiling {
-    int pairs, subs, xtiles, ytiles, height;
-};
-
 // GRAD = false: Out += LCE(In).
-// GRAD = true:  Out += LCE^T(In) (taps reversed) and the tap gradients from the same window (see k_lce_grad in
-//               bra_lce_dev.h for the identities): (V left, V right) against the window's pairs (p, p + 1), 25 sums
-//               per channel kept across the workgroup's tiles, Part[group][C][25] at the end.
+// GRAD = true:  Out += LCE^T(In) and the tap gradients, summed over the workgroup's tiles: Part[group][C][25].
 template <bool GRAD>
 __global__ __launch_bounds__(256) void k_lce_pairs(const bf16_t *__restrict__ In, const bf16_t *__restrict__ V,
                                                    const bf16_t *__restrict__ Wlce, bf16_t *__restrict__ Out, int ldo,
                                                    float *__restrict__ Part, Dims D, Tiling T, int cblocks, long tiles,
                                                    int tiles_per_wg)
 {
-    __shared__ __attribute__((aligned(16))) float red[GRAD ? 25 * 256 : 15 * 64];
-    unsigned (*table)[3][64] = (unsigned (*)[3][64])red;      // [ky][(w0,w1) | (w2,w3) | (0,w4)][channel]
+    __shared__ __attribute__((aligned(16))) float red[GRAD ? 25 * 256 : kTapBytes / 4];
     const int block = mfma::swizzled_block(), cb = block % cblocks, c0 = 64 * cb, grp = block / cblocks;
     const long first = (long)grp * tiles_per_wg, last = min(tiles, first + tiles_per_wg);
     if (first >= tiles) return;
     const int cp = threadIdx.x % 32, slot = threadIdx.x / 32;
-    for (int e = threadIdx.x; e < 5 * 64; e += 256) {
-        const int ch = e % 64, ky = e / 64;
-        unsigned t[5];
-#pragma unroll
-        for (int kx = 0; kx < 5; ++kx) {
-            const int tap = 5 * ky + kx;
-            t[kx] = c0 + ch < D.C ? Wlce[(size_t)(c0 + ch) * 25 + (GRAD ? 24 - tap : tap)] : 0;
-        }
-        table[ky][0][ch] = t[0] | t[1] << 16;
-        table[ky][1][ch] = t[2] | t[3] << 16;
-        table[ky][2][ch] = t[4] << 16;
-    }
-    __syncthreads();
+    TapTable &table = *(TapTable *)red;
+    stage_taps<GRAD, 256>(table, Wlce, c0, D.C);
     const bool live = c0 + 2 * cp < D.C;
     const int cl = live ? 2 * cp : 0;
     u32x2 w[5][3];
-#pragma unroll
-    for (int ky = 0; ky < 5; ++ky)
-#pragma unroll
-        for (int t = 0; t < 3; ++t) w[ky][t] = *(const u32x2 *)&table[ky][t][cl];
+    load_taps(w, table, cl);
     float acc[GRAD ? 25 : 1][2];
 #pragma unroll
     for (int t = 0; t < (GRAD ? 25 : 1); ++t) acc[t][0] = acc[t][1] = 0.f;
     if (GRAD) __syncthreads();
-
-    const int px = slot % T.pairs, sub = slot / T.pairs;
-    for (long tile = first; tile < last; ++tile) {
-        const int yt = (int)(tile / T.xtiles % T.ytiles), ybase = yt * T.subs * T.height;
-        const int x0 = 2 * ((int)(tile % T.xtiles) * T.pairs + px), y0 = ybase + sub * T.height;
-        const size_t b = tile / ((long)T.xtiles * T.ytiles);
-        if (sub >= T.subs || x0 >= D.W || y0 >= D.H) continue;
-        const int y1 = min(y0 + T.height, D.H), ytop = max(ybase - 2, 0);
-        const bool right = x0 + 1 < D.W;
-        // bases are the same for all lanes, lane offsets 32-bit from the tile's first row
-        const char *ibase = (const char *)(In + (b * D.N + (size_t)ytop * D.W) * D.C + c0);
-        const char *vbase = GRAD ? (const char *)(V + (b * D.N + (size_t)ytop * D.W) * D.C + c0) : nullptr;
-        char *obase = (char *)(Out + (b * D.N + (size_t)ytop * D.W) * ldo + c0);
-        const unsigned irow = 2u * D.W * D.C, orow = 2u * D.W * ldo;
-        unsigned xo[6];
-        bool xok[6];
-#pragma unroll
-        for (int j = 0; j < 6; ++j) {
-            xok[j] = (unsigned)(x0 + j - 2) < (unsigned)D.W;
-            xo[j] = 2u * (min(max(x0 + j - 2, 0), D.W - 1) * D.C + cl);
-        }
-        const unsigned oo[2] = {2u * (x0 * ldo + cl), 2u * ((right ? x0 + 1 : x0) * ldo + cl)};
-        const bool edge = !__all(xok[0] && xok[1] && xok[4] && xok[5]);
-        auto request_row = [&](int y, unsigned (&raw)[6]) {
-            const unsigned row = (unsigned)(min(max(y, 0), D.H - 1) - ytop) * irow;
-#pragma unroll
-            for (int j = 0; j < 6; ++j) raw[j] = *(const unsigned *)(ibase + (row + xo[j]));
-        };
-        auto pack_row = [&](int y, unsigned (&raw)[6]) {
-            if (edge || (unsigned)y >= (unsigned)D.H) {
-                const bool in = (unsigned)y < (unsigned)D.H;
-#pragma unroll
-                for (int j = 0; j < 6; ++j) raw[j] = in && xok[j] ? raw[j] : 0u;
-            }
-            Row R;
-#pragma unroll
-            for (int t = 0; t < 3; ++t) {
-                R.even[0][t] = pair_lo(raw[2 * t], raw[2 * t + 1]);
-                R.even[1][t] = pair_hi(raw[2 * t], raw[2 * t + 1]);
-                if (t == 2) break;
-                R.odd[0][t] = pair_lo(raw[2 * t + 1], raw[2 * t + 2]);
-                R.odd[1][t] = pair_hi(raw[2 * t + 1], raw[2 * t + 2]);
-            }
-            return R;
-        };
-        unsigned next[6], nv[2], nd[2];
-        auto request = [&](int y) {          // what step y needs: row y + 2 of In, Out (and V) of row y
-            const unsigned yc = min(y, D.H - 1) - ytop;
-            request_row(y + 2, next);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                if (GRAD) nv[j] = *(const unsigned *)(vbase + (yc * irow + xo[j && right ? 3 : 2]));
-                nd[j] = *(const unsigned *)(obase + (yc * orow + oo[j]));
-            }
-        };
-        Row win[5];
-        {
-            unsigned rows[4][6];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) request_row(y0 + r - 2, rows[r]);
-            request(y0);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) win[r] = pack_row(y0 + r - 2, rows[r]);
-        }
-        for (int yb = y0; yb < y1; yb += 5) {
-#pragma unroll
-            for (int u = 0; u < 5; ++u) {
-                const int y = yb + u;
-                if (y >= y1) break;
-                win[(u + 4) % 5] = pack_row(y + 2, next);
-                unsigned vp[2] = {0u, 0u};
-                if (GRAD) {
-                    const unsigned vr = right ? nv[1] : 0u;
-                    vp[0] = pair_lo(nv[0], vr);
-                    vp[1] = pair_hi(nv[0], vr);
-                }
-                float o[2][2] = {{bf16_lo(nd[0]), bf16_hi(nd[0])}, {bf16_lo(nd[1]), bf16_hi(nd[1])}};   // [column][channel]
-                request(y + 1);
-#pragma unroll
-                for (int r = 0; r < 5; ++r) {
-                    const Row &R = win[(u + r) % 5];
-#pragma unroll
-                    for (int v = 0; v < 2; ++v) {
-#pragma unroll
-                        for (int t = 0; t < 2; ++t) {
-                            o[0][v] = dot2(w[r][t][v], R.even[v][t], o[0][v]);
-                            o[1][v] = dot2(w[r][t][v], R.odd[v][t], o[1][v]);
-                        }
-                        o[0][v] = dot2(w[r][2][v], R.odd[v][1], o[0][v]);
-                        o[1][v] = dot2(w[r][2][v], R.even[v][2], o[1][v]);
-                        if (GRAD) {
-#pragma unroll
-                            for (int t = 0; t < 2; ++t) {
-                                acc[5 * r + 2 * t][v] = dot2(vp[v], R.even[v][t], acc[5 * r + 2 * t][v]);
-                                acc[5 * r + 2 * t + 1][v] = dot2(vp[v], R.odd[v][t], acc[5 * r + 2 * t + 1][v]);
-                            }
-                            acc[5 * r + 4][v] = dot2(vp[v], R.even[v][2], acc[5 * r + 4][v]);
-                        }
-                    }
-                }
-                if (live) {
-                    char *row = obase + (unsigned)(y - ytop) * orow;
-                    *(unsigned *)(row + oo[0]) = mfma::pack_bf16(o[0][0], o[0][1]);
-                    if (right) *(unsigned *)(row + oo[1]) = mfma::pack_bf16(o[1][0], o[1][1]);
-                }
-            }
-        }
-    }
+    for (long tile = first; tile < last; ++tile) walk_tile<GRAD, true>(In, V, Out, ldo, D, T, tile, slot, c0, cl, live, w, acc);
     if (!GRAD) return;
     // the 8 slots' sums of a channel through LDS, added in a fixed order
 #pragma unroll
@@ -196,29 +48,64 @@ __global__ __launch_bounds__(256) void k_lce_pairs(const bf16_t *__restrict__ In
     }
 }
 
-// Lane offsets are 32-bit: the rows of a tile (with the window, within the map) must span less than 2 GiB in either map.
-bool offsets_fit(const Dims &D, const Tiling &T, int ldo)
-{
-    return (long)std::min(T.subs * T.height + 4, D.H) * D.W * std::max(D.C, ldo) * 2 < (1L << 31);
-}
+// Out = LCE(In) beside the rows of A^r and their top-k: the routing is a chain of latencies on a few workgroups (13 us for
+// 8 x 64 regions of 768 channels), and the convolution needs nothing of it.  Workgroups below route_blocks (a multiple of 8;
+// those without rows leave) do the routing, the others two tiles each.  Routing, convolution in place and attention took 119.5 us
+// as a layer of 2 x 200 x 300 x 64, S = 16, and 124.0 of 8 x 32 x 32 x 768; with the convolution here 113.6 and 110.
+constexpr int kStoreThreads = 64 * route::kWaves;
 
-// Strips of 20 rows, or 10 or 5 where that leaves fewer than `want` tiles or the rows span too much.
-Tiling tiling(const Dims &D, int ldo, long want, long &tiles)
-{
+struct StoreJob {
+    const bf16_t *In, *Wlce;
+    bf16_t *Out;
     Tiling T;
-    const int xp = (D.W + 1) / 2;
-    T.pairs = xp < 8 ? xp : 8;
-    T.xtiles = (xp + T.pairs - 1) / T.pairs;
-    for (T.height = 20;; T.height /= 2) {
-        const int strips = (D.H + T.height - 1) / T.height;
-        T.subs = 8 / T.pairs < strips ? 8 / T.pairs : strips;
-        T.ytiles = (strips + T.subs - 1) / T.subs;
-        tiles = (long)D.B * T.xtiles * T.ytiles;
-        if (T.height == 5 || (tiles >= want && offsets_fit(D, T, ldo))) return T;
+    int cblocks;
+    long tiles;
+};
+
+__global__ __launch_bounds__(kStoreThreads, 4) void k_route_lce(const float *__restrict__ Qr, const float *__restrict__ Kr, int32_t *__restrict__ Ir,
+                                                                int CS, int rows_blocks, int route_blocks, StoreJob J, Dims D)
+{
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    const int bi = blockIdx.x;
+    if (bi < route_blocks) {
+        if (bi < rows_blocks) route::route_block<true, 3>(Qr, Kr, D.C, Ir, nullptr, D, CS, bi, smem);
+        return;
     }
+    const int per_xcd = ((int)gridDim.x - route_blocks) / 8, block = (bi % 8) * per_xcd + (bi - route_blocks) / 8;
+    const int c0 = 64 * (block % J.cblocks), cl = 2 * (threadIdx.x % 32);
+    if ((long)(block / J.cblocks) * 2 >= J.tiles) return;
+    TapTable &table = *(TapTable *)smem;
+    stage_taps<false, kStoreThreads>(table, J.Wlce, c0, D.C);
+    u32x2 w[5][3];
+    load_taps(w, table, cl);
+    float none[1][2];
+    const long tile = (long)(block / J.cblocks) * 2 + threadIdx.x / 256;
+    if (tile < J.tiles)
+        walk_tile<false, false>(J.In, (const bf16_t *)nullptr, J.Out, D.C, D, J.T, tile, threadIdx.x / 32 % 8, c0, cl, true, w, none);
 }
 
 }  // namespace
+
+// Qr = NULL: the convolution alone.  BRA_ERR_UNSUPPORTED, with nothing enqueued, for maps too wide for its strips.
+int route_rows_lce_bf16(const Dims &D, const float *Qr, const float *Kr, int32_t *Ir, const bf16_t *V, const bf16_t *Wlce, bf16_t *O,
+                        hipStream_t st)
+{
+    StoreJob J = {V, Wlce, O, Tiling{}, D.C / 64, 0};
+    J.T = tiling(D, D.C, 1536 / J.cblocks, J.tiles);
+    const long lce_blocks = ((J.tiles + 1) / 2 * J.cblocks + 7) / 8 * 8;
+    if (D.C % 64 || !route::supported(D) || !offsets_fit(D, J.T, D.C) || lce_blocks > 0x3fffffffL) return BRA_ERR_UNSUPPORTED;
+    const route::Plan p = route::plan(D, D.C);
+    const int rb = Qr ? p.blocks : 0, route_blocks = (rb + 7) / 8 * 8;
+    const size_t smem = std::max(rb ? p.smem : 0, kTapBytes);
+    static bool opted = false;
+    if (!opted && smem > 64 * 1024) {
+        if (hipFuncSetAttribute((const void *)k_route_lce, hipFuncAttributeMaxDynamicSharedMemorySize, mfma::kMaxLds) != hipSuccess) return BRA_ERR_LAUNCH;
+        opted = true;
+    }
+    ProfScope ps(st, rb ? K_MFMA_ROUTE_ROWS : K_MFMA_LCE_ADD);
+    hipLaunchKernelGGL(k_route_lce, dim3((unsigned)(route_blocks + lce_blocks)), dim3(kStoreThreads), smem, st, Qr, Kr, Ir, p.CS, rb, route_blocks, J, D);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
 
 // Maps so wide that not even strips of 5 rows fit (119 million values in a row) take the kernels of bra_lce_dev.h, whose
 // addresses are 64-bit throughout.

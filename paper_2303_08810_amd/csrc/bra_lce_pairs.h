@@ -1,0 +1,218 @@
+// LCE (Eq. 7: depth-wise 5 x 5 correlation, stride 1, zero padding 2) and its gradients on bf16 maps, on the
+// two-element dot product v_dot2_f32_bf16 (two multiply-adds with a float32 sum per lane and instruction).
+//
+// A thread has 2 channels (one 32-bit load per token) of 2 neighbouring columns and walks down a strip of rows with
+// the window of 5 rows x 6 columns in registers.  Per channel and row the left output takes the column pairs (0,1),
+// (2,3), (3,4) against (w0,w1), (w2,w3), (0,w4); the right one the pairs (1,2), (3,4), (4,5) against the same taps.  A
+// pair costs one byte permute.  The zero meets a column that the output takes anyway, in the same channel: an infinity
+// may leave an output as NaN, but nothing reaches another channel or an output further away (columns as loaded, both
+// channels in one operand with w4 in one half, did that: 0 times infinity in the neighbour).
+// The next row is requested a step ahead and nothing is staged through LDS.
+// What bounds it: the dot products and permutes (about 0.4 of the time by instruction count) and, at 3 to 4 wavefronts
+// per SIMD, the latency they do not cover; an LDS-tiled version on float32 multiply-adds took 69 us for all three
+// correlations of a 64 x 56 x 56 x 64 map.
+#pragma once
+
+#include "bra_lce_dev.h"
+
+#include <algorithm>
+
+namespace bra {
+namespace lce {
+
+using mfma::bf16_hi;
+using mfma::bf16_lo;
+using mfma::dot2;
+using mfma::pair_hi;
+using mfma::pair_lo;
+using mfma::u32x2;
+
+// A window row: pairs of columns (0,1), (2,3), (4,5) | (1,2), (3,4) per channel.
+struct Row {
+    unsigned even[2][3], odd[2][2];
+};
+
+// How a workgroup's 8 column-pair slots lie on a map: `pairs` of them side by side, `subs` strips above each other
+// (narrow maps).
+struct Tiling {
+    int pairs, subs, xtiles, ytiles, height;
+};
+
+// The taps of 64 channels from c0 on as operands, through LDS: [ky][(w0,w1) | (w2,w3) | (0,w4)][channel].
+typedef unsigned TapTable[5][3][64];
+constexpr size_t kTapBytes = sizeof(TapTable);
+
+template <bool REVERSED, int NT>
+__device__ __forceinline__ void stage_taps(TapTable &table, const bf16_t *__restrict__ Wlce, int c0, int C)
+{
+    for (int e = threadIdx.x; e < 5 * 64; e += NT) {
+        const int ch = e % 64, ky = e / 64;
+        unsigned t[5];
+#pragma unroll
+        for (int kx = 0; kx < 5; ++kx) {
+            const int tap = 5 * ky + kx;
+            t[kx] = c0 + ch < C ? Wlce[(size_t)(c0 + ch) * 25 + (REVERSED ? 24 - tap : tap)] : 0;
+        }
+        table[ky][0][ch] = t[0] | t[1] << 16;
+        table[ky][1][ch] = t[2] | t[3] << 16;
+        table[ky][2][ch] = t[4] << 16;
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ void load_taps(u32x2 (&w)[5][3], const TapTable &table, int cl)
+{
+#pragma unroll
+    for (int ky = 0; ky < 5; ++ky)
+#pragma unroll
+        for (int t = 0; t < 3; ++t) w[ky][t] = *(const u32x2 *)&table[ky][t][cl];
+}
+
+// One tile for the thread's slot (0 .. 7) and channels c0 + cl, c0 + cl + 1 (live: they exist).
+// GRAD = false: Out = LCE(In), with ADDS added to what is there.
+// GRAD = true:  the same with w the reversed taps (LCE^T), and the tap gradients from the same window (see k_lce_grad in
+//               bra_lce_dev.h for the identities): (V left, V right) against the window's pairs (p, p + 1), 25 sums
+//               per channel added to acc.
+template <bool GRAD, bool ADDS>
+__device__ __forceinline__ void walk_tile(const bf16_t *__restrict__ In, const bf16_t *__restrict__ V, bf16_t *__restrict__ Out, int ldo,
+                                          const Dims &D, const Tiling &T, long tile, int slot, int c0, int cl, bool live,
+                                          const u32x2 (&w)[5][3], float (&acc)[GRAD ? 25 : 1][2])
+{
+    const int px = slot % T.pairs, sub = slot / T.pairs;
+    const int yt = (int)(tile / T.xtiles % T.ytiles), ybase = yt * T.subs * T.height;
+    const int x0 = 2 * ((int)(tile % T.xtiles) * T.pairs + px), y0 = ybase + sub * T.height;
+    const size_t b = tile / ((long)T.xtiles * T.ytiles);
+    if (sub >= T.subs || x0 >= D.W || y0 >= D.H) return;
+    const int y1 = min(y0 + T.height, D.H), ytop = max(ybase - 2, 0);
+    const bool right = x0 + 1 < D.W;
+    // bases are the same for all lanes, lane offsets 32-bit from the tile's first row
+    const char *ibase = (const char *)(In + (b * D.N + (size_t)ytop * D.W) * D.C + c0);
+    const char *vbase = GRAD ? (const char *)(V + (b * D.N + (size_t)ytop * D.W) * D.C + c0) : nullptr;
+    char *obase = (char *)(Out + (b * D.N + (size_t)ytop * D.W) * ldo + c0);
+    const unsigned irow = 2u * D.W * D.C, orow = 2u * D.W * ldo;
+    unsigned xo[6];
+    bool xok[6];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        xok[j] = (unsigned)(x0 + j - 2) < (unsigned)D.W;
+        xo[j] = 2u * (min(max(x0 + j - 2, 0), D.W - 1) * D.C + cl);
+    }
+    const unsigned oo[2] = {2u * (x0 * ldo + cl), 2u * ((right ? x0 + 1 : x0) * ldo + cl)};
+    const bool edge = !__all(xok[0] && xok[1] && xok[4] && xok[5]);
+    auto request_row = [&](int y, unsigned (&raw)[6]) {
+        const unsigned row = (unsigned)(min(max(y, 0), D.H - 1) - ytop) * irow;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) raw[j] = *(const unsigned *)(ibase + (row + xo[j]));
+    };
+    auto pack_row = [&](int y, unsigned (&raw)[6]) {
+        if (edge || (unsigned)y >= (unsigned)D.H) {
+            const bool in = (unsigned)y < (unsigned)D.H;
+#pragma unroll
+            for (int j = 0; j < 6; ++j) raw[j] = in && xok[j] ? raw[j] : 0u;
+        }
+        Row R;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            R.even[0][t] = pair_lo(raw[2 * t], raw[2 * t + 1]);
+            R.even[1][t] = pair_hi(raw[2 * t], raw[2 * t + 1]);
+            if (t == 2) break;
+            R.odd[0][t] = pair_lo(raw[2 * t + 1], raw[2 * t + 2]);
+            R.odd[1][t] = pair_hi(raw[2 * t + 1], raw[2 * t + 2]);
+        }
+        return R;
+    };
+    unsigned next[6], nv[2], nd[2];
+    auto request = [&](int y) {          // what step y needs: row y + 2 of In, Out (and V) of row y
+        const unsigned yc = min(y, D.H - 1) - ytop;
+        request_row(y + 2, next);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (GRAD) nv[j] = *(const unsigned *)(vbase + (yc * irow + xo[j && right ? 3 : 2]));
+            if (ADDS) nd[j] = *(const unsigned *)(obase + (yc * orow + oo[j]));
+        }
+    };
+    Row win[5];
+    {
+        unsigned rows[4][6];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) request_row(y0 + r - 2, rows[r]);
+        request(y0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) win[r] = pack_row(y0 + r - 2, rows[r]);
+    }
+    for (int yb = y0; yb < y1; yb += 5) {
+#pragma unroll
+        for (int u = 0; u < 5; ++u) {
+            const int y = yb + u;
+            if (y >= y1) break;
+            win[(u + 4) % 5] = pack_row(y + 2, next);
+            unsigned vp[2] = {0u, 0u};
+            if (GRAD) {
+                const unsigned vr = right ? nv[1] : 0u;
+                vp[0] = pair_lo(nv[0], vr);
+                vp[1] = pair_hi(nv[0], vr);
+            }
+            float o[2][2] = {{0.f, 0.f}, {0.f, 0.f}};                  // [column][channel]
+            if (ADDS) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    o[j][0] = bf16_lo(nd[j]);
+                    o[j][1] = bf16_hi(nd[j]);
+                }
+            }
+            request(y + 1);
+#pragma unroll
+            for (int r = 0; r < 5; ++r) {
+                const Row &R = win[(u + r) % 5];
+#pragma unroll
+                for (int v = 0; v < 2; ++v) {
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        o[0][v] = dot2(w[r][t][v], R.even[v][t], o[0][v]);
+                        o[1][v] = dot2(w[r][t][v], R.odd[v][t], o[1][v]);
+                    }
+                    o[0][v] = dot2(w[r][2][v], R.odd[v][1], o[0][v]);
+                    o[1][v] = dot2(w[r][2][v], R.even[v][2], o[1][v]);
+                    if (GRAD) {
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) {
+                            acc[5 * r + 2 * t][v] = dot2(vp[v], R.even[v][t], acc[5 * r + 2 * t][v]);
+                            acc[5 * r + 2 * t + 1][v] = dot2(vp[v], R.odd[v][t], acc[5 * r + 2 * t + 1][v]);
+                        }
+                        acc[5 * r + 4][v] = dot2(vp[v], R.even[v][2], acc[5 * r + 4][v]);
+                    }
+                }
+            }
+            if (live) {
+                char *row = obase + (unsigned)(y - ytop) * orow;
+                *(unsigned *)(row + oo[0]) = mfma::pack_bf16(o[0][0], o[0][1]);
+                if (right) *(unsigned *)(row + oo[1]) = mfma::pack_bf16(o[1][0], o[1][1]);
+            }
+        }
+    }
+}
+
+// Lane offsets are 32-bit: the rows of a tile (with the window, within the map) must span less than 2 GiB in either map.
+inline bool offsets_fit(const Dims &D, const Tiling &T, int ldo)
+{
+    return (long)std::min(T.subs * T.height + 4, D.H) * D.W * std::max(D.C, ldo) * 2 < (1L << 31);
+}
+
+// Strips of 20 rows, or 10 or 5 where that leaves fewer than `want` tiles or the rows span too much.
+inline Tiling tiling(const Dims &D, int ldo, long want, long &tiles)
+{
+    Tiling T;
+    const int xp = (D.W + 1) / 2;
+    T.pairs = xp < 8 ? xp : 8;
+    T.xtiles = (xp + T.pairs - 1) / T.pairs;
+    for (T.height = 20;; T.height /= 2) {
+        const int strips = (D.H + T.height - 1) / T.height;
+        T.subs = 8 / T.pairs < strips ? 8 / T.pairs : strips;
+        T.ytiles = (strips + T.subs - 1) / T.subs;
+        tiles = (long)D.B * T.xtiles * T.ytiles;
+        if (T.height == 5 || (tiles >= want && offsets_fit(D, T, ldo))) return T;
+    }
+}
+
+}  // namespace lce
+}  // namespace bra

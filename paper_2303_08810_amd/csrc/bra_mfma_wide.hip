@@ -65,6 +65,16 @@ __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X,
     }
 }
 
+// Four channels of an attention output, added to what is there (LCE(V)) or not.
+__device__ __forceinline__ void store_output(bf16_t *p, f32x4 v, bool adds)
+{
+    if (adds) {
+        const u32x2 u = *(const u32x2 *)p;
+        v += f32x4{bf16_lo(u[0]), bf16_hi(u[0]), bf16_lo(u[1]), bf16_hi(u[1])};
+    }
+    *(u32x2 *)p = pack4(v);
+}
+
 // ---------------------------------------------------------------------------
 // Routed attention (Eq. 6, Eq. 1) for any region size and heads of 32 or 64 channels.  Q comes multiplied by
 // scale * log2(e), so scores are exponents of 2.
@@ -229,8 +239,7 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
             const float inv = 1.0f / cross_row_sum(l[q][hh]);
             if (!store) continue;
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt)
-                *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(acc[q][hh][dt] * inv);
+            for (int dt = 0; dt < NDT; ++dt) store_output(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g, acc[q][hh][dt] * inv, A.adds);
         }
     }
 }
@@ -381,8 +390,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__rest
             const float inv = 1.0f / cross_row_sum(l[q][hh]);
             if (!store) continue;
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt)
-                *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(acc[q][hh][dt] * inv);
+            for (int dt = 0; dt < NDT; ++dt) store_output(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g, acc[q][hh][dt] * inv, A.adds);
         }
     }
 }
@@ -536,16 +544,24 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     int rc = gemm((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, GemmOut{{w.q, w.k, w.v}, D.C, {fq, fk}, nullptr, nullptr, 0, q_scale, pad, GemmRows{}},
                   pooled ? &rj : nullptr, K_MFMA_QKV, st);
     if (rc != BRA_OK) return rc;
-    if (route) {
+    AttnArgs A = {};
+    const bool map_tail = map_tail_supported(D);      // forms the LCE itself
+    if (!map_tail) {
+        // LCE(V) into the output map, to which the attention adds itself: what the convolution needs is there as soon as the
+        // routing's input is, and the routing leaves most of the chip idle
+        rc = lce::route_rows_lce_bf16(D, route ? w.qr : nullptr, w.kr, Ir_dst, w.v, (const bf16_t *)Wlce, w.o, st);
+        if (rc != BRA_OK && rc != BRA_ERR_UNSUPPORTED) return rc;
+        A.adds = rc == BRA_OK;
+    }
+    if (route && !A.adds) {
         rc = route_rows(D, w.qr, w.kr, D.C, Ir_dst, nullptr, st);
         if (rc != BRA_OK) return rc;
-        Ir_src = Ir_dst;
     }
-    AttnArgs A = {};
+    if (route) Ir_src = Ir_dst;
     A.X = (const bf16_t *)X; A.Q = w.q; A.K = w.k; A.V = w.v;
     A.Ir_src = Ir_src; A.Ir_out = Ir_out_opt; A.Wlce = (const bf16_t *)Wlce; A.Y = (bf16_t *)Y;
     A.c_exp = c_exp;
-    if (map_tail_supported(D)) {
+    if (map_tail) {
         rc = launch_map_tail(D, A, w.o, st);
     } else {
         {
@@ -553,7 +569,7 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
             if (D.n <= 32 && D.k <= 1024) launch_attn_rows(D, A, w.o, st);      // its tables fit in LDS
             else launch_attn_gen(D, A, w.o, st);
         }
-        rc = lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);
+        rc = A.adds ? BRA_OK : lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);
     }
     if (rc != BRA_OK) return rc;
     return gemm(w.o, (const bf16_t *)Wo, D.C, M, D.C, D.C,

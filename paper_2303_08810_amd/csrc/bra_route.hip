@@ -1,15 +1,5 @@
-// Region-level routing from float32 Q^r, K^r (Sec. 3.2): rows of A^r = Q^r (K^r)^T (Eq. 4) on the float32
-// matrix-core instruction and their top-k (Eq. 5), for any channel count and up to 1024 regions.
-//
-// Workgroup = (image, 16 query regions), 8 wavefronts.  A pass covers 64 KGP key regions: wavefront w takes key
-// group w / CS (4 tiles of 16 regions) and every CS-th step of 16 channels, with all operands straight from memory
-// (16 bytes per lane and row; the tensors sit in the L2 of the launch before); the channel slices meet in LDS and
-// are added in a fixed order.  Then each wavefront ranks 2 of the rows.
-// The work is tiny (50 MFLOP for 8 x 64 regions of 768 channels) and was bound by a chain of 12 staged channel
-// chunks, about a microsecond each (13.5 us); here the chain is one round of loads, one reduction, one ranking.
-#include "bra_mfma_dev.h"
-
-#include <type_traits>
+// Routing rows on their own (bra_route_dev.h).
+#include "bra_route_dev.h"
 
 namespace bra {
 
@@ -17,166 +7,32 @@ using namespace mfma;
 
 namespace {
 
-constexpr int kRows = 16, kWaves = 8, kPitch = 64 + 4;
-constexpr int kMaxSlots = 16;       // entries of a row per lane: R <= 64 * 16
-
-__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
 template <bool VEC>
-__device__ __forceinline__ f32x4 load4(const float *p, int left)
-{
-    if (VEC) return *(const f32x4 *)p;
-    return f32x4{left > 0 ? p[0] : 0.f, left > 1 ? p[1] : 0.f, left > 2 ? p[2] : 0.f, left > 3 ? p[3] : 0.f};
-}
-
-// The k largest of a row of R > 64 entries, lane j holding entries j, j + 64, ..: rounds of wavefront maximum over
-// the entries not taken yet, the lowest index among equal values (order as in wave_topk).
-template <int SLOTS>
-__device__ void topk_wide(const float *row, int R, int k, int lane, int32_t *out)
-{
-    uint32_t key[SLOTS];
-#pragma unroll
-    for (int t = 0; t < SLOTS; ++t) {
-        const int j = lane + 64 * t;
-        key[t] = j < R ? topk_order_key(row[j], j, R) : 0u;         // a value's key is never 0
-    }
-    for (int p = 0; p < k; ++p) {
-        uint32_t best = 0u;
-        int at = 0;
-#pragma unroll
-        for (int t = 0; t < SLOTS; ++t)
-            if (key[t] > best) { best = key[t]; at = t; }
-        const uint32_t m = wave_umax(best);
-        // lowest index among the holders: the largest complement
-        const int j = lane + 64 * at;
-        const int first = 0x7fffffff - (int)wave_umax(best == m ? (uint32_t)(0x7fffffff - j) : 0u);
-        if (lane == 0) out[p] = first;
-#pragma unroll
-        for (int t = 0; t < SLOTS; ++t)
-            if (first == lane + 64 * t) key[t] = 0u;
-    }
-}
-
-// VEC: C and ld multiples of 4 (16-byte loads).  CS, KGP: channel slices and key groups per pass, CS * KGP = 8.
-template <bool VEC>
-__global__ __launch_bounds__(64 * kWaves) void k_route_rows(const float *__restrict__ Qr, const float *__restrict__ Kr,
+__global__ __launch_bounds__(64 * route::kWaves) void k_route_rows(const float *__restrict__ Qr, const float *__restrict__ Kr,
                                                             int ld, int32_t *__restrict__ Ir, float *__restrict__ Ar,
                                                             Dims D, int CS)
 {
     extern __shared__ __attribute__((aligned(16))) float smem[];
-    float *red = smem;                                  // [wavefront][16 rows][kPitch]
-    float *rows = smem + kWaves * kRows * kPitch;       // [16][row pitch]: the rows of A^r
-    const int KGP = kWaves / CS, groups = (D.R + 63) / 64, pitch = 64 * groups + 4;
-    const int rtiles = (D.R + kRows - 1) / kRows, b = blockIdx.x / rtiles, r0 = (blockIdx.x % rtiles) * kRows;
-    const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
-    const int cs = w % CS, steps = (D.C + 15) / 16;
-    const size_t img = (size_t)b * D.R * ld;
-    const float *qrow = Qr + img + (size_t)min(r0 + i, D.R - 1) * ld;
-    for (int kg0 = 0; kg0 < groups; kg0 += KGP) {
-        const int kg = kg0 + w / CS;
-        f32x4 acc[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (kg < groups) {
-            const float *krow[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) krow[t] = Kr + img + (size_t)min(64 * kg + 16 * t + i, D.R - 1) * ld;
-            // up to NB steps at once: their loads are all requested before the first product (a step past the end
-            // repeats the last one and is blanked)
-            auto batch = [&](int s, auto nb) {
-                constexpr int NB = decltype(nb)::value;
-                f32x4 q[NB], kv[NB][4];
-#pragma unroll
-                for (int u = 0; u < NB; ++u) {
-                    const int c = 16 * min(s + u * CS, steps - 1) + 4 * g, cc = VEC ? min(c, D.C - 4) : c;
-                    q[u] = load4<VEC>(qrow + cc, D.C - c);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) kv[u][t] = load4<VEC>(krow[t] + cc, D.C - c);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int u = 0; u < NB; ++u) {
-                    // channels past the end: blanked on one side
-                    if (16 * (s + u * CS) + 4 * g >= D.C) q[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) acc[t] = mfma_f32(q[u][e], kv[u][t][e], acc[t]);   // D[query 4 g + j][key i]
-                }
-            };
-            for (int s = cs; s < steps;) {
-                const int left = (steps - s + CS - 1) / CS;
-                if (left > 3) {
-                    batch(s, std::integral_constant<int, 6>{});
-                    s += 6 * CS;
-                } else if (left > 1) {
-                    batch(s, std::integral_constant<int, 3>{});
-                    s += 3 * CS;
-                } else {
-                    batch(s, std::integral_constant<int, 1>{});
-                    s += CS;
-                }
-            }
-        }
-        if (kg0) __syncthreads();                        // the previous pass has been added up
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) red[(w * kRows + 4 * g + j) * kPitch + 16 * t + i] = acc[t][j];
-        __syncthreads();
-        for (int e = tid; e < KGP * kRows * 64; e += 64 * kWaves) {
-            const int col = e % 64, row = (e / 64) % kRows, kq = e / (64 * kRows);
-            float s = 0.f;
-            for (int u = 0; u < CS; ++u) s += red[((kq * CS + u) * kRows + row) * kPitch + col];
-            if (kg0 + kq < groups) rows[row * pitch + 64 * (kg0 + kq) + col] = s;
-        }
-    }
-    __syncthreads();
-    const size_t out0 = (size_t)b * D.R + r0;
-    if (Ar) {
-        for (int row = w; row < kRows && r0 + row < D.R; row += kWaves)
-            for (int j = lane; j < D.R; j += 64) Ar[(out0 + row) * D.R + j] = rows[row * pitch + j];
-    }
-    const int first = 2 * w, nrows = min(2, D.R - r0 - first);
-    if (nrows <= 0) return;
-    if (groups == 1) {
-        const float v[2] = {rows[first * pitch + lane], rows[(first + 1) * pitch + lane]};
-        wave_topk_rows<2>(v, nrows, lane, D.R, D.k, Ir + (out0 + first) * D.k);
-    } else {
-        for (int rr = 0; rr < nrows; ++rr) {
-            const float *row = rows + (first + rr) * pitch;
-            int32_t *out = Ir + (out0 + first + rr) * D.k;
-            if (groups <= 4) topk_wide<4>(row, D.R, D.k, lane, out);
-            else topk_wide<kMaxSlots>(row, D.R, D.k, lane, out);
-        }
-    }
+    route::route_block<VEC, 6>(Qr, Kr, ld, Ir, Ar, D, CS, blockIdx.x, smem);
 }
 
 }  // namespace
 
 int route_rows(const Dims &D, const float *Qr, const float *Kr, int ld, int32_t *Ir, float *Ar_opt, hipStream_t st)
 {
-    if (D.R > kWave * kMaxSlots) return BRA_ERR_UNSUPPORTED;
-    const int steps = (D.C + 15) / 16, groups = (D.R + 63) / 64;
-    // channel slices: as many as there are steps, but no more than leaves work for all wavefronts on the key groups
-    int CS = kWaves;
-    while (CS > 1 && (CS > steps || kWaves / CS < std::min(groups, 4))) CS /= 2;
-    const size_t smem = (size_t)(kWaves * kRows * kPitch + kRows * (64 * groups + 4)) * sizeof(float);
-    const bool vec = D.C % 4 == 0 && ld % 4 == 0;
+    if (!route::supported(D)) return BRA_ERR_UNSUPPORTED;
+    const route::Plan p = route::plan(D, ld);
     static bool opted = false;
-    if (!opted && smem > 64 * 1024) {
+    if (!opted && p.smem > 64 * 1024) {
         if (hipFuncSetAttribute((const void *)k_route_rows<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess ||
             hipFuncSetAttribute((const void *)k_route_rows<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess)
             return BRA_ERR_LAUNCH;
         opted = true;
     }
-    const unsigned grid = (unsigned)((long)D.B * ((D.R + kRows - 1) / kRows));
     ProfScope ps(st, K_MFMA_ROUTE_ROWS);
-    if (vec) hipLaunchKernelGGL(k_route_rows<true>, dim3(grid), dim3(64 * kWaves), smem, st, Qr, Kr, ld, Ir, Ar_opt, D, CS);
-    else hipLaunchKernelGGL(k_route_rows<false>, dim3(grid), dim3(64 * kWaves), smem, st, Qr, Kr, ld, Ir, Ar_opt, D, CS);
+    const dim3 grid((unsigned)p.blocks), threads(64 * route::kWaves);
+    if (p.vec) hipLaunchKernelGGL(k_route_rows<true>, grid, threads, p.smem, st, Qr, Kr, ld, Ir, Ar_opt, D, p.CS);
+    else hipLaunchKernelGGL(k_route_rows<false>, grid, threads, p.smem, st, Qr, Kr, ld, Ir, Ar_opt, D, p.CS);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
