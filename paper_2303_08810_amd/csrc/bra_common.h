@@ -142,9 +142,6 @@ size_t padded_workspace_bytes(const Dims &Dp, size_t bra_bytes);
 int padded_forward(const Dims &Dp, int H, int W, const void *X, const void *Wqkv, const void *Wo, const void *Wlce,
                    void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, int path, hipStream_t st);
 
-// Q, K, V = X Wqkv into three token maps for any C that is a multiple of 64 (bra_mfma_wide.hip).
-int wide_project_qkv(const Dims &D, const void *X, const void *Wqkv, bf16_t *Q, bf16_t *K, bf16_t *V, float q_scale, hipStream_t st);
-
 // Backward pass with fixed routing on the matrix cores (bra_mfma_bwd.hip).
 bool mfma_backward_supported(const Dims &D);
 size_t mfma_backward_workspace_bytes(const Dims &D);

@@ -41,6 +41,14 @@ int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, co
 // Out = In Wt^T: Wt [Nout][ldw], the contraction axis contiguous.
 int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout, bf16_t *Out, int kernel_id, hipStream_t st);
 
+// Out = In W and Out = In Wt^T (b.W is Wt) over the same M rows and contraction, in one launch.
+struct GemmHalf {
+    const bf16_t *In, *W;
+    int ldw, Nout;
+    GemmOut out;
+};
+int gemm_pair(const GemmHalf &a, const GemmHalf &b, long M, int K, int kernel_id, hipStream_t st);
+
 // Contractions over all M tokens: Part[share][KA][N] = A^T B over the share's tokens, for two products in one launch with
 // gemm_tn_shares(M, ..) shares each (their sum, in a fixed order, is the product).  Sizes and pitches multiples of 8.
 struct GemmTn {

@@ -165,24 +165,16 @@ __device__ __forceinline__ long stored_row(const GemmRows &r, int m)
     return y < r.H && x < r.W ? ((long)b * r.H + y) * r.W + x : -1;
 }
 
+// Workgroups of an XCD take neighbouring tiles, the output tiles of the same rows one after the other (swizzled()).
 // EXT: bias, GELU, residual or rows that are not in memory (GemmRows).  NB: buffers, 1 for K = 64, else 2.
-template <int BM, int BN, int NB, bool REGIONS, bool BT, bool EXT>
-__global__ __launch_bounds__(256, BM == 64 && BN == 64 ? 3 : 2) void k_gemm_dma(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw,
-                                                  int M, int K, int Nout, GemmOut out, GemmRegions reg, int reg_blocks)
+// lds: NB chunks of In and of W.
+template <int BM, int BN, int NB, bool BT, bool EXT>
+__device__ __forceinline__ void dma_tile(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int M, int K, int Nout,
+                                         const GemmOut &out, int block, bf16_t *lds)
 {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int AE = BM * 64, BE = BN * 64;     // elements of a chunk
-    bf16_t *lds = (bf16_t *)smem;                 // buffers of a chunk of In, then W, each
-    if (REGIONS && (int)blockIdx.x < reg_blocks) {
-        bf16_t *const planes[3] = {lds, lds + 64 * kGemmPitch, lds + 2 * 64 * kGemmPitch};
-        gemm64<2>(reg, W, ldw, K, blockIdx.x, lds + 3 * 64 * kGemmPitch, planes);
-        return;
-    }
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, h = lane / 32, c = lane % 32;
     const int otiles = (Nout + BN - 1) / BN;
-    // workgroups of an XCD take neighbouring tiles, the output tiles of the same rows one after the other
-    const int nb = (int)gridDim.x - reg_blocks, per_xcd = nb / 8, bi = (int)blockIdx.x - reg_blocks;
-    const int block = (bi % 8) * per_xcd + bi / 8;
     const int m0 = (block / otiles) * BM, o0 = (block % otiles) * BN;
     if (m0 >= M) return;                          // the grid is rounded up to a multiple of 8
 
@@ -337,22 +329,57 @@ __global__ __launch_bounds__(256, BM == 64 && BN == 64 ? 3 : 2) void k_gemm_dma(
 }
 
 template <int BM, int BN, int NB, bool REGIONS, bool BT, bool EXT>
+__global__ __launch_bounds__(256, BM == 64 && BN == 64 ? 3 : 2) void k_gemm_dma(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw,
+                                                  int M, int K, int Nout, GemmOut out, GemmRegions reg, int reg_blocks)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    bf16_t *lds = (bf16_t *)smem;
+    if (REGIONS && (int)blockIdx.x < reg_blocks) {
+        bf16_t *const planes[3] = {lds, lds + 64 * kGemmPitch, lds + 2 * 64 * kGemmPitch};
+        gemm64<2>(reg, W, ldw, K, blockIdx.x, lds + 3 * 64 * kGemmPitch, planes);
+        return;
+    }
+    dma_tile<BM, BN, NB, BT, EXT>(In, W, ldw, M, K, Nout, out, swizzled((int)blockIdx.x - reg_blocks, (int)gridDim.x - reg_blocks), lds);
+}
+
+// Two products over the same rows and contraction in one launch: Q, K, V = X Wqkv and dO = dY Wo^T (W transposed).  12544 x 384:
+// 24.1 us, 29.8 as two launches; 2048 x 768 13.1 and 23.
+template <int BM, int BN, int NB>
+__global__ __launch_bounds__(256, BM == 64 && BN == 64 ? 3 : 2) void k_gemm_pair(const bf16_t *__restrict__ In0, const bf16_t *__restrict__ W0, int ldw0, int Nout0,
+                                                  GemmOut out0, const bf16_t *__restrict__ In1, const bf16_t *__restrict__ W1, int ldw1, int Nout1,
+                                                  GemmOut out1, int M, int K, int blocks0)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int bi = blockIdx.x;
+    if (bi < blocks0) dma_tile<BM, BN, NB, false, false>(In0, W0, ldw0, M, K, Nout0, out0, swizzled(bi, blocks0), (bf16_t *)smem);
+    else dma_tile<BM, BN, NB, true, false>(In1, W1, ldw1, M, K, Nout1, out1, swizzled(bi - blocks0, (int)gridDim.x - blocks0), (bf16_t *)smem);
+}
+
+template <int BM, int BN>
+long tile_blocks(long M, int Nout) { return ((M + BM - 1) / BM * ((Nout + BN - 1) / BN) + 7) / 8 * 8; }
+
+// LDS of a workgroup.  A single chunk: four workgroups per compute unit (with eight, 200704 x 64 x 64 takes 13.7 us instead of 12.9).
+template <int BM, int BN, int NB>
+constexpr size_t ring_bytes() { return NB == 1 ? 40 * 1024 : (size_t)NB * (BM + BN) * 64 * 2; }
+
+template <typename K>
+bool opt_in(K kernel, bool &done)
+{
+    if (!done) done = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) == hipSuccess;
+    return done;
+}
+
+template <int BM, int BN, int NB, bool REGIONS, bool BT, bool EXT>
 int launch_dma_t(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out,
                const GemmRegions &reg, hipStream_t st)
 {
     static bool opted = false;
-    if (!opted) {
-        if (hipFuncSetAttribute((const void *)k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess)
-            return BRA_ERR_LAUNCH;
-        opted = true;
-    }
-    const long tiles = (M + BM - 1) / BM * ((Nout + BN - 1) / BN), blocks = (tiles + 7) / 8 * 8;
+    if (!opt_in(k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT>, opted)) return BRA_ERR_LAUNCH;
+    const long blocks = tile_blocks<BM, BN>(M, Nout);
     const long rb = REGIONS ? (reg.M + 63) / 64 * ((reg.Nout + 63) / 64) : 0;
     if (blocks + rb > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    // a single chunk: four workgroups per compute unit (with eight, 200704 x 64 x 64 takes 13.7 us instead of 12.9)
-    const size_t ring = NB == 1 ? 40 * 1024 : (size_t)NB * (BM + BN) * 64 * 2, region = REGIONS ? kGemm64Bytes : 0;
-    hipLaunchKernelGGL((k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT>), dim3((unsigned)(blocks + rb)), dim3(256), std::max(ring, region), st, In, W, ldw,
-                       (int)M, K, Nout, out, reg, (int)rb);
+    hipLaunchKernelGGL((k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT>), dim3((unsigned)(blocks + rb)), dim3(256),
+                       std::max(ring_bytes<BM, BN, NB>(), REGIONS ? kGemm64Bytes : 0), st, In, W, ldw, (int)M, K, Nout, out, reg, (int)rb);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -367,28 +394,51 @@ int launch_dma(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int No
     return launch_dma_t<BM, BN, NB, REGIONS, BT, false>(In, W, ldw, M, K, Nout, out, reg, st);
 }
 
+enum Tile { kOneChunk, kWide, kMid, kNarrow };
+
+// One chunk: no tile reads anything twice, small ones overlap their loads and stores best (126464 x 64 x 192: 14.0 us, 14.8
+// with 64 x 128, 15.6 with 128 x 128).
+// Wide tiles read less per product, narrow ones deal out more evenly over the 256 compute units.  Time is that of the
+// compute unit with the most tiles: 744, 433 or 260 for one of 128 x 128, 64 x 128 or 64 x 64 (12544 x 768 x 2304:
+// 52.1, 60.7 and 71.1 us for 7, 14 and 28 tiles), three tenths more where it has a single one and nothing to overlap it
+// with.  Measured, 128 x 128 / 64 x 128 / 64 x 64 (us): 8192 x 768 x 2304: 37.2 / 38.9 / 47.1; 8192 x 768 x 768: 15.9 / 14.6 /
+// 17.1; 12544 x 1152 x 384: 20.8 / 19.3 / 21.9; 12544 x 512 x 512: 12.4 / 14.0 / 12.7; 3136 x 768 x 768: 9.9 / 9.3 / 8.3;
+// 12544 x 256 x 768: 12.2 / 11.2 / 12.0; 1568 x 384 x 1152: 6.6 / 5.2 / 4.8.  A third buffer, 256 x 128 tiles with 8 wavefronts
+// and chunks of 32 gained nothing.
+// Nout1: columns of a second product over the same rows.
+Tile pick_tile(long M, int K, int Nout, int Nout1 = 0)
+{
+    if (K == 64) return kOneChunk;
+    auto cost = [&](int bm, int bn, long tile) {
+        const long rounds = ((M + bm - 1) / bm * ((Nout + bn - 1) / bn + (Nout1 + bn - 1) / bn) + 255) / 256;
+        return tile * rounds * (rounds == 1 ? 13 : 10);
+    };
+    const long wide = cost(128, 128, 744), mid = cost(64, 128, 433), narrow = cost(64, 64, 260);
+    return wide <= mid && wide <= narrow ? kWide : mid <= narrow ? kMid : kNarrow;
+}
+
 template <bool REGIONS, bool BT = false>
 int launch_big(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, const GemmRegions &reg,
                hipStream_t st)
 {
-    // One chunk: no tile reads anything twice, small ones overlap their loads and stores best (126464 x 64 x 192: 14.0 us, 14.8
-    // with 64 x 128, 15.6 with 128 x 128).
-    if (K == 64) return launch_dma<64, 64, 1, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
-    // Wide tiles read less per product, narrow ones deal out more evenly over the 256 compute units.  Time is that of the
-    // compute unit with the most tiles: 744, 433 or 260 for one of 128 x 128, 64 x 128 or 64 x 64 (12544 x 768 x 2304:
-    // 52.1, 60.7 and 71.1 us for 7, 14 and 28 tiles), three tenths more where it has a single one and nothing to overlap it
-    // with.  Measured, 128 x 128 / 64 x 128 / 64 x 64 (us): 8192 x 768 x 2304: 37.2 / 38.9 / 47.1; 8192 x 768 x 768: 15.9 / 14.6 /
-    // 17.1; 12544 x 1152 x 384: 20.8 / 19.3 / 21.9; 12544 x 512 x 512: 12.4 / 14.0 / 12.7; 3136 x 768 x 768: 9.9 / 9.3 / 8.3;
-    // 12544 x 256 x 768: 12.2 / 11.2 / 12.0; 1568 x 384 x 1152: 6.6 / 5.2 / 4.8.  A third buffer, 256 x 128 tiles with 8 wavefronts
-    // and chunks of 32 gained nothing.
-    auto cost = [&](int bm, int bn, long tile) {
-        const long rounds = ((M + bm - 1) / bm * ((Nout + bn - 1) / bn) + 255) / 256;
-        return tile * rounds * (rounds == 1 ? 13 : 10);
-    };
-    const long wide = cost(128, 128, 744), mid = cost(64, 128, 433), narrow = cost(64, 64, 260);
-    if (wide <= mid && wide <= narrow) return launch_dma<128, 128, 2, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
-    if (mid <= narrow) return launch_dma<64, 128, 2, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
-    return launch_dma<64, 64, 2, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
+    switch (pick_tile(M, K, Nout)) {
+    case kOneChunk: return launch_dma<64, 64, 1, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
+    case kWide: return launch_dma<128, 128, 2, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
+    case kMid: return launch_dma<64, 128, 2, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
+    default: return launch_dma<64, 64, 2, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
+    }
+}
+
+template <int BM, int BN, int NB>
+int launch_pair(const GemmHalf &a, const GemmHalf &b, long M, int K, hipStream_t st)
+{
+    static bool opted = false;
+    if (!opt_in(k_gemm_pair<BM, BN, NB>, opted)) return BRA_ERR_LAUNCH;
+    const long b0 = tile_blocks<BM, BN>(M, a.Nout), b1 = tile_blocks<BM, BN>(M, b.Nout);
+    if (b0 + b1 > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((k_gemm_pair<BM, BN, NB>), dim3((unsigned)(b0 + b1)), dim3(256), (ring_bytes<BM, BN, NB>()), st, a.In, a.W, a.ldw, a.Nout, a.out,
+                       b.In, b.W, b.ldw, b.Nout, b.out, (int)M, K, (int)b0);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
 // ---------------------------------------------------------------------------
@@ -408,24 +458,12 @@ struct ProjLds {
     static constexpr size_t bytes = BT ? (size_t)N * pitch * 2 : (size_t)(K * pitch + K / 8 * 64) * 2;
 };
 
+// W into LDS.
 template <int K, int N, bool BT>
-__global__ __launch_bounds__(1024) void k_proj(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw, long M,
-                                               int per_group, GemmOut out)
+__device__ __forceinline__ void proj_stage(bf16_t *Ws, const bf16_t *__restrict__ W, int ldw)
 {
-    typedef ProjLds<K, N, BT> L;
-    constexpr int P = L::pitch, KS = K / 32, TP = N / 32;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    bf16_t *Ws = (bf16_t *)smem;
-    const int T = blockDim.x, tid = threadIdx.x, waves = T / kWave;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
-    const long tiles = (M + 15) / 16, first = (long)blockIdx.x * per_group, last = min(tiles, first + per_group);
-    bf16x8 x[2][KS];
-    auto fetch = [&](long tile, bf16x8 (&r)[KS]) {
-        const bf16_t *row = In + min(min(tile, tiles - 1) * 16 + i, M - 1) * K + 8 * g;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) r[ks] = *(const bf16x8 *)(row + 32 * ks);
-    };
-    fetch(first + wave, x[0]);
+    constexpr int P = ProjLds<K, N, BT>::pitch;
+    const int T = blockDim.x, tid = threadIdx.x;
     if (BT) {
         for (int e = tid; e < N * (K / 8); e += T) {
             const int o = e / (K / 8), k8 = e % (K / 8);
@@ -440,54 +478,88 @@ __global__ __launch_bounds__(1024) void k_proj(const bf16_t *__restrict__ In, co
             *(u32x2 *)(dst + 16) = u32x2{v[2], v[3]};
         }
     }
-    __syncthreads();
-    int again = 0;      // set anew for every tile: the operands are not kept in registers across tiles
+}
+
+// One tile of 16 rows: xf its operands.  again: set anew by the caller for every tile, so that the operands are not kept in
+// registers across tiles.
+template <int K, int N, bool BT>
+__device__ __forceinline__ void proj_tile(const bf16_t *Ws, int again, const bf16x8 (&xf)[K / 32], long t, long M, const GemmOut &out)
+{
+    constexpr int P = ProjLds<K, N, BT>::pitch, KS = K / 32, TP = N / 32;
+    const int lane = threadIdx.x % kWave, g = lane / 16, i = lane % 16;
     auto operand = [&](int tp, int half, int ks) {
         if (BT) return *(const bf16x8 *)(Ws + again + (32 * tp + 8 * (i / 4) + 4 * half + i % 4) * P + 32 * ks + 8 * g);
-        const bf16_t *p = Ws + (32 * ks + 8 * g + i / 4) * P + (4 * ks + g) * 64 + 32 * tp + 16 * half + 4 * (i % 4);
+        const bf16_t *p = Ws + (32 * ks + 8 * g + i / 4) * P + (4 * ks + g) * 64 + 32 * tp + 16 * half + 4 * (i % 4) + again;
         const u32x2 r0 = __builtin_bit_cast(u32x2, lds_read_tr16(p)), r1 = __builtin_bit_cast(u32x2, lds_read_tr16(p + 4 * P));
         return __builtin_bit_cast(bf16x8, u32x4{r0[0], r0[1], r1[0], r1[1]});
     };
-    auto tile = [&](long t, const bf16x8 (&xf)[KS]) {
-        asm volatile("" : "+s"(again));
-        const long m = t * 16 + i;
-        const size_t at = (size_t)min(m, M - 1) * K + 8 * g;
+    const long m = t * 16 + i;
+    const size_t at = (size_t)min(m, M - 1) * K + 8 * g;
 #pragma unroll
-        for (int tp = 0; tp < TP; ++tp) {
-            f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    for (int tp = 0; tp < TP; ++tp) {
+        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int half = 0; half < 2; ++half) acc[half] = mfma16(operand(tp, half, ks), xf[ks], acc[half]);
-            const float scale = 32 * tp < K ? out.scale0 : 1.0f;
-            const float v[8] = {acc[0][0] * scale, acc[0][1] * scale, acc[0][2] * scale, acc[0][3] * scale,
-                                acc[1][0] * scale, acc[1][1] * scale, acc[1][2] * scale, acc[1][3] * scale};
-            if (m < M) *(bf16x8 *)((bf16_t *)out.buf[32 * tp / K] + at + 32 * tp % K) = pack8(v);
-        }
-    };
-    for (long t = first + wave; t < last; t += 2 * waves) {
-        fetch(t + waves, x[1]);
-        tile(t, x[0]);
-        if (t + waves >= last) break;
-        fetch(t + 2 * waves, x[0]);
-        tile(t + waves, x[1]);
+            for (int half = 0; half < 2; ++half) acc[half] = mfma16(operand(tp, half, ks), xf[ks], acc[half]);
+        const float scale = 32 * tp < K ? out.scale0 : 1.0f;
+        const float v[8] = {acc[0][0] * scale, acc[0][1] * scale, acc[0][2] * scale, acc[0][3] * scale,
+                            acc[1][0] * scale, acc[1][1] * scale, acc[1][2] * scale, acc[1][3] * scale};
+        if (m < M) *(bf16x8 *)((bf16_t *)out.buf[32 * tp / K] + at + 32 * tp % K) = pack8(v);
     }
 }
 
-template <int K, int N, bool BT>
-int launch_proj_t(const bf16_t *In, const bf16_t *W, int ldw, long M, const GemmOut &out, hipStream_t st)
+// PAIR: the workgroup also holds a K x K matrix W1, given transposed, and forms Out1 = In1 W1^T for its rows (Q, K, V and dO of the
+// backward pass; 64 x 56 x 56 x 64: 35.5 us for 39 in two launches, 25088 x 128: 24.9 for 29).
+template <int K, int N, bool PAIR>
+__global__ __launch_bounds__(1024) void k_proj(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw, long M,
+                                               int per_group, GemmOut out, const bf16_t *__restrict__ In1, const bf16_t *__restrict__ W1, int ldw1, GemmOut out1)
+{
+    constexpr int KS = K / 32;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    bf16_t *Ws = (bf16_t *)smem, *W1s = (bf16_t *)(smem + ProjLds<K, N, false>::bytes);
+    const int T = blockDim.x, tid = threadIdx.x, waves = T / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const long tiles = (M + 15) / 16, first = (long)blockIdx.x * per_group, last = min(tiles, first + per_group);
+    bf16x8 x[2][KS], y[2][KS];
+    auto fetch = [&](long tile, int set) {
+        const size_t row = (size_t)min(min(tile, tiles - 1) * 16 + i, M - 1) * K + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            x[set][ks] = *(const bf16x8 *)(In + row + 32 * ks);
+            if (PAIR) y[set][ks] = *(const bf16x8 *)(In1 + row + 32 * ks);
+        }
+    };
+    fetch(first + wave, 0);
+    proj_stage<K, N, false>(Ws, W, ldw);
+    if (PAIR) proj_stage<K, K, true>(W1s, W1, ldw1);
+    __syncthreads();
+    int again = 0;
+    auto work = [&](long t, int set) {
+        asm volatile("" : "+s"(again));
+        proj_tile<K, N, false>(Ws, again, x[set], t, M, out);
+        if (PAIR) proj_tile<K, K, true>(W1s, again, y[set], t, M, out1);
+    };
+    for (long t = first + wave; t < last; t += 2 * waves) {
+        fetch(t + waves, 1);
+        work(t, 0);
+        if (t + waves >= last) break;
+        fetch(t + 2 * waves, 0);
+        work(t + waves, 1);
+    }
+}
+
+template <int K, int N, bool PAIR = false>
+int launch_proj_t(const bf16_t *In, const bf16_t *W, int ldw, long M, const GemmOut &out, hipStream_t st, const GemmHalf &second = GemmHalf{})
 {
     static bool opted = false;
-    if (!opted) {
-        if (hipFuncSetAttribute((const void *)k_proj<K, N, BT>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess)
-            return BRA_ERR_LAUNCH;
-        opted = true;
-    }
+    if (!opt_in(k_proj<K, N, PAIR>, opted)) return BRA_ERR_LAUNCH;
     // as many wavefronts as deal out a compute unit's share of the tiles in even rounds
     const long tiles = (M + 15) / 16, per = (tiles + 255) / 256, rounds = (per + 15) / 16;
     const int waves = (int)std::max(4L, (per + rounds - 1) / rounds);
-    hipLaunchKernelGGL((k_proj<K, N, BT>), dim3((unsigned)((tiles + per - 1) / per)), dim3(64 * waves), (ProjLds<K, N, BT>::bytes), st,
-                       In, W, ldw, M, (int)per, out);
+    hipLaunchKernelGGL((k_proj<K, N, PAIR>), dim3((unsigned)((tiles + per - 1) / per)), dim3(64 * waves),
+                       (ProjLds<K, N, false>::bytes + (PAIR ? ProjLds<K, K, true>::bytes : 0)), st, In, W, ldw, M, (int)per, out, second.In, second.W,
+                       second.ldw, second.out);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -504,8 +576,8 @@ bool proj_ok(long M, int K, int N, const GemmOut &out, bool regions)
 
 int launch_proj(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int N, const GemmOut &out, hipStream_t st)
 {
-    if (K == 64) return launch_proj_t<64, 192, false>(In, W, ldw, M, out, st);
-    return N == K ? launch_proj_t<128, 128, false>(In, W, ldw, M, out, st) : launch_proj_t<128, 384, false>(In, W, ldw, M, out, st);
+    if (K == 64) return launch_proj_t<64, 192>(In, W, ldw, M, out, st);
+    return N == K ? launch_proj_t<128, 128>(In, W, ldw, M, out, st) : launch_proj_t<128, 384>(In, W, ldw, M, out, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -646,8 +718,22 @@ int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout
     if (!sizes_ok(M, K, Nout)) return BRA_ERR_UNSUPPORTED;
     const GemmOut out = {{Out, nullptr, nullptr}, Nout, {nullptr, nullptr}, nullptr, nullptr, 0};
     ProfScope ps(st, kernel_id);
-    if (K == Nout && proj_ok(M, K, Nout, out, false)) return launch_proj_t<128, 128, true>(In, Wt, ldw, M, out, st);
     return launch_big<false, true>(In, Wt, ldw, M, K, Nout, out, GemmRegions{}, st);
+}
+
+int gemm_pair(const GemmHalf &a, const GemmHalf &b, long M, int K, int kernel_id, hipStream_t st)
+{
+    if (!sizes_ok(M, K, a.Nout) || !sizes_ok(M, K, b.Nout)) return BRA_ERR_UNSUPPORTED;
+    ProfScope ps(st, kernel_id);
+    if (b.Nout == K && proj_ok(M, K, a.Nout, a.out, false) && a.Nout == 3 * K)
+        return K == 64 ? launch_proj_t<64, 192, true>(a.In, a.W, a.ldw, M, a.out, st, b) : launch_proj_t<128, 384, true>(a.In, a.W, a.ldw, M, a.out, st, b);
+    // tiles of both together
+    switch (pick_tile(M, K, a.Nout, b.Nout)) {
+    case kOneChunk: return launch_pair<64, 64, 1>(a, b, M, K, st);
+    case kWide: return launch_pair<128, 128, 2>(a, b, M, K, st);
+    case kMid: return launch_pair<64, 128, 2>(a, b, M, K, st);
+    default: return launch_pair<64, 64, 2>(a, b, M, K, st);
+    }
 }
 
 // Two workgroups per compute unit over the 128 x 128 blocks of both products.

@@ -7,45 +7,20 @@ namespace lce {
 
 namespace {
 
-// GRAD = false: Out += LCE(In).
-// GRAD = true:  Out += LCE^T(In) and the tap gradients, summed over the workgroup's tiles: Part[group][C][25].
-template <bool GRAD>
-__global__ __launch_bounds__(256) void k_lce_pairs(const bf16_t *__restrict__ In, const bf16_t *__restrict__ V,
-                                                   const bf16_t *__restrict__ Wlce, bf16_t *__restrict__ Out, int ldo,
-                                                   float *__restrict__ Part, Dims D, Tiling T, int cblocks, long tiles,
-                                                   int tiles_per_wg)
+__global__ __launch_bounds__(256) void k_lce_add(Job J, Dims D)
 {
-    __shared__ __attribute__((aligned(16))) float red[GRAD ? 25 * 256 : kTapBytes / 4];
-    const int block = mfma::swizzled_block(), cb = block % cblocks, c0 = 64 * cb, grp = block / cblocks;
-    const long first = (long)grp * tiles_per_wg, last = min(tiles, first + tiles_per_wg);
-    if (first >= tiles) return;
-    const int cp = threadIdx.x % 32, slot = threadIdx.x / 32;
-    TapTable &table = *(TapTable *)red;
-    stage_taps<GRAD, 256>(table, Wlce, c0, D.C);
-    const bool live = c0 + 2 * cp < D.C;
-    const int cl = live ? 2 * cp : 0;
-    u32x2 w[5][3];
-    load_taps(w, table, cl);
-    float acc[GRAD ? 25 : 1][2];
-#pragma unroll
-    for (int t = 0; t < (GRAD ? 25 : 1); ++t) acc[t][0] = acc[t][1] = 0.f;
-    if (GRAD) __syncthreads();
-    for (long tile = first; tile < last; ++tile) walk_tile<GRAD, true>(In, V, Out, ldo, D, T, tile, slot, c0, cl, live, w, acc);
-    if (!GRAD) return;
-    // the 8 slots' sums of a channel through LDS, added in a fixed order
-#pragma unroll
-    for (int v = 0; v < 2; ++v) {
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < (GRAD ? 25 : 1); ++t) red[t * 256 + threadIdx.x] = acc[t][v];
-        __syncthreads();
-        for (int e = threadIdx.x; e < 25 * 32; e += 256) {
-            const int t = e / 32, ch = c0 + 2 * (e % 32) + v;
-            float s = 0.f;
-            for (int k = 0; k < 8; ++k) s += red[t * 256 + k * 32 + e % 32];
-            if (ch < D.C) Part[((size_t)grp * D.C + ch) * 25 + 24 - t] = s;
-        }
-    }
+    __shared__ __attribute__((aligned(16))) float lds[job_bytes<false>() / 4];
+    job_block<false, true>(J, D, mfma::swizzled_block(), lds);
+}
+
+// dV += LCE^T(dO) with the tap gradients, and O += LCE(V), in one launch (two launches took 41.6 us for 64 x 14 x 14 x 384, this
+// one 26.6).
+__global__ __launch_bounds__(256) void k_lce_backward(Job grad, Job add, int grad_blocks, Dims D)
+{
+    __shared__ __attribute__((aligned(16))) float lds[job_bytes<true>() / 4];
+    const int bi = blockIdx.x;
+    if (bi < grad_blocks) job_block<true, true>(grad, D, mfma::swizzled(bi, grad_blocks), lds);
+    else job_block<false, true>(add, D, mfma::swizzled(bi - grad_blocks, (int)gridDim.x - grad_blocks), lds);
 }
 
 // Out = LCE(In) beside the rows of A^r and their top-k: the routing is a chain of latencies on a few workgroups (13 us for
@@ -54,16 +29,8 @@ __global__ __launch_bounds__(256) void k_lce_pairs(const bf16_t *__restrict__ In
 // as a layer of 2 x 200 x 300 x 64, S = 16, and 124.0 of 8 x 32 x 32 x 768; with the convolution here 113.6 and 110.
 constexpr int kStoreThreads = 64 * route::kWaves;
 
-struct StoreJob {
-    const bf16_t *In, *Wlce;
-    bf16_t *Out;
-    Tiling T;
-    int cblocks;
-    long tiles;
-};
-
 __global__ __launch_bounds__(kStoreThreads, 4) void k_route_lce(const float *__restrict__ Qr, const float *__restrict__ Kr, int32_t *__restrict__ Ir,
-                                                                int CS, int rows_blocks, int route_blocks, StoreJob J, Dims D)
+                                                                int CS, int rows_blocks, int route_blocks, Job J, Dims D)
 {
     extern __shared__ __attribute__((aligned(16))) float smem[];
     const int bi = blockIdx.x;
@@ -86,12 +53,48 @@ __global__ __launch_bounds__(kStoreThreads, 4) void k_route_lce(const float *__r
 
 }  // namespace
 
+namespace {
+
+Job plain_job(const Dims &D, const bf16_t *In, const bf16_t *Wlce, bf16_t *Out, int ldo)
+{
+    Job J = {In, nullptr, Wlce, Out, nullptr, ldo, (D.C + 63) / 64, 1, 0, Tiling{}};
+    J.T = tiling(D, ldo, 1536 / J.cblocks, J.tiles);
+    return J;
+}
+
+// Workgroups with tap gradients, each with the tiles of one group: two per compute unit, so that the third place is left to
+// the kernel beside them (query side of 64 x 56 x 56 x 64, k = 1, with the pass in front: 55.4 us, 57.8 with three per compute
+// unit; the two passes alone for 64 x 14 x 14 x 384: 26.6 and 30.3).  Workgroups of the other pass, behind the key side: three
+// per compute unit (28 x 28 x 128 at B = 64: 40 us, 42 with one tile each; two per compute unit: 41, but 65 for 57 at 64 channels).
+constexpr int kGradSlots = 512, kAddSlots = 768;
+
+Job job(const Dims &D, const bf16_t *In, const bf16_t *V, const bf16_t *Wlce, bf16_t *Out, int ldo, float *Part, int workgroups)
+{
+    Job J = {In, V, Wlce, Out, Part, ldo, (D.C + 63) / 64, 1, 0, Tiling{}};
+    const long want = std::max(1, workgroups / J.cblocks);
+    J.T = tiling(D, ldo, want, J.tiles);
+    J.per_wg = (int)((J.tiles + want - 1) / want);
+    return J;
+}
+
+LcePlan wide_grad_plan(const Dims &D) { return lce_plan(D, 768, 8); }      // 8 columns per workgroup: two channels per thread
+
+}  // namespace
+
+BackwardJobs backward_jobs(const Dims &D, const bf16_t *dO, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, bf16_t *dV, int lddv, float *Part)
+{
+    BackwardJobs L;
+    L.grad = job(D, dO, V, Wlce, dV, lddv, Part, kGradSlots);
+    L.add = job(D, V, nullptr, Wlce, O, D.C, nullptr, kAddSlots);
+    L.fit = offsets_fit(D, L.grad.T, lddv) && offsets_fit(D, L.add.T, D.C);
+    return L;
+}
+
 // Qr = NULL: the convolution alone.  BRA_ERR_UNSUPPORTED, with nothing enqueued, for maps too wide for its strips.
 int route_rows_lce_bf16(const Dims &D, const float *Qr, const float *Kr, int32_t *Ir, const bf16_t *V, const bf16_t *Wlce, bf16_t *O,
                         hipStream_t st)
 {
-    StoreJob J = {V, Wlce, O, Tiling{}, D.C / 64, 0};
-    J.T = tiling(D, D.C, 1536 / J.cblocks, J.tiles);
+    const Job J = plain_job(D, V, Wlce, O, D.C);
     const long lce_blocks = ((J.tiles + 1) / 2 * J.cblocks + 7) / 8 * 8;
     if (D.C % 64 || !route::supported(D) || !offsets_fit(D, J.T, D.C) || lce_blocks > 0x3fffffffL) return BRA_ERR_UNSUPPORTED;
     const route::Plan p = route::plan(D, D.C);
@@ -111,59 +114,33 @@ int route_rows_lce_bf16(const Dims &D, const float *Qr, const float *Kr, int32_t
 // addresses are 64-bit throughout.
 int lce_add_bf16(const Dims &D, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, int ldo, int kernel_id, hipStream_t st)
 {
-    const int cblocks = (D.C + 63) / 64;
-    long tiles;
-    const Tiling T = tiling(D, ldo, 1536 / cblocks, tiles);
-    const long blocks = tiles * cblocks;
-    if (!offsets_fit(D, T, ldo)) return launch_lce<bf16_t, bf16_t>(D, V, D.C, Wlce, O, ldo, kernel_id, st);
-    if (D.C % 2 || ldo % 2 || blocks > 0x7ffffff0L) return BRA_ERR_UNSUPPORTED;
+    const Job J = plain_job(D, V, Wlce, O, ldo);
+    if (!offsets_fit(D, J.T, ldo)) return launch_lce<bf16_t, bf16_t>(D, V, D.C, Wlce, O, ldo, kernel_id, st);
+    if (D.C % 2 || ldo % 2 || J.blocks() > 0x7ffffff0L) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);
-    hipLaunchKernelGGL(k_lce_pairs<false>, dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), 0, st, V, (const bf16_t *)nullptr,
-                       Wlce, O, ldo, (float *)nullptr, D, T, cblocks, tiles, 1);
+    hipLaunchKernelGGL(k_lce_add, dim3((unsigned)J.blocks()), dim3(256), 0, st, J, D);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
-namespace {
-
-// About 768 workgroups (three per compute unit), each with the tiles of one group.
-constexpr int kGradSlots = 768;
-
-Tiling grad_plan(const Dims &D, int lddv, long &tiles, int &per_wg, int &groups)
-{
-    const int cblocks = (D.C + 63) / 64;
-    const long want = std::max(1, kGradSlots / cblocks);
-    const Tiling T = tiling(D, lddv, want, tiles);
-    per_wg = (int)((tiles + want - 1) / want);
-    groups = (int)((tiles + per_wg - 1) / per_wg);
-    return T;
-}
-
-LcePlan wide_grad_plan(const Dims &D) { return lce_plan(D, kGradSlots, 8); }      // 8 columns per workgroup: two channels per thread
-
-}  // namespace
-
 int lce_grad_groups_bf16(const Dims &D, int lddv)
 {
-    long tiles;
-    int per_wg, groups;
-    return offsets_fit(D, grad_plan(D, lddv, tiles, per_wg, groups), lddv) ? groups : wide_grad_plan(D).groups;
+    const BackwardJobs L = backward_jobs(D, nullptr, nullptr, nullptr, nullptr, nullptr, lddv, nullptr);
+    return L.fit ? (int)L.grad.groups() : wide_grad_plan(D).groups;
 }
 
-int lce_grad_bf16(const Dims &D, const bf16_t *dO, const bf16_t *V, const bf16_t *Wlce, bf16_t *dV, int lddv, float *Part,
-                  int kernel_id, hipStream_t st)
+int lce_backward_bf16(const Dims &D, const BackwardJobs &L, int kernel_id, hipStream_t st)
 {
-    const int cblocks = (D.C + 63) / 64;
-    long tiles;
-    int per_wg, groups;
-    const Tiling T = grad_plan(D, lddv, tiles, per_wg, groups);
-    if (D.C % 2 || lddv % 2) return BRA_ERR_UNSUPPORTED;
-    if (!offsets_fit(D, T, lddv)) {
+    const Job &G = L.grad, &A = L.add;
+    if (D.C % 2 || G.ldo % 2) return BRA_ERR_UNSUPPORTED;
+    if (!L.fit) {
+        const int rc = launch_lce<bf16_t, bf16_t>(D, A.In, D.C, A.Wlce, A.Out, A.ldo, kernel_id, st);
+        if (rc != BRA_OK) return rc;
         ProfScope ps(st, kernel_id);
-        return launch_lce_grad<bf16_t, bf16_t>(D, wide_grad_plan(D), dO, V, D.C, Wlce, dV, lddv, Part, st);
+        return launch_lce_grad<bf16_t, bf16_t>(D, wide_grad_plan(D), G.In, G.V, D.C, G.Wlce, G.Out, G.ldo, G.Part, st);
     }
+    if (G.blocks() + A.blocks() > 0x7ffffff0L) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);
-    hipLaunchKernelGGL(k_lce_pairs<true>, dim3((unsigned)((groups * cblocks + 7) / 8 * 8)), dim3(256), 0, st, dO, V, Wlce, dV,
-                       lddv, Part, D, T, cblocks, tiles, per_wg);
+    hipLaunchKernelGGL(k_lce_backward, dim3((unsigned)(G.blocks() + A.blocks())), dim3(256), 0, st, G, A, (int)G.blocks(), D);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 

@@ -278,14 +278,12 @@ int launch_lce_grad(const Dims &D, const LcePlan &p, const TM *dO, const TM *V, 
 }
 
 // bf16 maps with an even number of channels (bra_lce.hip), on the two-element bf16 dot product: O += LCE(V);
-// dV += LCE^T(dO) with the tap gradients as lce_grad_groups_bf16 arrays of 25 C floats.
+// the passes of the gradients (backward_jobs) leave the tap gradients as lce_grad_groups_bf16 arrays of 25 C floats.
 int lce_add_bf16(const Dims &D, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, int ldo, int kernel_id, hipStream_t st);
 // O = LCE(V), and beside it in the same launch the rows of A^r from Q^r, K^r [B, R, C] and their top-k.
 int route_rows_lce_bf16(const Dims &D, const float *Qr, const float *Kr, int32_t *Ir, const bf16_t *V, const bf16_t *Wlce, bf16_t *O,
                         hipStream_t st);
 int lce_grad_groups_bf16(const Dims &D, int lddv);
-int lce_grad_bf16(const Dims &D, const bf16_t *dO, const bf16_t *V, const bf16_t *Wlce, bf16_t *dV, int lddv, float *Part,
-                  int kernel_id, hipStream_t st);
 
 }  // namespace lce
 }  // namespace bra

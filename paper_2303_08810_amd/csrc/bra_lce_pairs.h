@@ -192,6 +192,17 @@ __device__ __forceinline__ void walk_tile(const bf16_t *__restrict__ In, const b
     }
 }
 
+// Workgroups of a pass beside those of another kernel, in front of them or behind: true for the `beside` ones of the pass.
+// block: the number within its own kind.  (Evenly among the others, the two slow each other down: see launch_attn_bwd.)
+__device__ __forceinline__ bool block_of_pass(int beside, bool front, int &block, int &blocks)
+{
+    const int others = (int)gridDim.x - beside, first = front ? 0 : others;
+    const bool of_pass = (int)blockIdx.x >= first && (int)blockIdx.x < first + beside;
+    block = (int)blockIdx.x - (of_pass ? first : front ? beside : 0);
+    blocks = of_pass ? beside : others;
+    return of_pass;
+}
+
 // Lane offsets are 32-bit: the rows of a tile (with the window, within the map) must span less than 2 GiB in either map.
 inline bool offsets_fit(const Dims &D, const Tiling &T, int ldo)
 {
@@ -213,6 +224,68 @@ inline Tiling tiling(const Dims &D, int ldo, long want, long &tiles)
         if (T.height == 5 || (tiles >= want && offsets_fit(D, T, ldo))) return T;
     }
 }
+
+// A pass over a map; what it writes is walk_tile's.  Part (GRAD): [group][C][25], the tap gradients summed over the tiles
+// of a workgroup.
+struct Job {
+    const bf16_t *In, *V, *Wlce;
+    bf16_t *Out;
+    float *Part;
+    int ldo, cblocks, per_wg;
+    long tiles;
+    Tiling T;
+
+    __host__ __device__ long groups() const { return (tiles + per_wg - 1) / per_wg; }
+    __host__ __device__ long blocks() const { return (groups() * cblocks + 7) / 8 * 8; }
+};
+
+// LDS of job_block.
+template <bool GRAD>
+constexpr size_t job_bytes() { return GRAD ? 25 * 256 * 4 : kTapBytes; }
+
+// Workgroup `block` of J, 256 threads.
+template <bool GRAD, bool ADDS>
+__device__ __forceinline__ void job_block(const Job &J, const Dims &D, int block, float *red)
+{
+    const int cb = block % J.cblocks, c0 = 64 * cb, grp = block / J.cblocks;
+    const long first = (long)grp * J.per_wg, last = min(J.tiles, first + J.per_wg);
+    if (first >= J.tiles) return;
+    const int cp = threadIdx.x % 32, slot = threadIdx.x / 32;
+    TapTable &table = *(TapTable *)red;
+    stage_taps<GRAD, 256>(table, J.Wlce, c0, D.C);
+    const bool live = c0 + 2 * cp < D.C;
+    const int cl = live ? 2 * cp : 0;
+    u32x2 w[5][3];
+    load_taps(w, table, cl);
+    float acc[GRAD ? 25 : 1][2];
+#pragma unroll
+    for (int t = 0; t < (GRAD ? 25 : 1); ++t) acc[t][0] = acc[t][1] = 0.f;
+    if (GRAD) __syncthreads();
+    for (long tile = first; tile < last; ++tile) walk_tile<GRAD, ADDS>(J.In, J.V, J.Out, J.ldo, D, J.T, tile, slot, c0, cl, live, w, acc);
+    if (!GRAD) return;
+    // the 8 slots' sums of a channel through LDS, added in a fixed order
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < (GRAD ? 25 : 1); ++t) red[t * 256 + threadIdx.x] = acc[t][v];
+        __syncthreads();
+        for (int e = threadIdx.x; e < 25 * 32; e += 256) {
+            const int t = e / 32, ch = c0 + 2 * (e % 32) + v;
+            float s = 0.f;
+            for (int k = 0; k < 8; ++k) s += red[t * 256 + k * 32 + e % 32];
+            if (ch < D.C) J.Part[((size_t)grp * D.C + ch) * 25 + 24 - t] = s;
+        }
+    }
+}
+
+// The two passes of the gradients: dV += (or =) LCE^T(dO) with the tap gradients, and O += LCE(V).  fit: walk_tile takes both.
+struct BackwardJobs {
+    Job grad, add;
+    bool fit;
+};
+BackwardJobs backward_jobs(const Dims &D, const bf16_t *dO, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, bf16_t *dV, int lddv, float *Part);
+int lce_backward_bf16(const Dims &D, const BackwardJobs &L, int kernel_id, hipStream_t st);
 
 }  // namespace lce
 }  // namespace bra

@@ -265,11 +265,15 @@ BwdWs carve_bwd(const Dims &D, void *ws)
 bool launched() { return hipGetLastError() == hipSuccess; }
 
 // Small maps of small regions go by whole images (Q as projected), everything else region by region (Q in units of log2).
-int attn_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, hipStream_t st)
+// O = attention + LCE(V) (Eq. 7), dQ, dK, dV and the partial sums of the tap gradients.
+int attention_and_lce(const Dims &D, const BwdWs &w, const int32_t *Ir, const bf16_t *Wlce, hipStream_t st)
 {
-    if (attn_bwd_map_ok(D))
-        return launch_attn_bwd_map(D, w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, K_GEN_BACKWARD, st);
-    return launch_attn_bwd(D, AttnBwdArgs{w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, w.lse, w.dsum}, K_GEN_BACKWARD, st);
+    const lce::BackwardJobs L = lce::backward_jobs(D, w.dO, w.v, Wlce, w.o, w.dqkv + 2 * D.C, 3 * D.C, w.part_lce);
+    const AttnBwdArgs A = {w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, w.lse, w.dsum};
+    const bool map = attn_bwd_map_ok(D);
+    const int rc = map ? launch_attn_bwd_map(D, w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, K_GEN_BACKWARD, st) : launch_attn_bwd(D, A, L, K_GEN_BACKWARD, st);
+    if (rc != BRA_OK || (!map && L.fit)) return rc;
+    return lce::lce_backward_bf16(D, L, K_GEN_BACKWARD, st);
 }
 
 // Images with more routing entries than this keep to the float32 kernels.
@@ -297,16 +301,12 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
     const int C = D.C;
     const long M = (long)D.B * D.N;
     // Q, K, V once more (Eq. 3); dO = dY Wo^T
-    int rc = wide_project_qkv(D, X, Wqkv, w.q, w.k, w.v, attn_bwd_map_ok(D) ? 1.0f : D.scale * 1.4426950408889634f, st);
+    const float q_scale = attn_bwd_map_ok(D) ? 1.0f : D.scale * 1.4426950408889634f;
+    int rc = gemm_pair(GemmHalf{(const bf16_t *)X, (const bf16_t *)Wqkv, 3 * C, 3 * C, GemmOut{{w.q, w.k, w.v}, C, {nullptr, nullptr}, nullptr, nullptr, 0, q_scale}},
+                       GemmHalf{(const bf16_t *)dY, (const bf16_t *)Wo, C, C, GemmOut{{w.dO, nullptr, nullptr}, C, {nullptr, nullptr}, nullptr, nullptr, 0}},
+                       M, C, K_GEN_BACKWARD, st);
     if (rc != BRA_OK) return rc;
-    rc = gemm_bt((const bf16_t *)dY, (const bf16_t *)Wo, C, M, C, C, w.dO, K_GEN_BACKWARD, st);
-    if (rc != BRA_OK) return rc;
-    rc = attn_bwd(D, w, Ir, st);                                              // O, dQ; then dK, dV
-    if (rc != BRA_OK) return rc;
-    // O = attention + LCE(V) (Eq. 7) for dWo; dV += LCE^T(dO) and the tap-gradient partial sums
-    rc = lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, C, K_GEN_BACKWARD, st);
-    if (rc != BRA_OK) return rc;
-    rc = lce::lce_grad_bf16(D, w.dO, w.v, (const bf16_t *)Wlce, w.dqkv + 2 * C, 3 * C, w.part_lce, K_GEN_BACKWARD, st);
+    rc = attention_and_lce(D, w, Ir, (const bf16_t *)Wlce, st);
     if (rc != BRA_OK) return rc;
     const ProjPlan pp = proj_plan(M, C);
     const bool with_o = C == 64;          // dWo = O^T dY rides in the same pass where the registers allow it

@@ -1,7 +1,7 @@
 // Attention backward over regions of any size (bra_mfma_bwd_attn.hip; internal).
 #pragma once
 
-#include "bra_common.h"
+#include "bra_lce_pairs.h"
 
 namespace bra {
 
@@ -12,6 +12,7 @@ struct AttnBwdArgs {
     float *lse, *dsum;                 // [B][heads][N] row statistics
 };
 
-int launch_attn_bwd(const Dims &D, const AttnBwdArgs &A, int kernel_id, hipStream_t st);
+// With lce.fit both passes of lce are done within the two launches.
+int launch_attn_bwd(const Dims &D, const AttnBwdArgs &A, const lce::BackwardJobs &lce, int kernel_id, hipStream_t st);
 
 }  // namespace bra

@@ -18,6 +18,12 @@
 // of 64, k = 36 (2 tokens): 215 + 172 -> 65 + 88; 12 x 112 x 120 x 64, k = 1 (210 tokens): 112 + 105 -> 68 + 75;
 // 64 x 56 x 56 x 64, k = 1: 36 + 49 -> 39 + 41, there bound by memory (150 MB per kernel).  D = dO . O instead of the sum
 // over the keys took 47, 65, 68 and 37 us on the query side, with the rounding of the bf16 weights in D.
+//
+// Both launches also carry a pass of the depth-wise convolution's gradients (bra_lce_pairs.h), which needs nothing of them: the
+// query side LCE^T(dO) into dV with the tap gradients, the key side O += LCE(V), and adds its dV to what is there.  Each launch
+// costs about 6 us to fill and to drain the chip, and neither kind of work alone keeps the memory busy.  Whole gradient with
+// launches of their own and here (us): 1 x 56 x 56 x 64, k = 1: 44.4 -> 32; 64 x 56 x 56 x 64: 216 -> 192; 64 x 28 x 28 x 128,
+// k = 4: 176 -> 162; 8 x 32 x 32 x 768, k = 12: 277 -> 263; 12 x 112 x 120 x 64: 266 -> 231.
 #include "bra_attn_dev.h"
 #include "bra_mfma_bwd_attn.h"
 
@@ -40,9 +46,9 @@ struct Rows {
 
 // The workgroup's or wavefront's place in the grid: (image, region, tile of tokens, group of 64 channels); false: none.
 template <Mode MODE>
-__device__ __forceinline__ bool place(const Dims &D, int tiles, int items, int wave, int &b, int &reg, int &tile, int &cg)
+__device__ __forceinline__ bool place(const Dims &D, int tiles, int items, int wid, int wave, int &b, int &reg, int &tile, int &cg)
 {
-    const int ncg = D.C / 64, wid = swizzled_block();          // those of an image share an L2
+    const int ncg = D.C / 64;
     const int item = MODE != kWaves ? wid : __builtin_amdgcn_readfirstlane(4 * wid + wave);
     if (item >= items) return false;
     cg = item % ncg;
@@ -58,7 +64,7 @@ __device__ __forceinline__ bool place(const Dims &D, int tiles, int items, int w
 // the weights that entered O).  The second goes over the blocks backwards, so that the
 // last two are still in LDS (up to 128 or 64 routed keys: nothing is read twice).
 template <int HD, int NQ, Mode MODE>
-__global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_attn_bwd_q(AttnBwdArgs A, Dims D, int tiles, int items, int walks)
+__global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_attn_bwd_q(AttnBwdArgs A, Dims D, int tiles, int items, int walks, lce::Job J, int lce_blocks, int lce_front)
 {
     using R = Rows<MODE>;
     constexpr bool SHARED = R::SHARED, SPLIT = MODE == kSplit;
@@ -66,11 +72,17 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
     __shared__ __attribute__((aligned(16))) bf16_t lds[R::bufs * R::buf];
     constexpr int kPart = 64 * (3 + 4 * NDT);    // SPLIT: m, l, D and the sums of a wavefront, one query tile and head
     __shared__ __attribute__((aligned(16))) float sums[SPLIT ? NQ * HPW * 4 * kPart : 4];
+    static_assert(lce::job_bytes<true>() <= sizeof(lds), "the pass shares the buffers");
+    int wg, wgs;
+    if (lce::block_of_pass(lce_blocks, lce_front, wg, wgs)) {
+        lce::job_block<true, false>(J, D, swizzled(wg, wgs), (float *)lds);
+        return;
+    }
     extern __shared__ int origin_tables[];       // [k] or [4][k]: first token of the routed regions; with `walks` [n] or [4][n]: tokens of a region's slots
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C = D.C, n = D.n, kn = D.kn;
     int b, reg, tile, cg;
-    if (!place<MODE>(D, tiles, items, wave, b, reg, tile, cg)) return;
+    if (!place<MODE>(D, tiles, items, swizzled(wg, wgs), wave, b, reg, tile, cg)) return;
     const Places<false> at(D);
     const float n_inv = 1.0f / (float)n;
     const size_t img = (size_t)b * D.N * C + 64 * cg;
@@ -434,7 +446,7 @@ __device__ __forceinline__ int list_of_group(const int32_t *__restrict__ irb, in
 }
 
 template <int HD, int NK, Mode MODE>
-__global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_attn_bwd_kv(AttnBwdArgs A, Dims D, int tiles, int items, int walks)
+__global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_attn_bwd_kv(AttnBwdArgs A, Dims D, int tiles, int items, int walks, lce::Job J, int lce_blocks)
 {
     using R = Rows<MODE>;
     constexpr bool SHARED = R::SHARED, SPLIT = MODE == kSplit;
@@ -445,11 +457,16 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
     __shared__ __attribute__((aligned(16))) float sums[SPLIT ? NK * 4 * 2048 : 4];
     __shared__ int lists[SHARED ? kListShared : 4 * kListWave];
     __shared__ int counts[16];
+    int wg, wgs;
+    if (lce::block_of_pass(lce_blocks, false, wg, wgs)) {
+        lce::job_block<false, true>(J, D, swizzled(wg, wgs), (float *)lds);
+        return;
+    }
     extern __shared__ int slot_tables[];         // with `walks` [n] or [4][n]: tokens of a region's slots
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C = D.C, n = D.n;
     int b, reg, tile, cg;
-    if (!place<MODE>(D, tiles, items, wave, b, reg, tile, cg)) return;
+    if (!place<MODE>(D, tiles, items, swizzled(wg, wgs), wave, b, reg, tile, cg)) return;
     const Places<false> at(D);
     const float n_inv = 1.0f / (float)n, k_inv = 1.0f / (float)D.k;
     const size_t img = (size_t)b * D.N * C + 64 * cg;
@@ -638,6 +655,13 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
             if (!idle) block(s);
         }
     }
+    auto store_dv = [&](bf16_t *at, f32x4 v) {   // with the pass, LCE^T(dO) is there
+        if (lce_blocks) {
+            const u32x2 there = *(const u32x2 *)at;
+            v += f32x4{bf16_lo(there[0]), bf16_hi(there[0]), bf16_lo(there[1]), bf16_hi(there[1])};
+        }
+        *(u32x2 *)at = pack4(v);
+    };
     if constexpr (SPLIT) {
         // wavefront w adds up and stores channels 16 w .. 16 w + 15 of both
 #pragma unroll
@@ -659,7 +683,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
             for (int u = 0; u < 2; ++u, part += 1024)
                 sum[u] = (*(const f32x4 *)part + *(const f32x4 *)(part + 256)) + (*(const f32x4 *)(part + 512) + *(const f32x4 *)(part + 768));
             *(u32x2 *)dst = pack4(sum[0] * kLn2);
-            *(u32x2 *)(dst + C) = pack4(sum[1]);
+            store_dv(dst + C, sum[1]);
         }
         return;
     }
@@ -672,34 +696,40 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) {
                 *(u32x2 *)(row + HD * hh + 16 * dt) = pack4(dk[q][hh][dt] * kLn2);
-                *(u32x2 *)(row + C + HD * hh + 16 * dt) = pack4(dv[q][hh][dt]);
+                store_dv(row + C + HD * hh + 16 * dt, dv[q][hh][dt]);
             }
     }
 }
 
 template <int HD, int N, Mode MODE>
-int launch_t(const Dims &D, const AttnBwdArgs &A, int kernel_id, hipStream_t st)
+int launch_t(const Dims &D, const AttnBwdArgs &A, const lce::BackwardJobs &L, int kernel_id, hipStream_t st)
 {
     const int per_tile = (MODE == kShared ? 64 : 16) * N, tiles = (D.n + per_tile - 1) / per_tile;
     const long items = (long)D.B * D.R * tiles * (D.C / 64), blocks = ((MODE == kWaves ? (items + 3) / 4 : items) + 7) / 8 * 8;
     if (blocks > 0x7fffffffL / 4) return BRA_ERR_UNSUPPORTED;
+    // The pass with the tap gradients is in front where the attention takes several rounds of workgroups, behind where all of it
+    // is resident at once (2 x 128 x 128 x 64, k = 4, 512 workgroups: query side 48.5 us with the pass behind, 63 in front;
+    // 64 x 56 x 56 x 64, k = 1, 3136 workgroups: 64.5 behind, 55.4 in front, 70 with the two kinds in turn).  The other pass is
+    // always behind: its many short workgroups fill up the last round (12 x 112 x 120 x 64, k = 1: key side 76 us, in front 87).
+    const bool front = blocks > 768;
+    const long with_q = L.fit ? L.grad.blocks() : 0, with_kv = L.fit ? L.add.blocks() : 0;
     // kWaves has at most 32 tokens per region and always walks (up to 4096 regions)
     const size_t tables = MODE == kShared ? 1 : 4;
     const int walks = MODE == kSplit ? walk_ok(D) && D.n <= 256 : walk_ok(D);
     {
         ProfScope ps(st, kernel_id);
-        hipLaunchKernelGGL((k_attn_bwd_q<HD, N, MODE>), dim3((unsigned)blocks), dim3(256), tables * (D.k + (walks ? D.n : 0)) * sizeof(int), st,
-                           A, D, tiles, (int)items, walks);
+        hipLaunchKernelGGL((k_attn_bwd_q<HD, N, MODE>), dim3((unsigned)(blocks + with_q)), dim3(256), tables * (D.k + (walks ? D.n : 0)) * sizeof(int), st,
+                           A, D, tiles, (int)items, walks, L.grad, (int)with_q, front);
     }
     if (hipGetLastError() != hipSuccess) return BRA_ERR_LAUNCH;
     ProfScope ps(st, kernel_id);
-    hipLaunchKernelGGL((k_attn_bwd_kv<HD, N, MODE>), dim3((unsigned)blocks), dim3(256), tables * (walks ? D.n : 0) * sizeof(int), st, A, D, tiles,
-                       (int)items, walks);
+    hipLaunchKernelGGL((k_attn_bwd_kv<HD, N, MODE>), dim3((unsigned)(blocks + with_kv)), dim3(256), tables * (walks ? D.n : 0) * sizeof(int), st, A, D, tiles,
+                       (int)items, walks, L.add, (int)with_kv);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
 template <int HD>
-int launch_hd(const Dims &D, const AttnBwdArgs &A, int kernel_id, hipStream_t st)
+int launch_hd(const Dims &D, const AttnBwdArgs &A, const lce::BackwardJobs &L, int kernel_id, hipStream_t st)
 {
     const long regions = (long)D.B * D.R * (D.C / 64), t64 = (D.n + 63) / 64, t128 = (D.n + 127) / 128;
     const long waves = regions * (D.n <= 32 ? 1 : 4 * t64);
@@ -707,22 +737,22 @@ int launch_hd(const Dims &D, const AttnBwdArgs &A, int kernel_id, hipStream_t st
     // (us for the whole gradient: 3 x 14 x 49 x 64, k = 20: 66 -> 50; 28 x 28 x 64, k = 4, 64 routed keys: 45 -> 42; but
     // 392 wavefronts and 80 keys: 66 -> 69, 196 and 4 keys: 49 -> 60).
     if (waves <= 256 && D.kn >= 64) {
-        if (D.n <= 16) return launch_t<HD, 1, kSplit>(D, A, kernel_id, st);
-        return launch_t<HD, 2, kSplit>(D, A, kernel_id, st);
+        if (D.n <= 16) return launch_t<HD, 1, kSplit>(D, A, L, kernel_id, st);
+        return launch_t<HD, 2, kSplit>(D, A, L, kernel_id, st);
     }
-    if (D.n <= 16) return launch_t<HD, 1, kWaves>(D, A, kernel_id, st);
-    if (D.n <= 32) return launch_t<HD, 2, kWaves>(D, A, kernel_id, st);
+    if (D.n <= 16) return launch_t<HD, 1, kWaves>(D, A, L, kernel_id, st);
+    if (D.n <= 32) return launch_t<HD, 2, kWaves>(D, A, L, kernel_id, st);
     // two token tiles per wavefront (every operand read serves both) where they leave no more than an eighth of their
     // tokens empty beyond the narrow ones and there are workgroups enough
-    if (t128 * 128 * 8 <= t64 * 64 * 9 && regions * t128 >= 512) return launch_t<HD, 2, kShared>(D, A, kernel_id, st);
-    return launch_t<HD, 1, kShared>(D, A, kernel_id, st);
+    if (t128 * 128 * 8 <= t64 * 64 * 9 && regions * t128 >= 512) return launch_t<HD, 2, kShared>(D, A, L, kernel_id, st);
+    return launch_t<HD, 1, kShared>(D, A, L, kernel_id, st);
 }
 
 }  // namespace
 
-int launch_attn_bwd(const Dims &D, const AttnBwdArgs &A, int kernel_id, hipStream_t st)
+int launch_attn_bwd(const Dims &D, const AttnBwdArgs &A, const lce::BackwardJobs &L, int kernel_id, hipStream_t st)
 {
-    return D.d == 32 ? launch_hd<32>(D, A, kernel_id, st) : launch_hd<64>(D, A, kernel_id, st);
+    return D.d == 32 ? launch_hd<32>(D, A, L, kernel_id, st) : launch_hd<64>(D, A, L, kernel_id, st);
 }
 
 }  // namespace bra

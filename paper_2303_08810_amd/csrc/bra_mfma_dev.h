@@ -665,11 +665,8 @@ struct AttnArgs {
 
 // Workgroup -> work item.  Consecutive block ids are dealt round-robin to the 8 XCDs;
 // undo that so that the workgroups of one image share an L2.  gridDim.x % 8 == 0.
-__device__ __forceinline__ int swizzled_block()
-{
-    const int per_xcd = gridDim.x / 8;
-    return ((int)blockIdx.x % 8) * per_xcd + (int)blockIdx.x / 8;
-}
+__device__ __forceinline__ int swizzled(int block, int blocks) { return (block % 8) * (blocks / 8) + block / 8; }
+__device__ __forceinline__ int swizzled_block() { return swizzled(blockIdx.x, gridDim.x); }
 
 }  // namespace mfma
 

@@ -493,16 +493,6 @@ int route_steps(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideWs
 
 }  // namespace
 
-// Q, K, V = X Wqkv into three token maps (Eq. 3) for any C that is a multiple of 64: the projection of
-// the wide pipeline, for the backward pass.
-int wide_project_qkv(const Dims &D, const void *X, const void *Wqkv, bf16_t *Q, bf16_t *K, bf16_t *V, float q_scale, hipStream_t st)
-{
-    const long M = (long)D.B * D.N;
-    if (D.C % 64 || M > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    return gemm((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, GemmOut{{Q, K, V}, D.C, {nullptr, nullptr}, nullptr, nullptr, 0, q_scale}, nullptr,
-                K_MFMA_QKV, st);
-}
-
 bool wide_supported(const Dims &D)
 {
     if (D.dtype != BRA_BF16 || D.C % 64 != 0 || D.C > 4096) return false;
