@@ -355,6 +355,8 @@ __global__ __launch_bounds__(256, BM == 64 && BN == 64 ? 3 : 2) void k_gemm_pair
     else dma_tile<BM, BN, NB, true, false>(In1, W1, ldw1, M, K, Nout1, out1, swizzled(bi - blocks0, (int)gridDim.x - blocks0), (bf16_t *)smem);
 }
 
+long region_blocks(const GemmRegions &r) { return (r.M + 63) / 64 * ((r.Nout + 63) / 64); }
+
 template <int BM, int BN>
 long tile_blocks(long M, int Nout) { return ((M + BM - 1) / BM * ((Nout + BN - 1) / BN) + 7) / 8 * 8; }
 
@@ -376,7 +378,7 @@ int launch_dma_t(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int 
     static bool opted = false;
     if (!opt_in(k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT>, opted)) return BRA_ERR_LAUNCH;
     const long blocks = tile_blocks<BM, BN>(M, Nout);
-    const long rb = REGIONS ? (reg.M + 63) / 64 * ((reg.Nout + 63) / 64) : 0;
+    const long rb = REGIONS ? region_blocks(reg) : 0;
     if (blocks + rb > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     hipLaunchKernelGGL((k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT>), dim3((unsigned)(blocks + rb)), dim3(256),
                        std::max(ring_bytes<BM, BN, NB>(), REGIONS ? kGemm64Bytes : 0), st, In, W, ldw, (int)M, K, Nout, out, reg, (int)rb);
@@ -405,12 +407,12 @@ enum Tile { kOneChunk, kWide, kMid, kNarrow };
 // 17.1; 12544 x 1152 x 384: 20.8 / 19.3 / 21.9; 12544 x 512 x 512: 12.4 / 14.0 / 12.7; 3136 x 768 x 768: 9.9 / 9.3 / 8.3;
 // 12544 x 256 x 768: 12.2 / 11.2 / 12.0; 1568 x 384 x 1152: 6.6 / 5.2 / 4.8.  A third buffer, 256 x 128 tiles with 8 wavefronts
 // and chunks of 32 gained nothing.
-// Nout1: columns of a second product over the same rows.
-Tile pick_tile(long M, int K, int Nout, int Nout1 = 0)
+// Nout1: columns of a second product over the same rows; others: workgroups of a region-level product in the launch.
+Tile pick_tile(long M, int K, int Nout, int Nout1, long others)
 {
     if (K == 64) return kOneChunk;
     auto cost = [&](int bm, int bn, long tile) {
-        const long rounds = ((M + bm - 1) / bm * ((Nout + bn - 1) / bn + (Nout1 + bn - 1) / bn) + 255) / 256;
+        const long rounds = ((M + bm - 1) / bm * ((Nout + bn - 1) / bn + (Nout1 + bn - 1) / bn) + others + 255) / 256;
         return tile * rounds * (rounds == 1 ? 13 : 10);
     };
     const long wide = cost(128, 128, 744), mid = cost(64, 128, 433), narrow = cost(64, 64, 260);
@@ -421,7 +423,7 @@ template <bool REGIONS, bool BT = false>
 int launch_big(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, const GemmRegions &reg,
                hipStream_t st)
 {
-    switch (pick_tile(M, K, Nout)) {
+    switch (pick_tile(M, K, Nout, 0, REGIONS ? region_blocks(reg) : 0)) {
     case kOneChunk: return launch_dma<64, 64, 1, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
     case kWide: return launch_dma<128, 128, 2, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
     case kMid: return launch_dma<64, 128, 2, REGIONS, BT>(In, W, ldw, M, K, Nout, out, reg, st);
@@ -728,7 +730,7 @@ int gemm_pair(const GemmHalf &a, const GemmHalf &b, long M, int K, int kernel_id
     if (b.Nout == K && proj_ok(M, K, a.Nout, a.out, false) && a.Nout == 3 * K)
         return K == 64 ? launch_proj_t<64, 192, true>(a.In, a.W, a.ldw, M, a.out, st, b) : launch_proj_t<128, 384, true>(a.In, a.W, a.ldw, M, a.out, st, b);
     // tiles of both together
-    switch (pick_tile(M, K, a.Nout, b.Nout)) {
+    switch (pick_tile(M, K, a.Nout, b.Nout, 0)) {
     case kOneChunk: return launch_pair<64, 64, 1>(a, b, M, K, st);
     case kWide: return launch_pair<128, 128, 2>(a, b, M, K, st);
     case kMid: return launch_pair<64, 128, 2>(a, b, M, K, st);

@@ -65,15 +65,23 @@ __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X,
     }
 }
 
-// Four channels of an attention output, added to what is there (LCE(V)) or not.
-__device__ __forceinline__ void store_output(bf16_t *p, f32x4 v, bool adds)
-{
-    if (adds) {
-        const u32x2 u = *(const u32x2 *)p;
-        v += f32x4{bf16_lo(u[0]), bf16_hi(u[0]), bf16_lo(u[1]), bf16_hi(u[1])};
+// What an output is added to (LCE(V)): the lane's four channels of 16-channel tile dt of NQ query tiles.
+template <int NQ>
+struct Added {
+    u32x2 v[NQ][4];
+
+    __device__ __forceinline__ void load(const bf16_t *O, const size_t (&token)[NQ], int C, int g)
+    {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) v[q][dt] = *(const u32x2 *)(O + token[q] * C + 16 * dt + 4 * g);
     }
-    *(u32x2 *)p = pack4(v);
-}
+    __device__ __forceinline__ f32x4 to(f32x4 x, int q, int dt) const
+    {
+        return x + f32x4{bf16_lo(v[q][dt][0]), bf16_hi(v[q][dt][0]), bf16_lo(v[q][dt][1]), bf16_hi(v[q][dt][1])};
+    }
+};
 
 // ---------------------------------------------------------------------------
 // Routed attention (Eq. 6, Eq. 1) for any region size and heads of 32 or 64 channels.  Q comes multiplied by
@@ -90,7 +98,7 @@ __device__ __forceinline__ void store_output(bf16_t *p, f32x4 v, bool adds)
 // its addition to the denominator and half a conversion; with maxima instead of additions and denominators from a product
 // it took 68 us.  One query tile per wavefront instead of two: 74 us (4 x 64 x 64 x 384, heads of 64, k = 4: 45 for 39).
 template <int HD, int NQ>
-__global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, int walks)
+__global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, int walks)
 {
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16;
     __shared__ __attribute__((aligned(16))) bf16_t K0[64 * 64];
@@ -112,16 +120,6 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
         const int sy = fast_div(slot, rw_inv);
         return sy * D.W + slot - sy * D.rw;
     };
-    const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
-    const bool report = A.Ir_out && A.Ir_out != A.Ir_src && qt == 0 && cg == 0;
-    for (int p = tid; p < D.k; p += 256) {
-        const int j = irp[p];
-        origins[p] = region_origin(region_index(j, D.R));
-        if (report) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = j;
-    }
-    int *slots = origins + D.k;
-    if (walks)
-        for (int t = tid; t < n; t += 256) slots[t] = in_region(t);
     size_t qtok[NQ];
     bf16x8 qf[NQ][HPW][KSD];
 #pragma unroll
@@ -133,6 +131,18 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
             for (int ks = 0; ks < KSD; ++ks)
                 qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + HD * hh + 32 * ks + 8 * g);
     }
+    Added<NQ> added;
+    if (NQ == 1 && A.adds) added.load(O + img, qtok, C, g);
+    const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
+    const bool report = A.Ir_out && A.Ir_out != A.Ir_src && qt == 0 && cg == 0;
+    for (int p = tid; p < D.k; p += 256) {
+        const int j = irp[p];
+        origins[p] = region_origin(region_index(j, D.R));
+        if (report) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = j;
+    }
+    int *slots = origins + D.k;
+    if (walks)
+        for (int t = tid; t < n; t += 256) slots[t] = in_region(t);
     // the operands have arrived before the loop: otherwise the compiler waits for them, and with them for the direct loads
     // in flight, in every pass
 #pragma unroll
@@ -231,6 +241,7 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
         if (k0 + 128 < kn) request(k0 + 128, kv[1][0], kv[1][1]);
         if (!idle) block(k0 + 64, K0, V0, std::false_type{});
     }
+    if (NQ > 1 && A.adds) added.load(O + img, qtok, C, g);      // 16 registers that the sweep does not have
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const bool store = 64 * NQ * qt + 16 * (NQ * wave + q) + i < n;
@@ -239,7 +250,11 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
             const float inv = 1.0f / cross_row_sum(l[q][hh]);
             if (!store) continue;
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt) store_output(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g, acc[q][hh][dt] * inv, A.adds);
+            for (int dt = 0; dt < NDT; ++dt) {
+                f32x4 v = acc[q][hh][dt] * inv;
+                if (A.adds) v = added.to(v, q, NDT * hh + dt);
+                *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(v);
+            }
         }
     }
 }
@@ -250,14 +265,20 @@ __global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void k_attn_gen(AttnArgs A, b
 // (2 or 1 heads), any four of them in a workgroup.  It brings its K and V rows straight from memory into its own part of LDS, 32 keys at a time into one
 // of two buffers while the other is worked on; there is no barrier.  Rows of 128 bytes lie unpadded, their pieces
 // exchanged as above.
-// Bound by the gather out of the L2s: 302 MB for 8 images of 32 x 32 x 768 with 12 regions of 16 tokens each.
+// Bound by the gather out of the L2s: 302 MB for 8 images of 32 x 32 x 768 with 12 regions of 16 tokens each; with few keys by
+// the chain of loads before the first product (routing entry, row, output) and the wavefronts that hide it: the second buffer
+// is left out for up to 32 keys, so that four workgroups share a compute unit instead of two, and what the output is added to
+// and the queries are requested with the routing entries (64 x 16 x 24 x 384, k = 1: attention 51.7 -> 31.9 us, layer 146 ->
+// 126; 32 x 16 x 16 x 768, k = 2: 49.1 -> 29.7; 29 x 8 x 8 x 768, k = 33: 46.1 -> 40.3).
+constexpr int kRowsBuffer = 4 * 2 * 32 * 64 * 2;       // bytes
+
 template <int HD, int NQ>
 __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int items)
 {
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16, KB = 32;
-    __shared__ __attribute__((aligned(16))) bf16_t S0[4 * 2 * KB * 64];      // [wavefront][K, V][32 keys][64]
-    __shared__ __attribute__((aligned(16))) bf16_t S1[4 * 2 * KB * 64];
-    extern __shared__ int origin_tables[];       // [4][k]: first token of the routed regions; [4][32]: tokens of a region's slots
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    bf16_t *S0 = (bf16_t *)smem, *S1 = S0 + (D.kn > KB ? kRowsBuffer / 2 : 0);       // [wavefront][K, V][32 keys][64]
+    int *origin_tables = (int *)((char *)S1 + kRowsBuffer);      // [4][k]: first token of the routed regions; [4][32]: tokens of a region's slots
     const int C = D.C, ncg = C / 64, n = D.n, kn = D.kn;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, g = lane / 16, i = lane % 16;
     const int item = __builtin_amdgcn_readfirstlane(4 * swizzled_block() + wave);      // those of an image share an L2
@@ -273,16 +294,6 @@ __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__rest
         const int sy = fast_div(slot, rw_inv);
         return sy * D.W + slot - sy * D.rw;
     };
-    const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
-    const bool report = A.Ir_out && A.Ir_out != A.Ir_src && cg == 0;
-    for (int p = lane; p < D.k; p += kWave) {
-        const int j = irp[p];
-        origins[p] = region_origin(region_index(j, D.R));
-        if (report) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = j;
-    }
-    if (lane < n) slots[lane] = in_region(lane);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // the tables are read by other lanes
-
     const size_t img = (size_t)b * D.N * C + 64 * cg;
     const int origin = region_origin(reg);
     size_t qtok[NQ];
@@ -296,6 +307,17 @@ __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__rest
             for (int ks = 0; ks < KSD; ++ks)
                 qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + HD * hh + 32 * ks + 8 * g);
     }
+    Added<NQ> added;
+    if (A.adds) added.load(O + img, qtok, C, g);
+    const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
+    const bool report = A.Ir_out && A.Ir_out != A.Ir_src && cg == 0;
+    for (int p = lane; p < D.k; p += kWave) {
+        const int j = irp[p];
+        origins[p] = region_origin(region_index(j, D.R));
+        if (report) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = j;
+    }
+    if (lane < n) slots[lane] = in_region(lane);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // the tables are read by other lanes
     // the operands have arrived before the loop: otherwise the compiler waits for them, and with them for the direct loads
     // in flight, in every pass
 #pragma unroll
@@ -390,7 +412,11 @@ __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__rest
             const float inv = 1.0f / cross_row_sum(l[q][hh]);
             if (!store) continue;
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt) store_output(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g, acc[q][hh][dt] * inv, A.adds);
+            for (int dt = 0; dt < NDT; ++dt) {
+                f32x4 v = acc[q][hh][dt] * inv;
+                if (A.adds) v = added.to(v, q, NDT * hh + dt);
+                *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(v);
+            }
         }
     }
 }
@@ -441,15 +467,24 @@ GemmRegions region_job(const Dims &D, const WideWs &w)
     return GemmRegions{w.xr, (long)D.B * D.R, 2 * D.C, {w.qr, w.kr}, D.C};
 }
 
-void launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
+template <int HD, int NQ>
+int launch_attn_rows_t(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
 {
     const int items = D.B * D.R * (D.C / 64), blocks = (items + 3) / 4;
-    const dim3 grid((unsigned)((blocks + 7) / 8 * 8)), block(256);
-    const size_t smem = (size_t)4 * (D.k + 32) * sizeof(int);
-    if (D.d == 32 && D.n <= 16) hipLaunchKernelGGL((k_attn_rows<32, 1>), grid, block, smem, st, A, O, D, items);
-    else if (D.d == 32) hipLaunchKernelGGL((k_attn_rows<32, 2>), grid, block, smem, st, A, O, D, items);
-    else if (D.n <= 16) hipLaunchKernelGGL((k_attn_rows<64, 1>), grid, block, smem, st, A, O, D, items);
-    else hipLaunchKernelGGL((k_attn_rows<64, 2>), grid, block, smem, st, A, O, D, items);
+    const size_t smem = (size_t)(D.kn > 32 ? 2 : 1) * kRowsBuffer + (size_t)4 * (D.k + 32) * sizeof(int);
+    static bool opted = false;
+    if (!opted && smem > 64 * 1024) {
+        if (hipFuncSetAttribute((const void *)k_attn_rows<HD, NQ>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess) return BRA_ERR_LAUNCH;
+        opted = true;
+    }
+    hipLaunchKernelGGL((k_attn_rows<HD, NQ>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), smem, st, A, O, D, items);
+    return BRA_OK;
+}
+
+int launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
+{
+    if (D.d == 32) return D.n <= 16 ? launch_attn_rows_t<32, 1>(D, A, O, st) : launch_attn_rows_t<32, 2>(D, A, O, st);
+    return D.n <= 16 ? launch_attn_rows_t<64, 1>(D, A, O, st) : launch_attn_rows_t<64, 2>(D, A, O, st);
 }
 
 template <int NQ>
@@ -556,9 +591,10 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     } else {
         {
             ProfScope ps(st, K_MFMA_ATTENTION);
-            if (D.n <= 32 && D.k <= 1024) launch_attn_rows(D, A, w.o, st);      // its tables fit in LDS
+            if (D.n <= 32 && D.k <= 1024) rc = launch_attn_rows(D, A, w.o, st);      // its tables fit in LDS
             else launch_attn_gen(D, A, w.o, st);
         }
+        if (rc != BRA_OK) return rc;
         rc = A.adds ? BRA_OK : lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);
     }
     if (rc != BRA_OK) return rc;
