@@ -316,19 +316,31 @@ constexpr size_t gemm_lds_floats()
     return f32 > terms ? f32 : terms;
 }
 
+template <bool BT, bool VEC, int BN, typename TA, typename TB, typename TO>
+__device__ __forceinline__ void any_gemm_tile(const GemmJob<TA, TB, TO> &J, int block, float *smem)
+{
+    if constexpr (VEC && std::is_same<TB, bf16_t>::value) gemm_tile_bf16<BT, BN>(J, block, (bf16_t *)smem);
+    else gemm_tile<BT, VEC, BN>(J, block, smem);
+}
+
 // Workgroups below blocks0 do job J0, the rest J1 (of the same B matrix type, A and Out float32): the
 // region-level projection of the routing rides in the token projection's launch.
 template <bool BT, bool VEC, int BN, typename TA, typename TB, typename TO>
 __global__ __launch_bounds__(256) void k_gemm(GemmJob<TA, TB, TO> J0, GemmJob<float, TB, float> J1, int blocks0)
 {
     __shared__ __attribute__((aligned(16))) float smem[gemm_lds_floats<BN, BT>()];
-    if ((int)blockIdx.x < blocks0) {
-        if constexpr (VEC && std::is_same<TB, bf16_t>::value) gemm_tile_bf16<BT, BN>(J0, blockIdx.x, (bf16_t *)smem);
-        else gemm_tile<BT, VEC, BN>(J0, blockIdx.x, smem);
-        return;
-    }
-    if constexpr (VEC && std::is_same<TB, bf16_t>::value) gemm_tile_bf16<BT, BN>(J1, (int)blockIdx.x - blocks0, (bf16_t *)smem);
-    else gemm_tile<BT, VEC, BN>(J1, (int)blockIdx.x - blocks0, smem);
+    if ((int)blockIdx.x < blocks0) any_gemm_tile<BT, VEC, BN>(J0, blockIdx.x, smem);
+    else any_gemm_tile<BT, VEC, BN>(J1, (int)blockIdx.x - blocks0, smem);
+}
+
+// J0 and a product with its matrix transposed (Q, K, V = X Wqkv and dO = dY Wo^T of the gradients) in one launch.
+template <bool VEC, int BN, typename T>
+__global__ __launch_bounds__(256) void k_gemm_both(GemmJob<T, T, float> J0, GemmJob<T, T, float> J1, int blocks0)
+{
+    constexpr size_t n0 = gemm_lds_floats<BN, false>(), n1 = gemm_lds_floats<BN, true>();
+    __shared__ __attribute__((aligned(16))) float smem[n0 > n1 ? n0 : n1];
+    if ((int)blockIdx.x < blocks0) any_gemm_tile<false, VEC, BN>(J0, blockIdx.x, smem);
+    else any_gemm_tile<true, VEC, BN>(J1, (int)blockIdx.x - blocks0, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -419,7 +431,7 @@ __device__ __forceinline__ void rows_product(const float *T, int P, const f32x4 
 // HPW = 1: as many wavefronts as the region's query tiles of 16 fill (3 to 8; more tiles are dealt out evenly).
 template <int DP, int HPW, bool VEC>
 __global__ __launch_bounds__(HPW == 1 ? 512 : 256, DP == 32 ? 4 : 2) void k_attention(const float *__restrict__ QKV, const int32_t *__restrict__ Ir,
-                                                   float *__restrict__ O, Dims D, int hgroups, int qtiles)
+                                                   float *__restrict__ O, Dims D, int hgroups, int qtiles, bool adds)
 {
     typedef AttnShape<DP, HPW> L;
     constexpr int P = L::P, KB = L::KB, CW = L::CW, KT = KB / 16, NS = DP / 16;
@@ -533,7 +545,10 @@ __global__ __launch_bounds__(HPW == 1 ? 512 : 256, DP == 32 ? 4 : 2) void k_atte
 #pragma unroll
         for (int dt = 0; dt < NS; ++dt) {
             const int ch = 16 * dt + 4 * g;
-            if (ch < D.d) store4<VEC>(orow + ch, acc[dt] * inv, D.d - ch);
+            if (ch >= D.d) continue;
+            f32x4 v = acc[dt] * inv;
+            if (adds) v += load4<VEC>(orow + ch, D.d - ch);      // LCE(V)
+            store4<VEC>(orow + ch, v, D.d - ch);
         }
     }
 }
@@ -548,14 +563,20 @@ template <int DP, int HPW, bool VEC>
 __global__ __launch_bounds__(256) void k_attn_bwd_q(const float *__restrict__ QKV, const float *__restrict__ dO,
                                                     const int32_t *__restrict__ Ir, float *__restrict__ O,
                                                     float *__restrict__ dQKV, float *__restrict__ lse,
-                                                    float *__restrict__ dsum, Dims D, int hgroups, int qtiles)
+                                                    float *__restrict__ dsum, Dims D, int hgroups, int qtiles,
+                                                    lce::GradJob<float> J, int lce_blocks)
 {
     typedef AttnShape<DP, HPW> L;
-    constexpr int P = L::P, KB = L::KB, CW = L::CW, KT = KB / 16, NS = DP / 16;
-    __shared__ __attribute__((aligned(16))) float Ks[KB * P];
-    __shared__ __attribute__((aligned(16))) float Vs[KB * P];
-    const int hg = blockIdx.x % hgroups, qt = (blockIdx.x / hgroups) % qtiles;
-    const int reg = (blockIdx.x / (hgroups * qtiles)) % D.R, b = blockIdx.x / (hgroups * qtiles * D.R);
+    constexpr int P = L::P, KB = L::KB, CW = L::CW, KT = KB / 16, NS = DP / 16, kFloats = 2 * KB * P > 25 * 256 ? 2 * KB * P : 25 * 256;
+    __shared__ __attribute__((aligned(16))) float lds[kFloats];
+    float *Ks = lds, *Vs = lds + KB * P;
+    int wg, wgs;
+    if (lce::block_of_pass(lce_blocks, false, wg, wgs)) {
+        lce::lce_grad_block<VEC ? 2 : 1, false>(J, D, mfma::swizzled(wg, wgs), lds);
+        return;
+    }
+    const int hg = wg % hgroups, qt = (wg / hgroups) % qtiles;
+    const int reg = (wg / (hgroups * qtiles)) % D.R, b = wg / (hgroups * qtiles * D.R);
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C3 = 3 * D.C, kn = D.kn, nblocks = (kn + KB - 1) / KB, hl = wave / L::TPH, h = hg * HPW + hl;
     const size_t itok = (size_t)b * D.N;
@@ -708,16 +729,22 @@ template <int DP, int HPW, bool VEC>
 __global__ __launch_bounds__(256) void k_attn_bwd_kv(const float *__restrict__ QKV, const float *__restrict__ dO,
                                                      const int32_t *__restrict__ Ir, const float *__restrict__ lse,
                                                      const float *__restrict__ dsum, float *__restrict__ dQKV, Dims D,
-                                                     int hgroups, int ktiles)
+                                                     int hgroups, int ktiles, lce::AddJob<float> J, int lce_blocks)
 {
     typedef AttnShape<DP, HPW> L;
     constexpr int P = L::P, QB = L::KB, CW = L::CW, QTL = QB / 16, NS = DP / 16;
-    __shared__ __attribute__((aligned(16))) float Qs[QB * P];
-    __shared__ __attribute__((aligned(16))) float Gs[QB * P];
+    __shared__ __attribute__((aligned(16))) float lds[2 * QB * P];
+    float *Qs = lds, *Gs = lds + QB * P;
+    static_assert(2 * QB * P >= 25 * 64, "the pass shares the buffers");
     __shared__ __attribute__((aligned(16))) float lse_s[HPW * QB], dd_s[HPW * QB];
     __shared__ int list[bwd::kListChunk], counts[16];
-    const int hg = blockIdx.x % hgroups, kt = (blockIdx.x / hgroups) % ktiles;
-    const int reg = (blockIdx.x / (hgroups * ktiles)) % D.R, b = blockIdx.x / (hgroups * ktiles * D.R);
+    int wg, wgs;
+    if (lce::block_of_pass(lce_blocks, false, wg, wgs)) {
+        lce::lce_block<VEC ? 2 : 1, true, 256>(J, D, mfma::swizzled(wg, wgs), lds);
+        return;
+    }
+    const int hg = wg % hgroups, kt = (wg / hgroups) % ktiles;
+    const int reg = (wg / (hgroups * ktiles)) % D.R, b = wg / (hgroups * ktiles * D.R);
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C3 = 3 * D.C, hl = wave / L::TPH, h = hg * HPW + hl;
     const size_t itok = (size_t)b * D.N;
@@ -814,7 +841,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const float *__restrict__ Q
             const int ch = 16 * dt + 4 * g;
             if (ch >= D.d) continue;
             store4<VEC>(row + D.C + ch, ak[dt] * D.scale, D.d - ch);
-            store4<VEC>(row + 2 * D.C + ch, av[dt], D.d - ch);
+            store4<VEC>(row + 2 * D.C + ch, av[dt] + load4<VEC>(row + 2 * D.C + ch, D.d - ch), D.d - ch);    // LCE^T(dO) is there
         }
     }
 }
@@ -895,11 +922,15 @@ __device__ __forceinline__ void tn_tile(const TnJob<TA, TB> &J, int block, long 
             }
 }
 
-template <bool VEC, typename TA0, typename TB0, typename TA1, typename TB1>
-__global__ __launch_bounds__(256) void k_gemm_tn(TnJob<TA0, TB0> J0, TnJob<TA1, TB1> J1, long M, int share_tokens)
+// What is left once dQ, dK and dV are there, in one launch: dX = [dQ | dK | dV] Wqkv^T (J), dWqkv and dWo (J0, J1).
+template <bool VEC, int BN, typename T>
+__global__ __launch_bounds__(256) void k_gemm_end(TnJob<T, float> J0, TnJob<float, T> J1, long M, int share_tokens, GemmJob<float, T, T> J)
 {
-    __shared__ __attribute__((aligned(16))) float smem[2 * 32 * (64 + 4)];
-    if ((int)blockIdx.x < J0.blocks) tn_tile<VEC>(J0, blockIdx.x, M, share_tokens, smem);
+    constexpr size_t n = gemm_lds_floats<BN, true>(), tn = 2 * 32 * (64 + 4);
+    __shared__ __attribute__((aligned(16))) float smem[n > tn ? n : tn];
+    const int block = (int)blockIdx.x - J0.blocks - J1.blocks;
+    if (block >= 0) any_gemm_tile<true, VEC, BN>(J, block, smem);
+    else if ((int)blockIdx.x < J0.blocks) tn_tile<VEC>(J0, blockIdx.x, M, share_tokens, smem);
     else tn_tile<VEC>(J1, (int)blockIdx.x - J0.blocks, M, share_tokens, smem);
 }
 

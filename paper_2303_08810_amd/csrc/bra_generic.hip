@@ -10,6 +10,7 @@
 // Region pooling uses mean(X^r) W = mean(X^r W), which is exact in real arithmetic
 // (the mean is linear; same argument as Appendix A).
 #include "bra_f32_dev.h"
+#include "bra_route_dev.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -32,7 +33,7 @@ constexpr int kAttnMaxD = 256;      // head width limit of the generic attention
 // projected map by index.  QKV is [B, N, 3C] float32 (q | k | v per token).
 __global__ __launch_bounds__(256) void gen_attention(const float *__restrict__ QKV,
                                                      const int32_t *__restrict__ Ir,
-                                                     float *__restrict__ O, Dims D, float scale)
+                                                     float *__restrict__ O, Dims D, float scale, bool adds)
 {
     __shared__ float qs[4][kAttnMaxD];
     __shared__ float sc[4][kAttnChunk];
@@ -111,7 +112,9 @@ __global__ __launch_bounds__(256) void gen_attention(const float *__restrict__ Q
         if (active) {
             for (int t = 0; t < kAttnMaxD / kWave; ++t) {
                 const int c = lane + t * kWave;
-                if (c < D.d) O[((size_t)b * D.N + qtok) * D.C + hd * D.d + c] = acc[t] / l;
+                if (c >= D.d) continue;
+                float *o = O + ((size_t)b * D.N + qtok) * D.C + hd * D.d + c;
+                *o = adds ? *o + acc[t] / l : acc[t] / l;
             }
         }
     }
@@ -204,8 +207,50 @@ int launch_route(const Dims &D, const T *X, const T *Wqkv, int32_t *Ir, float *A
     return route_rows(D, w.qk, w.qk + D.C, 2 * D.C, Ir, Ar_opt, st);
 }
 
+// The rows of A^r and their top-k, and O = LCE(V) in the same launch: the routing keeps few compute units busy, with a chain
+// of latencies, and the convolution needs nothing of it.  Workgroups below route_blocks (a multiple of 8; those without
+// rows leave) do the routing.  Layer of 16 x 56 x 56 x 64 float32: 77 us with the two apart, 66.7; 4 x 14 x 14 x 256: 45 and 39.
+constexpr int kRouteThreads = 64 * route::kWaves;
+
+template <bool VEC>
+__global__ __launch_bounds__(kRouteThreads, 4) void k_route_lce(const float *__restrict__ Qr, const float *__restrict__ Kr, int ld,
+                                                                int32_t *__restrict__ Ir, int CS, int rows_blocks, int route_blocks,
+                                                                lce::AddJob<float> J, Dims D)
+{
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    const int block = (int)blockIdx.x - route_blocks;
+    if (block >= 0) lce::lce_block<VEC ? 2 : 1, false, kRouteThreads>(J, D, mfma::swizzled(block, (int)gridDim.x - route_blocks), smem);
+    else if ((int)blockIdx.x < rows_blocks) route::route_block<VEC, 3>(Qr, Kr, ld, Ir, nullptr, D, CS, blockIdx.x, smem);
+}
+
+// added: O holds LCE(V) (not for maps that lce_block does not take).
+int launch_route_lce(const Dims &D, const GenericWs &w, const lce::Taps &taps, int32_t *Ir, bool &added, hipStream_t st)
+{
+    const int C = D.C;
+    const route::Plan p = route::plan(D, 2 * C);
+    const lce::AddJob<float> J = lce::add_job<float>(D, w.qkv + 2 * C, 3 * C, taps, w.o, C, p.vec ? 2 : 1, kRouteThreads);
+    added = J.blocks > 0;
+    if (!added) return route_rows(D, w.qk, w.qk + C, 2 * C, Ir, nullptr, st);
+    if (!route::supported(D)) return BRA_ERR_UNSUPPORTED;
+    const int route_blocks = (p.blocks + 7) / 8 * 8;
+    const size_t smem = std::max(p.smem, (size_t)25 * 64 * sizeof(float));
+    if ((long)route_blocks + J.blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    static bool opted = false;
+    if (!opted && smem > 64 * 1024) {
+        if (hipFuncSetAttribute((const void *)k_route_lce<true>, hipFuncAttributeMaxDynamicSharedMemorySize, mfma::kMaxLds) != hipSuccess ||
+            hipFuncSetAttribute((const void *)k_route_lce<false>, hipFuncAttributeMaxDynamicSharedMemorySize, mfma::kMaxLds) != hipSuccess)
+            return BRA_ERR_LAUNCH;
+        opted = true;
+    }
+    ProfScope ps(st, K_MFMA_ROUTE_ROWS);
+    const dim3 grid((unsigned)(route_blocks + J.blocks)), threads(kRouteThreads);
+    if (p.vec) hipLaunchKernelGGL(k_route_lce<true>, grid, threads, smem, st, w.qk, w.qk + C, 2 * C, Ir, p.CS, p.blocks, route_blocks, J, D);
+    else hipLaunchKernelGGL(k_route_lce<false>, grid, threads, smem, st, w.qk, w.qk + C, 2 * C, Ir, p.CS, p.blocks, route_blocks, J, D);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
 template <int DP, int HPW, bool VEC>
-int launch_attention_t(const Dims &D, const float *qkv, const int32_t *Ir, float *o, hipStream_t st)
+int launch_attention_t(const Dims &D, const float *qkv, const int32_t *Ir, float *o, bool adds, hipStream_t st)
 {
     const int hgroups = (D.heads + HPW - 1) / HPW, tiles = (D.n + 15) / 16;
     int waves = 4, qtiles = 1;
@@ -226,7 +271,7 @@ int launch_attention_t(const Dims &D, const float *qkv, const int32_t *Ir, float
     const long blocks = (long)D.B * D.R * hgroups * qtiles;
     if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     hipLaunchKernelGGL((f32::k_attention<DP, HPW, VEC>), dim3((unsigned)blocks), dim3(64 * waves), 0, st, qkv, Ir, o, D, hgroups,
-                       qtiles);
+                       qtiles, adds);
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -237,23 +282,24 @@ int heads_per_group(const Dims &D)
     return D.heads > want / 2 ? want : (D.heads >= 2 ? 2 : 1);
 }
 
-int launch_attention(const Dims &D, const float *qkv, const int32_t *Ir, float *o, hipStream_t st)
+// adds: to what o holds (LCE(V)).
+int launch_attention(const Dims &D, const float *qkv, const int32_t *Ir, float *o, bool adds, hipStream_t st)
 {
     ProfScope ps(st, K_GEN_ATTENTION);
     if (D.d > kAttnF32MaxD) {
         hipLaunchKernelGGL(gen_attention, dim3(D.B * D.R * D.heads), dim3(256), D.k * sizeof(int), st, qkv, Ir, o, D,
-                           D.scale);
+                           D.scale, adds);
         return launched() ? BRA_OK : BRA_ERR_LAUNCH;
     }
     const int hpw = heads_per_group(D);
     const bool vec = D.d % 4 == 0;
     if (D.d <= 32) {
-        if (hpw == 4) return vec ? launch_attention_t<32, 4, true>(D, qkv, Ir, o, st) : launch_attention_t<32, 4, false>(D, qkv, Ir, o, st);
-        if (hpw == 2) return vec ? launch_attention_t<32, 2, true>(D, qkv, Ir, o, st) : launch_attention_t<32, 2, false>(D, qkv, Ir, o, st);
-        return vec ? launch_attention_t<32, 1, true>(D, qkv, Ir, o, st) : launch_attention_t<32, 1, false>(D, qkv, Ir, o, st);
+        if (hpw == 4) return vec ? launch_attention_t<32, 4, true>(D, qkv, Ir, o, adds, st) : launch_attention_t<32, 4, false>(D, qkv, Ir, o, adds, st);
+        if (hpw == 2) return vec ? launch_attention_t<32, 2, true>(D, qkv, Ir, o, adds, st) : launch_attention_t<32, 2, false>(D, qkv, Ir, o, adds, st);
+        return vec ? launch_attention_t<32, 1, true>(D, qkv, Ir, o, adds, st) : launch_attention_t<32, 1, false>(D, qkv, Ir, o, adds, st);
     }
-    if (hpw >= 2) return vec ? launch_attention_t<64, 2, true>(D, qkv, Ir, o, st) : launch_attention_t<64, 2, false>(D, qkv, Ir, o, st);
-    return vec ? launch_attention_t<64, 1, true>(D, qkv, Ir, o, st) : launch_attention_t<64, 1, false>(D, qkv, Ir, o, st);
+    if (hpw >= 2) return vec ? launch_attention_t<64, 2, true>(D, qkv, Ir, o, adds, st) : launch_attention_t<64, 2, false>(D, qkv, Ir, o, adds, st);
+    return vec ? launch_attention_t<64, 1, true>(D, qkv, Ir, o, adds, st) : launch_attention_t<64, 1, false>(D, qkv, Ir, o, adds, st);
 }
 
 template <typename T>
@@ -269,6 +315,7 @@ int forward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *Wl
     const int C = D.C;
     const f32::GemmJob<T, T, float> qkv_job = {X, Wqkv, w.qkv, M, C, 3 * C, 3 * C, 3 * C, C, nullptr, nullptr, 0};
     const int32_t *Ir = Ir_in_opt;
+    bool adds = false;
     int rc;
     if (!Ir_in_opt) {
         int32_t *dst = Ir_out_opt ? Ir_out_opt : w.ir;
@@ -279,7 +326,8 @@ int forward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *Wl
             rc = launch_gemm<false>(qkv_job, &rj, st);
         }
         if (rc != BRA_OK) return rc;
-        rc = route_rows(D, w.qk, w.qk + C, 2 * C, dst, nullptr, st);
+        // LCE(V) into the output map beside the routing; the attention adds itself to it
+        rc = launch_route_lce(D, w, lce::Taps(Wlce), dst, adds, st);
         if (rc != BRA_OK) return rc;
         Ir = dst;
     } else {
@@ -290,10 +338,12 @@ int forward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *Wl
         rc = launch_gemm<false>(qkv_job, (const f32::GemmJob<float, T, float> *)nullptr, st);
         if (rc != BRA_OK) return rc;
     }
-    rc = launch_attention(D, w.qkv, Ir, w.o, st);
+    rc = launch_attention(D, w.qkv, Ir, w.o, adds, st);
     if (rc != BRA_OK) return rc;
-    rc = lce::launch_lce(D, w.qkv + 2 * C, 3 * C, Wlce, w.o, C, K_GEN_LCE, st);
-    if (rc != BRA_OK) return rc;
+    if (!adds) {
+        rc = lce::launch_lce<float>(D, w.qkv + 2 * C, 3 * C, lce::Taps(Wlce), w.o, C, K_GEN_LCE, st);
+        if (rc != BRA_OK) return rc;
+    }
     ProfScope ps(st, K_GEN_GEMM_WO);
     return launch_gemm<false>(f32::GemmJob<float, T, T>{w.o, Wo, Y, M, C, C, C, C, C, nullptr, nullptr, 0},
                               (const f32::GemmJob<float, T, float> *)nullptr, st);
@@ -434,7 +484,9 @@ SharePlan share_plan(long M, int C)
     return {(int)((steps + per - 1) / per), (int)(per * 32)};
 }
 
-lce::LcePlan lce_grad_plan(const Dims &D) { return lce::lce_plan(D, 768, D.C % 2 == 0 ? 8 : 4); }
+// Channels per thread of the passes: those of the attention kernels that carry them (4-channel loads: two).  Two workgroups
+// per compute unit (29 x 28 x 28 x 96: whole gradient 176 us, 182 with three).
+lce::LcePlan lce_grad_plan(const Dims &D) { return lce::lce_plan(D, 512, D.d % 4 == 0 ? 8 : 4); }
 
 struct BwdWs {
     float *qkv, *o, *dO, *dqkv, *lse, *dsum, *part_qkv, *part_o, *part_lce;
@@ -467,29 +519,74 @@ BwdWs carve_bwd(const Dims &D, void *ws)
 }
 
 template <int DP, int HPW, bool VEC>
-int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, hipStream_t st)
+int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lce::Taps &taps, hipStream_t st)
 {
     const int hgroups = (D.heads + HPW - 1) / HPW, qt = f32::AttnShape<DP, HPW>::QT, tiles = (D.n + qt - 1) / qt;
     const long blocks = (long)D.B * D.R * hgroups * tiles;
-    if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((f32::k_attn_bwd_q<DP, HPW, VEC>), dim3((unsigned)blocks), dim3(256), 0, st, w.qkv, w.dO, Ir, w.o,
-                       w.dqkv, w.lse, w.dsum, D, hgroups, tiles);
-    hipLaunchKernelGGL((f32::k_attn_bwd_kv<DP, HPW, VEC>), dim3((unsigned)blocks), dim3(256), 0, st, w.qkv, w.dO, Ir, w.lse,
-                       w.dsum, w.dqkv, D, hgroups, tiles);
-    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+    // The passes of the depth-wise convolution's gradients lie behind the workgroups of the attention: the one with the tap
+    // gradients beside the query side, which leaves dV to be added to by the key side, O += LCE(V) beside the key side.  In
+    // front of the query side it was slower (4 x 56 x 56 x 64, k = 2: 100.9 us behind, 105.6 in front; 8 x 28 x 28 x 128: 92.0, 95.5).
+    const float *V = w.qkv + 2 * D.C;
+    const lce::GradJob<float> grad = {w.dO, V, taps, w.dqkv + 2 * D.C, w.part_lce, 3 * D.C, 3 * D.C, lce_grad_plan(D)};
+    const lce::AddJob<float> add = lce::add_job<float>(D, V, 3 * D.C, taps, w.o, D.C, VEC ? 2 : 1, 256);
+    if (blocks + std::max(grad.p.blocks(), add.blocks) > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((f32::k_attn_bwd_q<DP, HPW, VEC>), dim3((unsigned)(blocks + grad.p.blocks())), dim3(256), 0, st, w.qkv, w.dO, Ir, w.o,
+                       w.dqkv, w.lse, w.dsum, D, hgroups, tiles, grad, grad.p.blocks());
+    hipLaunchKernelGGL((f32::k_attn_bwd_kv<DP, HPW, VEC>), dim3((unsigned)(blocks + add.blocks)), dim3(256), 0, st, w.qkv, w.dO, Ir, w.lse,
+                       w.dsum, w.dqkv, D, hgroups, tiles, add, add.blocks);
+    if (!launched()) return BRA_ERR_LAUNCH;
+    return add.blocks ? BRA_OK : lce::launch_lce<float>(D, V, 3 * D.C, taps, w.o, D.C, K_GEN_BACKWARD, st);
 }
 
-int launch_attn_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, hipStream_t st)
+int launch_attn_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, const lce::Taps &taps, hipStream_t st)
 {
     const int hpw = heads_per_group(D);
     const bool vec = D.d % 4 == 0;
     if (D.d <= 32) {
-        if (hpw == 4) return vec ? launch_attn_bwd_t<32, 4, true>(D, w, Ir, st) : launch_attn_bwd_t<32, 4, false>(D, w, Ir, st);
-        if (hpw == 2) return vec ? launch_attn_bwd_t<32, 2, true>(D, w, Ir, st) : launch_attn_bwd_t<32, 2, false>(D, w, Ir, st);
-        return vec ? launch_attn_bwd_t<32, 1, true>(D, w, Ir, st) : launch_attn_bwd_t<32, 1, false>(D, w, Ir, st);
+        if (hpw == 4) return vec ? launch_attn_bwd_t<32, 4, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<32, 4, false>(D, w, Ir, taps, st);
+        if (hpw == 2) return vec ? launch_attn_bwd_t<32, 2, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<32, 2, false>(D, w, Ir, taps, st);
+        return vec ? launch_attn_bwd_t<32, 1, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<32, 1, false>(D, w, Ir, taps, st);
     }
-    if (hpw >= 2) return vec ? launch_attn_bwd_t<64, 2, true>(D, w, Ir, st) : launch_attn_bwd_t<64, 2, false>(D, w, Ir, st);
-    return vec ? launch_attn_bwd_t<64, 1, true>(D, w, Ir, st) : launch_attn_bwd_t<64, 1, false>(D, w, Ir, st);
+    if (hpw >= 2) return vec ? launch_attn_bwd_t<64, 2, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<64, 2, false>(D, w, Ir, taps, st);
+    return vec ? launch_attn_bwd_t<64, 1, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<64, 1, false>(D, w, Ir, taps, st);
+}
+
+// The gradients take five launches: the products of the recomputation, query side and key side (each with a depth-wise pass),
+// the products that end them, the sums of the partial matrices.  With a launch for each of the eight kernels (us): 8 x 28 x 28
+// x 128 float32, k = 4: 117 -> 91; 1 x 14 x 14 x 64: 53 -> 31; 2 x 14 x 14 x 256, k = 16: 98 -> 68; 29 x 28 x 28 x 96 bf16: 204 -> 176.
+// 64-column tiles where the wider ones leave the chip under-filled, as in launch_gemm_vec.
+template <typename T>
+int launch_gemm_both(const f32::GemmJob<T, T, float> &J0, const f32::GemmJob<T, T, float> &J1, hipStream_t st)
+{
+    const long mt = (J0.M + f32::kGemmBM - 1) / f32::kGemmBM;
+    const bool narrow = J1.N <= 64 || mt * ((J0.N + 127) / 128 + (J1.N + 127) / 128) < 512;
+    const int bn = narrow ? 64 : 128;
+    const long b0 = mt * ((J0.N + bn - 1) / bn), b1 = mt * ((J1.N + bn - 1) / bn);
+    if (b0 + b1 > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)(b0 + b1));
+    const bool vec = J1.K % 4 == 0;              // all sizes and pitches are multiples of C
+    if (vec && narrow) hipLaunchKernelGGL((f32::k_gemm_both<true, 64, T>), grid, dim3(256), 0, st, J0, J1, (int)b0);
+    else if (vec) hipLaunchKernelGGL((f32::k_gemm_both<true, 128, T>), grid, dim3(256), 0, st, J0, J1, (int)b0);
+    else if (narrow) hipLaunchKernelGGL((f32::k_gemm_both<false, 64, T>), grid, dim3(256), 0, st, J0, J1, (int)b0);
+    else hipLaunchKernelGGL((f32::k_gemm_both<false, 128, T>), grid, dim3(256), 0, st, J0, J1, (int)b0);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+template <typename T>
+int launch_gemm_end(const f32::TnJob<T, float> &J0, const f32::TnJob<float, T> &J1, int share_tokens, const f32::GemmJob<float, T, T> &J, hipStream_t st)
+{
+    const long mt = (J.M + f32::kGemmBM - 1) / f32::kGemmBM;
+    const bool narrow = J.N <= 64 || mt * ((J.N + 127) / 128) < 512;
+    const int bn = narrow ? 64 : 128;
+    const long blocks = mt * ((J.N + bn - 1) / bn) + J0.blocks + J1.blocks;
+    if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)blocks);
+    const bool vec = J.N % 4 == 0;               // all sizes and pitches are multiples of C
+    if (vec && narrow) hipLaunchKernelGGL((f32::k_gemm_end<true, 64, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
+    else if (vec) hipLaunchKernelGGL((f32::k_gemm_end<true, 128, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
+    else if (narrow) hipLaunchKernelGGL((f32::k_gemm_end<false, 64, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
+    else hipLaunchKernelGGL((f32::k_gemm_end<false, 128, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
 template <typename T>
@@ -500,32 +597,21 @@ int backward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *W
     const long M = (long)D.B * D.N;
     const int C = D.C, C3 = 3 * D.C;
     ProfScope ps(st, K_GEN_BACKWARD);
-    const f32::GemmJob<float, T, float> *none = nullptr;
-    // forward intermediates again: Q | K | V (the attention output comes out of the query side)
-    int rc = launch_gemm<false>(f32::GemmJob<T, T, float>{X, Wqkv, w.qkv, M, C, C3, C3, C3, C, nullptr, nullptr, 0}, none, st);
+    // forward intermediates again: Q | K | V (the attention output comes out of the query side); dO = dY Wo^T
+    int rc = launch_gemm_both<T>(f32::GemmJob<T, T, float>{X, Wqkv, w.qkv, M, C, C3, C3, C3, C, nullptr, nullptr, 0},
+                                 f32::GemmJob<T, T, float>{dY, Wo, w.dO, M, C, C, C, C, C, nullptr, nullptr, 0}, st);
     if (rc != BRA_OK) return rc;
-    // dO = dY Wo^T
-    rc = launch_gemm<true>(f32::GemmJob<T, T, float>{dY, Wo, w.dO, M, C, C, C, C, C, nullptr, nullptr, 0}, none, st);
-    if (rc != BRA_OK) return rc;
-    rc = launch_attn_bwd(D, w, Ir, st);
-    if (rc != BRA_OK) return rc;
-    // O = attention + LCE(V) for dWo; dV += LCE^T(dO) and the tap gradients
-    rc = lce::launch_lce(D, w.qkv + 2 * C, C3, Wlce, w.o, C, K_GEN_BACKWARD, st);
+    // O = attention + LCE(V) for dWo, dQ, dK, dV and the tap gradients
+    rc = launch_attn_bwd(D, w, Ir, lce::Taps(Wlce), st);
     if (rc != BRA_OK) return rc;
     const lce::LcePlan lp = lce_grad_plan(D);
-    rc = lce::launch_lce_grad(D, lp, w.dO, w.qkv + 2 * C, C3, Wlce, w.dqkv + 2 * C, C3, w.part_lce, st);
-    if (rc != BRA_OK) return rc;
-    // dX = [dQ | dK | dV] Wqkv^T
-    rc = launch_gemm<true>(f32::GemmJob<float, T, T>{w.dqkv, Wqkv, dX, M, C3, C3, C, C, C3, nullptr, nullptr, 0}, none, st);
-    if (rc != BRA_OK) return rc;
-    // dWqkv = X^T [dQ | dK | dV], dWo = O^T dY
+    // dX = [dQ | dK | dV] Wqkv^T; dWqkv = X^T [dQ | dK | dV], dWo = O^T dY
     const SharePlan sp = share_plan(M, C);
     const int cb = (C + 63) / 64;
-    const f32::TnJob<T, float> jq = {X, w.dqkv, w.part_qkv, C, C3, C, C3, cb * ((C3 + 63) / 64) * sp.shares};
-    const f32::TnJob<float, T> jo = {w.o, dY, w.part_o, C, C, C, C, cb * cb * sp.shares};
-    const dim3 tgrid((unsigned)(jq.blocks + jo.blocks));
-    if (C % 4 == 0) hipLaunchKernelGGL((f32::k_gemm_tn<true, T, float, float, T>), tgrid, dim3(256), 0, st, jq, jo, M, sp.tokens);
-    else hipLaunchKernelGGL((f32::k_gemm_tn<false, T, float, float, T>), tgrid, dim3(256), 0, st, jq, jo, M, sp.tokens);
+    rc = launch_gemm_end<T>(f32::TnJob<T, float>{X, w.dqkv, w.part_qkv, C, C3, C, C3, cb * ((C3 + 63) / 64) * sp.shares},
+                            f32::TnJob<float, T>{w.o, dY, w.part_o, C, C, C, C, cb * cb * sp.shares}, sp.tokens,
+                            f32::GemmJob<float, T, T>{w.dqkv, Wqkv, dX, M, C3, C3, C, C, C3, nullptr, nullptr, 0}, st);
+    if (rc != BRA_OK) return rc;
     const bwd::ReduceJob r0 = bwd::reduce_job(w.part_qkv, dWqkv, sp.shares, C3 * C), r1 = bwd::reduce_job(w.part_o, dWo, sp.shares, C * C),
                          r2 = bwd::reduce_job(w.part_lce, dWlce, lp.groups, 25 * C);
     hipLaunchKernelGGL(bwd::k_reduce_parts, dim3(r0.blocks + r1.blocks + r2.blocks), dim3(256), 0, st, r0, r1, r2);

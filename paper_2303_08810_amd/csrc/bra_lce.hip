@@ -115,7 +115,7 @@ int route_rows_lce_bf16(const Dims &D, const float *Qr, const float *Kr, int32_t
 int lce_add_bf16(const Dims &D, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, int ldo, int kernel_id, hipStream_t st)
 {
     const Job J = plain_job(D, V, Wlce, O, ldo);
-    if (!offsets_fit(D, J.T, ldo)) return launch_lce<bf16_t, bf16_t>(D, V, D.C, Wlce, O, ldo, kernel_id, st);
+    if (!offsets_fit(D, J.T, ldo)) return launch_lce<bf16_t>(D, V, D.C, Taps(Wlce), O, ldo, kernel_id, st);
     if (D.C % 2 || ldo % 2 || J.blocks() > 0x7ffffff0L) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);
     hipLaunchKernelGGL(k_lce_add, dim3((unsigned)J.blocks()), dim3(256), 0, st, J, D);
@@ -133,10 +133,10 @@ int lce_backward_bf16(const Dims &D, const BackwardJobs &L, int kernel_id, hipSt
     const Job &G = L.grad, &A = L.add;
     if (D.C % 2 || G.ldo % 2) return BRA_ERR_UNSUPPORTED;
     if (!L.fit) {
-        const int rc = launch_lce<bf16_t, bf16_t>(D, A.In, D.C, A.Wlce, A.Out, A.ldo, kernel_id, st);
+        const int rc = launch_lce<bf16_t>(D, A.In, D.C, Taps(A.Wlce), A.Out, A.ldo, kernel_id, st);
         if (rc != BRA_OK) return rc;
         ProfScope ps(st, kernel_id);
-        return launch_lce_grad<bf16_t, bf16_t>(D, wide_grad_plan(D), G.In, G.V, D.C, G.Wlce, G.Out, G.ldo, G.Part, st);
+        return launch_lce_grad<bf16_t>(D, GradJob<bf16_t>{G.In, G.V, Taps(G.Wlce), G.Out, G.Part, D.C, G.ldo, wide_grad_plan(D)}, st);
     }
     if (G.blocks() + A.blocks() > 0x7ffffff0L) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);

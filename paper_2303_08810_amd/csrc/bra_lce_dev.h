@@ -6,6 +6,7 @@
 
 #include "bra_mfma_dev.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace bra {
@@ -59,25 +60,160 @@ __device__ __forceinline__ void store_channels(bf16_t *p, const Channels<VW> &r)
     else *p = f32_to_bf16(r.v[0]);
 }
 
+// Workgroups of a pass beside those of another kernel, in front of them or behind: true for the `beside` ones of the pass.
+// block: the number within its own kind.  (Evenly among the others, the two slow each other down: see launch_attn_bwd.)
+__device__ __forceinline__ bool block_of_pass(int beside, bool front, int &block, int &blocks)
+{
+    const int others = (int)gridDim.x - beside, first = front ? 0 : others;
+    const bool of_pass = (int)blockIdx.x >= first && (int)blockIdx.x < first + beside;
+    block = (int)blockIdx.x - (of_pass ? first : front ? beside : 0);
+    blocks = of_pass ? beside : others;
+    return of_pass;
+}
+
+// The [C][25] taps, float32 or bf16.
+struct Taps {
+    const void *w;
+    bool bf16;
+
+    Taps() : w(nullptr), bf16(false) {}
+    explicit Taps(const float *p) : w(p), bf16(false) {}
+    explicit Taps(const bf16_t *p) : w(p), bf16(true) {}
+};
+
+// The taps of channels c0 .. c0 + 63 (those that exist) -> table[25][64], requested all at once.
+template <int NT>
+__device__ __forceinline__ void stage_taps(const Taps &taps, int c0, int C, float *table)
+{
+    constexpr int L = (25 * 64 + NT - 1) / NT;
+    const int count = min(64, C - c0) * 25;
+    float v[L];
+    if (taps.bf16) {
+#pragma unroll
+        for (int u = 0; u < L; ++u) v[u] = bf16_to_f32(((const bf16_t *)taps.w)[(size_t)c0 * 25 + min((int)threadIdx.x + NT * u, count - 1)]);
+    } else {
+#pragma unroll
+        for (int u = 0; u < L; ++u) v[u] = ((const float *)taps.w)[(size_t)c0 * 25 + min((int)threadIdx.x + NT * u, count - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < L; ++u) {
+        const int e = threadIdx.x + NT * u;
+        if (e < count) table[e % 25 * 64 + e / 25] = v[u];
+    }
+    __syncthreads();
+}
+
 // ---------------------------------------------------------------------------
 // Out[t][c] += sum_{ky,kx} w[c][ky][kx] In[t + (ky - 2, kx - 2)][c] over the H x W map (zero outside):
-// LCE (Eq. 7).  Workgroup: 64 channels of 256 VW / 64 column pieces; a thread walks down kLceRows rows of one
-// column with VW (2 or 1) channels: an input row of 5 columns is read once and goes into the output rows it
-// belongs to.  The taps pass through LDS once per workgroup: read per thread from the [C][25] tensor they would
-// cost a cache line per lane.  (Requesting all 40 values first, or a row ahead, was no faster: 21 and 23 against 17 us
-// on a 16 x 56 x 56 x 64 map; the registers cost more wavefronts than the latency they hide.)
+// LCE (Eq. 7).  Workgroup: 64 channels; a wavefront takes kLceRows rows of VW neighbouring pairs of columns, a thread VW (2 or
+// 1) channels of one pair: an input row of 6 columns is read once and goes into the outputs it belongs to.  Image and rows
+// are the same for all lanes, so that a load is a scalar row address and a 32-bit lane offset.  The taps pass through
+// LDS once per workgroup: read per thread from the [C][25] tensor they would cost a cache line per lane.
+// Bound by the latency of its eight rows of loads and by the FMAs.  16 x 56 x 56 x 64 float32 beside the routing: 11 us for
+// both, 19 with one column per thread and addresses of its own for every load (k_lce_far; 122 registers for 84).
 // Row pitches ldi, ldo.
 constexpr int kLceRows = 4;
 
-template <typename TM, typename TW, int VW>
-__global__ __launch_bounds__(256) void k_lce(const TM *__restrict__ In, int ldi, const TW *__restrict__ Wlce,
-                                             TM *__restrict__ Out, int ldo, Dims D, int cblocks)
+template <typename TM>
+struct AddJob {
+    const TM *In;
+    Taps taps;
+    TM *Out;
+    int ldi, ldo, cblocks, blocks, groups;       // groups: of VW pairs of columns in a row
+};
+
+// Workgroup `block` of J, NT threads; table: [25][64].  ADDS = false: Out = LCE(In).
+template <int VW, bool ADDS, int NT, typename TM>
+__device__ __forceinline__ void lce_block(const AddJob<TM> &J, const Dims &D, int block, float *table)
 {
-    __shared__ float taps[25][64];
+    constexpr int CPW = 64 / VW;
+    const int cb = block % J.cblocks, c0 = 64 * cb, strips = (D.H + kLceRows - 1) / kLceRows;
+    stage_taps<NT>(J.taps, c0, D.C, table);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64, cl = lane % CPW * VW;
+    const int q = block / J.cblocks * (NT / 64) + wave, gx = q % J.groups, y0 = q / J.groups % strips * kLceRows, b = q / (J.groups * strips);
+    const int x = 2 * (gx * VW + lane / CPW);
+    if (b >= D.B || x >= D.W || c0 + cl >= D.C) return;
+    const bool right = x + 1 < D.W;
+    unsigned xo[6];
+    bool xok[6];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        xok[j] = (unsigned)(x + j - 2) < (unsigned)D.W;
+        xo[j] = (unsigned)sizeof(TM) * (min(max(x + j - 2, 0), D.W - 1) * J.ldi + cl);
+    }
+    const bool edge = !__all(xok[0] && xok[1] && xok[4] && xok[5]);
+    float w[25][VW];
+#pragma unroll
+    for (int t = 0; t < 25; ++t)
+#pragma unroll
+        for (int v = 0; v < VW; ++v) w[t][v] = table[64 * t + cl + v];
+    Channels<VW> acc[kLceRows][2] = {};
+    const char *img = (const char *)(J.In + (size_t)b * D.N * J.ldi + c0);
+    const size_t pitch = sizeof(TM) * (size_t)D.W * J.ldi;
+#pragma unroll
+    for (int dy = 0; dy < kLceRows + 4; ++dy) {
+        const int y = y0 + dy - 2;
+        if (y < 0 || y >= D.H) continue;
+        const char *row = img + y * pitch;
+        Channels<VW> in[6];
+#pragma unroll
+        for (int j = 0; j < 6; ++j) in[j] = load_channels<VW>((const TM *)(row + xo[j]));
+        if (edge) {
+#pragma unroll
+            for (int j = 0; j < 6; ++j)
+#pragma unroll
+                for (int v = 0; v < VW; ++v) in[j].v[v] = xok[j] ? in[j].v[v] : 0.f;
+        }
+#pragma unroll
+        for (int r = 0; r < kLceRows; ++r) {
+            const int ky = dy - r;
+            if (ky < 0 || ky > 4) continue;
+#pragma unroll
+            for (int kx = 0; kx < 5; ++kx)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int v = 0; v < VW; ++v) acc[r][j].v[v] = fmaf(w[5 * ky + kx][v], in[kx + j].v[v], acc[r][j].v[v]);
+        }
+    }
+    char *out = (char *)(J.Out + ((size_t)b * D.N + (size_t)y0 * D.W) * J.ldo + c0);
+    const unsigned oo = (unsigned)sizeof(TM) * (x * J.ldo + cl), ostep = (unsigned)sizeof(TM) * J.ldo;
+#pragma unroll
+    for (int r = 0; r < kLceRows; ++r) {
+        if (y0 + r >= D.H) break;
+        char *row = out + r * (sizeof(TM) * (size_t)D.W * J.ldo);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (j && !right) break;
+            TM *at = (TM *)(row + (oo + j * ostep));
+            Channels<VW> o = acc[r][j];
+            if (ADDS) {
+                const Channels<VW> there = load_channels<VW>(at);
+#pragma unroll
+                for (int v = 0; v < VW; ++v) o.v[v] += there.v[v];
+            }
+            store_channels<VW>(at, o);
+        }
+    }
+}
+
+template <typename TM, int VW>
+__global__ __launch_bounds__(256, 4) void k_lce(AddJob<TM> J, Dims D)
+{
+    __shared__ float table[25 * 64];
+    lce_block<VW, true, 256>(J, D, mfma::swizzled_block(), table);
+}
+
+// The same for maps that k_lce's 32-bit offsets and numbers do not cover: a thread takes kLceRows rows of one column, all
+// addresses 64-bit.
+template <typename TM, int VW>
+__global__ __launch_bounds__(256) void k_lce_far(const TM *__restrict__ In, int ldi, Taps source, TM *__restrict__ Out, int ldo,
+                                                 Dims D, int cblocks)
+{
+    __shared__ float taps[25 * 64];
     constexpr int CPW = 64 / VW, COLS = 256 / CPW;
     const int block = mfma::swizzled_block(), cb = block % cblocks, c0 = 64 * cb, yb_n = (D.H + kLceRows - 1) / kLceRows;
-    for (int e = threadIdx.x; e < min(64, D.C - c0) * 25; e += 256) taps[e % 25][e / 25] = load_f32(Wlce + (size_t)c0 * 25 + e);
-    __syncthreads();
+    stage_taps<256>(source, c0, D.C, taps);
     const int cl = ((int)threadIdx.x % CPW) * VW, c = c0 + cl;
     const long q = (long)(block / cblocks) * COLS + threadIdx.x / CPW;
     if (q >= (long)D.B * yb_n * D.W || c >= D.C) return;
@@ -89,7 +225,7 @@ __global__ __launch_bounds__(256) void k_lce(const TM *__restrict__ In, int ldi,
 #pragma unroll
     for (int t = 0; t < 25; ++t)
 #pragma unroll
-        for (int v = 0; v < VW; ++v) w[t][v] = taps[t][cl + v];
+        for (int v = 0; v < VW; ++v) w[t][v] = taps[64 * t + cl + v];
     Channels<VW> acc[kLceRows];
 #pragma unroll
     for (int r = 0; r < kLceRows; ++r)
@@ -128,20 +264,64 @@ __global__ __launch_bounds__(256) void k_lce(const TM *__restrict__ In, int ldi,
     }
 }
 
-// Launch of k_lce; a BRA_* code.
-template <typename TM, typename TW>
-int launch_lce(const Dims &D, const TM *In, int ldi, const TW *Wlce, TM *Out, int ldo, int kernel_id, hipStream_t st)
+// blocks: a multiple of 8; 0 where offsets or numbers need more than 32 bits.  channels: per thread, threads: per workgroup.
+template <typename TM>
+AddJob<TM> add_job(const Dims &D, const TM *In, int ldi, const Taps &taps, TM *Out, int ldo, int channels, int threads)
 {
-    const int cblocks = (D.C + 63) / 64;
-    const long pieces = (long)D.B * ((D.H + kLceRows - 1) / kLceRows) * D.W;
-    const bool pairs = D.C % 2 == 0;
-    const int cols = pairs ? 8 : 4;
-    const long blocks = (pieces + cols - 1) / cols * cblocks;
-    if (blocks > 0x7ffffff0L) return BRA_ERR_UNSUPPORTED;
+    const int cblocks = (D.C + 63) / 64, pairs = (D.W + 1) / 2, groups = (pairs + channels - 1) / channels, per = threads / 64;
+    const long waves = (long)D.B * ((D.H + kLceRows - 1) / kLceRows) * groups, blocks = (waves + per - 1) / per * cblocks;
+    const bool fits = (long)D.W * std::max(ldi, ldo) * (long)sizeof(TM) < (1L << 31) && waves + per < (1L << 31) && blocks < 0x7ffffff0L;
+    return AddJob<TM>{In, taps, Out, ldi, ldo, cblocks, fits ? (int)((blocks + 7) / 8 * 8) : 0, groups};
+}
+
+// Out += LCE(In), any map; a BRA_* code.
+template <typename TM>
+int launch_lce(const Dims &D, const TM *In, int ldi, const Taps &taps, TM *Out, int ldo, int kernel_id, hipStream_t st)
+{
+    const bool two = D.C % 2 == 0;
+    const AddJob<TM> J = add_job<TM>(D, In, ldi, taps, Out, ldo, two ? 2 : 1, 256);
+    const int cols = two ? 8 : 4;
+    const long blocks = ((long)D.B * ((D.H + kLceRows - 1) / kLceRows) * D.W + cols - 1) / cols * J.cblocks;
+    if (!J.blocks && blocks > 0x7ffffff0L) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);
-    if (pairs) hipLaunchKernelGGL((k_lce<TM, TW, 2>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), 0, st, In, ldi, Wlce, Out, ldo, D, cblocks);
-    else hipLaunchKernelGGL((k_lce<TM, TW, 1>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), 0, st, In, ldi, Wlce, Out, ldo, D, cblocks);
+    const dim3 far((unsigned)((blocks + 7) / 8 * 8)), near((unsigned)J.blocks);
+    if (J.blocks && two) hipLaunchKernelGGL((k_lce<TM, 2>), near, dim3(256), 0, st, J, D);
+    else if (J.blocks) hipLaunchKernelGGL((k_lce<TM, 1>), near, dim3(256), 0, st, J, D);
+    else if (two) hipLaunchKernelGGL((k_lce_far<TM, 2>), far, dim3(256), 0, st, In, ldi, taps, Out, ldo, D, J.cblocks);
+    else hipLaunchKernelGGL((k_lce_far<TM, 1>), far, dim3(256), 0, st, In, ldi, taps, Out, ldo, D, J.cblocks);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+struct LcePlan {
+    int cblocks, height, strips_per_wg, groups;
+    long strips;
+
+    __host__ __device__ int blocks() const { return (groups * cblocks + 7) / 8 * 8; }
+};
+
+template <typename TM>
+struct GradJob {
+    const TM *dO, *V;
+    Taps taps;
+    TM *dV;
+    float *Part;
+    int ldv, lddv;
+    LcePlan p;
+};
+
+// About `slots` workgroups of `cols` columns in all, each with the strips of one group.
+inline LcePlan lce_plan(const Dims &D, int slots, int cols)
+{
+    LcePlan p;
+    p.cblocks = (D.C + 63) / 64;
+    const long want = slots / p.cblocks > 0 ? slots / p.cblocks : 1;
+    for (p.height = 20;; p.height /= 2) {            // 20, 10, 5
+        p.strips = (long)D.B * ((D.H + p.height - 1) / p.height) * ((D.W + cols - 1) / cols);
+        if (p.height == 5 || p.strips >= want) break;
+    }
+    p.strips_per_wg = (int)((p.strips + want - 1) / want);
+    p.groups = (int)((p.strips + p.strips_per_wg - 1) / p.strips_per_wg);
+    return p;
 }
 
 // ---------------------------------------------------------------------------
@@ -157,18 +337,19 @@ int launch_lce(const Dims &D, const TM *In, int ldi, const TW *Wlce, TM *Out, in
 // height is a multiple of 5 (the window's rows rotate through fixed registers): 20, or less where that leaves
 // too few workgroups (8 x 28 x 28 x 128 float32: 26 us with strips of 20, 128 workgroups).
 
-template <typename TM, typename TW, int VW>
-__global__ __launch_bounds__(256) void k_lce_grad(const TM *__restrict__ dO, const TM *__restrict__ V, int ldv,
-                                                  const TW *__restrict__ Wlce, TM *__restrict__ dV, int lddv,
-                                                  float *__restrict__ Part, Dims D, int cblocks, long strips,
-                                                  int strips_per_wg, int height)
+// Workgroup `block` of J, 256 threads; red: [25][256].  ADDS = false: dV = LCE^T(dO).
+template <int VW, bool ADDS, typename TM>
+__device__ __forceinline__ void lce_grad_block(const GradJob<TM> &J, const Dims &D, int block, float *red)
 {
     constexpr int CPW = 64 / VW, COLS = 256 / CPW;
-    __shared__ float red[25 * 256];
-    const int block = mfma::swizzled_block(), cb = block % cblocks, c0 = 64 * cb, grp = block / cblocks;
+    const TM *__restrict__ dO = J.dO, *__restrict__ V = J.V;
+    TM *__restrict__ dV = J.dV;
+    float *__restrict__ Part = J.Part;
+    const int ldv = J.ldv, lddv = J.lddv, height = J.p.height, strips_per_wg = J.p.strips_per_wg;
+    const long strips = J.p.strips;
+    const int cblocks = J.p.cblocks, cb = block % cblocks, c0 = 64 * cb, grp = block / cblocks;
     if (grp * (long)strips_per_wg >= strips) return;
-    for (int e = threadIdx.x; e < min(64, D.C - c0) * 25; e += 256) red[(e % 25) * 64 + e / 25] = load_f32(Wlce + (size_t)c0 * 25 + e);
-    __syncthreads();
+    stage_taps<256>(J.taps, c0, D.C, red);
     const int cl = ((int)threadIdx.x % CPW) * VW, col = threadIdx.x / CPW;
     const bool live = c0 + cl < D.C;
     const int c = live ? c0 + cl : c0;
@@ -211,7 +392,8 @@ __global__ __launch_bounds__(256) void k_lce_grad(const TM *__restrict__ dO, con
                 load_row(y + 2, win[(u + 4) % 5]);
                 const size_t tok = b * D.N + (size_t)y * D.W + x;
                 const Channels<VW> vc = load_channels<VW>(V + tok * ldv + c);
-                Channels<VW> dv = load_channels<VW>(dV + tok * lddv + c);
+                Channels<VW> dv = {};
+                if (ADDS) dv = load_channels<VW>(dV + tok * lddv + c);
 #pragma unroll
                 for (int r = 0; r < 5; ++r)
 #pragma unroll
@@ -242,38 +424,20 @@ __global__ __launch_bounds__(256) void k_lce_grad(const TM *__restrict__ dO, con
     }
 }
 
-struct LcePlan {
-    int cblocks, height, strips_per_wg, groups;
-    long strips;
-};
-
-// About `slots` workgroups of `cols` columns in all, each with the strips of one group.
-inline LcePlan lce_plan(const Dims &D, int slots, int cols)
+template <typename TM, int VW>
+__global__ __launch_bounds__(256) void k_lce_grad(GradJob<TM> J, Dims D)
 {
-    LcePlan p;
-    p.cblocks = (D.C + 63) / 64;
-    const long want = slots / p.cblocks > 0 ? slots / p.cblocks : 1;
-    for (p.height = 20;; p.height /= 2) {            // 20, 10, 5
-        p.strips = (long)D.B * ((D.H + p.height - 1) / p.height) * ((D.W + cols - 1) / cols);
-        if (p.height == 5 || p.strips >= want) break;
-    }
-    p.strips_per_wg = (int)((p.strips + want - 1) / want);
-    p.groups = (int)((p.strips + p.strips_per_wg - 1) / p.strips_per_wg);
-    return p;
+    __shared__ float red[25 * 256];
+    lce_grad_block<VW, true>(J, D, mfma::swizzled_block(), red);
 }
 
-// Launch of k_lce_grad (Part: lce_plan(D, slots).groups arrays of 25 C floats); a BRA_* code.
-template <typename TM, typename TW>
-int launch_lce_grad(const Dims &D, const LcePlan &p, const TM *dO, const TM *V, int ldv, const TW *Wlce, TM *dV, int lddv,
-                    float *Part, hipStream_t st)
+// Launch of k_lce_grad (Part: p.groups arrays of 25 C floats); a BRA_* code.
+template <typename TM>
+int launch_lce_grad(const Dims &D, const GradJob<TM> &J, hipStream_t st)
 {
-    const dim3 grid((unsigned)((p.groups * p.cblocks + 7) / 8 * 8));
-    if (D.C % 2 == 0)
-        hipLaunchKernelGGL((k_lce_grad<TM, TW, 2>), grid, dim3(256), 0, st, dO, V, ldv, Wlce, dV, lddv, Part, D, p.cblocks,
-                           p.strips, p.strips_per_wg, p.height);
-    else
-        hipLaunchKernelGGL((k_lce_grad<TM, TW, 1>), grid, dim3(256), 0, st, dO, V, ldv, Wlce, dV, lddv, Part, D, p.cblocks,
-                           p.strips, p.strips_per_wg, p.height);
+    const dim3 grid((unsigned)J.p.blocks());
+    if (D.C % 2 == 0) hipLaunchKernelGGL((k_lce_grad<TM, 2>), grid, dim3(256), 0, st, J, D);
+    else hipLaunchKernelGGL((k_lce_grad<TM, 1>), grid, dim3(256), 0, st, J, D);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 

@@ -192,17 +192,6 @@ __device__ __forceinline__ void walk_tile(const bf16_t *__restrict__ In, const b
     }
 }
 
-// Workgroups of a pass beside those of another kernel, in front of them or behind: true for the `beside` ones of the pass.
-// block: the number within its own kind.  (Evenly among the others, the two slow each other down: see launch_attn_bwd.)
-__device__ __forceinline__ bool block_of_pass(int beside, bool front, int &block, int &blocks)
-{
-    const int others = (int)gridDim.x - beside, first = front ? 0 : others;
-    const bool of_pass = (int)blockIdx.x >= first && (int)blockIdx.x < first + beside;
-    block = (int)blockIdx.x - (of_pass ? first : front ? beside : 0);
-    blocks = of_pass ? beside : others;
-    return of_pass;
-}
-
 // Lane offsets are 32-bit: the rows of a tile (with the window, within the map) must span less than 2 GiB in either map.
 inline bool offsets_fit(const Dims &D, const Tiling &T, int ldo)
 {
