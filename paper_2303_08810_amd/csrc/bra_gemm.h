@@ -59,6 +59,9 @@ struct GemmTn {
 int gemm_tn_shares(long M, int KA0, int N0, int KA1, int N1);
 int gemm_tn(const GemmTn &J0, const GemmTn &J1, long M, int kernel_id, hipStream_t st);
 
+// The same and b: Out = In Wt^T over the M rows into one buffer, a contraction of K > 64; small ones in one launch.
+int gemm_bt_tn(const GemmTn &J0, const GemmTn &J1, const GemmHalf &b, long M, int K, int kernel_id, hipStream_t st);
+
 // The region-level product on its own.
 int gemm_regions(const GemmRegions &r, const bf16_t *W, int ldw, int K, int kernel_id, hipStream_t st);
 

@@ -694,6 +694,36 @@ __global__ __launch_bounds__(256, 2) void k_gemm_tn(GemmTn J0, GemmTn J1, int bl
     tn_block(second ? J1 : J0, second ? (int)blockIdx.x - blocks0 : (int)blockIdx.x, M, share_tokens, A0, A1, B0, B1);
 }
 
+// Out = In Wt^T and both contractions over the tokens in one launch: dX, dWqkv and dWo, once dQ, dK and dV are there.
+constexpr size_t kTnBytes = 4 * 64 * 128 * 2;
+
+template <int BM, int BN>
+__global__ __launch_bounds__(256, 2) void k_gemm_bt_tn(GemmTn J0, GemmTn J1, int blocks0, int tiles, int share_tokens, const bf16_t *__restrict__ In,
+                                                       const bf16_t *__restrict__ Wt, int ldw, int M, int K, int Nout, GemmOut out)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    bf16_t *lds = (bf16_t *)smem;
+    if ((int)blockIdx.x < tiles) {
+        dma_tile<BM, BN, 2, true, false>(In, Wt, ldw, M, K, Nout, out, swizzled(blockIdx.x, tiles), lds);
+        return;
+    }
+    const int block = (int)blockIdx.x - tiles;
+    const bool second = block >= blocks0;
+    tn_block(second ? J1 : J0, second ? block - blocks0 : block, M, share_tokens, lds, lds + 8192, lds + 2 * 8192, lds + 3 * 8192);
+}
+
+template <int BM, int BN>
+int launch_bt_tn(const GemmTn &J0, const GemmTn &J1, long blocks0, long tn_blocks, int share_tokens, const GemmHalf &b, long M, int K, hipStream_t st)
+{
+    static bool opted = false;
+    if (!opt_in(k_gemm_bt_tn<BM, BN>, opted)) return BRA_ERR_LAUNCH;
+    const long blocks = tile_blocks<BM, BN>(M, b.Nout);
+    if (tn_blocks + blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((k_gemm_bt_tn<BM, BN>), dim3((unsigned)(tn_blocks + blocks)), dim3(256), (std::max(kTnBytes, ring_bytes<BM, BN, 2>())), st,
+                       J0, J1, (int)blocks0, (int)blocks, share_tokens, b.In, b.W, b.ldw, (int)M, K, b.Nout, b.out);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
 bool sizes_ok(long M, int K, int Nout) { return M >= 1 && M <= 0x7fffffffL && K >= 64 && K % 64 == 0 && Nout >= 8 && Nout % 8 == 0; }
 
 }  // namespace
@@ -760,6 +790,26 @@ int gemm_tn(const GemmTn &J0, const GemmTn &J1, long M, int kernel_id, hipStream
     ProfScope ps(st, kernel_id);
     hipLaunchKernelGGL(k_gemm_tn, dim3((unsigned)(blocks(J0) + blocks(J1))), dim3(256), 0, st, J0, J1, (int)blocks(J0), M, tokens);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+// One launch where the product by itself leaves the chip under-filled, up to 256 tiles of 128 x 128.  Whole gradient with two
+// launches and one (us): 8 x 14 x 14 x 256, k = 16 (26 tiles) 47.7 / 43.1; 2 x 7 x 7 x 768 (6) 57.0 / 50.5; 16 x 7 x 7 x 512 (28)
+// 64 / 59; above, each fills the chip and the two get into each other's way: 64 x 14 x 14 x 384 (294) 181 / 184, 8 x 32 x 32 x 768
+// (384) 258 / 266.
+int gemm_bt_tn(const GemmTn &J0, const GemmTn &J1, const GemmHalf &b, long M, int K, int kernel_id, hipStream_t st)
+{
+    if (tile_blocks<128, 128>(M, b.Nout) > 256) {
+        const int rc = gemm_bt(b.In, b.W, b.ldw, M, K, b.Nout, (bf16_t *)b.out.buf[0], kernel_id, st);
+        return rc == BRA_OK ? gemm_tn(J0, J1, M, kernel_id, st) : rc;
+    }
+    if (!sizes_ok(M, K, b.Nout) || (J0.KA | J0.N | J1.KA | J1.N | J0.lda | J0.ldb | J1.lda | J1.ldb) % 8) return BRA_ERR_UNSUPPORTED;
+    const int tokens = tn_share_tokens(M, J0.KA, J0.N, J1.KA, J1.N), shares = gemm_tn_shares(M, J0.KA, J0.N, J1.KA, J1.N);
+    auto blocks = [&](const GemmTn &J) { return (long)((J.KA + 127) / 128) * ((J.N + 127) / 128) * shares; };
+    const long b0 = blocks(J0), tn = b0 + blocks(J1);
+    ProfScope ps(st, kernel_id);
+    // that few tiles are never the wide ones
+    if (pick_tile(M, K, b.Nout, 0, 0) == kNarrow) return launch_bt_tn<64, 64>(J0, J1, b0, tn, tokens, b, M, K, st);
+    return launch_bt_tn<64, 128>(J0, J1, b0, tn, tokens, b, M, K, st);
 }
 
 int gemm_regions(const GemmRegions &r, const bf16_t *W, int ldw, int K, int kernel_id, hipStream_t st)

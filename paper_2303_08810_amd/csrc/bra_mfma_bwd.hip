@@ -336,10 +336,9 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
             if (rc != BRA_OK) return rc;
         }
     } else {
-        rc = gemm_bt(w.dqkv, (const bf16_t *)Wqkv, 3 * C, M, 3 * C, C, (bf16_t *)dX, K_GEN_BACKWARD, st);
-        if (rc != BRA_OK) return rc;
-        rc = gemm_tn(GemmTn{(const bf16_t *)X, w.dqkv, w.part_qkv, C, 3 * C, C, 3 * C},
-                     GemmTn{w.o, (const bf16_t *)dY, w.part_o, C, C, C, C}, M, K_GEN_BACKWARD, st);
+        rc = gemm_bt_tn(GemmTn{(const bf16_t *)X, w.dqkv, w.part_qkv, C, 3 * C, C, 3 * C}, GemmTn{w.o, (const bf16_t *)dY, w.part_o, C, C, C, C},
+                        GemmHalf{w.dqkv, (const bf16_t *)Wqkv, 3 * C, C, GemmOut{{dX, nullptr, nullptr}, C, {nullptr, nullptr}, nullptr, nullptr, 0}},
+                        M, 3 * C, K_GEN_BACKWARD, st);
         if (rc != BRA_OK) return rc;
     }
     {

@@ -1,6 +1,7 @@
 """GPU parity of the gradients where several kinds of work share a launch: the pass with the tap gradients in front of the
 query side (more than 768 workgroups) and behind it (up to 768), for each layout of the attention; Q, K, V and dO from one
-launch with each tile of the product; both depth-wise passes together."""
+launch with each tile of the product; both depth-wise passes together; dX and the weight gradients in one launch (up to 256
+tiles of 128 x 128) and in two."""
 import pytest
 
 from synthetic_inputs import make_inputs
@@ -18,6 +19,10 @@ SHAPES = [  # (B, H, W, C, heads, S, k)
     (90, 7, 7, 320, 10, 7, 3),       # 64 x 128
     (3, 14, 14, 192, 6, 7, 4),       # 64 x 64
     (1, 5, 5, 64, 1, 5, 2),          # one tile, one chunk
+    (84, 14, 14, 192, 6, 7, 1),      # dX: 258 tiles of 128 x 128
+    (83, 14, 14, 192, 6, 7, 1),      # 256, as tiles of 64 x 64
+    (27, 14, 14, 704, 22, 7, 1),     # 252, as tiles of 64 x 128
+    (1, 7, 7, 192, 3, 7, 3),
 ]
 
 
