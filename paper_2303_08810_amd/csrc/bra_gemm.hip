@@ -407,12 +407,14 @@ enum Tile { kOneChunk, kWide, kMid, kNarrow };
 // 17.1; 12544 x 1152 x 384: 20.8 / 19.3 / 21.9; 12544 x 512 x 512: 12.4 / 14.0 / 12.7; 3136 x 768 x 768: 9.9 / 9.3 / 8.3;
 // 12544 x 256 x 768: 12.2 / 11.2 / 12.0; 1568 x 384 x 1152: 6.6 / 5.2 / 4.8.  A third buffer, 256 x 128 tiles with 8 wavefronts
 // and chunks of 32 gained nothing.
-// Nout1: columns of a second product over the same rows; others: workgroups of a region-level product in the launch.
+// Nout1: columns of a second product over the same rows.  others: workgroups of a region-level product in the launch, each as
+// long as a 64 x 128 tile (32 x 16 x 16 x 768, 768 of them: 64 x 128 tiles, a layer in 129.7 us, for 128 x 128, 133.6; 8 x 32 x 32 x 768,
+// 192 of them: 128 x 128, 107.2, for 64 x 128, 109.8).
 Tile pick_tile(long M, int K, int Nout, int Nout1, long others)
 {
     if (K == 64) return kOneChunk;
     auto cost = [&](int bm, int bn, long tile) {
-        const long rounds = ((M + bm - 1) / bm * ((Nout + bn - 1) / bn + (Nout1 + bn - 1) / bn) + others + 255) / 256;
+        const long rounds = ((M + bm - 1) / bm * ((Nout + bn - 1) / bn + (Nout1 + bn - 1) / bn) + others * 433 / tile + 255) / 256;
         return tile * rounds * (rounds == 1 ? 13 : 10);
     };
     const long wide = cost(128, 128, 744), mid = cost(64, 128, 433), narrow = cost(64, 64, 260);
