@@ -341,11 +341,15 @@ int route_c(const Dims &D, const float *X, const float *Wqkv, int32_t *Ir, float
 
 }  // namespace
 
+// As long as the workgroups (image, region) run at once, one per compute unit with 128 channels and about four with 64; more
+// take the general kernels.  Here / there (us, regions of 4 x 4 tokens, 49 per image): C = 128, k = 1: 4 images 32.3 / 31.9, 6:
+// 53.8 / 33.6, 32: 176 / 78; k = 4: 33.2 / 34.8, 55.5 / 36.7, 182 / 88; C = 64, k = 1: 1 image 14.2 / 25.0, 16: 33.0 / 34.1, 24:
+// 43.0 / 41.1, 32: 56.1 / 46.6.
 bool f32_small_ok(const Dims &D)
 {
     static const bool off = experiment_flag("BRA_NO_F32_SMALL");
     return !off && D.dtype == BRA_F32 && D.rh == 4 && D.rw == 4 && D.d == 32 && (D.C == 64 || D.C == 128) &&
-           D.R <= 64 && D.k * kN <= kKeys && (size_t)D.B * D.N * 3 * D.C < ((size_t)1 << 31);
+           D.R <= 64 && D.k * kN <= kKeys && (long)D.B * D.R <= (D.C == 64 ? 1024 : 256);
 }
 
 int f32_small_forward(const Dims &D, const float *X, const float *Wqkv, const float *Wo, const float *Wlce, float *Y,

@@ -38,3 +38,13 @@ def test_convolution_alone(dtype, B, H, W, C, heads, S, k):
     Ir = np.stack([rng.permutation(S * S)[:k] for _ in range(B * S * S)]).reshape(B, S * S, k).astype(np.int32)
     Y = bra.bra_forward(*(to_device(a, dtype) for a in (X, Wqkv, Wo, Wlce)), S, k, heads, Ir_in=torch.from_numpy(Ir).cuda(), path="generic")
     check_output(to_numpy(Y), run_oracle(X, Wqkv, Wo, Wlce, dict(S=S, k=k, heads=heads), Ir_in=Ir)["Y"], dtype)
+
+
+@pytest.mark.parametrize("B,C", [(4, 128), (5, 128), (16, 64), (17, 64)])
+def test_batches_around_the_small_kernels(B, C):
+    # 64 regions per image: the last batch that runs at once and the first that takes the general kernels
+    X, Wqkv, Wo, Wlce = make_inputs(B, 32, 32, C, seed=9570 + C, dtype="f32")
+    compare(X, Wqkv, Wo, Wlce, "f32", 8, 2, C // 32, "generic", images=[0, B - 1])
+    Xd, Wd, Wod, Wld = (to_device(a, "f32") for a in (X, Wqkv, Wo, Wlce))
+    Y, Ir = bra.bra_forward(Xd, Wd, Wod, Wld, 8, 2, C // 32, want_Ir=True, path="generic")
+    assert torch.equal(Ir, bra.bra_route(Xd, Wd, 8, 2, C // 32))
