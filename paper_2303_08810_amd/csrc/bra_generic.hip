@@ -146,13 +146,25 @@ constexpr int kAttnF32MaxD = 64;    // head width up to which attention runs on 
 
 bool launched() { return hipGetLastError() == hipSuccess; }
 
-// One or two products in one launch (J1: NULL for one).  64-column tiles where 128-column ones would leave
-// the chip under-filled or half empty, as for the bf16 product.
+// 64-column tiles with a float32 matrix, where the matrix cores are the bound and nothing may be left of a tile (50176 x 64 x
+// 192: 19.4 us, 23.7 with 128 columns; whole gradient of 3136 x 384: 199 and 205, of 6272 x 128 the same); with a bf16 one where
+// wider ones would leave the chip under-filled (else memory is the bound: 42336 x 96 x 288 takes 18.5 with narrow tiles, 17.1).
+// The other tile.
+template <typename TB>
+constexpr int kWideBN = std::is_same<TB, float>::value ? 64 : 128;
+
+template <typename TB>
+bool narrow_tiles(long M, int N, int N1 = 0)
+{
+    const long mt = (M + f32::kGemmBM - 1) / f32::kGemmBM;
+    return std::is_same<TB, float>::value || N <= 64 || mt * ((N + 127) / 128 + (N1 + 127) / 128) < 512;
+}
+
+// One or two products in one launch (J1: NULL for one).
 template <bool BT, bool VEC, typename TA, typename TB, typename TO>
 int launch_gemm_vec(const f32::GemmJob<TA, TB, TO> &J0, const f32::GemmJob<float, TB, float> *J1, hipStream_t st)
 {
-    const long mt0 = (J0.M + f32::kGemmBM - 1) / f32::kGemmBM;
-    const bool narrow = J0.N <= 64 || mt0 * ((J0.N + 127) / 128) < 512;
+    const bool narrow = narrow_tiles<TB>(J0.M, J0.N);
     const int bn = narrow ? 64 : 128;
     auto blocks = [&](long M, int N) { return (M + f32::kGemmBM - 1) / f32::kGemmBM * ((N + bn - 1) / bn); };
     const long b0 = blocks(J0.M, J0.N), b1 = J1 ? blocks(J1->M, J1->N) : 0;
@@ -162,7 +174,7 @@ int launch_gemm_vec(const f32::GemmJob<TA, TB, TO> &J0, const f32::GemmJob<float
     if (narrow)
         hipLaunchKernelGGL((f32::k_gemm<BT, VEC, 64, TA, TB, TO>), dim3((unsigned)(b0 + b1)), dim3(256), 0, st, J0, j1, (int)b0);
     else
-        hipLaunchKernelGGL((f32::k_gemm<BT, VEC, 128, TA, TB, TO>), dim3((unsigned)(b0 + b1)), dim3(256), 0, st, J0, j1, (int)b0);
+        hipLaunchKernelGGL((f32::k_gemm<BT, VEC, kWideBN<TB>, TA, TB, TO>), dim3((unsigned)(b0 + b1)), dim3(256), 0, st, J0, j1, (int)b0);
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -554,21 +566,20 @@ int launch_attn_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, const lce:
 // The gradients take five launches: the products of the recomputation, query side and key side (each with a depth-wise pass),
 // the products that end them, the sums of the partial matrices.  With a launch for each of the eight kernels (us): 8 x 28 x 28
 // x 128 float32, k = 4: 117 -> 91; 1 x 14 x 14 x 64: 53 -> 31; 2 x 14 x 14 x 256, k = 16: 98 -> 68; 29 x 28 x 28 x 96 bf16: 204 -> 176.
-// 64-column tiles where the wider ones leave the chip under-filled, as in launch_gemm_vec.
 template <typename T>
 int launch_gemm_both(const f32::GemmJob<T, T, float> &J0, const f32::GemmJob<T, T, float> &J1, hipStream_t st)
 {
     const long mt = (J0.M + f32::kGemmBM - 1) / f32::kGemmBM;
-    const bool narrow = J1.N <= 64 || mt * ((J0.N + 127) / 128 + (J1.N + 127) / 128) < 512;
+    const bool narrow = J1.N <= 64 || narrow_tiles<T>(J0.M, J0.N, J1.N);
     const int bn = narrow ? 64 : 128;
     const long b0 = mt * ((J0.N + bn - 1) / bn), b1 = mt * ((J1.N + bn - 1) / bn);
     if (b0 + b1 > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)(b0 + b1));
     const bool vec = J1.K % 4 == 0;              // all sizes and pitches are multiples of C
     if (vec && narrow) hipLaunchKernelGGL((f32::k_gemm_both<true, 64, T>), grid, dim3(256), 0, st, J0, J1, (int)b0);
-    else if (vec) hipLaunchKernelGGL((f32::k_gemm_both<true, 128, T>), grid, dim3(256), 0, st, J0, J1, (int)b0);
+    else if (vec) hipLaunchKernelGGL((f32::k_gemm_both<true, kWideBN<T>, T>), grid, dim3(256), 0, st, J0, J1, (int)b0);
     else if (narrow) hipLaunchKernelGGL((f32::k_gemm_both<false, 64, T>), grid, dim3(256), 0, st, J0, J1, (int)b0);
-    else hipLaunchKernelGGL((f32::k_gemm_both<false, 128, T>), grid, dim3(256), 0, st, J0, J1, (int)b0);
+    else hipLaunchKernelGGL((f32::k_gemm_both<false, kWideBN<T>, T>), grid, dim3(256), 0, st, J0, J1, (int)b0);
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -576,16 +587,16 @@ template <typename T>
 int launch_gemm_end(const f32::TnJob<T, float> &J0, const f32::TnJob<float, T> &J1, int share_tokens, const f32::GemmJob<float, T, T> &J, hipStream_t st)
 {
     const long mt = (J.M + f32::kGemmBM - 1) / f32::kGemmBM;
-    const bool narrow = J.N <= 64 || mt * ((J.N + 127) / 128) < 512;
+    const bool narrow = narrow_tiles<T>(J.M, J.N);
     const int bn = narrow ? 64 : 128;
     const long blocks = mt * ((J.N + bn - 1) / bn) + J0.blocks + J1.blocks;
     if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)blocks);
     const bool vec = J.N % 4 == 0;               // all sizes and pitches are multiples of C
     if (vec && narrow) hipLaunchKernelGGL((f32::k_gemm_end<true, 64, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
-    else if (vec) hipLaunchKernelGGL((f32::k_gemm_end<true, 128, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
+    else if (vec) hipLaunchKernelGGL((f32::k_gemm_end<true, kWideBN<T>, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
     else if (narrow) hipLaunchKernelGGL((f32::k_gemm_end<false, 64, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
-    else hipLaunchKernelGGL((f32::k_gemm_end<false, 128, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
+    else hipLaunchKernelGGL((f32::k_gemm_end<false, kWideBN<T>, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
