@@ -115,10 +115,6 @@ int f32_small_route(const Dims &D, const float *X, const float *Wqkv, int32_t *I
 // 1024 regions).
 int route_rows(const Dims &D, const float *Qr, const float *Kr, int ld, int32_t *Ir, float *Ar_opt, hipStream_t st);
 
-size_t valu_route_scratch_bytes(const Dims &D);
-int valu_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt,
-               void *scratch, hipStream_t st);
-
 bool mfma_supported(const Dims &D);
 size_t mfma_workspace_bytes(const Dims &D);
 int mfma_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *ws,

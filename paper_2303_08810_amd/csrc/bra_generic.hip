@@ -703,26 +703,3 @@ int generic_forward(const Dims &D, const void *X, const void *Wqkv, const void *
 }
 
 }  // namespace bra
-
-namespace bra {
-
-// Routing with caller-provided scratch (xr, qr, kr: [B, R, C] float32 each), used by
-// the matrix-core family for shapes its own routing kernels do not cover.
-size_t valu_route_scratch_bytes(const Dims &D)
-{
-    return 3 * align256((size_t)D.B * D.R * D.C * sizeof(float));
-}
-
-int valu_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt,
-               void *scratch, hipStream_t st)
-{
-    GenericWs w;
-    const size_t each = align256((size_t)D.B * D.R * D.C * sizeof(float));
-    w.xr = (float *)scratch;
-    w.qk = (float *)((char *)scratch + each);
-    if (D.dtype == BRA_F32)
-        return launch_route<float>(D, (const float *)X, (const float *)Wqkv, Ir, Ar_opt, w, st);
-    return launch_route<bf16_t>(D, (const bf16_t *)X, (const bf16_t *)Wqkv, Ir, Ar_opt, w, st);
-}
-
-}  // namespace bra

@@ -125,17 +125,6 @@ struct PrepArgs {
     Dims dims = {};
 };
 
-// `total` = prep_total(C) (all weights) or 3 C^2 (projection weights only; Wo and Wlce
-// may be NULL).
-__global__ void k_prep_weights(const bf16_t *__restrict__ Wqkv, const bf16_t *__restrict__ Wo,
-                               const bf16_t *__restrict__ Wlce, bf16_t *__restrict__ WT,
-                               bf16_t *__restrict__ WoT, bf16_t *__restrict__ Wa,
-                               bf16_t *__restrict__ Wf, int C, int total)
-{
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < total) prep_weight_element(Wqkv, Wo, Wlce, WT, WoT, Wa, Wf, C, e);
-}
-
 // ---------------------------------------------------------------------------
 // Region pooling (Sec. 3.2, "Region-to-region routing"): Xr[b, r, :] = mean of the
 // tokens of region r, in float32 with a fixed summation order.  Workgroup (b, group)
@@ -1519,12 +1508,9 @@ void k_fused(AttnArgs A, Dims D)
 struct MfmaWs {
     bf16_t *q, *k, *v, *o, *wt, *wot, *wa, *wf;
     float *xr, *u, *p;
-    void *route;
     int32_t *ir;
     size_t bytes;
 };
-
-bool fast_route_ok(const Dims &D) { return D.S <= kFastRouteMaxS; }
 
 int halo_rows(const Dims &D)
 {
@@ -1536,7 +1522,7 @@ int halo_rows(const Dims &D)
 bool fused_ok(const Dims &D)
 {
     static const bool disabled = experiment_flag("BRA_DISABLE_FUSED");
-    if (disabled || !fast_route_ok(D)) return false;
+    if (disabled) return false;
     if (D.C != 64) return false;
     return D.n == 64 && D.k == 1 && (D.rw == 8 || D.rw == 16);
 }
@@ -1579,7 +1565,7 @@ TileMap tile_map(const Dims &D, bool pooled)
 
 bool pooled_projection(const Dims &D)
 {
-    return fast_route_ok(D) && (region_tiles_ok(D) || D.rh * (D.rw >> pool_group_log2(D)) <= 8);
+    return region_tiles_ok(D) || D.rh * (D.rw >> pool_group_log2(D)) <= 8;
 }
 
 MfmaWs carve(const Dims &D, void *ws)
@@ -1600,7 +1586,6 @@ MfmaWs carve(const Dims &D, void *ws)
     w.xr = (float *)take((size_t)D.B * D.R * D.C * sizeof(float));
     w.u = (float *)take(D.C == 64 && fused_ok(D) ? (size_t)D.B * D.R * D.C * sizeof(float) : 0);
     w.p = (float *)take(pooled_projection(D) ? (size_t)D.B * D.H * (D.W >> pool_group_log2(D)) * 2 * D.C * sizeof(float) : 0);
-    w.route = take(fast_route_ok(D) ? 0 : valu_route_scratch_bytes(D));
     w.ir = (int32_t *)take((size_t)D.B * D.R * D.k * sizeof(int32_t));
     w.bytes = off;
     return w;
@@ -1756,36 +1741,24 @@ int forward_c(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const bf16_t *
     const bool fused = C == 64 && fused_ok(D);
     bool prep_pending = false;      // the weights still have to be rearranged, next to the projection
     bool route_with_qkv = false;    // the routing from pooled X rides in the projection kernel's launch
-    if (!fast_route_ok(D)) {
-        if (!Ir_in_opt) {
-            int rc = valu_route(D, X, Wqkv, Ir_dst, nullptr, w.route, st);
-            if (rc != BRA_OK) return rc;
+    // pool X and route before the rest, with the weight rearrangement in the same launch;
+    // the pooled-projection pipelines need neither and rearrange next to the projection
+    static const bool route_launch = experiment_flag("BRA_FUSED_ROUTE_LAUNCH");
+    const bool inline_route = fused && !route_launch;     // the k = 1 kernel routes by itself, from the routing vectors
+    {
+        const bool from_x = (fused || !pooled_projection(D)) && !Ir_in_opt;
+        if (fused || from_x)
+            launch_pool<C>(D, X, Wqkv, Wo, Wlce, w, /*pool=*/from_x, prep_total(C), st, /*with_u=*/inline_route);
+        if (from_x && !inline_route) {
+            // next to the projection (which does not depend on it) where there is one
+            route_with_qkv = !fused && !experiment_flag("BRA_ROUTE_LAUNCH");
+            if (!route_with_qkv) {
+                const int rc = launch_route<C>(D, w, Ir_dst, nullptr, st);
+                if (rc != BRA_OK) return rc;
+            }
             Ir_src = Ir_dst;
         }
-        ProfScope ps(st, K_MFMA_PREP);
-        const int total = prep_total(C);
-        hipLaunchKernelGGL(k_prep_weights, dim3((total + 255) / 256), dim3(256), 0, st, Wqkv, Wo, Wlce,
-                           w.wt, w.wot, w.wa, w.wf, C, total);
-    } else {
-        // pool X and route before the rest, with the weight rearrangement in the same launch;
-        // the pooled-projection pipelines need neither and rearrange next to the projection
-        static const bool route_launch = experiment_flag("BRA_FUSED_ROUTE_LAUNCH");
-        const bool inline_route = fused && !route_launch;     // the k = 1 kernel routes by itself, from the routing vectors
-        {
-            const bool from_x = (fused || !pooled_projection(D)) && !Ir_in_opt;
-            if (fused || from_x)
-                launch_pool<C>(D, X, Wqkv, Wo, Wlce, w, /*pool=*/from_x, prep_total(C), st, /*with_u=*/inline_route);
-            if (from_x && !inline_route) {
-                // next to the projection (which does not depend on it) where there is one
-                route_with_qkv = !fused && !experiment_flag("BRA_ROUTE_LAUNCH");
-                if (!route_with_qkv) {
-                    const int rc = launch_route<C>(D, w, Ir_dst, nullptr, st);
-                    if (rc != BRA_OK) return rc;
-                }
-                Ir_src = Ir_dst;
-            }
-            prep_pending = !(fused || from_x);
-        }
+        prep_pending = !(fused || from_x);
     }
     // the many-block attention kernel takes Q in units of log2 of the softmax weights
     const bool q32 = !fused && attn_big_ok(D) && attn_q32_ok(D) && !experiment_flag("BRA_ATTN_OLD");
@@ -1905,13 +1878,15 @@ static bool specialised(const Dims &D)
     if (D.dtype != BRA_BF16 || D.d != 32) return false;
     if (D.C != 64 && D.C != 128 && D.C != 256) return false;
     if ((long)D.B * D.R * (D.n / 64 + 1) + 8 > 0x7fffffffL) return false;
-    // Regions of fewer than 16 tokens, where both pipelines use the same attention: the general one's smaller launches win
-    // for one token per region (4 x 7 x 7 x 64: 20.5 against 16.3 us), for more than 64 regions, whose routing is not part
-    // of the projection's launch (4 x 32 x 32 x 64, S = 16: 39 against 29), for C = 64, and for C = 128 up to 8192 tokens
-    // (16 x 16 x 32, k = 12: 42.8 against 38.4; 48 x 16 x 32: 65 against 72).
-    if (D.n < 16 && (D.n == 1 || !fast_route_ok(D) || D.C == 64 || (D.C == 128 && (long)D.B * D.N <= 8192)) && wide_supported(D))
-        return false;
-    if (!fast_route_ok(D) && !generic_supported(D)) return false;   // fallback routing kernels
+    // More than 64 regions: their routing is not among these kernels, and the general pipeline, which carries the convolution
+    // beside it, is faster throughout (S = 16, us, here with launches for the routing / there: 4 x 64 x 64 x 64, k = 4: 33 / 28;
+    // 16 x 64 x 64 x 64, k = 1: 55 / 46; 10 x 64 x 64 x 128, k = 13: 84 / 72; 128 x 128 x 128, k = 4: 52 / 38; 4 of them 103 / 85).
+    if (D.S > kFastRouteMaxS) return false;
+    // Regions of fewer than 16 tokens: the image-resident attention needs a (image, head) pair per compute unit, and the
+    // projection with the pooling in it many tokens.  Here / there (us): 14 x 14 x 256, k = 16: B = 24 43.5 / 38.2, 64 49.6 /
+    // 69.2; 14 x 28 x 256, k = 1: 6 41.3 / 27.1, 24 58.8 / 41.4, 64 78.5 / 77.7; 14 x 14 x 128, k = 16: 24 35.5 / 27.2, 64 38.1 / 41.0;
+    // 14 x 28 x 128, k = 1, whose 8 tokens need twice the passes: 24 50.5 / 27.6, 64 50.7 / 44.9; 14 x 14 x 64: 64 29.1 / 26.2.
+    if (D.n < 16 && (D.n == 1 || D.C == 64 || D.B * (D.C / 32) < 256 || (D.C == 128 && (D.n > 4 || (long)D.B * D.N <= 8192)))) return false;
     return attn_big_ok(D) || small_supported(D);
 }
 
@@ -1936,7 +1911,6 @@ int mfma_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, floa
 {
     if (wide_shape(D)) return wide_route(D, X, Wqkv, Ir, Ar_opt, ws, st);
     MfmaWs w = carve(D, ws);
-    if (!fast_route_ok(D)) return valu_route(D, X, Wqkv, Ir, Ar_opt, w.route, st);
     const bf16_t *x = (const bf16_t *)X, *wq = (const bf16_t *)Wqkv;
     switch (D.C) {
     case 64: return route_c<64>(D, x, wq, Ir, Ar_opt, w, st);

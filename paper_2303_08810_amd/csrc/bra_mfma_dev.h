@@ -678,7 +678,7 @@ bool small_needs_projection(const Dims &D);   // launch_small left O = attention
 int launch_small(const Dims &D, const mfma::AttnArgs &A, bf16_t *O, hipStream_t st);
 // Attention of regions of 1, 2, 4 or 8 tokens + LCE into O for any C that is a multiple of 64
 // (image-resident attention; A.Q/K/V, Ir_src, Ir_out, Wlce, c_exp set).
-bool map_tail_supported(const Dims &D);
+bool map_tail_pays(const Dims &D);
 int launch_map_tail(const Dims &D, const mfma::AttnArgs &A, bf16_t *O, hipStream_t st);
 // Attention + LCE + W^o for regions of 64 n tokens with 32 queries per wavefront
 // (bra_mfma_attn.hip); A.Q must hold Q multiplied by scale * log2(e).

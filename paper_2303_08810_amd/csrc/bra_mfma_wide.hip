@@ -564,13 +564,13 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     if (pooled) launch_pool(D, (const bf16_t *)X, w, pad, st);
     const GemmRegions rj = region_job(D, w);
     const float c_exp = D.scale * 1.4426950408889634f;
-    const float q_scale = map_tail_supported(D) ? 1.0f : c_exp;     // k_attn_rows, k_attn_gen take scores in units of log2
+    const float q_scale = map_tail_pays(D) ? 1.0f : c_exp;     // k_attn_rows, k_attn_gen take scores in units of log2
     float *fq = route && !pooled ? w.qr : nullptr, *fk = route && !pooled ? w.kr : nullptr;
     int rc = gemm((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, GemmOut{{w.q, w.k, w.v}, D.C, {fq, fk}, nullptr, nullptr, 0, q_scale, pad, GemmRows{}},
                   pooled ? &rj : nullptr, K_MFMA_QKV, st);
     if (rc != BRA_OK) return rc;
     AttnArgs A = {};
-    const bool map_tail = map_tail_supported(D);      // forms the LCE itself
+    const bool map_tail = map_tail_pays(D);      // forms the LCE itself
     if (!map_tail) {
         // LCE(V) into the output map, to which the attention adds itself: what the convolution needs is there as soon as the
         // routing's input is, and the routing leaves most of the chip idle
