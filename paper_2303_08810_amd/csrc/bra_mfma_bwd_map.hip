@@ -348,8 +348,10 @@ int launch(const Dims &D, const bf16_t *Q, const bf16_t *K, const bf16_t *V, con
 bool attn_bwd_map_ok(const Dims &D)
 {
     // regions of up to 8 tokens: larger ones fill the per-region kernels' tiles and gather each row fewer times
-    // and fewer workgroups than half the compute units leave the chip idle (5 images of 14 x 14 x 64: 63 us, region by region 45)
-    return D.d == 32 && (long)D.B * D.heads >= 128 && D.n <= 8 && D.k > 1 && (long)D.B * D.heads < 0x7ffffff0L && map_smem(D.N, D.R, D.k, 16).bytes <= (size_t)kMaxLds;
+    // and few workgroups leave the chip idle: by images / by regions, whole gradient (us), 128 of them: 64 x 7 x 7 x 64, k = 16
+    // 42.0 / 37.1; 64 x 14 x 14 x 64, k = 44 88 / 78; 64 x 14 x 28 x 64, k = 16 80 / 73; 192: 24 x 14 x 14 x 256, k = 16 71.6 /
+    // 76.9; 8 x 7 x 7 x 768, k = 44 70.8 / 81.2
+    return D.d == 32 && (long)D.B * D.heads >= 160 && D.n <= 8 && D.k > 1 && (long)D.B * D.heads < 0x7ffffff0L && map_smem(D.N, D.R, D.k, 16).bytes <= (size_t)kMaxLds;
 }
 
 int launch_attn_bwd_map(const Dims &D, const bf16_t *Q, const bf16_t *K, const bf16_t *V, const bf16_t *dO, const int32_t *Ir,

@@ -1,7 +1,7 @@
 """GPU parity of the gradients where several kinds of work share a launch: the pass with the tap gradients in front of the
 query side (more than 768 workgroups) and behind it (up to 768), for each layout of the attention; Q, K, V and dO from one
 launch with each tile of the product; both depth-wise passes together; dX and the weight gradients in one launch (up to 256
-tiles of 128 x 128) and in two."""
+tiles of 128 x 128) and in two; attention by regions and by whole images."""
 import pytest
 
 from synthetic_inputs import make_inputs
@@ -23,6 +23,8 @@ SHAPES = [  # (B, H, W, C, heads, S, k)
     (83, 14, 14, 192, 6, 7, 1),      # 256, as tiles of 64 x 64
     (27, 14, 14, 704, 22, 7, 1),     # 252, as tiles of 64 x 128
     (1, 7, 7, 192, 3, 7, 3),
+    (79, 7, 7, 64, 2, 7, 5),         # 158 (image, head) pairs: region by region
+    (80, 7, 7, 64, 2, 7, 5),         # 160: by whole images
 ]
 
 
