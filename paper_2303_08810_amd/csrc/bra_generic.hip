@@ -542,8 +542,20 @@ int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lc
     const lce::GradJob<float> grad = {w.dO, V, taps, w.dqkv + 2 * D.C, w.part_lce, 3 * D.C, 3 * D.C, lce_grad_plan(D)};
     const lce::AddJob<float> add = lce::add_job<float>(D, V, 3 * D.C, taps, w.o, D.C, VEC ? 2 : 1, 256);
     if (blocks + std::max(grad.p.blocks(), add.blocks) > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((f32::k_attn_bwd_q<DP, HPW, VEC>), dim3((unsigned)(blocks + grad.p.blocks())), dim3(256), 0, st, w.qkv, w.dO, Ir, w.o,
-                       w.dqkv, w.lse, w.dsum, D, hgroups, tiles, grad, grad.p.blocks());
+    auto query_side = [&](auto kb) {
+        hipLaunchKernelGGL((f32::k_attn_bwd_q<DP, HPW, VEC, decltype(kb)::value>), dim3((unsigned)(blocks + grad.p.blocks())), dim3(256), 0, st,
+                           w.qkv, w.dO, Ir, w.o, w.dqkv, w.lse, w.dsum, D, hgroups, tiles, grad, grad.p.blocks());
+    };
+    constexpr int KB = f32::AttnShape<DP, HPW>::KB;
+    // 33 to 64 routed keys as a single block of 64, so that they are not taken twice (8 x 28 x 28 x 128, k = 4: 91.5 -> 88.1 us; 29 x
+    // 28 x 28 x 96 bf16, k = 3: 164.8 -> 152.9; 16 x 14 x 14 x 256, k = 16: 165.5 -> 150.3); more keys in two sweeps of such blocks
+    // were slower (16 x 14 x 14 x 256, k = 20: 190 -> 208), and so were heads of 64 channels (8 x 16 x 16 x 192: 82.1 -> 84.2).
+    if constexpr (DP == 32 && KB == 32) {
+        if (D.kn > 32 && D.kn <= 64) query_side(std::integral_constant<int, 64>{});
+        else query_side(std::integral_constant<int, 32>{});
+    } else {
+        query_side(std::integral_constant<int, KB>{});
+    }
     hipLaunchKernelGGL((f32::k_attn_bwd_kv<DP, HPW, VEC>), dim3((unsigned)(blocks + add.blocks)), dim3(256), 0, st, w.qkv, w.dO, Ir, w.lse,
                        w.dsum, w.dqkv, D, hgroups, tiles, add, add.blocks);
     if (!launched()) return BRA_ERR_LAUNCH;

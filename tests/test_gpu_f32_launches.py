@@ -48,3 +48,13 @@ def test_batches_around_the_small_kernels(B, C):
     Xd, Wd, Wod, Wld = (to_device(a, "f32") for a in (X, Wqkv, Wo, Wlce))
     Y, Ir = bra.bra_forward(Xd, Wd, Wod, Wld, 8, 2, C // 32, want_Ir=True, path="generic")
     assert torch.equal(Ir, bra.bra_route(Xd, Wd, 8, 2, C // 32))
+
+
+@pytest.mark.parametrize("dtype,B,H,W,C,heads,S,k", [
+    ("f32", 1, 7, 7, 128, 4, 7, 32), ("f32", 1, 7, 7, 128, 4, 7, 33), ("f32", 2, 12, 12, 96, 3, 3, 4),
+    ("bf16", 2, 12, 12, 96, 3, 3, 5), ("f32", 1, 9, 21, 80, 4, 3, 3),
+])
+def test_gradients_around_one_block_of_keys(dtype, B, H, W, C, heads, S, k):
+    # 32, 33, 64, 80 and 63 routed keys
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=9580 + H * W + k, dtype=dtype)
+    compare_backward(X, Wqkv, Wo, Wlce, dtype, heads, S, k, path="generic")
