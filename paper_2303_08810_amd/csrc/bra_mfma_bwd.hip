@@ -2,7 +2,7 @@
 // multiple of 64 up to 4096, at most 4096 routing entries per image), with the routing index held fixed.
 //
 // Chain rule through Eq. 6-7 and Eq. 1-2, with O = Attention(Q, K^g, V^g) + LCE(V), Y = O Wo:
-//     dO = dY Wo^T                     general product, Wo taken transposed as it lies
+//     dO = dY Wo^T                     beside Q, K, V, Wo taken transposed as it lies
 //     P  = softmax(scale Q K^T)        recomputed per (region, head) from the re-projected Q, K
 //     dP = dO V^T,  dS = scale P o (dP - D),  D = rowsum(P o dP)
 //     dQ = dS K                        query side: it also leaves the row statistics (log-sum-exp and D) and the
@@ -10,11 +10,11 @@
 //     dK = dS^T Q,  dV = P^T dO        key side: from the query regions routed to a KEY region, found in Ir, with P and
 //                                      dS recomputed from the statistics and sums in registers: no atomic adds
 //                                      (k_attn_bwd_map on small maps, else k_attn_bwd_q and k_attn_bwd_kv)
-//     O += LCE(V)                      k_lce_pairs
+//     O += LCE(V)                      in the key side's launch, or k_lce_backward
 //     dV += LCE^T(dO) (the correlation with the taps reversed) and
-//     dWlce[c][ky][kx] = sum_t dO[t][c] V[t + (ky - 2, kx - 2)][c]       k_lce_pairs
-//     dX = [dQ | dK | dV] Wqkv^T,  dWqkv = X^T [dQ | dK | dV]      k_bwd_proj, one pass over the gradient map
-//     dWo = O^T dY                     k_gemm_tn (contraction over tokens)
+//     dWlce[c][ky][kx] = sum_t dO[t][c] V[t + (ky - 2, kx - 2)][c]       in the query side's launch, or k_lce_backward
+//     dX = [dQ | dK | dV] Wqkv^T,  dWqkv = X^T [dQ | dK | dV]      k_bwd_proj, one pass over the gradient map, or k_gemm_bt_tn
+//     dWo = O^T dY                     k_bwd_proj or k_gemm_tn (contraction over tokens)
 // All products take bf16 operands and accumulate in float32; dQ, dK, dV and dO are rounded to
 // bf16 between the kernels (they are matrix-core operands of the next product).  The weight
 // gradients are summed from per-workgroup partial sums in a fixed order (k_reduce_parts).

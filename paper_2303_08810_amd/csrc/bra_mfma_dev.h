@@ -660,7 +660,6 @@ struct AttnArgs {
     float c_exp;                    // softmax scale * log2(e)
     int total;                      // workgroups that have work
     int trace = 0;                  // experiment builds: leave phase timestamps in Y
-    bool adds = false;              // general pipeline: the output map holds LCE(V), to which the attention is added
 };
 
 // Workgroup -> work item.  Consecutive block ids are dealt round-robin to the 8 XCDs;

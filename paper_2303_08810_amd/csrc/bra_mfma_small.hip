@@ -11,7 +11,7 @@
 // applies W^o (Eq. 2), so the attention output never travels through memory (k_small).
 // Smaller regions use separate kernels: on small maps the image-resident attention
 // k_attn_map / k_attn_map4 (a head's Q, K, V of a whole image in LDS, the LCE added from the
-// same V slice), else k_attn_small (attention output to memory) and k_lce_pairs (bra_lce.hip: adds
+// same V slice), else k_attn_small (attention output to memory) and k_lce_add (bra_lce.hip: adds
 // the LCE in place); then the projection kernel with W^o.
 #include "bra_lce_dev.h"
 

@@ -8,9 +8,9 @@
 //   k_gemm_dma    Q | K | V = X Wqkv (Eq. 3), bf16 out; in the same launch Q^r | K^r = Xr [Wq | Wk] in float32: the
 //                 means are split exactly into three bf16 terms, so the products are those of the float32 computation
 //                 (one token per region: no means, the token projection leaves float32 copies of Q and K instead)
-//   k_route_rows  rows of A^r = Q^r (K^r)^T (Eq. 4) and their top-k (Eq. 5)
-//   image-resident attention (small maps, regions of up to 8 tokens; bra_mfma_small.hip), k_attn_rows (regions of up to
-//   32 tokens) or k_attn_gen, then k_lce_pairs adds the LCE in place            (Eq. 6, 7)
+//   k_route_lce   rows of A^r = Q^r (K^r)^T (Eq. 4) and their top-k (Eq. 5), and O = LCE(V) (Eq. 7) beside them
+//   k_attn_rows (regions of up to 32 tokens) or k_attn_gen, added to O          (Eq. 6)
+//   or k_route_rows and the image-resident attention with its own LCE (map_tail_pays; bra_mfma_small.hip)
 //   k_gemm_dma    Y = O Wo (Eq. 2)
 #include "bra_attn_dev.h"
 #include "bra_gemm.h"
@@ -98,7 +98,7 @@ struct Added {
 // its addition to the denominator and half a conversion; with maxima instead of additions and denominators from a product
 // it took 68 us.  One query tile per wavefront instead of two: 74 us (4 x 64 x 64 x 384, heads of 64, k = 4: 45 for 39).
 template <int HD, int NQ>
-__global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, int walks)
+__global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, int walks, bool adds)
 {
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16;
     __shared__ __attribute__((aligned(16))) bf16_t K0[64 * 64];
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
                 qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + HD * hh + 32 * ks + 8 * g);
     }
     Added<NQ> added;
-    if (NQ == 1 && A.adds) added.load(O + img, qtok, C, g);
+    if (NQ == 1 && adds) added.load(O + img, qtok, C, g);
     const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
     const bool report = A.Ir_out && A.Ir_out != A.Ir_src && qt == 0 && cg == 0;
     for (int p = tid; p < D.k; p += 256) {
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
         if (k0 + 128 < kn) request(k0 + 128, kv[1][0], kv[1][1]);
         if (!idle) block(k0 + 64, K0, V0, std::false_type{});
     }
-    if (NQ > 1 && A.adds) added.load(O + img, qtok, C, g);      // 16 registers that the sweep does not have
+    if (NQ > 1 && adds) added.load(O + img, qtok, C, g);      // 16 registers that the sweep does not have
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const bool store = 64 * NQ * qt + 16 * (NQ * wave + q) + i < n;
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) {
                 f32x4 v = acc[q][hh][dt] * inv;
-                if (A.adds) v = added.to(v, q, NDT * hh + dt);
+                if (adds) v = added.to(v, q, NDT * hh + dt);
                 *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(v);
             }
         }
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
 constexpr int kRowsBuffer = 4 * 2 * 32 * 64 * 2;       // bytes
 
 template <int HD, int NQ>
-__global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int items)
+__global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int items, bool adds)
 {
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16, KB = 32;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__rest
                 qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + HD * hh + 32 * ks + 8 * g);
     }
     Added<NQ> added;
-    if (A.adds) added.load(O + img, qtok, C, g);
+    if (adds) added.load(O + img, qtok, C, g);
     const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
     const bool report = A.Ir_out && A.Ir_out != A.Ir_src && cg == 0;
     for (int p = lane; p < D.k; p += kWave) {
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__rest
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) {
                 f32x4 v = acc[q][hh][dt] * inv;
-                if (A.adds) v = added.to(v, q, NDT * hh + dt);
+                if (adds) v = added.to(v, q, NDT * hh + dt);
                 *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(v);
             }
         }
@@ -468,7 +468,7 @@ GemmRegions region_job(const Dims &D, const WideWs &w)
 }
 
 template <int HD, int NQ>
-int launch_attn_rows_t(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
+int launch_attn_rows_t(const Dims &D, const AttnArgs &A, bf16_t *O, bool adds, hipStream_t st)
 {
     const int items = D.B * D.R * (D.C / 64), blocks = (items + 3) / 4;
     const size_t smem = (size_t)(D.kn > 32 ? 2 : 1) * kRowsBuffer + (size_t)4 * (D.k + 32) * sizeof(int);
@@ -477,34 +477,35 @@ int launch_attn_rows_t(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t 
         if (hipFuncSetAttribute((const void *)k_attn_rows<HD, NQ>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess) return BRA_ERR_LAUNCH;
         opted = true;
     }
-    hipLaunchKernelGGL((k_attn_rows<HD, NQ>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), smem, st, A, O, D, items);
+    hipLaunchKernelGGL((k_attn_rows<HD, NQ>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), smem, st, A, O, D, items, adds);
     return BRA_OK;
 }
 
-int launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
+int launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, bool adds, hipStream_t st)
 {
-    if (D.d == 32) return D.n <= 16 ? launch_attn_rows_t<32, 1>(D, A, O, st) : launch_attn_rows_t<32, 2>(D, A, O, st);
-    return D.n <= 16 ? launch_attn_rows_t<64, 1>(D, A, O, st) : launch_attn_rows_t<64, 2>(D, A, O, st);
+    if (D.d == 32) return D.n <= 16 ? launch_attn_rows_t<32, 1>(D, A, O, adds, st) : launch_attn_rows_t<32, 2>(D, A, O, adds, st);
+    return D.n <= 16 ? launch_attn_rows_t<64, 1>(D, A, O, adds, st) : launch_attn_rows_t<64, 2>(D, A, O, adds, st);
 }
 
 template <int NQ>
-void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
+void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, bool adds, hipStream_t st)
 {
     const int qtiles = (D.n + 64 * NQ - 1) / (64 * NQ);
     const dim3 grid((unsigned)((long)D.B * D.R * qtiles * (D.C / 64)));
     const int walks = walk_ok(D);
     const size_t smem = (size_t)(D.k + (walks ? D.n : 0)) * sizeof(int);
-    if (D.d == 32) hipLaunchKernelGGL((k_attn_gen<32, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks);
-    else hipLaunchKernelGGL((k_attn_gen<64, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks);
+    if (D.d == 32) hipLaunchKernelGGL((k_attn_gen<32, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks, adds);
+    else hipLaunchKernelGGL((k_attn_gen<64, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks, adds);
 }
 
-void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
+// adds: to what O holds (LCE(V)).
+void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, bool adds, hipStream_t st)
 {
     // two query tiles per wavefront (every K and V operand read serves both; measured above) where the wider tile leaves no
     // more than an eighth of its queries empty beyond the narrow one and there are workgroups enough
     const int t64 = (D.n + 63) / 64, t128 = (D.n + 127) / 128;
-    if (t128 * 128 * 8 <= t64 * 64 * 9 && (long)D.B * D.R * t128 * (D.C / 64) >= 512) launch_attn_gen_t<2>(D, A, O, st);
-    else launch_attn_gen_t<1>(D, A, O, st);
+    if (t128 * 128 * 8 <= t64 * 64 * 9 && (long)D.B * D.R * t128 * (D.C / 64) >= 512) launch_attn_gen_t<2>(D, A, O, adds, st);
+    else launch_attn_gen_t<1>(D, A, O, adds, st);
 }
 
 // Pooling, region-level projections, A^r rows and top-k on their own.
@@ -570,15 +571,16 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
                   pooled ? &rj : nullptr, K_MFMA_QKV, st);
     if (rc != BRA_OK) return rc;
     AttnArgs A = {};
+    bool adds = false;
     const bool map_tail = map_tail_pays(D);      // forms the LCE itself
     if (!map_tail) {
         // LCE(V) into the output map, to which the attention adds itself: what the convolution needs is there as soon as the
         // routing's input is, and the routing leaves most of the chip idle
         rc = lce::route_rows_lce_bf16(D, route ? w.qr : nullptr, w.kr, Ir_dst, w.v, (const bf16_t *)Wlce, w.o, st);
         if (rc != BRA_OK && rc != BRA_ERR_UNSUPPORTED) return rc;
-        A.adds = rc == BRA_OK;
+        adds = rc == BRA_OK;
     }
-    if (route && !A.adds) {
+    if (route && !adds) {
         rc = route_rows(D, w.qr, w.kr, D.C, Ir_dst, nullptr, st);
         if (rc != BRA_OK) return rc;
     }
@@ -591,11 +593,11 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     } else {
         {
             ProfScope ps(st, K_MFMA_ATTENTION);
-            if (D.n <= 32 && D.k <= 1024) rc = launch_attn_rows(D, A, w.o, st);      // its tables fit in LDS
-            else launch_attn_gen(D, A, w.o, st);
+            if (D.n <= 32 && D.k <= 1024) rc = launch_attn_rows(D, A, w.o, adds, st);      // its tables fit in LDS
+            else launch_attn_gen(D, A, w.o, adds, st);
         }
         if (rc != BRA_OK) return rc;
-        rc = A.adds ? BRA_OK : lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);
+        rc = adds ? BRA_OK : lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);
     }
     if (rc != BRA_OK) return rc;
     return gemm(w.o, (const bf16_t *)Wo, D.C, M, D.C, D.C,

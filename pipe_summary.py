@@ -29,7 +29,7 @@ from traffic_summary import NAMES
 
 MORE = {"k_gemm": "gemm", "k_gemm_dma": "gemm", "k_proj": "gemm", "k_token_ln": "block_ln", "k_pos_ln": "block_pos_ln", "k_mlp_fused64": "block_mlp_fused", "k_mlp_stream": "block_mlp_fused",
         "k_attn_gen": "mfma_attention", "k_attn_rows": "mfma_attention", "k_pool_wide": "mfma_pool_qk",
-        "k_route_rows": "mfma_route_rows"}
+        "k_route_rows": "mfma_route_rows", "k_route_lce": "mfma_route_rows"}
 SIMDS, PEAK_HZ, ENGINES = 1024, 2.4e9, 32
 
 

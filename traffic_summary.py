@@ -18,7 +18,7 @@ NAMES = {"k_fused": "mfma_fused_k1", "k_pool": "mfma_pool_qk", "k_route": "mfma_
          "k_route_p": "mfma_route_rows", "k_route_u": "mfma_route_rows", "k_route_w": "mfma_route_rows",
          "k_attn_map": "mfma_attn_small", "k_attn_map4": "mfma_attn_small",
          "k_qkv": "mfma_qkv", "k_attn_big": "mfma_attention", "k_attn_q32": "mfma_attention", "k_attn_small": "mfma_attn_small",
-         "k_small": "mfma_attn_small", "k_lce_pairs": "mfma_lce_add", "k_prep_weights": "mfma_prep",
+         "k_small": "mfma_attn_small", "k_lce_add": "mfma_lce_add", "k_route_lce": "mfma_route_rows",
          "k_token_ln": "block_ln", "k_pos_ln": "block_pos_ln", "k_mlp_fused64": "block_mlp_fused", "k_mlp_stream": "block_mlp_fused",
          "k_util_copy": "copy"}
 
