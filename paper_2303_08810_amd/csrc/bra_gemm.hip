@@ -3,6 +3,7 @@
 #include "bra_gemm.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace bra {
 
@@ -770,11 +771,18 @@ int gemm_pair(const GemmHalf &a, const GemmHalf &b, long M, int K, int kernel_id
     }
 }
 
-// Two workgroups per compute unit over the 128 x 128 blocks of both products.
+// Shares of the tokens: at most two workgroups per compute unit over the 128 x 128 blocks of both products, and fewer where a
+// share's partial matrices cost more to write and to add up again than its 64-token chunks cost to multiply: chunks / shares x
+// 0.6 us + shares x elements x 1.8 ps is least at `paid`.  Whole gradient with 512 / blocks shares and now (us): 16 x 14 x 14 x 256,
+// k = 16 59.2 / 56.1, 8 x 14 x 14 x 384 57.0 / 52.9, 16 x 7 x 7 x 512 64.4 / 59.4, 16 x 28 x 28 x 128, k = 4 60.2 / 55.6,
+// 64 x 14 x 14 x 384 186.1 / 183.0; nearly as many shares as before, and nothing gained, 32 x 14 x 14 x 512 131.8 / 133.1.  One workgroup
+// per compute unit throughout was faster yet at C = 128 (100 x 28 x 28, k = 4 209.7 to 212.8) and slower where shares are
+// long: 16 x 14 x 14 x 1024 193 to 177.
 static int tn_share_tokens(long M, int KA0, int N0, int KA1, int N1)
 {
     auto blocks = [](int a, int n) { return (long)((a + 127) / 128) * ((n + 127) / 128); };
-    const long want = std::max(1L, 512 / (blocks(KA0, N0) + blocks(KA1, N1))), chunks = (M + 63) / 64;
+    const long chunks = (M + 63) / 64, paid = lrint(sqrt(3.3e5 * chunks / ((double)KA0 * N0 + (double)KA1 * N1)));
+    const long want = std::max(1L, std::min(512 / (blocks(KA0, N0) + blocks(KA1, N1)), paid));
     return (int)((chunks + want - 1) / want * 64);
 }
 

@@ -61,33 +61,31 @@ __device__ __forceinline__ bf16x8 tr_operand(const bf16_t *T, int pitch, int row
 // The two products that read the gradient map G = [dQ | dK | dV] ([M][3C]), in one pass over it:
 //     dX = G Wqkv^T                    (derivative of Eq. 3 with respect to X)
 //     dWqkv = X^T G                    (with respect to the weights; contraction over tokens)
-// A workgroup of C / 16 wavefronts streams 64-token tiles of G and X through LDS (the next tile
+// and, from the same tiles of O and dY beside them, dWo = O^T dY (Eq. 4).
+// C = 64.  A group of four wavefronts streams 64-token tiles of all four maps through LDS (the next tile
 // travels to registers meanwhile).  Wavefront w holds rows 16 w .. 16 w + 15 of Wqkv as A
 // operands and forms dX^T[channel][token] = Wqkv G^T tile by tile (B operand: a token's row of G);
 // and it keeps rows 16 w .. 16 w + 15 of dWqkv as 3C / 16 accumulators over all its tiles (both
-// operands by transposing reads), written at the end as Part[workgroup][C][3C] for k_reduce_parts.
-// With WO the same pass also streams O and dY and keeps dWo = O^T dY (rows 16 w .. 16 w + 15, C / 16
-// accumulators more: taken where the registers allow it, C = 64).
-template <int C, bool WO>
-struct ProjSmem {
-    static constexpr int GS = 3 * C + 8, XS = C + 8;
-    static constexpr size_t bytes = (size_t)64 * (GS + (WO ? 3 : 1) * XS) * 2;
-};
-
+// operands by transposing reads), written at the end as Part[workgroup][C][3C] for k_reduce_parts, and those of dWo as C / 16.
 // H = 2: two such groups of wavefronts in one workgroup, tile by tile in turn, add their sums through LDS at the end:
 // half as many partial matrices to write and to read again, which bound the end of the call.
-template <int C, bool WO, int H>
-__global__ __launch_bounds__(4 * C * H) void k_bwd_proj(const bf16_t *__restrict__ G, const bf16_t *__restrict__ X,
-                                                    const bf16_t *__restrict__ Wqkv, bf16_t *__restrict__ dX,
-                                                    float *__restrict__ Part, const bf16_t *__restrict__ O,
-                                                    const bf16_t *__restrict__ dY, float *__restrict__ PartO, long M,
-                                                    int tiles, int tiles_per_wg)
+struct ProjSmem {
+    static constexpr int C = 64, GS = 3 * C + 8, XS = C + 8;
+    static constexpr size_t bytes = (size_t)64 * (GS + 3 * XS) * 2;
+};
+
+template <int H>
+__global__ __launch_bounds__(256 * H) void k_bwd_proj(const bf16_t *__restrict__ G, const bf16_t *__restrict__ X,
+                                                      const bf16_t *__restrict__ Wqkv, bf16_t *__restrict__ dX,
+                                                      float *__restrict__ Part, const bf16_t *__restrict__ O,
+                                                      const bf16_t *__restrict__ dY, float *__restrict__ PartO, long M,
+                                                      int tiles, int tiles_per_wg)
 {
-    constexpr int NT = 4 * C, GS = ProjSmem<C, WO>::GS, XS = ProjSmem<C, WO>::XS, KS = 3 * C / 32, CT = 3 * C / 16;
-    constexpr int GCH = 3 * C / 8, XCH = C / 8, GL = 64 * GCH / NT, XL = 64 * XCH / NT, OT = WO ? C / 16 : 1;
+    constexpr int C = ProjSmem::C, NT = 4 * C, GS = ProjSmem::GS, XS = ProjSmem::XS, KS = 3 * C / 32, CT = 3 * C / 16;
+    constexpr int GCH = 3 * C / 8, XCH = C / 8, GL = 64 * GCH / NT, XL = 64 * XCH / NT, OT = C / 16;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int half = H == 1 ? 0 : (int)threadIdx.x / NT, tid = threadIdx.x % NT;
-    bf16_t *Gs = (bf16_t *)(smem + half * ProjSmem<C, WO>::bytes), *Xs = Gs + 64 * GS, *Os = Xs + 64 * XS, *Ys = Os + 64 * XS;
+    bf16_t *Gs = (bf16_t *)(smem + half * ProjSmem::bytes), *Xs = Gs + 64 * GS, *Os = Xs + 64 * XS, *Ys = Os + 64 * XS;
     const int w = tid / 64, lane = tid % 64, g = lane / 16, i = lane % 16;
     bf16x8 wf[KS];
 #pragma unroll
@@ -97,7 +95,7 @@ __global__ __launch_bounds__(4 * C * H) void k_bwd_proj(const bf16_t *__restrict
     for (int ct = 0; ct < CT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ct = 0; ct < OT; ++ct) acco[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    u32x4 gr[GL], xr[XL], orr[WO ? XL : 1], yr[WO ? XL : 1];
+    u32x4 gr[GL], xr[XL], orr[XL], yr[XL];
     auto fetch = [&](long tile) {
 #pragma unroll
         for (int u = 0; u < GL; ++u) {
@@ -110,10 +108,8 @@ __global__ __launch_bounds__(4 * C * H) void k_bwd_proj(const bf16_t *__restrict
             const int idx = tid + NT * u;
             const size_t at = (size_t)min(tile * 64 + idx / XCH, M - 1) * C + (idx % XCH) * 8;
             xr[u] = *(const u32x4 *)(X + at);
-            if (WO) {
-                orr[u] = *(const u32x4 *)(O + at);
-                yr[u] = *(const u32x4 *)(dY + at);
-            }
+            orr[u] = *(const u32x4 *)(O + at);
+            yr[u] = *(const u32x4 *)(dY + at);
         }
     };
     const int first = blockIdx.x * tiles_per_wg, last = min(tiles, first + tiles_per_wg);
@@ -128,10 +124,7 @@ __global__ __launch_bounds__(4 * C * H) void k_bwd_proj(const bf16_t *__restrict
                 if ((long)tile * 64 + (tid + NT * u) / GCH >= rows) gr[u] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int u = 0; u < XL; ++u)
-                if ((long)tile * 64 + (tid + NT * u) / XCH >= rows) {
-                    xr[u] = u32x4{0u, 0u, 0u, 0u};
-                    if (WO) orr[u] = yr[u] = xr[u];
-                }
+                if ((long)tile * 64 + (tid + NT * u) / XCH >= rows) xr[u] = orr[u] = yr[u] = u32x4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
         for (int u = 0; u < GL; ++u) {
@@ -142,10 +135,8 @@ __global__ __launch_bounds__(4 * C * H) void k_bwd_proj(const bf16_t *__restrict
         for (int u = 0; u < XL; ++u) {
             const int idx = tid + NT * u;
             *(u32x4 *)(Xs + (idx / XCH) * XS + (idx % XCH) * 8) = xr[u];
-            if (WO) {
-                *(u32x4 *)(Os + (idx / XCH) * XS + (idx % XCH) * 8) = orr[u];
-                *(u32x4 *)(Ys + (idx / XCH) * XS + (idx % XCH) * 8) = yr[u];
-            }
+            *(u32x4 *)(Os + (idx / XCH) * XS + (idx % XCH) * 8) = orr[u];
+            *(u32x4 *)(Ys + (idx / XCH) * XS + (idx % XCH) * 8) = yr[u];
         }
         __syncthreads();
         if (t0 + H < last) fetch(tile + H);
@@ -163,12 +154,9 @@ __global__ __launch_bounds__(4 * C * H) void k_bwd_proj(const bf16_t *__restrict
             const bf16x8 xa = tr_operand(Xs, XS, 32 * ks, 16 * w, g, i);
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) acc[ct] = mfma16(xa, tr_operand(Gs, GS, 32 * ks, 16 * ct, g, i), acc[ct]);
-            if (WO) {
-                const bf16x8 oa = tr_operand(Os, XS, 32 * ks, 16 * w, g, i);
+            const bf16x8 oa = tr_operand(Os, XS, 32 * ks, 16 * w, g, i);
 #pragma unroll
-                for (int ct = 0; ct < OT; ++ct)
-                    acco[ct] = mfma16(oa, tr_operand(Ys, XS, 32 * ks, 16 * ct, g, i), acco[ct]);
-            }
+            for (int ct = 0; ct < OT; ++ct) acco[ct] = mfma16(oa, tr_operand(Ys, XS, 32 * ks, 16 * ct, g, i), acco[ct]);
         }
     }
     if (H == 2) {
@@ -192,41 +180,41 @@ __global__ __launch_bounds__(4 * C * H) void k_bwd_proj(const bf16_t *__restrict
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int j = 0; j < 4; ++j) out[(size_t)(16 * w + 4 * g + j) * 3 * C + 16 * ct + i] = acc[ct][j];
-    if (WO) {
-        float *outo = PartO + (size_t)blockIdx.x * C * C;
+    float *outo = PartO + (size_t)blockIdx.x * C * C;
 #pragma unroll
-        for (int ct = 0; ct < OT; ++ct)
+    for (int ct = 0; ct < OT; ++ct)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) outo[(size_t)(16 * w + 4 * g + j) * C + 16 * ct + i] = acco[ct][j];
-    }
+        for (int j = 0; j < 4; ++j) outo[(size_t)(16 * w + 4 * g + j) * C + 16 * ct + i] = acco[ct][j];
 }
 
-// Tiles of k_bwd_proj per workgroup: all workgroups resident at once.  At C = 64 two groups of wavefronts share a
-// workgroup (`halves`) from more than 256 tiles, one per compute unit, on.  Whole gradient with two groups and with one
+// Tiles of k_bwd_proj per workgroup: all workgroups resident at once, two per compute unit.  Two groups of wavefronts share a
+// workgroup (`halves`) from more than 256 tiles on.  Whole gradient with two groups and with one
 // (us, k = 1): 294 tiles 65.1 / 69.6, 392 70.9 / 75.5, 490 74.6 / 80.0, 3136 214 / 225; below the line 49 tiles 48.1 / 47.4,
 // but 98 52.0 / 52.4, 196 58.6 / 59.0, 256 86.0 / 87.5: a line between 50 and 98 tiles would gain up to 2 % there.
 struct ProjPlan {
     int tiles, per_wg, groups, halves;
 };
 
-ProjPlan proj_plan(long M, int C)
+ProjPlan proj_plan(long M)
 {
     ProjPlan p;
     p.tiles = (int)((M + 63) / 64);
-    const int slots = C == 64 ? 512 : 256;
-    p.per_wg = (p.tiles + slots - 1) / slots;
-    p.halves = C == 64 && p.tiles > 256 ? 2 : 1;
+    p.per_wg = (p.tiles + 511) / 512;
+    p.halves = p.tiles > 256 ? 2 : 1;
     p.per_wg *= p.halves;
     p.groups = (p.tiles + p.per_wg - 1) / p.per_wg;
     return p;
 }
 
-// k_bwd_proj keeps 3C / 16 accumulators per wavefront: up to C = 128; wider layers take the plain
-// product for dX and k_gemm_tn for dWqkv.
-bool fused_projection(int C) { return C <= 128; }
+// One pass over the gradient map at C = 64; wider layers take the plain product for dX and shares of the tokens for both weight
+// gradients: a workgroup that keeps all of dWqkv writes it once per compute unit, 50 MB of partial matrices at C = 128
+// and their second reading.  Whole gradient in one pass and so (us): 64 x 56 x 56 x 64, k = 1 192 / 213, 32 images 109 / 114,
+// 8 56.7 / 57.8, 4 45.8 / 43.9; 64 x 28 x 28 x 128, k = 4 160 / 139, 16 images 78.3 / 55.6, 4 47.1 / 35.7, 2 x 128 x 128 x 128,
+// S = 16 158 / 131, one image of 14 x 14 x 128 34.7 / 26.2.
+bool fused_projection(int C) { return C == 64; }
 
-// Partial matrices of dWqkv (and of dWo, but for C = 128 where it is a launch of its own).
-int weight_parts(long M, int C) { return fused_projection(C) ? proj_plan(M, C).groups : gemm_tn_shares(M, C, 3 * C, C, C); }
+// Partial matrices of dWqkv and of dWo.
+int weight_parts(long M, int C) { return fused_projection(C) ? proj_plan(M).groups : gemm_tn_shares(M, C, 3 * C, C, C); }
 
 struct BwdWs {
     bf16_t *q, *k, *v, *dO, *o, *dqkv;
@@ -256,7 +244,7 @@ BwdWs carve_bwd(const Dims &D, void *ws)
     w.dsum = (float *)take((size_t)M * D.heads * 4);
     const int parts = weight_parts(M, D.C);
     w.part_qkv = (float *)take((size_t)parts * 3 * C * C * 4);
-    w.part_o = (float *)take((size_t)(D.C == 128 ? gemm_tn_shares(M, D.C, D.C, 0, 0) : parts) * C * C * 4);
+    w.part_o = (float *)take((size_t)parts * C * C * 4);
     w.part_lce = (float *)take((size_t)lce::lce_grad_groups_bf16(D, 3 * D.C) * 25 * C * 4);
     w.bytes = off;
     return w;
@@ -308,33 +296,19 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
     if (rc != BRA_OK) return rc;
     rc = attention_and_lce(D, w, Ir, (const bf16_t *)Wlce, st);
     if (rc != BRA_OK) return rc;
-    const ProjPlan pp = proj_plan(M, C);
-    const bool with_o = C == 64;          // dWo = O^T dY rides in the same pass where the registers allow it
     if (fused_projection(C)) {
-        // dX = [dQ | dK | dV] Wqkv^T and the partial sums of dWqkv = X^T [dQ | dK | dV] (and of dWo)
-        static bool opted[3] = {false, false, false};
-        if (!(C == 128 ? opt_in(k_bwd_proj<128, false, 1>, opted[2])
-                       : pp.halves == 2 ? opt_in(k_bwd_proj<64, true, 2>, opted[1]) : opt_in(k_bwd_proj<64, true, 1>, opted[0])))
-            return BRA_ERR_LAUNCH;
+        // dX = [dQ | dK | dV] Wqkv^T and the partial sums of dWqkv = X^T [dQ | dK | dV] and of dWo
+        const ProjPlan pp = proj_plan(M);
+        static bool opted[2] = {false, false};
+        if (!(pp.halves == 2 ? opt_in(k_bwd_proj<2>, opted[1]) : opt_in(k_bwd_proj<1>, opted[0]))) return BRA_ERR_LAUNCH;
         ProfScope ps(st, K_GEN_BACKWARD);
         if (pp.halves == 2)
-            hipLaunchKernelGGL((k_bwd_proj<64, true, 2>), dim3(pp.groups), dim3(512), (2 * ProjSmem<64, true>::bytes), st,
-                               w.dqkv, (const bf16_t *)X, (const bf16_t *)Wqkv, (bf16_t *)dX, w.part_qkv, w.o,
-                               (const bf16_t *)dY, w.part_o, M, pp.tiles, pp.per_wg);
-        else if (C == 64)
-            hipLaunchKernelGGL((k_bwd_proj<64, true, 1>), dim3(pp.groups), dim3(256), (ProjSmem<64, true>::bytes), st,
-                               w.dqkv, (const bf16_t *)X, (const bf16_t *)Wqkv, (bf16_t *)dX, w.part_qkv, w.o,
-                               (const bf16_t *)dY, w.part_o, M, pp.tiles, pp.per_wg);
+            hipLaunchKernelGGL(k_bwd_proj<2>, dim3(pp.groups), dim3(512), 2 * ProjSmem::bytes, st, w.dqkv, (const bf16_t *)X,
+                               (const bf16_t *)Wqkv, (bf16_t *)dX, w.part_qkv, w.o, (const bf16_t *)dY, w.part_o, M, pp.tiles, pp.per_wg);
         else
-            hipLaunchKernelGGL((k_bwd_proj<128, false, 1>), dim3(pp.groups), dim3(512), (ProjSmem<128, false>::bytes), st,
-                               w.dqkv, (const bf16_t *)X, (const bf16_t *)Wqkv, (bf16_t *)dX, w.part_qkv, nullptr,
-                               nullptr, nullptr, M, pp.tiles, pp.per_wg);
+            hipLaunchKernelGGL(k_bwd_proj<1>, dim3(pp.groups), dim3(256), ProjSmem::bytes, st, w.dqkv, (const bf16_t *)X,
+                               (const bf16_t *)Wqkv, (bf16_t *)dX, w.part_qkv, w.o, (const bf16_t *)dY, w.part_o, M, pp.tiles, pp.per_wg);
         if (!launched()) return BRA_ERR_LAUNCH;
-        if (!with_o) {
-            const GemmTn none = {};
-            rc = gemm_tn(GemmTn{w.o, (const bf16_t *)dY, w.part_o, C, C, C, C}, none, M, K_GEN_BACKWARD, st);
-            if (rc != BRA_OK) return rc;
-        }
     } else {
         rc = gemm_bt_tn(GemmTn{(const bf16_t *)X, w.dqkv, w.part_qkv, C, 3 * C, C, 3 * C}, GemmTn{w.o, (const bf16_t *)dY, w.part_o, C, C, C, C},
                         GemmHalf{w.dqkv, (const bf16_t *)Wqkv, 3 * C, C, GemmOut{{dX, nullptr, nullptr}, C, {nullptr, nullptr}, nullptr, nullptr, 0}},
@@ -344,7 +318,7 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
     {
         const int parts = weight_parts(M, C);
         const ReduceJob j0 = reduce_job(w.part_qkv, dWqkv, parts, 3 * C * C);
-        const ReduceJob j1 = reduce_job(w.part_o, dWo, C == 128 ? gemm_tn_shares(M, C, C, 0, 0) : parts, C * C);
+        const ReduceJob j1 = reduce_job(w.part_o, dWo, parts, C * C);
         const ReduceJob j2 = reduce_job(w.part_lce, dWlce, lce::lce_grad_groups_bf16(D, 3 * D.C), 25 * C);
         ProfScope ps(st, K_GEN_BACKWARD);
         hipLaunchKernelGGL(k_reduce_parts, dim3(j0.blocks + j1.blocks + j2.blocks), dim3(256), 0, st, j0, j1, j2);
