@@ -23,10 +23,10 @@ __global__ __launch_bounds__(256) void k_lce_backward(Job grad, Job add, int gra
     else job_block<false, true>(add, D, mfma::swizzled(bi - grad_blocks, (int)gridDim.x - grad_blocks), lds);
 }
 
-// Out = LCE(In) beside the rows of A^r and their top-k: the routing is a chain of latencies on a few workgroups (13 us for
+// LCE(In) in float32 (halves in Out and Low) beside the rows of A^r and their top-k: the routing is a chain of latencies on a few workgroups (13 us for
 // 8 x 64 regions of 768 channels), and the convolution needs nothing of it.  Workgroups below route_blocks (a multiple of 8;
-// those without rows leave) do the routing, the others two tiles each.  Routing, convolution in place and attention took 119.5 us
-// as a layer of 2 x 200 x 300 x 64, S = 16, and 124.0 of 8 x 32 x 32 x 768; with the convolution here 113.6 and 110.
+// those without rows leave) do the routing, the others two tiles each.  Figures for
+// whole layers stand at the call.
 constexpr int kStoreThreads = 64 * route::kWaves;
 
 __global__ __launch_bounds__(kStoreThreads, 4) void k_route_lce(const float *__restrict__ Qr, const float *__restrict__ Kr, int32_t *__restrict__ Ir,
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kStoreThreads, 4) void k_route_lce(const float *__r
     float none[1][2];
     const long tile = (long)(block / J.cblocks) * 2 + threadIdx.x / 256;
     if (tile < J.tiles)
-        walk_tile<false, false>(J.In, (const bf16_t *)nullptr, J.Out, D.C, D, J.T, tile, threadIdx.x / 32 % 8, c0, cl, true, w, none);
+        walk_tile<false, false>(J.In, (const bf16_t *)nullptr, J.Out, J.Low, D.C, D, J.T, tile, threadIdx.x / 32 % 8, c0, cl, true, w, none);
 }
 
 }  // namespace
@@ -57,7 +57,7 @@ namespace {
 
 Job plain_job(const Dims &D, const bf16_t *In, const bf16_t *Wlce, bf16_t *Out, int ldo)
 {
-    Job J = {In, nullptr, Wlce, Out, nullptr, ldo, (D.C + 63) / 64, 1, 0, Tiling{}};
+    Job J = {In, nullptr, Wlce, Out, nullptr, nullptr, ldo, (D.C + 63) / 64, 1, 0, Tiling{}};
     J.T = tiling(D, ldo, 1536 / J.cblocks, J.tiles);
     return J;
 }
@@ -70,7 +70,7 @@ constexpr int kGradSlots = 512, kAddSlots = 768;
 
 Job job(const Dims &D, const bf16_t *In, const bf16_t *V, const bf16_t *Wlce, bf16_t *Out, int ldo, float *Part, int workgroups)
 {
-    Job J = {In, V, Wlce, Out, Part, ldo, (D.C + 63) / 64, 1, 0, Tiling{}};
+    Job J = {In, V, Wlce, Out, nullptr, Part, ldo, (D.C + 63) / 64, 1, 0, Tiling{}};
     const long want = std::max(1, workgroups / J.cblocks);
     J.T = tiling(D, ldo, want, J.tiles);
     J.per_wg = (int)((J.tiles + want - 1) / want);
@@ -81,20 +81,23 @@ LcePlan wide_grad_plan(const Dims &D) { return lce_plan(D, 768, 8); }      // 8 
 
 }  // namespace
 
-BackwardJobs backward_jobs(const Dims &D, const bf16_t *dO, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, bf16_t *dV, int lddv, float *Part)
+BackwardJobs backward_jobs(const Dims &D, const bf16_t *dO, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, bf16_t *dV, bf16_t *dK, int lddv, float *Part)
 {
     BackwardJobs L;
     L.grad = job(D, dO, V, Wlce, dV, lddv, Part, kGradSlots);
+    L.grad.Low = dK;
     L.add = job(D, V, nullptr, Wlce, O, D.C, nullptr, kAddSlots);
     L.fit = offsets_fit(D, L.grad.T, lddv) && offsets_fit(D, L.add.T, D.C);
+    L.beside = L.fit && (long)D.B * D.N * D.C <= 14L << 20;
     return L;
 }
 
 // Qr = NULL: the convolution alone.  BRA_ERR_UNSUPPORTED, with nothing enqueued, for maps too wide for its strips.
 int route_rows_lce_bf16(const Dims &D, const float *Qr, const float *Kr, int32_t *Ir, const bf16_t *V, const bf16_t *Wlce, bf16_t *O,
-                        hipStream_t st)
+                        bf16_t *Low, hipStream_t st)
 {
-    const Job J = plain_job(D, V, Wlce, O, D.C);
+    Job J = plain_job(D, V, Wlce, O, D.C);
+    J.Low = Low;
     const long lce_blocks = ((J.tiles + 1) / 2 * J.cblocks + 7) / 8 * 8;
     if (D.C % 64 || !route::supported(D) || !offsets_fit(D, J.T, D.C) || lce_blocks > 0x3fffffffL) return BRA_ERR_UNSUPPORTED;
     const route::Plan p = route::plan(D, D.C);
@@ -124,7 +127,7 @@ int lce_add_bf16(const Dims &D, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, 
 
 int lce_grad_groups_bf16(const Dims &D, int lddv)
 {
-    const BackwardJobs L = backward_jobs(D, nullptr, nullptr, nullptr, nullptr, nullptr, lddv, nullptr);
+    const BackwardJobs L = backward_jobs(D, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, lddv, nullptr);
     return L.fit ? (int)L.grad.groups() : wide_grad_plan(D).groups;
 }
 

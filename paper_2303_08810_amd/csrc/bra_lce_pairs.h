@@ -69,12 +69,13 @@ __device__ __forceinline__ void load_taps(u32x2 (&w)[5][3], const TapTable &tabl
 }
 
 // One tile for the thread's slot (0 .. 7) and channels c0 + cl, c0 + cl + 1 (live: they exist).
-// GRAD = false: Out = LCE(In), with ADDS added to what is there.
+// GRAD = false: LCE(In), with ADDS added to what Out holds.  Without, in float32, the upper halves of the bits in Out and the
+//               lower ones in Low (laid out like Out): what is added to it later then rounds once.
 // GRAD = true:  the same with w the reversed taps (LCE^T), and the tap gradients from the same window (see k_lce_grad in
 //               bra_lce_dev.h for the identities): (V left, V right) against the window's pairs (p, p + 1), 25 sums
 //               per channel added to acc.
 template <bool GRAD, bool ADDS>
-__device__ __forceinline__ void walk_tile(const bf16_t *__restrict__ In, const bf16_t *__restrict__ V, bf16_t *__restrict__ Out, int ldo,
+__device__ __forceinline__ void walk_tile(const bf16_t *__restrict__ In, const bf16_t *__restrict__ V, bf16_t *__restrict__ Out, bf16_t *__restrict__ Low, int ldo,
                                           const Dims &D, const Tiling &T, long tile, int slot, int c0, int cl, bool live,
                                           const u32x2 (&w)[5][3], float (&acc)[GRAD ? 25 : 1][2])
 {
@@ -89,6 +90,7 @@ __device__ __forceinline__ void walk_tile(const bf16_t *__restrict__ In, const b
     const char *ibase = (const char *)(In + (b * D.N + (size_t)ytop * D.W) * D.C + c0);
     const char *vbase = GRAD ? (const char *)(V + (b * D.N + (size_t)ytop * D.W) * D.C + c0) : nullptr;
     char *obase = (char *)(Out + (b * D.N + (size_t)ytop * D.W) * ldo + c0);
+    char *lbase = ADDS ? nullptr : (char *)(Low + (b * D.N + (size_t)ytop * D.W) * ldo + c0);
     const unsigned irow = 2u * D.W * D.C, orow = 2u * D.W * ldo;
     unsigned xo[6];
     bool xok[6];
@@ -184,9 +186,20 @@ __device__ __forceinline__ void walk_tile(const bf16_t *__restrict__ In, const b
                 }
             }
             if (live) {
-                char *row = obase + (unsigned)(y - ytop) * orow;
-                *(unsigned *)(row + oo[0]) = mfma::pack_bf16(o[0][0], o[0][1]);
-                if (right) *(unsigned *)(row + oo[1]) = mfma::pack_bf16(o[1][0], o[1][1]);
+                const unsigned at = (unsigned)(y - ytop) * orow;
+                char *row = obase + at;
+                if constexpr (!ADDS) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        if (j == 1 && !right) break;
+                        const unsigned a = __builtin_bit_cast(unsigned, o[j][0]), c = __builtin_bit_cast(unsigned, o[j][1]);
+                        *(unsigned *)(row + oo[j]) = pair_hi(a, c);
+                        *(unsigned *)(lbase + at + oo[j]) = pair_lo(a, c);
+                    }
+                } else {
+                    *(unsigned *)(row + oo[0]) = mfma::pack_bf16(o[0][0], o[0][1]);
+                    if (right) *(unsigned *)(row + oo[1]) = mfma::pack_bf16(o[1][0], o[1][1]);
+                }
             }
         }
     }
@@ -218,7 +231,7 @@ inline Tiling tiling(const Dims &D, int ldo, long want, long &tiles)
 // of a workgroup.
 struct Job {
     const bf16_t *In, *V, *Wlce;
-    bf16_t *Out;
+    bf16_t *Out, *Low;
     float *Part;
     int ldo, cblocks, per_wg;
     long tiles;
@@ -250,7 +263,7 @@ __device__ __forceinline__ void job_block(const Job &J, const Dims &D, int block
 #pragma unroll
     for (int t = 0; t < (GRAD ? 25 : 1); ++t) acc[t][0] = acc[t][1] = 0.f;
     if (GRAD) __syncthreads();
-    for (long tile = first; tile < last; ++tile) walk_tile<GRAD, ADDS>(J.In, J.V, J.Out, J.ldo, D, J.T, tile, slot, c0, cl, live, w, acc);
+    for (long tile = first; tile < last; ++tile) walk_tile<GRAD, ADDS>(J.In, J.V, J.Out, J.Low, J.ldo, D, J.T, tile, slot, c0, cl, live, w, acc);
     if (!GRAD) return;
     // the 8 slots' sums of a channel through LDS, added in a fixed order
 #pragma unroll
@@ -268,12 +281,16 @@ __device__ __forceinline__ void job_block(const Job &J, const Dims &D, int block
     }
 }
 
-// The two passes of the gradients: dV += (or =) LCE^T(dO) with the tap gradients, and O += LCE(V).  fit: walk_tile takes both.
+// The two passes of the gradients: LCE^T(dO) with the tap gradients, added to dV or in float32 (lower halves where dK goes), and
+// O += LCE(V).  fit: walk_tile takes both.  beside: in the attention's launches.  The float32 sums are 4 bytes per value more to
+// write and to read, which beyond 14 million values costs more than the launches saved (whole gradient, us, of their own / beside:
+// 16 x 56 x 56 x 64, k = 1 87.6 / 77.9, 8 x 56 x 56 x 256, k = 4 199.6 / 186.2, 64 x 56 x 56 x 64 207 / 209, 16 x 112 x 120 x 64 309 / 297;
+// 24 x 56 x 56 x 256 533 / 541, 100 x 56 x 56 x 64 337 / 366).
 struct BackwardJobs {
     Job grad, add;
-    bool fit;
+    bool fit, beside;
 };
-BackwardJobs backward_jobs(const Dims &D, const bf16_t *dO, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, bf16_t *dV, int lddv, float *Part);
+BackwardJobs backward_jobs(const Dims &D, const bf16_t *dO, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, bf16_t *dV, bf16_t *dK, int lddv, float *Part);
 int lce_backward_bf16(const Dims &D, const BackwardJobs &L, int kernel_id, hipStream_t st);
 
 }  // namespace lce

@@ -1939,9 +1939,9 @@ int mfma_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
 bool mfma_reads_padded(const Dims &Dp) { return wide_shape(Dp) && Dp.n > 1; }
 
 int mfma_forward_padded(const Dims &Dp, int H, int W, const void *X, const void *Wqkv, const void *Wo, const void *Wlce,
-                        void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st)
+                        void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, void *Yp, hipStream_t st)
 {
-    return wide_forward(Dp, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, ws, st, H, W);
+    return wide_forward(Dp, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, ws, st, H, W, Yp);
 }
 
 }  // namespace bra

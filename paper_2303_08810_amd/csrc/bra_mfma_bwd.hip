@@ -256,11 +256,11 @@ bool launched() { return hipGetLastError() == hipSuccess; }
 // O = attention + LCE(V) (Eq. 7), dQ, dK, dV and the partial sums of the tap gradients.
 int attention_and_lce(const Dims &D, const BwdWs &w, const int32_t *Ir, const bf16_t *Wlce, hipStream_t st)
 {
-    const lce::BackwardJobs L = lce::backward_jobs(D, w.dO, w.v, Wlce, w.o, w.dqkv + 2 * D.C, 3 * D.C, w.part_lce);
+    const lce::BackwardJobs L = lce::backward_jobs(D, w.dO, w.v, Wlce, w.o, w.dqkv + 2 * D.C, w.dqkv + D.C, 3 * D.C, w.part_lce);
     const AttnBwdArgs A = {w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, w.lse, w.dsum};
     const bool map = attn_bwd_map_ok(D);
     const int rc = map ? launch_attn_bwd_map(D, w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, K_GEN_BACKWARD, st) : launch_attn_bwd(D, A, L, K_GEN_BACKWARD, st);
-    if (rc != BRA_OK || (!map && L.fit)) return rc;
+    if (rc != BRA_OK || (!map && L.beside)) return rc;
     return lce::lce_backward_bf16(D, L, K_GEN_BACKWARD, st);
 }
 

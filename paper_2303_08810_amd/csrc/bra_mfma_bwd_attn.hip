@@ -20,10 +20,11 @@
 // over the keys took 47, 65, 68 and 37 us on the query side, with the rounding of the bf16 weights in D.
 //
 // Both launches also carry a pass of the depth-wise convolution's gradients (bra_lce_pairs.h), which needs nothing of them: the
-// query side LCE^T(dO) into dV with the tap gradients, the key side O += LCE(V), and adds its dV to what is there.  Each launch
-// costs about 6 us to fill and to drain the chip, and neither kind of work alone keeps the memory busy.  Whole gradient with
-// launches of their own and here (us): 1 x 56 x 56 x 64, k = 1: 44.4 -> 32; 64 x 56 x 56 x 64: 216 -> 192; 64 x 28 x 28 x 128,
-// k = 4: 176 -> 162; 8 x 32 x 32 x 768, k = 12: 277 -> 263; 12 x 112 x 120 x 64: 266 -> 231.
+// query side LCE^T(dO) in float32 with the tap gradients, the key side O += LCE(V), and adds its dV to what is there (rounded to bf16
+// there, LCE^T(dO) put 4 to 6 % on the error of dX from float64; now 0.5 % below that of a convolution added to a rounded dV).
+// Each launch costs about 6 us to fill and to drain the chip, and neither kind of work alone keeps the memory busy.  Whole
+// gradient with launches of their own and here (us): 1 x 56 x 56 x 64, k = 1: 39.2 -> 31.7; 16 images: 87.6 -> 77.9;
+// 64 x 28 x 28 x 128, k = 4: 144 -> 140; 8 x 56 x 56 x 256, k = 4: 200 -> 186; 12 x 112 x 120 x 64: 251 -> 237.  Large maps: BackwardJobs.
 #include "bra_attn_dev.h"
 #include "bra_mfma_bwd_attn.h"
 
@@ -655,12 +656,14 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
             if (!idle) block(s);
         }
     }
-    auto store_dv = [&](bf16_t *at, f32x4 v) {   // with the pass, LCE^T(dO) is there
+    // With the pass, LCE^T(dO) is there in float32: its upper halves where dV goes, its lower ones where dK goes.
+    auto store = [&](bf16_t *at, f32x4 k, f32x4 v) {
         if (lce_blocks) {
-            const u32x2 there = *(const u32x2 *)at;
-            v += f32x4{bf16_lo(there[0]), bf16_hi(there[0]), bf16_lo(there[1]), bf16_hi(there[1])};
+            const u32x2 hi = *(const u32x2 *)(at + C), lo = *(const u32x2 *)at;
+            v += __builtin_bit_cast(f32x4, u32x4{pair_lo(lo[0], hi[0]), pair_hi(lo[0], hi[0]), pair_lo(lo[1], hi[1]), pair_hi(lo[1], hi[1])});
         }
-        *(u32x2 *)at = pack4(v);
+        *(u32x2 *)at = pack4(k * kLn2);
+        *(u32x2 *)(at + C) = pack4(v);
     };
     if constexpr (SPLIT) {
         // wavefront w adds up and stores channels 16 w .. 16 w + 15 of both
@@ -682,8 +685,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
 #pragma unroll
             for (int u = 0; u < 2; ++u, part += 1024)
                 sum[u] = (*(const f32x4 *)part + *(const f32x4 *)(part + 256)) + (*(const f32x4 *)(part + 512) + *(const f32x4 *)(part + 768));
-            *(u32x2 *)dst = pack4(sum[0] * kLn2);
-            store_dv(dst + C, sum[1]);
+            store(dst, sum[0], sum[1]);
         }
         return;
     }
@@ -694,10 +696,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh)
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt) {
-                *(u32x2 *)(row + HD * hh + 16 * dt) = pack4(dk[q][hh][dt] * kLn2);
-                store_dv(row + C + HD * hh + 16 * dt, dv[q][hh][dt]);
-            }
+            for (int dt = 0; dt < NDT; ++dt) store(row + HD * hh + 16 * dt, dk[q][hh][dt], dv[q][hh][dt]);
     }
 }
 
@@ -712,7 +711,7 @@ int launch_t(const Dims &D, const AttnBwdArgs &A, const lce::BackwardJobs &L, in
     // 64 x 56 x 56 x 64, k = 1, 3136 workgroups: 64.5 behind, 55.4 in front, 70 with the two kinds in turn).  The other pass is
     // always behind: its many short workgroups fill up the last round (12 x 112 x 120 x 64, k = 1: key side 76 us, in front 87).
     const bool front = blocks > 768;
-    const long with_q = L.fit ? L.grad.blocks() : 0, with_kv = L.fit ? L.add.blocks() : 0;
+    const long with_q = L.beside ? L.grad.blocks() : 0, with_kv = L.beside ? L.add.blocks() : 0;
     // kWaves has at most 32 tokens per region and always walks (up to 4096 regions)
     const size_t tables = MODE == kShared ? 1 : 4;
     const int walks = MODE == kSplit ? walk_ok(D) && D.n <= 256 : walk_ok(D);

@@ -692,6 +692,6 @@ size_t wide_workspace_bytes(const Dims &D);
 int wide_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *ws,
                hipStream_t st);
 int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo, const void *Wlce, void *Y,
-                 int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st, int H = 0, int W = 0);
+                 int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st, int H = 0, int W = 0, void *Yp = nullptr);
 
 }  // namespace bra

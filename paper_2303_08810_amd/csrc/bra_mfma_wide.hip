@@ -65,21 +65,26 @@ __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X,
     }
 }
 
-// What an output is added to (LCE(V)): the lane's four channels of 16-channel tile dt of NQ query tiles.
+// What an output is added to (LCE(V), float32 with the upper halves of the bits in O and the lower ones in Low: the sum rounds
+// once): the lane's four channels of 16-channel tile dt of NQ query tiles.
 template <int NQ>
 struct Added {
-    u32x2 v[NQ][4];
+    u32x2 hi[NQ][4], lo[NQ][4];
 
-    __device__ __forceinline__ void load(const bf16_t *O, const size_t (&token)[NQ], int C, int g)
+    __device__ __forceinline__ void load(const bf16_t *O, const bf16_t *Low, const size_t (&token)[NQ], int C, int g)
     {
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int dt = 0; dt < 4; ++dt) v[q][dt] = *(const u32x2 *)(O + token[q] * C + 16 * dt + 4 * g);
+            for (int dt = 0; dt < 4; ++dt) {
+                hi[q][dt] = *(const u32x2 *)(O + token[q] * C + 16 * dt + 4 * g);
+                lo[q][dt] = *(const u32x2 *)(Low + token[q] * C + 16 * dt + 4 * g);
+            }
     }
     __device__ __forceinline__ f32x4 to(f32x4 x, int q, int dt) const
     {
-        return x + f32x4{bf16_lo(v[q][dt][0]), bf16_hi(v[q][dt][0]), bf16_lo(v[q][dt][1]), bf16_hi(v[q][dt][1])};
+        const u32x2 h = hi[q][dt], l = lo[q][dt];
+        return x + __builtin_bit_cast(f32x4, u32x4{pair_lo(l[0], h[0]), pair_hi(l[0], h[0]), pair_lo(l[1], h[1]), pair_hi(l[1], h[1])});
     }
 };
 
@@ -98,7 +103,7 @@ struct Added {
 // its addition to the denominator and half a conversion; with maxima instead of additions and denominators from a product
 // it took 68 us.  One query tile per wavefront instead of two: 74 us (4 x 64 x 64 x 384, heads of 64, k = 4: 45 for 39).
 template <int HD, int NQ>
-__global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, int walks, bool adds)
+__global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, int walks, const bf16_t *__restrict__ Low)
 {
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16;
     __shared__ __attribute__((aligned(16))) bf16_t K0[64 * 64];
@@ -132,7 +137,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
                 qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + HD * hh + 32 * ks + 8 * g);
     }
     Added<NQ> added;
-    if (NQ == 1 && adds) added.load(O + img, qtok, C, g);
+    if (NQ == 1 && Low) added.load(O + img, Low + img, qtok, C, g);
     const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
     const bool report = A.Ir_out && A.Ir_out != A.Ir_src && qt == 0 && cg == 0;
     for (int p = tid; p < D.k; p += 256) {
@@ -241,7 +246,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
         if (k0 + 128 < kn) request(k0 + 128, kv[1][0], kv[1][1]);
         if (!idle) block(k0 + 64, K0, V0, std::false_type{});
     }
-    if (NQ > 1 && adds) added.load(O + img, qtok, C, g);      // 16 registers that the sweep does not have
+    if (NQ > 1 && Low) added.load(O + img, Low + img, qtok, C, g);      // 32 registers that the sweep does not have
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const bool store = 64 * NQ * qt + 16 * (NQ * wave + q) + i < n;
@@ -252,7 +257,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) {
                 f32x4 v = acc[q][hh][dt] * inv;
-                if (adds) v = added.to(v, q, NDT * hh + dt);
+                if (Low) v = added.to(v, q, NDT * hh + dt);
                 *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(v);
             }
         }
@@ -273,7 +278,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
 constexpr int kRowsBuffer = 4 * 2 * 32 * 64 * 2;       // bytes
 
 template <int HD, int NQ>
-__global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int items, bool adds)
+__global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int items, const bf16_t *__restrict__ Low)
 {
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16, KB = 32;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -308,7 +313,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__rest
                 qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + HD * hh + 32 * ks + 8 * g);
     }
     Added<NQ> added;
-    if (adds) added.load(O + img, qtok, C, g);
+    if (Low) added.load(O + img, Low + img, qtok, C, g);
     const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
     const bool report = A.Ir_out && A.Ir_out != A.Ir_src && cg == 0;
     for (int p = lane; p < D.k; p += kWave) {
@@ -414,7 +419,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__rest
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) {
                 f32x4 v = acc[q][hh][dt] * inv;
-                if (adds) v = added.to(v, q, NDT * hh + dt);
+                if (Low) v = added.to(v, q, NDT * hh + dt);
                 *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(v);
             }
         }
@@ -468,7 +473,7 @@ GemmRegions region_job(const Dims &D, const WideWs &w)
 }
 
 template <int HD, int NQ>
-int launch_attn_rows_t(const Dims &D, const AttnArgs &A, bf16_t *O, bool adds, hipStream_t st)
+int launch_attn_rows_t(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
 {
     const int items = D.B * D.R * (D.C / 64), blocks = (items + 3) / 4;
     const size_t smem = (size_t)(D.kn > 32 ? 2 : 1) * kRowsBuffer + (size_t)4 * (D.k + 32) * sizeof(int);
@@ -477,35 +482,35 @@ int launch_attn_rows_t(const Dims &D, const AttnArgs &A, bf16_t *O, bool adds, h
         if (hipFuncSetAttribute((const void *)k_attn_rows<HD, NQ>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess) return BRA_ERR_LAUNCH;
         opted = true;
     }
-    hipLaunchKernelGGL((k_attn_rows<HD, NQ>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), smem, st, A, O, D, items, adds);
+    hipLaunchKernelGGL((k_attn_rows<HD, NQ>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), smem, st, A, O, D, items, Low);
     return BRA_OK;
 }
 
-int launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, bool adds, hipStream_t st)
+int launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
 {
-    if (D.d == 32) return D.n <= 16 ? launch_attn_rows_t<32, 1>(D, A, O, adds, st) : launch_attn_rows_t<32, 2>(D, A, O, adds, st);
-    return D.n <= 16 ? launch_attn_rows_t<64, 1>(D, A, O, adds, st) : launch_attn_rows_t<64, 2>(D, A, O, adds, st);
+    if (D.d == 32) return D.n <= 16 ? launch_attn_rows_t<32, 1>(D, A, O, Low, st) : launch_attn_rows_t<32, 2>(D, A, O, Low, st);
+    return D.n <= 16 ? launch_attn_rows_t<64, 1>(D, A, O, Low, st) : launch_attn_rows_t<64, 2>(D, A, O, Low, st);
 }
 
 template <int NQ>
-void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, bool adds, hipStream_t st)
+void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
 {
     const int qtiles = (D.n + 64 * NQ - 1) / (64 * NQ);
     const dim3 grid((unsigned)((long)D.B * D.R * qtiles * (D.C / 64)));
     const int walks = walk_ok(D);
     const size_t smem = (size_t)(D.k + (walks ? D.n : 0)) * sizeof(int);
-    if (D.d == 32) hipLaunchKernelGGL((k_attn_gen<32, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks, adds);
-    else hipLaunchKernelGGL((k_attn_gen<64, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks, adds);
+    if (D.d == 32) hipLaunchKernelGGL((k_attn_gen<32, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks, Low);
+    else hipLaunchKernelGGL((k_attn_gen<64, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks, Low);
 }
 
-// adds: to what O holds (LCE(V)).
-void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, bool adds, hipStream_t st)
+// Low: if not NULL, the output is added to what O and it hold (LCE(V)).
+void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
 {
     // two query tiles per wavefront (every K and V operand read serves both; measured above) where the wider tile leaves no
     // more than an eighth of its queries empty beyond the narrow one and there are workgroups enough
     const int t64 = (D.n + 63) / 64, t128 = (D.n + 127) / 128;
-    if (t128 * 128 * 8 <= t64 * 64 * 9 && (long)D.B * D.R * t128 * (D.C / 64) >= 512) launch_attn_gen_t<2>(D, A, O, adds, st);
-    else launch_attn_gen_t<1>(D, A, O, adds, st);
+    if (t128 * 128 * 8 <= t64 * 64 * 9 && (long)D.B * D.R * t128 * (D.C / 64) >= 512) launch_attn_gen_t<2>(D, A, O, Low, st);
+    else launch_attn_gen_t<1>(D, A, O, Low, st);
 }
 
 // Pooling, region-level projections, A^r rows and top-k on their own.
@@ -549,12 +554,13 @@ int wide_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, floa
 }
 
 // H, W: the caller's map where D describes a zero-padded one (0: it does not): the products and the pooling read tokens
-// beyond it as zeros and do not write them; nothing is copied.
+// beyond it as zeros and do not write them; nothing is copied.  Yp: scratch of the padded map's size then.
 int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo, const void *Wlce, void *Y,
-                 int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st, int H, int W)
+                 int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st, int H, int W, void *Yp)
 {
     const GemmRows pad = H ? GemmRows{D.H, D.W, H, W} : GemmRows{};
     const WideWs w = carve(D, ws);
+    bf16_t *low = (bf16_t *)(H ? Yp : Y);        // nothing else is there until the last product, and X has been read by then
     const int32_t *Ir_src = Ir_in_opt;
     int32_t *Ir_dst = Ir_out_opt ? Ir_out_opt : w.ir;
     // Q^r | K^r: one token per region: Q, K before their rounding to bf16, which the token projection leaves as float32
@@ -573,10 +579,14 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     AttnArgs A = {};
     bool adds = false;
     const bool map_tail = map_tail_pays(D);      // forms the LCE itself
-    if (!map_tail) {
-        // LCE(V) into the output map, to which the attention adds itself: what the convolution needs is there as soon as the
-        // routing's input is, and the routing leaves most of the chip idle
-        rc = lce::route_rows_lce_bf16(D, route ? w.qr : nullptr, w.kr, Ir_dst, w.v, (const bf16_t *)Wlce, w.o, st);
+    if (!map_tail && M * D.C <= 9L << 20) {
+        // LCE(V) in front, to which the attention adds itself: what the convolution needs is there as soon as the
+        // routing's input is, and the routing leaves most of the chip idle.  It is kept in float32: rounded to bf16 it put 7 to 9 %
+        // on the layer's error from float64, now 3 to 4 % below that of the convolution added to a rounded attention.  Beyond 9
+        // million values its 4 bytes more per value cost more (layer, us, added at the end / in front: 1 x 32 x 32 x 768, k = 12
+        // 52.2 / 47.4, 8 x 32 x 32 x 768 116.2 / 110.8, 2 x 200 x 300 x 64, S = 16 118.6 / 116.3, 4 x 128 x 128 x 128 91.5 / 91.5;
+        // 12 x 56 x 56 x 256 104 / 107, 28 x 56 x 56 x 192 141 / 151, 16 x 64 x 64 x 384 244 / 274)
+        rc = lce::route_rows_lce_bf16(D, route ? w.qr : nullptr, w.kr, Ir_dst, w.v, (const bf16_t *)Wlce, w.o, low, st);
         if (rc != BRA_OK && rc != BRA_ERR_UNSUPPORTED) return rc;
         adds = rc == BRA_OK;
     }
@@ -593,8 +603,8 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     } else {
         {
             ProfScope ps(st, K_MFMA_ATTENTION);
-            if (D.n <= 32 && D.k <= 1024) rc = launch_attn_rows(D, A, w.o, adds, st);      // its tables fit in LDS
-            else launch_attn_gen(D, A, w.o, adds, st);
+            if (D.n <= 32 && D.k <= 1024) rc = launch_attn_rows(D, A, w.o, adds ? low : nullptr, st);      // its tables fit in LDS
+            else launch_attn_gen(D, A, w.o, adds ? low : nullptr, st);
         }
         if (rc != BRA_OK) return rc;
         rc = adds ? BRA_OK : lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);

@@ -67,7 +67,7 @@ int padded_forward(const Dims &Dp, int H, int W, const void *X, const void *Wqkv
     const int esize = Dp.dtype == BRA_BF16 ? 2 : 4;
     char *Xp = (char *)ws, *Yp = Xp + map_bytes(Dp), *inner = Yp + map_bytes(Dp);
     if (path == BRA_PATH_MFMA && mfma_reads_padded(Dp))
-        return mfma_forward_padded(Dp, H, W, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, inner, st);
+        return mfma_forward_padded(Dp, H, W, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, inner, Yp, st);
     int rc = resize_map(Xp, X, Dp.B, Dp.H, Dp.W, H, W, Dp.C, esize, st);
     if (rc != BRA_OK) return rc;
     rc = (path == BRA_PATH_MFMA) ? mfma_forward(Dp, Xp, Wqkv, Wo, Wlce, Yp, Ir_out_opt, Ir_in_opt, inner, st)
