@@ -122,7 +122,8 @@ int mfma_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, floa
 int mfma_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo, const void *Wlce,
                  void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st);
 
-// Whether the pipeline for the padded shape takes the caller's H x W map itself, and that pipeline.  Yp: scratch of the padded map's size.
+// Whether the pipeline for the padded shape takes the caller's H x W map itself, and that pipeline.
+// Yp: scratch of the padded map's size.
 bool mfma_reads_padded(const Dims &Dp);
 int mfma_forward_padded(const Dims &Dp, int H, int W, const void *X, const void *Wqkv, const void *Wo, const void *Wlce,
                         void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, void *Yp, hipStream_t st);

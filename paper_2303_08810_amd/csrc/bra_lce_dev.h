@@ -444,7 +444,8 @@ int launch_lce_grad(const Dims &D, const GradJob<TM> &J, hipStream_t st)
 // bf16 maps with an even number of channels (bra_lce.hip), on the two-element bf16 dot product: O += LCE(V);
 // the passes of the gradients (backward_jobs) leave the tap gradients as lce_grad_groups_bf16 arrays of 25 C floats.
 int lce_add_bf16(const Dims &D, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, int ldo, int kernel_id, hipStream_t st);
-// LCE(V) in float32, the upper halves in O and the lower ones in Low, and beside it in the same launch the rows of A^r from Q^r, K^r [B, R, C] and their top-k.
+// LCE(V) in float32, the upper halves of the bits in O and the lower ones in Low, and beside it in the same launch the rows of
+// A^r from Q^r, K^r [B, R, C] and their top-k.
 int route_rows_lce_bf16(const Dims &D, const float *Qr, const float *Kr, int32_t *Ir, const bf16_t *V, const bf16_t *Wlce, bf16_t *O,
                         bf16_t *Low, hipStream_t st);
 int lce_grad_groups_bf16(const Dims &D, int lddv);

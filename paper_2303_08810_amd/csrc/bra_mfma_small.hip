@@ -804,19 +804,22 @@ static int launch_small_c(const Dims &D, const AttnArgs &A0, bf16_t *O, hipStrea
     return lce::lce_add_bf16(D, A.V, A.Wlce, O, D.C, K_MFMA_LCE_ADD, st);
 }
 
-// Any C that is a multiple of 64: regions of up to 4 tokens on a map that fits the image-resident attention, where that is
+// Any C that is a multiple of 64: regions of up to 8 tokens on a map that fits the image-resident attention, where that is
 // faster than a wavefront per region and 64 channels (k_attn_rows) with the convolution beside the routing: with an
 // (image, head) pair per compute unit or more, and either many blocks of 32 keys for those wavefronts or so many workgroups
 // of the routing that the convolution is not hidden beside them.  Layer, image-resident / by regions (us): 6 x 14 x 14 x 512,
 // k = 8: 48.8 / 35.6; 24 x 14 x 14 x 192, k = 1: 37.4 / 27.9; 24 x 14 x 14 x 512, k = 8: 61.2 / 54.8; 24 x 7 x 7 x 768, k = 1: 47.8 / 46.0;
 // 16 x 7 x 7 x 512, k = 49: 35.5 / 38.6; 16 x 14 x 14 x 768, k = 49: 88.8 / 93.1; 32 x 8 x 8 x 768, k = 12: 61.5 / 68.8; 64 x 7 x 7 x
-// 128, k = 16: 25.3 / 27.4.  Regions of 8 tokens take twice the passes: 6 x 14 x 28 x 512, k = 1: 62.5 / 36.5; 24 x 14 x 28 x 768,
-// k = 8: 139.7 / 130.5; 32 x 16 x 32 x 768, k = 49: 323 / 326.
+// 128, k = 16: 25.3 / 27.4.  Regions of 8 tokens take twice the passes and want three rounds of pairs: 6 x 14 x 28 x 512,
+// k = 1: 62.5 / 36.5; 24 x 14 x 28 x 768, k = 8: 136.7 / 130.1; 24 x 14 x 28 x 384, k = 45: 107.8 / 86.7; 64 x 14 x 28 x 384, k = 4: 132.8 / 122.2,
+// k = 20: 156.6 / 156.3, but 63 images, k = 45: 190.6 / 198.7; 64 x 14 x 28 x 512, k = 16: 197 / 204; 32 x 16 x 32 x 768, k = 49: 291 / 296.
 bool map_tail_pays(const Dims &D)
 {
     if (D.C % 64 != 0 || D.d != 32) return false;
-    if (D.n > 4 || (D.n & (D.n - 1)) != 0 || D.W > 64 || (long)D.B * (D.C / 32) < 256) return false;
+    const long pairs = (long)D.B * (D.C / 32);
+    if (D.n > 8 || (D.n & (D.n - 1)) != 0 || D.W > 64 || pairs < 256) return false;
     const long blocks = (long)D.B * D.R * (D.C / 64) * ((D.kn + 31) / 32), routing = (long)D.B * ((D.R + 15) / 16);
+    if (D.n == 8) return pairs >= 720 && blocks >= 96000 && map_attention(D);
     return (blocks >= 12000 || routing >= 192) && map_attention(D);
 }
 

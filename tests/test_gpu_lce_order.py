@@ -1,5 +1,5 @@
 """The depth-wise convolution in front of what it is added to, as float32 halves in two maps, and behind it: GPU parity beyond
-the lines up to which it runs in front (9 x 2^20 values in the forward, 14 x 2^20 in the gradients; other files hold the sizes
+the lines up to which it runs in front (6 or 9 x 2^20 values in the forward, 14 x 2^20 in the gradients; other files hold the sizes
 below), and the number of roundings where it does.  With taps so large that nothing else shows, Y carries those of V, O and Y
 and dX those of dO, dV and dX.  A rounding to bf16 is 1.66e-3 rms of a spread of values: three of them 2.87e-3, four (the
 convolution rounded before it is added to) 3.3e-3; the bound lies between."""
@@ -48,9 +48,15 @@ def test_convolution_rounds_once(B, H, W, C, heads, S, k):
     assert e <= THREE_ROUNDINGS and d <= THREE_ROUNDINGS
 
 
-def test_convolution_behind_attention():
-    X, Wqkv, Wo, Wlce = make_inputs(17, 56, 56, 192, seed=9950, dtype="bf16")      # 9.8 x 2^20 values
-    compare(X, Wqkv, Wo, Wlce, "bf16", 7, 1, 6, "mfma")
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", [
+    (17, 56, 56, 192, 6, 7, 1),      # 9.8 x 2^20 values
+    (30, 49, 49, 128, 4, 7, 1),      # 8.8, short rows in the routing
+    (62, 14, 28, 512, 16, 7, 16),    # regions of 8 tokens by whole images
+    (61, 14, 28, 512, 16, 7, 16),    # and region by region
+])
+def test_convolution_behind_attention(B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=9950, dtype="bf16")
+    compare(X, Wqkv, Wo, Wlce, "bf16", S, k, heads, "mfma")
 
 
 def test_convolution_behind_gradients():
