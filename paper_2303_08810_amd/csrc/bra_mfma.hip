@@ -1892,6 +1892,15 @@ static bool specialised(const Dims &D)
 
 bool wide_shape(const Dims &D) { return !specialised(D); }
 
+// Attention kernels outside the general pipeline that add the convolution in float32 and round O once take the shape:
+// k_attn_q32, k_attn_big, k_small, or the image-resident attention with room for its tile.
+bool layer_rounds_once(const Dims &D)
+{
+    if (D.n <= 8) return map_tail_rounds_once(D);
+    if (D.dtype != BRA_BF16 || D.d != 32 || (D.C != 64 && D.C != 128 && D.C != 256)) return false;
+    return attn_big_ok(D) || (small_supported(D) && !small_needs_projection(D));
+}
+
 // The matrix-core kernels address a token's channels within its image by 32-bit element
 // offsets and divide key / slot numbers with fast_div (exact below 2^20).
 static bool addressable(const Dims &D)

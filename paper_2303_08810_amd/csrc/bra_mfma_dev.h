@@ -678,6 +678,7 @@ int launch_small(const Dims &D, const mfma::AttnArgs &A, bf16_t *O, hipStream_t 
 // Attention of regions of 1, 2, 4 or 8 tokens + LCE into O for any C that is a multiple of 64
 // (image-resident attention; A.Q/K/V, Ir_src, Ir_out, Wlce, c_exp set).
 bool map_tail_pays(const Dims &D);
+bool map_tail_rounds_once(const Dims &D);     // it takes the shape and adds the LCE in float32
 int launch_map_tail(const Dims &D, const mfma::AttnArgs &A, bf16_t *O, hipStream_t st);
 // Attention + LCE + W^o for regions of 64 n tokens with 32 queries per wavefront
 // (bra_mfma_attn.hip); A.Q must hold Q multiplied by scale * log2(e).
@@ -687,6 +688,7 @@ int launch_attn_q32(const Dims &D, const mfma::AttnArgs &A, hipStream_t st);
 // Pipeline for other channel counts (bra_mfma_wide.hip): any multiple of 64 with heads of 32
 // channels, at most 64 regions of 1, 2, 4 or 8 tokens.
 bool wide_shape(const Dims &D);          // not one of the specialised channel counts
+bool layer_rounds_once(const Dims &D);   // a kernel outside this pipeline takes the shape and adds the LCE in float32
 bool wide_supported(const Dims &D);
 size_t wide_workspace_bytes(const Dims &D);
 int wide_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *ws,

@@ -823,6 +823,11 @@ bool map_tail_pays(const Dims &D)
     return (blocks >= 12000 || routing >= 192) && map_attention(D);
 }
 
+bool map_tail_rounds_once(const Dims &D)
+{
+    return D.C % 64 == 0 && D.d == 32 && D.n <= 8 && (D.n & (D.n - 1)) == 0 && D.W <= 64 && map_adds_lce(D);
+}
+
 int launch_map_tail(const Dims &D, const AttnArgs &A, bf16_t *O, hipStream_t st)
 {
     int log2n = 0;

@@ -1,6 +1,6 @@
 """The depth-wise convolution in front of what it is added to, as float32 halves in two maps, and behind it: GPU parity beyond
 the lines up to which it runs in front (6 or 9 x 2^20 values in the forward, 14 x 2^20 in the gradients; other files hold the sizes
-below), and the number of roundings where it does.  With taps so large that nothing else shows, Y carries those of V, O and Y
+below), and the number of roundings where it does, and where a kernel with the convolution in it takes the shape, at any size.  With taps so large that nothing else shows, Y carries those of V, O and Y
 and dX those of dO, dV and dX.  A rounding to bf16 is 1.66e-3 rms of a spread of values: three of them 2.87e-3, four (the
 convolution rounded before it is added to) 3.3e-3; the bound lies between."""
 import numpy as np
@@ -46,6 +46,31 @@ def test_convolution_rounds_once(B, H, W, C, heads, S, k):
     d = rms_error(dX, obw.bra_backward(X, Wqkv, Wo, Wlce, dY, Ir, S=S, heads=heads)["dX"])
     print(f"rms error of Y {e:.3e}, of dX {d:.3e}", flush=True)
     assert e <= THREE_ROUNDINGS and d <= THREE_ROUNDINGS
+
+
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", [
+    (16, 128, 128, 64, 2, 16, 4),    # more than 64 regions, of 64 tokens
+    (5, 128, 128, 128, 4, 16, 1),
+    (37, 64, 64, 64, 2, 16, 4),      # of 16
+    (20, 64, 64, 128, 4, 16, 4),
+    (10, 64, 64, 256, 8, 16, 1),
+    (64, 14, 28, 384, 12, 7, 4),     # 8 tokens, maps whose convolution the image-resident attention has room for
+    (61, 14, 28, 512, 16, 7, 16),
+    (64, 10, 20, 768, 24, 5, 8),
+])
+def test_one_rounding_beyond_the_lines(B, H, W, C, heads, S, k):
+    # the other way round: equal scores, so that the attention is a mean of kn values of V and as exact as they are, and a
+    # convolution of a third of it, which shows a rounding of the attention before it is added to
+    X, Wqkv, Wo, Wlce, Ir, _ = heavy_taps(B, H, W, C, S, k)
+    Wqkv[:, :C] = 0
+    Wlce = round_to_bf16(Wlce * np.float32(0.3 / 64 / np.sqrt(k * (H // S) * (W // S))))
+    x, wqkv, wo, wlce = (to_device(a, "bf16") for a in (X, Wqkv, Wo, Wlce))
+    Y = bra.bra_forward(x, wqkv, wo, wlce, S, k, heads, Ir_in=torch.from_numpy(Ir).cuda(), path="mfma")
+    some = [0, B - 1]      # images are independent of each other
+    ref = run_oracle(X[some], Wqkv, Wo, Wlce, dict(S=S, k=k, heads=heads), Ir_in=Ir[some])["Y"]
+    e = rms_error(Y[some], np.asarray(ref, np.float64))
+    print(f"rms error of Y {e:.3e}", flush=True)
+    assert e <= THREE_ROUNDINGS
 
 
 @pytest.mark.parametrize("B,H,W,C,heads,S,k", [
