@@ -163,8 +163,9 @@ int bra_padded_workspace_bytes(const bra_shape *shape, size_t *out_bytes)
     ps.H = Dp.H; ps.W = Dp.W;
     int path = pick_path(&ps, Dp);
     if (path < 0) return path;
-    const size_t inner = (path == BRA_PATH_MFMA) ? mfma_workspace_bytes(Dp) : generic_workspace_bytes(Dp);
-    *out_bytes = (Dp.H == shape->H && Dp.W == shape->W) ? inner : padded_workspace_bytes(Dp, inner);
+    if (Dp.H == shape->H && Dp.W == shape->W) return bra_workspace_bytes(&ps, out_bytes);
+    const size_t inner = (path == BRA_PATH_MFMA) ? mfma_padded_workspace_bytes(Dp) : generic_workspace_bytes(Dp);
+    *out_bytes = padded_workspace_bytes(Dp, inner);
     return BRA_OK;
 }
 
@@ -182,7 +183,7 @@ int bra_forward_padded(const bra_shape *shape, const void *X, const void *Wqkv, 
         return bra_forward(&ps, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, ws, ws_bytes, hip_stream);
     int path = pick_path(&ps, Dp);
     if (path < 0) return path;
-    const size_t inner = (path == BRA_PATH_MFMA) ? mfma_workspace_bytes(Dp) : generic_workspace_bytes(Dp);
+    const size_t inner = (path == BRA_PATH_MFMA) ? mfma_padded_workspace_bytes(Dp) : generic_workspace_bytes(Dp);
     if (!ws_ok(ws, ws_bytes, padded_workspace_bytes(Dp, inner))) return BRA_ERR_WORKSPACE;
     return padded_forward(Dp, shape->H, shape->W, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, ws, path,
                           (hipStream_t)hip_stream);

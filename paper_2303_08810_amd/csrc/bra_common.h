@@ -125,6 +125,7 @@ int mfma_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
 // Whether the pipeline for the padded shape takes the caller's H x W map itself, and that pipeline.
 // Yp: scratch of the padded map's size.
 bool mfma_reads_padded(const Dims &Dp);
+size_t mfma_padded_workspace_bytes(const Dims &Dp);
 int mfma_forward_padded(const Dims &Dp, int H, int W, const void *X, const void *Wqkv, const void *Wo, const void *Wlce,
                         void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, void *Yp, hipStream_t st);
 

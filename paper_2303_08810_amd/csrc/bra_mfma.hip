@@ -1507,7 +1507,7 @@ void k_fused(AttnArgs A, Dims D)
 // ---------------------------------------------------------------------------
 struct MfmaWs {
     bf16_t *q, *k, *v, *o, *wt, *wot, *wa, *wf;
-    float *xr, *u, *p;
+    float *xr, *u, *p, *means;
     int32_t *ir;
     size_t bytes;
 };
@@ -1518,11 +1518,14 @@ int halo_rows(const Dims &D)
     return (qh + 4) * (D.rw + 4);
 }
 
+// More than 64 regions: their rows of A^r are the general pipeline's.
+bool far_routing(const Dims &D) { return D.S > kFastRouteMaxS; }
+
 // The fused pipeline pays one extra K/V projection per routed key block.
 bool fused_ok(const Dims &D)
 {
     static const bool disabled = experiment_flag("BRA_DISABLE_FUSED");
-    if (disabled) return false;
+    if (disabled || far_routing(D)) return false;
     if (D.C != 64) return false;
     return D.n == 64 && D.k == 1 && (D.rw == 8 || D.rw == 16);
 }
@@ -1565,7 +1568,7 @@ TileMap tile_map(const Dims &D, bool pooled)
 
 bool pooled_projection(const Dims &D)
 {
-    return region_tiles_ok(D) || D.rh * (D.rw >> pool_group_log2(D)) <= 8;
+    return !far_routing(D) && (region_tiles_ok(D) || D.rh * (D.rw >> pool_group_log2(D)) <= 8);
 }
 
 MfmaWs carve(const Dims &D, void *ws)
@@ -1587,6 +1590,7 @@ MfmaWs carve(const Dims &D, void *ws)
     w.u = (float *)take(D.C == 64 && fused_ok(D) ? (size_t)D.B * D.R * D.C * sizeof(float) : 0);
     w.p = (float *)take(pooled_projection(D) ? (size_t)D.B * D.H * (D.W >> pool_group_log2(D)) * 2 * D.C * sizeof(float) : 0);
     w.ir = (int32_t *)take((size_t)D.B * D.R * D.k * sizeof(int32_t));
+    w.means = (float *)take(far_routing(D) ? wide_means_bytes(D) : 0);
     w.bytes = off;
     return w;
 }
@@ -1746,7 +1750,12 @@ int forward_c(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const bf16_t *
     static const bool route_launch = experiment_flag("BRA_FUSED_ROUTE_LAUNCH");
     const bool inline_route = fused && !route_launch;     // the k = 1 kernel routes by itself, from the routing vectors
     {
-        const bool from_x = (fused || !pooled_projection(D)) && !Ir_in_opt;
+        const bool far = far_routing(D), from_x = !far && (fused || !pooled_projection(D)) && !Ir_in_opt;
+        if (far && !Ir_in_opt) {
+            const int rc = wide_route_pooled(D, X, Wqkv, Ir_dst, nullptr, w.means, st);
+            if (rc != BRA_OK) return rc;
+            Ir_src = Ir_dst;
+        }
         if (fused || from_x)
             launch_pool<C>(D, X, Wqkv, Wo, Wlce, w, /*pool=*/from_x, prep_total(C), st, /*with_u=*/inline_route);
         if (from_x && !inline_route) {
@@ -1837,7 +1846,9 @@ int route_c(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, int32_t *Ir, flo
 {
     // the same kernels as bra_forward runs for this shape, so that both give the same index
     int rc;
-    if (C == 64 && fused_ok(D)) {
+    if (far_routing(D)) {
+        rc = wide_route_pooled(D, X, Wqkv, Ir, Ar_opt, w.means, st);
+    } else if (C == 64 && fused_ok(D)) {
         launch_pool<C>(D, X, Wqkv, nullptr, nullptr, w, /*pool=*/true, 0, st, /*with_u=*/true);
         ProfScope ps(st, K_MFMA_ROUTE_ROWS);
         hipLaunchKernelGGL(k_route_u, dim3(D.B * D.R), dim3(256), 0, st, w.xr, w.u, Ir, Ar_opt, D);
@@ -1870,6 +1881,19 @@ bool attn_big_ok(const Dims &D)
 
 }  // namespace
 
+// More than 64 regions: where the convolution, attention and W^o in one kernel, behind the general pipeline's routing, are faster
+// than the general pipeline, whose float32 convolution moves 8 bytes more per value.  Both round O once.  Layer, S = 16 (us, general / here),
+// by millions of values: 128 x 128 x 64, k = 4: 4 50.2 / 51.7, 6 67.7 / 63.1, 8 81.8 / 75.2, 16 154.7 / 132.9, 32 310 / 261;
+// 256 x 256 x 64, k = 1: 4 52.8 / 51.7, 8 83.0 / 74.5, 32 286 / 249; 64 x 64 x 128, k = 4: 4 49.9 / 52.3, 6 68.0 / 62.0, 16 164 / 133;
+// k = 13: 16 198 / 191.  Later for 64 x 64 x 64, k = 4: 8 87.7 / 85.5, 16 174 / 163 (k = 1: 157 / 158) and 64 x 64 x 256, k = 4: 12 142.8 /
+// 142.9, 24 274 / 260 (k = 1: 12 131 / 140, 32 336 / 341).  Not for 128 x 128 x 128, k = 4: 8 84.6 / 96.4, 32 295 / 319.
+static bool far_pays(const Dims &D)
+{
+    const long values = (long)D.B * D.N * D.C;
+    if (attn_big_ok(D)) return D.C == 64 && values > 5L << 20;
+    return D.n == 16 && small_supported(D) && !small_needs_projection(D) && values > (D.C == 128 ? 5L : 14L) << 20;
+}
+
 // Shapes of the kernels specialised by channel count.
 static bool specialised(const Dims &D)
 {
@@ -1878,10 +1902,7 @@ static bool specialised(const Dims &D)
     if (D.dtype != BRA_BF16 || D.d != 32) return false;
     if (D.C != 64 && D.C != 128 && D.C != 256) return false;
     if ((long)D.B * D.R * (D.n / 64 + 1) + 8 > 0x7fffffffL) return false;
-    // More than 64 regions: their routing is not among these kernels, and the general pipeline, which carries the convolution
-    // beside it, is faster throughout (S = 16, us, here with launches for the routing / there: 4 x 64 x 64 x 64, k = 4: 33 / 28;
-    // 16 x 64 x 64 x 64, k = 1: 55 / 46; 10 x 64 x 64 x 128, k = 13: 84 / 72; 128 x 128 x 128, k = 4: 52 / 38; 4 of them 103 / 85).
-    if (D.S > kFastRouteMaxS) return false;
+    if (far_routing(D)) return wide_supported(D) && far_pays(D);
     // Regions of fewer than 16 tokens: the image-resident attention needs a (image, head) pair per compute unit, and the
     // projection with the pooling in it many tokens.  Here / there (us): 14 x 14 x 256, k = 16: B = 24 43.5 / 38.2, 64 49.6 /
     // 69.2; 14 x 28 x 256, k = 1: 6 41.3 / 27.1, 24 58.8 / 41.4, 64 78.5 / 77.7; 14 x 14 x 128, k = 16: 24 35.5 / 27.2, 64 38.1 / 41.0;
@@ -1945,7 +1966,10 @@ int mfma_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     }
 }
 
-bool mfma_reads_padded(const Dims &Dp) { return wide_shape(Dp) && Dp.n > 1; }
+// A copy of the padded map costs more than what far_pays() gains.
+bool mfma_reads_padded(const Dims &Dp) { return (wide_shape(Dp) || far_routing(Dp)) && Dp.n > 1; }     // far_routing(): the general pipeline takes it too
+
+size_t mfma_padded_workspace_bytes(const Dims &Dp) { return mfma_reads_padded(Dp) ? wide_workspace_bytes(Dp) : mfma_workspace_bytes(Dp); }
 
 int mfma_forward_padded(const Dims &Dp, int H, int W, const void *X, const void *Wqkv, const void *Wo, const void *Wlce,
                         void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, void *Yp, hipStream_t st)

@@ -514,23 +514,24 @@ void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *
     else launch_attn_gen_t<1>(D, A, O, Low, st);
 }
 
-// Pooling, region-level projections, A^r rows and top-k on their own.
+// Pooling, region-level projections, A^r rows and top-k on their own, for regions of more than one token.
+int route_pooled(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideWs &w, int32_t *Ir, float *Ar_opt, hipStream_t st)
+{
+    launch_pool(D, X, w, GemmRows{}, st);
+    const int rc = gemm_regions(region_job(D, w), Wqkv, 3 * D.C, D.C, K_MFMA_ROUTE_ROWS, st);
+    return rc == BRA_OK ? route_rows(D, w.qr, w.kr, D.C, Ir, Ar_opt, st) : rc;
+}
+
 int route_steps(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideWs &w, int32_t *Ir, float *Ar_opt,
                 hipStream_t st)
 {
-    int rc;
-    if (D.n == 1) {
-        // one token per region: the means are the (bf16) tokens themselves, so Q^r | K^r is the plain projection of X
-        // with float32 results: no pooling, no split.  The same product as in wide_forward (a sum's order does not
-        // depend on the tile), so that both decide on the same bits
-        rc = gemm(X, Wqkv, 3 * D.C, (long)D.B * D.R, D.C, 2 * D.C, GemmOut{{w.q, w.k, nullptr}, D.C, {w.qr, w.kr}, nullptr, nullptr, 0}, nullptr,
-                  K_MFMA_ROUTE_ROWS, st);
-    } else {
-        launch_pool(D, X, w, GemmRows{}, st);
-        rc = gemm_regions(region_job(D, w), Wqkv, 3 * D.C, D.C, K_MFMA_ROUTE_ROWS, st);
-    }
-    if (rc != BRA_OK) return rc;
-    return route_rows(D, w.qr, w.kr, D.C, Ir, Ar_opt, st);
+    if (D.n > 1) return route_pooled(D, X, Wqkv, w, Ir, Ar_opt, st);
+    // one token per region: the means are the (bf16) tokens themselves, so Q^r | K^r is the plain projection of X
+    // with float32 results: no pooling, no split.  The same product as in wide_forward (a sum's order does not
+    // depend on the tile), so that both decide on the same bits
+    const int rc = gemm(X, Wqkv, 3 * D.C, (long)D.B * D.R, D.C, 2 * D.C, GemmOut{{w.q, w.k, nullptr}, D.C, {w.qr, w.kr}, nullptr, nullptr, 0}, nullptr,
+                        K_MFMA_ROUTE_ROWS, st);
+    return rc == BRA_OK ? route_rows(D, w.qr, w.kr, D.C, Ir, Ar_opt, st) : rc;
 }
 
 }  // namespace
@@ -552,6 +553,18 @@ int wide_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, floa
 {
     const WideWs w = carve(D, ws);
     return route_steps(D, (const bf16_t *)X, (const bf16_t *)Wqkv, w, Ir, Ar_opt, st);
+}
+
+size_t wide_means_bytes(const Dims &D) { return 3 * align256((size_t)D.B * D.R * D.C * 4); }
+
+int wide_route_pooled(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *means, hipStream_t st)
+{
+    const size_t each = wide_means_bytes(D) / 3;
+    WideWs w = {};
+    w.xr = (float *)means;
+    w.qr = (float *)((char *)means + each);
+    w.kr = (float *)((char *)means + 2 * each);
+    return route_pooled(D, (const bf16_t *)X, (const bf16_t *)Wqkv, w, Ir, Ar_opt, st);
 }
 
 // H, W: the caller's map where D describes a zero-padded one (0: it does not): the products and the pooling read tokens

@@ -22,6 +22,15 @@ SHAPES = [  # (B, H, W, C, heads, S, k)
     (48, 7, 7, 192, 6, 7, 3),        # 288 pairs, 192 workgroups of the routing
     (1, 64, 64, 64, 2, 16, 4),       # 256 regions of 16 tokens
     (1, 72, 72, 128, 4, 9, 2),       # 81 of 64
+    (5, 128, 128, 64, 2, 16, 4),     # 256 of 64, 5 x 2^20 values
+    (6, 128, 128, 64, 2, 16, 4),     # above: the layer kernels behind the general pipeline's routing
+    (9, 72, 144, 64, 2, 9, 2),       # 81 of 128
+    (10, 64, 64, 128, 4, 16, 5),
+    (11, 64, 64, 128, 4, 16, 5),
+    (3, 128, 128, 128, 4, 32, 4),    # 1024 of 16
+    (56, 64, 64, 64, 2, 16, 4),      # 14 x 2^20
+    (57, 64, 64, 64, 2, 16, 4),
+    (15, 64, 64, 256, 8, 16, 2),
 ]
 
 
@@ -32,3 +41,15 @@ def test_lines(B, H, W, C, heads, S, k):
     Xd, Wd, Wod, Wld = (to_device(a, "bf16") for a in (X, Wqkv, Wo, Wlce))
     Y, Ir = bra.bra_forward(Xd, Wd, Wod, Wld, S, k, heads, want_Ir=True, path="mfma")
     assert torch.equal(Ir, bra.bra_route(Xd, Wd, S, k, heads, path="mfma"))
+
+
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", [(7, 127, 126, 64, 2, 16, 4), (12, 63, 60, 128, 4, 16, 4)])
+def test_padded_maps_of_many_regions(B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = (to_device(a, "bf16") for a in make_inputs(B, H, W, C, seed=9560, dtype="bf16"))
+    Y, Ir = bra.bra_forward_padded(X, Wqkv, Wo, Wlce, S, k, heads, want_Ir=True)
+    whole = torch.zeros(B, -(-H // S) * S, -(-W // S) * S, C, dtype=X.dtype, device=X.device)
+    whole[:, :H, :W] = X
+    Y2, Ir2 = bra.bra_forward(whole, Wqkv, Wo, Wlce, S, k, heads, want_Ir=True)
+    assert torch.equal(Ir, Ir2)
+    # two results with three independent roundings each: sqrt(2) x 2.9e-3 apart
+    assert float((Y.double() - Y2[:, :H, :W].double()).norm() / Y2[:, :H, :W].double().norm()) < 5e-3
