@@ -105,12 +105,14 @@ int bra_forward(const bra_shape *shape, const void *X, const void *Wqkv, const v
 
 /* bra_forward for callers that cannot allocate device memory or hand over a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid allocation.  Same
- * arguments and results as bra_forward (bit for bit: the same kernels run), but the scratch
- * memory is a buffer of BRA_STATIC_SCRATCH_BYTES inside the library's code object; every GPU the
- * library runs on holds one such buffer from the time the library is loaded there until the
- * process ends.  The call allocates and frees nothing.  The first call on each device looks up
+ * arguments and results as bra_forward (bit for bit: the same kernels run; where S > 8 and the
+ * pipeline that bra_forward takes does not fit the buffer, but one with a map less of scratch does,
+ * that one runs: the same index, results to the same precision), but the scratch memory is a
+ * buffer of BRA_STATIC_SCRATCH_BYTES inside the library's code object; every GPU the library
+ * runs on holds one such buffer from the time the library is loaded there until the process
+ * ends.  The call allocates and frees nothing.  The first call on each device looks up
  * the buffer's address (hipGetSymbolAddress; no allocation, but not to be captured into a
- * graph); later calls only enqueue kernels.  Shapes whose workspace (bra_workspace_bytes)
+ * graph); later calls only enqueue kernels.  Other shapes whose workspace (bra_workspace_bytes)
  * exceeds the buffer are rejected with BRA_ERR_TOO_LARGE before anything is enqueued; the
  * other errors are those of bra_forward.  The buffer keeps the previous call's contents (no
  * kernel of the forward pass needs it zeroed).  All calls on one GPU share it: calls that may

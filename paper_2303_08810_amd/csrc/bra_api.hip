@@ -140,7 +140,9 @@ int bra_forward_static(const bra_shape *shape, const void *X, const void *Wqkv, 
     if (!X || !Wqkv || !Wo || !Wlce || !Y) return BRA_ERR_NULL;
     int path = pick_path(shape, D);
     if (path < 0) return path;
-    const size_t need = (path == BRA_PATH_MFMA) ? mfma_workspace_bytes(D) : generic_workspace_bytes(D);
+    size_t need = (path == BRA_PATH_MFMA) ? mfma_workspace_bytes(D) : generic_workspace_bytes(D);
+    const bool compact = path == BRA_PATH_MFMA && need > (size_t)BRA_STATIC_SCRATCH_BYTES;
+    if (compact) need = mfma_compact_workspace_bytes(D);
     if (need > (size_t)BRA_STATIC_SCRATCH_BYTES) return BRA_ERR_TOO_LARGE;
     void *ws = nullptr;
     rc = static_scratch(&ws);
@@ -149,7 +151,7 @@ int bra_forward_static(const bra_shape *shape, const void *X, const void *Wqkv, 
     // no kernel of the forward pass expects zeroed scratch (no counters, no accumulation into it):
     // every buffer carved from it is written before it is read within the call
     if (path == BRA_PATH_MFMA)
-        return mfma_forward(D, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, ws, st);
+        return mfma_forward(D, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, ws, st, compact);
     return generic_forward(D, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, ws, st);
 }
 

@@ -120,7 +120,9 @@ size_t mfma_workspace_bytes(const Dims &D);
 int mfma_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *ws,
                hipStream_t st);
 int mfma_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo, const void *Wlce,
-                 void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st);
+                 void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st, bool compact = false);
+// What mfma_forward needs with `compact`: the pipeline with the least scratch instead of the fastest.
+size_t mfma_compact_workspace_bytes(const Dims &D);
 
 // Whether the pipeline for the padded shape takes the caller's H x W map itself, and that pipeline.
 // Yp: scratch of the padded map's size.

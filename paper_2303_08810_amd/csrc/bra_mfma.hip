@@ -1891,18 +1891,19 @@ static bool far_pays(const Dims &D)
 {
     const long values = (long)D.B * D.N * D.C;
     if (attn_big_ok(D)) return D.C == 64 && values > 5L << 20;
-    return D.n == 16 && small_supported(D) && !small_needs_projection(D) && values > (D.C == 128 ? 5L : 14L) << 20;
+    return values > (D.C == 128 ? 5L : 14L) << 20;
 }
 
-// Shapes of the kernels specialised by channel count.
-static bool specialised(const Dims &D)
+// Shapes of the kernels specialised by channel count.  compact: wherever they need less scratch than the general pipeline.
+static bool specialised(const Dims &D, bool compact = false)
 {
     static const bool general_only = experiment_flag("BRA_GENERAL_PIPELINE");
     if (general_only) return false;
     if (D.dtype != BRA_BF16 || D.d != 32) return false;
     if (D.C != 64 && D.C != 128 && D.C != 256) return false;
     if ((long)D.B * D.R * (D.n / 64 + 1) + 8 > 0x7fffffffL) return false;
-    if (far_routing(D)) return wide_supported(D) && far_pays(D);
+    if (far_routing(D))
+        return wide_supported(D) && (attn_big_ok(D) || (D.n == 16 && small_supported(D) && !small_needs_projection(D))) && (compact || far_pays(D));
     // Regions of fewer than 16 tokens: the image-resident attention needs a (image, head) pair per compute unit, and the
     // projection with the pooling in it many tokens.  Here / there (us): 14 x 14 x 256, k = 16: B = 24 43.5 / 38.2, 64 49.6 /
     // 69.2; 14 x 28 x 256, k = 1: 6 41.3 / 27.1, 24 58.8 / 41.4, 64 78.5 / 77.7; 14 x 14 x 128, k = 16: 24 35.5 / 27.2, 64 38.1 / 41.0;
@@ -1936,6 +1937,8 @@ size_t mfma_workspace_bytes(const Dims &D)
     return wide_shape(D) ? wide_workspace_bytes(D) : carve(D, nullptr).bytes;
 }
 
+size_t mfma_compact_workspace_bytes(const Dims &D) { return specialised(D, true) ? carve(D, nullptr).bytes : wide_workspace_bytes(D); }
+
 int mfma_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *ws,
                hipStream_t st)
 {
@@ -1951,9 +1954,9 @@ int mfma_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, floa
 }
 
 int mfma_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo, const void *Wlce,
-                 void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st)
+                 void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st, bool compact)
 {
-    if (wide_shape(D)) return wide_forward(D, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, ws, st);
+    if (!specialised(D, compact)) return wide_forward(D, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, ws, st);
     MfmaWs w = carve(D, ws);
     const bf16_t *x = (const bf16_t *)X, *wq = (const bf16_t *)Wqkv, *wo = (const bf16_t *)Wo,
                  *wl = (const bf16_t *)Wlce;

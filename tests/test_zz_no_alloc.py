@@ -52,3 +52,17 @@ def test_static_scratch_forced_routing_and_limit():
     with pytest.raises(bra.BraError) as e:
         bra.bra_forward_static(X, *W, cfg.S, cfg.k, cfg.heads, out=torch.empty_like(X))
     assert e.value.code == -8
+
+
+# Layers whose fastest pipeline does not fit the buffer and whose other one does, by its scratch of three maps instead of four
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", [
+    (1, 256, 256, 64, 2, 16, 1), (2, 128, 128, 128, 4, 16, 2), (9, 64, 64, 128, 4, 16, 4), (17, 64, 64, 64, 2, 16, 4), (4, 64, 64, 256, 8, 16, 2)])
+def test_static_scratch_of_the_smaller_pipeline(B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = (to_device(a, "bf16") for a in make_inputs(B, H, W, C, seed=98, dtype="bf16"))
+    assert bra.workspace_bytes(bra.make_shape(B, H, W, C, heads, S, k, torch.bfloat16)) > bra.STATIC_SCRATCH_BYTES
+    Y0, I0 = bra.bra_forward(X, Wqkv, Wo, Wlce, S, k, heads, want_Ir=True)
+    Y1, I1 = torch.full_like(X, 7.0), torch.full((B, S * S, k), -1, dtype=torch.int32, device=X.device)
+    bra.bra_forward_static(X, Wqkv, Wo, Wlce, S, k, heads, out=Y1, Ir_out=I1)
+    assert torch.equal(I1, I0)
+    # two results with three independent roundings each: sqrt(2) x 2.9e-3 apart
+    assert float((Y1.double() - Y0.double()).norm() / Y0.double().norm()) < 5e-3
