@@ -691,6 +691,7 @@ bool wide_shape(const Dims &D);          // not one of the specialised channel c
 bool layer_rounds_once(const Dims &D);   // a kernel outside this pipeline takes the shape and adds the LCE in float32
 bool wide_supported(const Dims &D);
 size_t wide_workspace_bytes(const Dims &D);
+bool convolution_in_front(const Dims &D);     // of the attention, in float32; else behind it
 int wide_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *ws,
                hipStream_t st);
 // Its routing steps alone, for regions of more than one token; means: scratch of wide_means_bytes(D).

@@ -805,22 +805,29 @@ static int launch_small_c(const Dims &D, const AttnArgs &A0, bf16_t *O, hipStrea
 }
 
 // Any C that is a multiple of 64: regions of up to 8 tokens on a map that fits the image-resident attention, where that is
-// faster than a wavefront per region and 64 channels (k_attn_rows) with the convolution beside the routing: with an
-// (image, head) pair per compute unit or more, and either many blocks of 32 keys for those wavefronts or so many workgroups
-// of the routing that the convolution is not hidden beside them.  Layer, image-resident / by regions (us): 6 x 14 x 14 x 512,
-// k = 8: 48.8 / 35.6; 24 x 14 x 14 x 192, k = 1: 37.4 / 27.9; 24 x 14 x 14 x 512, k = 8: 61.2 / 54.8; 24 x 7 x 7 x 768, k = 1: 47.8 / 46.0;
-// 16 x 7 x 7 x 512, k = 49: 35.5 / 38.6; 16 x 14 x 14 x 768, k = 49: 88.8 / 93.1; 32 x 8 x 8 x 768, k = 12: 61.5 / 68.8; 64 x 7 x 7 x
-// 128, k = 16: 25.3 / 27.4.  Regions of 8 tokens take twice the passes and want three rounds of pairs: 6 x 14 x 28 x 512,
-// k = 1: 62.5 / 36.5; 24 x 14 x 28 x 768, k = 8: 136.7 / 130.1; 24 x 14 x 28 x 384, k = 45: 107.8 / 86.7; 64 x 14 x 28 x 384, k = 4: 132.8 / 122.2,
-// k = 20: 156.6 / 156.3, but 63 images, k = 45: 190.6 / 198.7; 64 x 14 x 28 x 512, k = 16: 197 / 204; 32 x 16 x 32 x 768, k = 49: 291 / 296.
+// faster than a wavefront per region and 64 channels (k_attn_rows) with the convolution beside the routing.  It wants an
+// (image, head) pair per compute unit, and pays where those wavefronts take more than one block of 32 keys, with two pairs per
+// compute unit, or where the routing fills the chip by itself (256 workgroups), so that the convolution is not hidden beside it.
+// Layer, image-resident / by regions (us): 24 x 14 x 14 x 512 (384 pairs), 32 keys 61.8 / 57.0, 64 keys 62.3 / 65.6; 16 x 14 x 14 x 768
+// (384), 16 keys 70.0 / 67.2, 64 keys 71.6 / 76.0; 48 x 14 x 14 x 192 (288), 16 keys 46.6 / 41.6, 64 keys 48.2 / 48.4; 16 x 7 x 7 x 512, 49 keys
+// 35.6 / 39.2; 30 x 8 x 8 x 640 (600), 14 keys 53.4 / 56.8; 64 x 14 x 14 x 384 (768), 4 keys 78.6 / 85.2; 64 x 7 x 7 x 128, 16 keys 25.1 / 28.1.
+// Regions of 8 tokens take twice the passes: not with a single block of keys (64 x 14 x 28 x 384, k = 4 132 / 125), and with as many
+// pairs as give every workgroup one to itself, in rounds that are full where a compute unit holds one: pairs / 256 = 2.0
+// 32 x 14 x 28 x 512, k = 16 111.7 / 115.7, 2.02 43 x 14 x 28 x 384, k = 16 116.5 / 109.1, 2.6 28 x 14 x 28 x 768, k = 8 158.7 / 161.2,
+// 2.7 58 x 28 x 14 x 384, k = 11 136.6 / 132.3, 3.5 45 x 14 x 28 x 640, k = 41 262 / 254, 3.8 40 x 14 x 28 x 768, k = 16 234 / 236, 3.0 32 x 14 x 28 x 768, k = 16 186 / 195, 1.1 24 x 14 x 28 x 384, k = 45 109 / 88; two per compute
+// unit: 73 x 20 x 10 x 768, k = 14 202 / 231, 64 x 10 x 20 x 512, k = 8 97 / 108.  Where there is no room for its convolution, and it rounds O twice,
+// only beyond the size up to which the other pipeline rounds it once, and with four pairs per compute unit (67 x 12 x 24 x 512, k = 18 164 / 171;
+// 64 x 16 x 32 x 512, k = 16 257 / 269, but 46 x 32 x 16 x 512, k = 10 197.8 / 193.4).
 bool map_tail_pays(const Dims &D)
 {
     if (D.C % 64 != 0 || D.d != 32) return false;
-    const long pairs = (long)D.B * (D.C / 32);
-    if (D.n > 8 || (D.n & (D.n - 1)) != 0 || D.W > 64 || pairs < 256) return false;
-    const long blocks = (long)D.B * D.R * (D.C / 64) * ((D.kn + 31) / 32), routing = (long)D.B * ((D.R + 15) / 16);
-    if (D.n == 8) return pairs >= 720 && blocks >= 96000 && map_attention(D);
-    return (blocks >= 12000 || routing >= 192) && map_attention(D);
+    const long pairs = (long)D.B * (D.C / 32), routing = (long)D.B * ((D.R + 15) / 16);
+    if (D.n > 8 || (D.n & (D.n - 1)) != 0 || D.W > 64 || pairs < 256 || !map_attention(D)) return false;
+    if (D.n <= 4) return D.kn > 32 || pairs >= 512 || routing >= 256;
+    if (D.kn <= 32) return false;
+    if (!map_adds_lce(D)) return pairs >= 1024 && !convolution_in_front(D);
+    const bool two = map_smem(D, true) <= (size_t)kMaxLds / 2;
+    return pairs >= 512 && (two || 16 * pairs >= 15 * ((pairs + 255) / 256 * 256));
 }
 
 bool map_tail_rounds_once(const Dims &D)

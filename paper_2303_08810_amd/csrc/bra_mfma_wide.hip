@@ -546,6 +546,20 @@ bool wide_supported(const Dims &D)
     return true;
 }
 
+// LCE(V) in front, to which the attention adds itself: what the convolution needs is there as soon as the
+// routing's input is, and the routing leaves most of the chip idle.  It is kept in float32: rounded to bf16 it put 7 to 9 %
+// on the layer's error from float64, now 3 to 4 % below that of the convolution added to a rounded attention.  Beyond 9
+// million values, or 6 where the routing's rows are short, its 4 bytes more per value cost more (layer, us, added at the end / in front: 1 x 32 x 32 x 768, k = 12
+// 52.2 / 47.4, 8 x 32 x 32 x 768 116.2 / 110.8, 2 x 200 x 300 x 64, S = 16 118.6 / 116.3, 4 x 128 x 128 x 128 91.5 / 91.5;
+// 12 x 56 x 56 x 256 104 / 107, 28 x 56 x 56 x 192 141 / 151, 16 x 64 x 64 x 384 244 / 274;
+// 24 x 14 x 28 x 768, k = 8 132.5 / 130, but 64 x 42 x 42 x 64, k = 4 76.0 / 77.8, 64 x 21 x 21 x 256 95.5 / 97.5; 20 x 42 x 42 x 128 59.4 / 57.8).
+// At any size where other kernels take the shape that round O once: with the convolution behind, O is rounded twice, 3.3e-3
+// from float64 for 2.87e-3 where the convolution is a third of the attention (5 x 128 x 128 x 128, S = 16, k = 1, equal scores).
+bool convolution_in_front(const Dims &D)
+{
+    return (long)D.B * D.N * D.C <= (D.R * D.C >= 14 << 10 ? 9L : 6L) << 20 || layer_rounds_once(D);
+}
+
 size_t wide_workspace_bytes(const Dims &D) { return carve(D, nullptr).bytes; }
 
 int wide_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *ws,
@@ -593,16 +607,7 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     AttnArgs A = {};
     bool adds = false;
     const bool map_tail = map_tail_pays(D);      // forms the LCE itself
-    if (!map_tail && (M * D.C <= (D.R * D.C >= 14 << 10 ? 9L : 6L) << 20 || layer_rounds_once(D))) {
-        // LCE(V) in front, to which the attention adds itself: what the convolution needs is there as soon as the
-        // routing's input is, and the routing leaves most of the chip idle.  It is kept in float32: rounded to bf16 it put 7 to 9 %
-        // on the layer's error from float64, now 3 to 4 % below that of the convolution added to a rounded attention.  Beyond 9
-        // million values, or 6 where the routing's rows are short, its 4 bytes more per value cost more (layer, us, added at the end / in front: 1 x 32 x 32 x 768, k = 12
-        // 52.2 / 47.4, 8 x 32 x 32 x 768 116.2 / 110.8, 2 x 200 x 300 x 64, S = 16 118.6 / 116.3, 4 x 128 x 128 x 128 91.5 / 91.5;
-        // 12 x 56 x 56 x 256 104 / 107, 28 x 56 x 56 x 192 141 / 151, 16 x 64 x 64 x 384 244 / 274;
-        // 24 x 14 x 28 x 768, k = 8 132.5 / 130, but 64 x 42 x 42 x 64, k = 4 76.0 / 77.8, 64 x 21 x 21 x 256 95.5 / 97.5; 20 x 42 x 42 x 128 59.4 / 57.8).
-        // At any size where other kernels take the shape that round O once: with the convolution behind, O is rounded twice, 3.3e-3
-        // from float64 for 2.87e-3 where the convolution is a third of the attention (5 x 128 x 128 x 128, S = 16, k = 1, equal scores).
+    if (!map_tail && convolution_in_front(D)) {
         rc = lce::route_rows_lce_bf16(D, route ? w.qr : nullptr, w.kr, Ir_dst, w.v, (const bf16_t *)Wlce, w.o, low, st);
         if (rc != BRA_OK && rc != BRA_ERR_UNSUPPORTED) return rc;
         adds = rc == BRA_OK;

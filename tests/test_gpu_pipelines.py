@@ -31,6 +31,14 @@ SHAPES = [  # (B, H, W, C, heads, S, k)
     (56, 64, 64, 64, 2, 16, 4),      # 14 x 2^20
     (57, 64, 64, 64, 2, 16, 4),
     (15, 64, 64, 256, 8, 16, 2),
+    (16, 14, 14, 512, 16, 7, 9),     # 4 tokens, 36 keys, 256 pairs
+    (12, 10, 10, 768, 24, 5, 9),     # 288
+    (31, 14, 28, 512, 16, 7, 5),     # 8 tokens, 40 keys: 496 pairs, 512 and 528, two rounds and a little more
+    (32, 14, 28, 512, 16, 7, 5),
+    (33, 14, 28, 512, 16, 7, 5),
+    (32, 10, 20, 512, 16, 5, 5),     # two workgroups per compute unit
+    (64, 12, 24, 512, 16, 6, 12),    # no room for the convolution: 9 x 2^20 values
+    (65, 12, 24, 512, 16, 6, 12),
 ]
 
 
