@@ -411,14 +411,21 @@ enum Tile { kOneChunk, kWide, kMid, kNarrow };
 // Nout1: columns of a second product over the same rows.  others: workgroups of a region-level product in the launch, each as
 // long as a 64 x 128 tile (32 x 16 x 16 x 768, 768 of them: 64 x 128 tiles, a layer in 129.7 us, for 128 x 128, 133.6; 8 x 32 x 32 x 768,
 // 192 of them: 128 x 128, 107.2, for 64 x 128, 109.8).
+// Weights that an XCD's 4 MB L2 does not hold come in again for every row tile: a tenth more for tiles of 64 rows, from 40 of them on
+// (4900 x 1024 x 3072 with its regions 66.6 / 77.8 / 87.8, 3920 x 1024 x 3072 52.9 / 58.6 / 66.1, 3920 x 1280 x 3840 80 / 106 / 112; but 4900 x
+// 3072 x 1024 52.5 / 49.0, and 1960 x 1024 x 3072 33.5 / 31.2).
+// Up to three chunks and one and a half wide tiles of columns: the wide tile's empty half is a quarter of a short product
+// (125440 x 192 x 192 25.3 / 26.3 / 23.8, 50176 13.4 / 13.6 / 12.4).
 Tile pick_tile(long M, int K, int Nout, int Nout1, long others)
 {
     if (K == 64) return kOneChunk;
+    if (K <= 192 && Nout > 128 && Nout + Nout1 <= 192) return kNarrow;
     auto cost = [&](int bm, int bn, long tile) {
         const long rounds = ((M + bm - 1) / bm * ((Nout + bn - 1) / bn + (Nout1 + bn - 1) / bn) + others * 433 / tile + 255) / 256;
         return tile * rounds * (rounds == 1 ? 13 : 10);
     };
-    const long wide = cost(128, 128, 744), mid = cost(64, 128, 433), narrow = cost(64, 64, 260);
+    const bool again = (long)K * Nout * 2 > 4L << 20 && M > 2560;
+    const long wide = cost(128, 128, 744), mid = cost(64, 128, again ? 476 : 433), narrow = cost(64, 64, again ? 286 : 260);
     return wide <= mid && wide <= narrow ? kWide : mid <= narrow ? kMid : kNarrow;
 }
 

@@ -16,6 +16,8 @@ EDGES = [  # (B, H, W, C, heads, S, k)
     (23, 14, 14, 320, 10, 7, 3),     # the same with region rows
     (3, 14, 14, 192, 6, 7, 4),       # 64 x 64 tiles
     (1, 3, 3, 64, 1, 3, 2),          # 9 rows, one chunk
+    (25, 14, 14, 1024, 32, 7, 3),    # weights of 6 MB, 4900 rows, with region rows
+    (20, 14, 14, 192, 6, 7, 3),      # W^o: 3920 rows of one and a half tiles of columns
 ]
 
 
