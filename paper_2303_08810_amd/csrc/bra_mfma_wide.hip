@@ -103,15 +103,15 @@ struct Added {
 // issue in 73 % of the cycles and the matrix cores work in 25 %.  Of 5.2 vector instructions per score 2.5 are its 2^x,
 // its addition to the denominator and half a conversion; with maxima instead of additions and denominators from a product
 // it took 68 us.  One query tile per wavefront instead of two: 74 us (4 x 64 x 64 x 384, heads of 64, k = 4: 45 for 39).
-template <int HD, int NQ>
-__global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, int walks, const bf16_t *__restrict__ Low)
+template <int HD, int NQ, bool WALK>
+__global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, const bf16_t *__restrict__ Low)
 {
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16;
     __shared__ __attribute__((aligned(16))) bf16_t K0[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t K1[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t V0[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t V1[64 * 64];
-    extern __shared__ int origins[];             // [k]: first token of the routed regions; with `walks` [n]: tokens of a region's slots
+    extern __shared__ int origins[];             // [k]: first token of the routed regions; with WALK [n]: tokens of a region's slots
     const int C = D.C, ncg = C / 64, n = D.n, kn = D.kn;
     const int cg = blockIdx.x % ncg, qt = (blockIdx.x / ncg) % qtiles;
     const int reg = (blockIdx.x / (ncg * qtiles)) % D.R, b = blockIdx.x / (ncg * qtiles * D.R);
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
         if (report) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = j;
     }
     int *slots = origins + D.k;
-    if (walks)
+    if (WALK)
         for (int t = tid; t < n; t += 256) slots[t] = in_region(t);
     // the operands have arrived before the loop: otherwise the compiler waits for them, and with them for the direct loads
     // in flight, in every pass
@@ -159,14 +159,14 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
             for (int ks = 0; ks < KSD; ++ks) asm volatile("" : "+v"(qf[q][hh][ks]));
     // direct loads: a wavefront brings rows 16 w .. 16 w + 15 of K and V, 8 rows of 8 pieces each, block after block
     RowWalk<2> walk;
-    walk.start(16 * wave + lane / 8, 8, 64, n, n_inv);
+    if constexpr (WALK) walk.start(16 * wave + lane / 8, 8, 64, n, n_inv);
     const unsigned piece = 16 * ((lane % 8) ^ (lane / 8));
     auto request = [&](int k0, unsigned Ks, unsigned Vs) {
         lds_reads_done();
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const unsigned at = 1024 * (2 * wave + u);
-            if (walks) {
+            if constexpr (WALK) {
                 const unsigned off = row_offset(walk.token(u, origins, D.k - 1, slots), C, piece);
                 load_to_lds_untracked(A.K + img, off, Ks + at);
                 load_to_lds_untracked(A.V + img, off, Vs + at);
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
                 load_to_lds_untracked(A.V + e, Vs + at);
             }
         }
-        walk.advance();
+        if constexpr (WALK) walk.advance();
     };
     float m[NQ][HPW], l[NQ][HPW];
     f32x4 acc[NQ][HPW][NDT];
@@ -493,15 +493,25 @@ int launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *
     return D.n <= 16 ? launch_attn_rows_t<64, 1>(D, A, O, Low, st) : launch_attn_rows_t<64, 2>(D, A, O, Low, st);
 }
 
-template <int NQ>
-void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
+template <int HD, int NQ, bool WALK>
+void launch_attn_gen_w(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
 {
     const int qtiles = (D.n + 64 * NQ - 1) / (64 * NQ);
     const dim3 grid((unsigned)((long)D.B * D.R * qtiles * (D.C / 64)));
-    const int walks = walk_ok(D);
-    const size_t smem = (size_t)(D.k + (walks ? D.n : 0)) * sizeof(int);
-    if (D.d == 32) hipLaunchKernelGGL((k_attn_gen<32, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks, Low);
-    else hipLaunchKernelGGL((k_attn_gen<64, NQ>), grid, dim3(256), smem, st, A, O, D, qtiles, walks, Low);
+    const size_t smem = (size_t)(D.k + (WALK ? D.n : 0)) * sizeof(int);
+    hipLaunchKernelGGL((k_attn_gen<HD, NQ, WALK>), grid, dim3(256), smem, st, A, O, D, qtiles, Low);
+}
+
+// Rows by walking (a table of the region's tokens more, an addition instead of divisions) from more than three blocks of keys on;
+// a kernel of its own for each: both ways in one take 125 registers instead of 118 and 120 (one query tile, heads of 32).  Layer,
+// both in one / by divisions / by walking (us): 40 x 56 x 56 x 192, k = 1 (one block) 176.6 / 174.0 / 174.5; 30 x 42 x 42 x 192, k = 5 (180 keys)
+// 114.8 / 110.3 / 113.1; 20 x 77 x 77 x 64, k = 2 (242) 73.9 / 74.4 / 73.7; 2 x 200 x 300 x 64, S = 16, k = 4 (988) 115.8 / 115.1 / 114.2.
+template <int NQ>
+void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
+{
+    const bool walks = walk_ok(D) && D.kn > 192;
+    if (D.d == 32) walks ? launch_attn_gen_w<32, NQ, true>(D, A, O, Low, st) : launch_attn_gen_w<32, NQ, false>(D, A, O, Low, st);
+    else walks ? launch_attn_gen_w<64, NQ, true>(D, A, O, Low, st) : launch_attn_gen_w<64, NQ, false>(D, A, O, Low, st);
 }
 
 // Low: if not NULL, the output is added to what O and it hold (LCE(V)).

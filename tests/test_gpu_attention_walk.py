@@ -19,6 +19,8 @@ SHAPES = [  # (B, H, W, C, heads, S, k)
     (1, 82, 50, 64, 1, 2, 3),        # 1025, three regions
     (1, 32, 32, 64, 2, 2, 4),        # 256 slots, four wavefronts per tile in the gradients
     (1, 20, 52, 64, 1, 2, 2),        # 260
+    (2, 24, 24, 64, 1, 3, 3),        # 64 slots, 192 keys: divisions in the forward pass
+    (1, 15, 39, 192, 6, 3, 3),       # 65, 195 keys
 ]
 
 

@@ -50,6 +50,7 @@ TILES = [  # the kernel for larger regions: one and two query tiles per wavefron
     (1, 24, 28, 192, 6, 4, 5),       # n = 42, 210 keys
     (2, 16, 64, 64, 1, 2, 3),        # n = 256, heads of 64
     (64, 26, 38, 64, 2, 2, 4),       # n = 247: 128-query tiles, 988 keys (images 0 and 63 compared)
+    (11, 77, 77, 64, 2, 7, 1),       # n = 121: 128-query tiles, 121 keys, rows by divisions
     (1, 104, 152, 64, 2, 8, 4),      # n = 247: 256 of 256 queries in two 128-query tiles, 988 keys
 ]
 
