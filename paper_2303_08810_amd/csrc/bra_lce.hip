@@ -88,7 +88,8 @@ BackwardJobs backward_jobs(const Dims &D, const bf16_t *dO, const bf16_t *V, con
     L.grad.Low = dK;
     L.add = job(D, V, nullptr, Wlce, O, D.C, nullptr, kAddSlots);
     L.fit = offsets_fit(D, L.grad.T, lddv) && offsets_fit(D, L.add.T, D.C);
-    L.beside = L.fit && (long)D.B * D.N * D.C <= 14L << 20;
+    const long values = (long)D.B * D.N * D.C;
+    L.beside = L.fit && (values <= 14L << 20 || (D.n > 96 && D.C <= 128 && values <= 28L << 20));
     return L;
 }
 

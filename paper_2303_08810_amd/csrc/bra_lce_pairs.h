@@ -283,9 +283,14 @@ __device__ __forceinline__ void job_block(const Job &J, const Dims &D, int block
 
 // The two passes of the gradients: LCE^T(dO) with the tap gradients, added to dV or in float32 (lower halves where dK goes), and
 // O += LCE(V).  fit: walk_tile takes both.  beside: in the attention's launches.  The float32 sums are 4 bytes per value more to
-// write and to read, which beyond 14 million values costs more than the launches saved (whole gradient, us, of their own / beside:
-// 16 x 56 x 56 x 64, k = 1 87.6 / 77.9, 8 x 56 x 56 x 256, k = 4 199.6 / 186.2, 64 x 56 x 56 x 64 207 / 209, 16 x 112 x 120 x 64 309 / 297;
-// 24 x 56 x 56 x 256 533 / 541, 100 x 56 x 56 x 64 337 / 366).
+// write and to read, which costs more than the launches saved where the attention has little to do meanwhile: few keys and
+// small regions, or rows of many channels.  Beyond 14 million values they are beside only for regions of more than 96 tokens and up to 128
+// channels; up to 14 million always, also where that is slower, because what they are added to is then rounded once (dX of 8 x
+// 56 x 56 x 64 3.69e-3 from float64 instead of 3.71e-3).  Whole gradient, us, of their own / beside, by millions of values:
+// 64 tokens per region, 56 x 56 x 64, k = 1: 3.1 87.6 / 77.9, 9.2 169 / 175, 12.3 207 / 208, 13.8 232 / 242, 19 336 / 364, k = 4: 12.3
+// 269 / 260, 13.8 298 / 296, 19 419 / 426; 56 x 56 x 256, k = 4: 6.1 199.6 / 186.2, 13.8 402 / 409, 18 531 / 537; 16 tokens, 28 x 28 x 256, k = 4:
+// 7.7 206 / 202, 15 382 / 393.  81 tokens, 64 channels: 15.5 365 / 366; 100: 14.4 291 / 282; 121: 14.5 280 / 268, 17 504 / 495, 128 channels 17
+// 376 / 375, 256: 17 437 / 449; 256 tokens, 64 channels, k = 1: 15 344 / 322, 24.5 532 / 525, 37 772 / 781, 128: 17 419 / 401, 192: 23 590 / 597.
 struct BackwardJobs {
     Job grad, add;
     bool fit, beside;

@@ -1,5 +1,5 @@
 """The depth-wise convolution in front of what it is added to, as float32 halves in two maps, and behind it: GPU parity beyond
-the lines up to which it runs in front (6 or 9 x 2^20 values in the forward, 14 x 2^20 in the gradients; other files hold the sizes
+the lines up to which it runs in front (6 or 9 x 2^20 values in the forward, 14 x 2^20 and more in the gradients; other files hold the sizes
 below), and the number of roundings where it does, and where a kernel with the convolution in it takes the shape, at any size.  With taps so large that nothing else shows, Y carries those of V, O and Y
 and dX those of dO, dV and dX.  A rounding to bf16 is 1.66e-3 rms of a spread of values: three of them 2.87e-3, four (the
 convolution rounded before it is added to) 3.3e-3; the bound lies between."""
@@ -84,6 +84,7 @@ def test_convolution_behind_attention(B, H, W, C, heads, S, k):
     compare(X, Wqkv, Wo, Wlce, "bf16", S, k, heads, "mfma")
 
 
-def test_convolution_behind_gradients():
-    X, Wqkv, Wo, Wlce = make_inputs(75, 56, 56, 64, seed=9951, dtype="bf16")       # 14.4 x 2^20
+@pytest.mark.parametrize("B,H,W", [(75, 56, 56), (19, 112, 112)])      # 14.4 x 2^20: behind; 14.6, 256 tokens per region: beside
+def test_convolution_of_large_gradients(B, H, W):
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, 64, seed=9951, dtype="bf16")
     compare_backward(X, Wqkv, Wo, Wlce, "bf16", 2, 7, 1, path="mfma")
