@@ -189,8 +189,8 @@ __global__ __launch_bounds__(256 * H) void k_bwd_proj(const bf16_t *__restrict__
 
 // Tiles of k_bwd_proj per workgroup: all workgroups resident at once, two per compute unit.  Two groups of wavefronts share a
 // workgroup (`halves`) from more than 256 tiles on.  Whole gradient with two groups and with one
-// (us, k = 1): 294 tiles 65.1 / 69.6, 392 70.9 / 75.5, 490 74.6 / 80.0, 3136 214 / 225; below the line 49 tiles 48.1 / 47.4,
-// but 98 52.0 / 52.4, 196 58.6 / 59.0, 256 86.0 / 87.5: a line between 50 and 98 tiles would gain up to 2 % there.
+// (us, k = 1): 294 tiles 53.9 / 58.4, 392 59.1 / 63.6, 490 65.5 / 70.8, 3136 207.0 / 216.5; below the line 49 tiles 32.5 / 31.8, 98 39.2 /
+// 39.4, 196 47.2 / 47.3, 256 (16 x 32 x 32 x 64) 39.6 / 41.9: a line between 200 and 256 tiles would gain up to 5 % there.
 struct ProjPlan {
     int tiles, per_wg, groups, halves;
 };
@@ -208,8 +208,8 @@ ProjPlan proj_plan(long M)
 
 // One pass over the gradient map at C = 64; wider layers take the plain product for dX and shares of the tokens for both weight
 // gradients: a workgroup that keeps all of dWqkv writes it once per compute unit, 50 MB of partial matrices at C = 128
-// and their second reading.  Whole gradient in one pass and so (us): 64 x 56 x 56 x 64, k = 1 192 / 213, 32 images 109 / 114,
-// 8 56.7 / 57.8, 4 45.8 / 43.9; 64 x 28 x 28 x 128, k = 4 160 / 139, 16 images 78.3 / 55.6, 4 47.1 / 35.7, 2 x 128 x 128 x 128,
+// and their second reading.  Whole gradient in one pass and so (us): 64 x 56 x 56 x 64, k = 1 207 / 221, 32 images 118.9 / 121.2,
+// 8 58.9 / 59.8, 4 47.2 / 46.6; 64 x 28 x 28 x 128, k = 4 160 / 139, 16 images 78.3 / 55.6, 4 47.1 / 35.7, 2 x 128 x 128 x 128,
 // S = 16 158 / 131, one image of 14 x 14 x 128 34.7 / 26.2.
 bool fused_projection(int C) { return C == 64; }
 

@@ -685,9 +685,8 @@ int launch_map_tail(const Dims &D, const mfma::AttnArgs &A, bf16_t *O, hipStream
 bool attn_q32_ok(const Dims &D);
 int launch_attn_q32(const Dims &D, const mfma::AttnArgs &A, hipStream_t st);
 
-// Pipeline for other channel counts (bra_mfma_wide.hip): any multiple of 64 with heads of 32
-// channels, at most 64 regions of 1, 2, 4 or 8 tokens.
-bool wide_shape(const Dims &D);          // not one of the specialised channel counts
+// General pipeline (bra_mfma_wide.hip): any C that is a multiple of 64, heads of 32 or 64 channels, any regions.
+bool wide_shape(const Dims &D);          // the specialised kernels do not take it
 bool layer_rounds_once(const Dims &D);   // a kernel outside this pipeline takes the shape and adds the LCE in float32
 bool wide_supported(const Dims &D);
 size_t wide_workspace_bytes(const Dims &D);

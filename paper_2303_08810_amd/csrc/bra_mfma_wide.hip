@@ -99,10 +99,10 @@ struct Added {
 // the other is worked on; 16-byte pieces are exchanged (piece c of row r at c ^ r % 8), so that K's row reads and V's
 // transposing reads meet different banks.  Queries past the end of the region and keys past k n
 // repeat the last one and are masked.
-// Bound by vector issue: 2 x 208 x 304 x 64, 16 x 16 regions, k = 4 (250 M scores) takes 66 us, in which the vector ALUs
-// issue in 73 % of the cycles and the matrix cores work in 25 %.  Of 5.2 vector instructions per score 2.5 are its 2^x,
-// its addition to the denominator and half a conversion; with maxima instead of additions and denominators from a product
-// it took 68 us.  One query tile per wavefront instead of two: 74 us (4 x 64 x 64 x 384, heads of 64, k = 4: 45 for 39).
+// Bound by vector issue: 2 x 208 x 304 x 64, 16 x 16 regions, k = 4 (250 M scores) takes 69 us, the convolution it is added to
+// with it, in which the vector ALUs issue in 68 % of the cycles and the matrix cores work in 24 %.  Of 5.0 vector instructions per score
+// 2.5 are its 2^x, its addition to the denominator and half a conversion; with maxima instead of additions and denominators from a
+// product it took 2 us more.  One query tile per wavefront instead of two: 8 us more (4 x 64 x 64 x 384, heads of 64, k = 4: 45 for 39).
 template <int HD, int NQ, bool WALK>
 __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, const bf16_t *__restrict__ Low)
 {
@@ -558,11 +558,13 @@ bool wide_supported(const Dims &D)
 
 // LCE(V) in front, to which the attention adds itself: what the convolution needs is there as soon as the
 // routing's input is, and the routing leaves most of the chip idle.  It is kept in float32: rounded to bf16 it put 7 to 9 %
-// on the layer's error from float64, now 3 to 4 % below that of the convolution added to a rounded attention.  Beyond 9
-// million values, or 6 where the routing's rows are short, its 4 bytes more per value cost more (layer, us, added at the end / in front: 1 x 32 x 32 x 768, k = 12
-// 52.2 / 47.4, 8 x 32 x 32 x 768 116.2 / 110.8, 2 x 200 x 300 x 64, S = 16 118.6 / 116.3, 4 x 128 x 128 x 128 91.5 / 91.5;
-// 12 x 56 x 56 x 256 104 / 107, 28 x 56 x 56 x 192 141 / 151, 16 x 64 x 64 x 384 244 / 274;
-// 24 x 14 x 28 x 768, k = 8 132.5 / 130, but 64 x 42 x 42 x 64, k = 4 76.0 / 77.8, 64 x 21 x 21 x 256 95.5 / 97.5; 20 x 42 x 42 x 128 59.4 / 57.8).
+// on the layer's error from float64, now 3 to 4 % below that of the convolution added to a rounded attention.  On large maps its
+// 4 bytes more per value cost more than that hides: beyond 9 million values, or 6 where the rows of the routing are short.  Between the
+// two 256 regions gain, 64 regions break even or lose up to 4 % and keep the better precision.  Layer, behind / in front (us), by millions
+// of values: 1 x 32 x 32 x 768, k = 12 52.2 / 47.4, 8 of them: 6 115 / 109, 10: 7.5 140 / 136; S = 16: 2 x 200 x 300 x 64 7.3 120 / 117, 1 x
+// 250 x 180 x 128 5.5 98 / 91; 20 x 28 x 28 x 512 7.7 107 / 106; 48 x 14 x 14 x 768 6.9 148.5 / 150; 24 x 28 x 28 x 384 6.9 89.5 / 90.6; 20 x 40
+// x 40 x 256, S = 8 7.8 92 / 96.  Short rows: 64 x 42 x 42 x 64, k = 4 6.9 76.3 / 78.6; 64 x 21 x 21 x 256 6.9 97 / 100; 48 x 28 x 28 x 192
+// 6.9 76.8 / 81.9; 28 x 49 x 49 x 64 4.1 59.4 / 57.7.  Beyond: 64 x 21 x 21 x 384 10.3 148 / 163; 16 x 64 x 64 x 384 24 244 / 274.
 // At any size where other kernels take the shape that round O once: with the convolution behind, O is rounded twice, 3.3e-3
 // from float64 for 2.87e-3 where the convolution is a third of the attention (5 x 128 x 128 x 128, S = 16, k = 1, equal scores).
 bool convolution_in_front(const Dims &D)

@@ -77,7 +77,7 @@ def test_one_rounding_beyond_the_lines(B, H, W, C, heads, S, k):
     (17, 56, 56, 192, 6, 7, 1),      # 9.8 x 2^20 values
     (30, 49, 49, 128, 4, 7, 1),      # 8.8, short rows in the routing
     (62, 14, 28, 512, 16, 7, 16),    # regions of 8 tokens by whole images
-    (61, 14, 28, 512, 16, 7, 16),    # and region by region
+    (58, 14, 28, 512, 16, 7, 16),    # and region by region, in front
 ])
 def test_convolution_behind_attention(B, H, W, C, heads, S, k):
     X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=9950, dtype="bf16")
