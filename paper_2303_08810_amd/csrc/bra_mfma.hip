@@ -1890,7 +1890,7 @@ bool attn_big_ok(const Dims &D)
 static bool far_pays(const Dims &D)
 {
     const long values = (long)D.B * D.N * D.C;
-    if (attn_big_ok(D)) return D.C == 64 && values > 5L << 20;
+    if (attn_big_ok(D)) return D.C == 64 && attn_q32_ok(D) && values > 5L << 20;
     return values > (D.C == 128 ? 5L : 14L) << 20;
 }
 

@@ -14,7 +14,7 @@
 //     its accumulator input: the scores leave the matrix cores as the arguments of 2^x;
 //   * the reference follows the running maximum lazily (only when a score exceeds it by 2^8),
 //     so a key block costs per score: half of a 3-way maximum, the 2^x, half a packed
-//     conversion; the softmax denominators come from a product with an all-ones operand;
+//     conversion; the softmax denominators come from a product with an all-ones operand (up to 64 regions per image);
 //   * key-block addresses come from a table built once per workgroup; K / V blocks of 64 routed
 //     tokens are copied by index into a two-stage LDS ring, three blocks ahead in registers, with
 //     waits that leave the later loads pending; one barrier per block.
@@ -101,7 +101,9 @@ __device__ __forceinline__ void lce_store(float *Ls, int rw, const float (&res)[
     }
 }
 
-template <int C, int KSPLIT>
+// F32_SUM: denominators are sums of the float32 weights, each lane its own, as in the general pipeline, which the layers of more than
+// 64 regions come from (16 x 128 x 128 x 64, S = 16, k = 4: 131.0 us with the product, 131.7 so; 4 x 256 x 256 x 64, k = 2: 155.0, 155.7).
+template <int C, int KSPLIT, bool F32_SUM>
 __global__ __launch_bounds__(4 * C * KSPLIT) __attribute__((amdgpu_waves_per_eu(2 * KSPLIT, 2 * KSPLIT)))
 void k_attn_q32(AttnArgs A, Dims D)
 {
@@ -233,7 +235,7 @@ void k_attn_q32(AttnArgs A, Dims D)
     lce_store<C, OS, NT, NTASK>((float *)Hs, D.rw, lce);
 
     // Online-softmax state of the two query tiles over this wavefront's share of the keys.
-    f32x4 acc[2][2], lacc[2], negm[2];
+    f32x4 acc[2][2], lacc[2], negm[2];         // F32_SUM: lacc[.][0] alone, this lane's share
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
         acc[qt][0] = acc[qt][1] = lacc[qt] = negm[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -287,6 +289,7 @@ void k_attn_q32(AttnArgs A, Dims D)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(s[qt][2 * tp + e / 4][e % 4]);
                 pb[qt][tp] = pack8(p);
+                if (F32_SUM) lacc[qt][0] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
             }
         }
 #pragma unroll
@@ -304,7 +307,7 @@ void k_attn_q32(AttnArgs A, Dims D)
             }
 #pragma unroll
             for (int qt = 0; qt < 2; ++qt)
-                lacc[qt] = mfma16(__builtin_bit_cast(bf16x8, ones), pb[qt][tp], lacc[qt]);   // sums of the rounded P
+                if (!F32_SUM) lacc[qt] = mfma16(__builtin_bit_cast(bf16x8, ones), pb[qt][tp], lacc[qt]);   // sums of the rounded P
         }
     };
 
@@ -351,6 +354,10 @@ void k_attn_q32(AttnArgs A, Dims D)
     // The ring is free (the loop ended with a barrier).  Two wavefronts that split the keys merge
     // their softmax states: the second hands over (reference, denominator, sums), the first
     // combines them against the larger reference.
+    if constexpr (F32_SUM) {
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) lacc[qt][0] = cross_row_sum(lacc[qt][0]);
+    }
     if constexpr (KSPLIT == 2) {
         float *Xs = (float *)(smem + SM::x_off) + ((size_t)pair * kWave + lane) * 20;
         if (ks == 1) {
@@ -440,19 +447,19 @@ size_t q32_smem(const Dims &D)
     return Q32Smem<C>::bytes((qh + 4) * (D.rw + 4), D.kn / 64);
 }
 
-template <int C, int KSPLIT>
+template <int C, int KSPLIT, bool F32_SUM>
 int launch_q32(const Dims &D, const AttnArgs &A, hipStream_t st)
 {
     static bool opted = false;
     if (!opted) {
-        if (hipFuncSetAttribute((const void *)k_attn_q32<C, KSPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute((const void *)k_attn_q32<C, KSPLIT, F32_SUM>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kMaxLds) != hipSuccess)
             return BRA_ERR_LAUNCH;
         opted = true;
     }
     const int grid = ((A.total + 7) / 8) * 8;
     ProfScope ps(st, K_MFMA_ATTENTION);
-    hipLaunchKernelGGL((k_attn_q32<C, KSPLIT>), dim3(grid), dim3(4 * C * KSPLIT), q32_smem<C>(D), st, A, D);
+    hipLaunchKernelGGL((k_attn_q32<C, KSPLIT, F32_SUM>), dim3(grid), dim3(4 * C * KSPLIT), q32_smem<C>(D), st, A, D);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -469,8 +476,9 @@ bool attn_q32_ok(const Dims &D)
 
 int launch_attn_q32(const Dims &D, const AttnArgs &A, hipStream_t st)
 {
-    if (D.C == 64) return experiment_flag("BRA_Q32_NOSPLIT") ? launch_q32<64, 1>(D, A, st) : launch_q32<64, 2>(D, A, st);
-    return launch_q32<128, 1>(D, A, st);
+    if (D.S > kFastRouteMaxS) return D.C == 64 ? launch_q32<64, 2, true>(D, A, st) : launch_q32<128, 1, true>(D, A, st);
+    if (D.C == 64) return experiment_flag("BRA_Q32_NOSPLIT") ? launch_q32<64, 1, false>(D, A, st) : launch_q32<64, 2, false>(D, A, st);
+    return launch_q32<128, 1, false>(D, A, st);
 }
 
 }  // namespace bra

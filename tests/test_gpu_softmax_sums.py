@@ -13,11 +13,11 @@ pytestmark = pytest.mark.gpu
 KEYS = 770
 
 
-def layer(B, rh, rw, S, C, heads, values):
+def layer(B, rh, rw, S, C, heads, values, keys=KEYS):
     """X, Wqkv, Wo, Wlce, routing: all queries attend the tokens of the first k regions, Q K^T is 0 for the image's first
     token and -log2(255) for the others (with scale ln 2 the exponent of 2), V is 1 on the first token or on the others."""
-    H, W, k, d = S * rh, S * rw, KEYS // (rh * rw), C // heads
-    assert k * rh * rw == KEYS and k <= S * S
+    H, W, k, d = S * rh, S * rw, keys // (rh * rw), C // heads
+    assert k * rh * rw == keys and k <= S * S
     X = torch.zeros(B, H, W, C, device="cuda")
     X[..., 0] = 1.0
     X[:, 0, 0, 0] = 0.0
@@ -40,6 +40,20 @@ def test_forward_denominators(B, rh, rw, S, C, heads):
     (X, Wqkv, Wo, Wlce), Ir, k = layer(B, rh, rw, S, C, heads, "first")
     Y = bra.bra_forward(X, Wqkv, Wo, Wlce, S, k, heads, Ir_in=Ir, scale=math.log(2.0), path="mfma")
     assert torch.equal(Y.float(), torch.full_like(Y.float(), 255 / 1024))
+
+
+# More than 64 regions of 64 tokens: by 64 queries on 5.1 x 2^20 values (also C = 128 where less scratch is asked for), and in the
+# general pipeline on fewer.  255 / 2302 is 226.86 units of the last place, with weights rounded to bf16 226.08
+@pytest.mark.parametrize("B,C,heads", [(16, 64, 2), (1, 64, 2), (7, 128, 4)])
+def test_forward_denominators_of_many_regions(B, C, heads):
+    (X, Wqkv, Wo, Wlce), Ir, k = layer(B, 8, 8, 9, C, heads, "first", keys=2048)
+    want = torch.tensor(255 / 2302).bfloat16().float().item()
+    Y = bra.bra_forward(X, Wqkv, Wo, Wlce, 9, k, heads, Ir_in=Ir, scale=math.log(2.0), path="mfma")
+    assert torch.equal(Y.float(), torch.full_like(Y.float(), want))
+    if bra.workspace_bytes(bra.make_shape(B, 72, 72, C, heads, 9, k, torch.bfloat16)) > bra.STATIC_SCRATCH_BYTES and C == 128:
+        Y = torch.empty_like(X)
+        bra.bra_forward_static(X, Wqkv, Wo, Wlce, 9, k, heads, out=Y, Ir_in=Ir, scale=math.log(2.0))
+        assert torch.equal(Y.float(), torch.full_like(Y.float(), want))
 
 
 # a wavefront per region (16 and 32 tokens), four wavefronts per tile, 64 and 128 tokens per workgroup
