@@ -811,6 +811,8 @@ static int launch_small_c(const Dims &D, const AttnArgs &A0, bf16_t *O, hipStrea
 // Layer, image-resident / by regions (us): 24 x 14 x 14 x 512 (384 pairs), 32 keys 61.8 / 57.0, 64 keys 62.3 / 65.6; 16 x 14 x 14 x 768
 // (384), 16 keys 70.0 / 67.2, 64 keys 71.6 / 76.0; 48 x 14 x 14 x 192 (288), 16 keys 46.6 / 41.6, 64 keys 48.2 / 48.4; 16 x 7 x 7 x 512, 49 keys
 // 35.6 / 39.2; 30 x 8 x 8 x 640 (600), 14 keys 53.4 / 56.8; 64 x 14 x 14 x 384 (768), 4 keys 78.6 / 85.2; 64 x 7 x 7 x 128, 16 keys 25.1 / 28.1.
+// 49 regions and more have the 12000 blocks of keys anyway; layers of fewer regions that do not have them stay with k_attn_rows, whose
+// denominators are sums of the float32 weights (k_attn_map4's are of the rounded ones).
 // Regions of 8 tokens take twice the passes: not with a single block of keys (64 x 14 x 28 x 384, k = 4 132 / 125), and with as many
 // pairs as give every workgroup one to itself, in rounds that are full where a compute unit holds one: pairs / 256 = 2.0
 // 32 x 14 x 28 x 512, k = 16 111.7 / 115.7, 2.02 43 x 14 x 28 x 384, k = 16 116.5 / 109.1, 2.6 28 x 14 x 28 x 768, k = 8 158.7 / 161.2,
@@ -823,7 +825,8 @@ bool map_tail_pays(const Dims &D)
     if (D.C % 64 != 0 || D.d != 32) return false;
     const long pairs = (long)D.B * (D.C / 32), routing = (long)D.B * ((D.R + 15) / 16);
     if (D.n > 8 || (D.n & (D.n - 1)) != 0 || D.W > 64 || pairs < 256 || !map_attention(D)) return false;
-    if (D.n <= 4) return D.kn > 32 || pairs >= 512 || routing >= 256;
+    const long blocks = (long)D.B * D.R * (D.C / 64) * ((D.kn + 31) / 32);
+    if (D.n <= 4) return routing >= 256 || (blocks >= 12000 && (D.kn > 32 || pairs >= 512));
     if (D.kn <= 32) return false;
     if (!map_adds_lce(D)) return pairs >= 1024 && !convolution_in_front(D);
     const bool two = map_smem(D, true) <= (size_t)kMaxLds / 2;
