@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kRouteThreads, 4) void k_route_lce(const float *__r
     extern __shared__ __attribute__((aligned(16))) float smem[];
     const int block = (int)blockIdx.x - route_blocks;
     if (block >= 0) lce::lce_block<VEC ? 2 : 1, false, kRouteThreads>(J, D, mfma::swizzled(block, (int)gridDim.x - route_blocks), smem);
-    else if ((int)blockIdx.x < rows_blocks) route::route_block<VEC, 3>(Qr, Kr, ld, Ir, nullptr, D, CS, blockIdx.x, smem);
+    else if ((int)blockIdx.x < rows_blocks) route::route_block<VEC, true, 3>(Qr, Kr, ld, Ir, nullptr, D, CS, blockIdx.x, smem);
 }
 
 // added: O holds LCE(V) (not for maps that lce_block does not take).

@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kStoreThreads, 4) void k_route_lce(const float *__r
     extern __shared__ __attribute__((aligned(16))) float smem[];
     const int bi = blockIdx.x;
     if (bi < route_blocks) {
-        if (bi < rows_blocks) route::route_block<true, 3>(Qr, Kr, D.C, Ir, nullptr, D, CS, bi, smem);
+        if (bi < rows_blocks) route::route_block<true, false, 3>(Qr, Kr, D.C, Ir, nullptr, D, CS, bi, smem);
         return;
     }
     const int per_xcd = ((int)gridDim.x - route_blocks) / 8, block = (bi % 8) * per_xcd + (bi - route_blocks) / 8;

@@ -13,7 +13,7 @@ __global__ __launch_bounds__(64 * route::kWaves) void k_route_rows(const float *
                                                             Dims D, int CS)
 {
     extern __shared__ __attribute__((aligned(16))) float smem[];
-    route::route_block<VEC, 6>(Qr, Kr, ld, Ir, Ar, D, CS, blockIdx.x, smem);
+    route::route_block<VEC, true, 6>(Qr, Kr, ld, Ir, Ar, D, CS, blockIdx.x, smem);
 }
 
 }  // namespace

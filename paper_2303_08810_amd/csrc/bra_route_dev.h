@@ -66,10 +66,12 @@ __device__ __forceinline__ void topk_wide(const float *row, int R, int k, int la
     }
 }
 
-// VEC: C and ld multiples of 4 (16-byte loads).  CS, KGP: channel slices and key groups per pass, CS * KGP = 8.
-// Called by 64 kWaves threads.
-// MOST: steps requested at once (the sums do not depend on it).
-template <bool VEC, int MOST>
+// VEC: C and ld multiples of 4 (16-byte loads).  PART: C may not be a multiple of 16.  CS, KGP: channel slices and key
+// groups per pass, CS * KGP = 8.  Called by 64 kWaves threads.
+// MOST: steps requested at once.  The sums do not depend on it, infinities and NaN included: bra_route and bra_forward take
+// different ones, and a step repeated past the end with blanked queries alone made NaN of an infinite K^r in one and not the other.
+// As many steps as are left, no more (bra_route of 2 x 14 x 14 x 512, four steps: 23.5 us with six, 21.8).
+template <bool VEC, bool PART, int MOST>
 __device__ __forceinline__ void route_block(const float *__restrict__ Qr, const float *__restrict__ Kr, int ld, int32_t *__restrict__ Ir,
                                             float *__restrict__ Ar, const Dims &D, int CS, int block, float *smem)
 {
@@ -90,8 +92,7 @@ __device__ __forceinline__ void route_block(const float *__restrict__ Qr, const 
             const float *krow[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) krow[t] = Kr + img + (size_t)min(64 * kg + 16 * t + i, D.R - 1) * ld;
-            // NB steps at once: their loads are all requested before the first product (a step past the end
-            // repeats the last one and is blanked)
+            // NB steps at once: their loads are all requested before the first product
             auto batch = [&](int s, auto nb) {
                 constexpr int NB = decltype(nb)::value;
                 f32x4 q[NB], kv[NB][4];
@@ -105,8 +106,13 @@ __device__ __forceinline__ void route_block(const float *__restrict__ Qr, const 
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int u = 0; u < NB; ++u) {
-                    // channels past the end: blanked on one side
-                    if (16 * (s + u * CS) + 4 * g >= D.C) q[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    // channels past the end, in the last of all steps alone: blanked on both sides
+                    const bool past = 16 * (s + u * CS) + 4 * g >= D.C;
+                    if (past) q[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (VEC && PART && u == NB - 1) {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) kv[u][t] = past ? f32x4{0.f, 0.f, 0.f, 0.f} : kv[u][t];
+                    }
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -115,16 +121,16 @@ __device__ __forceinline__ void route_block(const float *__restrict__ Qr, const 
             };
             for (int s = cs; s < steps;) {
                 const int left = (steps - s + CS - 1) / CS;
-                if (MOST > 3 && left > 3) {
-                    batch(s, std::integral_constant<int, MOST>{});
-                    s += MOST * CS;
-                } else if (left > 1) {
-                    batch(s, std::integral_constant<int, 3>{});
-                    s += 3 * CS;
-                } else {
-                    batch(s, std::integral_constant<int, 1>{});
-                    s += CS;
-                }
+                auto take = [&](auto nb) {
+                    batch(s, nb);
+                    s += decltype(nb)::value * CS;
+                };
+                if (left >= MOST) take(std::integral_constant<int, MOST>{});
+                else if (MOST > 5 && left == 5) take(std::integral_constant<int, 5>{});
+                else if (MOST > 4 && left == 4) take(std::integral_constant<int, 4>{});
+                else if (MOST > 3 && left == 3) take(std::integral_constant<int, 3>{});
+                else if (left == 2) take(std::integral_constant<int, 2>{});
+                else take(std::integral_constant<int, 1>{});
             }
         }
         if (kg0) __syncthreads();                        // the previous pass has been added up

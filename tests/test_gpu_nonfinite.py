@@ -58,3 +58,26 @@ def test_depthwise_channels_independent(H, W, C, heads, S, channel):
     Woi[channel, 9] = 2.0 ** 40
     dW = gradients(X, Wqkv, Woi, dYi)[1][:, 2 * C:]
     assert np.isfinite(dW[:, other]).all() and not np.isfinite(dW[:, channel]).any()
+
+
+# K^r infinite in one of the last channels, the ones that were repeated where a batch of the routing's steps ran past the end: A^r is
+# +-inf in that region's column, by the sign of Q^r there, in bra_route (steps by six) as in bra_forward (by three).  512 channels
+# are four steps per slice (eight with more than 64 regions), 320 two and three, 192 one and two; 40 end within a step of 16
+@pytest.mark.parametrize("dtype,C,heads,S", [("bf16", 512, 16, 7), ("bf16", 320, 10, 7), ("bf16", 192, 6, 7), ("bf16", 512, 16, 9), ("f32", 512, 16, 7),
+                                             ("f32", 40, 1, 7), ("f32", 48, 2, 9), ("f32", 39, 3, 7)])
+def test_routing_by_an_infinite_key(dtype, C, heads, S):
+    H, region = 2 * S, 5
+    X, Wqkv, Wo, Wlce = make_inputs(1, H, H, C, seed=9960 + C + S, dtype=dtype)
+    means = X.astype(np.float64).reshape(S, 2, S, 2, C).mean(axis=(1, 3)).reshape(S * S, C)
+    Wqkv[7] = 0
+    q = (means @ Wqkv.astype(np.float64))[:, C - 2]      # Q^r of the channel (channel 7 of X does not enter)
+    assert np.abs(q).min() > 1e-5
+    X[..., 7] = 0
+    X[0, 2 * (region // S), 2 * (region % S), 7] = 2.0 ** 100
+    Wqkv[7, C + C - 2] = 2.0 ** 40
+    args = [to_device(a, dtype) for a in (X, Wqkv, Wo, Wlce)]
+    Ir = bra.bra_route(*args[:2], S, 3, heads)
+    used = bra.bra_forward(*args, S, 3, heads, want_Ir=True)[1]
+    assert torch.equal(Ir, used)
+    Ir = Ir[0].cpu().numpy()
+    assert (Ir[q > 0, 0] == region).all() and (Ir[q < 0] != region).all()
