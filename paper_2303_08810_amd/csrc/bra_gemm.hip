@@ -279,11 +279,12 @@ __device__ __forceinline__ void dma_tile(const bf16_t *__restrict__ In, const bf
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         // a 32-output tile lies in one buffer (cols is a multiple of 32): looked up once per tile, for the whole wavefront
-        const int ot = __builtin_amdgcn_readfirstlane(o0 + wn + 32 * nt), which = ot / out.cols, ct = ot - which * out.cols;
+        const int ot = __builtin_amdgcn_readfirstlane(o0 + wn + 32 * nt);
+        if (ot >= Nout) continue;                  // of no buffer
+        const int which = ot / out.cols, ct = ot - which * out.cols;
         bf16_t *buf = (bf16_t *)out.buf[which];
         float *fbuf = which < 2 ? out.f32[which] : nullptr;
         const float scale = which == 0 ? out.scale0 : 1.0f;
-        if (ot >= Nout) continue;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const int m = m0 + wm + 32 * mt + c;
