@@ -32,7 +32,11 @@ SHAPES = [  # (B, H, W, C, heads, S, k)
     (57, 64, 64, 64, 2, 16, 4),
     (15, 64, 64, 256, 8, 16, 2),
     (16, 14, 14, 512, 16, 7, 9),     # 4 tokens, 36 keys, 256 pairs
-    (12, 10, 10, 768, 24, 5, 9),     # 288
+    (12, 10, 10, 768, 24, 5, 9),     # 288, 25 regions: 7200 blocks of keys
+    (19, 10, 10, 768, 24, 5, 9),     # 11400
+    (20, 10, 10, 768, 24, 5, 9),     # 12000
+    (39, 10, 10, 768, 24, 5, 8),     # 936 pairs, one block of keys each: 11700
+    (40, 10, 10, 768, 24, 5, 8),     # 12000
     (31, 14, 28, 512, 16, 7, 5),     # 8 tokens, 40 keys: 496 pairs, 512 and 528, two rounds and a little more
     (32, 14, 28, 512, 16, 7, 5),
     (33, 14, 28, 512, 16, 7, 5),

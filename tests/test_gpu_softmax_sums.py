@@ -56,6 +56,16 @@ def test_forward_denominators_of_many_regions(B, C, heads):
         assert torch.equal(Y.float(), torch.full_like(Y.float(), want))
 
 
+# Few regions and few keys: 288 pairs of image and head, 96 keys, fewer blocks of keys than the image-resident attention takes.  With
+# V = 161 / 128, 234.6 units of the last place, with weights rounded to bf16 234.35
+def test_forward_denominators_of_few_regions():
+    (X, Wqkv, Wo, Wlce), Ir, k = layer(12, 2, 2, 5, 768, 24, "first", keys=96)
+    Wqkv[2, 2 * 768:] = 161 / 128
+    Y = bra.bra_forward(X, Wqkv, Wo, Wlce, 5, k, 24, Ir_in=Ir, scale=math.log(2.0), path="mfma")
+    want = torch.tensor(161 / 128 * 255 / 350).bfloat16().float().item()
+    assert torch.equal(Y.float(), torch.full_like(Y.float(), want))
+
+
 # a wavefront per region (16 and 32 tokens), four wavefronts per tile, 64 and 128 tokens per workgroup
 BACKWARD = [(6, 2, 7, 8, 64, 1), (6, 2, 11, 7, 64, 2), (1, 2, 7, 8, 64, 2), (1, 2, 11, 7, 64, 1), (3, 7, 11, 4, 64, 2),
             (57, 10, 11, 3, 64, 1), (57, 10, 11, 3, 64, 2)]
