@@ -70,7 +70,8 @@ __device__ __forceinline__ void topk_wide(const float *row, int R, int k, int la
 // groups per pass, CS * KGP = 8.  Called by 64 kWaves threads.
 // MOST: steps requested at once.  The sums do not depend on it, infinities and NaN included: bra_route and bra_forward take
 // different ones, and a step repeated past the end with blanked queries alone made NaN of an infinite K^r in one and not the other.
-// As many steps as are left, no more (bra_route of 2 x 14 x 14 x 512, four steps: 23.5 us with six, 21.8).
+// As many steps as are left, no more (bra_route of 2 x 14 x 14 x 512, four steps: 23.5 us with six, 21.8); beside the convolution
+// one by one after the threes (code for two as well: 2 x 8 x 24 x 512 33.9 us, 33.5 without; 11 x 7 x 7 x 768 39.4 and 38.9).
 template <bool VEC, bool PART, int MOST>
 __device__ __forceinline__ void route_block(const float *__restrict__ Qr, const float *__restrict__ Kr, int ld, int32_t *__restrict__ Ir,
                                             float *__restrict__ Ar, const Dims &D, int CS, int block, float *smem)
@@ -129,7 +130,7 @@ __device__ __forceinline__ void route_block(const float *__restrict__ Qr, const 
                 else if (MOST > 5 && left == 5) take(std::integral_constant<int, 5>{});
                 else if (MOST > 4 && left == 4) take(std::integral_constant<int, 4>{});
                 else if (MOST > 3 && left == 3) take(std::integral_constant<int, 3>{});
-                else if (left == 2) take(std::integral_constant<int, 2>{});
+                else if (MOST > 3 && left == 2) take(std::integral_constant<int, 2>{});
                 else take(std::integral_constant<int, 1>{});
             }
         }
