@@ -12,7 +12,7 @@ struct AttnBwdArgs {
     float *lse, *dsum;                 // [B][heads][N] row statistics
 };
 
-// With lce.fit both passes of lce are done within the two launches.
+// With lce.beside both passes of lce are done within the two launches; without, the caller runs them afterwards.
 int launch_attn_bwd(const Dims &D, const AttnBwdArgs &A, const lce::BackwardJobs &lce, int kernel_id, hipStream_t st);
 
 }  // namespace bra
