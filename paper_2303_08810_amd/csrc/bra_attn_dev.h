@@ -15,6 +15,7 @@ namespace mfma {
 // That sum also decides when the reference has to move: only when a lane's weights of a block exceed 2^8 together, which
 // needs no maximum and no exchange between lanes; the quotient O / l does not depend on it.  FIRST: the reference is this
 // block's maximum.  With dp (scores of the gradient in the same layout) also d: the lane's share of sum p dp.
+constexpr float kHeadroom = 8.0f;
 template <bool FIRST, int KT, int NDT>
 __device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, float &l, f32x4 (&acc)[NDT], bf16x8 (&pb)[KT / 2],
                                              const f32x4 *dp = nullptr, float *d = nullptr)
@@ -25,7 +26,7 @@ __device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, float &l,
         for (int t = 0; t < KT; ++t)
 #pragma unroll
             for (int j = 0; j < 4; ++j) mx = fmaxf(mx, s[t][j]);
-        const float up = keep ? fmaxf(cross_row_max(mx), 0.f) : cross_row_max(mx);
+        const float top = cross_row_max(mx), up = keep && !(top > 0.f) ? 0.f : top + kHeadroom;
         m += up;
 #pragma unroll
         for (int t = 0; t < KT; ++t)

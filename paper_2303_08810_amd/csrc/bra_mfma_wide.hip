@@ -68,16 +68,16 @@ __global__ __launch_bounds__(256) void k_pool_wide(const bf16_t *__restrict__ X,
 
 // What an output is added to (LCE(V), float32 with the upper halves of the bits in O and the lower ones in Low: the sum rounds
 // once): the lane's four channels of 16-channel tile dt of NQ query tiles.
-template <int NQ>
+template <int NQ, int NDT>
 struct Added {
-    u32x2 hi[NQ][4], lo[NQ][4];
+    u32x2 hi[NQ][NDT], lo[NQ][NDT];
 
     __device__ __forceinline__ void load(const bf16_t *O, const bf16_t *Low, const size_t (&token)[NQ], int C, int g)
     {
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int dt = 0; dt < 4; ++dt) {
+            for (int dt = 0; dt < NDT; ++dt) {
                 hi[q][dt] = *(const u32x2 *)(O + token[q] * C + 16 * dt + 4 * g);
                 lo[q][dt] = *(const u32x2 *)(Low + token[q] * C + 16 * dt + 4 * g);
             }
@@ -93,31 +93,41 @@ struct Added {
 // Routed attention (Eq. 6, Eq. 1) for any region size and heads of 32 or 64 channels.  Q comes multiplied by
 // scale * log2(e), so scores are exponents of 2.
 //
-// Regions of more than 32 tokens: workgroup (image, region, tile of 64 NQ queries of the region, group of 64 channels = 2
-// or 1 heads), wavefront w with NQ query tiles of 16.  The k n routed keys are taken 64 at a time: their K and V rows (the
+// Regions of more than 32 tokens: workgroup (image, group of 64 channels = 2 or 1 heads, region, tile of 64 NQ queries of the
+// region), a wavefront with NQ query tiles of 16 and HPW heads.  The k n routed keys are taken 64 at a time: their K and V rows (the
 // group's 128 bytes each, found by index in the projected maps) go straight from memory into one of two LDS buffers while
 // the other is worked on; 16-byte pieces are exchanged (piece c of row r at c ^ r % 8), so that K's row reads and V's
 // transposing reads meet different banks.  Queries past the end of the region and keys past k n
 // repeat the last one and are masked.
-// Bound by vector issue: 2 x 208 x 304 x 64, 16 x 16 regions, k = 4 (250 M scores) takes 69 us, the convolution it is added to
-// with it, in which the vector ALUs issue in 68 % of the cycles and the matrix cores work in 24 %.  Of 5.0 vector instructions per score
-// 2.5 are its 2^x, its addition to the denominator and half a conversion; with maxima instead of additions and denominators from a
-// product it took 2 us more.  One query tile per wavefront instead of two: 8 us more (4 x 64 x 64 x 384, heads of 64, k = 4: 45 for 39).
-template <int HD, int NQ, bool WALK>
-__global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, const bf16_t *__restrict__ Low)
+// Bound by vector issue: 2 x 208 x 304 x 64, 16 x 16 regions, k = 4 (250 M scores) takes 64 us, the convolution it is added to
+// with it.  A wavefront's 16 x 64 scores take 16 2^x (8 clocks each), 15 additions, 8 conversions, about 6 other vector instructions
+// and 8 products, of which each keeps the vector pipe for about 9 clocks beside 2^x.  One head per wavefront and eight of
+// them, 124 registers: four wavefronts per SIMD where both heads (154 registers) left three and the last quarter of 1024 workgroups
+// to a second round (70.7 us); four registers of -m as the products' accumulator input instead of moves for every tile.  One
+// query tile per wavefront instead of two: 8 us more (4 x 64 x 64 x 384, heads of 64, k = 4: 45 for 39).
+template <int HD, int HPW>
+constexpr int genWaves = 4 * (64 / HD) / HPW;
+
+template <int HD, int NQ, int HPW, bool WALK>
+__global__ __launch_bounds__((64 * genWaves<HD, HPW>), HD == 32 && HPW == 1 ? 4 : 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, const bf16_t *__restrict__ Low)
 {
-    constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16;
+    constexpr int WAVES = genWaves<HD, HPW>, PARTS = WAVES / 4, KSD = HD / 32, NDT = HD / 16;
     __shared__ __attribute__((aligned(16))) bf16_t K0[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t K1[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t V0[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t V1[64 * 64];
     extern __shared__ int origins[];             // [k]: first token of the routed regions; with WALK [n]: tokens of a region's slots
     const int C = D.C, ncg = C / 64, n = D.n, kn = D.kn;
-    const int cg = blockIdx.x % ncg, qt = (blockIdx.x / ncg) % qtiles;
-    const int reg = (blockIdx.x / (ncg * qtiles)) % D.R, b = blockIdx.x / (ncg * qtiles * D.R);
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
+    // workgroups of an image and channel group share an L2: a gathered row of 128 bytes is a line of one group (10 x 64 x 64 x 384,
+    // k = 6: layer 153.8 us; groups next to each other 158.0, all over the XCDs 160.1)
+    const int block = swizzled_block();
+    const int qt = block % qtiles, reg = (block / qtiles) % D.R;
+    const int cg = (block / (qtiles * D.R)) % ncg, b = block / (qtiles * D.R * ncg);
+    if (b >= D.B) return;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), part = wave % PARTS, qw = wave / PARTS, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const float rw_inv = 1.0f / (float)D.rw, n_inv = 1.0f / (float)n, s_inv = 1.0f / (float)D.S;
     const size_t img = (size_t)b * D.N * C + 64 * cg;
+    const int c0 = 64 / PARTS * part;             // the wavefront's first channel of the group
     auto region_origin = [&](int r) {
         const int ry = fast_div(r, s_inv);
         return ry * D.rh * D.W + (r - ry * D.S) * D.rw;
@@ -130,25 +140,25 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
     bf16x8 qf[NQ][HPW][KSD];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        qtok[q] = (size_t)region_origin(reg) + in_region(min(64 * NQ * qt + 16 * (NQ * wave + q) + i, n - 1));
+        qtok[q] = (size_t)region_origin(reg) + in_region(min(64 * NQ * qt + 16 * (NQ * qw + q) + i, n - 1));
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh)
 #pragma unroll
             for (int ks = 0; ks < KSD; ++ks)
-                qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + HD * hh + 32 * ks + 8 * g);
+                qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + c0 + HD * hh + 32 * ks + 8 * g);
     }
-    Added<NQ> added;
-    if (NQ == 1 && Low) added.load(O + img, Low + img, qtok, C, g);
+    Added<NQ, NDT * HPW> added;
+    if (NQ == 1 && Low) added.load(O + img + c0, Low + img + c0, qtok, C, g);
     const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
     const bool report = A.Ir_out && A.Ir_out != A.Ir_src && qt == 0 && cg == 0;
-    for (int p = tid; p < D.k; p += 256) {
+    for (int p = tid; p < D.k; p += 64 * WAVES) {
         const int j = irp[p];
         origins[p] = region_origin(region_index(j, D.R));
         if (report) A.Ir_out[((size_t)b * D.R + reg) * D.k + p] = j;
     }
     int *slots = origins + D.k;
     if (WALK)
-        for (int t = tid; t < n; t += 256) slots[t] = in_region(t);
+        for (int t = tid; t < n; t += 64 * WAVES) slots[t] = in_region(t);
     // the operands have arrived before the loop: otherwise the compiler waits for them, and with them for the direct loads
     // in flight, in every pass
 #pragma unroll
@@ -157,21 +167,22 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
         for (int hh = 0; hh < HPW; ++hh)
 #pragma unroll
             for (int ks = 0; ks < KSD; ++ks) asm volatile("" : "+v"(qf[q][hh][ks]));
-    // direct loads: a wavefront brings rows 16 w .. 16 w + 15 of K and V, 8 rows of 8 pieces each, block after block
-    RowWalk<2> walk;
-    if constexpr (WALK) walk.start(16 * wave + lane / 8, 8, 64, n, n_inv);
+    // direct loads: a wavefront brings its share of the rows of K and V, 8 rows of 8 pieces each, block after block
+    constexpr int LOADS = 8 / WAVES;
+    RowWalk<LOADS> walk;
+    if constexpr (WALK) walk.start(8 * LOADS * wave + lane / 8, 8, 64, n, n_inv);
     const unsigned piece = 16 * ((lane % 8) ^ (lane / 8));
     auto request = [&](int k0, unsigned Ks, unsigned Vs) {
         lds_reads_done();
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const unsigned at = 1024 * (2 * wave + u);
+        for (int u = 0; u < LOADS; ++u) {
+            const unsigned at = 1024 * (LOADS * wave + u);
             if constexpr (WALK) {
                 const unsigned off = row_offset(walk.token(u, origins, D.k - 1, slots), C, piece);
                 load_to_lds_untracked(A.K + img, off, Ks + at);
                 load_to_lds_untracked(A.V + img, off, Vs + at);
             } else {
-                const int key = min(k0 + 16 * wave + 8 * u + lane / 8, kn - 1), p = fast_div(key, n_inv);
+                const int key = min(k0 + 8 * (LOADS * wave + u) + lane / 8, kn - 1), p = fast_div(key, n_inv);
                 const size_t e = img + (size_t)(origins[p] + in_region(key - p * n)) * C + piece / 2;
                 load_to_lds_untracked(A.K + e, Ks + at);
                 load_to_lds_untracked(A.V + e, Vs + at);
@@ -179,17 +190,19 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
         }
         if constexpr (WALK) walk.advance();
     };
+    constexpr bool KEPT = HD == 32 && HPW == 1;      // registers for four copies of -m
     float m[NQ][HPW], l[NQ][HPW];
-    f32x4 acc[NQ][HPW][NDT];
+    f32x4 acc[NQ][HPW][NDT], neg[NQ][HPW];
 #pragma unroll
     for (int q = 0; q < NQ; ++q)
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
             m[q][hh] = l[q][hh] = 0.f;
+            neg[q][hh] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-    auto block = [&](int k0, const bf16_t *Ks, const bf16_t *Vs, auto first) {
+    auto block_of_keys = [&](int k0, const bf16_t *Ks, const bf16_t *Vs, auto first) {
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
             bf16x8 pb[NQ][2];
@@ -198,14 +211,15 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
-                    for (int ks = 0; ks < KSD; ++ks) kf[t][ks] = row_operand(Ks, 16 * t + i, HD / 8 * hh + 4 * ks + g);
+                    for (int ks = 0; ks < KSD; ++ks) kf[t][ks] = row_operand(Ks, 16 * t + i, (c0 + HD * hh) / 8 + 4 * ks + g);
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
                     f32x4 s[4];
-                    const float neg = -m[q][hh];
+                    const float was = m[q][hh];
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
-                        s[t] = f32x4{neg, neg, neg, neg};
+                        const float neg1 = -m[q][hh];
+                        s[t] = KEPT ? neg[q][hh] : f32x4{neg1, neg1, neg1, neg1};
 #pragma unroll
                         for (int ks = 0; ks < KSD; ++ks) s[t] = mfma16(kf[t][ks], qf[q][hh][ks], s[t]);
                     }
@@ -217,6 +231,11 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
                                 if (k0 + 16 * t + 4 * g + j >= kn) s[t][j] = -INFINITY;
                     }
                     softmax_step<decltype(first)::value>(s, m[q][hh], l[q][hh], acc[q][hh], pb[q]);
+                    if (KEPT && (decltype(first)::value || __builtin_amdgcn_ballot_w64(m[q][hh] != was) != 0)) {
+                        const float neg1 = -m[q][hh];
+                        neg[q][hh] = f32x4{neg1, neg1, neg1, neg1};
+                        asm volatile("" : "+v"(neg[q][hh]));      // four registers: made anew from one, they are 3 moves per product
+                    }
                     if (NQ > 1) __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -224,33 +243,33 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
             for (int tp = 0; tp < 2; ++tp)
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt) {
-                    const bf16x8 vf = column_operand(Vs, 32 * tp, HD * hh + 16 * dt, g, i);
+                    const bf16x8 vf = column_operand(Vs, 32 * tp, c0 + HD * hh + 16 * dt, g, i);
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) acc[q][hh][dt] = mfma16(vf, pb[q][tp], acc[q][hh][dt]);
                 }
             __builtin_amdgcn_sched_barrier(0);    // one head at a time: interleaved, they take twice the registers
         }
     };
-    const bool idle = 64 * NQ * qt + 16 * NQ * wave >= n;      // a wavefront without queries only brings its rows
+    const bool idle = 64 * NQ * qt + 16 * NQ * qw >= n;      // a wavefront without queries only brings its rows
     __syncthreads();                              // the table is in place
     const unsigned kv[2][2] = {{lds_address(K0), lds_address(V0)}, {lds_address(K1), lds_address(V1)}};
     request(0, kv[0][0], kv[0][1]);
     arrive_barrier();
     if (64 < kn) request(64, kv[1][0], kv[1][1]);
-    if (!idle) block(0, K0, V0, std::true_type{});
+    if (!idle) block_of_keys(0, K0, V0, std::true_type{});
     for (int k0 = 64; k0 < kn; k0 += 128) {
         arrive_barrier();
         if (k0 + 64 < kn) request(k0 + 64, kv[0][0], kv[0][1]);
-        if (!idle) block(k0, K1, V1, std::false_type{});
+        if (!idle) block_of_keys(k0, K1, V1, std::false_type{});
         if (k0 + 64 >= kn) break;
         arrive_barrier();
         if (k0 + 128 < kn) request(k0 + 128, kv[1][0], kv[1][1]);
-        if (!idle) block(k0 + 64, K0, V0, std::false_type{});
+        if (!idle) block_of_keys(k0 + 64, K0, V0, std::false_type{});
     }
-    if (NQ > 1 && Low) added.load(O + img, Low + img, qtok, C, g);      // 32 registers that the sweep does not have
+    if (NQ > 1 && Low) added.load(O + img + c0, Low + img + c0, qtok, C, g);      // registers that the sweep does not have
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        const bool store = 64 * NQ * qt + 16 * (NQ * wave + q) + i < n;
+        const bool store = 64 * NQ * qt + 16 * (NQ * qw + q) + i < n;
 #pragma unroll
         for (int hh = 0; hh < HPW; ++hh) {
             const float inv = 1.0f / cross_row_sum(l[q][hh]);
@@ -259,7 +278,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_gen(AttnArgs A, bf16_t *__restr
             for (int dt = 0; dt < NDT; ++dt) {
                 f32x4 v = acc[q][hh][dt] * inv;
                 if (Low) v = added.to(v, q, NDT * hh + dt);
-                *(u32x2 *)(O + img + qtok[q] * C + HD * hh + 16 * dt + 4 * g) = pack4(v);
+                *(u32x2 *)(O + img + qtok[q] * C + c0 + HD * hh + 16 * dt + 4 * g) = pack4(v);
             }
         }
     }
@@ -313,7 +332,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__rest
             for (int ks = 0; ks < KSD; ++ks)
                 qf[q][hh][ks] = *(const bf16x8 *)(A.Q + img + qtok[q] * C + HD * hh + 32 * ks + 8 * g);
     }
-    Added<NQ> added;
+    Added<NQ, 4> added;
     if (Low) added.load(O + img, Low + img, qtok, C, g);
     const int32_t *irp = A.Ir_src + ((size_t)b * D.R + reg) * D.k;
     const bool report = A.Ir_out && A.Ir_out != A.Ir_src && cg == 0;
@@ -493,35 +512,39 @@ int launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *
     return D.n <= 16 ? launch_attn_rows_t<64, 1>(D, A, O, Low, st) : launch_attn_rows_t<64, 2>(D, A, O, Low, st);
 }
 
-template <int HD, int NQ, bool WALK>
+template <int HD, int NQ, int HPW, bool WALK>
 void launch_attn_gen_w(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
 {
     const int qtiles = (D.n + 64 * NQ - 1) / (64 * NQ);
-    const dim3 grid((unsigned)((long)D.B * D.R * qtiles * (D.C / 64)));
+    const dim3 grid((unsigned)(((long)D.B * D.R * qtiles * (D.C / 64) + 7) / 8 * 8));
     const size_t smem = (size_t)(D.k + (WALK ? D.n : 0)) * sizeof(int);
-    hipLaunchKernelGGL((k_attn_gen<HD, NQ, WALK>), grid, dim3(256), smem, st, A, O, D, qtiles, Low);
+    hipLaunchKernelGGL((k_attn_gen<HD, NQ, HPW, WALK>), grid, dim3(64 * genWaves<HD, HPW>), smem, st, A, O, D, qtiles, Low);
 }
 
 // Rows by walking (a table of the region's tokens more, an addition instead of divisions) from more than three blocks of keys on;
 // a kernel of its own for each: both ways in one take 125 registers instead of 118 and 120 (one query tile, heads of 32).  Layer,
 // both in one / by divisions / by walking (us): 40 x 56 x 56 x 192, k = 1 (one block) 176.6 / 174.0 / 174.5; 30 x 42 x 42 x 192, k = 5 (180 keys)
 // 114.8 / 110.3 / 113.1; 20 x 77 x 77 x 64, k = 2 (242) 73.9 / 74.4 / 73.7; 2 x 200 x 300 x 64, S = 16, k = 4 (988) 115.8 / 115.1 / 114.2.
-template <int NQ>
+template <int NQ, int HPW>
 void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
 {
     const bool walks = walk_ok(D) && D.kn > 192;
-    if (D.d == 32) walks ? launch_attn_gen_w<32, NQ, true>(D, A, O, Low, st) : launch_attn_gen_w<32, NQ, false>(D, A, O, Low, st);
-    else walks ? launch_attn_gen_w<64, NQ, true>(D, A, O, Low, st) : launch_attn_gen_w<64, NQ, false>(D, A, O, Low, st);
+    if (D.d == 32) walks ? launch_attn_gen_w<32, NQ, HPW, true>(D, A, O, Low, st) : launch_attn_gen_w<32, NQ, HPW, false>(D, A, O, Low, st);
+    else walks ? launch_attn_gen_w<64, NQ, 1, true>(D, A, O, Low, st) : launch_attn_gen_w<64, NQ, 1, false>(D, A, O, Low, st);
 }
 
 // Low: if not NULL, the output is added to what O and it hold (LCE(V)).
 void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
 {
     // two query tiles per wavefront (every K and V operand read serves both; measured above) where the wider tile leaves no
-    // more than an eighth of its queries empty beyond the narrow one and there are workgroups enough
+    // more than an eighth of its queries empty beyond the narrow one and there are workgroups enough.  One query tile: a head per
+    // wavefront while the workgroups are few (layer of 1 x 72 x 72 x 192, S = 8, k = 12 47.9 -> 44.3 us, 1 x 100 x 150 x 64, S = 16, k = 8
+    // 44.7 -> 41.8), both heads from four workgroups per compute unit on, whose prologue is paid by half as many wavefronts
+    // (30 x 42 x 42 x 192, k = 5 103.9, with one head each 107.5)
     const int t64 = (D.n + 63) / 64, t128 = (D.n + 127) / 128;
-    if (t128 * 128 * 8 <= t64 * 64 * 9 && (long)D.B * D.R * t128 * (D.C / 64) >= 512) launch_attn_gen_t<2>(D, A, O, Low, st);
-    else launch_attn_gen_t<1>(D, A, O, Low, st);
+    if (t128 * 128 * 8 <= t64 * 64 * 9 && (long)D.B * D.R * t128 * (D.C / 64) >= 512) launch_attn_gen_t<2, 1>(D, A, O, Low, st);
+    else if ((long)D.B * D.R * t64 * (D.C / 64) >= 1024) launch_attn_gen_t<1, 2>(D, A, O, Low, st);
+    else launch_attn_gen_t<1, 1>(D, A, O, Low, st);
 }
 
 // Pooling, region-level projections, A^r rows and top-k on their own, for regions of more than one token.
