@@ -35,9 +35,22 @@ struct GemmRegions {
     int cols;
 };
 
+// Rows of In and of the output taken region by region (n tokens each, row-major within the region) of maps of S x S regions of
+// rh x rw tokens, of which In holds the top-left H x W part (the rest reads as zeros), and float32 means over each region's tokens of the results that
+// go to buf[0] and buf[1] of the output, before they are rounded and scaled.  An output buffer that is NULL is not written.
+struct GemmMeans {
+    float *buf[2];
+    int regions, R, S, n, rh, rw, H, W;
+    float n_inv, R_inv, S_inv, rw_inv;
+};
+// Tiles hold whole regions: not of more tokens than the smallest tile has rows.
+constexpr int kMeansMaxTokens = 64;
+
 // Out = In W: In [M, K] bf16, W row-major [K][ldw]; K a multiple of 64, Nout of 8.
 int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, const GemmRegions *regions,
          int kernel_id, hipStream_t st);
+// The same over the regions of a map, with their means; K <= 4096.
+int gemm_means(const bf16_t *In, const bf16_t *W, int ldw, int K, int Nout, const GemmOut &out, const GemmMeans &means, int kernel_id, hipStream_t st);
 // Out = In Wt^T: Wt [Nout][ldw], the contraction axis contiguous.
 int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout, bf16_t *Out, int kernel_id, hipStream_t st);
 

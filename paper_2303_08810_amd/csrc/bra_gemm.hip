@@ -166,26 +166,90 @@ __device__ __forceinline__ long stored_row(const GemmRows &r, int m)
     return y < r.H && x < r.W ? ((long)b * r.H + y) * r.W + x : -1;
 }
 
+// LDS of a workgroup.  A single chunk: four workgroups per compute unit (with eight, 200704 x 64 x 64 takes 13.7 us instead of 12.9).
+template <int BM, int BN, int NB>
+constexpr size_t ring_bytes() { return NB == 1 ? 40 * 1024 : (size_t)NB * (BM + BN) * 64 * 2; }
+
+// What lies in front of the table of rows of a product with means.
+template <int BM, int BN, int NB>
+__host__ __device__ constexpr size_t means_ring()
+{
+    constexpr size_t chunks = NB == 1 ? 38 * 1024 : (size_t)NB * (BM + BN) * 64 * 2, results = (size_t)BM * (BN + 4) * sizeof(float);
+    return chunks > results ? chunks : results;
+}
+
+// Tokens of row `row` of tile `tile` of a product that goes region by region, in the map and in what is stored of it; -1: none.
+template <int BM>
+__device__ __forceinline__ void region_row(const GemmMeans &g, int tile, int row, int &token, int &stored)
+{
+    token = stored = -1;
+    const int per = fast_div(BM, g.n_inv), first = tile * per, b0 = (unsigned)first / (unsigned)g.R, r0 = first - b0 * g.R;
+    const int j = fast_div(row, g.n_inv), t = row - j * g.n;
+    if (j >= per || first + j >= g.regions) return;
+    const int over = fast_div(r0 + j, g.R_inv), reg = r0 + j - over * g.R;
+    const int ry = fast_div(reg, g.S_inv), ty = fast_div(t, g.rw_inv);
+    const int y = ry * g.rh + ty, x = (reg - ry * g.S) * g.rw + t - ty * g.rw;
+    token = ((b0 + over) * g.S * g.rh + y) * g.S * g.rw + x;
+    if (y < g.H && x < g.W) stored = ((b0 + over) * g.H + y) * g.W + x;
+}
+
+// Rows whose sums a wavefront forms in registers: aligned groups of a tile's rows that lie in one region.
+__device__ __forceinline__ int means_group(int n) { return n % 16 == 0 ? 16 : n % 4 == 0 ? 4 : 1; }
+
+// Sums over the four lanes of a quad of 16 values per lane, a quarter to each lane: entries 8 (c % 2) + 4 (c / 2 % 2) + 0 .. 3.
+__device__ __forceinline__ f32x4 quad_sums(const f32x16 &v, int c)
+{
+    const bool odd = c & 1, hi = c & 2;
+    float x[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        x[e] = v[e];
+        asm volatile("" : "+v"(x[e]));            // a select of two entries of v becomes a chain of 16 compares otherwise
+    }
+    float pair[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) pair[e] = (odd ? x[8 + e] : x[e]) + dpp_get<0xB1>(odd ? x[e] : x[8 + e]);
+    f32x4 quad;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) quad[e] = (hi ? pair[4 + e] : pair[e]) + dpp_get<0x4E>(hi ? pair[e] : pair[4 + e]);
+    return quad;
+}
+
 // Workgroups of an XCD take neighbouring tiles, the output tiles of the same rows one after the other (swizzled()).
 // EXT: bias, GELU, residual or rows that are not in memory (GemmRows).  NB: buffers, 1 for K = 64, else 2.
 // lds: NB chunks of In and of W.
-template <int BM, int BN, int NB, bool BT, bool EXT>
+// MEANS: rows region by region, see GemmMeans (M is not looked at); a table in LDS has the tokens of the tile's rows.  The float32 results of
+// the columns that have means are added up over aligned groups of 16 or 4 rows in registers (means_group()), where that is less
+// than a region the groups' sums, or with an odd number of rows the results, meet in LDS: the order does not depend on the tile.  All by way of
+// LDS it took 1 us more of 64 x 14 x 14 x 384's layer (68.5 -> 67.0) and of 8 x 32 x 32 x 768's bra_route (39.2 -> 38.3).
+template <int BM, int BN, int NB, bool BT, bool EXT, bool MEANS = false>
 __device__ __forceinline__ void dma_tile(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int M, int K, int Nout,
-                                         const GemmOut &out, int block, bf16_t *lds)
+                                         const GemmOut &out, int block, bf16_t *lds, const GemmMeans *means = nullptr)
 {
     constexpr int AE = BM * 64, BE = BN * 64;     // elements of a chunk
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, h = lane / 32, c = lane % 32;
     const int otiles = (Nout + BN - 1) / BN;
     const int m0 = (block / otiles) * BM, o0 = (block % otiles) * BN;
-    if (m0 >= M) return;                          // the grid is rounded up to a multiple of 8
+    if (!MEANS && m0 >= M) return;                // the grid is rounded up to a multiple of 8
+    const int *rows = nullptr;                    // tokens of the tile's rows, in the map and as stored
+    if constexpr (MEANS) {
+        if (block / otiles * fast_div(BM, means->n_inv) >= means->regions) return;
+        int *table = (int *)((char *)lds + means_ring<BM, BN, NB>());
+        if (tid < BM) region_row<BM>(*means, block / otiles, tid, table[tid], table[BM + tid]);
+        __syncthreads();
+        rows = table;
+    }
 
     constexpr int LA = BM / 32, LB = BN / 32;     // direct loads of a wavefront per chunk
     const bf16_t *ap[LA], *bp[LB];
 #pragma unroll
     for (int u = 0; u < LA; ++u) {
         const int row = 8 * (wave * LA + u) + lane / 8, piece = (lane % 8) ^ (row % 8);
-        ap[u] = In + (size_t)min(m0 + row, M - 1) * K + 8 * piece;
-        if (EXT && out.in_rows.Hp) {
+        ap[u] = In + (size_t)(MEANS ? 0 : min(m0 + row, M - 1)) * K + 8 * piece;
+        if constexpr (MEANS) {
+            const int at = rows[BM + row];
+            ap[u] = (at >= 0 ? In + (size_t)at * K : zero_row) + 8 * piece;
+        } else if (EXT && out.in_rows.Hp) {
             const long at = stored_row(out.in_rows, min(m0 + row, M - 1));
             ap[u] = (at >= 0 ? In + (size_t)at * K : zero_row) + 8 * piece;
         }
@@ -276,19 +340,63 @@ __device__ __forceinline__ void dma_tile(const bf16_t *__restrict__ In, const bf
         }
     }
     products_done();
+    constexpr int MP = BN + 4;                    // floats per row of sums in LDS
+    const bool averaged = MEANS && o0 < 2 * out.cols;
+    float *sums = (float *)lds;
+    if constexpr (MEANS) {
+        auto lay_down = [&](auto group) {
+            constexpr int G = decltype(group)::value;
+            const bool whole = G == means->n;
+            if (!whole) __syncthreads();          // the last chunk has been read
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const int ot = __builtin_amdgcn_readfirstlane(o0 + wn + 32 * nt), which = (ot >= out.cols) + (ot >= 2 * out.cols);
+                float *to = which < 2 ? means->buf[which] + ot - which * out.cols : nullptr;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    const int row = wm + 32 * mt + c;
+                    if constexpr (G == 1) {
+#pragma unroll
+                        for (int e = 0; e < 16; e += 4)
+                            *(f32x4 *)(sums + row * MP + wn + 32 * nt + 8 * h + 16 * (e / 8) + e % 8) = f32x4{acc[nt][mt][e], acc[nt][mt][e + 1], acc[nt][mt][e + 2], acc[nt][mt][e + 3]};
+                        continue;
+                    }
+                    f32x4 quad = quad_sums(acc[nt][mt], c);
+                    if constexpr (G == 16)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            quad[e] += dpp_get<0x124>(quad[e]);       // row_ror:4
+                            quad[e] += dpp_get<0x128>(quad[e]);       // row_ror:8
+                        }
+                    if (c % G >= 4) continue;
+                    const int col = 8 * h + 16 * (c % 2) + 4 * (c / 2 % 2);
+                    const int region = block / otiles * (BM / G) + row / G;
+                    if (!whole) *(f32x4 *)(sums + row / G * MP + wn + 32 * nt + col) = quad;
+                    else if (to && region < means->regions) *(f32x4 *)(to + (size_t)region * out.cols + col) = quad * means->n_inv;
+                }
+            }
+        };
+        if (averaged) {
+            const int G = means_group(means->n);
+            if (G == 16) lay_down(std::integral_constant<int, 16>{});
+            else if (G == 4) lay_down(std::integral_constant<int, 4>{});
+            else lay_down(std::integral_constant<int, 1>{});
+        }
+    }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         // a 32-output tile lies in one buffer (cols is a multiple of 32): looked up once per tile, for the whole wavefront
         const int ot = __builtin_amdgcn_readfirstlane(o0 + wn + 32 * nt);
         if (ot >= Nout) continue;                  // of no buffer
-        const int which = ot / out.cols, ct = ot - which * out.cols;
+        const int which = (ot >= out.cols) + (ot >= 2 * out.cols), ct = ot - which * out.cols;
         bf16_t *buf = (bf16_t *)out.buf[which];
+        if (MEANS && !buf) continue;
         float *fbuf = which < 2 ? out.f32[which] : nullptr;
         const float scale = which == 0 ? out.scale0 : 1.0f;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const int m = m0 + wm + 32 * mt + c;
-            if (m >= M) continue;
+            const int m = MEANS ? rows[wm + 32 * mt + c] : m0 + wm + 32 * mt + c;
+            if (MEANS ? m < 0 : m >= M) continue;
             size_t row = (size_t)m * out.cols;
             if (EXT && out.out_rows.Hp) {
                 const long at = stored_row(out.out_rows, m);
@@ -328,6 +436,21 @@ __device__ __forceinline__ void dma_tile(const bf16_t *__restrict__ In, const bf
             }
         }
     }
+    if constexpr (MEANS) {
+        const int n = means->n, G = means_group(n), per = fast_div(BM, means->n_inv), rows_each = n / G;
+        if (!averaged || G == n) return;
+        __syncthreads();
+        constexpr int GROUPS = BN / 4, TR = 256 / GROUPS;
+        const int col = o0 + 4 * (tid % GROUPS), which = (col >= out.cols) + (col >= 2 * out.cols);
+        const int first = block / otiles * per;
+        for (int j = tid / GROUPS; j < per && first + j < means->regions; j += TR) {
+            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+            const float *p = sums + j * rows_each * MP + 4 * (tid % GROUPS);
+#pragma unroll 4
+            for (int t = 0; t < rows_each; ++t) sum += *(const f32x4 *)(p + t * MP);
+            if (which < 2) *(f32x4 *)(means->buf[which] + (size_t)(first + j) * out.cols + col - which * out.cols) = sum * means->n_inv;
+        }
+    }
 }
 
 template <int BM, int BN, int NB, bool REGIONS, bool BT, bool EXT>
@@ -342,6 +465,14 @@ __global__ __launch_bounds__(256, BM == 64 && BN == 64 ? 3 : 2) void k_gemm_dma(
         return;
     }
     dma_tile<BM, BN, NB, BT, EXT>(In, W, ldw, M, K, Nout, out, swizzled((int)blockIdx.x - reg_blocks, (int)gridDim.x - reg_blocks), lds);
+}
+
+template <int BM, int BN, int NB>
+__global__ __launch_bounds__(256, BM == 64 && BN == 64 ? 3 : 2) void k_gemm_means(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw,
+                                                  int K, int Nout, GemmOut out, GemmMeans means)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    dma_tile<BM, BN, NB, false, false, true>(In, W, ldw, 0, K, Nout, out, swizzled_block(), (bf16_t *)smem, &means);
 }
 
 // Two products over the same rows and contraction in one launch: Q, K, V = X Wqkv and dO = dY Wo^T (W transposed).  12544 x 384:
@@ -361,10 +492,6 @@ long region_blocks(const GemmRegions &r) { return (r.M + 63) / 64 * ((r.Nout + 6
 
 template <int BM, int BN>
 long tile_blocks(long M, int Nout) { return ((M + BM - 1) / BM * ((Nout + BN - 1) / BN) + 7) / 8 * 8; }
-
-// LDS of a workgroup.  A single chunk: four workgroups per compute unit (with eight, 200704 x 64 x 64 takes 13.7 us instead of 12.9).
-template <int BM, int BN, int NB>
-constexpr size_t ring_bytes() { return NB == 1 ? 40 * 1024 : (size_t)NB * (BM + BN) * 64 * 2; }
 
 template <typename K>
 bool opt_in(K kernel, bool &done)
@@ -398,6 +525,18 @@ int launch_dma(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int No
     return launch_dma_t<BM, BN, NB, REGIONS, BT, false>(In, W, ldw, M, K, Nout, out, reg, st);
 }
 
+template <int BM, int BN, int NB>
+int launch_means(const bf16_t *In, const bf16_t *W, int ldw, int K, int Nout, const GemmOut &out, const GemmMeans &means, hipStream_t st)
+{
+    static bool opted = false;
+    if (!opt_in(k_gemm_means<BM, BN, NB>, opted)) return BRA_ERR_LAUNCH;
+    const long blocks = (((long)means.regions + BM / means.n - 1) / (BM / means.n) * ((Nout + BN - 1) / BN) + 7) / 8 * 8;
+    if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((k_gemm_means<BM, BN, NB>), dim3((unsigned)blocks), dim3(256), (means_ring<BM, BN, NB>() + 2 * BM * sizeof(int)), st, In, W, ldw, K, Nout, out,
+                       means);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
 enum Tile { kOneChunk, kWide, kMid, kNarrow };
 
 // One chunk: no tile reads anything twice, small ones overlap their loads and stores best (126464 x 64 x 192: 14.0 us, 14.8
@@ -417,12 +556,14 @@ enum Tile { kOneChunk, kWide, kMid, kNarrow };
 // 3072 x 1024 52.5 / 49.0, and 1960 x 1024 x 3072 33.5 / 31.2).
 // Up to three chunks and one and a half wide tiles of columns: the wide tile's empty half is a quarter of a short product
 // (125440 x 192 x 192 25.3 / 26.3 / 23.8, 50176 13.4 / 13.6 / 12.4).
-Tile pick_tile(long M, int K, int Nout, int Nout1, long others)
+// n: rows in tiles of whole groups of n.
+Tile pick_tile(long M, int K, int Nout, int Nout1, long others, int n = 1)
 {
     if (K == 64) return kOneChunk;
     if (K <= 192 && Nout > 128 && Nout + Nout1 <= 192) return kNarrow;
     auto cost = [&](int bm, int bn, long tile) {
-        const long rounds = ((M + bm - 1) / bm * ((Nout + bn - 1) / bn + (Nout1 + bn - 1) / bn) + others * 433 / tile + 255) / 256;
+        const long groups = bm / n, row_tiles = (M / n + groups - 1) / groups;
+        const long rounds = (row_tiles * ((Nout + bn - 1) / bn + (Nout1 + bn - 1) / bn) + others * 433 / tile + 255) / 256;
         return tile * rounds * (rounds == 1 ? 13 : 10);
     };
     const bool again = (long)K * Nout * 2 > 4L << 20 && M > 2560;
@@ -754,6 +895,19 @@ int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, co
     ProfScope ps(st, kernel_id);
     if (regions) return launch_big<true>(In, W, ldw, M, K, Nout, out, *regions, st);
     return launch_big<false>(In, W, ldw, M, K, Nout, out, GemmRegions{}, st);
+}
+
+int gemm_means(const bf16_t *In, const bf16_t *W, int ldw, int K, int Nout, const GemmOut &out, const GemmMeans &means, int kernel_id, hipStream_t st)
+{
+    const long M = (long)means.regions * means.n;
+    if (!sizes_ok(M, K, Nout) || out.cols % 32 || K > 4096 || means.n > kMeansMaxTokens) return BRA_ERR_UNSUPPORTED;
+    ProfScope ps(st, kernel_id);
+    switch (pick_tile(M, K, Nout, 0, 0, means.n)) {
+    case kOneChunk: return launch_means<64, 64, 1>(In, W, ldw, K, Nout, out, means, st);
+    case kWide: return launch_means<128, 128, 2>(In, W, ldw, K, Nout, out, means, st);
+    case kMid: return launch_means<64, 128, 2>(In, W, ldw, K, Nout, out, means, st);
+    default: return launch_means<64, 64, 2>(In, W, ldw, K, Nout, out, means, st);
+    }
 }
 
 int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout, bf16_t *Out, int kernel_id, hipStream_t st)

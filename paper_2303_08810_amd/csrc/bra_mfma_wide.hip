@@ -4,9 +4,11 @@
 // variants' stages (C = 384, 768), S = 16 on large maps, and the plain-ViT adaptation of the
 // appendix (32x32 map, S = 8, k = 12, 12 heads of 64 channels).
 //
-//   k_pool_wide   Xr[b, r, :] = mean of the region's tokens, float32            (Sec. 3.2)
-//   k_gemm_dma    Q | K | V = X Wqkv (Eq. 3), bf16 out; in the same launch Q^r | K^r = Xr [Wq | Wk] in float32: the
-//                 means are split exactly into three bf16 terms, so the products are those of the float32 computation
+//   k_gemm_means  Q | K | V = X Wqkv (Eq. 3), bf16 out, and Q^r | K^r, the means of Q and K over each region, from the
+//                 float32 results (Sec. 3.2)
+//   or, on larger maps (means_from_projection), k_pool_wide, Xr[b, r, :] = mean of the region's tokens, float32, and k_gemm_dma with
+//                 Q^r | K^r = Xr [Wq | Wk] in the launch of Q | K | V: the means are split exactly into three bf16 terms, so
+//                 the products are those of the float32 computation
 //                 (one token per region: no means, the token projection leaves float32 copies of Q and K instead)
 //   k_route_lce   rows of A^r = Q^r (K^r)^T (Eq. 4) and their top-k (Eq. 5), and LCE(V) (Eq. 7) in float32 beside them
 //   k_attn_rows (regions of up to 32 tokens) or k_attn_gen, O = the two together   (Eq. 6)
@@ -492,6 +494,29 @@ GemmRegions region_job(const Dims &D, const WideWs &w)
     return GemmRegions{w.xr, (long)D.B * D.R, 2 * D.C, {w.qr, w.kr}, D.C};
 }
 
+GemmMeans means_job(const Dims &D, const WideWs &w, int H, int W)
+{
+    return GemmMeans{{w.qr, w.kr}, D.B * D.R, D.R, D.S, D.n, D.rh, D.rw, H ? H : D.H, H ? W : D.W, 1.0f / D.n, 1.0f / D.R, 1.0f / D.S, 1.0f / D.rw};
+}
+
+// The means of Q and K out of the token projection's float32 results, whose tiles then go region by region, in the place of a pooling
+// pass and a region-level product: always the faster for bra_forward, by 5 us (a launch) on small maps and the region-level product's
+// time on larger ones.  bra_route, which has to decide on the same bits, then projects all tokens instead of their means: the
+// line lies where that takes as long.  bra_route / bra_forward before -> now (us): 1 x 28 x 28 x 384, k = 9 19.0 -> 12.4 / 33.1 -> 26.7,
+// 6 x 14 x 14 x 256 16.5 -> 11.2 / 27.8 -> 22.4, 64 x 14 x 14 x 384 30.7 -> 24.4 / 77.5 -> 66.7, 32 x 16 x 16 x 768 41.8 -> 36.1 / 123.5 ->
+// 101.4, 4 x 32 x 32 x 384 20.2 -> 14.8 / 39.9 -> 35.8; beyond: 8 x 32 x 32 x 768 32.4 -> 38.2 / 104.5 -> 99.0, 20 x 56 x 56 x 192 18.9 -> 25.6 /
+// 112.0 -> 106.6.  By millions of values and tokens per region, bra_route before -> now: 8 of C = 192 11.5 37.6 -> 37.9, of C = 384 9.6
+// 32.4 -> 33.1, of C = 768 3.0 30.7 -> 25.7, 7.8 37.1 -> 41.4; 16 4.7 18.5 -> 16.7 (C = 192), 9.4 26.4 -> 30.4 (384), 7.9 32.1 -> 40.8 (768); 64 4.7
+// 16.8 -> 16.8, 3.1 20.1 -> 17.0, 3.1 28.4 -> 25.5; 36, of which a tile of 64 rows leaves 28 idle, 2.0 15.8 -> 14.0, 4.7 16.7 -> 18.0 (192), 4.1 20.1 -> 22.8 (384).
+bool means_from_projection(const Dims &D)
+{
+    if (D.n == 1 || D.n > kMeansMaxTokens) return false;
+    const long values = (long)D.B * D.N * D.C;
+    if (D.n <= 9) return values <= (D.n <= 4 || D.C <= 384 ? 8L << 20 : 11L << 19);
+    if (D.n <= 16) return values <= 5L << 20;
+    return values <= (D.n > 32 && D.n < 60 ? 2L << 20 : 4L << 20);
+}
+
 template <int HD, int NQ>
 int launch_attn_rows_t(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
 {
@@ -558,6 +583,11 @@ int route_pooled(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideW
 int route_steps(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const WideWs &w, int32_t *Ir, float *Ar_opt,
                 hipStream_t st)
 {
+    if (means_from_projection(D)) {               // Q and K themselves are not stored
+        const int rc = gemm_means(X, Wqkv, 3 * D.C, D.C, 2 * D.C, GemmOut{{nullptr, nullptr, nullptr}, D.C, {nullptr, nullptr}, nullptr, nullptr, 0},
+                                  means_job(D, w, 0, 0), K_MFMA_ROUTE_ROWS, st);
+        return rc == BRA_OK ? route_rows(D, w.qr, w.kr, D.C, Ir, Ar_opt, st) : rc;
+    }
     if (D.n > 1) return route_pooled(D, X, Wqkv, w, Ir, Ar_opt, st);
     // one token per region: the means are the (bf16) tokens themselves, so Q^r | K^r is the plain projection of X
     // with float32 results: no pooling, no split.  The same product as in wide_forward (a sum's order does not
@@ -630,14 +660,15 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
     // copies; else the projection of the region means, in the same launch as the tokens' (on its own it was a chain of
     // 12 chunks on a few workgroups: 13.7 us at C = 768)
     const long M = (long)D.B * D.N;
-    const bool route = !Ir_in_opt, pooled = route && D.n > 1;
+    const bool route = !Ir_in_opt, means = route && means_from_projection(D), pooled = route && !means && D.n > 1;
     if (pooled) launch_pool(D, (const bf16_t *)X, w, pad, st);
     const GemmRegions rj = region_job(D, w);
     const float c_exp = D.scale * 1.4426950408889634f;
     const float q_scale = map_tail_pays(D) ? 1.0f : c_exp;     // k_attn_rows, k_attn_gen take scores in units of log2
-    float *fq = route && !pooled ? w.qr : nullptr, *fk = route && !pooled ? w.kr : nullptr;
-    int rc = gemm((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, GemmOut{{w.q, w.k, w.v}, D.C, {fq, fk}, nullptr, nullptr, 0, q_scale, pad, GemmRows{}},
-                  pooled ? &rj : nullptr, K_MFMA_QKV, st);
+    const bool copies = route && D.n == 1;
+    const GemmOut qkv = {{w.q, w.k, w.v}, D.C, {copies ? w.qr : nullptr, copies ? w.kr : nullptr}, nullptr, nullptr, 0, q_scale, pad, GemmRows{}};
+    int rc = means ? gemm_means((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, D.C, 3 * D.C, qkv, means_job(D, w, H, W), K_MFMA_QKV, st)
+                   : gemm((const bf16_t *)X, (const bf16_t *)Wqkv, 3 * D.C, M, D.C, 3 * D.C, qkv, pooled ? &rj : nullptr, K_MFMA_QKV, st);
     if (rc != BRA_OK) return rc;
     AttnArgs A = {};
     bool adds = false;
