@@ -193,6 +193,10 @@ __device__ __forceinline__ void region_row(const GemmMeans &g, int tile, int row
     if (y < g.H && x < g.W) stored = ((b0 + over) * g.H + y) * g.W + x;
 }
 
+// How far the pieces of row `row` of a transposed W are turned: differently for the 8 rows that 8 lanes next to each other read, which
+// differ in bits 0, 1 and 3 (see fragments()).
+__device__ __forceinline__ int bt_turn(int row) { return row % 4 + row / 8 % 2 * 4; }
+
 // Rows whose sums a wavefront forms in registers: aligned groups of a tile's rows that lie in one region.
 __device__ __forceinline__ int means_group(int n) { return n % 16 == 0 ? 16 : n % 4 == 0 ? 4 : 1; }
 
@@ -222,7 +226,7 @@ __device__ __forceinline__ f32x4 quad_sums(const f32x16 &v, int c)
 // the columns that have means are added up over aligned groups of 16 or 4 rows in registers (means_group()), where that is less
 // than a region the groups' sums, or with an odd number of rows the results, meet in LDS: the order does not depend on the tile.  All by way of
 // LDS it took 1 us more of 64 x 14 x 14 x 384's layer (68.5 -> 67.0) and of 8 x 32 x 32 x 768's bra_route (39.2 -> 38.3).
-template <int BM, int BN, int NB, bool BT, bool EXT, bool MEANS = false>
+template <int BM, int BN, int NB, bool BT, bool EXT, bool MEANS = false, bool BASED = false>
 __device__ __forceinline__ void dma_tile(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int M, int K, int Nout,
                                          const GemmOut &out, int block, bf16_t *lds, const GemmMeans *means = nullptr)
 {
@@ -241,11 +245,17 @@ __device__ __forceinline__ void dma_tile(const bf16_t *__restrict__ In, const bf
     }
 
     constexpr int LA = BM / 32, LB = BN / 32;     // direct loads of a wavefront per chunk
-    const bf16_t *ap[LA], *bp[LB];
+    // W by bytes from the chunk's first row, and with BASED In from the tile's.  Beside the region-level product of K >= 512 that is
+    // faster (8 x 32 x 32 x 768: the launch 41 us for 47, the layer 108.7 -> 104.5; 16 x 21 x 35 x 512 88.9 -> 86.1), with K = 384 and less it is
+    // not always (64 x 16 x 24 x 384 123.8 -> 125.7, 20 x 56 x 56 x 192 111.7 -> 110.6), alone it is slower (8 x 32 x 32 x 768 with a given index 96.7 ->
+    // 100.8, gradients of 64 x 14 x 14 x 384 167 -> 176)
+    const bf16_t *ap[LA], *abase = In + (size_t)(BASED ? m0 : 0) * K, *bbase = W;
+    unsigned aoff[LA], boff[LB];
 #pragma unroll
     for (int u = 0; u < LA; ++u) {
         const int row = 8 * (wave * LA + u) + lane / 8, piece = (lane % 8) ^ (row % 8);
         ap[u] = In + (size_t)(MEANS ? 0 : min(m0 + row, M - 1)) * K + 8 * piece;
+        aoff[u] = 2 * ((min(m0 + row, M - 1) - m0) * K + 8 * piece);
         if constexpr (MEANS) {
             const int at = rows[BM + row];
             ap[u] = (at >= 0 ? In + (size_t)at * K : zero_row) + 8 * piece;
@@ -258,23 +268,27 @@ __device__ __forceinline__ void dma_tile(const bf16_t *__restrict__ In, const bf
 #pragma unroll
     for (int u = 0; u < LB; ++u) {
         if (BT) {
-            const int row = 8 * (wave * LB + u) + lane / 8, piece = (lane % 8) ^ (row % 8);
-            bp[u] = W + (size_t)min(o0 + row, Nout - 1) * ldw + 8 * piece;
+            const int row = 8 * (wave * LB + u) + lane / 8, piece = (lane % 8) ^ bt_turn(row);
+            boff[u] = 2 * ((min(o0 + row, Nout - 1) - o0) * ldw + 8 * piece);
             continue;
         }
         const int k = RPI * (wave * LB + u) + lane / CH;
         const int piece = (lane % CH) ^ (BN == 128 ? 4 * (k % 4) : 4 * (k / 2 % 2));
-        bp[u] = W + (size_t)k * ldw + min(o0 + 8 * piece, Nout - 8);
+        boff[u] = 2 * (k * ldw + min(o0 + 8 * piece, Nout - 8));
     }
+    if (BT) bbase += (size_t)o0 * ldw;
     const unsigned base = lds_address(lds);
     auto request = [&](int chunk, int buffer) {
         const int k0 = 64 * chunk;
         const unsigned at = base + buffer * (AE + BE) * 2;
         lds_reads_done();
 #pragma unroll
-        for (int u = 0; u < LA; ++u) load_to_lds_untracked(ap[u] + k0, at + 1024 * (wave * LA + u));
+        for (int u = 0; u < LA; ++u) {
+            if (!BASED) load_to_lds_untracked(ap[u] + k0, at + 1024 * (wave * LA + u));
+            else load_to_lds_untracked(abase + k0, aoff[u], at + 1024 * (wave * LA + u));
+        }
 #pragma unroll
-        for (int u = 0; u < LB; ++u) load_to_lds_untracked(bp[u] + (BT ? (size_t)k0 : (size_t)k0 * ldw), at + AE * 2 + 1024 * (wave * LB + u));
+        for (int u = 0; u < LB; ++u) load_to_lds_untracked(bbase + (BT ? (size_t)k0 : (size_t)k0 * ldw), boff[u], at + AE * 2 + 1024 * (wave * LB + u));
     };
     constexpr int MT = BM / 64, NT = BN / 64;     // 32 x 32 tiles of a wavefront
     const int wm = (wave / 2) * (BM / 2), wn = (wave % 2) * (BN / 2);
@@ -299,7 +313,7 @@ __device__ __forceinline__ void dma_tile(const bf16_t *__restrict__ In, const bf
             if (BT) {
                 // operand row c is output c with its two middle bits exchanged
                 const int row = wn + 32 * nt + (c & 0x13) + ((c & 4) << 1) + ((c & 8) >> 1);
-                wf[nt] = *(const bf16x8 *)(Bs + row * 64 + 8 * ((2 * ks + h) ^ (row % 8)));
+                wf[nt] = *(const bf16x8 *)(Bs + row * 64 + 8 * ((2 * ks + h) ^ bt_turn(row)));
                 continue;
             }
             u32x2 r[2];
@@ -453,7 +467,7 @@ __device__ __forceinline__ void dma_tile(const bf16_t *__restrict__ In, const bf
     }
 }
 
-template <int BM, int BN, int NB, bool REGIONS, bool BT, bool EXT>
+template <int BM, int BN, int NB, bool REGIONS, bool BT, bool EXT, bool BASED>
 __global__ __launch_bounds__(256, BM == 64 && BN == 64 ? 3 : 2) void k_gemm_dma(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw,
                                                   int M, int K, int Nout, GemmOut out, GemmRegions reg, int reg_blocks)
 {
@@ -464,7 +478,7 @@ __global__ __launch_bounds__(256, BM == 64 && BN == 64 ? 3 : 2) void k_gemm_dma(
         gemm64<2>(reg, W, ldw, K, blockIdx.x, lds + 3 * 64 * kGemmPitch, planes);
         return;
     }
-    dma_tile<BM, BN, NB, BT, EXT>(In, W, ldw, M, K, Nout, out, swizzled((int)blockIdx.x - reg_blocks, (int)gridDim.x - reg_blocks), lds);
+    dma_tile<BM, BN, NB, BT, EXT, false, BASED>(In, W, ldw, M, K, Nout, out, swizzled((int)blockIdx.x - reg_blocks, (int)gridDim.x - reg_blocks), lds);
 }
 
 template <int BM, int BN, int NB>
@@ -500,16 +514,16 @@ bool opt_in(K kernel, bool &done)
     return done;
 }
 
-template <int BM, int BN, int NB, bool REGIONS, bool BT, bool EXT>
+template <int BM, int BN, int NB, bool REGIONS, bool BT, bool EXT, bool BASED = false>
 int launch_dma_t(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out,
                const GemmRegions &reg, hipStream_t st)
 {
     static bool opted = false;
-    if (!opt_in(k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT>, opted)) return BRA_ERR_LAUNCH;
+    if (!opt_in(k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT, BASED>, opted)) return BRA_ERR_LAUNCH;
     const long blocks = tile_blocks<BM, BN>(M, Nout);
     const long rb = REGIONS ? region_blocks(reg) : 0;
     if (blocks + rb > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT>), dim3((unsigned)(blocks + rb)), dim3(256),
+    hipLaunchKernelGGL((k_gemm_dma<BM, BN, NB, REGIONS, BT, EXT, BASED>), dim3((unsigned)(blocks + rb)), dim3(256),
                        std::max(ring_bytes<BM, BN, NB>(), REGIONS ? kGemm64Bytes : 0), st, In, W, ldw, (int)M, K, Nout, out, reg, (int)rb);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
@@ -521,6 +535,9 @@ int launch_dma(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int No
     if constexpr (!BT) {
         if (out.bias || out.gelu || out.res || out.in_rows.Hp || out.out_rows.Hp)
             return launch_dma_t<BM, BN, NB, REGIONS, false, true>(In, W, ldw, M, K, Nout, out, reg, st);
+    }
+    if constexpr (REGIONS && BM == 128) {
+        if (K >= 512) return launch_dma_t<BM, BN, NB, true, BT, false, true>(In, W, ldw, M, K, Nout, out, reg, st);
     }
     return launch_dma_t<BM, BN, NB, REGIONS, BT, false>(In, W, ldw, M, K, Nout, out, reg, st);
 }
@@ -738,28 +755,55 @@ int launch_proj(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int N
 // Part[share][a][n] = sum over the share's tokens t of A[t][a] B[t][n] (the weight gradients dWqkv = X^T dQKV and
 // dWo = O^T dY, both in one launch): a 128 x 128 block of the output per workgroup, 64 tokens at a time straight into one of
 // two LDS buffers; both operands by transposing reads (pieces exchanged as for W above).
-__device__ __forceinline__ void tn_block(const GemmTn &J, int block, long M, int share_tokens, bf16_t *A0, bf16_t *A1,
-                                         bf16_t *B0, bf16_t *B1)
+// Bound by the loads: a share's rows are read by all blocks of it, 236 MB for 58 of 64 x 14 x 14 x 384.  All blocks of a share on one XCD, loads that
+// the compiler does not count and no address arithmetic beyond a base per chunk: 36.5 -> 22 us (29 with the XCD's blocks alone;
+// the matrix instructions take 7).  A ring of four buffers of 32 tokens was no faster, one workgroup per compute unit with four of 64 31.
+constexpr int kTnTokens = 64;
+constexpr size_t kTnBytes = (size_t)2 * 2 * kTnTokens * 128 * 2;
+
+// block: of `blocks` (a multiple of 8), those of both products of a share one after the other, so that an XCD's L2 has the rows of its
+// shares.
+__device__ __forceinline__ void tn_block(const GemmTn &J0, const GemmTn &J1, int block, int blocks, long M, int share_tokens, bf16_t *lds)
 {
-    const int nb = (J.N + 127) / 128, ab = (J.KA + 127) / 128;
-    const int n0 = 128 * (block % nb), a0 = 128 * (block / nb % ab), share = block / (nb * ab);
+    auto blocks_of = [](const GemmTn &J) { return ((J.N + 127) / 128) * ((J.KA + 127) / 128); };
+    const int first = blocks_of(J0), each = first + blocks_of(J1), at = swizzled(block, blocks), share = at / each, rest = at - share * each;
+    const GemmTn &J = rest < first ? J0 : J1;
+    block = rest < first ? rest : rest - first;
+    constexpr int TOK = kTnTokens, LOADS = TOK / 16;       // direct loads of each operand, by a wavefront
+    const int nb = (J.N + 127) / 128;
+    const int n0 = 128 * (block % nb), a0 = 128 * (block / nb);
     const long t_begin = (long)share * share_tokens, t_end = min(M, t_begin + share_tokens);
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, h = lane / 32, c = lane % 32;
+    if (t_begin >= M) return;                     // the grid is rounded up
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, h = lane / 32, c = lane % 32;
     const int ldl = lane / 16;                                // row of a direct load (4 rows of 16 pieces)
-    const bf16_t *ap[4], *bp[4];
+    const int piece = (lane % 16) ^ (4 * (ldl % 4));
+    const int row0 = 4 * wave * LOADS + ldl, acol = min(a0 + 8 * piece, J.KA - 8), bcol = min(n0 + 8 * piece, J.N - 8);
+    const bf16_t *abase = J.A + t_begin * J.lda, *bbase = J.Bm + t_begin * J.ldb;
+    unsigned aoff[LOADS], boff[LOADS];            // bytes from the chunk's first row
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int k = 4 * (wave * 4 + u) + ldl, piece = (lane % 16) ^ (4 * (k % 4));
-        ap[u] = J.A + min(a0 + 8 * piece, J.KA - 8);
-        bp[u] = J.Bm + min(n0 + 8 * piece, J.N - 8);
+    for (int u = 0; u < LOADS; ++u) {
+        aoff[u] = 2 * ((row0 + 4 * u) * J.lda + acol);
+        boff[u] = 2 * ((row0 + 4 * u) * J.ldb + bcol);
     }
-    auto request = [&](long t0, bf16_t *As, bf16_t *Bs) {
+    const unsigned base = lds_address(lds) + 1024 * LOADS * wave;
+    // the chunks one after the other: the bases move along
+    auto request = [&](int chunk) {
+        const unsigned at = base + chunk % 2 * (2 * TOK * 128 * 2);
+        lds_reads_done();
+        const int there = (int)min((long)TOK, t_end - t_begin - (long)TOK * chunk);      // rows; beyond, the last one is repeated
+        if (there < TOK)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const size_t t = min(t0 + 4 * (wave * 4 + u) + ldl, t_end - 1);
-            load_to_lds(ap[u] + t * J.lda, As + 512 * (wave * 4 + u));
-            load_to_lds(bp[u] + t * J.ldb, Bs + 512 * (wave * 4 + u));
+            for (int u = 0; u < LOADS; ++u) {
+                aoff[u] = 2 * (min(row0 + 4 * u, there - 1) * J.lda + acol);
+                boff[u] = 2 * (min(row0 + 4 * u, there - 1) * J.ldb + bcol);
+            }
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u) {
+            load_to_lds_untracked(abase, aoff[u], at + 1024 * u);
+            load_to_lds_untracked(bbase, boff[u], at + TOK * 128 * 2 + 1024 * u);
         }
+        abase += (size_t)TOK * J.lda;
+        bbase += (size_t)TOK * J.ldb;
     };
     const int wa = (wave / 2) * 64, wn = (wave % 2) * 64;
     f32x16 acc[2][2];
@@ -790,8 +834,8 @@ __device__ __forceinline__ void tn_block(const GemmTn &J, int block, long M, int
         };
         fragments(0);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            if (ks < 3) fragments(ks + 1);
+        for (int ks = 0; ks < TOK / 16; ++ks) {
+            if (ks + 1 < TOK / 16) fragments(ks + 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int x = 0; x < 2; ++x)
@@ -800,27 +844,21 @@ __device__ __forceinline__ void tn_block(const GemmTn &J, int block, long M, int
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // tokens past the end add nothing: their rows of A are blanked once the chunk has arrived
-    auto blank = [&](long t0, bf16_t *As) {
-        if (t0 + 64 > t_end) {
-            for (int e = tid; e < 64 * 16; e += 256)
-                if (t0 + e / 16 >= t_end) *(u32x4 *)(As + 8 * e) = u32x4{0u, 0u, 0u, 0u};
+    const int chunks = (int)((t_end - t_begin + TOK - 1) / TOK);
+    request(0);
+    for (int k = 0; k < chunks; ++k) {
+        arrive_barrier();                          // the chunk has arrived; the other buffer has been read
+        if (k + 1 < chunks) request(k + 1);
+        bf16_t *As = lds + k % 2 * (2 * TOK * 128);
+        // tokens past the end add nothing: their rows of A are blanked
+        if (t_begin + (long)TOK * (k + 1) > t_end) {
+            for (int e = tid; e < TOK * 16; e += 256)
+                if (t_begin + (long)TOK * k + e / 16 >= t_end) *(u32x4 *)(As + 8 * e) = u32x4{0u, 0u, 0u, 0u};
             __syncthreads();
         }
-    };
-    request(t_begin, A0, B0);
-    for (long t0 = t_begin; t0 < t_end; t0 += 128) {
-        arrive_barrier();
-        if (t0 + 64 < t_end) request(t0 + 64, A1, B1);
-        blank(t0, A0);
-        multiply(A0, B0);
-        arrive_barrier();
-        if (t0 + 128 < t_end) request(t0 + 128, A0, B0);
-        if (t0 + 64 < t_end) {
-            blank(t0 + 64, A1);
-            multiply(A1, B1);
-        }
+        multiply(As, As + TOK * 128);
     }
+    products_done();
     float *out = J.Part + (size_t)share * J.KA * J.N;
 #pragma unroll
     for (int x = 0; x < 2; ++x)
@@ -829,28 +867,24 @@ __device__ __forceinline__ void tn_block(const GemmTn &J, int block, long M, int
             const int n = n0 + wn + 32 * y + c;
             if (n >= J.N) continue;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int a = a0 + wa + 32 * x + 8 * (e / 4) + 4 * h + e % 4;
-                if (a < J.KA) out[(size_t)a * J.N + n] = acc[x][y][e];
+            for (int e = 0; e < 16; e += 4) {
+                const int a = a0 + wa + 32 * x + 2 * e + 4 * h;
+                if (a >= J.KA) continue;              // KA is a multiple of 8
+#pragma unroll
+                for (int d = 0; d < 4; ++d) out[(size_t)(a + d) * J.N + n] = acc[x][y][e + d];
             }
         }
 }
 
-__global__ __launch_bounds__(256, 2) void k_gemm_tn(GemmTn J0, GemmTn J1, int blocks0, long M, int share_tokens)
+__global__ __launch_bounds__(256, 2) void k_gemm_tn(GemmTn J0, GemmTn J1, long M, int share_tokens)
 {
-    __shared__ __attribute__((aligned(16))) bf16_t A0[64 * 128];
-    __shared__ __attribute__((aligned(16))) bf16_t A1[64 * 128];
-    __shared__ __attribute__((aligned(16))) bf16_t B0[64 * 128];
-    __shared__ __attribute__((aligned(16))) bf16_t B1[64 * 128];
-    const bool second = (int)blockIdx.x >= blocks0;
-    tn_block(second ? J1 : J0, second ? (int)blockIdx.x - blocks0 : (int)blockIdx.x, M, share_tokens, A0, A1, B0, B1);
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    tn_block(J0, J1, blockIdx.x, gridDim.x, M, share_tokens, (bf16_t *)lds);
 }
 
 // Out = In Wt^T and both contractions over the tokens in one launch: dX, dWqkv and dWo, once dQ, dK and dV are there.
-constexpr size_t kTnBytes = 4 * 64 * 128 * 2;
-
 template <int BM, int BN>
-__global__ __launch_bounds__(256, 2) void k_gemm_bt_tn(GemmTn J0, GemmTn J1, int blocks0, int tiles, int share_tokens, const bf16_t *__restrict__ In,
+__global__ __launch_bounds__(256, 2) void k_gemm_bt_tn(GemmTn J0, GemmTn J1, int tiles, int share_tokens, const bf16_t *__restrict__ In,
                                                        const bf16_t *__restrict__ Wt, int ldw, int M, int K, int Nout, GemmOut out)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -859,20 +893,18 @@ __global__ __launch_bounds__(256, 2) void k_gemm_bt_tn(GemmTn J0, GemmTn J1, int
         dma_tile<BM, BN, 2, true, false>(In, Wt, ldw, M, K, Nout, out, swizzled(blockIdx.x, tiles), lds);
         return;
     }
-    const int block = (int)blockIdx.x - tiles;
-    const bool second = block >= blocks0;
-    tn_block(second ? J1 : J0, second ? block - blocks0 : block, M, share_tokens, lds, lds + 8192, lds + 2 * 8192, lds + 3 * 8192);
+    tn_block(J0, J1, (int)blockIdx.x - tiles, (int)gridDim.x - tiles, M, share_tokens, lds);
 }
 
 template <int BM, int BN>
-int launch_bt_tn(const GemmTn &J0, const GemmTn &J1, long blocks0, long tn_blocks, int share_tokens, const GemmHalf &b, long M, int K, hipStream_t st)
+int launch_bt_tn(const GemmTn &J0, const GemmTn &J1, long tn_blocks, int share_tokens, const GemmHalf &b, long M, int K, hipStream_t st)
 {
     static bool opted = false;
     if (!opt_in(k_gemm_bt_tn<BM, BN>, opted)) return BRA_ERR_LAUNCH;
     const long blocks = tile_blocks<BM, BN>(M, b.Nout);
     if (tn_blocks + blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     hipLaunchKernelGGL((k_gemm_bt_tn<BM, BN>), dim3((unsigned)(tn_blocks + blocks)), dim3(256), (std::max(kTnBytes, ring_bytes<BM, BN, 2>())), st,
-                       J0, J1, (int)blocks0, (int)blocks, share_tokens, b.In, b.W, b.ldw, (int)M, K, b.Nout, b.out);
+                       J0, J1, (int)blocks, share_tokens, b.In, b.W, b.ldw, (int)M, K, b.Nout, b.out);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -948,6 +980,13 @@ static int tn_share_tokens(long M, int KA0, int N0, int KA1, int N1)
     return (int)((chunks + want - 1) / want * 64);
 }
 
+// Workgroups of both products, a multiple of 8.
+static long tn_blocks(const GemmTn &J0, const GemmTn &J1, int shares)
+{
+    auto blocks = [](const GemmTn &J) { return (long)((J.KA + 127) / 128) * ((J.N + 127) / 128); };
+    return ((blocks(J0) + blocks(J1)) * shares + 7) / 8 * 8;
+}
+
 int gemm_tn_shares(long M, int KA0, int N0, int KA1, int N1)
 {
     const int t = tn_share_tokens(M, KA0, N0, KA1, N1);
@@ -958,9 +997,10 @@ int gemm_tn(const GemmTn &J0, const GemmTn &J1, long M, int kernel_id, hipStream
 {
     if (M < 1 || (J0.KA | J0.N | J1.KA | J1.N | J0.lda | J0.ldb | J1.lda | J1.ldb) % 8) return BRA_ERR_UNSUPPORTED;
     const int tokens = tn_share_tokens(M, J0.KA, J0.N, J1.KA, J1.N), shares = gemm_tn_shares(M, J0.KA, J0.N, J1.KA, J1.N);
-    auto blocks = [&](const GemmTn &J) { return (long)((J.KA + 127) / 128) * ((J.N + 127) / 128) * shares; };
+    static bool opted = false;
+    if (!opt_in(k_gemm_tn, opted)) return BRA_ERR_LAUNCH;
     ProfScope ps(st, kernel_id);
-    hipLaunchKernelGGL(k_gemm_tn, dim3((unsigned)(blocks(J0) + blocks(J1))), dim3(256), 0, st, J0, J1, (int)blocks(J0), M, tokens);
+    hipLaunchKernelGGL(k_gemm_tn, dim3((unsigned)tn_blocks(J0, J1, shares)), dim3(256), kTnBytes, st, J0, J1, M, tokens);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -976,12 +1016,11 @@ int gemm_bt_tn(const GemmTn &J0, const GemmTn &J1, const GemmHalf &b, long M, in
     }
     if (!sizes_ok(M, K, b.Nout) || (J0.KA | J0.N | J1.KA | J1.N | J0.lda | J0.ldb | J1.lda | J1.ldb) % 8) return BRA_ERR_UNSUPPORTED;
     const int tokens = tn_share_tokens(M, J0.KA, J0.N, J1.KA, J1.N), shares = gemm_tn_shares(M, J0.KA, J0.N, J1.KA, J1.N);
-    auto blocks = [&](const GemmTn &J) { return (long)((J.KA + 127) / 128) * ((J.N + 127) / 128) * shares; };
-    const long b0 = blocks(J0), tn = b0 + blocks(J1);
+    const long tn = tn_blocks(J0, J1, shares);
     ProfScope ps(st, kernel_id);
     // that few tiles are never the wide ones
-    if (pick_tile(M, K, b.Nout, 0, 0) == kNarrow) return launch_bt_tn<64, 64>(J0, J1, b0, tn, tokens, b, M, K, st);
-    return launch_bt_tn<64, 128>(J0, J1, b0, tn, tokens, b, M, K, st);
+    if (pick_tile(M, K, b.Nout, 0, 0) == kNarrow) return launch_bt_tn<64, 64>(J0, J1, tn, tokens, b, M, K, st);
+    return launch_bt_tn<64, 128>(J0, J1, tn, tokens, b, M, K, st);
 }
 
 int gemm_regions(const GemmRegions &r, const bf16_t *W, int ldw, int K, int kernel_id, hipStream_t st)
