@@ -122,6 +122,7 @@ __device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int bloc
     const int ntiles = (J.N + BN - 1) / BN;
     const long m0 = (long)(block / ntiles) * kGemmBM;
     const int n0 = (block % ntiles) * BN;
+    if (m0 >= J.M) return;                       // grids are rounded up to multiples of 8
     constexpr int NA = kGemmBM * BK / 4 / 256, NB = BN * BK / 4 / 256;
     f32x4 ra[NA], rb[NB];
     // Rows past the end repeat the last one (never stored).  k past the end is blanked where the values go to LDS:
@@ -221,6 +222,7 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmJob<TA, bf16_t, TO> &J,
     const int ntiles = (J.N + BN - 1) / BN;
     const long m0 = (long)(block / ntiles) * kGemmBM;
     const int n0 = (block % ntiles) * BN;
+    if (m0 >= J.M) return;                       // grids are rounded up to multiples of 8
     typename std::conditional<SPLIT, f32x4, u32x2>::type ra[NA];
     u32x2 rb[NB];
     auto fetch = [&](int k0) {               // past the end: as in gemm_tile
@@ -316,10 +318,12 @@ constexpr size_t gemm_lds_floats()
     return f32 > terms ? f32 : terms;
 }
 
+// Of `blocks` workgroups.  On the bf16 instruction, where memory is the bound, those of the same rows on one XCD (layer of 50 x 28 x 28 x 96
+// bf16 76.0 -> 74.9 us, 62 x 16 x 16 x 96 56.5 -> 54.7); on the float32 one that was slower (2 x 64 x 64 x 128 49.4 -> 53.1).
 template <bool BT, bool VEC, int BN, typename TA, typename TB, typename TO>
-__device__ __forceinline__ void any_gemm_tile(const GemmJob<TA, TB, TO> &J, int block, float *smem)
+__device__ __forceinline__ void any_gemm_tile(const GemmJob<TA, TB, TO> &J, int block, int blocks, float *smem)
 {
-    if constexpr (VEC && std::is_same<TB, bf16_t>::value) gemm_tile_bf16<BT, BN>(J, block, (bf16_t *)smem);
+    if constexpr (VEC && std::is_same<TB, bf16_t>::value) gemm_tile_bf16<BT, BN>(J, mfma::swizzled(block, blocks), (bf16_t *)smem);
     else gemm_tile<BT, VEC, BN>(J, block, smem);
 }
 
@@ -329,8 +333,8 @@ template <bool BT, bool VEC, int BN, typename TA, typename TB, typename TO>
 __global__ __launch_bounds__(256) void k_gemm(GemmJob<TA, TB, TO> J0, GemmJob<float, TB, float> J1, int blocks0)
 {
     __shared__ __attribute__((aligned(16))) float smem[gemm_lds_floats<BN, BT>()];
-    if ((int)blockIdx.x < blocks0) any_gemm_tile<BT, VEC, BN>(J0, blockIdx.x, smem);
-    else any_gemm_tile<BT, VEC, BN>(J1, (int)blockIdx.x - blocks0, smem);
+    if ((int)blockIdx.x < blocks0) any_gemm_tile<BT, VEC, BN>(J0, blockIdx.x, blocks0, smem);
+    else any_gemm_tile<BT, VEC, BN>(J1, (int)blockIdx.x - blocks0, (int)gridDim.x - blocks0, smem);
 }
 
 // J0 and a product with its matrix transposed (Q, K, V = X Wqkv and dO = dY Wo^T of the gradients) in one launch.
@@ -339,8 +343,8 @@ __global__ __launch_bounds__(256) void k_gemm_both(GemmJob<T, T, float> J0, Gemm
 {
     constexpr size_t n0 = gemm_lds_floats<BN, false>(), n1 = gemm_lds_floats<BN, true>();
     __shared__ __attribute__((aligned(16))) float smem[n0 > n1 ? n0 : n1];
-    if ((int)blockIdx.x < blocks0) any_gemm_tile<false, VEC, BN>(J0, blockIdx.x, smem);
-    else any_gemm_tile<true, VEC, BN>(J1, (int)blockIdx.x - blocks0, smem);
+    if ((int)blockIdx.x < blocks0) any_gemm_tile<false, VEC, BN>(J0, blockIdx.x, blocks0, smem);
+    else any_gemm_tile<true, VEC, BN>(J1, (int)blockIdx.x - blocks0, (int)gridDim.x - blocks0, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -437,8 +441,10 @@ __global__ __launch_bounds__(HPW == 1 ? 512 : 256, DP == 32 ? 4 : 2) void k_atte
     constexpr int P = L::P, KB = L::KB, CW = L::CW, KT = KB / 16, NS = DP / 16;
     __shared__ __attribute__((aligned(16))) float Ks[KB * P];
     __shared__ __attribute__((aligned(16))) float Vs[KB * P];
-    const int hg = blockIdx.x % hgroups, qt = (blockIdx.x / hgroups) % qtiles;
-    const int reg = (blockIdx.x / (hgroups * qtiles)) % D.R, b = blockIdx.x / (hgroups * qtiles * D.R);
+    // workgroups of an image and head group on one XCD (layer of 32 x 28 x 28 x 128, k = 4 85.4 -> 82.7 us)
+    const int block = mfma::swizzled_block(), qt = block % qtiles, reg = (block / qtiles) % D.R;
+    const int hg = (block / (qtiles * D.R)) % hgroups, b = block / (qtiles * D.R * hgroups);
+    if (b >= D.B) return;
     const int T = HPW == 1 ? (int)blockDim.x : 256, tph = HPW == 1 ? T / kWave : L::TPH;      // query tiles
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C3 = 3 * D.C, kn = D.kn, hl = HPW == 1 ? 0 : wave / L::TPH, h = hg * HPW + hl;
@@ -575,8 +581,9 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q(const float *__restrict__ QK
         lce::lce_grad_block<VEC ? 2 : 1, false>(J, D, mfma::swizzled(wg, wgs), lds);
         return;
     }
-    const int hg = wg % hgroups, qt = (wg / hgroups) % qtiles;
-    const int reg = (wg / (hgroups * qtiles)) % D.R, b = wg / (hgroups * qtiles * D.R);
+    wg = mfma::swizzled(wg, wgs);
+    const int qt = wg % qtiles, reg = (wg / qtiles) % D.R, hg = (wg / (qtiles * D.R)) % hgroups, b = wg / (qtiles * D.R * hgroups);
+    if (b >= D.B) return;
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C3 = 3 * D.C, kn = D.kn, nblocks = (kn + KB - 1) / KB, hl = wave / L::TPH, h = hg * HPW + hl;
     const size_t itok = (size_t)b * D.N;
@@ -743,8 +750,9 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const float *__restrict__ Q
         lce::lce_block<VEC ? 2 : 1, true, 256>(J, D, mfma::swizzled(wg, wgs), lds);
         return;
     }
-    const int hg = wg % hgroups, kt = (wg / hgroups) % ktiles;
-    const int reg = (wg / (hgroups * ktiles)) % D.R, b = wg / (hgroups * ktiles * D.R);
+    wg = mfma::swizzled(wg, wgs);
+    const int kt = wg % ktiles, reg = (wg / ktiles) % D.R, hg = (wg / (ktiles * D.R)) % hgroups, b = wg / (ktiles * D.R * hgroups);
+    if (b >= D.B) return;
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C3 = 3 * D.C, hl = wave / L::TPH, h = hg * HPW + hl;
     const size_t itok = (size_t)b * D.N;
@@ -856,16 +864,16 @@ struct TnJob {
     const TA *A;
     const TB *Bm;
     float *Part;
-    int lda, ldb, KA, N, blocks;
+    int lda, ldb, KA, N;
+    __host__ __device__ int blocks() const { return ((N + 63) / 64) * ((KA + 63) / 64); }      // of a share
 };
 
 template <bool VEC, typename TA, typename TB>
-__device__ __forceinline__ void tn_tile(const TnJob<TA, TB> &J, int block, long M, int share_tokens, float *smem)
+__device__ __forceinline__ void tn_tile(const TnJob<TA, TB> &J, int block, int share, long M, int share_tokens, float *smem)
 {
     constexpr int P = 64 + 4, TT = 32, NL = TT * 16 / 256;
     float *As = smem, *Bs = smem + TT * P;
-    const int nb = (J.N + 63) / 64, ab = (J.KA + 63) / 64;
-    const int n0 = 64 * (block % nb), a0 = 64 * (block / nb % ab), share = block / (nb * ab);
+    const int nb = (J.N + 63) / 64, n0 = 64 * (block % nb), a0 = 64 * (block / nb);
     const long t_begin = (long)share * share_tokens, t_end = min(M, t_begin + share_tokens);
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     f32x4 ra[NL], rb[NL], acc[2][2];
@@ -924,14 +932,20 @@ __device__ __forceinline__ void tn_tile(const TnJob<TA, TB> &J, int block, long 
 
 // What is left once dQ, dK and dV are there, in one launch: dX = [dQ | dK | dV] Wqkv^T (J), dWqkv and dWo (J0, J1).
 template <bool VEC, int BN, typename T>
-__global__ __launch_bounds__(256) void k_gemm_end(TnJob<T, float> J0, TnJob<float, T> J1, long M, int share_tokens, GemmJob<float, T, T> J)
+__global__ __launch_bounds__(256) void k_gemm_end(TnJob<T, float> J0, TnJob<float, T> J1, long M, int share_tokens, int tn_blocks, GemmJob<float, T, T> J)
 {
     constexpr size_t n = gemm_lds_floats<BN, true>(), tn = 2 * 32 * (64 + 4);
     __shared__ __attribute__((aligned(16))) float smem[n > tn ? n : tn];
-    const int block = (int)blockIdx.x - J0.blocks - J1.blocks;
-    if (block >= 0) any_gemm_tile<true, VEC, BN>(J, block, smem);
-    else if ((int)blockIdx.x < J0.blocks) tn_tile<VEC>(J0, blockIdx.x, M, share_tokens, smem);
-    else tn_tile<VEC>(J1, (int)blockIdx.x - J0.blocks, M, share_tokens, smem);
+    const int block = (int)blockIdx.x - tn_blocks;
+    if (block >= 0) {
+        any_gemm_tile<true, VEC, BN>(J, block, (int)gridDim.x - tn_blocks, smem);
+        return;
+    }
+    // the blocks of a share one after the other, so that an XCD's L2 has its tokens
+    const int at = mfma::swizzled(blockIdx.x, tn_blocks), each = J0.blocks() + J1.blocks(), share = at / each, rest = at - share * each;
+    if ((long)share * share_tokens >= M) return;
+    if (rest < J0.blocks()) tn_tile<VEC>(J0, rest, share, M, share_tokens, smem);
+    else tn_tile<VEC>(J1, rest - J0.blocks(), share, M, share_tokens, smem);
 }
 
 }  // namespace f32

@@ -160,13 +160,17 @@ bool narrow_tiles(long M, int N, int N1 = 0)
     return std::is_same<TB, float>::value || N <= 64 || mt * ((N + 127) / 128 + (N1 + 127) / 128) < 512;
 }
 
+// Workgroups of so many tiles: those with a bf16 matrix are dealt out by XCD.
+template <typename TB>
+long tile_blocks(long tiles) { return std::is_same<TB, float>::value ? tiles : (tiles + 7) / 8 * 8; }
+
 // One or two products in one launch (J1: NULL for one).
 template <bool BT, bool VEC, typename TA, typename TB, typename TO>
 int launch_gemm_vec(const f32::GemmJob<TA, TB, TO> &J0, const f32::GemmJob<float, TB, float> *J1, hipStream_t st)
 {
     const bool narrow = narrow_tiles<TB>(J0.M, J0.N);
     const int bn = narrow ? 64 : 128;
-    auto blocks = [&](long M, int N) { return (M + f32::kGemmBM - 1) / f32::kGemmBM * ((N + bn - 1) / bn); };
+    auto blocks = [&](long M, int N) { return tile_blocks<TB>((M + f32::kGemmBM - 1) / f32::kGemmBM * ((N + bn - 1) / bn)); };
     const long b0 = blocks(J0.M, J0.N), b1 = J1 ? blocks(J1->M, J1->N) : 0;
     if (b0 + b1 > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     const f32::GemmJob<float, TB, float> none = {};
@@ -280,7 +284,7 @@ int launch_attention_t(const Dims &D, const float *qkv, const int32_t *Ir, float
         const int qt = f32::AttnShape<DP, HPW>::QT;
         qtiles = (D.n + qt - 1) / qt;
     }
-    const long blocks = (long)D.B * D.R * hgroups * qtiles;
+    const long blocks = ((long)D.B * D.R * hgroups * qtiles + 7) / 8 * 8;
     if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     hipLaunchKernelGGL((f32::k_attention<DP, HPW, VEC>), dim3((unsigned)blocks), dim3(64 * waves), 0, st, qkv, Ir, o, D, hgroups,
                        qtiles, adds);
@@ -534,7 +538,7 @@ template <int DP, int HPW, bool VEC>
 int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lce::Taps &taps, hipStream_t st)
 {
     const int hgroups = (D.heads + HPW - 1) / HPW, qt = f32::AttnShape<DP, HPW>::QT, tiles = (D.n + qt - 1) / qt;
-    const long blocks = (long)D.B * D.R * hgroups * tiles;
+    const long blocks = ((long)D.B * D.R * hgroups * tiles + 7) / 8 * 8;
     // The passes of the depth-wise convolution's gradients lie behind the workgroups of the attention: the one with the tap
     // gradients beside the query side, which leaves dV to be added to by the key side, O += LCE(V) beside the key side.  In
     // front of the query side it was slower (4 x 56 x 56 x 64, k = 2: 100.9 us behind, 105.6 in front; 8 x 28 x 28 x 128: 92.0, 95.5).
@@ -584,7 +588,7 @@ int launch_gemm_both(const f32::GemmJob<T, T, float> &J0, const f32::GemmJob<T, 
     const long mt = (J0.M + f32::kGemmBM - 1) / f32::kGemmBM;
     const bool narrow = J1.N <= 64 || narrow_tiles<T>(J0.M, J0.N, J1.N);
     const int bn = narrow ? 64 : 128;
-    const long b0 = mt * ((J0.N + bn - 1) / bn), b1 = mt * ((J1.N + bn - 1) / bn);
+    const long b0 = tile_blocks<T>(mt * ((J0.N + bn - 1) / bn)), b1 = tile_blocks<T>(mt * ((J1.N + bn - 1) / bn));
     if (b0 + b1 > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)(b0 + b1));
     const bool vec = J1.K % 4 == 0;              // all sizes and pitches are multiples of C
@@ -596,19 +600,19 @@ int launch_gemm_both(const f32::GemmJob<T, T, float> &J0, const f32::GemmJob<T, 
 }
 
 template <typename T>
-int launch_gemm_end(const f32::TnJob<T, float> &J0, const f32::TnJob<float, T> &J1, int share_tokens, const f32::GemmJob<float, T, T> &J, hipStream_t st)
+int launch_gemm_end(const f32::TnJob<T, float> &J0, const f32::TnJob<float, T> &J1, int shares, int share_tokens, const f32::GemmJob<float, T, T> &J, hipStream_t st)
 {
     const long mt = (J.M + f32::kGemmBM - 1) / f32::kGemmBM;
     const bool narrow = narrow_tiles<T>(J.M, J.N);
     const int bn = narrow ? 64 : 128;
-    const long blocks = mt * ((J.N + bn - 1) / bn) + J0.blocks + J1.blocks;
+    const long tn = ((long)(J0.blocks() + J1.blocks()) * shares + 7) / 8 * 8, blocks = tn + tile_blocks<T>(mt * ((J.N + bn - 1) / bn));
     if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)blocks);
     const bool vec = J.N % 4 == 0;               // all sizes and pitches are multiples of C
-    if (vec && narrow) hipLaunchKernelGGL((f32::k_gemm_end<true, 64, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
-    else if (vec) hipLaunchKernelGGL((f32::k_gemm_end<true, kWideBN<T>, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
-    else if (narrow) hipLaunchKernelGGL((f32::k_gemm_end<false, 64, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
-    else hipLaunchKernelGGL((f32::k_gemm_end<false, kWideBN<T>, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, J);
+    if (vec && narrow) hipLaunchKernelGGL((f32::k_gemm_end<true, 64, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, (int)tn, J);
+    else if (vec) hipLaunchKernelGGL((f32::k_gemm_end<true, kWideBN<T>, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, (int)tn, J);
+    else if (narrow) hipLaunchKernelGGL((f32::k_gemm_end<false, 64, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, (int)tn, J);
+    else hipLaunchKernelGGL((f32::k_gemm_end<false, kWideBN<T>, T>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, (int)tn, J);
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -630,9 +634,8 @@ int backward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *W
     const lce::LcePlan lp = lce_grad_plan(D);
     // dX = [dQ | dK | dV] Wqkv^T; dWqkv = X^T [dQ | dK | dV], dWo = O^T dY
     const SharePlan sp = share_plan(M, C);
-    const int cb = (C + 63) / 64;
-    rc = launch_gemm_end<T>(f32::TnJob<T, float>{X, w.dqkv, w.part_qkv, C, C3, C, C3, cb * ((C3 + 63) / 64) * sp.shares},
-                            f32::TnJob<float, T>{w.o, dY, w.part_o, C, C, C, C, cb * cb * sp.shares}, sp.tokens,
+    rc = launch_gemm_end<T>(f32::TnJob<T, float>{X, w.dqkv, w.part_qkv, C, C3, C, C3},
+                            f32::TnJob<float, T>{w.o, dY, w.part_o, C, C, C, C}, sp.shares, sp.tokens,
                             f32::GemmJob<float, T, T>{w.dqkv, Wqkv, dX, M, C3, C3, C, C, C3, nullptr, nullptr, 0}, st);
     if (rc != BRA_OK) return rc;
     const bwd::ReduceJob r0 = bwd::reduce_job(w.part_qkv, dWqkv, sp.shares, C3 * C), r1 = bwd::reduce_job(w.part_o, dWo, sp.shares, C * C),
