@@ -24,6 +24,7 @@ using mfma::bf16_lo;
 using mfma::cross_row_max;
 using mfma::cross_row_sum;
 using mfma::f32x2;
+using mfma::f32x16;
 using mfma::f32x4;
 using mfma::kWave;
 using mfma::divide;
@@ -92,14 +93,92 @@ struct GemmJob {
     int gelu;
 };
 
+// Rows taken region by region (n <= 64 tokens each) of maps of S x S regions of rh x rw tokens, a tile with 64 / n whole
+// regions, and float32 means over each region's tokens of the first `cols` columns: [regions][cols].
+struct MeansJob {
+    float *Means;
+    int cols, regions, R, S, n, rh, rw;
+    float n_inv, R_inv, S_inv, rw_inv;
+};
+
+// The token of row `row` of tile `tile`, or -1.
+__device__ __forceinline__ int region_row(const MeansJob &g, int tile, int row)
+{
+    const int per = mfma::fast_div(kGemmBM, g.n_inv), first = tile * per, b0 = (unsigned)first / (unsigned)g.R, r0 = first - b0 * g.R;
+    const int j = mfma::fast_div(row, g.n_inv), t = row - j * g.n;
+    if (j >= per || first + j >= g.regions) return -1;
+    const int over = mfma::fast_div(r0 + j, g.R_inv), reg = r0 + j - over * g.R;
+    const int ry = mfma::fast_div(reg, g.S_inv), ty = mfma::fast_div(t, g.rw_inv);
+    return ((b0 + over) * g.S * g.rh + ry * g.rh + ty) * g.S * g.rw + (reg - ry * g.S) * g.rw + t - ty * g.rw;
+}
+
+// The means of a tile's columns out of its accumulators: sums over aligned groups of 16 or 4 rows in registers (mfma::quad_sums: the
+// quad's lanes end with the four columns of one 16 x 16 product each), where that is less than a region the groups, or with an odd
+// number of rows all of them, meet in LDS.  The order does not depend on the tile's width.  sums: 64 x (BN + 4) floats.
+template <int BN>
+__device__ __forceinline__ void tile_means(const MeansJob &g, const f32x4 (&acc)[2][BN / 32], int tile, int n0, int N, float *sums)
+{
+    constexpr int MP = BN + 4, GROUPS = BN / 4, TR = 256 / GROUPS;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, lg = lane / 16, i = lane % 16, wr = wave / 2, wc = wave % 2;
+    const int per = mfma::fast_div(kGemmBM, g.n_inv), first = tile * per, cols = min(g.cols, N);
+    auto lay_down = [&](auto group) {
+        constexpr int G = decltype(group)::value;
+        const bool whole = G == g.n;
+        if (!whole) __syncthreads();              // the last chunk has been read
+#pragma unroll
+        for (int t0 = 0; t0 < BN / 32; t0 += 2) {
+            if constexpr (G == 1) {
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                    for (int t = t0; t < t0 + 2; ++t) {
+                        const int row = 32 * wr + 16 * rt + i, col = (BN / 2) * wc + 16 * t + 4 * lg, region = tile * kGemmBM + row;
+                        if (!whole) *(f32x4 *)(sums + row * MP + col) = acc[rt][t];
+                        else if (n0 + col < cols && region < g.regions) *(f32x4 *)(g.Means + (size_t)region * g.cols + n0 + col) = acc[rt][t];
+                    }
+                continue;
+            }
+            f32x16 v;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = acc[e / 8][t0 + e / 4 % 2][e % 4];
+            f32x4 quad = mfma::quad_sums(v, i);
+            if constexpr (G == 16)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    quad[e] += mfma::dpp_get<0x124>(quad[e]);       // row_ror:4
+                    quad[e] += mfma::dpp_get<0x128>(quad[e]);       // row_ror:8
+                }
+            if (i % G >= 4) continue;
+            const int row = 32 * wr + 16 * (i % 2) + i, col = (BN / 2) * wc + 16 * (t0 + i / 2 % 2) + 4 * lg, region = tile * (kGemmBM / G) + row / G;
+            if (!whole) *(f32x4 *)(sums + row / G * MP + col) = quad;
+            else if (n0 + col < cols && region < g.regions) *(f32x4 *)(g.Means + (size_t)region * g.cols + n0 + col) = quad * g.n_inv;
+        }
+    };
+    const int G = mfma::means_group(g.n);
+    if (G == 16) lay_down(std::integral_constant<int, 16>{});
+    else if (G == 4) lay_down(std::integral_constant<int, 4>{});
+    else lay_down(std::integral_constant<int, 1>{});
+    if (G == g.n) return;
+    __syncthreads();
+    const int col = 4 * (tid % GROUPS), rows_each = g.n / G;
+    for (int j = tid / GROUPS; j < per && first + j < g.regions; j += TR) {
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int t = 0; t < rows_each; ++t) sum += *(const f32x4 *)(sums + (j * rows_each + t) * MP + col);
+        if (n0 + col < cols) *(f32x4 *)(g.Means + (size_t)(first + j) * g.cols + n0 + col) = sum * g.n_inv;
+    }
+}
+
 // A wavefront's 32 rows from m0 on x BN / 2 columns from n0 on, with bias, GELU and residual.
+// rows: if not NULL, the rows' tokens from the tile's row m0 on.
 template <bool VEC, int BN, typename TA, typename TB, typename TO>
-__device__ __forceinline__ void gemm_store(const GemmJob<TA, TB, TO> &J, const f32x4 (&acc)[2][BN / 32], long m0, int n0, int g, int i)
+__device__ __forceinline__ void gemm_store(const GemmJob<TA, TB, TO> &J, const f32x4 (&acc)[2][BN / 32], long m0, int n0, int g, int i,
+                                           const int *rows = nullptr)
 {
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) {
-        const long m = m0 + 16 * rt + i;
-        if (m >= J.M) continue;
+        const long m = rows ? (long)rows[16 * rt + i] : m0 + 16 * rt + i;
+        if (rows ? m < 0 : m >= J.M) continue;
 #pragma unroll
         for (int t = 0; t < BN / 32; ++t) {
             const int n = n0 + 16 * t + 4 * g, left = J.N - n;
@@ -113,8 +192,9 @@ __device__ __forceinline__ void gemm_store(const GemmJob<TA, TB, TO> &J, const f
     }
 }
 
-template <bool BT, bool VEC, int BN, typename TA, typename TB, typename TO>
-__device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int block, float *smem)
+// MEANS: rows region by region, see MeansJob (M is not looked at); rows: a table of 64 in LDS.
+template <bool BT, bool VEC, int BN, bool MEANS = false, typename TA, typename TB, typename TO>
+__device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int block, float *smem, const MeansJob *means = nullptr, int *rows = nullptr)
 {
     constexpr int BK = kGemmBK, PA = BK + 4, PB = BT ? BK + 4 : BN + 4, NT = BN / 32;
     float *As = smem, *Bs = smem + kGemmBM * PA;
@@ -122,7 +202,11 @@ __device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int bloc
     const int ntiles = (J.N + BN - 1) / BN;
     const long m0 = (long)(block / ntiles) * kGemmBM;
     const int n0 = (block % ntiles) * BN;
-    if (m0 >= J.M) return;                       // grids are rounded up to multiples of 8
+    if (!MEANS && m0 >= J.M) return;             // grids are rounded up to multiples of 8
+    if constexpr (MEANS) {
+        if (tid < kGemmBM) rows[tid] = region_row(*means, block / ntiles, tid);
+        __syncthreads();
+    }
     constexpr int NA = kGemmBM * BK / 4 / 256, NB = BN * BK / 4 / 256;
     f32x4 ra[NA], rb[NB];
     // Rows past the end repeat the last one (never stored).  k past the end is blanked where the values go to LDS:
@@ -131,7 +215,7 @@ __device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int bloc
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
             const int idx = tid + 256 * u, k = k0 + 4 * (idx % (BK / 4));
-            const long m = min(m0 + idx / (BK / 4), J.M - 1);
+            const long m = MEANS ? (long)max(rows[idx / (BK / 4)], 0) : min(m0 + idx / (BK / 4), J.M - 1);
             ra[u] = load4<VEC>(J.A + m * J.lda + (VEC ? min(k, J.K - 4) : k), J.K - k);
         }
 #pragma unroll
@@ -200,7 +284,8 @@ __device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int bloc
                     for (int rt = 0; rt < 2; ++rt) acc[rt][t] = mfma_f32(wa[t][e], xb[rt][e], acc[rt][t]);
         }
     }
-    gemm_store<VEC, BN>(J, acc, m0 + 32 * wr, n0 + (BN / 2) * wc, g, i);
+    if (!MEANS || J.Out) gemm_store<VEC, BN>(J, acc, m0 + 32 * wr, n0 + (BN / 2) * wc, g, i, MEANS ? rows + 32 * wr : nullptr);
+    if (MEANS && n0 < means->cols) tile_means<BN>(*means, acc, block / ntiles, n0, J.N, smem);
 }
 
 // The same tile for a bf16 B, on v_mfma_f32_16x16x32_bf16, one step per chunk (the float32 instruction takes 16 times as
@@ -209,8 +294,9 @@ __device__ __forceinline__ void gemm_tile(const GemmJob<TA, TB, TO> &J, int bloc
 // transposing read, 128 bytes more after every 8 of them keep its lane groups on different banks.  Channel counts are
 // multiples of 4.  58310 x 96 x 288 with float32 results: 26 us (48 on the float32 instruction; 78 MB).
 // 58310 x 96 x 96 with a float32 A 10.5 us (19.4).
-template <bool BT, int BN, typename TA, typename TO>
-__device__ __forceinline__ void gemm_tile_bf16(const GemmJob<TA, bf16_t, TO> &J, int block, bf16_t *smem)
+template <bool BT, int BN, bool MEANS = false, typename TA, typename TO>
+__device__ __forceinline__ void gemm_tile_bf16(const GemmJob<TA, bf16_t, TO> &J, int block, bf16_t *smem, const MeansJob *means = nullptr,
+                                               int *rows = nullptr)
 {
     using mfma::bf16x8;
     using mfma::u32x4;
@@ -222,14 +308,20 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmJob<TA, bf16_t, TO> &J,
     const int ntiles = (J.N + BN - 1) / BN;
     const long m0 = (long)(block / ntiles) * kGemmBM;
     const int n0 = (block % ntiles) * BN;
-    if (m0 >= J.M) return;                       // grids are rounded up to multiples of 8
+    if (!MEANS && m0 >= J.M) return;             // grids are rounded up to multiples of 8
+    if constexpr (MEANS) {
+        if (block / ntiles * mfma::fast_div(kGemmBM, means->n_inv) >= means->regions) return;
+        if (tid < kGemmBM) rows[tid] = region_row(*means, block / ntiles, tid);
+        __syncthreads();
+    }
     typename std::conditional<SPLIT, f32x4, u32x2>::type ra[NA];
     u32x2 rb[NB];
     auto fetch = [&](int k0) {               // past the end: as in gemm_tile
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
             const int idx = tid + 256 * u, k = k0 + 4 * (idx % (BK / 4));
-            ra[u] = *(const decltype(&ra[0]))(J.A + min(m0 + idx / (BK / 4), J.M - 1) * J.lda + min(k, J.K - 4));
+            const long m = MEANS ? (long)max(rows[idx / (BK / 4)], 0) : min(m0 + idx / (BK / 4), J.M - 1);
+            ra[u] = *(const decltype(&ra[0]))(J.A + m * J.lda + min(k, J.K - 4));
         }
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
@@ -307,7 +399,8 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmJob<TA, bf16_t, TO> &J,
                 for (int q = TERMS - 1; q >= 0; --q) acc[rt][t] = mfma::mfma16(wf, xb[rt][q], acc[rt][t]);
         }
     }
-    gemm_store<true, BN>(J, acc, m0 + 32 * wr, n0 + (BN / 2) * wc, g, i);
+    if (!MEANS || J.Out) gemm_store<true, BN>(J, acc, m0 + 32 * wr, n0 + (BN / 2) * wc, g, i, MEANS ? rows + 32 * wr : nullptr);
+    if (MEANS && n0 < means->cols) tile_means<BN>(*means, acc, block / ntiles, n0, J.N, (float *)smem);
 }
 
 template <int BN, bool BT>
@@ -335,6 +428,17 @@ __global__ __launch_bounds__(256) void k_gemm(GemmJob<TA, TB, TO> J0, GemmJob<fl
     __shared__ __attribute__((aligned(16))) float smem[gemm_lds_floats<BN, BT>()];
     if ((int)blockIdx.x < blocks0) any_gemm_tile<BT, VEC, BN>(J0, blockIdx.x, blocks0, smem);
     else any_gemm_tile<BT, VEC, BN>(J1, (int)blockIdx.x - blocks0, (int)gridDim.x - blocks0, smem);
+}
+
+// A product whose rows go region by region, with their means.
+template <int BN, typename T>
+__global__ __launch_bounds__(256) void k_gemm_means(GemmJob<T, T, float> J, MeansJob means)
+{
+    constexpr size_t n = gemm_lds_floats<BN, false>(), sums = (size_t)kGemmBM * (BN + 4);
+    __shared__ __attribute__((aligned(16))) float smem[n > sums ? n : sums];
+    __shared__ int rows[kGemmBM];
+    if constexpr (std::is_same<T, bf16_t>::value) gemm_tile_bf16<false, BN, true>(J, mfma::swizzled_block(), (bf16_t *)smem, &means, rows);
+    else gemm_tile<false, true, BN, true>(J, blockIdx.x, smem, &means, rows);
 }
 
 // J0 and a product with its matrix transposed (Q, K, V = X Wqkv and dO = dY Wo^T of the gradients) in one launch.

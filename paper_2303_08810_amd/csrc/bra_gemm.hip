@@ -197,28 +197,6 @@ __device__ __forceinline__ void region_row(const GemmMeans &g, int tile, int row
 // differ in bits 0, 1 and 3 (see fragments()).
 __device__ __forceinline__ int bt_turn(int row) { return row % 4 + row / 8 % 2 * 4; }
 
-// Rows whose sums a wavefront forms in registers: aligned groups of a tile's rows that lie in one region.
-__device__ __forceinline__ int means_group(int n) { return n % 16 == 0 ? 16 : n % 4 == 0 ? 4 : 1; }
-
-// Sums over the four lanes of a quad of 16 values per lane, a quarter to each lane: entries 8 (c % 2) + 4 (c / 2 % 2) + 0 .. 3.
-__device__ __forceinline__ f32x4 quad_sums(const f32x16 &v, int c)
-{
-    const bool odd = c & 1, hi = c & 2;
-    float x[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        x[e] = v[e];
-        asm volatile("" : "+v"(x[e]));            // a select of two entries of v becomes a chain of 16 compares otherwise
-    }
-    float pair[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) pair[e] = (odd ? x[8 + e] : x[e]) + dpp_get<0xB1>(odd ? x[e] : x[8 + e]);
-    f32x4 quad;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) quad[e] = (hi ? pair[4 + e] : pair[e]) + dpp_get<0x4E>(hi ? pair[e] : pair[4 + e]);
-    return quad;
-}
-
 // Workgroups of an XCD take neighbouring tiles, the output tiles of the same rows one after the other (swizzled()).
 // EXT: bias, GELU, residual or rows that are not in memory (GemmRows).  NB: buffers, 1 for K = 64, else 2.
 // lds: NB chunks of In and of W.

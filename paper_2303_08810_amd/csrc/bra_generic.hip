@@ -209,11 +209,52 @@ f32::GemmJob<float, T, float> region_job(const Dims &D, const T *Wqkv, const Gen
     return {w.xr, Wqkv, w.qk, (long)D.B * D.R, D.C, 3 * D.C, 2 * D.C, 2 * D.C, D.C, nullptr, nullptr, 0};
 }
 
+// The means of Q and K out of the token projection, whose tiles go region by region: faster for bra_forward throughout (a pooling pass
+// and a region-level product less).  bra_route, which has to decide on the same bits, projects all tokens for it; the lines lie
+// where that takes as long.  bra_forward before -> now / bra_route (us): 4 x 14 x 14 x 256 38.3 -> 35.9 / 18.8 -> 15.7, 2 x 64 x 64 x 128 49.5 -> 44.8, 1 x 21
+// x 21 x 768 79.3 -> 65.7, 50 x 28 x 28 x 96 bf16 74.7 -> 69.7 / 17.6 -> 15.2.  float32, by tiles of bra_route's product, beyond a round of them times
+// C: 56 thousand (C = 192) 17.1 -> 16.6, 66 (128) 15.5 -> 14.1, 72 (128) 16.9 -> 17.0, 88 (96, regions of 36 tokens) 14.1 -> 17.0, 100 (64) 15.0 -> 18.4; 312 tiles of C = 768
+// 36.0 -> 44.2, 168 35.5 -> 32.2.  bf16, by millions of values: 3.1 (C = 160) 17.4 -> 14.4, 5.5 (96) 28.8 -> 27.8, 5.5 (288) 25.2 -> 27.6, 9.2 (160) 24.4 -> 25.9,
+// regions of 4 tokens 9.2 47.3 -> 44.7.
+bool means_from_projection(const Dims &D)
+{
+    const long values = (long)D.B * D.N * D.C;
+    if (D.n > f32::kGemmBM || D.C % 4 != 0 || (long)D.B * D.N > 0x7fffffffL) return false;
+    if (D.dtype == BRA_BF16) return values <= (D.n <= 4 ? 10L << 20 : 4L << 20);
+    const long per = f32::kGemmBM / D.n, tiles = ((long)D.B * D.R + per - 1) / per * ((2L * D.C + 63) / 64);
+    return D.n == 1 || tiles <= 256 || tiles * D.C <= (D.n <= 4 ? 80000 : 66000);
+}
+
+// Out: Q | K | V of all tokens, or NULL for Q^r | K^r alone.
+template <typename T>
+int launch_gemm_means(const Dims &D, const T *X, const T *Wqkv, float *Out, const GenericWs &w, hipStream_t st)
+{
+    const int C = D.C, N = Out ? 3 * C : 2 * C, per = f32::kGemmBM / D.n;
+    const f32::GemmJob<T, T, float> J = {X, Wqkv, Out, (long)D.B * D.N, C, 3 * C, 3 * C, N, C, nullptr, nullptr, 0};
+    const f32::MeansJob means = {w.qk, 2 * C, D.B * D.R, D.R, D.S, D.n, D.rh, D.rw, 1.0f / D.n, 1.0f / D.R, 1.0f / D.S, 1.0f / D.rw};
+    const long row_tiles = ((long)D.B * D.R + per - 1) / per;
+    const bool narrow = narrow_tiles<T>(row_tiles * f32::kGemmBM, N);
+    const int bn = narrow ? 64 : 128;
+    const long blocks = tile_blocks<T>(row_tiles * ((N + bn - 1) / bn));
+    if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    if (narrow) hipLaunchKernelGGL((f32::k_gemm_means<64, T>), dim3((unsigned)blocks), dim3(256), 0, st, J, means);
+    else hipLaunchKernelGGL((f32::k_gemm_means<kWideBN<T>, T>), dim3((unsigned)blocks), dim3(256), 0, st, J, means);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
 // Routing on its own: region means, their projection, rows of A^r and top-k.  The arithmetic of every entry is that
 // of forward_t, so both give the same index.
 template <typename T>
 int launch_route(const Dims &D, const T *X, const T *Wqkv, int32_t *Ir, float *Ar_opt, const GenericWs &w, hipStream_t st)
 {
+    if (means_from_projection(D)) {
+        {
+            ProfScope ps(st, K_GEN_REGION_QK);
+            const int rc = launch_gemm_means<T>(D, X, Wqkv, nullptr, w, st);
+            if (rc != BRA_OK) return rc;
+        }
+        return route_rows(D, w.qk, w.qk + D.C, 2 * D.C, Ir, Ar_opt, st);
+    }
     launch_pool<T>(D, X, w.xr, st);
     {
         ProfScope ps(st, K_GEN_REGION_QK);
@@ -335,9 +376,12 @@ int forward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *Wl
     int rc;
     if (!Ir_in_opt) {
         int32_t *dst = Ir_out_opt ? Ir_out_opt : w.ir;
-        launch_pool<T>(D, X, w.xr, st);
-        const f32::GemmJob<float, T, float> rj = region_job<T>(D, Wqkv, w);
-        {
+        if (means_from_projection(D)) {
+            ProfScope ps(st, K_GEN_GEMM_QKV);
+            rc = launch_gemm_means<T>(D, X, Wqkv, w.qkv, w, st);
+        } else {
+            launch_pool<T>(D, X, w.xr, st);
+            const f32::GemmJob<float, T, float> rj = region_job<T>(D, Wqkv, w);
             ProfScope ps(st, K_GEN_GEMM_QKV);
             rc = launch_gemm<false>(qkv_job, &rj, st);
         }

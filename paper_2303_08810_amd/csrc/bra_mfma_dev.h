@@ -391,6 +391,28 @@ __device__ __forceinline__ float dpp_get(float x)
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(xi, xi, CTRL, 0xf, 0xf, false));
 }
 
+// Means of regions out of a product's accumulators: rows whose sums a wavefront forms in registers: aligned groups of a tile's rows that lie in one region.
+__device__ __forceinline__ int means_group(int n) { return n % 16 == 0 ? 16 : n % 4 == 0 ? 4 : 1; }
+
+// Sums over the four lanes of a quad of 16 values per lane, a quarter to each lane: entries 8 (c % 2) + 4 (c / 2 % 2) + 0 .. 3.
+__device__ __forceinline__ f32x4 quad_sums(const f32x16 &v, int c)
+{
+    const bool odd = c & 1, hi = c & 2;
+    float x[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        x[e] = v[e];
+        asm volatile("" : "+v"(x[e]));            // a select of two entries of v becomes a chain of 16 compares otherwise
+    }
+    float pair[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) pair[e] = (odd ? x[8 + e] : x[e]) + dpp_get<0xB1>(odd ? x[e] : x[8 + e]);
+    f32x4 quad;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) quad[e] = (hi ? pair[4 + e] : pair[e]) + dpp_get<0x4E>(hi ? pair[e] : pair[4 + e]);
+    return quad;
+}
+
 // Maxima over the 64 lanes of a wavefront of 4 values per lane at once, to every lane.
 // Lane pairs, then pairs of pairs, split the 4 values between them (each keeps the values
 // it will own and takes in the partner's copies), so the later steps handle one value per

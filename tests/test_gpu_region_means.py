@@ -47,6 +47,29 @@ def test_both_sides_of_the_lines(B, H, W, C, S, k):
     compare(X, Wqkv, Wo, Wlce, "bf16", S, k, C // 32, "mfma", images=[0, B - 1])
 
 
+F32 = [  # (dtype, B, H, W, C, heads, S, k): float32 kernels, which take odd multiples of 4 channels too
+    ("f32", 5, 7, 7, 64, 2, 7, 9),        # one token per region
+    ("f32", 3, 6, 3, 100, 2, 3, 4),       # 2, columns beyond the last tile
+    ("f32", 2, 14, 14, 96, 3, 7, 5),      # 4
+    ("f32", 2, 9, 9, 36, 1, 3, 3),        # 9
+    ("f32", 3, 16, 16, 64, 1, 4, 4),      # 16
+    ("f32", 1, 15, 12, 128, 4, 3, 2),     # 20
+    ("f32", 2, 16, 12, 192, 6, 2, 3),     # 48
+    ("f32", 1, 24, 24, 64, 2, 3, 4),      # 64
+    ("f32", 1, 26, 14, 64, 2, 2, 2),      # 91: beyond a tile
+    ("bf16", 2, 14, 14, 96, 3, 7, 5),
+    ("bf16", 40, 28, 28, 96, 3, 7, 4),    # tiles of 128 columns
+    ("bf16", 3, 9, 12, 160, 5, 3, 3),     # 12
+    ("bf16", 2, 15, 15, 100, 2, 3, 3),    # 25
+]
+
+
+@pytest.mark.parametrize("dtype,B,H,W,C,heads,S,k", F32)
+def test_means_of_the_float32_kernels(dtype, B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=9870 + H + C, dtype=dtype)
+    compare(X, Wqkv, Wo, Wlce, dtype, S, k, heads, "generic", images=[0, B - 1] if B > 1 else None)
+
+
 def test_an_infinity_stays_in_its_region():
     """Regions of 12 tokens share tiles and groups of rows are added up across lanes: only the affinities of the region that
     holds the infinity are not finite."""
