@@ -46,7 +46,7 @@ __global__ __launch_bounds__(kStoreThreads, 4) void k_route_lce(const float *__r
     u32x2 w[5][3];
     load_taps(w, table, cl);
     float none[1][2];
-    const long tile = (long)(block / J.cblocks) * 2 + threadIdx.x / 256;
+    const long tile = (long)(block / J.cblocks) * 2 + __builtin_amdgcn_readfirstlane(threadIdx.x / 256);
     if (tile < J.tiles)
         walk_tile<false, false>(J.In, (const bf16_t *)nullptr, J.Out, J.Low, D.C, D, J.T, tile, threadIdx.x / 32 % 8, c0, cl, true, w, none);
 }
@@ -55,10 +55,10 @@ __global__ __launch_bounds__(kStoreThreads, 4) void k_route_lce(const float *__r
 
 namespace {
 
-Job plain_job(const Dims &D, const bf16_t *In, const bf16_t *Wlce, bf16_t *Out, int ldo)
+Job plain_job(const Dims &D, const bf16_t *In, const bf16_t *Wlce, bf16_t *Out, int ldo, int beside)
 {
     Job J = {In, nullptr, Wlce, Out, nullptr, nullptr, ldo, (D.C + 63) / 64, 1, 0, Tiling{}};
-    J.T = tiling(D, ldo, 1536 / J.cblocks, J.tiles);
+    J.T = even_tiling(D, ldo, J.cblocks, beside, J.tiles);
     return J;
 }
 
@@ -97,12 +97,12 @@ BackwardJobs backward_jobs(const Dims &D, const bf16_t *dO, const bf16_t *V, con
 int route_rows_lce_bf16(const Dims &D, const float *Qr, const float *Kr, int32_t *Ir, const bf16_t *V, const bf16_t *Wlce, bf16_t *O,
                         bf16_t *Low, hipStream_t st)
 {
-    Job J = plain_job(D, V, Wlce, O, D.C);
+    const route::Plan p = route::plan(D, D.C);
+    const int rb = Qr ? p.blocks : 0, route_blocks = (rb + 7) / 8 * 8;
+    Job J = plain_job(D, V, Wlce, O, D.C, route_blocks);
     J.Low = Low;
     const long lce_blocks = ((J.tiles + 1) / 2 * J.cblocks + 7) / 8 * 8;
     if (D.C % 64 || !route::supported(D) || !offsets_fit(D, J.T, D.C) || lce_blocks > 0x3fffffffL) return BRA_ERR_UNSUPPORTED;
-    const route::Plan p = route::plan(D, D.C);
-    const int rb = Qr ? p.blocks : 0, route_blocks = (rb + 7) / 8 * 8;
     const size_t smem = std::max(rb ? p.smem : 0, kTapBytes);
     static bool opted = false;
     if (!opted && smem > 64 * 1024) {
@@ -118,7 +118,7 @@ int route_rows_lce_bf16(const Dims &D, const float *Qr, const float *Kr, int32_t
 // addresses are 64-bit throughout.
 int lce_add_bf16(const Dims &D, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, int ldo, int kernel_id, hipStream_t st)
 {
-    const Job J = plain_job(D, V, Wlce, O, ldo);
+    const Job J = plain_job(D, V, Wlce, O, ldo, 0);
     if (!offsets_fit(D, J.T, ldo)) return launch_lce<bf16_t>(D, V, D.C, Taps(Wlce), O, ldo, kernel_id, st);
     if (D.C % 2 || ldo % 2 || J.blocks() > 0x7ffffff0L) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);

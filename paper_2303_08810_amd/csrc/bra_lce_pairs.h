@@ -211,19 +211,65 @@ inline bool offsets_fit(const Dims &D, const Tiling &T, int ldo)
     return (long)std::min(T.subs * T.height + 4, D.H) * D.W * std::max(D.C, ldo) * 2 < (1L << 31);
 }
 
-// Strips of 20 rows, or 10 or 5 where that leaves fewer than `want` tiles or the rows span too much.
-inline Tiling tiling(const Dims &D, int ldo, long want, long &tiles)
+// Strips of `height` rows.
+inline Tiling strips_of(const Dims &D, int height, long &tiles)
 {
     Tiling T;
     const int xp = (D.W + 1) / 2;
     T.pairs = xp < 8 ? xp : 8;
     T.xtiles = (xp + T.pairs - 1) / T.pairs;
-    for (T.height = 20;; T.height /= 2) {
-        const int strips = (D.H + T.height - 1) / T.height;
-        T.subs = 8 / T.pairs < strips ? 8 / T.pairs : strips;
-        T.ytiles = (strips + T.subs - 1) / T.subs;
-        tiles = (long)D.B * T.xtiles * T.ytiles;
-        if (T.height == 5 || (tiles >= want && offsets_fit(D, T, ldo))) return T;
+    T.height = height;
+    const int strips = (D.H + height - 1) / height;
+    T.subs = 8 / T.pairs < strips ? 8 / T.pairs : strips;
+    T.ytiles = (strips + T.subs - 1) / T.subs;
+    tiles = (long)D.B * T.xtiles * T.ytiles;
+    return T;
+}
+
+// Strips of 20 rows, or 10 or 5 where that leaves fewer than `want` tiles or the rows span too much.
+inline Tiling tiling(const Dims &D, int ldo, long want, long &tiles)
+{
+    for (int height = 20;; height /= 2) {
+        const Tiling T = strips_of(D, height, tiles);
+        if (height == 5 || (tiles >= want && offsets_fit(D, T, ldo))) return T;
+    }
+}
+
+// Strips of even heights, 4 to 24 rows, two tiles to a block of 512 threads, two blocks to a compute unit.
+//
+// Beside the `beside` blocks that choose the regions: where all blocks of the launch find a compute unit each with strips of at most 16
+// rows, the lowest such strips. Those take no longer than the choice itself, 11 to 13 us, which takes 1.4 times that when it shares its
+// units. Measured with 24 blocks beside, 8 maps of 32 x 32 at 768 channels: 16 rows and 192 blocks 16.7 us, 11 to 4 rows and 288 to 768
+// blocks 21.9 to 18.6; with 64, 4 maps of 112 x 112 at 64 channels: 12 rows and 140 blocks 12.0, 8 rows and 200 blocks 13.8.
+//
+// Elsewhere the heights whose rounds take the least: a round of 512 blocks takes 0.6 us a row and as much as kStart rows before the first
+// is stored, and one of up to 256 takes kAlone of it. 64 maps of 21 x 21 at 384 channels: 21 rows 22.5 us, 11 rows 23.3, 7 rows 25.5, 5 rows
+// 30.1; 20 of 56 x 56 at 192: 14 rows 22, 8 rows 24, 4 rows 29.
+constexpr double kStart = 6, kAlone = 0.7;
+
+inline Tiling even_tiling(const Dims &D, int ldo, int cblocks, int beside, long &tiles)
+{
+    Tiling best = {};
+    bool found = false, apart = false;
+    double least = 0;
+    const double places = std::max(256, 512 - beside);
+    for (int strips = (D.H + 23) / 24;; ++strips) {
+        const int height = (D.H + strips - 1) / strips;
+        const bool last = height <= 4;
+        long n;
+        const Tiling T = strips_of(D, height, n);
+        const long blocks = (n + 1) / 2 * cblocks;
+        const bool alone = beside && height <= 16 && blocks + beside <= 256;
+        const double rounds = (double)blocks / places, whole = (double)(long)rounds, rest = rounds - whole;
+        const double cost = (whole + (rest > 0.5 ? 1 : rest > 0 ? kAlone : 0)) * (kStart + height);
+        if ((offsets_fit(D, T, ldo) || (last && !found)) && (alone || (!apart && (!found || cost < least)))) {
+            best = T;
+            least = cost;
+            tiles = n;
+            found = true;
+            apart = alone;
+        }
+        if (last) return best;
     }
 }
 
