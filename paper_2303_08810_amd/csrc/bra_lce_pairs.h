@@ -226,12 +226,13 @@ inline Tiling strips_of(const Dims &D, int height, long &tiles)
     return T;
 }
 
-// Strips of 20 rows, or 10 or 5 where that leaves fewer than `want` tiles or the rows span too much.
-inline Tiling tiling(const Dims &D, int ldo, long want, long &tiles)
+// Strips of even heights, at most 20 rows: the highest with `want` tiles and rows that span little enough, or 5.
+inline Tiling even_tiling(const Dims &D, int ldo, long want, long &tiles)
 {
-    for (int height = 20;; height /= 2) {
+    for (int strips = (D.H + 19) / 20;; ++strips) {
+        const int height = (D.H + strips - 1) / strips;
         const Tiling T = strips_of(D, height, tiles);
-        if (height == 5 || (tiles >= want && offsets_fit(D, T, ldo))) return T;
+        if (height <= 5 || (tiles >= want && offsets_fit(D, T, ldo))) return T;
     }
 }
 
@@ -247,7 +248,7 @@ inline Tiling tiling(const Dims &D, int ldo, long want, long &tiles)
 // 30.1; 20 of 56 x 56 at 192: 14 rows 22, 8 rows 24, 4 rows 29.
 constexpr double kStart = 6, kAlone = 0.7;
 
-inline Tiling even_tiling(const Dims &D, int ldo, int cblocks, int beside, long &tiles)
+inline Tiling forward_tiling(const Dims &D, int ldo, int cblocks, int beside, long &tiles)
 {
     Tiling best = {};
     bool found = false, apart = false;

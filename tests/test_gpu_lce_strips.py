@@ -1,8 +1,9 @@
 """GPU parity of the general pipeline's depth-wise convolution where the height of its strips changes: one strip of 24 rows,
-two of 13 and 12, low strips where every block has a compute unit beside the choice of regions, high ones where not."""
+two of 13 and 12, low strips where every block has a compute unit beside the choice of regions, high ones where not; and of the gradient's passes."""
 import pytest
 
 from synthetic_inputs import make_inputs
+from test_gpu_backward import compare_backward
 from test_gpu_parity import compare
 
 pytestmark = pytest.mark.gpu
@@ -22,3 +23,17 @@ STRIPS = [  # (B, H, W, C, heads, S, k)
 def test_lce_strips(B, H, W, C, heads, S, k):
     X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=7600 + H * W + C, dtype="bf16")
     compare(X, Wqkv, Wo, Wlce, "bf16", S, k, heads, "mfma", images=[0, B - 1])
+
+
+GRADIENT = [  # (B, H, W, C, heads, S, k): even strips of the two passes
+    (64, 14, 14, 384, 12, 7, 4),     # one strip of 14 rows
+    (3, 21, 10, 64, 1, 1, 1),        # five of 5 and 1
+    (16, 28, 28, 192, 6, 7, 1),      # four of 7
+    (32, 41, 36, 64, 2, 1, 1),       # three of 14 and 13
+]
+
+
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", GRADIENT)
+def test_gradient_strips(B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=7650 + H * W + C, dtype="bf16")
+    compare_backward(X, Wqkv, Wo, Wlce, "bf16", heads, S, k, path="mfma")
