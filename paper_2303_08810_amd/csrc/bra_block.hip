@@ -560,7 +560,7 @@ int launch_mlp_fused64(const Dims &D, const bf16_t *X1, const bf16_t *Y, const b
 
 // The same single-kernel MLP half for C = 64 CT (CT = 1..4) and any hidden = 64 NB: the weights
 // no longer fit in LDS, so the hidden layer is walked in blocks of 64 units.  Per block the
-// workgroup (4 wavefronts, 16 tokens each, one tile per wavefront) holds the 64 columns of W1
+// workgroup (4 or 8 wavefronts, 16 tokens each, one tile per wavefront; mlp_eight_waves()) holds the 64 columns of W1
 // and the 64 rows of W2 in LDS (requested into registers one block ahead), forms
 // GELU(Xn W1[:, block] + b1[block]) for its tokens and adds its product with W2[block, :] to the
 // output accumulators, which start from X2 + b2.  Operand layouts, fragment reads and LDS
@@ -577,8 +577,8 @@ struct MlpStreamSmem {
     static size_t bytes(int hidden) { return v_off + (size_t)(3 * C + hidden) * 4; }
 };
 
-template <int CT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CT <= 2 ? 3 : 2, 4))) void k_mlp_stream(const bf16_t *__restrict__ X1, const bf16_t *__restrict__ Y,
+template <int CT, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CT <= 2 ? NW == 8 ? 4 : 3 : 2, CT == 2 && NW == 4 ? 3 : 4))) void k_mlp_stream(const bf16_t *__restrict__ X1, const bf16_t *__restrict__ Y,
                                                     const bf16_t *__restrict__ W1, const float *__restrict__ b1,
                                                     const bf16_t *__restrict__ W2, const float *__restrict__ b2,
                                                     const float *__restrict__ gamma, const float *__restrict__ beta,
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CT <= 2 ? 3
 {
     typedef MlpStreamSmem<CT> SM;
     constexpr int C = SM::C, KS = C / 32, NT = C / 16, P1 = SM::P1, G1 = SM::G1, P2 = SM::P2, G2 = SM::G2;
-    constexpr int NP = C / 32;          // 16-byte pieces per thread of one block of W1 (8 C pieces), and of W2
+    constexpr int TH = 64 * NW, NP = 8 * C / TH;     // 16-byte pieces per thread of one block of W1, and of W2
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16_t *W1s = (bf16_t *)smem;
     bf16_t *W2s = (bf16_t *)(smem + SM::w2_off);
@@ -594,23 +594,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CT <= 2 ? 3
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int NB = hidden / 64;
 
-    for (int q = tid; q < C; q += 256) { gms[q] = gamma[q]; bts[q] = beta[q]; b2s[q] = b2[q]; }
-    for (int q = tid; q < hidden; q += 256) b1s[q] = b1[q];
+    for (int q = tid; q < C; q += TH) { gms[q] = gamma[q]; bts[q] = beta[q]; b2s[q] = b2[q]; }
+    for (int q = tid; q < hidden; q += TH) b1s[q] = b1[q];
 
     // this thread's pieces of a block: W1 rows k (8 pieces of 8 columns each), W2 rows of C / 8 pieces
     u32x4 r1[NP], r2[NP];
+    const unsigned from1 = 2u * (tid / 8 * hidden + 8 * (tid % 8));
     auto request = [&](int nb) {
 #pragma unroll
         for (int u = 0; u < NP; ++u) {
-            const int q = tid + 256 * u;
-            r1[u] = *(const u32x4 *)(W1 + (size_t)(q / 8) * hidden + 64 * nb + 8 * (q % 8));
-            r2[u] = *(const u32x4 *)(W2 + (size_t)(64 * nb + q / (C / 8)) * C + 8 * (q % (C / 8)));
+            const int q = tid + TH * u;
+            r1[u] = *(const u32x4 *)((const char *)(W1 + (size_t)(TH / 8) * u * hidden + 64 * nb) + from1);
+            r2[u] = *(const u32x4 *)((const char *)(W2 + (size_t)64 * nb * C) + 16u * q);
         }
     };
     auto park = [&]() {
 #pragma unroll
         for (int u = 0; u < NP; ++u) {
-            const int q = tid + 256 * u;
+            const int q = tid + TH * u;
             const int k = q / 8, h = q / (C / 8);
             *(u32x4 *)(W1s + k * P1 + (k / 8) * G1 + 8 * (q % 8)) = r1[u];
             u32x2 *dst = (u32x2 *)(W2s + h * P2 + (h / 4) * G2 + 8 * (q % (C / 8)));      // 8-byte aligned only
@@ -620,7 +621,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CT <= 2 ? 3
     };
     request(0);
 
-    const long tile = (long)blockIdx.x * 4 + wave;
+    const long tile = (long)blockIdx.x * NW + wave;
     const long tok = tile * 16 + i;
     const long tok_c = min(tok, tokens - 1);                    // rows past the end repeat the last; never stored
     float x2[KS][8];
@@ -715,23 +716,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CT <= 2 ? 3
     }
 }
 
-template <int CT>
+template <int CT, int NW>
 int launch_mlp_stream(const Dims &D, int hidden, const bf16_t *X1, const bf16_t *Y, const bra_block_params &p,
                       bf16_t *Xout, float eps, hipStream_t st)
 {
     const size_t smem = MlpStreamSmem<CT>::bytes(hidden);
     static size_t opted = 0;
     if (smem > opted) {
-        if (hipFuncSetAttribute((const void *)k_mlp_stream<CT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute((const void *)k_mlp_stream<CT, NW>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)smem) != hipSuccess)
             return BRA_ERR_LAUNCH;
         opted = smem;
     }
-    const long tokens = (long)D.B * D.N, grid = (tokens + 63) / 64;
+    const long tokens = (long)D.B * D.N, grid = (tokens + 16 * NW - 1) / (16 * NW);
     ProfScope ps(st, K_BLK_MLP_FUSED);
-    hipLaunchKernelGGL((k_mlp_stream<CT>), dim3((unsigned)grid), dim3(256), smem, st, X1, Y, (const bf16_t *)p.W1,
+    hipLaunchKernelGGL((k_mlp_stream<CT, NW>), dim3((unsigned)grid), dim3(64 * NW), smem, st, X1, Y, (const bf16_t *)p.W1,
                        p.b1, (const bf16_t *)p.W2, p.b2, p.ln2_gamma, p.ln2_beta, Xout, tokens, hidden, eps);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+// Workgroups of 8 wavefronts share a block of the weights, and its way into LDS, among twice the tokens; of 4 they spread further.  A
+// compute unit holds 3, 2 or 1 of 4 wavefronts and 2, 1 or 1 of 8 for C = 128, 192 or 256.  Block, us, with 4 / 8 and the workgroups of 4:
+//   C = 128: 16 x 28 x 28 (196) 48.2 / 50.3, 32 (392) 61.5 / 59.3, 48 (588, three a unit, with 8 four halves) 74.9 / 75.7, 64 (784, the last 16 of them
+//            in a round of their own) 92.2 / 87.4, 84 (1029) 109.1 / 108.8, 128 (1568) 145.1 / 142.8, 160 (1960) 178 / 171
+//   C = 192: 20 x 28 x 28 (245) 72.1 / 75.9, 30 (368) 93.6 / 88.8, 40 (490) 111.2 / 107.3, 60 (735: a round and a half of 512) 152.2 / 155.5
+//   C = 256: 64 x 14 x 14 (196) 92.9 / 98.0, 84 (258: two rounds) 139.4 / 114.6, 128 (392) 154.0 / 130.1, 180 (552) 211 / 196
+bool mlp_eight_waves(const Dims &D)
+{
+    const long four = ((long)D.B * D.N + 63) / 64;
+    if (D.C == 192) return (four - 1) % 512 >= 256;
+    return four > 256 && !(D.C == 128 && four > 512 && four <= 768);
 }
 
 // C = 64 .. 256 with any hidden that fits the LDS budget takes the block-streaming kernel.
@@ -893,11 +907,12 @@ int block_forward(const Dims &D, int hidden, float eps, const void *X, const bra
         }
     }
     if (mlp_stream_shape(D, hidden)) {
+        const bool eight = mlp_eight_waves(D);
         switch (D.C / 64) {
-        case 1: return launch_mlp_stream<1>(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);
-        case 2: return launch_mlp_stream<2>(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);
-        case 3: return launch_mlp_stream<3>(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);
-        default: return launch_mlp_stream<4>(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);
+        case 1: return launch_mlp_stream<1, 4>(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);
+        case 2: return (eight ? launch_mlp_stream<2, 8> : launch_mlp_stream<2, 4>)(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);
+        case 3: return (eight ? launch_mlp_stream<3, 8> : launch_mlp_stream<3, 4>)(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);
+        default: return (eight ? launch_mlp_stream<4, 8> : launch_mlp_stream<4, 4>)(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);
         }
     }
     // X2 takes X1's place: every lane reads the elements it overwrites
