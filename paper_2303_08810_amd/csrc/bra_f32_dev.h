@@ -14,6 +14,7 @@
 #include "bra_bwd_dev.h"
 #include "bra_lce_dev.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace bra {
@@ -536,13 +537,70 @@ __device__ __forceinline__ void rows_product(const float *T, int P, const f32x4 
     }
 }
 
+// One block of KB keys: scores, softmax, weights times V.  Kw, Vw: this wavefront's head in the rows of K and V (pitch P); m: reference score; l:
+// this lane's part of the denominator; left: keys there are.
+template <int KB, int P, int NS>
+__device__ __forceinline__ void attention_block(const float *Kw, const float *Vw, const f32x4 (&qf)[NS], int left, bool begins, int g, int i, float &m,
+                                                float (&l)[4], f32x4 (&acc)[NS])
+{
+    constexpr int KT = KB / 16;
+    f32x4 st[KT];
+#pragma unroll
+    for (int t = 0; t < KT; ++t) st[t] = f32x4{-m, -m, -m, -m};
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        f32x4 kf[KT];
+#pragma unroll
+        for (int t = 0; t < KT; ++t) kf[t] = *(const f32x4 *)(Kw + (16 * t + i) * P + 16 * s + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int t = 0; t < KT; ++t) st[t] = mfma_f32(kf[t][e], qf[s][e], st[t]);   // S^T[key 16 t + 4 g + j][query i] - m
+    }
+    if (left < KB) {
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) st[t][j] = 16 * t + 4 * g + j < left ? st[t][j] : -INFINITY;
+    }
+    float mx = st[0][0];
+#pragma unroll
+    for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mx = fmaxf(mx, st[t][j]);
+    // the reference follows the maximum when a lane's own score exceeds it by 2^8; the quotient does not depend on it
+    if (begins || __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0) {
+        const float up = begins ? cross_row_max(mx) : fmaxf(cross_row_max(mx), 0.f);
+        m += up;
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) st[t][j] -= up;
+        if (!begins) {
+            const float alpha = __builtin_amdgcn_exp2f(-up);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) l[j] *= alpha;
+#pragma unroll
+            for (int dt = 0; dt < NS; ++dt) acc[dt] *= alpha;
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            st[t][j] = __builtin_amdgcn_exp2f(st[t][j]);
+            l[j] += st[t][j];
+        }
+    rows_product<KT, NS>(Vw + 4 * g * P + i, P, st, acc);
+}
+
 // HPW = 1: as many wavefronts as the region's query tiles of 16 fill (3 to 8; more tiles are dealt out evenly).
 template <int DP, int HPW, bool VEC>
 __global__ __launch_bounds__(HPW == 1 ? 512 : 256, DP == 32 ? 4 : 2) void k_attention(const float *__restrict__ QKV, const int32_t *__restrict__ Ir,
                                                    float *__restrict__ O, Dims D, int hgroups, int qtiles, bool adds)
 {
     typedef AttnShape<DP, HPW> L;
-    constexpr int P = L::P, KB = L::KB, CW = L::CW, KT = KB / 16, NS = DP / 16;
+    constexpr int P = L::P, KB = L::KB, CW = L::CW, NS = DP / 16;
     __shared__ __attribute__((aligned(16))) float Ks[KB * P];
     __shared__ __attribute__((aligned(16))) float Vs[KB * P];
     // workgroups of an image and head group on one XCD (layer of 32 x 28 x 28 x 128, k = 4 85.4 -> 82.7 us)
@@ -598,55 +656,7 @@ __global__ __launch_bounds__(HPW == 1 ? 512 : 256, DP == 32 ? 4 : 2) void k_atte
         __syncthreads();
         if (k0 + KB < kn) fetch(k0 + KB);
         if (idle) continue;                      // no queries: the wavefront only brings its rows
-        f32x4 st[KT];
-#pragma unroll
-        for (int t = 0; t < KT; ++t) st[t] = f32x4{-m, -m, -m, -m};
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            f32x4 kf[KT];
-#pragma unroll
-            for (int t = 0; t < KT; ++t) kf[t] = *(const f32x4 *)(Ks + (16 * t + i) * P + DP * hl + 16 * s + 4 * g);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int t = 0; t < KT; ++t) st[t] = mfma_f32(kf[t][e], qf[s][e], st[t]);   // S^T[key 16 t + 4 g + j][query i] - m
-        }
-        const int left = kn - k0;
-        if (left < KB) {
-#pragma unroll
-            for (int t = 0; t < KT; ++t)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) st[t][j] = 16 * t + 4 * g + j < left ? st[t][j] : -INFINITY;
-        }
-        float mx = st[0][0];
-#pragma unroll
-        for (int t = 0; t < KT; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) mx = fmaxf(mx, st[t][j]);
-        // the reference follows the maximum when a lane's own score exceeds it by 2^8; the quotient does not depend on it
-        if (k0 == 0 || __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0) {
-            const float up = k0 == 0 ? cross_row_max(mx) : fmaxf(cross_row_max(mx), 0.f);
-            m += up;
-#pragma unroll
-            for (int t = 0; t < KT; ++t)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) st[t][j] -= up;
-            if (k0) {
-                const float alpha = __builtin_amdgcn_exp2f(-up);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) l[j] *= alpha;
-#pragma unroll
-                for (int dt = 0; dt < NS; ++dt) acc[dt] *= alpha;
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < KT; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                st[t][j] = __builtin_amdgcn_exp2f(st[t][j]);
-                l[j] += st[t][j];
-            }
-        rows_product<KT, NS>(Vs + 4 * g * P + DP * hl + i, P, st, acc);
+        attention_block<KB, P, NS>(Ks + DP * hl, Vs + DP * hl, qf, kn - k0, k0 == 0, g, i, m, l, acc);
     }
     const float denominator = cross_row_sum((l[0] + l[1]) + (l[2] + l[3]));
     if (slot < D.n && h < D.heads) {
@@ -661,6 +671,106 @@ __global__ __launch_bounds__(HPW == 1 ? 512 : 256, DP == 32 ? 4 : 2) void k_atte
             store4<VEC>(orow + ch, v, D.d - ch);
         }
     }
+}
+
+// The same for both heads of 32 channels of C = 64, with Y = O Wo (Eq. 7) behind it: O, which holds LCE(V), is read and not written.  Of
+// 2 tph wavefronts w has head w / tph and queries 16 (w % tph) on, then 16 rows and 32 columns of Y.  The additions of Y are gemm_tile's.
+// NL: chunks of a thread; 4 for 4 wavefronts, 2 for 8 and more.
+// 16 x 56 x 56, k = 1: 24 us, 19 and 9.5 for the two apart, of 126 registers and four wavefronts per SIMD: bound by what hides the chain of a
+// block of keys, loads, scores, weights, products and a barrier, with a round and a half of workgroups.
+constexpr size_t out_lds_bytes(int tph) { return (size_t)std::max(2 * 64, 16 * tph + 64) * (64 + 4) * sizeof(float); }
+
+template <int NL>
+__global__ __launch_bounds__(NL == 4 ? 256 : 1024, 4) void k_attention_out(const float *__restrict__ QKV, const int32_t *__restrict__ Ir, const float *__restrict__ O,
+                                                          const float *__restrict__ Wo, float *__restrict__ Y, Dims D, int qtiles)
+{
+    constexpr int C = 64, C3 = 3 * C, P = C + 4, KB = 64, NS = 2;
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    float *Ks = smem, *Vs = smem + KB * P;
+    const int block = mfma::swizzled_block(), qt = block % qtiles, reg = (block / qtiles) % D.R, b = block / (qtiles * D.R);
+    if (b >= D.B) return;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int T = blockDim.x, tph = T / (2 * kWave), hl = wave >= tph, mine = wave - hl * tph, slot0 = 16 * (tph * qt + mine), kn = D.kn;
+    const float *img = QKV + (size_t)b * D.N * C3;
+    const int32_t *irp = Ir + ((size_t)b * D.R + reg) * D.k;
+    const Places<true> at(D);
+    const float n_inv = 1.0f / (float)D.n;
+    auto token = [&](int slot) { return at.origin(reg) + at.slot(min(slot, D.n - 1)); };
+    const float c_exp = D.scale * 1.4426950408889634f;
+    f32x4 qf[NS];
+    {
+        const float *row = img + (size_t)token(slot0 + i) * C3 + 32 * hl + 4 * g;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) qf[s] = *(const f32x4 *)(row + 16 * s) * c_exp;      // scores as exponents of 2
+    }
+    // a thread's chunks of 4 channels: chunk tid % 16 of every (T / 16)th of 64 rows from tid / 16 on
+    f32x4 kr[NL], vr[NL];
+    const int ch = 4 * (tid % 16), r0 = tid / 16, rows = T / 16;
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int key = min(k0 + min(r0 + rows * u, KB - 1), kn - 1), p = divide(key, D.n, n_inv);   // past the end: the last key, masked below
+            const float *row = img + (size_t)(at.origin(region_index(irp[p], D.R)) + at.slot(key - p * D.n)) * C3 + ch;
+            kr[u] = *(const f32x4 *)(row + C);
+            vr[u] = *(const f32x4 *)(row + 2 * C);
+        }
+    };
+    auto park = [&](float *to, const f32x4 (&r)[NL]) {
+#pragma unroll
+        for (int u = 0; u < NL; ++u)
+            if (r0 + rows * u < KB) *(f32x4 *)(to + (r0 + rows * u) * P + ch) = r[u];
+    };
+    float m = 0.f, l[4] = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[NS] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    fetch(0);
+    for (int k0 = 0; k0 < kn; k0 += KB) {
+        if (k0) __syncthreads();                 // the previous block has been read
+        park(Ks, kr);
+        park(Vs, vr);
+        __syncthreads();
+        if (k0 + KB < kn) fetch(k0 + KB);
+        else {                                   // what the end needs: LCE(V) of the queries, two rows per thread, and Wo
+#pragma unroll
+            for (int u = 0; u < 2; ++u) kr[u] = *(const f32x4 *)(O + ((size_t)b * D.N + token(16 * tph * qt + r0 + rows * u)) * C + ch);
+#pragma unroll
+            for (int u = 0; u < NL; ++u) vr[u] = *(const f32x4 *)(Wo + min(r0 + rows * u, KB - 1) * C + ch);
+        }
+        if (slot0 < D.n) attention_block<KB, P, NS>(Ks + 32 * hl, Vs + 32 * hl, qf, kn - k0, k0 == 0, g, i, m, l, acc);
+    }
+    const float inv = 1.0f / cross_row_sum((l[0] + l[1]) + (l[2] + l[3]));
+    float *Os = smem, *Ws = smem + 16 * tph * P;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) *(f32x4 *)(Os + (r0 + rows * u) * P + ch) = kr[u];
+    park(Ws, vr);
+    __syncthreads();
+#pragma unroll
+    for (int dt = 0; dt < NS; ++dt) {
+        float *o = Os + (16 * mine + i) * P + 32 * hl + 16 * dt + 4 * g;
+        f32x4 v = acc[dt] * inv;
+        v += *(const f32x4 *)o;
+        *(f32x4 *)o = v;
+    }
+    __syncthreads();
+    const int rt = wave / 2, n0 = 32 * (wave % 2), slot = 16 * (tph * qt + rt) + i;
+    f32x4 y[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int s = 0; s < C / 16; ++s) {
+        const f32x4 x = *(const f32x4 *)(Os + (16 * rt + i) * P + 16 * s + 4 * g);
+        float w[4][2];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) w[e][t] = Ws[(16 * s + 4 * g + e) * P + n0 + 16 * t + i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) y[t] = mfma_f32(w[e][t], x[e], y[t]);
+    }
+    if (slot >= D.n) return;
+    float *to = Y + ((size_t)b * D.N + token(slot)) * C + n0 + 4 * g;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) *(f32x4 *)(to + 16 * t) = y[t];
 }
 
 // ---------------------------------------------------------------------------

@@ -306,21 +306,28 @@ int launch_route_lce(const Dims &D, const GenericWs &w, const lce::Taps &taps, i
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
+// Query tiles of a region over workgroups: four per workgroup, or up to eight in one or more equal ones where that leaves a fifth
+// fewer wavefronts (5 tiles: with four a second workgroup for the last one holds its place as long as the first;
+// 17 x 49 x 70 x 96, k = 13: 441 -> 373 us)
+struct TileSplit {
+    int each, groups;
+};
+
+TileSplit split_tiles(int tiles, int least)
+{
+    const int quads = (tiles + 3) / 4, groups = (tiles + 7) / 8, even = std::max(least, (tiles + groups - 1) / groups);
+    return 5 * groups * even <= 4 * 4 * quads ? TileSplit{even, groups} : TileSplit{4, quads};
+}
+
 template <int DP, int HPW, bool VEC>
 int launch_attention_t(const Dims &D, const float *qkv, const int32_t *Ir, float *o, bool adds, hipStream_t st)
 {
     const int hgroups = (D.heads + HPW - 1) / HPW, tiles = (D.n + 15) / 16;
     int waves = 4, qtiles = 1;
     if (HPW == 1) {
-        // four query tiles per workgroup, or up to eight in one or more equal ones where that leaves a fifth fewer
-        // wavefronts (5 tiles: with four a second workgroup for the last one holds its place as long as the first;
-        // 17 x 49 x 70 x 96, k = 13: 441 -> 373 us)
-        qtiles = (tiles + 3) / 4;
-        const int groups = (tiles + 7) / 8, even = std::max(3, (tiles + groups - 1) / groups);
-        if (5 * groups * even <= 4 * 4 * qtiles) {
-            qtiles = groups;
-            waves = even;
-        }
+        const TileSplit split = split_tiles(tiles, 3);
+        qtiles = split.groups;
+        waves = split.each;
     } else {
         const int qt = f32::AttnShape<DP, HPW>::QT;
         qtiles = (D.n + qt - 1) / qt;
@@ -357,6 +364,44 @@ int launch_attention(const Dims &D, const float *qkv, const int32_t *Ir, float *
     }
     if (hpw >= 2) return vec ? launch_attention_t<64, 2, true>(D, qkv, Ir, o, adds, st) : launch_attention_t<64, 2, false>(D, qkv, Ir, o, adds, st);
     return vec ? launch_attention_t<64, 1, true>(D, qkv, Ir, o, adds, st) : launch_attention_t<64, 1, false>(D, qkv, Ir, o, adds, st);
+}
+
+// Query tiles of k_attention_out: as in k_attention, in fours also where eights would leave compute units without any.
+TileSplit out_split(const Dims &D)
+{
+    const int tiles = (D.n + 15) / 16;
+    const TileSplit split = tiles <= 2 ? TileSplit{2, 1} : split_tiles(tiles, 4);
+    return split.each > 4 && (long)D.B * D.R * split.groups < 256 ? TileSplit{4, (tiles + 3) / 4} : split;
+}
+
+// Attention and Y = O Wo in one kernel: two heads of 32 channels.  That is a launch and two passes over O less, 2 us on 3000 tokens and 9 on
+// 50000 (16 x 56 x 56 x 64, k = 1: 61.7 -> 57.2; 60 x 28 x 28, k = 1 69.5 -> 63.8; 2 x 112 x 112, S = 16, k = 4 59.2 -> 54.3; 2 x 80 x 80, S = 8 54.1 -> 49.5);
+// but both heads share a compute unit, and a block of keys takes its wavefronts' time, a microsecond for four: where that is more than 3 us
+// longer the heads stay apart (1 x 56 x 56, S = 7, k = 2, 3 and 8 25.4, 27.6, 36.8 apart and 24.2, 27.7, 42.0 together; 2 x 64 x 64, S = 4, k = 4 61.7 and 73.2),
+// for short maps (1 x 40 x 40, S = 4, k = 2 31.9 and 32.7) and many keys (1 x 128 x 128, S = 8, k = 4, 16 blocks 82.5 and 79.6; S = 4, 64 blocks 233.6 and 236.9).
+bool attention_with_out(const Dims &D)
+{
+    if (D.C != 64 || D.d != 32 || (long)D.B * D.N < 2048) return false;
+    const int tiles = (D.n + 15) / 16;
+    const TileSplit one = split_tiles(tiles, 3), both = out_split(D);
+    const long regions = (long)D.B * D.R, blocks = (D.kn + 63) / 64;
+    const long apart = tiles <= 2 ? (regions + 255) / 256 * 4 : (regions * 2 * one.groups + 255) / 256 * one.each;
+    const long together = (regions * both.groups + 255) / 256 * 2 * both.each;
+    return blocks <= 32 && blocks * (together - apart) <= 3 * apart;
+}
+
+// o holds LCE(V).
+int launch_attention_out(const Dims &D, const float *qkv, const int32_t *Ir, const float *o, const float *Wo, float *Y, hipStream_t st)
+{
+    const TileSplit split = out_split(D);
+    const long blocks = ((long)D.B * D.R * split.groups + 7) / 8 * 8;
+    if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    ProfScope ps(st, K_GEN_ATTENTION);
+    const dim3 grid((unsigned)blocks), threads(128 * split.each);
+    const size_t smem = f32::out_lds_bytes(split.each);
+    if (split.each == 2) hipLaunchKernelGGL(f32::k_attention_out<4>, grid, threads, smem, st, qkv, Ir, o, Wo, Y, D, split.groups);
+    else hipLaunchKernelGGL(f32::k_attention_out<2>, grid, threads, smem, st, qkv, Ir, o, Wo, Y, D, split.groups);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
 template <typename T>
@@ -397,6 +442,9 @@ int forward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *Wl
         ProfScope ps(st, K_GEN_GEMM_QKV);
         rc = launch_gemm<false>(qkv_job, (const f32::GemmJob<float, T, float> *)nullptr, st);
         if (rc != BRA_OK) return rc;
+    }
+    if constexpr (std::is_same<T, float>::value) {
+        if (adds && attention_with_out(D)) return launch_attention_out(D, w.qkv, Ir, w.o, Wo, Y, st);
     }
     rc = launch_attention(D, w.qkv, Ir, w.o, adds, st);
     if (rc != BRA_OK) return rc;
