@@ -14,7 +14,7 @@
 //   k_attn_rows (regions of up to 32 tokens) or k_attn_gen, O = the two together   (Eq. 6)
 //   or, on large maps, k_route_rows, the attention and k_lce_add
 //   or k_route_rows and the image-resident attention with its own LCE (map_tail_pays; bra_mfma_small.hip)
-//   k_gemm_dma    Y = O Wo (Eq. 2)
+//   k_gemm_dma    Y = O Wo (Eq. 2), or with two heads and regions of more than 32 tokens in k_attn_gen
 #include "bra_attn_dev.h"
 #include "bra_gemm.h"
 #include "bra_lce_dev.h"
@@ -110,14 +110,26 @@ struct Added {
 template <int HD, int HPW>
 constexpr int genWaves = 4 * (64 / HD) / HPW;
 
-template <int HD, int NQ, int HPW, bool WALK>
-__global__ __launch_bounds__((64 * genWaves<HD, HPW>), HD == 32 && HPW == 1 ? 4 : 3) void k_attn_gen(AttnArgs A, bf16_t *__restrict__ O, Dims D, int qtiles, const bf16_t *__restrict__ Low)
+// With OUT also Y = O Wo (Eq. 7), where C is the 64 channels of the workgroup: a lane's channels of an output are the operand of that product as they
+// are, Wo lies in LDS as a block of V does; O is not written.  Y may be where Low is: a workgroup reads its tokens before it writes them.
+// A launch and two passes over O less: padded 2 x 200 x 300, S = 16, k = 4 107.7 -> 102.5 us, 1 x 200 x 300, k = 2 56.1 -> 50.9, 1 x 100 x 150, k = 8
+// 41.3 -> 38.7; 4 x 112 x 112, S = 16, k = 4 43.9 -> 42.4.
+struct OutMap {
+    const bf16_t *Wo;
+    bf16_t *Y;
+    int H, W;                // of Y, where D describes a padded map, else 0
+};
+
+template <int HD, int NQ, int HPW, bool WALK, bool OUT>
+__global__ __launch_bounds__((64 * genWaves<HD, HPW>), HD == 32 && HPW == 1 ? 4 : 3) void k_attn_gen(AttnArgs A, bf16_t *O, Dims D, int qtiles, const bf16_t *Low, OutMap out)
 {
+    static_assert(!OUT || HD == 32, "two heads");
     constexpr int WAVES = genWaves<HD, HPW>, PARTS = WAVES / 4, KSD = HD / 32, NDT = HD / 16;
     __shared__ __attribute__((aligned(16))) bf16_t K0[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t K1[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t V0[64 * 64];
     __shared__ __attribute__((aligned(16))) bf16_t V1[64 * 64];
+    __shared__ __attribute__((aligned(16))) bf16_t Ws[OUT ? 64 * 64 : 8];
     extern __shared__ int origins[];             // [k]: first token of the routed regions; with WALK [n]: tokens of a region's slots
     const int C = D.C, ncg = C / 64, n = D.n, kn = D.kn;
     // workgroups of an image and channel group share an L2: a gathered row of 128 bytes is a line of one group (10 x 64 x 64 x 384,
@@ -254,6 +266,10 @@ __global__ __launch_bounds__((64 * genWaves<HD, HPW>), HD == 32 && HPW == 1 ? 4 
     };
     const bool idle = 64 * NQ * qt + 16 * NQ * qw >= n;      // a wavefront without queries only brings its rows
     __syncthreads();                              // the table is in place
+    if constexpr (OUT)
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u)
+            load_to_lds_untracked(out.Wo + 64 * (8 * (LOADS * wave + u) + lane / 8) + piece / 2, lds_address(Ws) + 1024 * (LOADS * wave + u));
     const unsigned kv[2][2] = {{lds_address(K0), lds_address(V0)}, {lds_address(K1), lds_address(V1)}};
     request(0, kv[0][0], kv[0][1]);
     arrive_barrier();
@@ -269,6 +285,47 @@ __global__ __launch_bounds__((64 * genWaves<HD, HPW>), HD == 32 && HPW == 1 ? 4 
         if (!idle) block_of_keys(k0 + 64, K0, V0, std::false_type{});
     }
     if (NQ > 1 && Low) added.load(O + img + c0, Low + img + c0, qtok, C, g);      // registers that the sweep does not have
+    if constexpr (OUT) {
+        bf16x8 o[NQ][2];                         // operands: slot e of head h is channel 32 h + 16 (e / 4) + 4 g + e % 4
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int hh = 0; hh < HPW; ++hh) {
+                const float inv = 1.0f / cross_row_sum(l[q][hh]);
+                const f32x4 v0 = added.to(acc[q][hh][0] * inv, q, NDT * hh), v1 = added.to(acc[q][hh][1] * inv, q, NDT * hh + 1);
+                const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                o[q][hh] = pack8(v);
+            }
+        if constexpr (PARTS == 2) {              // the heads' wavefronts of the same queries exchange them, each forms half of Y's columns
+            __syncthreads();                     // the last block has been read
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) *(bf16x8 *)((q ? K1 : K0) + 512 * (2 * qw + part) + 8 * lane) = o[q][0];
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) o[q][hh] = *(const bf16x8 *)((q ? K1 : K0) + 512 * (2 * qw + hh) + 8 * lane);
+        } else {
+            __syncthreads();                     // Low of all queries has been read
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int slot = 64 * NQ * qt + 16 * (NQ * qw + q) + i, sy = fast_div(slot, rw_inv), ry = fast_div(reg, s_inv);
+            const int y = ry * D.rh + sy, x = (reg - ry * D.S) * D.rw + slot - sy * D.rw;
+            const int H = out.H ? out.H : D.H, W = out.H ? out.W : D.W;
+            const bool store = slot < n && y < H && x < W;
+            bf16_t *to = out.Y + (((size_t)b * H + y) * W + x) * 64 + 4 * g;
+#pragma unroll
+            for (int u = 0; u < 4 / PARTS; ++u) {
+                const int t = 4 / PARTS * part + u;
+                f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) v = mfma16(column_operand(Ws, 32 * hh, 16 * t, g, i), o[q][hh], v);
+                if (store) *(u32x2 *)(to + 16 * t) = pack4(v);
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const bool store = 64 * NQ * qt + 16 * (NQ * qw + q) + i < n;
@@ -539,13 +596,13 @@ int launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *
     return D.n <= 16 ? launch_attn_rows_t<64, 1>(D, A, O, Low, st) : launch_attn_rows_t<64, 2>(D, A, O, Low, st);
 }
 
-template <int HD, int NQ, int HPW, bool WALK>
-void launch_attn_gen_w(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
+template <int HD, int NQ, int HPW, bool WALK, bool OUT>
+void launch_attn_gen_w(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, const OutMap &out, hipStream_t st)
 {
     const int qtiles = (D.n + 64 * NQ - 1) / (64 * NQ);
     const dim3 grid((unsigned)(((long)D.B * D.R * qtiles * (D.C / 64) + 7) / 8 * 8));
     const size_t smem = (size_t)(D.k + (WALK ? D.n : 0)) * sizeof(int);
-    hipLaunchKernelGGL((k_attn_gen<HD, NQ, HPW, WALK>), grid, dim3(64 * genWaves<HD, HPW>), smem, st, A, O, D, qtiles, Low);
+    hipLaunchKernelGGL((k_attn_gen<HD, NQ, HPW, WALK, OUT>), grid, dim3(64 * genWaves<HD, HPW>), smem, st, A, O, D, qtiles, Low, out);
 }
 
 // Rows by walking (a table of the region's tokens more, an addition instead of divisions) from more than three blocks of keys on;
@@ -553,15 +610,16 @@ void launch_attn_gen_w(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t
 // both in one / by divisions / by walking (us): 40 x 56 x 56 x 192, k = 1 (one block) 176.6 / 174.0 / 174.5; 30 x 42 x 42 x 192, k = 5 (180 keys)
 // 114.8 / 110.3 / 113.1; 20 x 77 x 77 x 64, k = 2 (242) 73.9 / 74.4 / 73.7; 2 x 200 x 300 x 64, S = 16, k = 4 (988) 115.8 / 115.1 / 114.2.
 template <int NQ, int HPW>
-void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
+void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, const OutMap &out, hipStream_t st)
 {
     const bool walks = walk_ok(D) && D.kn > 192;
-    if (D.d == 32) walks ? launch_attn_gen_w<32, NQ, HPW, true>(D, A, O, Low, st) : launch_attn_gen_w<32, NQ, HPW, false>(D, A, O, Low, st);
-    else walks ? launch_attn_gen_w<64, NQ, 1, true>(D, A, O, Low, st) : launch_attn_gen_w<64, NQ, 1, false>(D, A, O, Low, st);
+    if (out.Y) walks ? launch_attn_gen_w<32, NQ, HPW, true, true>(D, A, O, Low, out, st) : launch_attn_gen_w<32, NQ, HPW, false, true>(D, A, O, Low, out, st);
+    else if (D.d == 32) walks ? launch_attn_gen_w<32, NQ, HPW, true, false>(D, A, O, Low, out, st) : launch_attn_gen_w<32, NQ, HPW, false, false>(D, A, O, Low, out, st);
+    else walks ? launch_attn_gen_w<64, NQ, 1, true, false>(D, A, O, Low, out, st) : launch_attn_gen_w<64, NQ, 1, false, false>(D, A, O, Low, out, st);
 }
 
-// Low: if not NULL, the output is added to what O and it hold (LCE(V)).
-void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
+// Low: if not NULL, the output is added to what O and it hold (LCE(V)).  out.Y: not NULL for the output projection as well (C = 64, heads of 32, Low).
+void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, const OutMap &out, hipStream_t st)
 {
     // two query tiles per wavefront (every K and V operand read serves both; measured above) where the wider tile leaves no
     // more than an eighth of its queries empty beyond the narrow one and there are workgroups enough.  One query tile: a head per
@@ -569,9 +627,9 @@ void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *
     // 44.7 -> 41.8), both heads from four workgroups per compute unit on, whose prologue is paid by half as many wavefronts
     // (30 x 42 x 42 x 192, k = 5 103.9, with one head each 107.5)
     const int t64 = (D.n + 63) / 64, t128 = (D.n + 127) / 128;
-    if (t128 * 128 * 8 <= t64 * 64 * 9 && (long)D.B * D.R * t128 * (D.C / 64) >= 512) launch_attn_gen_t<2, 1>(D, A, O, Low, st);
-    else if ((long)D.B * D.R * t64 * (D.C / 64) >= 1024) launch_attn_gen_t<1, 2>(D, A, O, Low, st);
-    else launch_attn_gen_t<1, 1>(D, A, O, Low, st);
+    if (t128 * 128 * 8 <= t64 * 64 * 9 && (long)D.B * D.R * t128 * (D.C / 64) >= 512) launch_attn_gen_t<2, 1>(D, A, O, Low, out, st);
+    else if ((long)D.B * D.R * t64 * (D.C / 64) >= 1024) launch_attn_gen_t<1, 2>(D, A, O, Low, out, st);
+    else launch_attn_gen_t<1, 1>(D, A, O, Low, out, st);
 }
 
 // Pooling, region-level projections, A^r rows and top-k on their own, for regions of more than one token.
@@ -694,7 +752,11 @@ int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo,
         {
             ProfScope ps(st, K_MFMA_ATTENTION);
             if (D.n <= 32 && D.k <= 1024) rc = launch_attn_rows(D, A, w.o, adds ? low : nullptr, st);      // its tables fit in LDS
-            else launch_attn_gen(D, A, w.o, adds ? low : nullptr, st);
+            else {
+                const bool with_out = adds && D.C == 64 && D.d == 32;
+                launch_attn_gen(D, A, w.o, adds ? low : nullptr, with_out ? OutMap{(const bf16_t *)Wo, (bf16_t *)Y, H, W} : OutMap{}, st);
+                if (with_out) return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+            }
         }
         if (rc != BRA_OK) return rc;
         rc = adds ? BRA_OK : lce::lce_add_bf16(D, w.v, (const bf16_t *)Wlce, w.o, D.C, K_MFMA_LCE_ADD, st);
