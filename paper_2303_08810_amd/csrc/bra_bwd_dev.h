@@ -42,8 +42,10 @@ __device__ __forceinline__ int collect_entries(const int32_t *__restrict__ irb, 
 
 // ---------------------------------------------------------------------------
 // out[e] = sum_p part[p][e], p in a fixed order, for up to three arrays in one launch.  A thread sums 4 elements (16
-// bytes) of one of `slices` slices of p (a power of two up to 64, about a quarter of the number of partial arrays), the
+// bytes) of one of `slices` slices of p (a power of two up to 16, about a quarter of the number of partial arrays or less), the
 // slices are summed through LDS.  Counts are multiples of 4 and arrays 16-byte aligned, else VEC = false: single elements.
+// 256 consecutive bytes of an array at a time, eight arrays' on their way (64 slices of 64 bytes, four on their way: 64 x 56 x 56 x 64, 224
+// arrays of 64 KB, whole gradient 210.3 -> 208.3 us; 8 images 69.2 -> 66.4; 2 x 56 x 56 x 64 float32 58.9 -> 57.2).
 struct ReduceJob {
     const float *part;
     float *out;
@@ -54,7 +56,7 @@ struct ReduceJob {
 inline ReduceJob reduce_job(const float *part, float *out, int nparts, int count)
 {
     int slices = 1;
-    while (slices < 64 && 4 * slices <= nparts) slices *= 2;
+    while (slices < 16 && 4 * slices <= nparts) slices *= 2;
     const int vec = count % 4 == 0 && (uintptr_t)part % 16 == 0 && (uintptr_t)out % 16 == 0;
     const int elems = 256 / slices * (vec ? 4 : 1);
     return ReduceJob{part, out, nparts, count, slices, (count + elems - 1) / elems, vec};
@@ -68,7 +70,7 @@ __device__ __forceinline__ void reduce_block(const ReduceJob &job, int bi, V *re
     const V *part = (const V *)job.part;
     V sum = V{};
     if (e < n) {
-#pragma unroll 4
+#pragma unroll 8
         for (int p = y; p < job.nparts; p += job.slices) sum += part[(size_t)p * n + e];
     }
     red[y * per + x] = sum;
