@@ -1894,8 +1894,28 @@ static bool far_pays(const Dims &D)
     return values > (D.C == 128 ? 5L : 14L) << 20;
 }
 
-// Shapes of the kernels specialised by channel count.  compact: wherever they need less scratch than the general pipeline.
-static bool specialised(const Dims &D, bool compact = false)
+// Up to 64 regions, where the general pipeline with the means of Q and K out of its projection is faster than the kernels specialised by channel count
+// (bra_route, and the layer with a given index unless it says otherwise, with it), as long as it needs no more scratch than every entry has, so
+// that all of them take the same pipeline.  Layer, us, specialised / general:
+//   fewer than 16 tokens per region: 14 x 14 x 256, k = 16: B = 32 45.1 / 36.1, 64 51.3 / 46.4, beyond: 96 66.6 / 66.2, 128 77.1 / 78.7; 14 x 28 x 256, k = 4: 38
+//     69.4 / 48.9; 14 x 14 x 128, k = 16: 64 41.9 / 33.3, 96 (k = 4) 51.2 / 44.0, beyond: 150 59.8 / 62.7
+//   16 tokens: 28 x 28 x 256, k = 4: 4 27.3 / 23.7, 16 46.8 / 42.1, beyond: 32 66.2 / 70.2; 28 x 28 x 128: k = 4: 8 23.4 / 20.8, 16 27.8 / 25.6, 24 33.9 /
+//     34.4, 48 43.9 / 52.1; 28 x 28 x 64: k = 1: 4 16.3 / 18.0, 12 18.7 / 19.0, k = 8: 12 22.8 / 20.8, k = 4: 16 21.4 / 19.6, 64 40.4 / 38.1.  With a given
+//     index the specialised kernels have no routing to wait for: 8 x 28 x 28 x 128 16.1 / 19.8, 16 x 28 x 28 x 256 38.6 / 38.8
+//   64 tokens: 56 x 56 x 128, k = 4: 1 27.8 / 22.6, 8 46.1 / 41.3 (bra_route 13.5 / 12.6; 16 14.1 / 15.5); 56 x 56 x 64, k = 2: 1 16.9 / 16.4, 8 25.9 / 21.9
+//     (bra_route 9.3 / 9.6; 12 9.7 / 11.1)
+//   not 128 tokens and more: 2 x 56 x 112 x 64, k = 4 23.6 / 25.9, 1 x 64 x 64 x 64, S = 4 24.8 / 27.8
+static bool general_pays(const Dims &D, bool given)
+{
+    if (!wide_supported(D) || wide_workspace_bytes(D) > (size_t)BRA_STATIC_SCRATCH_BYTES) return false;
+    const long values = (long)D.B * D.N * D.C;
+    if (D.n < 16) return true;
+    if (D.n == 16) return !given && (D.C == 256 || (D.C == 128 ? values <= 2L << 20 : values >= 9L << 16));
+    return D.n == 64 && (D.C == 128 || (D.C == 64 && !fused_ok(D) && values <= 2L << 20));
+}
+
+// Shapes of the kernels specialised by channel count.  compact: wherever they need less scratch than the general pipeline.  given: with a given index.
+static bool specialised(const Dims &D, bool compact = false, bool given = false)
 {
     static const bool general_only = experiment_flag("BRA_GENERAL_PIPELINE");
     if (general_only) return false;
@@ -1904,12 +1924,11 @@ static bool specialised(const Dims &D, bool compact = false)
     if ((long)D.B * D.R * (D.n / 64 + 1) + 8 > 0x7fffffffL) return false;
     if (far_routing(D))
         return wide_supported(D) && (attn_big_ok(D) || (D.n == 16 && small_supported(D) && !small_needs_projection(D))) && (compact || far_pays(D));
-    // Regions of fewer than 16 tokens: the image-resident attention needs a (image, head) pair per compute unit, and the
-    // projection with the pooling in it many tokens.  Here / there (us): 14 x 14 x 256, k = 16: B = 24 43.5 / 38.2, 64 49.6 /
-    // 69.2; 14 x 28 x 256, k = 1: 6 41.3 / 27.1, 24 58.8 / 41.4, 64 78.5 / 77.7; 14 x 14 x 128, k = 16: 24 35.5 / 27.2, 64 38.1 / 41.0;
-    // 14 x 28 x 128, k = 1, whose 8 tokens need twice the passes: 24 50.5 / 27.6, 64 50.7 / 44.9; 14 x 14 x 64: 64 29.1 / 26.2.
-    if (D.n < 16 && (D.n == 1 || D.C == 64 || D.B * (D.C / 32) < 256 || (D.C == 128 && (D.n > 4 || (long)D.B * D.N <= 8192)))) return false;
-    return attn_big_ok(D) || small_supported(D);
+    // Regions of fewer than 16 tokens: the image-resident attention needs a (image, head) pair per compute unit, the projection
+    // with the pooling in it many tokens (general_pays()); 8 tokens need twice the passes (14 x 28 x 128, k = 1, B = 64 50.7 us, general 44.9),
+    // and so few channels are not worth it (64 x 14 x 14 x 64 29.1 / 26.2).
+    if (D.n < 16 && (D.n == 1 || D.C == 64 || D.B * (D.C / 32) < 256 || (D.C == 128 && D.n > 4))) return false;
+    return (attn_big_ok(D) || small_supported(D)) && !general_pays(D, given);
 }
 
 bool wide_shape(const Dims &D) { return !specialised(D); }
@@ -1934,7 +1953,8 @@ bool mfma_supported(const Dims &D) { return addressable(D) && (specialised(D) ||
 
 size_t mfma_workspace_bytes(const Dims &D)
 {
-    return wide_shape(D) ? wide_workspace_bytes(D) : carve(D, nullptr).bytes;
+    const size_t bytes = wide_shape(D) ? wide_workspace_bytes(D) : carve(D, nullptr).bytes;
+    return specialised(D, false, true) ? std::max(bytes, carve(D, nullptr).bytes) : bytes;
 }
 
 size_t mfma_compact_workspace_bytes(const Dims &D) { return specialised(D, true) ? carve(D, nullptr).bytes : wide_workspace_bytes(D); }
@@ -1956,7 +1976,7 @@ int mfma_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, floa
 int mfma_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo, const void *Wlce,
                  void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st, bool compact)
 {
-    if (!specialised(D, compact)) return wide_forward(D, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, ws, st);
+    if (!specialised(D, compact, !compact && Ir_in_opt)) return wide_forward(D, X, Wqkv, Wo, Wlce, Y, Ir_out_opt, Ir_in_opt, ws, st);
     MfmaWs w = carve(D, ws);
     const bf16_t *x = (const bf16_t *)X, *wq = (const bf16_t *)Wqkv, *wo = (const bf16_t *)Wo,
                  *wl = (const bf16_t *)Wlce;

@@ -514,6 +514,8 @@ struct WideWs {
 
 bool many_regions(const Dims &D) { return D.S > kFastRouteMaxS; }
 
+bool means_from_projection(const Dims &D);
+
 WideWs carve(const Dims &D, void *ws)
 {
     WideWs w;
@@ -525,7 +527,7 @@ WideWs carve(const Dims &D, void *ws)
     w.k = (bf16_t *)take(tok * D.C * 2);
     w.v = (bf16_t *)take(tok * D.C * 2);
     w.o = (bf16_t *)take(tok * D.C * 2);
-    w.xr = (float *)take(reg * D.C * 4);
+    w.xr = (float *)take(means_from_projection(D) ? 0 : reg * D.C * 4);       // means of X are taken only without those of Q and K
     w.qr = (float *)take(reg * D.C * 4);
     w.kr = (float *)take(reg * D.C * 4);
     w.ir = (int32_t *)take(reg * D.k * 4);

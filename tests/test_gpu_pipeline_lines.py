@@ -1,0 +1,41 @@
+"""GPU parity on both sides of the lines between the kernels specialised by channel count and the general pipeline, for
+regions of 2 to 64 tokens: the layer against the oracle with the index of bra_route, and with that index given, which 16 tokens per region
+send to the other pipeline, within the scratch that is asked for."""
+import pytest
+import torch
+
+import paper_2303_08810_amd as bra
+from parity_util import check_output, run_oracle, to_device, to_numpy
+from synthetic_inputs import make_inputs
+from test_gpu_parity import compare
+
+pytestmark = pytest.mark.gpu
+
+LINES = [  # (B, H, W, C, S, k)
+    (32, 14, 7, 256, 7, 4),                                  # 2 tokens
+    (65, 14, 14, 256, 7, 3), (68, 14, 14, 256, 7, 3),        # 4: about 32 MB of scratch
+    (36, 14, 28, 256, 7, 2), (39, 14, 28, 256, 7, 2),        # 8
+    (18, 28, 28, 256, 7, 2), (20, 28, 28, 256, 7, 2),        # 16
+    (20, 28, 28, 128, 7, 4), (21, 28, 28, 128, 7, 4),
+    (11, 28, 28, 64, 7, 4), (12, 28, 28, 64, 7, 4),
+    (9, 56, 56, 128, 7, 1), (11, 56, 56, 128, 7, 1),         # 64
+    (10, 56, 56, 64, 7, 2), (11, 56, 56, 64, 7, 2),
+    (2, 56, 112, 64, 7, 2),                                  # 128
+]
+
+
+@pytest.mark.parametrize("B,H,W,C,S,k", LINES)
+def test_lines(B, H, W, C, S, k):
+    arrays = make_inputs(B, H, W, C, seed=7900 + B + C, dtype="bf16")
+    some = [0, B - 1]
+    compare(*arrays, "bf16", S, k, C // 32, "mfma", images=some)
+    X, Wqkv, Wo, Wlce = (to_device(a, "bf16") for a in arrays)
+    need = bra.workspace_bytes(bra.make_shape(B, H, W, C, C // 32, S, k, torch.bfloat16))
+    buffer = torch.full((need + 4096,), 77, dtype=torch.uint8, device=X.device)
+    Ir = bra.bra_route(X, Wqkv, S, k, C // 32)
+    Y = bra.bra_forward(X, Wqkv, Wo, Wlce, S, k, C // 32, Ir_in=Ir, ws=buffer[:need])
+    torch.cuda.synchronize()
+    assert bool((buffer[need:] == 77).all())
+    Ir = Ir.cpu().numpy()[some]
+    ref = run_oracle(arrays[0][some], *arrays[1:], dict(S=S, k=k, heads=C // 32), Ir_in=Ir)
+    check_output(to_numpy(Y)[some], ref["Y"], "bf16")
