@@ -1883,15 +1883,15 @@ bool attn_big_ok(const Dims &D)
 
 // More than 64 regions: where the convolution, attention and W^o in one kernel, behind the general pipeline's routing, are faster
 // than the general pipeline, whose float32 convolution moves 8 bytes more per value.  Both round O once.  Layer, S = 16 (us, general / here),
-// by millions of values: 128 x 128 x 64, k = 4: 4 50.2 / 51.7, 6 67.7 / 63.1, 8 81.8 / 75.2, 16 154.7 / 132.9, 32 310 / 261;
-// 256 x 256 x 64, k = 1: 4 52.8 / 51.7, 8 83.0 / 74.5, 32 286 / 249; 64 x 64 x 128, k = 4: 4 49.9 / 52.3, 6 68.0 / 62.0, 16 164 / 133;
-// k = 13: 16 198 / 191.  Later for 64 x 64 x 64, k = 4: 8 87.7 / 85.5, 16 174 / 163 (k = 1: 157 / 158) and 64 x 64 x 256, k = 4: 12 142.8 /
-// 142.9, 24 274 / 260 (k = 1: 12 131 / 140, 32 336 / 341).  Not for 128 x 128 x 128, k = 4: 8 84.6 / 96.4, 32 295 / 319.
+// by millions of values: 128 x 128 x 64, k = 4: 6 55.5 / 62.4, 8 67.8 / 74.3, 16 115.5 / 122.8, 20 143.7 / 154.0, 22 169.1 / 165.2, 24 195.2 / 177.2;
+// 256 x 256 x 64, k = 1: 16 114.3 / 122.0, 20 138.0 / 144.5, 32 263 / 224; 64 x 64 x 128, k = 4: 4 49.9 / 52.3, 6 66.0 / 60.4, 8 79.7 / 70.7, 12 108.2 / 99.9
+// (k = 1: 72.6 / 69.6, 97.8 / 98.0); 64 x 64 x 256, k = 4: 16 146.9 / 172.9, 20 187.8 / 220.8, 24 248.9 / 254.6, 28 305.6 / 290.3 (k = 1 274.3 /
+// 284.2).  Not for 128 x 128 x 128, k = 4: 8 84.6 / 96.4, 32 295 / 319.
 static bool far_pays(const Dims &D)
 {
     const long values = (long)D.B * D.N * D.C;
-    if (attn_big_ok(D)) return D.C == 64 && attn_q32_ok(D) && values > 5L << 20;
-    return values > (D.C == 128 ? 5L : 14L) << 20;
+    if (attn_big_ok(D)) return D.C == 64 && attn_q32_ok(D) && values > 21L << 20;
+    return values > (D.C == 128 ? 5L : D.C == 64 ? 21L : 27L) << 20;
 }
 
 // Up to 64 regions, where the general pipeline with the means of Q and K out of its projection is faster than the kernels specialised by channel count

@@ -21,6 +21,9 @@ LINES = [  # (B, H, W, C, S, k)
     (9, 56, 56, 128, 7, 1), (11, 56, 56, 128, 7, 1),         # 64
     (10, 56, 56, 64, 7, 2), (11, 56, 56, 64, 7, 2),
     (2, 56, 112, 64, 7, 2),                                  # 128
+    (21, 128, 128, 64, 16, 1), (22, 128, 128, 64, 16, 1),    # 256 regions of 64
+    (84, 64, 64, 64, 16, 1), (85, 64, 64, 64, 16, 1),        # and of 16
+    (27, 64, 64, 256, 16, 1), (28, 64, 64, 256, 16, 1),
 ]
 
 
