@@ -595,10 +595,13 @@ __device__ __forceinline__ void attention_block(const float *Kw, const float *Vw
 }
 
 // HPW = 1: as many wavefronts as the region's query tiles of 16 fill (3 to 8; more tiles are dealt out evenly).
-template <int DP, int HPW, bool VEC>
+// OUT: with Y = O Wo (Eq. 7) for the four heads of C = 128 and regions of at most 16 tokens; O, which holds LCE(V), is read and not written.  A
+// wavefront forms 32 columns of Y, lane i's operands of two tiles being neighbours in a row of Wo.
+template <int DP, int HPW, bool VEC, bool OUT = false>
 __global__ __launch_bounds__(HPW == 1 ? 512 : 256, DP == 32 ? 4 : 2) void k_attention(const float *__restrict__ QKV, const int32_t *__restrict__ Ir,
-                                                   float *__restrict__ O, Dims D, int hgroups, int qtiles, bool adds)
+                                                   float *__restrict__ O, Dims D, int hgroups, int qtiles, bool adds, const float *__restrict__ Wo, float *__restrict__ Y)
 {
+    static_assert(!OUT || (DP == 32 && HPW == 4 && VEC), "C = 128");
     typedef AttnShape<DP, HPW> L;
     constexpr int P = L::P, KB = L::KB, CW = L::CW, NS = DP / 16;
     __shared__ __attribute__((aligned(16))) float Ks[KB * P];
@@ -659,6 +662,34 @@ __global__ __launch_bounds__(HPW == 1 ? 512 : 256, DP == 32 ? 4 : 2) void k_atte
         attention_block<KB, P, NS>(Ks + DP * hl, Vs + DP * hl, qf, kn - k0, k0 == 0, g, i, m, l, acc);
     }
     const float denominator = cross_row_sum((l[0] + l[1]) + (l[2] + l[3]));
+    if constexpr (OUT) {
+        const float inv = 1.0f / denominator, *added = O + ((size_t)b * D.N + qtok) * CW + DP * hl + 4 * g;
+        __syncthreads();                         // the last block has been read
+#pragma unroll
+        for (int dt = 0; dt < NS; ++dt) {
+            f32x4 v = acc[dt] * inv;
+            v += *(const f32x4 *)(added + 16 * dt);
+            *(f32x4 *)(Ks + i * P + DP * hl + 16 * dt + 4 * g) = v;
+        }
+        __syncthreads();
+        const float *w = Wo + (size_t)4 * g * CW + 32 * wave + 2 * i;
+        f32x4 y[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int s = 0; s < CW / 16; ++s) {
+            const f32x4 x = *(const f32x4 *)(Ks + i * P + 16 * s + 4 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const f32x2 v = *(const f32x2 *)(w + (size_t)(16 * s + e) * CW);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) y[t] = mfma_f32(v[t], x[e], y[t]);
+            }
+        }
+        if (slot >= D.n) return;
+        float *to = Y + ((size_t)b * D.N + qtok) * CW + 32 * wave + 8 * g;      // columns 8 g + 2 j + t
+        *(f32x4 *)to = f32x4{y[0][0], y[1][0], y[0][1], y[1][1]};
+        *(f32x4 *)(to + 4) = f32x4{y[0][2], y[1][2], y[0][3], y[1][3]};
+        return;
+    }
     if (slot < D.n && h < D.heads) {
         const float inv = 1.0f / denominator;
         float *orow = O + ((size_t)b * D.N + qtok) * D.C + h * D.d;

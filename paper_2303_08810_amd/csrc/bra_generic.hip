@@ -335,7 +335,7 @@ int launch_attention_t(const Dims &D, const float *qkv, const int32_t *Ir, float
     const long blocks = ((long)D.B * D.R * hgroups * qtiles + 7) / 8 * 8;
     if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     hipLaunchKernelGGL((f32::k_attention<DP, HPW, VEC>), dim3((unsigned)blocks), dim3(64 * waves), 0, st, qkv, Ir, o, D, hgroups,
-                       qtiles, adds);
+                       qtiles, adds, nullptr, nullptr);
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -374,13 +374,17 @@ TileSplit out_split(const Dims &D)
     return split.each > 4 && (long)D.B * D.R * split.groups < 256 ? TileSplit{4, (tiles + 3) / 4} : split;
 }
 
-// Attention and Y = O Wo in one kernel: two heads of 32 channels.  That is a launch and two passes over O less, 2 us on 3000 tokens and 9 on
+// Attention and Y = O Wo in one kernel: two or four heads of 32 channels.  For two that is a launch and two passes over O less, 2 us on 3000 tokens and 9 on
 // 50000 (16 x 56 x 56 x 64, k = 1: 61.7 -> 57.2; 60 x 28 x 28, k = 1 69.5 -> 63.8; 2 x 112 x 112, S = 16, k = 4 59.2 -> 54.3; 2 x 80 x 80, S = 8 54.1 -> 49.5);
 // but both heads share a compute unit, and a block of keys takes its wavefronts' time, a microsecond for four: where that is more than 3 us
 // longer the heads stay apart (1 x 56 x 56, S = 7, k = 2, 3 and 8 25.4, 27.6, 36.8 apart and 24.2, 27.7, 42.0 together; 2 x 64 x 64, S = 4, k = 4 61.7 and 73.2),
 // for short maps (1 x 40 x 40, S = 4, k = 2 31.9 and 32.7) and many keys (1 x 128 x 128, S = 8, k = 4, 16 blocks 82.5 and 79.6; S = 4, 64 blocks 233.6 and 236.9).
+// Four heads of 32, in regions of at most 16 tokens, share a workgroup anyway: 6 x 28 x 28 x 128, k = 4 35.8 -> 32.1 us, 40 images 92.6 -> 88.0, 1 x
+// 14 x 14 25.0 -> 20.3, 24 x 21 x 21 56.1 -> 53.6; but each region reads all of Wo and multiplies a tile of 16 rows: 64 x 14 x 14 x 128 (3136 regions of
+// 4 tokens), k = 16 76.8 and 83.1.
 bool attention_with_out(const Dims &D)
 {
+    if (D.C == 128 && D.d == 32 && D.n <= 16) return D.n > 9 || (long)D.B * D.R <= 1200;
     if (D.C != 64 || D.d != 32 || (long)D.B * D.N < 2048) return false;
     const int tiles = (D.n + 15) / 16;
     const TileSplit one = split_tiles(tiles, 3), both = out_split(D);
@@ -393,11 +397,15 @@ bool attention_with_out(const Dims &D)
 // o holds LCE(V).
 int launch_attention_out(const Dims &D, const float *qkv, const int32_t *Ir, const float *o, const float *Wo, float *Y, hipStream_t st)
 {
-    const TileSplit split = out_split(D);
+    const TileSplit split = D.C == 128 ? TileSplit{2, 1} : out_split(D);
     const long blocks = ((long)D.B * D.R * split.groups + 7) / 8 * 8;
     if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, K_GEN_ATTENTION);
     const dim3 grid((unsigned)blocks), threads(128 * split.each);
+    if (D.C == 128) {
+        hipLaunchKernelGGL((f32::k_attention<32, 4, true, true>), grid, threads, 0, st, qkv, Ir, const_cast<float *>(o), D, 1, 1, true, Wo, Y);
+        return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+    }
     const size_t smem = f32::out_lds_bytes(split.each);
     if (split.each == 2) hipLaunchKernelGGL(f32::k_attention_out<4>, grid, threads, smem, st, qkv, Ir, o, Wo, Y, D, split.groups);
     else hipLaunchKernelGGL(f32::k_attention_out<2>, grid, threads, smem, st, qkv, Ir, o, Wo, Y, D, split.groups);

@@ -1,4 +1,4 @@
-"""GPU parity of float32 layers whose attention carries the output projection (64 channels, two heads): one and two query tiles of a region,
+"""GPU parity of float32 layers whose attention carries the output projection (64 channels, two heads, and 128, four): one and two query tiles of a region,
 ragged ones, four to six in a workgroup and several workgroups per region, ragged blocks of keys; against the oracle and its float32 error
 bounds, and the same index as the routing on its own."""
 import pytest
@@ -27,3 +27,19 @@ SHAPES = [  # (B, H, W, S, k)
 def test_f32_attention_out(B, H, W, S, k):
     X, Wqkv, Wo, Wlce = make_inputs(B, H, W, 64, seed=7700 + H * W, dtype="f32")
     compare(X, Wqkv, Wo, Wlce, "f32", S, k, 2, "generic", images=[0, B - 1])
+
+
+WIDE = [  # (B, H, W, S, k)
+    (1, 14, 14, 7, 4),        # 4 tokens per region, half a block of keys
+    (24, 14, 14, 7, 16),      # 1176 regions: two blocks of keys
+    (25, 14, 14, 7, 5),       # 1225: the products apart
+    (3, 21, 21, 7, 11),       # 9 tokens, 99 keys
+    (6, 28, 28, 7, 4),        # 16 tokens
+    (2, 20, 12, 4, 16),       # 15 tokens, 240 keys
+]
+
+
+@pytest.mark.parametrize("B,H,W,S,k", WIDE)
+def test_f32_attention_out_four_heads(B, H, W, S, k):
+    X, Wqkv, Wo, Wlce = make_inputs(B, H, W, 128, seed=7760 + H * W, dtype="f32")
+    compare(X, Wqkv, Wo, Wlce, "f32", S, k, 4, "generic", images=[0, B - 1])
