@@ -1897,8 +1897,10 @@ static bool far_pays(const Dims &D)
 // Up to 64 regions, where the general pipeline with the means of Q and K out of its projection is faster than the kernels specialised by channel count
 // (bra_route, and the layer with a given index unless it says otherwise, with it), as long as it needs no more scratch than every entry has, so
 // that all of them take the same pipeline.  Layer, us, specialised / general:
-//   fewer than 16 tokens per region: 14 x 14 x 256, k = 16: B = 32 45.1 / 36.1, 64 51.3 / 46.4, beyond: 96 66.6 / 66.2, 128 77.1 / 78.7; 14 x 28 x 256, k = 4: 38
-//     69.4 / 48.9; 14 x 14 x 128, k = 16: 64 41.9 / 33.3, 96 (k = 4) 51.2 / 44.0, beyond: 150 59.8 / 62.7
+//   fewer than 16 tokens per region: 14 x 28 x 256, k = 4: B = 20 37.4 / 31.7, 38 68.9 / 69.0; 14 x 14 x 256, k = 16: 24 37.9 / 32.9, 40 47.2 / 42.9; 14 x 14 x 128,
+//     k = 16: 64 38.4 / 33.8, 83 46.8 / 44.8.  Of up to 4 tokens not beyond 2 million values: 14 x 14 x 256: 56 55.9 / 53.1, 64 49.6 / 48.2, 96 66.6 / 66.2, 128
+//     77.1 / 78.7; 14 x 14 x 128: 100 53.6 / 51.7, 150 59.8 / 62.7.  The two add a row of A^r up in different orders, so that a near tie can fall
+//     either way (2 of 188 thousand rows at 64 x 14 x 14 x 256): ever more rows, for ever less
 //   16 tokens: 28 x 28 x 256, k = 4: 4 27.3 / 23.7, 16 46.8 / 42.1, beyond: 32 66.2 / 70.2; 28 x 28 x 128: k = 4: 8 23.4 / 20.8, 16 27.8 / 25.6, 24 33.9 /
 //     34.4, 48 43.9 / 52.1; 28 x 28 x 64: k = 1: 4 16.3 / 18.0, 12 18.7 / 19.0, k = 8: 12 22.8 / 20.8, k = 4: 16 21.4 / 19.6, 64 40.4 / 38.1.  With a given
 //     index the specialised kernels have no routing to wait for: 8 x 28 x 28 x 128 16.1 / 19.8, 16 x 28 x 28 x 256 38.6 / 38.8
@@ -1909,7 +1911,7 @@ static bool general_pays(const Dims &D, bool given)
 {
     if (!wide_supported(D) || wide_workspace_bytes(D) > (size_t)BRA_STATIC_SCRATCH_BYTES) return false;
     const long values = (long)D.B * D.N * D.C;
-    if (D.n < 16) return true;
+    if (D.n < 16) return D.n > 4 || values <= 2L << 20;
     if (D.n == 16) return !given && (D.C == 256 || (D.C == 128 ? values <= 2L << 20 : values >= 9L << 16));
     return D.n == 64 && (D.C == 128 || (D.C == 64 && !fused_ok(D) && values <= 2L << 20));
 }

@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
 
 LINES = [  # (B, H, W, C, S, k)
     (32, 14, 7, 256, 7, 4),                                  # 2 tokens
-    (65, 14, 14, 256, 7, 3), (68, 14, 14, 256, 7, 3),        # 4: about 32 MB of scratch
+    (41, 14, 14, 256, 7, 3), (42, 14, 14, 256, 7, 3),        # 4
+    (83, 14, 14, 128, 7, 3), (84, 14, 14, 128, 7, 3),
+    (65, 14, 14, 256, 7, 3), (68, 14, 14, 256, 7, 3),
     (36, 14, 28, 256, 7, 2), (39, 14, 28, 256, 7, 2),        # 8
     (18, 28, 28, 256, 7, 2), (20, 28, 28, 256, 7, 2),        # 16
     (20, 28, 28, 128, 7, 4), (21, 28, 28, 128, 7, 4),
