@@ -18,8 +18,9 @@ LINES = [  # (B, H, W, C, S, k)
     (65, 14, 14, 256, 7, 3), (68, 14, 14, 256, 7, 3),
     (36, 14, 28, 256, 7, 2), (39, 14, 28, 256, 7, 2),        # 8
     (18, 28, 28, 256, 7, 2), (20, 28, 28, 256, 7, 2),        # 16
-    (20, 28, 28, 128, 7, 4), (21, 28, 28, 128, 7, 4),
-    (11, 28, 28, 64, 7, 4), (12, 28, 28, 64, 7, 4),
+    (2, 28, 28, 128, 7, 3), (10, 28, 28, 128, 7, 4), (11, 28, 28, 128, 7, 4),
+    (20, 28, 28, 128, 7, 8), (21, 28, 28, 128, 7, 8),
+    (11, 28, 28, 64, 7, 4), (12, 28, 28, 64, 7, 4), (26, 28, 28, 64, 7, 4), (27, 28, 28, 64, 7, 4),
     (9, 56, 56, 128, 7, 1), (11, 56, 56, 128, 7, 1),         # 64
     (10, 56, 56, 64, 7, 2), (11, 56, 56, 64, 7, 2),
     (2, 56, 112, 64, 7, 2),                                  # 128
