@@ -1752,7 +1752,7 @@ int forward_c(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const bf16_t *
     {
         const bool far = far_routing(D), from_x = !far && (fused || !pooled_projection(D)) && !Ir_in_opt;
         if (far && !Ir_in_opt) {
-            const int rc = wide_route_pooled(D, X, Wqkv, Ir_dst, nullptr, w.means, st);
+            const int rc = wide_route_far(D, X, Wqkv, Ir_dst, nullptr, w.means, st);
             if (rc != BRA_OK) return rc;
             Ir_src = Ir_dst;
         }
@@ -1847,7 +1847,7 @@ int route_c(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, int32_t *Ir, flo
     // the same kernels as bra_forward runs for this shape, so that both give the same index
     int rc;
     if (far_routing(D)) {
-        rc = wide_route_pooled(D, X, Wqkv, Ir, Ar_opt, w.means, st);
+        rc = wide_route_far(D, X, Wqkv, Ir, Ar_opt, w.means, st);
     } else if (C == 64 && fused_ok(D)) {
         launch_pool<C>(D, X, Wqkv, nullptr, nullptr, w, /*pool=*/true, 0, st, /*with_u=*/true);
         ProfScope ps(st, K_MFMA_ROUTE_ROWS);

@@ -717,7 +717,7 @@ int wide_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, floa
                hipStream_t st);
 // Its routing steps alone, for regions of more than one token; means: scratch of wide_means_bytes(D).
 size_t wide_means_bytes(const Dims &D);
-int wide_route_pooled(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *means, hipStream_t st);
+int wide_route_far(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *means, hipStream_t st);
 int wide_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo, const void *Wlce, void *Y,
                  int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st, int H = 0, int W = 0, void *Yp = nullptr);
 

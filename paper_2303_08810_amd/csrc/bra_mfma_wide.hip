@@ -700,14 +700,15 @@ int wide_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, floa
 
 size_t wide_means_bytes(const Dims &D) { return 3 * align256((size_t)D.B * D.R * D.C * 4); }
 
-int wide_route_pooled(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *means, hipStream_t st)
+// The index of wide_route and wide_forward, bit for bit, in less scratch (regions of more than one token).
+int wide_route_far(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *means, hipStream_t st)
 {
     const size_t each = wide_means_bytes(D) / 3;
     WideWs w = {};
     w.xr = (float *)means;
     w.qr = (float *)((char *)means + each);
     w.kr = (float *)((char *)means + 2 * each);
-    return route_pooled(D, (const bf16_t *)X, (const bf16_t *)Wqkv, w, Ir, Ar_opt, st);
+    return route_steps(D, (const bf16_t *)X, (const bf16_t *)Wqkv, w, Ir, Ar_opt, st);
 }
 
 // H, W: the caller's map where D describes a zero-padded one (0: it does not): the products and the pooling read tokens

@@ -1,5 +1,5 @@
-"""bra_route gives the very index that bra_forward uses, for every pipeline: both run the same arithmetic, so not even a
-tie that only roundings decide may come out differently."""
+"""bra_route and bra_forward_static give the very index that bra_forward uses, for every pipeline: all run the same arithmetic,
+so not even a tie that only roundings decide may come out differently."""
 import numpy as np
 import pytest
 import torch
@@ -30,8 +30,7 @@ SHAPES = [  # (dtype, B, H, W, C, heads, S, k)
 ]
 
 
-@pytest.mark.parametrize("dtype,B,H,W,C,heads,S,k", SHAPES)
-def test_route_matches_forward(dtype, B, H, W, C, heads, S, k):
+def paired_inputs(dtype, B, H, W, C, S):
     X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=9700 + C + H, dtype=dtype)
     # the halves of the channels have the same weights, and regions 2 r and 2 r + 1 the same tokens with the halves exchanged:
     # their affinities are equal and differ by the order of summation alone
@@ -40,7 +39,28 @@ def test_route_matches_forward(dtype, B, H, W, C, heads, S, k):
     pairs = S * S // 2
     V[:, 1:2 * pairs:2] = np.roll(V[:, 0:2 * pairs:2], C // 2, axis=-1)
     X = V.reshape(B, S, S, H // S, W // S, C).transpose(0, 1, 3, 2, 4, 5).reshape(B, H, W, C)
-    X, Wqkv, Wo, Wlce = (to_device(np.ascontiguousarray(a), dtype) for a in (X, Wqkv, Wo, Wlce))
+    return [to_device(np.ascontiguousarray(a), dtype) for a in (X, Wqkv, Wo, Wlce)]
+
+
+@pytest.mark.parametrize("dtype,B,H,W,C,heads,S,k", SHAPES)
+def test_route_matches_forward(dtype, B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = paired_inputs(dtype, B, H, W, C, S)
     Ir = bra.bra_route(X, Wqkv, S, k, heads)
     used = bra.bra_forward(X, Wqkv, Wo, Wlce, S, k, heads, want_Ir=True)[1]
     assert torch.equal(Ir, used), f"{int((Ir != used).sum())} of {Ir.numel()} entries differ"
+
+
+# More than 64 regions, where the pipeline of bra_forward needs more scratch than the built-in buffer has and another one runs
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", [
+    (17, 64, 64, 64, 2, 16, 32), (18, 64, 64, 64, 2, 16, 4),        # 16 tokens, 4.5 x 2^20 values: means out of the projection
+    (9, 64, 64, 128, 4, 16, 32), (4, 64, 64, 256, 8, 16, 32),
+    (4, 128, 128, 64, 2, 16, 8), (2, 128, 128, 128, 4, 16, 8),      # 64 tokens, 4 x 2^20
+    (5, 128, 128, 64, 2, 16, 8)])                                   # beyond: means of the tokens, projected
+def test_static_matches_forward(B, H, W, C, heads, S, k):
+    X, Wqkv, Wo, Wlce = paired_inputs("bf16", B, H, W, C, S)
+    assert bra.workspace_bytes(bra.make_shape(B, H, W, C, heads, S, k, torch.bfloat16)) > bra.STATIC_SCRATCH_BYTES
+    used = bra.bra_forward(X, Wqkv, Wo, Wlce, S, k, heads, want_Ir=True)[1]
+    static = torch.full_like(used, -1)
+    bra.bra_forward_static(X, Wqkv, Wo, Wlce, S, k, heads, out=torch.empty_like(X), Ir_out=static)
+    assert torch.equal(static, used), f"{int((static != used).sum())} of {used.numel()} entries differ"
+    assert torch.equal(bra.bra_route(X, Wqkv, S, k, heads), used)
