@@ -226,11 +226,15 @@ inline Tiling strips_of(const Dims &D, int height, long &tiles)
     return T;
 }
 
+// The fewest strips of less than `height` rows: the next ones worth a look, however high the map (a strip more each time took 158 us
+// per call on the host for 65536 rows).
+inline int lower_strips(const Dims &D, int height) { return (D.H + height - 2) / (height - 1); }
+
 // Strips of even heights, at most 20 rows: the highest with `want` tiles and rows that span little enough, or 5.
 inline Tiling even_tiling(const Dims &D, int ldo, long want, long &tiles)
 {
-    for (int strips = (D.H + 19) / 20;; ++strips) {
-        const int height = (D.H + strips - 1) / strips;
+    for (int strips = (D.H + 19) / 20, height;; strips = lower_strips(D, height)) {
+        height = (D.H + strips - 1) / strips;
         const Tiling T = strips_of(D, height, tiles);
         if (height <= 5 || (tiles >= want && offsets_fit(D, T, ldo))) return T;
     }
@@ -254,8 +258,8 @@ inline Tiling forward_tiling(const Dims &D, int ldo, int cblocks, int beside, lo
     bool found = false, apart = false;
     double least = 0;
     const double places = std::max(256, 512 - beside);
-    for (int strips = (D.H + 23) / 24;; ++strips) {
-        const int height = (D.H + strips - 1) / strips;
+    for (int strips = (D.H + 23) / 24, height;; strips = lower_strips(D, height)) {
+        height = (D.H + strips - 1) / strips;
         const bool last = height <= 4;
         long n;
         const Tiling T = strips_of(D, height, n);
