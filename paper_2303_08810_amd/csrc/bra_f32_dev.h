@@ -594,21 +594,36 @@ __device__ __forceinline__ void attention_block(const float *Kw, const float *Vw
     rows_product<KT, NS>(Vw + 4 * g * P + i, P, st, acc);
 }
 
+// What a workgroup of the attention works on.  by_image: those of an image and head group on one XCD, whose L2 then holds that
+// pair's rows (attention_by_image(), gradients_by_image()); else the head groups of a region next to each other, on different ones.
+struct AttnWork {
+    int tile, region, hg, image;
+};
+
+__device__ __forceinline__ AttnWork attn_work(int block, int blocks, bool by_image, int tiles, int hgroups, int R)
+{
+    if (by_image) {
+        const int at = mfma::swizzled(block, blocks), region = at / tiles, pair = region / R;
+        return AttnWork{at - region * tiles, region - pair * R, pair % hgroups, pair / hgroups};
+    }
+    const int tile = block / hgroups, region = tile / tiles, image = region / R;
+    return AttnWork{tile - region * tiles, region - image * R, block - tile * hgroups, image};
+}
+
 // HPW = 1: as many wavefronts as the region's query tiles of 16 fill (3 to 8; more tiles are dealt out evenly).
 // OUT: with Y = O Wo (Eq. 7) for the four heads of C = 128 and regions of at most 16 tokens; O, which holds LCE(V), is read and not written.  A
 // wavefront forms 32 columns of Y, lane i's operands of two tiles being neighbours in a row of Wo.
 template <int DP, int HPW, bool VEC, bool OUT = false>
 __global__ __launch_bounds__(HPW == 1 ? 512 : 256, DP == 32 ? 4 : 2) void k_attention(const float *__restrict__ QKV, const int32_t *__restrict__ Ir,
-                                                   float *__restrict__ O, Dims D, int hgroups, int qtiles, bool adds, const float *__restrict__ Wo, float *__restrict__ Y)
+                                                   float *__restrict__ O, Dims D, int hgroups, int qtiles, bool by_image, bool adds, const float *__restrict__ Wo, float *__restrict__ Y)
 {
     static_assert(!OUT || (DP == 32 && HPW == 4 && VEC), "C = 128");
     typedef AttnShape<DP, HPW> L;
     constexpr int P = L::P, KB = L::KB, CW = L::CW, NS = DP / 16;
     __shared__ __attribute__((aligned(16))) float Ks[KB * P];
     __shared__ __attribute__((aligned(16))) float Vs[KB * P];
-    // workgroups of an image and head group on one XCD (layer of 32 x 28 x 28 x 128, k = 4 85.4 -> 82.7 us)
-    const int block = mfma::swizzled_block(), qt = block % qtiles, reg = (block / qtiles) % D.R;
-    const int hg = (block / (qtiles * D.R)) % hgroups, b = block / (qtiles * D.R * hgroups);
+    const AttnWork work = attn_work(blockIdx.x, gridDim.x, by_image, qtiles, hgroups, D.R);
+    const int qt = work.tile, reg = work.region, hg = work.hg, b = work.image;
     if (b >= D.B) return;
     const int T = HPW == 1 ? (int)blockDim.x : 256, tph = HPW == 1 ? T / kWave : L::TPH;      // query tiles
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
@@ -814,7 +829,7 @@ template <int DP, int HPW, bool VEC, int KB>
 __global__ __launch_bounds__(256) void k_attn_bwd_q(const float *__restrict__ QKV, const float *__restrict__ dO,
                                                     const int32_t *__restrict__ Ir, float *__restrict__ O,
                                                     float *__restrict__ dQKV, float *__restrict__ lse,
-                                                    float *__restrict__ dsum, Dims D, int hgroups, int qtiles,
+                                                    float *__restrict__ dsum, Dims D, int hgroups, int qtiles, bool by_image,
                                                     lce::GradJob<float> J, int lce_blocks)
 {
     typedef AttnShape<DP, HPW> L;
@@ -826,8 +841,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q(const float *__restrict__ QK
         lce::lce_grad_block<VEC ? 2 : 1, false>(J, D, mfma::swizzled(wg, wgs), lds);
         return;
     }
-    wg = mfma::swizzled(wg, wgs);
-    const int qt = wg % qtiles, reg = (wg / qtiles) % D.R, hg = (wg / (qtiles * D.R)) % hgroups, b = wg / (qtiles * D.R * hgroups);
+    const AttnWork work = attn_work(wg, wgs, by_image, qtiles, hgroups, D.R);
+    const int qt = work.tile, reg = work.region, hg = work.hg, b = work.image;
     if (b >= D.B) return;
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C3 = 3 * D.C, kn = D.kn, nblocks = (kn + KB - 1) / KB, hl = wave / L::TPH, h = hg * HPW + hl;
@@ -981,7 +996,7 @@ template <int DP, int HPW, bool VEC>
 __global__ __launch_bounds__(256) void k_attn_bwd_kv(const float *__restrict__ QKV, const float *__restrict__ dO,
                                                      const int32_t *__restrict__ Ir, const float *__restrict__ lse,
                                                      const float *__restrict__ dsum, float *__restrict__ dQKV, Dims D,
-                                                     int hgroups, int ktiles, lce::AddJob<float> J, int lce_blocks)
+                                                     int hgroups, int ktiles, bool by_image, lce::AddJob<float> J, int lce_blocks)
 {
     typedef AttnShape<DP, HPW> L;
     constexpr int P = L::P, QB = L::KB, CW = L::CW, QTL = QB / 16, NS = DP / 16;
@@ -995,8 +1010,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv(const float *__restrict__ Q
         lce::lce_block<VEC ? 2 : 1, true, 256>(J, D, mfma::swizzled(wg, wgs), lds);
         return;
     }
-    wg = mfma::swizzled(wg, wgs);
-    const int kt = wg % ktiles, reg = (wg / ktiles) % D.R, hg = (wg / (ktiles * D.R)) % hgroups, b = wg / (ktiles * D.R * hgroups);
+    const AttnWork work = attn_work(wg, wgs, by_image, ktiles, hgroups, D.R);
+    const int kt = work.tile, reg = work.region, hg = work.hg, b = work.image;
     if (b >= D.B) return;
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C3 = 3 * D.C, hl = wave / L::TPH, h = hg * HPW + hl;

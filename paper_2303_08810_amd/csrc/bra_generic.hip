@@ -319,6 +319,28 @@ TileSplit split_tiles(int tiles, int least)
     return 5 * groups * even <= 4 * 4 * quads ? TileSplit{even, groups} : TileSplit{4, quads};
 }
 
+// Workgroups of an image and head group on one XCD, or the head groups of a region on different ones.  The first reads an image's rows into
+// one L2 instead of all; but of few images it leaves nothing to save where a region reads most of them, and the workgroups of an XCD
+// then ask for the same lines at the same time.  Layer with a given index, us, apart / by image: float32 24 x 16 x 16 x 64, S = 8, k = 16 36.9 / 30.8,
+// 4 x 24 x 32 x 128, S = 8, k = 4 33.9 / 30.5, 2 x 56 x 48 x 96, S = 8, k = 24 79.1 / 75.7; bf16 12 x 24 x 32 x 96, S = 8, k = 4 36.6 / 27.8; against that
+// float32 1 x 35 x 35 x 256, k = 40 69.6 / 78.2, 1 x 49 x 42 x 128, k = 16 47.2 / 50.0, 1 x 14 x 14 x 768, k = 49 75.2 / 78.4, 2 x 35 x 35 x 192, k = 40
+// 90.0 / 93.0.  Left on the wrong side: 4 x 21 x 28 x 128, k = 49 61.9 / 67.0.
+bool attention_by_image(const Dims &D, int hgroups)
+{
+    return D.B >= 4 || (long)D.B * hgroups >= 8 || 6L * D.k <= D.R || (D.B >= 2 && 8L * D.k <= 5L * D.R);
+}
+
+// The gradients: a key region's workgroup goes over all that chose it, so that an XCD with a part of a pair has more or less work than
+// the others, by chance; with a pair or more each, or many workgroups, that evens out.  us, apart / by image: float32 6 x 32 x 32 x 128, S = 8, k = 4
+// 89.4 / 84.8, bf16 64 x 28 x 28 x 96, k = 16 677 / 641, 1 x 192 x 192 x 96, S = 16, k = 4 790 / 767; against that bf16 1 x 56 x 84 x 96, k = 3 120.4 / 132.2, 1 x
+// 112 x 96 x 96, S = 16, k = 16 328.5 / 362.3, float32 1 x 48 x 48 x 192, S = 8, k = 2 82.6 / 88.7, 2 x 40 x 104 x 96, S = 8, k = 1 108.1 / 115.1.  Of one or
+// two head groups neither is the better one on average (0.90 to 1.05) until a region reads most of its image (2 x 21 x 21 x 256, k = 49
+// 156.8 / 164.0).
+bool gradients_by_image(const Dims &D, int hgroups, long workgroups)
+{
+    return (long)D.B * hgroups >= 8 || workgroups >= 2048 || (hgroups <= 2 && 2L * D.k <= D.R);
+}
+
 template <int DP, int HPW, bool VEC>
 int launch_attention_t(const Dims &D, const float *qkv, const int32_t *Ir, float *o, bool adds, hipStream_t st)
 {
@@ -335,7 +357,7 @@ int launch_attention_t(const Dims &D, const float *qkv, const int32_t *Ir, float
     const long blocks = ((long)D.B * D.R * hgroups * qtiles + 7) / 8 * 8;
     if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     hipLaunchKernelGGL((f32::k_attention<DP, HPW, VEC>), dim3((unsigned)blocks), dim3(64 * waves), 0, st, qkv, Ir, o, D, hgroups,
-                       qtiles, adds, nullptr, nullptr);
+                       qtiles, attention_by_image(D, hgroups), adds, nullptr, nullptr);
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -403,7 +425,7 @@ int launch_attention_out(const Dims &D, const float *qkv, const int32_t *Ir, con
     ProfScope ps(st, K_GEN_ATTENTION);
     const dim3 grid((unsigned)blocks), threads(128 * split.each);
     if (D.C == 128) {
-        hipLaunchKernelGGL((f32::k_attention<32, 4, true, true>), grid, threads, 0, st, qkv, Ir, const_cast<float *>(o), D, 1, 1, true, Wo, Y);
+        hipLaunchKernelGGL((f32::k_attention<32, 4, true, true>), grid, threads, 0, st, qkv, Ir, const_cast<float *>(o), D, 1, 1, attention_by_image(D, 1), true, Wo, Y);
         return launched() ? BRA_OK : BRA_ERR_LAUNCH;
     }
     const size_t smem = f32::out_lds_bytes(split.each);
@@ -639,6 +661,7 @@ int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lc
 {
     const int hgroups = (D.heads + HPW - 1) / HPW, qt = f32::AttnShape<DP, HPW>::QT, tiles = (D.n + qt - 1) / qt;
     const long blocks = ((long)D.B * D.R * hgroups * tiles + 7) / 8 * 8;
+    const bool by_image = gradients_by_image(D, hgroups, blocks);
     // The passes of the depth-wise convolution's gradients lie behind the workgroups of the attention: the one with the tap
     // gradients beside the query side, which leaves dV to be added to by the key side, O += LCE(V) beside the key side.  In
     // front of the query side it was slower (4 x 56 x 56 x 64, k = 2: 100.9 us behind, 105.6 in front; 8 x 28 x 28 x 128: 92.0, 95.5).
@@ -648,7 +671,7 @@ int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lc
     if (blocks + std::max(grad.p.blocks(), add.blocks) > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     auto query_side = [&](auto kb) {
         hipLaunchKernelGGL((f32::k_attn_bwd_q<DP, HPW, VEC, decltype(kb)::value>), dim3((unsigned)(blocks + grad.p.blocks())), dim3(256), 0, st,
-                           w.qkv, w.dO, Ir, w.o, w.dqkv, w.lse, w.dsum, D, hgroups, tiles, grad, grad.p.blocks());
+                           w.qkv, w.dO, Ir, w.o, w.dqkv, w.lse, w.dsum, D, hgroups, tiles, by_image, grad, grad.p.blocks());
     };
     constexpr int KB = f32::AttnShape<DP, HPW>::KB;
     // 33 to 64 routed keys as a single block of 64, so that they are not taken twice (8 x 28 x 28 x 128, k = 4: 91.5 -> 88.1 us; 29 x
@@ -661,7 +684,7 @@ int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lc
         query_side(std::integral_constant<int, KB>{});
     }
     hipLaunchKernelGGL((f32::k_attn_bwd_kv<DP, HPW, VEC>), dim3((unsigned)(blocks + add.blocks)), dim3(256), 0, st, w.qkv, w.dO, Ir, w.lse,
-                       w.dsum, w.dqkv, D, hgroups, tiles, add, add.blocks);
+                       w.dsum, w.dqkv, D, hgroups, tiles, by_image, add, add.blocks);
     if (!launched()) return BRA_ERR_LAUNCH;
     return add.blocks ? BRA_OK : lce::launch_lce<float>(D, V, 3 * D.C, taps, w.o, D.C, K_GEN_BACKWARD, st);
 }
