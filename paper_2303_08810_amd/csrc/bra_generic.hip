@@ -209,13 +209,15 @@ f32::GemmJob<float, T, float> region_job(const Dims &D, const T *Wqkv, const Gen
     return {w.xr, Wqkv, w.qk, (long)D.B * D.R, D.C, 3 * D.C, 2 * D.C, 2 * D.C, D.C, nullptr, nullptr, 0};
 }
 
-// The means of Q and K out of the token projection, whose tiles go region by region: faster for bra_forward throughout (a pooling pass
-// and a region-level product less).  bra_route, which has to decide on the same bits, projects all tokens for it; the lines lie
-// where that takes as long.  bra_forward before -> now / bra_route (us): 4 x 14 x 14 x 256 38.3 -> 35.9 / 18.8 -> 15.7, 2 x 64 x 64 x 128 49.5 -> 44.8, 1 x 21
-// x 21 x 768 79.3 -> 65.7, 50 x 28 x 28 x 96 bf16 74.7 -> 69.7 / 17.6 -> 15.2.  float32, by tiles of bra_route's product, beyond a round of them times
-// C: 56 thousand (C = 192) 17.1 -> 16.6, 66 (128) 15.5 -> 14.1, 72 (128) 16.9 -> 17.0, 88 (96, regions of 36 tokens) 14.1 -> 17.0, 100 (64) 15.0 -> 18.4; 312 tiles of C = 768
-// 36.0 -> 44.2, 168 35.5 -> 32.2.  bf16, by millions of values: 3.1 (C = 160) 17.4 -> 14.4, 5.5 (96) 28.8 -> 27.8, 5.5 (288) 25.2 -> 27.6, 9.2 (160) 24.4 -> 25.9,
-// regions of 4 tokens 9.2 47.3 -> 44.7.
+// The means of Q and K out of the token projection, whose tiles go region by region: a pooling pass and a region-level product less for
+// bra_forward.  bra_route, which has to decide on the same bits, projects all tokens for it; the lines lie about where that takes as
+// long.  bra_forward before -> now / bra_route (us): 4 x 14 x 14 x 256 38.3 -> 35.9 / 18.8 -> 15.7, 2 x 64 x 64 x 128 49.5 -> 44.8, 1 x 21 x 21 x 768 79.3 -> 65.7, 50 x 28
+// x 28 x 96 bf16 74.7 -> 69.7 / 17.6 -> 15.2.  bra_route pays more where tiles have idle rows: 2 x 35 x 35 x 192 (25 tokens per region) 41.4 -> 38.8 / 16.0 -> 17.3, 12 x 56 x
+// 48 x 96 bf16, S = 8 (42) 74.1 -> 72.6 / 14.0 -> 15.9, 21 x 35 x 35 x 64 (25) 14.3 -> 16.5; bra_forward where they make it two
+// rounds of workgroups for one: 1 x 35 x 35 x 256, k = 1 37.2 -> 39.0 / 17.9 -> 15.5.
+// float32, by tiles of bra_route's product times C, bra_route: 56 thousand (C = 192) 17.1 -> 16.6, 66 (128) 15.5 -> 14.1, 72 (128) 16.9 -> 17.0, 88 (96, 36 tokens) 14.1
+// -> 17.0, 100 (64) 15.0 -> 18.4; 312 tiles of C = 768 36.0 -> 44.2, 168 35.5 -> 32.2.  bf16, by millions of values: 3.1 (C = 160) 17.4 -> 14.4, 5.5 (96) 28.8 -> 27.8, 5.5
+// (288) 25.2 -> 27.6, 9.2 (160) 24.4 -> 25.9, regions of 4 tokens 9.2 47.3 -> 44.7.
 bool means_from_projection(const Dims &D)
 {
     const long values = (long)D.B * D.N * D.C;
@@ -398,9 +400,13 @@ TileSplit out_split(const Dims &D)
 
 // Attention and Y = O Wo in one kernel: two or four heads of 32 channels.  For two that is a launch and two passes over O less, 2 us on 3000 tokens and 9 on
 // 50000 (16 x 56 x 56 x 64, k = 1: 61.7 -> 57.2; 60 x 28 x 28, k = 1 69.5 -> 63.8; 2 x 112 x 112, S = 16, k = 4 59.2 -> 54.3; 2 x 80 x 80, S = 8 54.1 -> 49.5);
-// but both heads share a compute unit, and a block of keys takes its wavefronts' time, a microsecond for four: where that is more than 3 us
-// longer the heads stay apart (1 x 56 x 56, S = 7, k = 2, 3 and 8 25.4, 27.6, 36.8 apart and 24.2, 27.7, 42.0 together; 2 x 64 x 64, S = 4, k = 4 61.7 and 73.2),
-// for short maps (1 x 40 x 40, S = 4, k = 2 31.9 and 32.7) and many keys (1 x 128 x 128, S = 8, k = 4, 16 blocks 82.5 and 79.6; S = 4, 64 blocks 233.6 and 236.9).
+// but both heads share a compute unit, and a block of keys takes its wavefronts' time, a microsecond for four: longer than the apart ones by blocks *
+// (together - apart).  More than three times as long they stay apart, and beyond two rounds of workgroups where it is more than the apart time itself,
+// counting the wavefronts that have queries.  Together / apart, us, by that ratio: 1.0: 6 x 84 x 56, k = 2 0.96 of the time; 1.7: 6 x 112 x 32, S = 8, k = 5 1.02;
+// 2.0: 2 x 98 x 84, k = 2 64.2 / 62.1; 2.3: 6 x 56 x 56, S = 8, k = 8 66.5 / 63.5, 3 x 70 x 70, k = 4 67.4 / 63.2; 3.0: 2 x 84 x 84, k = 4 77.2 / 70.6; against that in fewer
+// rounds 2.0: 1 x 84 x 70, k = 1 0.95; 1 x 56 x 56, k = 2, 3 and 8 24.2, 27.7, 42.0 / 25.4, 27.6, 36.8; 2 x 64 x 64, S = 4, k = 4 73.2 / 61.7.  Left on the wrong side: 13 x
+// 42 x 56, k = 3 (three tiles in four wavefronts, 0.6) 60.0 / 58.0.  Apart for the shortest maps (1 x 40 x 40, S = 4, k = 2 32.7 / 31.9) and many keys
+// (1 x 128 x 128, S = 8, k = 4, 16 blocks 79.6 / 82.5; S = 4, 64 blocks 236.9 / 233.6).
 // Four heads of 32, in regions of at most 16 tokens, share a workgroup anyway: 6 x 28 x 28 x 128, k = 4 35.8 -> 32.1 us, 40 images 92.6 -> 88.0, 1 x
 // 14 x 14 25.0 -> 20.3, 24 x 21 x 21 56.1 -> 53.6; but each region reads all of Wo and multiplies a tile of 16 rows: 64 x 14 x 14 x 128 (3136 regions of
 // 4 tokens), k = 16 76.8 and 83.1.
@@ -413,7 +419,8 @@ bool attention_with_out(const Dims &D)
     const long regions = (long)D.B * D.R, blocks = (D.kn + 63) / 64;
     const long apart = tiles <= 2 ? (regions + 255) / 256 * 4 : (regions * 2 * one.groups + 255) / 256 * one.each;
     const long together = (regions * both.groups + 255) / 256 * 2 * both.each;
-    return blocks <= 32 && blocks * (together - apart) <= 3 * apart;
+    const long busy = together / both.each * std::min(both.each, tiles);
+    return blocks <= 32 && blocks * (together - apart) <= 3 * apart && (apart <= 10 || blocks * (busy - apart) <= apart);
 }
 
 // o holds LCE(V).

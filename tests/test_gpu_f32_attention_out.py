@@ -20,6 +20,8 @@ SHAPES = [  # (B, H, W, S, k)
     (14, 60, 35, 5, 1),       # 84 tokens: six tiles
     (36, 32, 32, 2, 1),       # 256 tokens: four workgroups of a region
     (4, 48, 63, 3, 1),        # 336 tokens: six, the last of one tile
+    (6, 49, 56, 7, 3), (6, 49, 56, 7, 4),        # 56 tokens, three blocks of keys and four: both sides of the line of three rounds
+    (2, 105, 35, 7, 4), (2, 105, 35, 7, 5),      # 75, five and six: of one
 ]
 
 
