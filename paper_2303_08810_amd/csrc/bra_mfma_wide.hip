@@ -626,13 +626,18 @@ void launch_attn_gen_t(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t
 void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, const OutMap &out, hipStream_t st)
 {
     // two query tiles per wavefront (every K and V operand read serves both; measured above) where the wider tile leaves no
-    // more than an eighth of its queries empty beyond the narrow one and there are workgroups enough.  One query tile: a head per
-    // wavefront while the workgroups are few (layer of 1 x 72 x 72 x 192, S = 8, k = 12 47.9 -> 44.3 us, 1 x 100 x 150 x 64, S = 16, k = 8
-    // 44.7 -> 41.8), both heads from four workgroups per compute unit on, whose prologue is paid by half as many wavefronts
-    // (30 x 42 x 42 x 192, k = 5 103.9, with one head each 107.5)
+    // more than an eighth of its queries empty beyond the narrow one and there are workgroups enough.  Both heads in a wavefront where a
+    // prologue paid by half as many outweighs the fourth wavefront per SIMD: two query tiles and many workgroups with few keys (layer, us, a
+    // head / both: 32 x 56 x 96 x 128, S = 8, k = 2 (168 keys) 143 / 133 with a given index, 40 x 56 x 70 x 128, k = 1 (80) 144.5 / 139.4, 15 x 176 x 128 x 64, S = 16, k = 4 (352)
+    // 163 / 156; mean of 232 with up to 192 keys 1.028, of 176 with up to 512 1.010; from 11 blocks of keys on, or few workgroups, the other way: 0.99; 4 x 48 x 112 x 128, S = 8,
+    // k = 1 38.1 / 39.2).  One query tile: from four workgroups per compute unit on (30 x 42 x 42 x 192, k = 5 107.5 / 103.9; 1 x 72 x 72 x 192, S = 8, k = 12 44.3 / 47.9, 1 x
+    // 100 x 150 x 64, S = 16, k = 8 41.8 / 44.7)
     const int t64 = (D.n + 63) / 64, t128 = (D.n + 127) / 128;
-    if (t128 * 128 * 8 <= t64 * 64 * 9 && (long)D.B * D.R * t128 * (D.C / 64) >= 512) launch_attn_gen_t<2, 1>(D, A, O, Low, out, st);
-    else if ((long)D.B * D.R * t64 * (D.C / 64) >= 1024) launch_attn_gen_t<1, 2>(D, A, O, Low, out, st);
+    const long regions = (long)D.B * D.R * (D.C / 64), wide = regions * t128;
+    if (t128 * 128 * 8 <= t64 * 64 * 9 && wide >= 512) {
+        if (D.kn <= 512 && wide >= (D.kn <= 192 ? 768 : 2048)) launch_attn_gen_t<2, 2>(D, A, O, Low, out, st);
+        else launch_attn_gen_t<2, 1>(D, A, O, Low, out, st);
+    } else if (regions * t64 >= 1024) launch_attn_gen_t<1, 2>(D, A, O, Low, out, st);
     else launch_attn_gen_t<1, 1>(D, A, O, Low, out, st);
 }
 

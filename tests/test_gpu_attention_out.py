@@ -19,6 +19,8 @@ SHAPES = [  # (B, H, W, k), 16 x 16 regions
     (4, 80, 112, 6),
     (2, 128, 256, 1),        # 128 tokens, 512 workgroups of two query tiles per wavefront
     (2, 112, 272, 2),        # 119 tokens
+    (3, 112, 272, 1),        # 768 workgroups: both heads of two query tiles
+    (8, 96, 176, 4),         # 66 tokens, 2048 workgroups: the same, keys by walking
 ]
 
 
@@ -32,6 +34,7 @@ PADDED = [  # (B, H, W, S, k)
     (1, 75, 110, 16, 3),     # 5 x 7 tokens, the last rows and columns beyond the map
     (2, 113, 260, 16, 1),    # 8 x 17
     (2, 121, 255, 16, 2),    # 8 x 16, two query tiles per wavefront
+    (3, 113, 260, 16, 1),    # both heads of two
 ]
 
 
