@@ -602,12 +602,9 @@ struct AttnWork {
 
 __device__ __forceinline__ AttnWork attn_work(int block, int blocks, bool by_image, int tiles, int hgroups, int R)
 {
-    if (by_image) {
-        const int at = mfma::swizzled(block, blocks), region = at / tiles, pair = region / R;
-        return AttnWork{at - region * tiles, region - pair * R, pair % hgroups, pair / hgroups};
-    }
-    const int tile = block / hgroups, region = tile / tiles, image = region / R;
-    return AttnWork{tile - region * tiles, region - image * R, block - tile * hgroups, image};
+    const int at = by_image ? mfma::swizzled(block, blocks) : block, n0 = by_image ? tiles : hgroups, n1 = by_image ? R : tiles, n2 = by_image ? hgroups : R;
+    const int q0 = at / n0, r0 = at - q0 * n0, q1 = q0 / n1, r1 = q0 - q1 * n1, image = q1 / n2, r2 = q1 - image * n2;
+    return by_image ? AttnWork{r0, r1, r2, image} : AttnWork{r1, r2, r0, image};
 }
 
 // HPW = 1: as many wavefronts as the region's query tiles of 16 fill (3 to 8; more tiles are dealt out evenly).
