@@ -98,7 +98,9 @@ int bra_route(const bra_shape *shape, const void *X, const void *Wqkv, int32_t *
  * within a row (not checked on the host: they are device data).  The kernels clamp
  * an out-of-range entry into [0, S*S) where they read it, so a wrong index gives a
  * wrong result, never an access outside the tensors; Ir_out_opt receives the
- * entries as given. */
+ * entries as given.  Where the routing costs nothing another pipeline can be the faster one, so that a call
+ * with the index that an earlier call returned gives the same Y up to the rounding of intermediate tensors, not
+ * bit for bit; a repeat of the same call does. */
 int bra_forward(const bra_shape *shape, const void *X, const void *Wqkv, const void *Wo,
                 const void *Wlce, void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt,
                 void *ws, size_t ws_bytes, void *hip_stream);

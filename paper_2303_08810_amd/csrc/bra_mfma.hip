@@ -1895,8 +1895,9 @@ static bool far_pays(const Dims &D)
 }
 
 // Up to 64 regions, where the general pipeline with the means of Q and K out of its projection is faster than the kernels specialised by channel count
-// (bra_route, and the layer with a given index unless it says otherwise, with it), as long as it needs no more scratch than every entry has, so
-// that all of them take the same pipeline.  Layer, us, specialised / general:
+// (bra_route with it, which has to give the index of bra_forward), as long as it needs no more scratch than every entry has, so
+// that all of them take the same pipeline.  With a given index the specialised kernels have no routing to wait for, and a layer with the index that it
+// has just returned may take the other pipeline: the same precision, other roundings.  Layer, us, specialised / general:
 //   fewer than 16 tokens per region: 14 x 28 x 256, k = 4: B = 20 37.4 / 31.7, 38 68.9 / 69.0; 14 x 14 x 256, k = 16: 24 37.9 / 32.9, 40 47.2 / 42.9; 14 x 14 x 128,
 //     k = 16: 64 38.4 / 33.8, 83 46.8 / 44.8.  Of up to 4 tokens not beyond 2 million values: 14 x 14 x 256: 56 55.9 / 53.1, 64 49.6 / 48.2, 96 66.6 / 66.2, 128
 //     77.1 / 78.7; 14 x 14 x 128: 100 53.6 / 51.7, 150 59.8 / 62.7.  The two add a row of A^r up in different orders, so that a near tie can fall
@@ -1904,9 +1905,11 @@ static bool far_pays(const Dims &D)
 //   16 tokens: 28 x 28 x 256, k = 4: 4 27.3 / 23.7, 16 46.8 / 42.1, 24 53.1 / 53.0, beyond: 32 66.2 / 70.2; k = 1: 10 29.3 / 29.1, 16 42.9 / 40.5.  28 x 28 x 128, k = 4: 8
 //     23.0 / 20.9, beyond: 16 25.5 / 25.9, 20 27.0 / 29.0; k = 8: 20 31.0 / 29.3; k = 16: 16 33.4 / 30.0; k = 1 not: 1 19.7 / 20.6, 16 24.3 / 26.0.  28 x 28 x 64: k = 1: 4
 //     16.3 / 18.0, 16 19.9 / 19.6; k = 2: 24 24.9 / 22.8; k = 8: 12 22.8 / 20.8; k = 4: 16 21.4 / 19.6, beyond: 40 28.2 / 30.8.  With a given
-//     index the specialised kernels have no routing to wait for: 8 x 28 x 28 x 128 16.1 / 19.8, 16 x 28 x 28 x 256 38.6 / 38.8
-//   64 tokens: 56 x 56 x 128, k = 4: 1 27.8 / 22.6, 8 46.1 / 41.3 (bra_route 13.5 / 12.6; 16 14.1 / 15.5); 56 x 56 x 64, k = 2: 1 16.9 / 16.4, 8 25.9 / 21.9
-//     (bra_route 9.3 / 9.6; 12 9.7 / 11.1)
+//     index not: 8 x 28 x 28 x 128 16.1 / 19.8, 16 x 28 x 28 x 256 38.6 / 38.8
+//   64 tokens: 56 x 56 x 128, k = 4: 1 27.8 / 22.6, 8 46.1 / 41.3 (bra_route 13.5 / 12.6; 16 14.1 / 15.5); k = 1: 8 40.2 / 36.8, 9 42.2 / 40.6, 10 42.4 / 43.4; 56 x 56 x 64,
+//     k = 2: 1 16.9 / 16.4, 8 25.9 / 21.9 (bra_route 8.6 / 9.1; 12 9.7 / 11.1).  With a given index 56 x 56 x 128, k = 4: 8 41.7 / 38.6; 56 x 56 x 64, k = 4 from more
+//     regions than compute units on: 1 13.9 / 15.3, 5 16.9 / 18.0, 6 22.2 / 20.4, 10 25.0 / 23.3
+//   fewer than 16 with a given index too: 20 x 14 x 35 x 256, k = 2 34.2 / 31.6
 //   not 128 tokens and more: 2 x 56 x 112 x 64, k = 4 23.6 / 25.9, 1 x 64 x 64 x 64, S = 4 24.8 / 27.8
 static bool general_pays(const Dims &D, bool given)
 {
@@ -1915,7 +1918,8 @@ static bool general_pays(const Dims &D, bool given)
     if (D.n < 16) return D.n > 4 || values <= 2L << 20;
     if (D.n == 16)
         return !given && (D.C == 256 || (D.C == 128 ? D.k >= 4 && values <= (D.k < 8 ? 16L : 32L) << 16 : values >= 9L << 16 && values <= 20L << 16));
-    return D.n == 64 && (D.C == 128 || (D.C == 64 && !fused_ok(D) && values <= 2L << 20));
+    if (D.n != 64) return false;
+    return D.C == 128 ? D.k > 1 || values <= 7L << 19 : D.C == 64 && !fused_ok(D) && values <= 2L << 20 && (!given || (long)D.B * D.R > 256);
 }
 
 // Shapes of the kernels specialised by channel count.  compact: wherever they need less scratch than the general pipeline.  given: with a given index.

@@ -1,6 +1,6 @@
 """GPU parity on both sides of the lines between the kernels specialised by channel count and the general pipeline, for
-regions of 2 to 64 tokens: the layer against the oracle with the index of bra_route, and with that index given, which 16 tokens per region
-send to the other pipeline, within the scratch that is asked for."""
+regions of 2 to 64 tokens: the layer against the oracle with the index of bra_route, and with that index given, which some of 16 and 64 tokens
+per region send to the other pipeline, within the scratch that is asked for."""
 import pytest
 import torch
 
@@ -21,7 +21,9 @@ LINES = [  # (B, H, W, C, S, k)
     (2, 28, 28, 128, 7, 3), (10, 28, 28, 128, 7, 4), (11, 28, 28, 128, 7, 4),
     (20, 28, 28, 128, 7, 8), (21, 28, 28, 128, 7, 8),
     (11, 28, 28, 64, 7, 4), (12, 28, 28, 64, 7, 4), (26, 28, 28, 64, 7, 4), (27, 28, 28, 64, 7, 4),
-    (9, 56, 56, 128, 7, 1), (11, 56, 56, 128, 7, 1),         # 64
+    (9, 56, 56, 128, 7, 1), (10, 56, 56, 128, 7, 1),         # 64
+    (10, 56, 56, 128, 7, 2), (11, 56, 56, 128, 7, 2),
+    (5, 56, 56, 64, 7, 3), (6, 56, 56, 64, 7, 3),            # with a given index
     (10, 56, 56, 64, 7, 2), (11, 56, 56, 64, 7, 2),
     (2, 56, 112, 64, 7, 2),                                  # 128
     (21, 128, 128, 64, 16, 1), (22, 128, 128, 64, 16, 1),    # 256 regions of 64
