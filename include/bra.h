@@ -114,9 +114,10 @@ int bra_forward(const bra_shape *shape, const void *X, const void *Wqkv, const v
  * runs on holds one such buffer from the time the library is loaded there until the process
  * ends.  The call allocates and frees nothing.  The first call on each device looks up
  * the buffer's address (hipGetSymbolAddress; no allocation, but not to be captured into a
- * graph); later calls only enqueue kernels.  Other shapes whose workspace (bra_workspace_bytes)
- * exceeds the buffer are rejected with BRA_ERR_TOO_LARGE before anything is enqueued; the
- * other errors are those of bra_forward.  The buffer keeps the previous call's contents (no
+ * graph); later calls only enqueue kernels.  Other calls whose pipeline needs more scratch than the
+ * buffer holds are rejected with BRA_ERR_TOO_LARGE before anything is enqueued (none whose
+ * bra_workspace_bytes fits; of the rest, those for which it is the pipeline with a given index that does not fit
+ * still run without one); the other errors are those of bra_forward.  The buffer keeps the previous call's contents (no
  * kernel of the forward pass needs it zeroed).  All calls on one GPU share it: calls that may
  * overlap on that GPU (different streams, or one stream from several threads) race; order them
  * on one stream. */

@@ -140,9 +140,9 @@ int bra_forward_static(const bra_shape *shape, const void *X, const void *Wqkv, 
     if (!X || !Wqkv || !Wo || !Wlce || !Y) return BRA_ERR_NULL;
     int path = pick_path(shape, D);
     if (path < 0) return path;
-    size_t need = (path == BRA_PATH_MFMA) ? mfma_workspace_bytes(D) : generic_workspace_bytes(D);
+    size_t need = (path == BRA_PATH_MFMA) ? mfma_forward_bytes(D, Ir_in_opt) : generic_workspace_bytes(D);
     const bool compact = path == BRA_PATH_MFMA && need > (size_t)BRA_STATIC_SCRATCH_BYTES;
-    if (compact) need = mfma_compact_workspace_bytes(D);
+    if (compact) need = mfma_compact_bytes(D, Ir_in_opt);
     if (need > (size_t)BRA_STATIC_SCRATCH_BYTES) return BRA_ERR_TOO_LARGE;
     void *ws = nullptr;
     rc = static_scratch(&ws);

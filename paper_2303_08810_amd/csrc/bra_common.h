@@ -121,8 +121,10 @@ int mfma_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, floa
                hipStream_t st);
 int mfma_forward(const Dims &D, const void *X, const void *Wqkv, const void *Wo, const void *Wlce,
                  void *Y, int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, hipStream_t st, bool compact = false);
-// What mfma_forward needs with `compact`: the pipeline with the least scratch instead of the fastest.
-size_t mfma_compact_workspace_bytes(const Dims &D);
+// What mfma_forward needs with or without a given index, and with `compact`: beyond 64 regions the pipeline with the least scratch
+// instead of the fastest.
+size_t mfma_forward_bytes(const Dims &D, bool given);
+size_t mfma_compact_bytes(const Dims &D, bool given);
 
 // Whether the pipeline for the padded shape takes the caller's H x W map itself, and that pipeline.
 // Yp: scratch of the padded map's size.

@@ -1959,13 +1959,14 @@ static bool addressable(const Dims &D)
 
 bool mfma_supported(const Dims &D) { return addressable(D) && (specialised(D) || wide_supported(D)); }
 
-size_t mfma_workspace_bytes(const Dims &D)
+size_t mfma_forward_bytes(const Dims &D, bool given) { return specialised(D, false, given) ? carve(D, nullptr).bytes : wide_workspace_bytes(D); }
+
+size_t mfma_compact_bytes(const Dims &D, bool given)
 {
-    const size_t bytes = wide_shape(D) ? wide_workspace_bytes(D) : carve(D, nullptr).bytes;
-    return specialised(D, false, true) ? std::max(bytes, carve(D, nullptr).bytes) : bytes;
+    return far_routing(D) && specialised(D, true) ? carve(D, nullptr).bytes : mfma_forward_bytes(D, given);
 }
 
-size_t mfma_compact_workspace_bytes(const Dims &D) { return specialised(D, true) ? carve(D, nullptr).bytes : wide_workspace_bytes(D); }
+size_t mfma_workspace_bytes(const Dims &D) { return std::max(mfma_forward_bytes(D, false), mfma_forward_bytes(D, true)); }
 
 int mfma_route(const Dims &D, const void *X, const void *Wqkv, int32_t *Ir, float *Ar_opt, void *ws,
                hipStream_t st)

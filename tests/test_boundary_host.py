@@ -112,6 +112,10 @@ def test_static_scratch_entry_point_rejects_before_launching():
     assert ws_bytes(B=64, C=128, heads=4, dtype=bra.BRA_BF16)[1] > bra.STATIC_SCRATCH_BYTES
     assert L.bra_forward_static(ctypes.byref(big), fake, fake, fake, fake, fake, None, None, None) == -8
     assert "scratch" in bra.strerror(-8)
+    # refused with a given index, whose pipeline is the one that does not fit
+    part = bra.make_shape(44, 32, 8, 256, 8, 4, 1, bra.BRA_BF16)
+    assert ws_bytes(B=44, H=32, W=8, C=256, heads=8, S=4, k=1, dtype=bra.BRA_BF16)[1] > bra.STATIC_SCRATCH_BYTES
+    assert L.bra_forward_static(ctypes.byref(part), fake, fake, fake, fake, fake, None, fake, None) == -8
 
 
 def test_block_and_padded_workspace_queries():

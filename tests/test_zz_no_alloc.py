@@ -54,6 +54,23 @@ def test_static_scratch_forced_routing_and_limit():
     assert e.value.code == -8
 
 
+# With a given index another pipeline: the same bits as bra_forward where it fits the buffer, refused where it does not
+@pytest.mark.parametrize("B,H,W,C,S,k,fits", [(8, 28, 28, 128, 7, 4, True), (8, 28, 28, 256, 7, 4, True), (3, 56, 56, 64, 7, 3, True),
+                                              (44, 32, 8, 256, 4, 1, False)])
+def test_static_scratch_with_a_given_index(B, H, W, C, S, k, fits):
+    arrays = make_inputs(B, H, W, C, seed=97, dtype="bf16")
+    both(*arrays, "bf16", S, k, C // 32)
+    X, Wqkv, Wo, Wlce = (to_device(a, "bf16") for a in arrays)
+    Ir = bra.bra_route(X, Wqkv, S, k, C // 32)
+    if fits:
+        both(*arrays, "bf16", S, k, C // 32, Ir_in=Ir)
+        return
+    out = torch.full_like(X, 7.0)
+    with pytest.raises(bra.BraError) as e:
+        bra.bra_forward_static(X, Wqkv, Wo, Wlce, S, k, C // 32, out=out, Ir_in=Ir)
+    assert e.value.code == -8 and bool((out == 7.0).all())
+
+
 # Layers whose fastest pipeline does not fit the buffer and whose other one does, by its scratch of three maps instead of four
 @pytest.mark.parametrize("B,H,W,C,heads,S,k", [
     (1, 256, 256, 64, 2, 16, 1), (2, 128, 128, 128, 4, 16, 2), (9, 64, 64, 128, 4, 16, 4), (17, 64, 64, 64, 2, 16, 4), (4, 64, 64, 256, 8, 16, 2)])
