@@ -8,19 +8,23 @@
 namespace bra {
 namespace mfma {
 
+// How far above the largest score a reference is put (in units of log2): a power of two that weights, denominators and sums carry without
+// loss, so that a later score moves the reference only once it is about twice as far above the earlier maximum.  A first block's
+// weights are at most 2^-8, later ones up to 2^8; what lies 2^118 below the maximum is lost instead of 2^126.
+constexpr float kHeadroom = 8.0f;
+
 // Softmax step for KT tiles of 16 keys x 16 queries of one head: scores
 // s[t][j] = S^T[key 16 t + 4 g + j][query i] relative to the reference m (which entered the product as its accumulator
 // input, so a score costs no subtraction), weights p = 2^s in the operand order of O^T += V^T P^T.  l: the lane's share of
 // the denominator, a sum of the float32 weights (over its keys: the caller adds up the four lane groups at the end).
 // That sum also decides when the reference has to move: only when a lane's weights of a block exceed 2^8 together, which
-// needs no maximum and no exchange between lanes; the quotient O / l does not depend on it.  FIRST: the reference is this
-// block's maximum.  With dp (scores of the gradient in the same layout) also d: the lane's share of sum p dp.
-constexpr float kHeadroom = 8.0f;
+// needs no maximum and no exchange between lanes; the quotient O / l does not depend on it.  FIRST: the reference is
+// kHeadroom above this block's maximum.  With dp (scores of the gradient in the same layout) also d: the lane's share of sum p dp.
 template <bool FIRST, int KT, int NDT>
 __device__ __forceinline__ void softmax_step(f32x4 (&s)[KT], float &m, float &l, f32x4 (&acc)[NDT], bf16x8 (&pb)[KT / 2],
                                              const f32x4 *dp = nullptr, float *d = nullptr)
 {
-    auto raise = [&](bool keep) {               // moves the reference to the largest score; returns by how much
+    auto raise = [&](bool keep) {               // moves the reference kHeadroom above the largest score; returns by how much
         float mx = s[0][0];
 #pragma unroll
         for (int t = 0; t < KT; ++t)

@@ -118,7 +118,7 @@ int route_rows_lce_bf16(const Dims &D, const float *Qr, const float *Kr, int32_t
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
-// Maps so wide that not even strips of 5 rows fit (119 million values in a row) take the kernels of bra_lce_dev.h, whose
+// Maps so wide that not even strips of 4 rows fit (134 million values in a row) take the kernels of bra_lce_dev.h, whose
 // addresses are 64-bit throughout.
 int lce_add_bf16(const Dims &D, const bf16_t *V, const bf16_t *Wlce, bf16_t *O, int ldo, int kernel_id, hipStream_t st)
 {

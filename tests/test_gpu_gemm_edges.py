@@ -13,10 +13,10 @@ EDGES = [  # (B, H, W, C, heads, S, k)
     (200, 7, 7, 448, 14, 7, 5),      # 128 x 128 tiles (77 row tiles, 10.5 column tiles), K = 7 chunks
     (50, 14, 14, 448, 14, 7, 5),     # the same with 2450 region rows
     (90, 7, 7, 320, 10, 7, 3),       # 64 x 128 tiles, K = 5 chunks
-    (23, 14, 14, 320, 10, 7, 3),     # the same with region rows
+    (36, 14, 14, 320, 10, 7, 3),     # the same with 1764 region rows
     (3, 14, 14, 192, 6, 7, 4),       # 64 x 64 tiles
     (1, 3, 3, 64, 1, 3, 2),          # 9 rows, one chunk
-    (25, 14, 14, 1024, 32, 7, 3),    # weights of 6 MB, 4900 rows, with region rows
+    (15, 18, 18, 1024, 32, 2, 2),    # weights of 6 MB, 4860 rows, with region rows (81 tokens each)
     (20, 14, 14, 192, 6, 7, 3),      # W^o: 3920 rows of one and a half tiles of columns
 ]
 

@@ -22,13 +22,13 @@ SHAPES = [  # (B, H, W, C, heads, S, k)
     (48, 7, 7, 192, 6, 7, 3),        # 288 pairs, 192 workgroups of the routing
     (1, 64, 64, 64, 2, 16, 4),       # 256 regions of 16 tokens
     (1, 72, 72, 128, 4, 9, 2),       # 81 of 64
-    (5, 128, 128, 64, 2, 16, 4),     # 256 of 64, 5 x 2^20 values
-    (6, 128, 128, 64, 2, 16, 4),     # above: the layer kernels behind the general pipeline's routing
+    (5, 128, 128, 64, 2, 16, 4),     # 256 of 64
+    (6, 128, 128, 64, 2, 16, 4),
     (9, 72, 144, 64, 2, 9, 2),       # 81 of 128
-    (10, 64, 64, 128, 4, 16, 5),
-    (11, 64, 64, 128, 4, 16, 5),
+    (10, 64, 64, 128, 4, 16, 5),     # 5 x 2^20 values
+    (11, 64, 64, 128, 4, 16, 5),     # above: the layer kernels behind the general pipeline's routing
     (3, 128, 128, 128, 4, 32, 4),    # 1024 of 16
-    (56, 64, 64, 64, 2, 16, 4),      # 14 x 2^20
+    (56, 64, 64, 64, 2, 16, 4),
     (57, 64, 64, 64, 2, 16, 4),
     (15, 64, 64, 256, 8, 16, 2),
     (16, 14, 14, 512, 16, 7, 9),     # 4 tokens, 36 keys, 256 pairs
@@ -55,7 +55,8 @@ def test_lines(B, H, W, C, heads, S, k):
     assert torch.equal(Ir, bra.bra_route(Xd, Wd, S, k, heads, path="mfma"))
 
 
-@pytest.mark.parametrize("B,H,W,C,heads,S,k", [(7, 127, 126, 64, 2, 16, 4), (12, 63, 60, 128, 4, 16, 4)])
+# The padded map by the general pipeline, the whole one by the layer kernels
+@pytest.mark.parametrize("B,H,W,C,heads,S,k", [(22, 127, 126, 64, 2, 16, 4), (12, 63, 60, 128, 4, 16, 4)])
 def test_padded_maps_of_many_regions(B, H, W, C, heads, S, k):
     X, Wqkv, Wo, Wlce = (to_device(a, "bf16") for a in make_inputs(B, H, W, C, seed=9560, dtype="bf16"))
     Y, Ir = bra.bra_forward_padded(X, Wqkv, Wo, Wlce, S, k, heads, want_Ir=True)
