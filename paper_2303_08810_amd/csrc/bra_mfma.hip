@@ -1899,9 +1899,9 @@ static bool far_pays(const Dims &D)
 // that all of them take the same pipeline.  With a given index the specialised kernels have no routing to wait for, and a layer with the index that it
 // has just returned may take the other pipeline: the same precision, other roundings.  Layer, us, specialised / general:
 //   fewer than 16 tokens per region: 14 x 28 x 256, k = 4: B = 20 37.4 / 31.7, 38 68.9 / 69.0; 14 x 14 x 256, k = 16: 24 37.9 / 32.9, 40 47.2 / 42.9; 14 x 14 x 128,
-//     k = 16: 64 38.4 / 33.8, 83 46.8 / 44.8.  Of up to 4 tokens not beyond 2 million values: 14 x 14 x 256: 56 55.9 / 53.1, 64 49.6 / 48.2, 96 66.6 / 66.2, 128
-//     77.1 / 78.7; 14 x 14 x 128: 100 53.6 / 51.7, 150 59.8 / 62.7.  The two add a row of A^r up in different orders, so that a near tie can fall
-//     either way (2 of 188 thousand rows at 64 x 14 x 14 x 256): ever more rows, for ever less
+//     k = 16: 64 38.4 / 33.8, 96 53.9 / 47.5; 14 x 14 x 256, k = 16: 48 51.3 / 45.4, 64 51.6 / 48.4 (k = 4 49.5 / 46.8; bra_route 23.5 / 20.0, with a given index 41.8 / 37.2), beyond
+//     the scratch 96 66.6 / 66.2, 128 77.1 / 78.7.  The general pipeline's A^r is the more exact one too: 1.5e-7 from float64 at 64 x 14 x 14 x 256 (2-norm, relative),
+//     the specialised kernels' 3.0e-7
 //   16 tokens: 28 x 28 x 256, k = 4: 4 27.3 / 23.7, 16 46.8 / 42.1, 24 53.1 / 53.0, beyond: 32 66.2 / 70.2; k = 1: 10 29.3 / 29.1, 16 42.9 / 40.5.  28 x 28 x 128, k = 4: 8
 //     23.0 / 20.9, beyond: 16 25.5 / 25.9, 20 27.0 / 29.0; k = 8: 20 31.0 / 29.3; k = 16: 16 33.4 / 30.0; k = 1 not: 1 19.7 / 20.6, 16 24.3 / 26.0.  28 x 28 x 64: k = 1: 4
 //     16.3 / 18.0, 16 19.9 / 19.6; k = 2: 24 24.9 / 22.8; k = 8: 12 22.8 / 20.8; k = 4: 16 21.4 / 19.6, beyond: 40 28.2 / 30.8.  With a given
@@ -1915,7 +1915,7 @@ static bool general_pays(const Dims &D, bool given)
 {
     if (!wide_supported(D) || wide_workspace_bytes(D) > (size_t)BRA_STATIC_SCRATCH_BYTES) return false;
     const long values = (long)D.B * D.N * D.C;
-    if (D.n < 16) return D.n > 4 || values <= 2L << 20;
+    if (D.n < 16) return true;
     if (D.n == 16)
         return !given && (D.C == 256 || (D.C == 128 ? D.k >= 4 && values <= (D.k < 8 ? 16L : 32L) << 16 : values >= 9L << 16 && values <= 20L << 16));
     if (D.n != 64) return false;

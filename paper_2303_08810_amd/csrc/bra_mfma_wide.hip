@@ -564,17 +564,17 @@ GemmMeans means_job(const Dims &D, const WideWs &w, int H, int W)
 // line lies where that takes as long.  bra_route / bra_forward before -> now (us): 1 x 28 x 28 x 384, k = 9 19.0 -> 12.4 / 33.1 -> 26.7,
 // 6 x 14 x 14 x 256 16.5 -> 11.2 / 27.8 -> 22.4, 64 x 14 x 14 x 384 30.7 -> 24.4 / 77.5 -> 66.7, 32 x 16 x 16 x 768 41.8 -> 36.1 / 123.5 ->
 // 101.4, 4 x 32 x 32 x 384 20.2 -> 14.8 / 39.9 -> 35.8; beyond: 8 x 32 x 32 x 768 32.4 -> 38.2 / 104.5 -> 99.0, 20 x 56 x 56 x 192 18.9 -> 25.6 /
-// 112.0 -> 106.6.  Regions of up to 4 tokens, whose means are a quarter of the tokens or more, from 512 channels on at any size, where the layer
-// gains a fifth; below, up to 2 million values: the sums' order decides near ties, of which thousands of rows have one now and then (64 x 14 x 14 x 384 80 -> 68, but one row's
-// regions changed in 10 sets of inputs): 64 x 14 x 14 x 768 55.7 -> 51.3 / 177 ->
-// 142, 100 of them 76.6 -> 77.3 / 272 -> 212, 150 x 14 x 14 x 512 68.5 -> 65.1 / 226 -> 184.  By millions of values and tokens per region, bra_route before -> now: 8 of C = 192 11.5 37.6 -> 37.9, of C = 384 9.6
+// 112.0 -> 106.6.  Regions of up to 4 tokens, whose means are a quarter of the tokens or more, at any size: 64 x 14 x 14 x 192 22.6 -> 16.1 / 51.4 -> 44.1,
+// x 384 31.3 -> 26.8 / 84.4 -> 71.7, x 768 55.7 -> 51.3 / 177 -> 142, 96 x 14 x 14 x 448 48.2 -> 43.8 / 142.7 -> 121.9, 100 x 14 x 14 x 768 76.6 -> 77.3 / 272 -> 212, 150 x 14 x 14 x
+// 512 68.5 -> 65.1 / 226 -> 184.  They are the more exact ones too: A^r of 64 x 14 x 14 x 384 is 1.7e-7 from float64 (2-norm, relative), with the means
+// of the tokens 2.7e-7, x 192 1.4e-7 and 1.9e-7.  By millions of values and tokens per region, bra_route before -> now: 8 of C = 192 11.5 37.6 -> 37.9, of C = 384 9.6
 // 32.4 -> 33.1, of C = 768 3.0 30.7 -> 25.7, 7.8 37.1 -> 41.4; 16 4.7 18.5 -> 16.7 (C = 192), 9.4 26.4 -> 30.4 (384), 7.9 32.1 -> 40.8 (768); 64 4.7
 // 16.8 -> 16.8, 3.1 20.1 -> 17.0, 3.1 28.4 -> 25.5; 36, of which a tile of 64 rows leaves 28 idle, 2.0 15.8 -> 14.0, 4.7 16.7 -> 18.0 (192), 4.1 20.1 -> 22.8 (384).
 bool means_from_projection(const Dims &D)
 {
     if (D.n == 1 || D.n > kMeansMaxTokens) return false;
     const long values = (long)D.B * D.N * D.C;
-    if (D.n <= 4) return D.C >= 512 || values <= 2L << 20;
+    if (D.n <= 4) return true;
     if (D.n <= 9) return values <= (D.C <= 384 ? 8L << 20 : 11L << 19);
     if (D.n <= 16) return values <= 5L << 20;
     return values <= (D.n > 32 && D.n < 60 ? 2L << 20 : 4L << 20);

@@ -13,9 +13,9 @@ pytestmark = pytest.mark.gpu
 
 LINES = [  # (B, H, W, C, S, k)
     (32, 14, 7, 256, 7, 4),                                  # 2 tokens
-    (41, 14, 14, 256, 7, 3), (42, 14, 14, 256, 7, 3),        # 4
-    (83, 14, 14, 128, 7, 3), (84, 14, 14, 128, 7, 3),
-    (65, 14, 14, 256, 7, 3), (68, 14, 14, 256, 7, 3),
+    (42, 14, 14, 256, 7, 3), (84, 14, 14, 128, 7, 3),        # 4
+    (66, 14, 14, 256, 7, 3), (67, 14, 14, 256, 7, 3),        # what the general pipeline needs fits the built-in scratch, and not
+    (133, 14, 14, 128, 7, 3), (134, 14, 14, 128, 7, 3),
     (36, 14, 28, 256, 7, 2), (39, 14, 28, 256, 7, 2),        # 8
     (18, 28, 28, 256, 7, 2), (20, 28, 28, 256, 7, 2),        # 16
     (2, 28, 28, 128, 7, 3), (10, 28, 28, 128, 7, 4), (11, 28, 28, 128, 7, 4),
