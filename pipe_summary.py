@@ -19,17 +19,15 @@ duration that bench.py measured with events, and
 from __future__ import annotations
 
 import collections
-import csv
-import glob
 import json
 import re
 import sys
 
-from traffic_summary import NAMES
+from traffic_summary import counter_rows
 
 MORE = {"k_gemm": "gemm", "k_gemm_dma": "gemm", "k_proj": "gemm", "k_token_ln": "block_ln", "k_pos_ln": "block_pos_ln", "k_mlp_fused64": "block_mlp_fused", "k_mlp_stream": "block_mlp_fused",
         "k_attn_gen": "mfma_attention", "k_attn_rows": "mfma_attention", "k_pool_wide": "mfma_pool_qk",
-        "k_route_rows": "mfma_route_rows", "k_route_lce": "mfma_route_rows"}
+        "k_route_lce": "mfma_route_rows"}
 SIMDS, PEAK_HZ, ENGINES = 1024, 2.4e9, 32
 
 
@@ -41,16 +39,13 @@ def main():
     else:
         durations = dict(line["other_workloads"][workload]["kernels_avg_us"])
     acc = collections.defaultdict(lambda: collections.defaultdict(list))
-    for path in glob.glob(directory + "/**/*counter_collection.csv", recursive=True):
-        for row in csv.DictReader(open(path)):
-            m = re.search(r"(k_[a-z0-9_]+)", row["Kernel_Name"])
-            if not m:
-                continue
-            name = NAMES.get(m.group(1)) or MORE.get(m.group(1))
-            if re.search(r"k_qkv<\d+, \d+, 1, \d+>", row["Kernel_Name"]):
-                name = "mfma_wo"
-            if name:
-                acc[name][row["Counter_Name"]].append(float(row["Counter_Value"]))
+    names, rows = counter_rows(directory)
+    for m, row in rows:
+        name = names.get(m.group(1)) or MORE.get(m.group(1))
+        if re.search(r"k_qkv<\d+, \d+, 1, \d+>", row["Kernel_Name"]):
+            name = "mfma_wo"
+        if name:
+            acc[name][row["Counter_Name"]].append(float(row["Counter_Value"]))
     print(f"# workload: {workload}")
     print("# columns: 'pipes' workload kernel avg_us mfma valu waves wait clock_GHz")
     for name, avg_us in durations.items():

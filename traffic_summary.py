@@ -17,26 +17,38 @@ COPY_BYTES = 64 << 20
 NAMES = {"k_fused": "mfma_fused_k1", "k_pool": "mfma_pool_qk", "k_route": "mfma_route_rows",
          "k_route_p": "mfma_route_rows", "k_route_u": "mfma_route_rows", "k_route_w": "mfma_route_rows",
          "k_attn_map": "mfma_attn_small", "k_attn_map4": "mfma_attn_small",
-         "k_qkv": "mfma_qkv", "k_attn_big": "mfma_attention", "k_attn_q32": "mfma_attention", "k_attn_small": "mfma_attn_small",
+         "k_qkv": "mfma_qkv", "k_gemm_means": "mfma_qkv", "k_route_rows": "mfma_route_rows", "k_attn_big": "mfma_attention", "k_attn_q32": "mfma_attention", "k_attn_small": "mfma_attn_small",
          "k_small": "mfma_attn_small", "k_lce_add": "mfma_lce_add", "k_route_lce": "mfma_route_rows",
          "k_token_ln": "block_ln", "k_pos_ln": "block_pos_ln", "k_mlp_fused64": "block_mlp_fused", "k_mlp_stream": "block_mlp_fused",
          "k_util_copy": "copy"}
 
 
-def averages(directory, counter):
-    acc = collections.defaultdict(list)
+def counter_rows(directory):
+    """Rows of a counter run with their kernel's symbol; where the projection leaves the region means, the plain product is W^o."""
+    rows = []
     for path in glob.glob(directory + "/**/*counter_collection.csv", recursive=True):
         for row in csv.DictReader(open(path)):
-            if row["Counter_Name"] != counter:
-                continue
             m = re.search(r"(k_[a-z0-9_]+)", row["Kernel_Name"])
-            if m and m.group(1) in NAMES:
-                name = NAMES[m.group(1)]
-                if re.search(r"k_qkv<\d+, \d+, 1, \d+>", row["Kernel_Name"]):   # the same kernel with Wo as its only matrix
-                    name = "mfma_wo"
-                if m.group(1) == "k_token_ln":                               # position encoding (0) or residual (1) + LayerNorm
-                    name = "block_pos_ln" if "k_token_ln<0" in row["Kernel_Name"] else "block_add_ln"
-                acc[name].append(float(row["Counter_Value"]))
+            if m:
+                rows.append((m, row))
+    names = dict(NAMES)
+    if any(m.group(1) == "k_gemm_means" for m, _ in rows):
+        names["k_gemm_dma"] = "mfma_wo"
+    return names, rows
+
+
+def averages(directory, counter):
+    acc = collections.defaultdict(list)
+    names, rows = counter_rows(directory)
+    for m, row in rows:
+        if row["Counter_Name"] != counter or m.group(1) not in names:
+            continue
+        name = names[m.group(1)]
+        if re.search(r"k_qkv<\d+, \d+, 1, \d+>", row["Kernel_Name"]):   # the same kernel with Wo as its only matrix
+            name = "mfma_wo"
+        if m.group(1) == "k_token_ln":                               # position encoding (0) or residual (1) + LayerNorm
+            name = "block_pos_ln" if "k_token_ln<0" in row["Kernel_Name"] else "block_add_ln"
+        acc[name].append(float(row["Counter_Value"]))
     return {k: sum(v) / len(v) for k, v in acc.items()}
 
 
