@@ -628,7 +628,7 @@ void launch_attn_gen(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *
     // two query tiles per wavefront (every K and V operand read serves both; measured above) where the wider tile leaves no
     // more than an eighth of its queries empty beyond the narrow one and there are workgroups enough.  Both heads in a wavefront where a
     // prologue paid by half as many outweighs the fourth wavefront per SIMD: two query tiles and many workgroups with few keys (layer, us, a
-    // head / both: 32 x 56 x 96 x 128, S = 8, k = 2 (168 keys) 143 / 133 with a given index, 40 x 56 x 70 x 128, k = 1 (80) 144.5 / 139.4, 15 x 176 x 128 x 64, S = 16, k = 4 (352)
+    // head / both: 32 x 56 x 96 x 128, S = 8, k = 2 (168 keys) 143 / 133 with a given index, 27 x 63 x 70 x 192, k = 1 (90) 171 / 163, 15 x 176 x 128 x 64, S = 16, k = 4 (352)
     // 163 / 156; mean of 232 with up to 192 keys 1.028, of 176 with up to 512 1.010; from 11 blocks of keys on, or few workgroups, the other way: 0.99; 4 x 48 x 112 x 128, S = 8,
     // k = 1 38.1 / 39.2).  One query tile: from four workgroups per compute unit on (30 x 42 x 42 x 192, k = 5 107.5 / 103.9; 1 x 72 x 72 x 192, S = 8, k = 12 44.3 / 47.9, 1 x
     // 100 x 150 x 64, S = 16, k = 8 41.8 / 44.7)
