@@ -292,9 +292,31 @@ struct Job {
     __host__ __device__ long blocks() const { return (groups() * cblocks + 7) / 8 * 8; }
 };
 
-// LDS of job_block.
+// LDS of job_block and taps_block: the tap gradients of 256 threads, kTapsAtOnce of them at a time.
+constexpr int kTapsAtOnce = 13;
 template <bool GRAD>
-constexpr size_t job_bytes() { return GRAD ? 25 * 256 * 4 : kTapBytes; }
+constexpr size_t job_bytes() { return GRAD ? kTapsAtOnce * 256 * 4 : kTapBytes; }
+
+// The 8 slots' sums of a channel through LDS, added in a fixed order, to Part[grp].
+__device__ __forceinline__ void store_tap_sums(const Job &J, const Dims &D, int grp, int c0, const float (&acc)[25][2], float *red)
+{
+#pragma unroll
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int t0 = 0; t0 < 25; t0 += kTapsAtOnce) {
+            const int count = 25 - t0 < kTapsAtOnce ? 25 - t0 : kTapsAtOnce;
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < count; ++t) red[t * 256 + threadIdx.x] = acc[t0 + t][v];
+            __syncthreads();
+            for (int e = threadIdx.x; e < count * 32; e += 256) {
+                const int t = e / 32, ch = c0 + 2 * (e % 32) + v;
+                float s = 0.f;
+                for (int k = 0; k < 8; ++k) s += red[t * 256 + k * 32 + e % 32];
+                if (ch < D.C) J.Part[((size_t)grp * D.C + ch) * 25 + 24 - t0 - t] = s;
+            }
+        }
+}
 
 // Workgroup `block` of J, 256 threads.
 template <bool GRAD, bool ADDS>
@@ -315,21 +337,86 @@ __device__ __forceinline__ void job_block(const Job &J, const Dims &D, int block
     for (int t = 0; t < (GRAD ? 25 : 1); ++t) acc[t][0] = acc[t][1] = 0.f;
     if (GRAD) __syncthreads();
     for (long tile = first; tile < last; ++tile) walk_tile<GRAD, ADDS>(J.In, J.V, J.Out, J.Low, J.ldo, D, J.T, tile, slot, c0, cl, live, w, acc);
-    if (!GRAD) return;
-    // the 8 slots' sums of a channel through LDS, added in a fixed order
+    if constexpr (GRAD) store_tap_sums(J, D, grp, c0, acc, red);
+}
+
+// The tap gradients alone, for one tile: a row of In at a time, with the window in V (5 rows of one pair per channel, instead of 5 rows of
+// five): 50 registers less than walk_tile's.  The same sums in the same order.
+__device__ __forceinline__ void walk_taps(const bf16_t *__restrict__ In, const bf16_t *__restrict__ V, const Dims &D, const Tiling &T, long tile, int slot,
+                                          int c0, int cl, float (&acc)[25][2])
+{
+    const int px = slot % T.pairs, sub = slot / T.pairs;
+    const int yt = (int)(tile / T.xtiles % T.ytiles), ybase = yt * T.subs * T.height;
+    const int x0 = 2 * ((int)(tile % T.xtiles) * T.pairs + px), y0 = ybase + sub * T.height;
+    const size_t b = tile / ((long)T.xtiles * T.ytiles);
+    if (sub >= T.subs || x0 >= D.W || y0 >= D.H) return;
+    const int y1 = min(y0 + T.height, D.H), ytop = max(ybase - 2, 0);
+    const bool right = x0 + 1 < D.W;
+    const size_t at = (b * D.N + (size_t)ytop * D.W) * D.C + c0;
+    const char *ibase = (const char *)(In + at), *vbase = (const char *)(V + at);
+    const unsigned irow = 2u * D.W * D.C;
+    unsigned xo[6];
+    bool xok[6];
 #pragma unroll
-    for (int v = 0; v < 2; ++v) {
-        __syncthreads();
+    for (int j = 0; j < 6; ++j) {
+        xok[j] = (unsigned)(x0 + j - 2) < (unsigned)D.W;
+        xo[j] = 2u * (min(max(x0 + j - 2, 0), D.W - 1) * D.C + cl);
+    }
+    const bool edge = !__all(xok[0] && xok[1] && xok[4] && xok[5]);
+    unsigned next[6], nv[2];
+    auto request = [&](int y) {          // row y of In, row y + 2 of V
+        const unsigned row = (unsigned)(min(max(y, 0), D.H - 1) - ytop) * irow, vrow = (unsigned)(min(y + 2, D.H - 1) - ytop) * irow;
 #pragma unroll
-        for (int t = 0; t < (GRAD ? 25 : 1); ++t) red[t * 256 + threadIdx.x] = acc[t][v];
-        __syncthreads();
-        for (int e = threadIdx.x; e < 25 * 32; e += 256) {
-            const int t = e / 32, ch = c0 + 2 * (e % 32) + v;
-            float s = 0.f;
-            for (int k = 0; k < 8; ++k) s += red[t * 256 + k * 32 + e % 32];
-            if (ch < D.C) J.Part[((size_t)grp * D.C + ch) * 25 + 24 - t] = s;
+        for (int j = 0; j < 6; ++j) next[j] = *(const unsigned *)(ibase + (row + xo[j]));
+#pragma unroll
+        for (int j = 0; j < 2; ++j) nv[j] = *(const unsigned *)(vbase + (vrow + xo[j && right ? 3 : 2]));
+    };
+    unsigned vp[5][2] = {};              // of the rows y - 2 .. y + 2
+    request(y0 - 2);
+    for (int yb = y0 - 2; yb < y1 + 2; yb += 5) {
+#pragma unroll
+        for (int u = 0; u < 5; ++u) {
+            const int y = yb + u;
+            if (y >= y1 + 2) break;
+            const bool in = (unsigned)y < (unsigned)D.H;
+            if (edge || !in) {
+#pragma unroll
+                for (int j = 0; j < 6; ++j) next[j] = in && xok[j] ? next[j] : 0u;
+            }
+            const unsigned vr = right ? nv[1] : 0u;
+            vp[u][0] = pair_lo(nv[0], vr);
+            vp[u][1] = pair_hi(nv[0], vr);
+            unsigned p[5][2];            // columns (j, j + 1) of In
+#pragma unroll
+            for (int j = 0; j < 5; ++j) {
+                p[j][0] = pair_lo(next[j], next[j + 1]);
+                p[j][1] = pair_hi(next[j], next[j + 1]);
+            }
+            request(y + 1);
+#pragma unroll
+            for (int r = 0; r < 5; ++r) {        // row y + 2 - r of V, if the tile has it, has this row as row r of its window
+                if (y + 2 - r < y0 || y + 2 - r >= y1) continue;
+#pragma unroll
+                for (int j = 0; j < 5; ++j)
+#pragma unroll
+                    for (int v = 0; v < 2; ++v) acc[5 * r + j][v] = dot2(vp[(u + 5 - r) % 5][v], p[j][v], acc[5 * r + j][v]);
+            }
         }
     }
+}
+
+// Workgroup `block` of J: its tap gradients alone.
+__device__ __forceinline__ void taps_block(const Job &J, const Dims &D, int block, float *red)
+{
+    const int c0 = 64 * (block % J.cblocks), grp = block / J.cblocks;
+    const long first = (long)grp * J.per_wg, last = min(J.tiles, first + J.per_wg);
+    if (first >= J.tiles) return;
+    const int cl = c0 + 2 * ((int)threadIdx.x % 32) < D.C ? 2 * ((int)threadIdx.x % 32) : 0;
+    float acc[25][2];
+#pragma unroll
+    for (int t = 0; t < 25; ++t) acc[t][0] = acc[t][1] = 0.f;
+    for (long tile = first; tile < last; ++tile) walk_taps(J.In, J.V, D, J.T, tile, threadIdx.x / 32, c0, cl, acc);
+    store_tap_sums(J, D, grp, c0, acc, red);
 }
 
 // The two passes of the gradients: LCE^T(dO) with the tap gradients, added to dV or in float32 (lower halves where dK goes), and

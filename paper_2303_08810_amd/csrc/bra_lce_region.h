@@ -1,0 +1,144 @@
+// LCE (Eq. 7: depth-wise 5 x 5 correlation, stride 1, zero padding 2) of one region and 64 channels of a bf16 map, inside a workgroup of
+// four wavefronts that works on that region anyway: what it is added to is then rounded once and no map lies between two kernels.
+//
+// The region with a halo of 2 goes from memory straight into LDS, a token's 64 channels in 128 bytes; the transposing LDS read gives
+// a lane four neighbouring columns of ONE channel, packed as the pairs that v_dot2_f32_bf16 takes, so that nothing is permuted but the odd
+// pairs (one instruction each): 264 vector instructions and 16 LDS reads for 16 outputs of a lane (walk_tile in bra_lce_pairs.h, whose
+// lanes load two channels of a token: 21 per output).  Pairs and taps are those of walk_tile, and so is what an infinity reaches.
+// Pieces of 16 bytes are exchanged: piece p of a token in column x of the halo at p ^ 2 (x / 2 % 4).  The columns of a read, and those of the
+// lane groups beside it, meet different banks then.
+#pragma once
+
+#include "bra_attn_dev.h"
+#include "bra_lce_pairs.h"
+
+namespace bra {
+namespace lce {
+
+// Items of 4 x 4 outputs; the halo is as wide and as high as whole items need.
+struct RegionHalo {
+    int quads, strips;                   // items side by side, above each other
+    __host__ __device__ constexpr RegionHalo(int rh, int rw) : quads((rw + 3) / 4), strips((rh + 3) / 4) {}
+    __host__ __device__ constexpr int items() const { return quads * strips; }
+    __host__ __device__ constexpr int width() const { return 4 * quads + 4; }
+    __host__ __device__ constexpr int tokens() const { return (4 * strips + 4) * width(); }
+    // LDS in bytes: the halo, later the float32 results of n tokens
+    __host__ __device__ constexpr int bytes(int n) const { return tokens() * 128 > 4 * n * 68 ? tokens() * 128 : 4 * n * 68; }
+};
+
+constexpr int kResultPitch = 68;         // floats per token of the results
+
+static __device__ bf16_t zero_piece[8];  // what tokens beyond the map read (never written)
+
+// Requests the halo of the region whose first token is (y0, x0).  map: the image's, at its first of 64 channels.  The caller waits.
+__device__ __forceinline__ void request_halo(const RegionHalo &r, const bf16_t *map, const Dims &D, int y0, int x0, unsigned at, int wave, int lane)
+{
+    const int width = r.width();
+    const float w_inv = 1.0f / (float)width;
+    for (int u = wave; u < r.tokens() / 8; u += 4) {
+        const int t = 8 * u + lane / 8, hy = mfma::divide(t, width, w_inv), hx = t - hy * width, y = y0 - 2 + hy, x = x0 - 2 + hx;
+        const int piece = (lane % 8) ^ 2 * (hx / 2 % 4);
+        const bool in = (unsigned)y < (unsigned)D.H && (unsigned)x < (unsigned)D.W;
+        mfma::load_to_lds_untracked(in ? map + ((size_t)y * D.W + x) * D.C + 8 * piece : zero_piece, at + 1024 * u);
+    }
+}
+
+// The taps of channel c (the lane's; a multiple of 64 channels) as operands, [ky][(w0,w1) | (w2,w3) | (0,w4)].  A channel's 25 lie in 13 words,
+// from the middle of the first one on if c is odd.
+template <bool REVERSED>
+struct LaneTaps {
+    unsigned raw[13];
+    bool odd;
+    __device__ __forceinline__ LaneTaps(const bf16_t *__restrict__ Wlce, int c) : odd(c % 2 != 0)
+    {
+        const unsigned *from = (const unsigned *)(Wlce + (size_t)c * 25 - (odd ? 1 : 0));
+#pragma unroll
+        for (int j = 0; j < 13; ++j) raw[j] = from[j];
+    }
+    __device__ __forceinline__ void operands(unsigned (&w)[5][3]) const
+    {
+        unsigned t[13];                  // taps (2 j, 2 j + 1)
+#pragma unroll
+        for (int j = 0; j < 13; ++j) t[j] = odd ? __builtin_amdgcn_alignbit(j < 12 ? raw[j + 1] : 0u, raw[j], 16) : raw[j];
+        auto pair = [&](int j) { return j % 2 ? __builtin_amdgcn_alignbit(t[j / 2 + 1], t[j / 2], 16) : t[j / 2]; };   // taps (j, j + 1)
+#pragma unroll
+        for (int ky = 0; ky < 5; ++ky) {
+            const int j = REVERSED ? 20 - 5 * ky : 5 * ky;
+            if (REVERSED) {              // taps 24 - 5 ky - kx
+                const unsigned a = pair(j + 3), c = pair(j + 1), e = j % 2 ? t[j / 2] >> 16 : t[j / 2];
+                w[ky][0] = __builtin_amdgcn_alignbit(a, a, 16);
+                w[ky][1] = __builtin_amdgcn_alignbit(c, c, 16);
+                w[ky][2] = e << 16;
+            } else {
+                w[ky][0] = pair(j);
+                w[ky][1] = pair(j + 2);
+                w[ky][2] = j % 2 ? t[(j + 4) / 2] & 0xffff0000u : t[(j + 4) / 2] << 16;
+            }
+        }
+    }
+};
+
+// Sums of the lane's channel: lane group q has items q, q + 4, .. , ROUNDS of them; o[round][row][column].
+template <int ROUNDS>
+__device__ __forceinline__ void halo_sums(const RegionHalo &r, const bf16_t *halo, const unsigned (&w)[5][3], int wave, int lane, float (&o)[ROUNDS][4][4])
+{
+    const int s = lane % 16, width = r.width();
+#pragma unroll
+    for (int round = 0; round < ROUNDS; ++round) {
+        if (4 * round >= r.items()) break;
+        const int item = min(4 * round + lane / 16, r.items() - 1), strip = item / r.quads, quad = item - strip * r.quads;
+        const bf16_t *at[2];             // the item's columns 0 to 3 and 4 to 7
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int hx = 4 * (quad + half) + s / 4;
+            at[half] = halo + (4 * strip * width + hx) * 64 + 8 * ((2 * wave + s % 4 / 2) ^ 2 * (hx / 2 % 4)) + 4 * (s % 2);
+        }
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[round][a][c] = 0.f;
+#pragma unroll
+        for (int y = 0; y < 8; ++y) {
+            unsigned p[7];               // columns (j, j + 1)
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const mfma::u32x2 v = __builtin_bit_cast(mfma::u32x2, mfma::lds_read_tr16(at[half] + y * width * 64));
+                p[4 * half] = v[0];
+                p[4 * half + 2] = v[1];
+            }
+#pragma unroll
+            for (int j = 1; j < 7; j += 2) p[j] = __builtin_amdgcn_alignbit(p[j + 1], p[j - 1], 16);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                if (y < a || y > a + 4) continue;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    o[round][a][c] = dot2(w[y - a][0], p[c], o[round][a][c]);
+                    o[round][a][c] = dot2(w[y - a][1], p[c + 2], o[round][a][c]);
+                    o[round][a][c] = dot2(w[y - a][2], p[c + 3], o[round][a][c]);
+                }
+            }
+        }
+    }
+}
+
+// Leaves them in LDS, row by token of the region, kResultPitch floats apart.
+template <int ROUNDS>
+__device__ __forceinline__ void park_sums(const RegionHalo &r, const Dims &D, float *to, int wave, int lane, const float (&o)[ROUNDS][4][4])
+{
+#pragma unroll
+    for (int round = 0; round < ROUNDS; ++round) {
+        const int item = 4 * round + lane / 16, strip = item / r.quads, quad = item - strip * r.quads;
+        if (4 * round >= r.items()) break;
+        if (item >= r.items()) continue;
+        float *at = to + (4 * strip * D.rw + 4 * quad) * kResultPitch + 16 * wave + lane % 16;
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (4 * strip + a < D.rh && 4 * quad + c < D.rw) at[(a * D.rw + c) * kResultPitch] = o[round][a][c];
+    }
+}
+
+}  // namespace lce
+}  // namespace bra

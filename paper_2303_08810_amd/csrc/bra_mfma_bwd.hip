@@ -10,8 +10,8 @@
 //     dK = dS^T Q,  dV = P^T dO        key side: from the query regions routed to a KEY region, found in Ir, with P and
 //                                      dS recomputed from the statistics and sums in registers: no atomic adds
 //                                      (k_attn_bwd_map on small maps, else k_attn_bwd_q and k_attn_bwd_kv)
-//     O += LCE(V)                      in the key side's launch, or k_lce_backward
-//     dV += LCE^T(dO) (the correlation with the taps reversed) and
+//     O += LCE(V)                      in the query side, in the key side's launch, or k_lce_backward
+//     dV += LCE^T(dO) (the correlation with the taps reversed; also in the key side) and
 //     dWlce[c][ky][kx] = sum_t dO[t][c] V[t + (ky - 2, kx - 2)][c]       in the query side's launch, or k_lce_backward
 //     dX = [dQ | dK | dV] Wqkv^T,  dWqkv = X^T [dQ | dK | dV]      k_bwd_proj, one pass over the gradient map, or k_gemm_bt_tn
 //     dWo = O^T dY                     k_bwd_proj or k_gemm_tn (contraction over tokens)
@@ -260,7 +260,7 @@ int attention_and_lce(const Dims &D, const BwdWs &w, const int32_t *Ir, const bf
     const AttnBwdArgs A = {w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, w.lse, w.dsum};
     const bool map = attn_bwd_map_ok(D);
     const int rc = map ? launch_attn_bwd_map(D, w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, K_GEN_BACKWARD, st) : launch_attn_bwd(D, A, L, K_GEN_BACKWARD, st);
-    if (rc != BRA_OK || (!map && L.beside)) return rc;
+    if (rc != BRA_OK || (!map && (L.beside || attn_bwd_convolves(D, L)))) return rc;
     return lce::lce_backward_bf16(D, L, K_GEN_BACKWARD, st);
 }
 

@@ -12,7 +12,8 @@ struct AttnBwdArgs {
     float *lse, *dsum;                 // [B][heads][N] row statistics
 };
 
-// With lce.beside both passes of lce are done within the two launches; without, the caller runs them afterwards.
+// With lce.beside, or where attn_bwd_convolves(), both passes of lce are done within the two launches; without, the caller runs them afterwards.
+bool attn_bwd_convolves(const Dims &D, const lce::BackwardJobs &lce);
 int launch_attn_bwd(const Dims &D, const AttnBwdArgs &A, const lce::BackwardJobs &lce, int kernel_id, hipStream_t st);
 
 }  // namespace bra

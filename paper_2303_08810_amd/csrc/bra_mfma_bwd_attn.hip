@@ -25,7 +25,18 @@
 // Each launch costs about 6 us to fill and to drain the chip, and neither kind of work alone keeps the memory busy.  Whole
 // gradient with launches of their own and here (us): 1 x 56 x 56 x 64, k = 1: 39.2 -> 31.7; 16 images: 87.6 -> 77.9;
 // 64 x 28 x 28 x 128, k = 4: 144 -> 140; 8 x 56 x 56 x 256, k = 4: 200 -> 186; 12 x 112 x 120 x 64: 251 -> 237.  Large maps: BackwardJobs.
+//
+// LCE: where a workgroup has its region whole and all routed keys in one block, the query side adds LCE(V) to O and the key side begins dV with
+// LCE^T(dO), both from the region's halo in LDS (bra_lce_region.h): 26 bytes per value less to move (the float32 between the
+// two kernels, O read and written once more, V and dO read once more), and O is rounded once (error of dWo of 64 x 56 x 56 x 64 from
+// float64 2.44e-3 -> 2.26e-3).  The tap gradients alone stay a pass.  Together with SINGLE, 64 x 56 x 56 x 64, k = 1: query side 71 -> 55 us,
+// key side 66 -> 58, whole gradient 209 -> 181; 16 images 79.3 -> 77.9, 2 images 40.0 -> 40.1.  Of the key side's 58 us the attention takes 43, the
+// products of the convolution 6, the halo's loads 5; the list of regions made while they arrive gave nothing, and the convolution
+// beside the first block costs 90 registers of scratch.  With more than one block (36 tokens, k = 6; 63 tokens, k = 4) it is 0 to 9 % slower than the passes.
+// SINGLE: all routed keys in one block: a head's scores and dP stay in registers from the weights to dS, which takes out the second sweep (a
+// third of the vector instructions) and 50 registers; 44 x 21 x 21 x 512, k = 2 281 -> 275 us.
 #include "bra_attn_dev.h"
+#include "bra_lce_region.h"
 #include "bra_mfma_bwd_attn.h"
 
 namespace bra {
@@ -59,27 +70,34 @@ __device__ __forceinline__ bool place(const Dims &D, int tiles, int items, int w
     return true;
 }
 
+// Items of a lane group at most (lce::halo_sums).
+constexpr int kLceRounds = 2;
+
 // ---------------------------------------------------------------------------
 // Query side: attention output O, row statistics lse and D, and dQ, in two sweeps over the region's k n routed keys.  The
 // first is the forward's attention and sums D = sum P dP beside it, from the float32 weights (dO . O has the rounding of
 // the weights that entered O).  The second goes over the blocks backwards, so that the
 // last two are still in LDS (up to 128 or 64 routed keys: nothing is read twice).
-template <int HD, int NQ, Mode MODE>
-__global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_attn_bwd_q(AttnBwdArgs A, Dims D, int tiles, int items, int walks, lce::Job J, int lce_blocks, int lce_front)
+template <int HD, int NQ, Mode MODE, bool LCE, bool SINGLE>
+__global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? (LCE ? 4 : 3) : 2) void k_attn_bwd_q(AttnBwdArgs A, Dims D, int tiles, int items, int walks, lce::Job J,
+                                                                                                     int lce_blocks, int lce_front)
 {
     using R = Rows<MODE>;
     constexpr bool SHARED = R::SHARED, SPLIT = MODE == kSplit;
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16, KB = R::KB, KT = KB / 16;
-    __shared__ __attribute__((aligned(16))) bf16_t lds[R::bufs * R::buf];
+    static_assert(!LCE || (SINGLE && SHARED && NQ == 1), "one block, one tile");
+    __shared__ __attribute__((aligned(16))) bf16_t lds[LCE ? R::buf : R::bufs * R::buf];
     constexpr int kPart = 64 * (3 + 4 * NDT);    // SPLIT: m, l, D and the sums of a wavefront, one query tile and head
     __shared__ __attribute__((aligned(16))) float sums[SPLIT ? NQ * HPW * 4 * kPart : 4];
     static_assert(lce::job_bytes<true>() <= sizeof(lds), "the pass shares the buffers");
+    // LCE: the halo of V, then LCE(V) of the tokens; [k] or [4][k]: first token of the routed regions; with `walks` [n] or [4][n]: tokens of a region's slots
+    extern __shared__ __attribute__((aligned(16))) int origin_tables[];
     int wg, wgs;
     if (lce::block_of_pass(lce_blocks, lce_front, wg, wgs)) {
-        lce::job_block<true, false>(J, D, swizzled(wg, wgs), (float *)lds);
+        if constexpr (LCE) lce::taps_block(J, D, swizzled(wg, wgs), (float *)lds);
+        else lce::job_block<true, false>(J, D, swizzled(wg, wgs), (float *)lds);
         return;
     }
-    extern __shared__ int origin_tables[];       // [k] or [4][k]: first token of the routed regions; with `walks` [n] or [4][n]: tokens of a region's slots
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C = D.C, n = D.n, kn = D.kn;
     int b, reg, tile, cg;
@@ -88,8 +106,11 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
     const float n_inv = 1.0f / (float)n;
     const size_t img = (size_t)b * D.N * C + 64 * cg;
     bf16_t *mine = lds + (SHARED ? 0 : wave * 2 * R::buf);
-    int *origins = origin_tables + (SHARED ? 0 : wave * D.k), *slots = origin_tables + (SHARED ? D.k : 4 * D.k + wave * n);
-    if (walks)
+    const lce::RegionHalo halo(D.rh, D.rw);
+    int *const tables = origin_tables + (LCE ? halo.bytes(n) / 4 : 0);
+    const lce::LaneTaps<false> taps(J.Wlce, 64 * cg + (LCE ? 16 * wave + lane % 16 : 0));
+    int *origins = tables + (SHARED ? 0 : wave * D.k), *slots = tables + (SHARED ? D.k : 4 * D.k + wave * n);
+    if (LCE || walks)
         for (int t = SHARED ? tid : lane; t < n; t += SHARED ? 256 : kWave) slots[t] = at.slot(t);
     for (int p = SHARED ? tid : lane; p < D.k; p += SHARED ? 256 : kWave)
         origins[p] = at.origin(region_index(A.Ir[((size_t)b * D.R + reg) * D.k + p], D.R));
@@ -117,6 +138,12 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
         for (int hh = 0; hh < HPW; ++hh)
 #pragma unroll
             for (int ks = 0; ks < KSD; ++ks) asm volatile("" : "+v"(qf[q][hh][ks]), "+v"(gf[q][hh][ks]));
+    unsigned w[5][3];
+    if constexpr (LCE) {
+        taps.operands(w);
+#pragma unroll
+        for (int ky = 0; ky < 5; ++ky) asm volatile("" : "+v"(w[ky][0]), "+v"(w[ky][1]), "+v"(w[ky][2]));
+    }
     if (SHARED) __syncthreads();
     else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // the table is read by other lanes
 
@@ -134,7 +161,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
         if (back) walk.retreat();
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) {
-            if (MODE == kWaves || walks) {
+            if (MODE == kWaves || LCE || walks) {
                 const unsigned off = row_offset(walk.token(u, origins, D.k - 1, slots), C, piece);
                 load_to_lds_untracked(A.K + img, off, to + 1024 * u);
                 load_to_lds_untracked(A.V + img, off, to + KB * 128 + 1024 * u);
@@ -151,7 +178,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
     // On return the block of step s is in LDS and that of step s + 1 requested.
     auto block_of = [&](int s) { return s < nb ? s : 2 * nb - 1 - s; };
     auto advance = [&](int s) {
-        const bool more = s + 1 < 2 * nb && (s + 1 < nb || s + 1 > nb + 1);
+        const bool more = !SINGLE && s + 1 < 2 * nb && (s + 1 < nb || s + 1 > nb + 1);
         if (s + 1 == nb + 2) {                   // from behind the last block to the one before the two that are in place
             walk.retreat();
             walk.retreat();
@@ -230,9 +257,117 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? 3 : 2) void k_att
         }
     };
     if (!SPLIT || nb > 0) {
+        if constexpr (LCE) {
+            const int ry = fast_div(reg, at.s_inv);
+            lce::request_halo(halo, A.V + img, D, ry * D.rh, (reg - ry * D.S) * D.rw, lds_address(origin_tables), wave, lane);
+        }
         request(0, false);
+        if constexpr (LCE) {
+            asm volatile("s_waitcnt vmcnt(%0)" : : "i"(2 * LOADS) : "memory");       // the halo is there, the block need not be
+            __syncthreads();
+            float o[kLceRounds][4][4];
+            lce::halo_sums<kLceRounds>(halo, (const bf16_t *)origin_tables, w, wave, lane, o);
+            __syncthreads();                     // the halo has been read
+            lce::park_sums<kLceRounds>(halo, D, (float *)origin_tables, wave, lane, o);
+        }
         advance(0);
-        if (!idle) forward(0, std::true_type{});
+        if constexpr (!SINGLE) {
+            if (!idle) forward(0, std::true_type{});
+        }
+    }
+    if constexpr (SINGLE) {
+        // a head at a time, its scores and dP in registers from beginning to end
+        if (idle) return;
+        const bf16_t *Ks = mine, *Vs = Ks + KB * 64;
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh) {
+            f32x4 sc[NQ][KT], dp[NQ][KT];
+#pragma unroll
+            for (int t = 0; t < KT; ++t) {
+                bf16x8 kf[KSD], vf[KSD];
+#pragma unroll
+                for (int ks = 0; ks < KSD; ++ks) {
+                    kf[ks] = row_operand(Ks, 16 * t + i, HD / 8 * hh + 4 * ks + g);
+                    vf[ks] = row_operand(Vs, 16 * t + i, HD / 8 * hh + 4 * ks + g);
+                }
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    sc[q][t] = dp[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < KSD; ++ks) {
+                        sc[q][t] = mfma16(kf[ks], qf[q][hh][ks], sc[q][t]);       // S^T[key 16 t + 4 g + j][query i]
+                        dp[q][t] = mfma16(vf[ks], gf[q][hh][ks], dp[q][t]);
+                    }
+                }
+            }
+            bf16x8 pb[NQ][KT / 2], db[NQ][KT / 2];
+            float inv[NQ];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                mask(sc[q], kn);
+                float mx = sc[q][0][0];
+#pragma unroll
+                for (int t = 0; t < KT; ++t)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) mx = fmaxf(mx, sc[q][t][j]);
+                mx = cross_row_max(mx);
+                float sum = 0.f, d = 0.f;
+#pragma unroll
+                for (int t = 0; t < KT; ++t)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        sc[q][t][j] = __builtin_amdgcn_exp2f(sc[q][t][j] - mx);
+                        sum += sc[q][t][j];
+                        d = fmaf(sc[q][t][j], dp[q][t][j], d);
+                    }
+                sum = cross_row_sum(sum);
+                inv[q] = 1.0f / sum;
+                d = cross_row_sum(d) * inv[q];
+#pragma unroll
+                for (int tp = 0; tp < KT / 2; ++tp) {
+                    float p[8], ds[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        p[e] = sc[q][2 * tp + e / 4][e % 4];
+                        ds[e] = p[e] * inv[q] * (dp[q][2 * tp + e / 4][e % 4] - d);
+                    }
+                    pb[q][tp] = pack8(p);
+                    db[q][tp] = pack8(ds);
+                }
+                if (q0 + 16 * q + i < n && g == 0) {
+                    const size_t e = ((size_t)b * D.heads + HPW * cg + hh) * D.N + tok[q];
+                    A.lse[e] = mx + __builtin_amdgcn_logf(sum);                  // v_log_f32: log2
+                    A.dsum[e] = d;
+                }
+            }
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) {
+                f32x4 o[NQ], dq[NQ];
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) o[q] = dq[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int tp = 0; tp < KT / 2; ++tp) {
+                    const bf16x8 vc = column_operand(Vs, 32 * tp, HD * hh + 16 * dt, g, i), kc = column_operand(Ks, 32 * tp, HD * hh + 16 * dt, g, i);
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) {
+                        o[q] = mfma16(vc, pb[q][tp], o[q]);
+                        dq[q] = mfma16(kc, db[q][tp], dq[q]);
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const int slot = q0 + 16 * q + i;
+                    if (slot >= n) continue;
+                    const int ch = HD * hh + 16 * dt + 4 * g;
+                    f32x4 v = o[q] * inv[q];
+                    if constexpr (LCE) v += *(const f32x4 *)((const float *)origin_tables + slot * lce::kResultPitch + ch);
+                    *(u32x2 *)(A.O + img + (size_t)tok[q] * C + ch) = pack4(v);
+                    *(u32x2 *)(A.dQKV + ((size_t)b * D.N + tok[q]) * 3 * C + 64 * cg + ch) = pack4(dq[q] * D.scale);
+                }
+            }
+            if (SHARED) __builtin_amdgcn_sched_barrier(0);    // one head at a time: interleaved, they take twice the registers
+        }
+        return;
     }
 #pragma unroll 1
     for (int s = 1; s < nb; ++s) {
@@ -446,8 +581,8 @@ __device__ __forceinline__ int list_of_group(const int32_t *__restrict__ irb, in
     return __builtin_amdgcn_readfirstlane(total);
 }
 
-template <int HD, int NK, Mode MODE>
-__global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_attn_bwd_kv(AttnBwdArgs A, Dims D, int tiles, int items, int walks, lce::Job J, int lce_blocks)
+template <int HD, int NK, Mode MODE, bool LCE>
+__global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? (LCE ? 4 : 3) : 2) void k_attn_bwd_kv(AttnBwdArgs A, Dims D, int tiles, int items, int walks, lce::Job J, int lce_blocks)
 {
     using R = Rows<MODE>;
     constexpr bool SHARED = R::SHARED, SPLIT = MODE == kSplit;
@@ -458,12 +593,12 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
     __shared__ __attribute__((aligned(16))) float sums[SPLIT ? NK * 4 * 2048 : 4];
     __shared__ int lists[SHARED ? kListShared : 4 * kListWave];
     __shared__ int counts[16];
-    int wg, wgs;
-    if (lce::block_of_pass(lce_blocks, false, wg, wgs)) {
+    int wg = blockIdx.x, wgs = gridDim.x;
+    if (!LCE && lce::block_of_pass(lce_blocks, false, wg, wgs)) {
         lce::job_block<false, true>(J, D, swizzled(wg, wgs), (float *)lds);
         return;
     }
-    extern __shared__ int slot_tables[];         // with `walks` [n] or [4][n]: tokens of a region's slots
+    extern __shared__ __attribute__((aligned(16))) int slot_tables[];         // with `walks` [n] or [4][n]: tokens of a region's slots
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
     const int C = D.C, n = D.n;
     int b, reg, tile, cg;
@@ -475,7 +610,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
     bf16_t *mine = lds + (SHARED ? 0 : wave * 2 * R::buf);
     float *my_stats = stats + (SHARED ? 0 : wave * 2 * kStats);
     int *list = lists + (SHARED ? 0 : wave * kListWave), *slots = slot_tables + (SHARED ? 0 : wave * n);
-    if (walks)
+    if (LCE || walks)
         for (int t = SHARED ? tid : lane; t < n; t += SHARED ? 256 : kWave) slots[t] = at.slot(t);
 
     const int q0 = SHARED ? 64 * NK * tile + 16 * NK * wave : 16 * NK * tile;
@@ -501,7 +636,23 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
         for (int hh = 0; hh < HPW; ++hh)
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) dk[q][hh][dt] = dv[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-
+    // dV begins with LCE^T(dO)
+    if constexpr (LCE) {
+        unsigned w[5][3];
+        const lce::RegionHalo halo(D.rh, D.rw);
+        const lce::LaneTaps<true> taps(J.Wlce, 64 * cg + 16 * wave + lane % 16);
+        const int ry = fast_div(reg, at.s_inv);
+        lce::request_halo(halo, A.dO + img, D, ry * D.rh, (reg - ry * D.S) * D.rw, lds_address(lds), wave, lane);
+        taps.operands(w);
+        arrive_barrier();
+        float o[kLceRounds][4][4];
+        lce::halo_sums<kLceRounds>(halo, lds, w, wave, lane, o);
+        __syncthreads();                         // the halo has been read
+        lce::park_sums<kLceRounds>(halo, D, (float *)lds, wave, lane, o);
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < HPW * NDT; ++a) dv[0][a / NDT][a % NDT] = *(const f32x4 *)((const float *)lds + min(q0 + i, n - 1) * lce::kResultPitch + 16 * a + 4 * g);
+    }
     int rows = 0;
     constexpr int STEP = SPLIT ? 4 : 1;          // as above
     const int start = SPLIT ? wave : 0;
@@ -521,7 +672,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
             const int r = min(KB * blk + row, rows - 1), p = divide(r, n, n_inv);
             return list[p] + at.slot(r - p * n);
         };
-        const bool tables = MODE == kWaves || walks;
+        const bool tables = MODE == kWaves || LCE || walks;
         lds_reads_done();
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) {
@@ -552,7 +703,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
         const int blk = STEP * local + start;
         const bf16_t *Qs = mine + (local % 2) * R::buf, *Gs = Qs + KB * 64;
         const float *st = my_stats + (local % 2) * kStats;
-#pragma unroll
+#pragma unroll(LCE ? 1 : KB / 32)
         for (int tp = 0; tp < KB / 32; ++tp) {
             const int left = rows - KB * blk - 32 * tp;
             if (tp && left <= 0) break;
@@ -658,7 +809,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
     }
     // With the pass, LCE^T(dO) is there in float32: its upper halves where dV goes, its lower ones where dK goes.
     auto store = [&](bf16_t *at, f32x4 k, f32x4 v) {
-        if (lce_blocks) {
+        if (!LCE && lce_blocks) {
             const u32x2 hi = *(const u32x2 *)(at + C), lo = *(const u32x2 *)at;
             v += __builtin_bit_cast(f32x4, u32x4{pair_lo(lo[0], hi[0]), pair_hi(lo[0], hi[0]), pair_lo(lo[1], hi[1]), pair_hi(lo[1], hi[1])});
         }
@@ -700,7 +851,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NK == 1 ? 3 : 2) void k_att
     }
 }
 
-template <int HD, int N, Mode MODE>
+template <int HD, int N, Mode MODE, bool LCE = false>
 int launch_t(const Dims &D, const AttnBwdArgs &A, const lce::BackwardJobs &L, int kernel_id, hipStream_t st)
 {
     const int per_tile = (MODE == kShared ? 64 : 16) * N, tiles = (D.n + per_tile - 1) / per_tile;
@@ -711,43 +862,74 @@ int launch_t(const Dims &D, const AttnBwdArgs &A, const lce::BackwardJobs &L, in
     // 64 x 56 x 56 x 64, k = 1, 3136 workgroups: 64.5 behind, 55.4 in front, 70 with the two kinds in turn).  The other pass is
     // always behind: its many short workgroups fill up the last round (12 x 112 x 120 x 64, k = 1: key side 76 us, in front 87).
     const bool front = blocks > 768;
-    const long with_q = L.beside ? L.grad.blocks() : 0, with_kv = L.beside ? L.add.blocks() : 0;
+    const long with_q = L.beside || LCE ? L.grad.blocks() : 0, with_kv = L.beside && !LCE ? L.add.blocks() : 0;
+    const int halo = LCE ? lce::RegionHalo(D.rh, D.rw).bytes(D.n) : 0;
     // kWaves has at most 32 tokens per region and always walks (up to 4096 regions)
     const size_t tables = MODE == kShared ? 1 : 4;
     const int walks = MODE == kSplit ? walk_ok(D) && D.n <= 256 : walk_ok(D);
-    {
+    auto query_side = [&](auto single) {
         ProfScope ps(st, kernel_id);
-        hipLaunchKernelGGL((k_attn_bwd_q<HD, N, MODE>), dim3((unsigned)(blocks + with_q)), dim3(256), tables * (D.k + (walks ? D.n : 0)) * sizeof(int), st,
-                           A, D, tiles, (int)items, walks, L.grad, (int)with_q, front);
+        hipLaunchKernelGGL((k_attn_bwd_q<HD, N, MODE, LCE, decltype(single)::value>), dim3((unsigned)(blocks + with_q)), dim3(256),
+                           halo + tables * (D.k + (walks ? D.n : 0)) * sizeof(int), st, A, D, tiles, (int)items, walks, L.grad, (int)with_q, front);
+    };
+    if constexpr (LCE) {
+        query_side(std::true_type{});
+    } else if constexpr (MODE == kWaves) {
+        if (D.kn <= Rows<MODE>::KB) query_side(std::true_type{});
+        else query_side(std::false_type{});
+    } else {
+        query_side(std::false_type{});
     }
     if (hipGetLastError() != hipSuccess) return BRA_ERR_LAUNCH;
     ProfScope ps(st, kernel_id);
-    hipLaunchKernelGGL((k_attn_bwd_kv<HD, N, MODE>), dim3((unsigned)(blocks + with_kv)), dim3(256), tables * (walks ? D.n : 0) * sizeof(int), st, A, D, tiles,
+    hipLaunchKernelGGL((k_attn_bwd_kv<HD, N, MODE, LCE>), dim3((unsigned)(blocks + with_kv)), dim3(256), tables * (walks ? D.n : 0) * sizeof(int), st, A, D, tiles,
                        (int)items, walks, L.add, (int)with_kv);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+long wave_groups(const Dims &D) { return (long)D.B * D.R * (D.C / 64); }
+
+// Two token tiles per wavefront (every operand read serves both) where they leave no more than an eighth of their
+// tokens empty beyond the narrow ones and there are workgroups enough.
+bool two_tiles(const Dims &D)
+{
+    const long t64 = (D.n + 63) / 64, t128 = (D.n + 127) / 128;
+    return t128 * 128 * 8 <= t64 * 64 * 9 && wave_groups(D) * t128 >= 512;
+}
+
+// A workgroup has its region whole and all routed keys in one block, and the key side's buffers hold the halo.
+bool convolves(const Dims &D, const lce::BackwardJobs &L)
+{
+    const lce::RegionHalo halo(D.rh, D.rw);
+    return L.fit && D.n <= 64 && D.kn <= Rows<kShared>::KB && walk_ok(D) && halo.items() <= 4 * kLceRounds &&
+           halo.bytes(D.n) <= 2 * Rows<kShared>::buf * (int)sizeof(bf16_t);
+}
+
+Mode mode_of(const Dims &D)
+{
+    const long waves = wave_groups(D) * (D.n <= 32 ? 1 : 4 * ((D.n + 63) / 64));
+    // Too few wavefronts for the 1024 SIMDs: four share the rows of a tile, where a row list has at least two blocks
+    // (us for the whole gradient: 3 x 14 x 49 x 64, k = 20: 66 -> 50; 28 x 28 x 64, k = 4, 64 routed keys: 45 -> 42; but
+    // 392 wavefronts and 80 keys: 66 -> 69, 196 and 4 keys: 49 -> 60).
+    if (waves <= 256 && D.kn >= 64) return kSplit;
+    return D.n <= 32 ? kWaves : kShared;
 }
 
 template <int HD>
 int launch_hd(const Dims &D, const AttnBwdArgs &A, const lce::BackwardJobs &L, int kernel_id, hipStream_t st)
 {
-    const long regions = (long)D.B * D.R * (D.C / 64), t64 = (D.n + 63) / 64, t128 = (D.n + 127) / 128;
-    const long waves = regions * (D.n <= 32 ? 1 : 4 * t64);
-    // Too few wavefronts for the 1024 SIMDs: four share the rows of a tile, where a row list has at least two blocks
-    // (us for the whole gradient: 3 x 14 x 49 x 64, k = 20: 66 -> 50; 28 x 28 x 64, k = 4, 64 routed keys: 45 -> 42; but
-    // 392 wavefronts and 80 keys: 66 -> 69, 196 and 4 keys: 49 -> 60).
-    if (waves <= 256 && D.kn >= 64) {
-        if (D.n <= 16) return launch_t<HD, 1, kSplit>(D, A, L, kernel_id, st);
-        return launch_t<HD, 2, kSplit>(D, A, L, kernel_id, st);
+    switch (mode_of(D)) {
+    case kSplit: return D.n <= 16 ? launch_t<HD, 1, kSplit>(D, A, L, kernel_id, st) : launch_t<HD, 2, kSplit>(D, A, L, kernel_id, st);
+    case kWaves: return D.n <= 16 ? launch_t<HD, 1, kWaves>(D, A, L, kernel_id, st) : launch_t<HD, 2, kWaves>(D, A, L, kernel_id, st);
+    default:
+        if (two_tiles(D)) return launch_t<HD, 2, kShared>(D, A, L, kernel_id, st);
+        return convolves(D, L) ? launch_t<HD, 1, kShared, true>(D, A, L, kernel_id, st) : launch_t<HD, 1, kShared>(D, A, L, kernel_id, st);
     }
-    if (D.n <= 16) return launch_t<HD, 1, kWaves>(D, A, L, kernel_id, st);
-    if (D.n <= 32) return launch_t<HD, 2, kWaves>(D, A, L, kernel_id, st);
-    // two token tiles per wavefront (every operand read serves both) where they leave no more than an eighth of their
-    // tokens empty beyond the narrow ones and there are workgroups enough
-    if (t128 * 128 * 8 <= t64 * 64 * 9 && regions * t128 >= 512) return launch_t<HD, 2, kShared>(D, A, L, kernel_id, st);
-    return launch_t<HD, 1, kShared>(D, A, L, kernel_id, st);
 }
 
 }  // namespace
+
+bool attn_bwd_convolves(const Dims &D, const lce::BackwardJobs &L) { return mode_of(D) == kShared && !two_tiles(D) && convolves(D, L); }
 
 int launch_attn_bwd(const Dims &D, const AttnBwdArgs &A, const lce::BackwardJobs &L, int kernel_id, hipStream_t st)
 {
