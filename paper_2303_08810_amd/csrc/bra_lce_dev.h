@@ -109,7 +109,7 @@ __device__ __forceinline__ void stage_taps(const Taps &taps, int c0, int C, floa
 // 1) channels of one pair: an input row of 6 columns is read once and goes into the outputs it belongs to.  Image and rows
 // are the same for all lanes, so that a load is a scalar row address and a 32-bit lane offset.  The taps pass through
 // LDS once per workgroup: read per thread from the [C][25] tensor they would cost a cache line per lane.
-// Bound by the latency of its eight rows of loads and by the FMAs.  16 x 56 x 56 x 64 float32 beside the routing: 11 us for
+// Bound by the FMAs and by the latency of the first of its eight rows; each further one is requested a row ahead.  16 x 56 x 56 x 64 float32 beside the routing: 11 us for
 // both, 19 with one column per thread and addresses of its own for every load (k_lce_far; 122 registers for 84).
 // Row pitches ldi, ldo.
 constexpr int kLceRows = 4;
@@ -150,14 +150,21 @@ __device__ __forceinline__ void lce_block(const AddJob<TM> &J, const Dims &D, in
     Channels<VW> acc[kLceRows][2] = {};
     const char *img = (const char *)(J.In + (size_t)b * D.N * J.ldi + c0);
     const size_t pitch = sizeof(TM) * (size_t)D.W * J.ldi;
+    Channels<VW> raw[2][6];
+    auto request = [&](int dy) {                 // from a row of the map in any case
+        const char *row = img + min(max(y0 + dy - 2, 0), D.H - 1) * pitch;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) raw[dy % 2][j] = load_channels<VW>((const TM *)(row + xo[j]));
+    };
+    request(0);
 #pragma unroll
     for (int dy = 0; dy < kLceRows + 4; ++dy) {
         const int y = y0 + dy - 2;
+        if (dy + 1 < kLceRows + 4) request(dy + 1);
         if (y < 0 || y >= D.H) continue;
-        const char *row = img + y * pitch;
         Channels<VW> in[6];
 #pragma unroll
-        for (int j = 0; j < 6; ++j) in[j] = load_channels<VW>((const TM *)(row + xo[j]));
+        for (int j = 0; j < 6; ++j) in[j] = raw[dy % 2][j];
         if (edge) {
 #pragma unroll
             for (int j = 0; j < 6; ++j)
@@ -335,7 +342,8 @@ inline LcePlan lce_plan(const Dims &D, int slots, int cols)
 // and leave as Part[group][C][25] (k_reduce_parts adds the groups in a fixed order).  Bound by those FMAs
 // (and, for VW = 2, by the two wavefronts per SIMD that about 190 registers allow).
 // height is a multiple of 5 (the window's rows rotate through fixed registers): 20, or less where that leaves
-// too few workgroups (8 x 28 x 28 x 128 float32: 26 us with strips of 20, 128 workgroups).
+// too few workgroups (8 x 28 x 28 x 128 float32: 26 us with strips of 20, 128 workgroups).  The next row is requested a step ahead (query
+// side with the pass of 60 x 28 x 28 x 96: 99 -> 90 us, 30 x 35 x 35 x 96 87 -> 78).
 
 // Workgroup `block` of J, 256 threads; red: [25][256].  ADDS = false: dV = LCE^T(dO).
 template <int VW, bool ADDS, typename TM>
@@ -370,30 +378,48 @@ __device__ __forceinline__ void lce_grad_block(const GradJob<TM> &J, const Dims 
         if (x >= D.W) continue;
         const int y1 = min(y0 + height, D.H);
         const TM *dimg = dO + b * D.N * D.C + c;
-        Channels<VW> win[5][5];
+        bool xok[5];
+        int xc[5];
+#pragma unroll
+        for (int kx = 0; kx < 5; ++kx) {
+            xok[kx] = (unsigned)(x + kx - 2) < (unsigned)D.W;
+            xc[kx] = min(max(x + kx - 2, 0), D.W - 1);
+        }
+        // rows come from clamped places and are blanked where they are used, not behind the loads
         auto load_row = [&](int y, Channels<VW> (&row)[5]) {
+            const size_t first = (size_t)min(max(y, 0), D.H - 1) * D.W;
+#pragma unroll
+            for (int kx = 0; kx < 5; ++kx) row[kx] = load_channels<VW>(dimg + (first + xc[kx]) * D.C);
+        };
+        auto blank = [&](int y, const Channels<VW> (&from)[5], Channels<VW> (&row)[5]) {
             const bool in = (unsigned)y < (unsigned)D.H;
 #pragma unroll
-            for (int kx = 0; kx < 5; ++kx) {
-                const int xx = x + kx - 2;
-                const bool ok = in && (unsigned)xx < (unsigned)D.W;
-                row[kx] = load_channels<VW>(dimg + (size_t)(ok ? y * D.W + xx : 0) * D.C);
+            for (int kx = 0; kx < 5; ++kx)
 #pragma unroll
-                for (int v = 0; v < VW; ++v) row[kx].v[v] = ok ? row[kx].v[v] : 0.f;
-            }
+                for (int v = 0; v < VW; ++v) row[kx].v[v] = in && xok[kx] ? from[kx].v[v] : 0.f;
+        };
+        Channels<VW> win[5][5], next[5], nv, nd = {};
+        auto request = [&](int y) {              // what step y needs
+            load_row(y + 2, next);
+            const size_t tok = b * D.N + (size_t)min(y, D.H - 1) * D.W + x;
+            nv = load_channels<VW>(V + tok * ldv + c);
+            if (ADDS) nd = load_channels<VW>(dV + tok * lddv + c);
         };
 #pragma unroll
         for (int r = 0; r < 4; ++r) load_row(y0 + r - 2, win[r]);
+        request(y0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) blank(y0 + r - 2, win[r], win[r]);
         for (int yb = y0; yb < y1; yb += 5) {
 #pragma unroll
             for (int u = 0; u < 5; ++u) {
                 const int y = yb + u;
                 if (y >= y1) break;
-                load_row(y + 2, win[(u + 4) % 5]);
+                blank(y + 2, next, win[(u + 4) % 5]);
                 const size_t tok = b * D.N + (size_t)y * D.W + x;
-                const Channels<VW> vc = load_channels<VW>(V + tok * ldv + c);
-                Channels<VW> dv = {};
-                if (ADDS) dv = load_channels<VW>(dV + tok * lddv + c);
+                const Channels<VW> vc = nv;
+                Channels<VW> dv = nd;
+                request(y + 1);
 #pragma unroll
                 for (int r = 0; r < 5; ++r)
 #pragma unroll
