@@ -822,7 +822,7 @@ __global__ __launch_bounds__(NL == 4 ? 256 : 1024, 4) void k_attention_out(const
 // the maximum m, l = sum e, O~ = sum e V and D~ = sum e dP (dP^T = V dO^T); at its end O, D = D~ / l and
 // lse = log2(l) + scale log2(e) m are final.  Second sweep: P = exp2(scale log2(e) s - lse),
 // dS = P (dP - D), dQ^T += K^T dS^T.  A single key block (k n <= KB) is not taken twice.
-template <int DP, int HPW, bool VEC, int KB>
+template <int DP, int HPW, bool VEC>
 __global__ __launch_bounds__(256) void k_attn_bwd_q(const float *__restrict__ QKV, const float *__restrict__ dO,
                                                     const int32_t *__restrict__ Ir, float *__restrict__ O,
                                                     float *__restrict__ dQKV, float *__restrict__ lse,
@@ -830,7 +830,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_q(const float *__restrict__ QK
                                                     lce::GradJob<float> J, int lce_blocks)
 {
     typedef AttnShape<DP, HPW> L;
-    constexpr int P = L::P, CW = L::CW, KT = KB / 16, NS = DP / 16, kFloats = 2 * KB * P > 25 * 256 ? 2 * KB * P : 25 * 256;
+    constexpr int P = L::P, CW = L::CW, KB = L::KB, KT = KB / 16, NS = DP / 16, kFloats = 2 * KB * P > 25 * 256 ? 2 * KB * P : 25 * 256;
     __shared__ __attribute__((aligned(16))) float lds[kFloats];
     float *Ks = lds, *Vs = lds + KB * P;
     int wg, wgs;

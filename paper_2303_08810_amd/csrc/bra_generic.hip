@@ -9,7 +9,7 @@
 // than 64 channels and the block's LayerNorms are scalar kernels.
 // Region pooling uses mean(X^r) W = mean(X^r W), which is exact in real arithmetic
 // (the mean is linear; same argument as Appendix A).
-#include "bra_f32_dev.h"
+#include "bra_f32_heads_dev.h"
 #include "bra_route_dev.h"
 
 #include <algorithm>
@@ -629,9 +629,11 @@ SharePlan share_plan(long M, int C)
     return {(int)((steps + per - 1) / per), (int)(per * 32)};
 }
 
-// Channels per thread of the passes: those of the attention kernels that carry them (4-channel loads: two).  Two workgroups
+// Which gradients k_heads_bwd_q and k_heads_bwd_kv take.  Channels per thread of the passes: those of the attention kernels that carry them (one with
+// these, else two with 4-channel loads).  Two workgroups
 // per compute unit (29 x 28 x 28 x 96: whole gradient 176 us, 182 with three).
-lce::LcePlan lce_grad_plan(const Dims &D) { return lce::lce_plan(D, 512, D.d % 4 == 0 ? 8 : 4); }
+bool by_heads(const Dims &D) { return D.n <= 32 && D.d <= 32; }
+lce::LcePlan lce_grad_plan(const Dims &D) { return lce::lce_plan(D, 512, D.d % 4 == 0 && !by_heads(D) ? 8 : 4); }
 
 struct BwdWs {
     float *qkv, *o, *dO, *dqkv, *lse, *dsum, *part_qkv, *part_o, *part_lce;
@@ -671,41 +673,73 @@ int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lc
     const bool by_image = gradients_by_image(D, hgroups, blocks);
     // The passes of the depth-wise convolution's gradients lie behind the workgroups of the attention: the one with the tap
     // gradients beside the query side, which leaves dV to be added to by the key side, O += LCE(V) beside the key side.  In
-    // front of the query side it was slower (4 x 56 x 56 x 64, k = 2: 100.9 us behind, 105.6 in front; 8 x 28 x 28 x 128: 92.0, 95.5).
+    // front of the query side it was slower (4 x 56 x 56 x 64, k = 2: 100.9 us behind, 105.6 in front).
     const float *V = w.qkv + 2 * D.C;
     const lce::GradJob<float> grad = {w.dO, V, taps, w.dqkv + 2 * D.C, w.part_lce, 3 * D.C, 3 * D.C, lce_grad_plan(D)};
     const lce::AddJob<float> add = lce::add_job<float>(D, V, 3 * D.C, taps, w.o, D.C, VEC ? 2 : 1, 256);
     if (blocks + std::max(grad.p.blocks(), add.blocks) > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    auto query_side = [&](auto kb) {
-        hipLaunchKernelGGL((f32::k_attn_bwd_q<DP, HPW, VEC, decltype(kb)::value>), dim3((unsigned)(blocks + grad.p.blocks())), dim3(256), 0, st,
-                           w.qkv, w.dO, Ir, w.o, w.dqkv, w.lse, w.dsum, D, hgroups, tiles, by_image, grad, grad.p.blocks());
-    };
-    constexpr int KB = f32::AttnShape<DP, HPW>::KB;
-    // 33 to 64 routed keys as a single block of 64, so that they are not taken twice (8 x 28 x 28 x 128, k = 4: 91.5 -> 88.1 us; 29 x
-    // 28 x 28 x 96 bf16, k = 3: 164.8 -> 152.9; 16 x 14 x 14 x 256, k = 16: 165.5 -> 150.3); more keys in two sweeps of such blocks
-    // were slower (16 x 14 x 14 x 256, k = 20: 190 -> 208), and so were heads of 64 channels (8 x 16 x 16 x 192: 82.1 -> 84.2).
-    if constexpr (DP == 32 && KB == 32) {
-        if (D.kn > 32 && D.kn <= 64) query_side(std::integral_constant<int, 64>{});
-        else query_side(std::integral_constant<int, 32>{});
-    } else {
-        query_side(std::integral_constant<int, KB>{});
-    }
+    hipLaunchKernelGGL((f32::k_attn_bwd_q<DP, HPW, VEC>), dim3((unsigned)(blocks + grad.p.blocks())), dim3(256), 0, st, w.qkv, w.dO, Ir, w.o, w.dqkv, w.lse,
+                       w.dsum, D, hgroups, tiles, by_image, grad, grad.p.blocks());
     hipLaunchKernelGGL((f32::k_attn_bwd_kv<DP, HPW, VEC>), dim3((unsigned)(blocks + add.blocks)), dim3(256), 0, st, w.qkv, w.dO, Ir, w.lse,
                        w.dsum, w.dqkv, D, hgroups, tiles, by_image, add, add.blocks);
     if (!launched()) return BRA_ERR_LAUNCH;
     return add.blocks ? BRA_OK : lce::launch_lce<float>(D, V, 3 * D.C, taps, w.o, D.C, K_GEN_BACKWARD, st);
 }
 
+// Wavefronts that share a head of a region: four or two while there are at most `most` of them, else the fewest that fill a workgroup.  They hide
+// a chain of rows, and the query side's sums meet twice, so that it turns earlier.  us, query side / key side with 1, 2, 4 per head:
+// 588 heads of regions (4 x 14 x 28 x 96, k = 16) 18.1, 15.7, 13.8 / 16.5, 14.1, 11.5; 1568 (8 x 28 x 28 x 128, k = 4) 18.1, 22.0, 25.4 / 21.1, 16.8, 20.8;
+// 3072 (3 x 32 x 32 x 128, S = 16, k = 11) 19.9, 23.3, 28.6 / 24.2, 29.6, 41.4.
+constexpr long kQueryShare = 2400, kKeyShare = 3200;
+
+int head_share(const Dims &D, long most)
+{
+    const long heads = (long)D.B * D.R * D.heads;
+    const int least = D.heads >= 3 ? 1 : D.heads == 2 ? 2 : 4;       // a workgroup has four wavefronts
+    return heads <= most / 4 ? 4 : heads <= most / 2 ? std::max(2, least) : least;
+}
+
+template <int NT, bool VEC>
+int launch_heads_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, const lce::Taps &taps, hipStream_t st)
+{
+    const float *V = w.qkv + 2 * D.C;
+    const lce::GradJob<float> grad = {w.dO, V, taps, w.dqkv + 2 * D.C, w.part_lce, 3 * D.C, 3 * D.C, lce_grad_plan(D)};
+    const lce::AddJob<float> add = lce::add_job<float>(D, V, 3 * D.C, taps, w.o, D.C, VEC ? 2 : 1, 256);
+    // workgroups of a side with `share` wavefronts per head
+    auto groups = [&](int share) { return (D.heads + 4 / share - 1) / (4 / share); };
+    auto blocks = [&](int share) { return ((long)D.B * D.R * groups(share) + 7) / 8 * 8; };
+    const int of_query = head_share(D, kQueryShare), of_key = head_share(D, kKeyShare);
+    if (blocks(std::max(of_query, of_key)) + std::max(grad.p.blocks(), add.blocks) > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
+    auto query_side = [&](auto share) {
+        constexpr int W = decltype(share)::value;
+        hipLaunchKernelGGL((f32::k_heads_bwd_q<NT, W, VEC>), dim3((unsigned)(blocks(W) + grad.p.blocks())), dim3(256), 0, st, w.qkv, w.dO, Ir, w.o, w.dqkv,
+                           w.lse, w.dsum, D, groups(W), gradients_by_image(D, groups(W), blocks(W)), grad, grad.p.blocks());
+    };
+    auto key_side = [&](auto share) {
+        constexpr int W = decltype(share)::value;
+        hipLaunchKernelGGL((f32::k_heads_bwd_kv<NT, W, VEC>), dim3((unsigned)(blocks(W) + add.blocks)), dim3(256), 0, st, w.qkv, w.dO, Ir, w.lse, w.dsum,
+                           w.dqkv, D, groups(W), gradients_by_image(D, groups(W), blocks(W)), add, add.blocks);
+    };
+    auto launch = [&](int share, auto side) {
+        if (share == 4) side(std::integral_constant<int, 4>{});
+        else if (share == 2) side(std::integral_constant<int, 2>{});
+        else side(std::integral_constant<int, 1>{});
+    };
+    launch(of_query, query_side);
+    launch(of_key, key_side);
+    if (!launched()) return BRA_ERR_LAUNCH;
+    return add.blocks ? BRA_OK : lce::launch_lce<float>(D, V, 3 * D.C, taps, w.o, D.C, K_GEN_BACKWARD, st);
+}
+
 int launch_attn_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, const lce::Taps &taps, hipStream_t st)
 {
-    const int hpw = heads_per_group(D);
     const bool vec = D.d % 4 == 0;
-    if (D.d <= 32) {
-        if (hpw == 4) return vec ? launch_attn_bwd_t<32, 4, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<32, 4, false>(D, w, Ir, taps, st);
-        if (hpw == 2) return vec ? launch_attn_bwd_t<32, 2, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<32, 2, false>(D, w, Ir, taps, st);
-        return vec ? launch_attn_bwd_t<32, 1, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<32, 1, false>(D, w, Ir, taps, st);
+    if (by_heads(D)) {
+        if (D.n <= 16) return vec ? launch_heads_bwd<1, true>(D, w, Ir, taps, st) : launch_heads_bwd<1, false>(D, w, Ir, taps, st);
+        return vec ? launch_heads_bwd<2, true>(D, w, Ir, taps, st) : launch_heads_bwd<2, false>(D, w, Ir, taps, st);
     }
-    if (hpw >= 2) return vec ? launch_attn_bwd_t<64, 2, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<64, 2, false>(D, w, Ir, taps, st);
+    if (D.d <= 32) return vec ? launch_attn_bwd_t<32, 1, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<32, 1, false>(D, w, Ir, taps, st);
+    if (heads_per_group(D) >= 2) return vec ? launch_attn_bwd_t<64, 2, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<64, 2, false>(D, w, Ir, taps, st);
     return vec ? launch_attn_bwd_t<64, 1, true>(D, w, Ir, taps, st) : launch_attn_bwd_t<64, 1, false>(D, w, Ir, taps, st);
 }
 
