@@ -292,19 +292,22 @@ struct Job {
     __host__ __device__ long blocks() const { return (groups() * cblocks + 7) / 8 * 8; }
 };
 
-// LDS of job_block and taps_block: the tap gradients of 256 threads, kTapsAtOnce of them at a time.
-constexpr int kTapsAtOnce = 13;
+// LDS of job_block: the tap gradients of 256 threads.  taps_block: half of them at a time (a whole call of 1 x 21 x 21 x 384, where these
+// sums come last, takes 0.3 us more so).
 template <bool GRAD>
-constexpr size_t job_bytes() { return GRAD ? kTapsAtOnce * 256 * 4 : kTapBytes; }
+constexpr size_t job_bytes() { return GRAD ? 25 * 256 * 4 : kTapBytes; }
+constexpr int kTapsAtOnce = 13;
+constexpr size_t kTapSumBytes = kTapsAtOnce * 256 * 4;
 
-// The 8 slots' sums of a channel through LDS, added in a fixed order, to Part[grp].
+// The 8 slots' sums of a channel through LDS, AT_ONCE taps at a time, added in a fixed order, to Part[grp].
+template <int AT_ONCE>
 __device__ __forceinline__ void store_tap_sums(const Job &J, const Dims &D, int grp, int c0, const float (&acc)[25][2], float *red)
 {
 #pragma unroll
     for (int v = 0; v < 2; ++v)
 #pragma unroll
-        for (int t0 = 0; t0 < 25; t0 += kTapsAtOnce) {
-            const int count = 25 - t0 < kTapsAtOnce ? 25 - t0 : kTapsAtOnce;
+        for (int t0 = 0; t0 < 25; t0 += AT_ONCE) {
+            const int count = 25 - t0 < AT_ONCE ? 25 - t0 : AT_ONCE;
             __syncthreads();
 #pragma unroll
             for (int t = 0; t < count; ++t) red[t * 256 + threadIdx.x] = acc[t0 + t][v];
@@ -337,7 +340,7 @@ __device__ __forceinline__ void job_block(const Job &J, const Dims &D, int block
     for (int t = 0; t < (GRAD ? 25 : 1); ++t) acc[t][0] = acc[t][1] = 0.f;
     if (GRAD) __syncthreads();
     for (long tile = first; tile < last; ++tile) walk_tile<GRAD, ADDS>(J.In, J.V, J.Out, J.Low, J.ldo, D, J.T, tile, slot, c0, cl, live, w, acc);
-    if constexpr (GRAD) store_tap_sums(J, D, grp, c0, acc, red);
+    if constexpr (GRAD) store_tap_sums<25>(J, D, grp, c0, acc, red);
 }
 
 // The tap gradients alone, for one tile: a row of In at a time, with the window in V (5 rows of one pair per channel, instead of 5 rows of
@@ -416,7 +419,7 @@ __device__ __forceinline__ void taps_block(const Job &J, const Dims &D, int bloc
 #pragma unroll
     for (int t = 0; t < 25; ++t) acc[t][0] = acc[t][1] = 0.f;
     for (long tile = first; tile < last; ++tile) walk_taps(J.In, J.V, D, J.T, tile, threadIdx.x / 32, c0, cl, acc);
-    store_tap_sums(J, D, grp, c0, acc, red);
+    store_tap_sums<kTapsAtOnce>(J, D, grp, c0, acc, red);
 }
 
 // The two passes of the gradients: LCE^T(dO) with the tap gradients, added to dV or in float32 (lower halves where dK goes), and

@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256, MODE == kShared && NQ == 1 ? (LCE ? 4 : 3) : 2
     __shared__ __attribute__((aligned(16))) bf16_t lds[LCE ? R::buf : R::bufs * R::buf];
     constexpr int kPart = 64 * (3 + 4 * NDT);    // SPLIT: m, l, D and the sums of a wavefront, one query tile and head
     __shared__ __attribute__((aligned(16))) float sums[SPLIT ? NQ * HPW * 4 * kPart : 4];
-    static_assert(lce::job_bytes<true>() <= sizeof(lds), "the pass shares the buffers");
+    static_assert((LCE ? lce::kTapSumBytes : lce::job_bytes<true>()) <= sizeof(lds), "the pass shares the buffers");
     // LCE: the halo of V, then LCE(V) of the tokens; [k] or [4][k]: first token of the routed regions; with `walks` [n] or [4][n]: tokens of a region's slots
     extern __shared__ __attribute__((aligned(16))) int origin_tables[];
     int wg, wgs;
