@@ -13,7 +13,7 @@
 // k_attn_map / k_attn_map4 (a head's Q, K, V of a whole image in LDS, the LCE added from the
 // same V slice), else k_attn_small (attention output to memory) and k_lce_add (bra_lce.hip: adds
 // the LCE in place); then the projection kernel with W^o.
-#include "bra_lce_dev.h"
+#include "bra_lce_region.h"
 
 namespace bra {
 
@@ -386,9 +386,11 @@ struct MapWork {
     int slot_off;    // this lane's token within a routed region, the same way: key l is token l % n
     char *wave_mem;  // 512 bytes of this wavefront's own
     float *Ls;       // [N][kMapLcePitch]: LCE of the head's channels (variants that add it)
+    bf16_t *zero;    // 16 bytes of zeros behind it (the same variants)
 };
 
 // Stages the head's K / V slice and the image's routing index; false: no work.
+template <bool LCE>
 __device__ __forceinline__ bool map_stage(const AttnArgs &A, const Dims &D, int split, char *smem, MapWork &w)
 {
     constexpr int T = kMapThreads;
@@ -400,6 +402,8 @@ __device__ __forceinline__ bool map_stage(const AttnArgs &A, const Dims &D, int 
     w.first = w.rows + D.R * D.k;
     w.wave_mem = (char *)(w.rows + (D.R * D.k + D.R + 3) / 4 * 4) + (threadIdx.x / kWave) * 512;   // 16-byte aligned
     w.Ls = (float *)((char *)(w.rows + (D.R * D.k + D.R + 3) / 4 * 4) + kMapWaves * 512);
+    w.zero = (bf16_t *)(w.Ls + (size_t)D.N * kMapLcePitch);
+    if (LCE && threadIdx.x < 8) w.zero[threadIdx.x] = 0;
     const int wid = swizzled_block();       // the heads of an image share the memory lines of its K / V rows
     if (wid >= A.total) return false;
     const int part = wid % split;
@@ -450,49 +454,55 @@ __device__ __forceinline__ bool map_stage(const AttnArgs &A, const Dims &D, int 
     return true;
 }
 
-// LCE (Eq. 7) of the head's 32 channels over the whole image, from the V slice in LDS into
-// w.Ls (float32): thread = (channel pair, group); a group takes (image row, 4-token segment)
-// items, the 2 x 25 weights of the pair stay in registers.  Tokens outside the image are zero.
+// LCE (Eq. 7) of the head's 32 channels over the whole image, from the V slice in LDS into w.Ls (float32).
+// Bound by vector issue, so on the two-element dot product, from transposing reads: they give a lane four neighbouring columns of
+// one channel as the pairs that it takes.  An item is 4 x 4 outputs of 16 channels on 16 lanes, 8 rows of two reads, about 300
+// instructions; two channels of 4 outputs per lane on float32 multiply-adds, each token read and unpacked for itself, took
+// twice that per output (kernel at 64 x 14 x 14 x 256, k = 16 20.7 -> 17.6 us).  Pairs and taps, and so what an infinity reaches, are those of lce::halo_sums.
+// Tokens outside the image read w.zero.
 __device__ __forceinline__ void map_lce(const AttnArgs &A, const Dims &D, const MapWork &w)
 {
-    const int cpair = threadIdx.x % 16, grp = threadIdx.x / 16;
-    unsigned wl[25];        // [W(c, 0..24) | W(c + 1, 0..24)] as 25 packed pairs
+    const int s = threadIdx.x % 16, grp = threadIdx.x / 16, ch = 16 * (grp % 2) + s;      // a group keeps to one half of the channels
+    unsigned wt[5][3];
+    lce::LaneTaps<false>(A.Wlce, 32 * w.h + ch).operands(wt);
+    const int quads = (D.W + 3) / 4, items = quads * ((D.H + 3) / 4);
+    const float q_inv = 1.0f / (float)quads;
+    for (int first = 2 * (threadIdx.x / kWave); first < items; first += kMapThreads / 32) {      // the same for all lanes of a wavefront
+        const int mine = first + grp / 2 % 2, item = min(mine, items - 1);
+        const int strip = fast_div(item, q_inv), y0 = 4 * strip, x0 = 4 * (item - strip * quads);
+        const int xl = x0 - 2 + s / 4, col = 16 * (grp % 2) + 4 * (s % 4);
+        const bool left = xl >= 0 && xl < D.W, right = xl + 4 < D.W;
+        const bf16_t *at = w.Vs + ((y0 - 2) * D.W + xl) * kMapPitch + col;
+        float o[4][4];
 #pragma unroll
-    for (int e = 0; e < 25; ++e) wl[e] = *(const unsigned *)(A.Wlce + (size_t)(32 * w.h + 2 * cpair) * 25 + 2 * e);
-    auto tap = [&](int ch, int t) {
-        const int e = 25 * ch + t;
-        return (e & 1) ? bf16_hi(wl[e / 2]) : bf16_lo(wl[e / 2]);
-    };
-    const int segs = (D.W + 3) / 4;
-    for (int item = grp; item < D.H * segs; item += kMapThreads / 16) {
-        const int y = item / segs, x0 = (item % segs) * 4;
-        float a0[4] = {0.f, 0.f, 0.f, 0.f}, a1[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int ky = 0; ky < 5; ++ky) {
-            const int yy = y + ky - 2;
-            const bool row_ok = yy >= 0 && yy < D.H;
-            float v0[8], v1[8];
+            for (int c = 0; c < 4; ++c) o[a][c] = 0.f;
 #pragma unroll
-            for (int x = 0; x < 8; ++x) {
-                const int xx = x0 + x - 2;
-                const bool ok = row_ok && xx >= 0 && xx < D.W;
-                const unsigned u = *(const unsigned *)(w.Vs + (ok ? yy * D.W + xx : 0) * kMapPitch + 2 * cpair);
-                v0[x] = ok ? bf16_lo(u) : 0.f;
-                v1[x] = ok ? bf16_hi(u) : 0.f;
-            }
+        for (int y = 0; y < 8; ++y, at += D.W * kMapPitch) {
+            const bool in = (unsigned)(y0 + y - 2) < (unsigned)D.H;
+            const u32x2 v0 = __builtin_bit_cast(u32x2, lds_read_tr16(in && left ? at : w.zero));
+            const u32x2 v1 = __builtin_bit_cast(u32x2, lds_read_tr16(in && right ? at + 4 * kMapPitch : w.zero));
+            unsigned p[7] = {v0[0], 0u, v0[1], 0u, v1[0], 0u, v1[1]};       // columns (j, j + 1)
 #pragma unroll
-            for (int kx = 0; kx < 5; ++kx) {
-                const float w0 = tap(0, ky * 5 + kx), w1 = tap(1, ky * 5 + kx);
+            for (int j = 1; j < 7; j += 2) p[j] = __builtin_amdgcn_alignbit(p[j + 1], p[j - 1], 16);
 #pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    a0[x] = fmaf(w0, v0[x + kx], a0[x]);
-                    a1[x] = fmaf(w1, v1[x + kx], a1[x]);
+            for (int a = 0; a < 4; ++a) {
+                if (y < a || y > a + 4) continue;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    o[a][c] = dot2(wt[y - a][0], p[c], o[a][c]);
+                    o[a][c] = dot2(wt[y - a][1], p[c + 2], o[a][c]);
+                    o[a][c] = dot2(wt[y - a][2], p[c + 3], o[a][c]);
                 }
             }
         }
+        float *to = w.Ls + (y0 * D.W + x0) * kMapLcePitch + ch;
 #pragma unroll
-        for (int x = 0; x < 4; ++x)
-            if (x0 + x < D.W) *(f32x2 *)(w.Ls + (y * D.W + x0 + x) * kMapLcePitch + 2 * cpair) = f32x2{a0[x], a1[x]};
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (mine < items && y0 + a < D.H && x0 + c < D.W) to[(a * D.W + c) * kMapLcePitch] = o[a][c];
     }
     __syncthreads();
 }
@@ -508,7 +518,7 @@ __global__ __launch_bounds__(kMapThreads) void k_attn_map(AttnArgs A, bf16_t *__
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     MapWork w;
-    if (!map_stage(A, D, split, smem, w)) return;
+    if (!map_stage<LCE>(A, D, split, smem, w)) return;
     if (LCE) map_lce(A, D, w);
     const bf16_t *Ks = w.Ks, *Vs = w.Vs;
     int *tokw = (int *)w.wave_mem;
@@ -579,7 +589,7 @@ __global__ __launch_bounds__(kMapThreads) void k_attn_map4(AttnArgs A, bf16_t *_
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     MapWork w;
-    if (!map_stage(A, D, split, smem, w)) return;
+    if (!map_stage<LCE>(A, D, split, smem, w)) return;
     if (LCE) map_lce(A, D, w);
     const bf16_t *Ks = w.Ks, *Vs = w.Vs;
     bf16_t *Pw = (bf16_t *)w.wave_mem;          // [64 keys][4 queries]
@@ -696,7 +706,7 @@ static bool one_kernel(const Dims &D)
 static size_t map_smem(const Dims &D, bool lce = false)
 {
     return (size_t)3 * D.N * kMapPitch * 2 + (size_t)((D.R * D.k + D.R + 3) / 4 * 4) * 4 + kMapWaves * 512 +
-           (lce ? (size_t)D.N * kMapLcePitch * 4 : 0);
+           (lce ? (size_t)D.N * kMapLcePitch * 4 + 16 : 0);
 }
 
 // The LCE rides along in the attention kernel when its float32 tile fits and does not cost
