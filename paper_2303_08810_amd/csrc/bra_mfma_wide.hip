@@ -346,23 +346,27 @@ __global__ __launch_bounds__((64 * genWaves<HD, HPW>), HD == 32 && HPW == 1 ? 4 
 // ---------------------------------------------------------------------------
 // The same for regions of at most 32 tokens (16 NQ of them in NQ query tiles), where the tile of 64 queries above leaves
 // half or more of its wavefronts with copies: a wavefront works on its own, with all queries of a region and 64 channels
-// (2 or 1 heads), any four of them in a workgroup.  It brings its K and V rows straight from memory into its own part of LDS, 32 keys at a time into one
-// of two buffers while the other is worked on; there is no barrier.  Rows of 128 bytes lie unpadded, their pieces
-// exchanged as above.
+// (2 or 1 heads), any four of them in a workgroup.  It brings its K and V rows straight from memory into its own part of LDS, 32 keys at a time;
+// a block's operands go to registers, and the block that takes its place is requested before it is worked on (with two buffers: the other one).  There is no barrier.  Rows of 128
+// bytes lie unpadded, their pieces exchanged as above.
 // Bound by the gather out of the L2s: 302 MB for 8 images of 32 x 32 x 768 with 12 regions of 16 tokens each; with few keys by
-// the chain of loads before the first product (routing entry, row, output) and the wavefronts that hide it: the second buffer
-// is left out for up to 32 keys, so that four workgroups share a compute unit instead of two, and what the output is added to
+// the chain of loads before the first product (routing entry, row, output) and the wavefronts that hide it, so that what the output is added to
 // and the queries are requested with the routing entries (64 x 16 x 24 x 384, k = 1: attention 51.7 -> 31.9 us, layer 146 ->
 // 126; 32 x 16 x 16 x 768, k = 2: 49.1 -> 29.7; 29 x 8 x 8 x 768, k = 33: 46.1 -> 40.3).
+// One buffer of 32 keys, so that four workgroups share a compute unit, where there are wavefronts for it; two, one ahead, where two per unit
+// take them all (kRowsShared) or registers leave no room for more (NQ = 2).  Layer, two buffers / one (us): 8 x 32 x 32 x 768, k = 12
+// 97.4 / 94.6, 4 images of 24 heads 62.6 / 60.5, 16 x 21 x 21 x 512, k = 20 72.8 / 67.0, 32 x 14 x 28 x 512, k = 6 98.3 / 93.8, 8 x 28 x 28 x 384, k = 9
+// 43.0 / 41.0; few: 2 x 32 x 32 x 768, k = 12 (1536 wavefronts) 45.6 / 45.9, 3 x 28 x 28 x 768, k = 6 44.0 / 44.3.
+constexpr int kRowsShared = 2048;
 constexpr int kRowsBuffer = 4 * 2 * 32 * 64 * 2;       // bytes
 
-template <int HD, int NQ>
-__global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int items, const bf16_t *__restrict__ Low)
+template <int HD, int NQ, int BUFFERS>
+__global__ __launch_bounds__(256, NQ == 2 || BUFFERS == 2 ? 2 : 4) void k_attn_rows(AttnArgs A, bf16_t *__restrict__ O, Dims D, int items, const bf16_t *__restrict__ Low)
 {
     constexpr int HPW = 64 / HD, KSD = HD / 32, NDT = HD / 16, KB = 32;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    bf16_t *S0 = (bf16_t *)smem, *S1 = S0 + (D.kn > KB ? kRowsBuffer / 2 : 0);       // [wavefront][K, V][32 keys][64]
-    int *origin_tables = (int *)((char *)S1 + kRowsBuffer);      // [4][k]: first token of the routed regions; [4][32]: tokens of a region's slots
+    bf16_t *S = (bf16_t *)smem;      // [buffer][wavefront][K, V][32 keys][64]
+    int *origin_tables = (int *)(smem + BUFFERS * kRowsBuffer);      // [4][k]: first token of the routed regions; [4][32]: tokens of a region's slots
     const int C = D.C, ncg = C / 64, n = D.n, kn = D.kn;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, g = lane / 16, i = lane % 16;
     const int item = __builtin_amdgcn_readfirstlane(4 * swizzled_block() + wave);      // those of an image share an L2
@@ -413,14 +417,14 @@ __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__rest
     // direct loads: 8 rows of 8 pieces each, block after block
     RowWalk<KB / 8> walk;
     walk.start(lane / 8, 8, KB, n, n_inv);
-    const unsigned piece = 16 * ((lane % 8) ^ (lane / 8)), mine[2] = {lds_address(S0 + wave * 2 * KB * 64), lds_address(S1 + wave * 2 * KB * 64)};
-    auto request = [&](unsigned at) {
+    const unsigned piece = 16 * ((lane % 8) ^ (lane / 8)), mine = lds_address(S + wave * 2 * KB * 64);
+    auto request = [&](int at) {
         lds_reads_done();
 #pragma unroll
         for (int u = 0; u < KB / 8; ++u) {
             const unsigned off = row_offset(walk.token(u, origins, D.k - 1, slots), C, piece);
-            load_to_lds_untracked(A.K + img, off, at + 1024 * u);
-            load_to_lds_untracked(A.V + img, off, at + KB * 128 + 1024 * u);
+            load_to_lds_untracked(A.K + img, off, mine + at + 1024 * u);
+            load_to_lds_untracked(A.V + img, off, mine + at + KB * 128 + 1024 * u);
         }
         walk.advance();
     };
@@ -434,59 +438,74 @@ __global__ __launch_bounds__(256, 2) void k_attn_rows(AttnArgs A, bf16_t *__rest
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-    auto block = [&](int k0, const bf16_t *S, auto first) {
-        const bf16_t *Ks = S + wave * 2 * KB * 64, *Vs = Ks + KB * 64;
+    auto read = [&](int buffer, int hh, bf16x8 (&kf)[2][KSD], bf16x8 (&vf)[NDT]) {
+        const bf16_t *Ks = S + buffer * (kRowsBuffer / 2) + wave * 2 * KB * 64, *Vs = Ks + KB * 64;
 #pragma unroll
-        for (int hh = 0; hh < HPW; ++hh) {
-            bf16x8 kf[2][KSD], vf[NDT];
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int ks = 0; ks < KSD; ++ks) kf[t][ks] = row_operand(Ks, 16 * t + i, HD / 8 * hh + 4 * ks + g);
 #pragma unroll
-                for (int ks = 0; ks < KSD; ++ks) kf[t][ks] = row_operand(Ks, 16 * t + i, HD / 8 * hh + 4 * ks + g);
+        for (int dt = 0; dt < NDT; ++dt) vf[dt] = column_operand(Vs, 0, HD * hh + 16 * dt, g, i);
+    };
+    auto work = [&](int k0, int hh, const bf16x8 (&kf)[2][KSD], const bf16x8 (&vf)[NDT], auto first) {
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt) vf[dt] = column_operand(Vs, 0, HD * hh + 16 * dt, g, i);
+        for (int q = 0; q < NQ; ++q) {
+            f32x4 s[2];
+            const float neg = -m[q][hh];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                f32x4 s[2];
-                const float neg = -m[q][hh];
+            for (int t = 0; t < 2; ++t) {
+                s[t] = f32x4{neg, neg, neg, neg};
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    s[t] = f32x4{neg, neg, neg, neg};
-#pragma unroll
-                    for (int ks = 0; ks < KSD; ++ks) s[t] = mfma16(kf[t][ks], qf[q][hh][ks], s[t]);   // S^T[key 16 t + 4 g + j][query i]
-                }
-                if (k0 + KB > kn) {
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (k0 + 16 * t + 4 * g + j >= kn) s[t][j] = -INFINITY;
-                }
-                bf16x8 pb[1];
-                softmax_step<decltype(first)::value>(s, m[q][hh], l[q][hh], acc[q][hh], pb);
-#pragma unroll
-                for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = mfma16(vf[dt], pb[0], acc[q][hh][dt]);
+                for (int ks = 0; ks < KSD; ++ks) s[t] = mfma16(kf[t][ks], qf[q][hh][ks], s[t]);   // S^T[key 16 t + 4 g + j][query i]
             }
+            if (k0 + KB > kn) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (k0 + 16 * t + 4 * g + j >= kn) s[t][j] = -INFINITY;
+            }
+            bf16x8 pb[1];
+            softmax_step<decltype(first)::value>(s, m[q][hh], l[q][hh], acc[q][hh], pb);
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) acc[q][hh][dt] = mfma16(vf[dt], pb[0], acc[q][hh][dt]);
         }
     };
-    // requests the keys from k0 on, if there are any, and waits for the 8 loads of the block before
-    auto advance = [&](int k0, unsigned at) {
-        if (k0 < kn) {
-            request(at);
-            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        } else {
+    request(0);
+    if constexpr (BUFFERS == 1) {
+        auto block = [&](int k0, auto first) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            bf16x8 kf[HPW][2][KSD], vf[HPW][NDT];
+#pragma unroll
+            for (int hh = 0; hh < HPW; ++hh) read(0, hh, kf[hh], vf[hh]);
+            if (k0 + KB < kn) request(0);
+#pragma unroll
+            for (int hh = 0; hh < HPW; ++hh) work(k0, hh, kf[hh], vf[hh], first);
+        };
+        block(0, std::true_type{});
+        for (int k0 = KB; k0 < kn; k0 += KB) block(k0, std::false_type{});
+    } else {
+        // requests the keys behind the block, if there are any, and waits for the 8 loads of the block itself
+        auto block = [&](int k0, int buffer, auto first) {
+            if (k0 + KB < kn) {
+                request((buffer ^ 1) * kRowsBuffer);
+                asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+            } else {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+#pragma unroll
+            for (int hh = 0; hh < HPW; ++hh) {
+                bf16x8 kf[2][KSD], vf[NDT];
+                read(buffer, hh, kf, vf);
+                work(k0, hh, kf, vf, first);
+            }
+        };
+        block(0, 0, std::true_type{});
+        for (int k0 = KB; k0 < kn; k0 += 2 * KB) {
+            block(k0, 1, std::false_type{});
+            if (k0 + KB >= kn) break;
+            block(k0 + KB, 0, std::false_type{});
         }
-    };
-    request(mine[0]);
-    advance(KB, mine[1]);
-    block(0, S0, std::true_type{});
-    for (int k0 = KB; k0 < kn; k0 += 2 * KB) {
-        advance(k0 + KB, mine[0]);
-        block(k0, S1, std::false_type{});
-        if (k0 + KB >= kn) break;
-        advance(k0 + 2 * KB, mine[1]);
-        block(k0 + KB, S0, std::false_type{});
     }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -580,18 +599,25 @@ bool means_from_projection(const Dims &D)
     return values <= (D.n > 32 && D.n < 60 ? 2L << 20 : 4L << 20);
 }
 
+template <int HD, int NQ, int BUFFERS>
+int launch_attn_rows_b(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, int items, hipStream_t st)
+{
+    const int blocks = (items + 3) / 4;
+    const size_t smem = (size_t)BUFFERS * kRowsBuffer + (size_t)4 * (D.k + 32) * sizeof(int);
+    static bool opted = false;
+    if (!opted && smem > 64 * 1024) {
+        if (hipFuncSetAttribute((const void *)k_attn_rows<HD, NQ, BUFFERS>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess) return BRA_ERR_LAUNCH;
+        opted = true;
+    }
+    hipLaunchKernelGGL((k_attn_rows<HD, NQ, BUFFERS>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), smem, st, A, O, D, items, Low);
+    return BRA_OK;
+}
+
 template <int HD, int NQ>
 int launch_attn_rows_t(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
 {
-    const int items = D.B * D.R * (D.C / 64), blocks = (items + 3) / 4;
-    const size_t smem = (size_t)(D.kn > 32 ? 2 : 1) * kRowsBuffer + (size_t)4 * (D.k + 32) * sizeof(int);
-    static bool opted = false;
-    if (!opted && smem > 64 * 1024) {
-        if (hipFuncSetAttribute((const void *)k_attn_rows<HD, NQ>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess) return BRA_ERR_LAUNCH;
-        opted = true;
-    }
-    hipLaunchKernelGGL((k_attn_rows<HD, NQ>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), smem, st, A, O, D, items, Low);
-    return BRA_OK;
+    const int items = D.B * D.R * (D.C / 64);
+    return D.kn > 32 && (NQ == 2 || items <= kRowsShared) ? launch_attn_rows_b<HD, NQ, 2>(D, A, O, Low, items, st) : launch_attn_rows_b<HD, NQ, 1>(D, A, O, Low, items, st);
 }
 
 int launch_attn_rows(const Dims &D, const AttnArgs &A, bf16_t *O, const bf16_t *Low, hipStream_t st)
