@@ -102,10 +102,11 @@ struct MeansJob {
     float n_inv, R_inv, S_inv, rw_inv;
 };
 
-// The token of row `row` of tile `tile`, or -1.
+// The token of row `row` of tile `tile` (BM rows), or -1.
+template <int BM = kGemmBM>
 __device__ __forceinline__ int region_row(const MeansJob &g, int tile, int row)
 {
-    const int per = mfma::fast_div(kGemmBM, g.n_inv), first = tile * per, b0 = (unsigned)first / (unsigned)g.R, r0 = first - b0 * g.R;
+    const int per = mfma::fast_div(BM, g.n_inv), first = tile * per, b0 = (unsigned)first / (unsigned)g.R, r0 = first - b0 * g.R;
     const int j = mfma::fast_div(row, g.n_inv), t = row - j * g.n;
     if (j >= per || first + j >= g.regions) return -1;
     const int over = mfma::fast_div(r0 + j, g.R_inv), reg = r0 + j - over * g.R;
@@ -450,6 +451,136 @@ __global__ __launch_bounds__(256) void k_gemm_both(GemmJob<T, T, float> J0, Gemm
     __shared__ __attribute__((aligned(16))) float smem[n0 > n1 ? n0 : n1];
     if ((int)blockIdx.x < blocks0) any_gemm_tile<false, VEC, BN>(J0, blockIdx.x, blocks0, smem);
     else any_gemm_tile<true, VEC, BN>(J1, (int)blockIdx.x - blocks0, (int)gridDim.x - blocks0, smem);
+}
+
+// Few rows: a tile of 16 RT rows x 32 columns per workgroup, whose wavefronts share the contraction and add up through LDS in a fixed
+// order.  The tiles above leave most of the chip idle there and walk the whole contraction with one wavefront per SIMD, 0.75 us for
+// 32 of it; here operands come straight from memory, four steps of 16 ahead, and nothing is waited for in between.
+// Whole tiles of columns and of steps (N % 32 = K % 16 = 0).  BT, MEANS: as above (n <= 16 RT).
+constexpr int kSplitPitch = 36;          // floats per row of partial sums
+template <int RT, int WAVES>
+constexpr size_t split_lds_floats() { return (size_t)WAVES * 16 * RT * kSplitPitch; }
+
+template <bool BT, int RT, int WAVES, bool MEANS = false>
+__device__ __forceinline__ void split_tile(const GemmJob<float, float, float> &J, int block, float *smem, const MeansJob *means = nullptr, int *rows = nullptr)
+{
+    constexpr int BM = 16 * RT, AHEAD = 4, P = kSplitPitch;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int ntiles = J.N / 32, tile = block / ntiles, n0 = 32 * (block - tile * ntiles);
+    const long m0 = (long)tile * BM;
+    if constexpr (MEANS) {
+        if (tid < BM) rows[tid] = region_row<BM>(*means, tile, tid);
+        __syncthreads();
+    }
+    const int steps = J.K / 16, s0 = steps * wave / WAVES, s1 = steps * (wave + 1) / WAVES;
+    const float *a[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) a[rt] = J.A + (MEANS ? (long)max(rows[16 * rt + i], 0) : min(m0 + 16 * rt + i, J.M - 1)) * J.lda + 4 * g;
+    const float *b = BT ? J.Bm + (long)(n0 + i) * J.ldb + 4 * g : J.Bm + (long)(4 * g) * J.ldb + n0 + 2 * i;
+    const long bstep = BT ? 16 : 16L * J.ldb;
+    f32x4 ra[2][AHEAD][RT], rb[2][AHEAD][2];     // [t]: k 4 g .. 4 g + 3 of column 16 t + i (BT) or 2 i + t
+    auto fetch = [&](int s, f32x4 (&x)[AHEAD][RT], f32x4 (&w)[AHEAD][2]) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int at = min(s + u, steps - 1);        // past the end: not used
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) x[u][rt] = *(const f32x4 *)(a[rt] + 16 * at);
+            const float *p = b + at * bstep;
+            if (BT) {
+                w[u][0] = *(const f32x4 *)p;
+                w[u][1] = *(const f32x4 *)(p + 16L * J.ldb);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const f32x2 v = *(const f32x2 *)(p + (long)e * J.ldb);
+                    w[u][0][e] = v[0];
+                    w[u][1][e] = v[1];
+                }
+            }
+        }
+    };
+    f32x4 acc[RT][2];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) acc[rt][0] = acc[rt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto work = [&](int s, const f32x4 (&x)[AHEAD][RT], const f32x4 (&w)[AHEAD][2]) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            if (s + u >= s1) break;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) acc[rt][t] = mfma_f32(w[u][t][e], x[u][rt][e], acc[rt][t]);
+        }
+    };
+    if (s0 < s1) fetch(s0, ra[0], rb[0]);
+    for (int s = s0; s < s1; s += 2 * AHEAD) {
+        if (s + AHEAD < s1) fetch(s + AHEAD, ra[1], rb[1]);
+        work(s, ra[0], rb[0]);
+        if (s + AHEAD >= s1) break;
+        if (s + 2 * AHEAD < s1) fetch(s + 2 * AHEAD, ra[0], rb[0]);
+        work(s + AHEAD, ra[1], rb[1]);
+    }
+    float *mine = smem + wave * BM * P;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        float *to = mine + (16 * rt + i) * P;
+        const f32x4 v0 = acc[rt][0], v1 = acc[rt][1];
+        *(f32x4 *)(to + (BT ? 4 * g : 8 * g)) = BT ? v0 : f32x4{v0[0], v1[0], v0[1], v1[1]};
+        *(f32x4 *)(to + (BT ? 16 + 4 * g : 8 * g + 4)) = BT ? v1 : f32x4{v0[2], v1[2], v0[3], v1[3]};
+    }
+    __syncthreads();
+    for (int e = tid; e < 8 * BM; e += 64 * WAVES) {
+        const int row = e / 8, n = n0 + 4 * (e % 8);
+        float *at = smem + row * P + 4 * (e % 8);
+        f32x4 v = *(const f32x4 *)at;
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) v += *(const f32x4 *)(at + w * BM * P);
+        if (MEANS) *(f32x4 *)at = v;
+        const long m = MEANS ? (long)rows[row] : m0 + row;
+        if ((MEANS ? m < 0 : m >= J.M) || (MEANS && !J.Out)) continue;
+        if (J.bias) v += *(const f32x4 *)(J.bias + n);
+        if (J.gelu) v = f32x4{gelu_f32(v[0]), gelu_f32(v[1]), gelu_f32(v[2]), gelu_f32(v[3])};
+        if (J.res) v += *(const f32x4 *)(J.res + m * J.ldo + n);
+        *(f32x4 *)(J.Out + m * J.ldo + n) = v;
+    }
+    if constexpr (MEANS) {
+        if (n0 >= means->cols) return;
+        __syncthreads();
+        const int n = means->n, per = mfma::fast_div(BM, means->n_inv), first = tile * per;
+        for (int e = tid; e < 8 * per; e += 64 * WAVES) {
+            const int j = e / 8;
+            if (first + j >= means->regions) break;
+            const float *at = smem + j * n * P + 4 * (e % 8);
+            f32x4 sum = *(const f32x4 *)at;
+            for (int t = 1; t < n; ++t) sum += *(const f32x4 *)(at + t * P);
+            *(f32x4 *)(means->Means + (size_t)(first + j) * means->cols + n0 + 4 * (e % 8)) = sum * means->n_inv;
+        }
+    }
+}
+
+template <bool BT, int RT>
+__global__ __launch_bounds__(512) void k_gemm_split(GemmJob<float, float, float> J)
+{
+    __shared__ __attribute__((aligned(16))) float smem[split_lds_floats<RT, 8>()];
+    split_tile<BT, RT, 8>(J, blockIdx.x, smem);
+}
+
+template <int RT>
+__global__ __launch_bounds__(512) void k_gemm_means_split(GemmJob<float, float, float> J, MeansJob means)
+{
+    __shared__ __attribute__((aligned(16))) float smem[split_lds_floats<RT, 8>()];
+    __shared__ int rows[16 * RT];
+    split_tile<false, RT, 8, true>(J, blockIdx.x, smem, &means, rows);
+}
+
+template <int RT>
+__global__ __launch_bounds__(512) void k_gemm_both_split(GemmJob<float, float, float> J0, GemmJob<float, float, float> J1, int blocks0)
+{
+    __shared__ __attribute__((aligned(16))) float smem[split_lds_floats<RT, 8>()];
+    if ((int)blockIdx.x < blocks0) split_tile<false, RT, 8>(J0, blockIdx.x, smem);
+    else split_tile<true, RT, 8>(J1, (int)blockIdx.x - blocks0, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -1188,13 +1319,19 @@ __device__ __forceinline__ void tn_tile(const TnJob<TA, TB> &J, int block, int s
 }
 
 // What is left once dQ, dK and dV are there, in one launch: dX = [dQ | dK | dV] Wqkv^T (J), dWqkv and dWo (J0, J1).
-template <bool VEC, int BN, typename T>
+// SPLIT: J by split_tile, float32.
+template <bool VEC, int BN, typename T, bool SPLIT = false>
 __global__ __launch_bounds__(256) void k_gemm_end(TnJob<T, float> J0, TnJob<float, T> J1, long M, int share_tokens, int tn_blocks, GemmJob<float, T, T> J)
 {
     constexpr size_t n = gemm_lds_floats<BN, true>(), tn = 2 * 32 * (64 + 4);
     __shared__ __attribute__((aligned(16))) float smem[n > tn ? n : tn];
     const int block = (int)blockIdx.x - tn_blocks;
     if (block >= 0) {
+        if constexpr (SPLIT) {
+            static_assert(split_lds_floats<1, 4>() <= n, "the sums fit");
+            split_tile<true, 1, 4>(J, block, smem);
+            return;
+        }
         any_gemm_tile<true, VEC, BN>(J, block, (int)gridDim.x - tn_blocks, smem);
         return;
     }

@@ -164,6 +164,25 @@ bool narrow_tiles(long M, int N, int N1 = 0)
 template <typename TB>
 long tile_blocks(long tiles) { return std::is_same<TB, float>::value ? tiles : (tiles + 7) / 8 * 8; }
 
+// Float32 products of few rows (N1: columns of a second one over the same rows) by split_tile: where the tiles of 64 x 64 leave half of the chip
+// idle or more. Those take 0.75 us for 32 of the contraction however few they are; the split ones read both operands two to four times as often,
+// which shows from 128 of the others on, and earlier where the contraction is short. Tiles of 64 / split (us, whole calls): 24 tiles, 1 x 7 x 7 x 512
+// 46.1 / 24.4; 72, 2 x 8 x 8 x 768 63.2 / 42.1; 112, 2 x 14 x 14 x 512's gradients 90.5 / 74.0; 80, 3 x 14 x 14 x 256 33.4 / 29.7; 12 rows of K = 3 C, gradients
+// of 1 x 7 x 7 x 768 131.5 / 83.8; beyond: 216, 7 x 7 x 7 x 768 67.7 / 79.1; 117 of K = 192, 1 x 28 x 28 x 192 26.7 / 27.9, 104 of K = 128, gradients of 1 x
+// 28 x 28 x 128 36.4 / 38.5.
+bool splits(long M, int N, int K, int N1 = 0)
+{
+    return K >= 64 && N % 32 == 0 && N1 % 32 == 0 && K % 16 == 0 && (M + 63) / 64 * ((N + 63) / 64 + (N1 + 63) / 64) <= (K >= 256 ? 128 : 64);
+}
+
+// Rows of its tiles, 16 or 32: by the rounds of 256 workgroups (2 x 8 x 8 x 768 42.1 / 47.1 us), the larger where they take the same, which read less
+// (3 x 14 x 14 x 256 29.8 / 29.1, 4 x 7 x 14 x 512's block 107 / 104).  A value's sums are the same with both.
+int split_rows(long M, int N, int N1 = 0)
+{
+    auto rounds = [&](int rows) { return ((M + rows - 1) / rows * ((N + N1) / 32) + 255) / 256; };
+    return rounds(16) < 2 * rounds(32) ? 16 : 32;
+}
+
 // One or two products in one launch (J1: NULL for one).
 template <bool BT, bool VEC, typename TA, typename TB, typename TO>
 int launch_gemm_vec(const f32::GemmJob<TA, TB, TO> &J0, const f32::GemmJob<float, TB, float> *J1, hipStream_t st)
@@ -187,6 +206,15 @@ int launch_gemm(const f32::GemmJob<TA, TB, TO> &J0, const f32::GemmJob<float, TB
 {
     auto quads = [](int a, int b, int c, int d, int e) { return (a | b | c | d | e) % 4 == 0; };
     const bool vec = quads(J0.lda, J0.ldb, J0.ldo, J0.N, J0.K) && (!J1 || quads(J1->lda, J1->ldb, J1->ldo, J1->N, J1->K));
+    if constexpr (!BT && std::is_same<TA, float>::value && std::is_same<TB, float>::value && std::is_same<TO, float>::value) {
+        if (vec && !J1 && splits(J0.M, J0.N, J0.K)) {
+            const int rows = split_rows(J0.M, J0.N);
+            const dim3 grid((unsigned)((J0.M + rows - 1) / rows * (J0.N / 32)));
+            if (rows == 16) hipLaunchKernelGGL((f32::k_gemm_split<false, 1>), grid, dim3(512), 0, st, J0);
+            else hipLaunchKernelGGL((f32::k_gemm_split<false, 2>), grid, dim3(512), 0, st, J0);
+            return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+        }
+    }
     return vec ? launch_gemm_vec<BT, true>(J0, J1, st) : launch_gemm_vec<BT, false>(J0, J1, st);
 }
 
@@ -234,6 +262,16 @@ int launch_gemm_means(const Dims &D, const T *X, const T *Wqkv, float *Out, cons
     const int C = D.C, N = Out ? 3 * C : 2 * C, per = f32::kGemmBM / D.n;
     const f32::GemmJob<T, T, float> J = {X, Wqkv, Out, (long)D.B * D.N, C, 3 * C, 3 * C, N, C, nullptr, nullptr, 0};
     const f32::MeansJob means = {w.qk, 2 * C, D.B * D.R, D.R, D.S, D.n, D.rh, D.rw, 1.0f / D.n, 1.0f / D.R, 1.0f / D.S, 1.0f / D.rw};
+    if constexpr (std::is_same<T, float>::value) {
+        // by the columns of Q and K for both callers: bra_route decides on the same bits as bra_forward
+        if (D.n <= 32 && C % 32 == 0 && splits(J.M, 2 * C, C)) {
+            const int rows = D.n <= 16 ? split_rows(J.M, 3 * C) : 32, each = rows / D.n;
+            const dim3 grid((unsigned)(((long)D.B * D.R + each - 1) / each * (N / 32)));
+            if (rows == 16) hipLaunchKernelGGL(f32::k_gemm_means_split<1>, grid, dim3(512), 0, st, J, means);
+            else hipLaunchKernelGGL(f32::k_gemm_means_split<2>, grid, dim3(512), 0, st, J, means);
+            return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+        }
+    }
     const long row_tiles = ((long)D.B * D.R + per - 1) / per;
     const bool narrow = narrow_tiles<T>(row_tiles * f32::kGemmBM, N);
     const int bn = narrow ? 64 : 128;
@@ -749,6 +787,15 @@ int launch_attn_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, const lce:
 template <typename T>
 int launch_gemm_both(const f32::GemmJob<T, T, float> &J0, const f32::GemmJob<T, T, float> &J1, hipStream_t st)
 {
+    if constexpr (std::is_same<T, float>::value) {
+        if (splits(J0.M, J0.N, J0.K, J1.N)) {
+            const int rows = split_rows(J0.M, J0.N, J1.N);
+            const long rt = (J0.M + rows - 1) / rows, s0 = rt * (J0.N / 32), s1 = rt * (J1.N / 32);
+            if (rows == 16) hipLaunchKernelGGL(f32::k_gemm_both_split<1>, dim3((unsigned)(s0 + s1)), dim3(512), 0, st, J0, J1, (int)s0);
+            else hipLaunchKernelGGL(f32::k_gemm_both_split<2>, dim3((unsigned)(s0 + s1)), dim3(512), 0, st, J0, J1, (int)s0);
+            return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+        }
+    }
     const long mt = (J0.M + f32::kGemmBM - 1) / f32::kGemmBM;
     const bool narrow = J1.N <= 64 || narrow_tiles<T>(J0.M, J0.N, J1.N);
     const int bn = narrow ? 64 : 128;
@@ -769,7 +816,15 @@ int launch_gemm_end(const f32::TnJob<T, float> &J0, const f32::TnJob<float, T> &
     const long mt = (J.M + f32::kGemmBM - 1) / f32::kGemmBM;
     const bool narrow = narrow_tiles<T>(J.M, J.N);
     const int bn = narrow ? 64 : 128;
-    const long tn = ((long)(J0.blocks() + J1.blocks()) * shares + 7) / 8 * 8, blocks = tn + tile_blocks<T>(mt * ((J.N + bn - 1) / bn));
+    const long tn = ((long)(J0.blocks() + J1.blocks()) * shares + 7) / 8 * 8;
+    if constexpr (std::is_same<T, float>::value) {
+        if (splits(J.M, J.N, J.K)) {
+            const dim3 grid((unsigned)(tn + (J.M + 15) / 16 * (J.N / 32)));
+            hipLaunchKernelGGL((f32::k_gemm_end<true, 64, T, true>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, (int)tn, J);
+            return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+        }
+    }
+    const long blocks = tn + tile_blocks<T>(mt * ((J.N + bn - 1) / bn));
     if (blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)blocks);
     const bool vec = J.N % 4 == 0;               // all sizes and pitches are multiples of C
