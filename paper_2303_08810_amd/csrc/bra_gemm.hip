@@ -578,6 +578,185 @@ int launch_big(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int No
     }
 }
 
+// Few rows: a tile of 32 rows x 32 outputs per workgroup, whose wavefronts share the contraction and add up through LDS in a fixed order.  The tiles
+// above leave most of the chip idle there and walk the whole contraction a chunk of 64 at a time, each 0.5 us of latency (128 x 2304 x 768:
+// 18 us on 24 workgroups).  A wavefront brings its steps of 32 by itself, both operands straight into its own ring of kSplitAhead steps, 64 bytes per
+// row; there is no barrier before the sums.  In's pieces of 16 bytes are exchanged (piece p of row r at p ^ (r / 4 % 4)): rows 4 apart meet
+// different banks.  W as above, its columns in order.  Nout and out.cols are multiples of 32; MEANS: n <= 32.
+constexpr int kSplitAhead = 3, kSplitPitch = 36;       // floats per row of sums
+template <int WAVES>
+constexpr size_t split_bytes()
+{
+    constexpr size_t ring = (size_t)WAVES * kSplitAhead * 4096, sums = (size_t)WAVES * 32 * kSplitPitch * 4;
+    return (ring > sums ? ring : sums) + 2 * 32 * sizeof(int);
+}
+
+template <bool BT, bool MEANS, int WAVES>
+__device__ __forceinline__ void split_tile(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int M, int K, int Nout, const GemmOut &out,
+                                           int block, char *smem, const GemmMeans *means = nullptr)
+{
+    constexpr int P = kSplitPitch, AHEAD = kSplitAhead;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, h = lane / 32, c = lane % 32;
+    const int ntiles = Nout / 32, tile = block / ntiles, n0 = 32 * (block - tile * ntiles), m0 = 32 * tile;
+    int *table = (int *)(smem + split_bytes<WAVES>() - 2 * 32 * sizeof(int));       // MEANS: tokens of the tile's rows
+    if constexpr (MEANS) {
+        if (tid < 32) region_row<32>(*means, tile, tid, table[tid], table[32 + tid]);
+        __syncthreads();
+    }
+    const int steps = K / 32, s0 = steps * wave / WAVES, s1 = steps * (wave + 1) / WAVES;
+    // direct loads: 16 rows of 4 pieces each
+    const bf16_t *x[2], *w[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int row = 16 * u + lane / 4, piece = (lane % 4) ^ (row / 4 % 4);
+        const long at = MEANS ? (long)table[32 + row] : out.in_rows.Hp ? stored_row(out.in_rows, min(m0 + row, M - 1)) : (long)min(m0 + row, M - 1);
+        x[u] = (at >= 0 ? In + (size_t)at * K : zero_row) + 8 * piece;
+        if (BT) w[u] = W + (size_t)(n0 + row) * ldw + 8 * piece;
+        else w[u] = W + (size_t)row * ldw + n0 + 8 * (lane % 4);
+    }
+    const size_t wstep = BT ? 32 : (size_t)32 * ldw;
+    char *ring = smem + wave * AHEAD * 4096;
+    const unsigned base = lds_address(ring);
+    auto request = [&](int s, int slot) {
+        lds_reads_done();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            load_to_lds_untracked(x[u] + 32 * s, base + 4096 * slot + 1024 * u);
+            load_to_lds_untracked(w[u] + s * wstep, base + 4096 * slot + 2048 + 1024 * u);
+        }
+    };
+    const int sl = lane % 16, q = lane / 16;
+    auto row_operand = [&](const bf16_t *T, int ks) { return *(const bf16x8 *)(T + c * 32 + 8 * ((2 * ks + h) ^ (c / 4 % 4))); };
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a)
+        if (s0 + a < s1) request(s0 + a, a);
+    for (int s = s0; s < s1; s += AHEAD) {
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a) {
+            if (s + a >= s1) break;
+            const int behind = s1 - 1 - s - a;     // steps requested after this one: four loads each
+            if (behind >= 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+            else if (behind == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const bf16_t *X = (const bf16_t *)(ring + 4096 * a), *B = X + 1024;
+            bf16x8 xf[2], wf[2];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                xf[ks] = row_operand(X, ks);
+                if (BT) {
+                    wf[ks] = row_operand(B, ks);
+                } else {
+                    u32x2 r[2];
+#pragma unroll
+                    for (int half = 0; half < 2; ++half)
+                        r[half] = __builtin_bit_cast(u32x2, lds_read_tr16(B + (16 * ks + 8 * (q / 2) + 4 * half + sl / 4) * 32 + 16 * (q % 2) + 4 * (sl % 4)));
+                    wf[ks] = __builtin_bit_cast(bf16x8, u32x4{r[0][0], r[0][1], r[1][0], r[1][1]});
+                }
+            }
+            if (s + a + AHEAD < s1) request(s + a + AHEAD, a);
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) acc = mfma32(wf[ks], xf[ks], acc);
+        }
+    }
+    products_done();
+    __syncthreads();                              // every ring has been read
+    float *sums = (float *)smem;
+#pragma unroll
+    for (int e = 0; e < 16; e += 4) *(f32x4 *)(sums + (wave * 32 + c) * P + 2 * e + 4 * h) = f32x4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
+    __syncthreads();
+    const int which = (n0 >= out.cols) + (n0 >= 2 * out.cols), col0 = n0 - which * out.cols;
+    bf16_t *buf = (bf16_t *)out.buf[which];
+    float *fbuf = which < 2 ? out.f32[which] : nullptr;
+    const float scale = which == 0 ? out.scale0 : 1.0f;
+    if (tid < 256) {                              // (row, 4 outputs)
+        const int row = tid / 8, col = 4 * (tid % 8);
+        float *at = sums + row * P + col;
+        f32x4 v = *(const f32x4 *)at;
+#pragma unroll
+        for (int u = 1; u < WAVES; ++u) v += *(const f32x4 *)(at + u * 32 * P);
+        if (MEANS) *(f32x4 *)at = v;
+        const int m = MEANS ? table[row] : m0 + row;
+        const long to = (MEANS ? m < 0 : m >= M) || !buf ? -1 : out.out_rows.Hp ? stored_row(out.out_rows, m) : m;
+        if (to >= 0) {
+            const size_t o = (size_t)to * out.cols + col0 + col;
+            if (fbuf) *(f32x4 *)(fbuf + o) = v;
+            v *= scale;
+            if (out.bias) v += *(const f32x4 *)(out.bias + n0 + col);
+            if (out.gelu) v = f32x4{gelu_f32(v[0]), gelu_f32(v[1]), gelu_f32(v[2]), gelu_f32(v[3])};
+            if (out.res) {
+                const u32x2 r = *(const u32x2 *)(out.res + (size_t)to * out.cols + n0 + col);
+                v += f32x4{bf16_lo(r[0]), bf16_hi(r[0]), bf16_lo(r[1]), bf16_hi(r[1])};
+            }
+            *(u32x2 *)(buf + o) = pack4(v);
+        }
+    }
+    if constexpr (MEANS) {
+        if (which >= 2) return;
+        __syncthreads();
+        const int n = means->n, per = fast_div(32, means->n_inv), first = tile * per;
+        for (int e = tid; e < 8 * per; e += 64 * WAVES) {
+            const int j = e / 8;
+            if (first + j >= means->regions) break;
+            const float *at = sums + j * n * P + 4 * (e % 8);
+            f32x4 sum = *(const f32x4 *)at;
+            for (int t = 1; t < n; ++t) sum += *(const f32x4 *)(at + t * P);
+            *(f32x4 *)(means->buf[which] + (size_t)(first + j) * out.cols + col0 + 4 * (e % 8)) = sum * means->n_inv;
+        }
+    }
+}
+
+constexpr int kSplitWaves = 8;
+
+template <bool BT>
+__global__ __launch_bounds__(64 * kSplitWaves) void k_gemm_split(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int M, int K, int Nout,
+                                                                 GemmOut out)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    split_tile<BT, false, kSplitWaves>(In, W, ldw, M, K, Nout, out, blockIdx.x, smem);
+}
+
+__global__ __launch_bounds__(64 * kSplitWaves) void k_gemm_means_split(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int K, int Nout,
+                                                                       GemmOut out, GemmMeans means)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    split_tile<false, true, kSplitWaves>(In, W, ldw, 0, K, Nout, out, blockIdx.x, smem, &means);
+}
+
+__global__ __launch_bounds__(64 * kSplitWaves) void k_gemm_pair_split(const bf16_t *__restrict__ In0, const bf16_t *__restrict__ W0, int ldw0, int Nout0, GemmOut out0,
+                                                                      const bf16_t *__restrict__ In1, const bf16_t *__restrict__ W1, int ldw1, int Nout1,
+                                                                      GemmOut out1, int M, int K, int blocks0)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int bi = blockIdx.x;
+    if (bi < blocks0) split_tile<false, false, kSplitWaves>(In0, W0, ldw0, M, K, Nout0, out0, bi, smem);
+    else split_tile<true, false, kSplitWaves>(In1, W1, ldw1, M, K, Nout1, out1, bi - blocks0, smem);
+}
+
+// Nout1: a second product over the same rows.  A round of workgroups, one per compute unit, holds as much as 64 tiles of 64 x 64 and takes about 4 us;
+// those take 0.5 us for 64 of the contraction, so that a short one leaves nothing to gain and a long one pays for a second round.  Tiles of 64 /
+// split (us, whole calls): 12 tiles, gradients of 1 x 7 x 7 x 512 34.1 / 27.0, of 2 x 7 x 7 x 768 46.8 / 38.1; 24, block of 2 x 8 x 8 x 768 73.7 / 60.3; block of
+// 1 x 14 x 14 x 384 45.9 / 40.7; two rounds: K = 2304, gradients of 2 x 14 x 14 x 768 (84) 49.1 / 44.0, but K = 256, 2 x 21 x 21 x 256 (112) 24.4 / 29.7, K = 384,
+// 1 x 28 x 28 x 384 (78) 27.4 / 28.3; K = 192, gradients of 2 x 24 x 24 x 192 29.8 / 31.9.
+bool splits(long M, int K, int Nout, int cols, int Nout1 = 0)
+{
+    const long tiles = (M + 63) / 64 * ((Nout + 63) / 64 + (Nout1 + 63) / 64);
+    return Nout % 32 == 0 && Nout1 % 32 == 0 && cols % 32 == 0 && tiles <= (K >= 1024 ? 128 : K >= 256 ? 64 : 0);
+}
+
+long split_blocks(long M, int Nout) { return (M + 31) / 32 * (Nout / 32); }
+
+template <bool BT>
+int launch_split(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, hipStream_t st)
+{
+    static bool opted = false;
+    if (!opt_in(k_gemm_split<BT>, opted)) return BRA_ERR_LAUNCH;
+    hipLaunchKernelGGL(k_gemm_split<BT>, dim3((unsigned)split_blocks(M, Nout)), dim3(64 * kSplitWaves), split_bytes<kSplitWaves>(), st, In, W, ldw, (int)M, K, Nout, out);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
 template <int BM, int BN, int NB>
 int launch_pair(const GemmHalf &a, const GemmHalf &b, long M, int K, hipStream_t st)
 {
@@ -861,6 +1040,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_tn(GemmTn J0, GemmTn J1, long M
 }
 
 // Out = In Wt^T and both contractions over the tokens in one launch: dX, dWqkv and dWo, once dQ, dK and dV are there.
+// BM = 0: Out by split_tile.
 template <int BM, int BN>
 __global__ __launch_bounds__(256, 2) void k_gemm_bt_tn(GemmTn J0, GemmTn J1, int tiles, int share_tokens, const bf16_t *__restrict__ In,
                                                        const bf16_t *__restrict__ Wt, int ldw, int M, int K, int Nout, GemmOut out)
@@ -868,7 +1048,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_bt_tn(GemmTn J0, GemmTn J1, int
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16_t *lds = (bf16_t *)smem;
     if ((int)blockIdx.x < tiles) {
-        dma_tile<BM, BN, 2, true, false>(In, Wt, ldw, M, K, Nout, out, swizzled(blockIdx.x, tiles), lds);
+        if constexpr (BM == 0) split_tile<true, false, 4>(In, Wt, ldw, M, K, Nout, out, blockIdx.x, smem);
+        else dma_tile<BM, BN, 2, true, false>(In, Wt, ldw, M, K, Nout, out, swizzled(blockIdx.x, tiles), lds);
         return;
     }
     tn_block(J0, J1, (int)blockIdx.x - tiles, (int)gridDim.x - tiles, M, share_tokens, lds);
@@ -879,9 +1060,17 @@ int launch_bt_tn(const GemmTn &J0, const GemmTn &J1, long tn_blocks, int share_t
 {
     static bool opted = false;
     if (!opt_in(k_gemm_bt_tn<BM, BN>, opted)) return BRA_ERR_LAUNCH;
-    const long blocks = tile_blocks<BM, BN>(M, b.Nout);
+    long blocks;
+    size_t bytes;
+    if constexpr (BM == 0) {
+        blocks = split_blocks(M, b.Nout);
+        bytes = split_bytes<4>();
+    } else {
+        blocks = tile_blocks<BM, BN>(M, b.Nout);
+        bytes = ring_bytes<BM, BN, 2>();
+    }
     if (tn_blocks + blocks > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((k_gemm_bt_tn<BM, BN>), dim3((unsigned)(tn_blocks + blocks)), dim3(256), (std::max(kTnBytes, ring_bytes<BM, BN, 2>())), st,
+    hipLaunchKernelGGL((k_gemm_bt_tn<BM, BN>), dim3((unsigned)(tn_blocks + blocks)), dim3(256), std::max(kTnBytes, bytes), st,
                        J0, J1, (int)blocks, share_tokens, b.In, b.W, b.ldw, (int)M, K, b.Nout, b.out);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
@@ -903,6 +1092,8 @@ int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, co
         return launch_proj(In, W, ldw, M, K, Nout, out, st);
     }
     ProfScope ps(st, kernel_id);
+    // float32 copies: by the columns that have them, as a product of those alone (bra_route decides on the same bits as bra_forward)
+    if (!regions && splits(M, K, out.f32[0] ? 2 * out.cols : Nout, out.cols)) return launch_split<false>(In, W, ldw, M, K, Nout, out, st);
     if (regions) return launch_big<true>(In, W, ldw, M, K, Nout, out, *regions, st);
     return launch_big<false>(In, W, ldw, M, K, Nout, out, GemmRegions{}, st);
 }
@@ -912,6 +1103,14 @@ int gemm_means(const bf16_t *In, const bf16_t *W, int ldw, int K, int Nout, cons
     const long M = (long)means.regions * means.n;
     if (!sizes_ok(M, K, Nout) || out.cols % 32 || K > 4096 || means.n > kMeansMaxTokens) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);
+    // by the columns of Q and K for both callers: bra_route decides on the same bits as bra_forward
+    if (means.n <= 32 && splits(M, K, 2 * out.cols, out.cols)) {
+        static bool opted = false;
+        if (!opt_in(k_gemm_means_split, opted)) return BRA_ERR_LAUNCH;
+        const long each = 32 / means.n, blocks = (means.regions + each - 1) / each * (Nout / 32);
+        hipLaunchKernelGGL(k_gemm_means_split, dim3((unsigned)blocks), dim3(64 * kSplitWaves), split_bytes<kSplitWaves>(), st, In, W, ldw, K, Nout, out, means);
+        return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+    }
     switch (pick_tile(M, K, Nout, 0, 0, means.n)) {
     case kOneChunk: return launch_means<64, 64, 1>(In, W, ldw, K, Nout, out, means, st);
     case kWide: return launch_means<128, 128, 2>(In, W, ldw, K, Nout, out, means, st);
@@ -925,6 +1124,7 @@ int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout
     if (!sizes_ok(M, K, Nout)) return BRA_ERR_UNSUPPORTED;
     const GemmOut out = {{Out, nullptr, nullptr}, Nout, {nullptr, nullptr}, nullptr, nullptr, 0};
     ProfScope ps(st, kernel_id);
+    if (splits(M, K, Nout, Nout)) return launch_split<true>(In, Wt, ldw, M, K, Nout, out, st);
     return launch_big<false, true>(In, Wt, ldw, M, K, Nout, out, GemmRegions{}, st);
 }
 
@@ -934,6 +1134,14 @@ int gemm_pair(const GemmHalf &a, const GemmHalf &b, long M, int K, int kernel_id
     ProfScope ps(st, kernel_id);
     if (b.Nout == K && proj_ok(M, K, a.Nout, a.out, false) && a.Nout == 3 * K)
         return K == 64 ? launch_proj_t<64, 192, true>(a.In, a.W, a.ldw, M, a.out, st, b) : launch_proj_t<128, 384, true>(a.In, a.W, a.ldw, M, a.out, st, b);
+    if (splits(M, K, a.Nout, a.out.cols, b.Nout) && b.out.cols % 32 == 0) {
+        static bool opted = false;
+        if (!opt_in(k_gemm_pair_split, opted)) return BRA_ERR_LAUNCH;
+        const long b0 = split_blocks(M, a.Nout), b1 = split_blocks(M, b.Nout);
+        hipLaunchKernelGGL(k_gemm_pair_split, dim3((unsigned)(b0 + b1)), dim3(64 * kSplitWaves), split_bytes<kSplitWaves>(), st, a.In, a.W, a.ldw, a.Nout, a.out,
+                           b.In, b.W, b.ldw, b.Nout, b.out, (int)M, K, (int)b0);
+        return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+    }
     // tiles of both together
     switch (pick_tile(M, K, a.Nout, b.Nout, 0)) {
     case kOneChunk: return launch_pair<64, 64, 1>(a, b, M, K, st);
@@ -996,6 +1204,7 @@ int gemm_bt_tn(const GemmTn &J0, const GemmTn &J1, const GemmHalf &b, long M, in
     const int tokens = tn_share_tokens(M, J0.KA, J0.N, J1.KA, J1.N), shares = gemm_tn_shares(M, J0.KA, J0.N, J1.KA, J1.N);
     const long tn = tn_blocks(J0, J1, shares);
     ProfScope ps(st, kernel_id);
+    if (splits(M, K, b.Nout, b.out.cols)) return launch_bt_tn<0, 0>(J0, J1, tn, tokens, b, M, K, st);
     // that few tiles are never the wide ones
     if (pick_tile(M, K, b.Nout, 0, 0) == kNarrow) return launch_bt_tn<64, 64>(J0, J1, tn, tokens, b, M, K, st);
     return launch_bt_tn<64, 128>(J0, J1, tn, tokens, b, M, K, st);
