@@ -3,7 +3,7 @@
 //   k_pos_ln          X1 = X + DWConv3x3(X) + bpos,  Xn = LayerNorm1(X1)      one pass over X
 //   (k_token_ln<POS> for channel counts with several chunks of 8 per lane)
 //   BRA               Y  = BRA(Xn)                   (Eq. 2-7; the kernel family picked for the shape)
-//   C <= 256:  k_mlp_fused64 (C = 64, weights resident in LDS) or k_mlp_stream (weights streamed):
+//   C <= 256:  k_mlp_fused64 (C = 64, weights resident in LDS), k_mlp_stream (weights streamed) or, on up to 4096 tokens, k_mlp_few:
 //                     Xout = X2 + MLP(LayerNorm2(X2)), X2 = X1 + Y, in one kernel
 //   otherwise:
 //   k_token_ln<ADD>   X2 = X1 + Y,                   Xn = LayerNorm2(X2)
@@ -13,7 +13,7 @@
 // The normalisation and residual links follow the pre-norm residual reading stated with the
 // entry point's declaration.  float32 tensors and sizes that are not multiples of 64 go to the
 // scalar kernels of the generic family instead.
-#include "bra_mfma_dev.h"
+#include "bra_attn_dev.h"
 
 #include <stdlib.h>
 
@@ -735,6 +735,180 @@ int launch_mlp_stream(const Dims &D, int hidden, const bf16_t *X1, const bf16_t 
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
+// Few tokens: 16 to a workgroup, whose 8 wavefronts share the hidden units, 32 at a time, and add their parts of the output up through LDS in a fixed
+// order.  Above, a workgroup of 64 tokens walks all of the hidden layer between barriers, 20 us at C = 192 and 31 at C = 256 however few there
+// are.  Here a wavefront brings the weights by itself, straight into a ring of RING steps of 32 x 32 of them (64 bytes per row), and there is
+// no barrier before the sums.  Bound by the weights' way to every compute unit, 0.8 MB at C = 256.  Same operands and roundings as above.
+template <int CT>
+struct MlpFewSmem {
+    static constexpr int C = 64 * CT, KS = C / 32, RING = CT == 3 ? 6 : 8, P = C + 4;      // RING divides 2 KS
+    static constexpr size_t ring = (size_t)8 * RING * 2048, sums = (size_t)8 * 16 * P * 4, b1_off = ring > sums ? ring : sums;
+    static size_t bytes(int hidden) { return b1_off + (size_t)hidden * 4; }
+};
+
+template <int CT>
+__global__ __launch_bounds__(512) void k_mlp_few(const bf16_t *__restrict__ X1, const bf16_t *__restrict__ Y, const bf16_t *__restrict__ W1,
+                                                 const float *__restrict__ b1, const bf16_t *__restrict__ W2, const float *__restrict__ b2,
+                                                 const float *__restrict__ gamma, const float *__restrict__ beta, bf16_t *__restrict__ Xout, long tokens,
+                                                 int hidden, float eps)
+{
+    typedef MlpFewSmem<CT> SM;
+    constexpr int C = SM::C, KS = SM::KS, NT = C / 16, R = SM::RING, P = SM::P;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    float *b1s = (float *)(smem + SM::b1_off);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, i = lane % 16;
+    const int blocks = (hidden / 32 - wave + 7) / 8;           // of this wavefront: units 32 (wave + 8 u) .. + 31
+    char *ring = smem + wave * R * 2048;
+    const unsigned base = lds_address(ring);
+    const bf16_t *w1 = W1 + (size_t)(lane / 4) * hidden + 32 * wave + 8 * (lane % 4), *w2 = W2 + (size_t)(32 * wave + lane / 4) * C + 8 * (lane % 4);
+    // step r of a block: 32 channels of W1's 32 columns (r < KS), 32 channels of W2's 32 rows
+    auto request = [&](int block, int r, int slot) {
+        lds_reads_done();
+        const bf16_t *from = r < KS ? w1 + (size_t)32 * r * hidden + 256 * block : w2 + (size_t)256 * block * C + 32 * (r - KS);
+        const size_t half = r < KS ? (size_t)16 * hidden : (size_t)16 * C;
+        load_to_lds_untracked(from, base + 2048 * slot);
+        load_to_lds_untracked(from + half, base + 2048 * slot + 1024);
+    };
+    if (blocks > 0)
+#pragma unroll
+        for (int r = 0; r < R; ++r) request(0, r, r);
+    for (int q = tid; q < hidden; q += 512) b1s[q] = b1[q];
+
+    const long first = (long)blockIdx.x * 16, tok_c = min(first + i, tokens - 1);       // rows past the end repeat the last; never stored
+    float x2[KS][8];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const u32x4 xa = *(const u32x4 *)(X1 + (size_t)tok_c * C + 32 * ks + 8 * g);
+        const u32x4 ya = *(const u32x4 *)(Y + (size_t)tok_c * C + 32 * ks + 8 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            x2[ks][2 * e] = bf16_lo(xa[e]) + bf16_lo(ya[e]);
+            x2[ks][2 * e + 1] = bf16_hi(xa[e]) + bf16_hi(ya[e]);
+        }
+    }
+    float s = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += x2[ks][e];
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    const float mean = s * (1.0f / C);
+    float qq = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { const float d = x2[ks][e] - mean; qq = fmaf(d, d, qq); }
+    qq += __shfl_xor(qq, 16);
+    qq += __shfl_xor(qq, 32);
+    const float rstd = __builtin_amdgcn_rsqf(qq * (1.0f / C) + eps);
+    bf16x8 bx[KS];
+    f32x4 acc2[NT];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const int c0 = 32 * ks + 8 * g;
+        float v[8];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const f32x4 gv = *(const f32x4 *)(gamma + c0 + 4 * h), bv = *(const f32x4 *)(beta + c0 + 4 * h);
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) v[4 * h + jj] = fmaf((x2[ks][4 * h + jj] - mean) * rstd, gv[jj], bv[jj]);
+            acc2[2 * ks + h] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        bx[ks] = pack8(v);
+    }
+    __syncthreads();                                            // b1 is in LDS
+    const int off1 = (8 * g + i / 4) * 32 + 4 * (i % 4), off2 = (4 * g + i / 4) * 32 + 8 * (i % 4);
+    for (int block = 0; block < blocks; ++block) {
+        const bool last = block + 1 == blocks;
+        f32x4 a[2];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) a[half] = *(const f32x4 *)(b1s + 32 * (wave + 8 * block) + 16 * half + 4 * g);
+        bf16x8 hb;
+#pragma unroll
+        for (int r = 0; r < 2 * KS; ++r) {
+            // the step has arrived: those behind it stay in flight, but for the last ones of all
+            if (last && r + R > 2 * KS) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * (R - 1)) : "memory");
+            const bf16_t *T = (const bf16_t *)(ring + 2048 * (r % R));
+            bf16x8 wf[2];
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const bf16_t *wp = r < KS ? T + off1 + 16 * half : T + off2 + 4 * half;
+                const u32x2 w0 = __builtin_bit_cast(u32x2, lds_read_tr16(wp));
+                const u32x2 w1v = __builtin_bit_cast(u32x2, lds_read_tr16(wp + (r < KS ? 4 : 16) * 32));
+                wf[half] = __builtin_bit_cast(bf16x8, u32x4{w0[0], w0[1], w1v[0], w1v[1]});
+            }
+            if (r + R < 2 * KS) request(block, r + R, r % R);
+            else if (!last) request(block + 1, r + R - 2 * KS, r % R);
+            if (r < KS) {
+#pragma unroll
+                for (int half = 0; half < 2; ++half) a[half] = mfma16(wf[half], bx[r], a[half]);
+                if (r == KS - 1) {
+                    float hv[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) hv[e] = gelu_f32(a[e / 4][e % 4]);
+                    hb = pack8(hv);
+                }
+            } else {
+#pragma unroll
+                for (int half = 0; half < 2; ++half) acc2[2 * (r - KS) + half] = mfma16(wf[half], hb, acc2[2 * (r - KS) + half]);
+            }
+        }
+    }
+    __syncthreads();                                            // every ring has been read
+    float *sums = (float *)smem;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) *(f32x4 *)(sums + (wave * 16 + i) * P + 32 * (t / 2) + 8 * g + 4 * (t % 2)) = acc2[t];
+    __syncthreads();
+    for (int e = tid; e < 16 * C / 8; e += 512) {
+        const int row = e / (C / 8), c0 = 8 * (e % (C / 8));
+        if (first + row >= tokens) continue;
+        const size_t at = (size_t)(first + row) * C + c0;
+        const u32x4 xa = *(const u32x4 *)(X1 + at), ya = *(const u32x4 *)(Y + at);
+        float v[8];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const f32x4 ov = *(const f32x4 *)(b2 + c0 + 4 * h);
+            f32x4 sum = *(const f32x4 *)(sums + row * P + c0 + 4 * h);
+#pragma unroll
+            for (int u = 1; u < 8; ++u) sum += *(const f32x4 *)(sums + (16 * u + row) * P + c0 + 4 * h);
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                const int q = 4 * h + jj;
+                const float x = q % 2 ? bf16_hi(xa[q / 2]) + bf16_hi(ya[q / 2]) : bf16_lo(xa[q / 2]) + bf16_lo(ya[q / 2]);
+                v[q] = x + ov[jj] + sum[jj];
+            }
+        }
+        *(bf16x8 *)(Xout + at) = pack8(v);
+    }
+}
+
+template <int CT>
+int launch_mlp_few(const Dims &D, int hidden, const bf16_t *X1, const bf16_t *Y, const bra_block_params &p, bf16_t *Xout, float eps, hipStream_t st)
+{
+    const size_t smem = MlpFewSmem<CT>::bytes(hidden);
+    static size_t opted = 0;
+    if (smem > opted) {
+        if (hipFuncSetAttribute((const void *)k_mlp_few<CT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) return BRA_ERR_LAUNCH;
+        opted = smem;
+    }
+    const long tokens = (long)D.B * D.N;
+    ProfScope ps(st, K_BLK_MLP_FUSED);
+    hipLaunchKernelGGL(k_mlp_few<CT>, dim3((unsigned)((tokens + 15) / 16)), dim3(512), smem, st, X1, Y, (const bf16_t *)p.W1, p.b1, (const bf16_t *)p.W2, p.b2,
+                       p.ln2_gamma, p.ln2_beta, Xout, tokens, hidden, eps);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
+// As long as there is a compute unit for each.  Block, workgroups of 64 tokens / of 16 (us): 3 x 14 x 14 x 192 44.1 / 36.1, 5 x 28 x 28 x 192 45.6 / 38.5, 8 x 28 x 28 x 192
+// (392 of 16) 50.4 / 52.1; 1 x 14 x 14 x 256 54.0 / 38.9, 20 x 14 x 14 x 256 62.6 / 49.2, 40 x 14 x 14 x 256 (490) 77.2 / 81.0; 1 x 28 x 28 x 128 34.7 / 31.3,
+// 5 x 28 x 28 x 128 35.8 / 32.9, 8 x 28 x 28 x 128 36.8 / 40.0.
+bool mlp_few(const Dims &D, int hidden)
+{
+    const size_t need = D.C == 128 ? MlpFewSmem<2>::bytes(hidden) : D.C == 192 ? MlpFewSmem<3>::bytes(hidden) : D.C == 256 ? MlpFewSmem<4>::bytes(hidden) : ~(size_t)0;
+    return need <= (size_t)kMaxLds && (long)D.B * D.N <= 256 * 16;
+}
+
 // Workgroups of 8 wavefronts share a block of the weights, and its way into LDS, among twice the tokens; of 4 they spread further.  A
 // compute unit holds 3, 2 or 1 of 4 wavefronts and 2, 1 or 1 of 8 for C = 128, 192 or 256.  Block, us, with 4 / 8 and the workgroups of 4:
 //   C = 128: 16 x 28 x 28 (196) 48.2 / 50.3, 32 (392) 61.5 / 59.3, 48 (588, three a unit, with 8 four halves) 74.9 / 75.7, 64 (784, the last 16 of them
@@ -798,6 +972,12 @@ int launch_token_ln(const Dims &D, const bf16_t *A, const bf16_t *Badd, const br
     iters = iters < 1 ? 1 : (iters > 8 ? 8 : iters);
     const long grid = ((tokens + slots * iters - 1) / (slots * iters) + 7) / 8 * 8;      // whole rounds over the XCDs
     ProfScope ps(st, MODE == kPos ? K_BLK_POS_LN : K_BLK_ADD_LN);
+    // few tokens with several chunks per lane: four channels per lane instead, all loads at once (block, us, chunks / that: 1 x 28 x 28 x 320 56.8 / 47.9,
+    // 1 x 14 x 14 x 768 60.3 / 58.7; more of them, whose taps then fill the registers: 26 x 7 x 7 x 768 93.6 / 100.9, 8 x 28 x 28 x 320 78.2 / 80.2)
+    if (!one && tokens * D.C <= 1L << 18) {
+        const int rc = token_ln_bf16(D, MODE == kPos, A, Badd, p, gamma, beta, Sum, Norm, eps, st);
+        if (rc != BRA_ERR_UNSUPPORTED) return rc;
+    }
     auto launch = [&](auto kernel, size_t smem) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), smem, st, A, Badd, (const bf16_t *)p.Wpos, p.bpos,
                            gamma, beta, Sum, Norm, D.H, D.W, D.C, tokens, G, (int)iters, eps);
@@ -907,6 +1087,11 @@ int block_forward(const Dims &D, int hidden, float eps, const void *X, const bra
         }
     }
     if (mlp_stream_shape(D, hidden)) {
+        if (mlp_few(D, hidden)) {
+            if (D.C == 128) return launch_mlp_few<2>(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);
+            if (D.C == 192) return launch_mlp_few<3>(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);
+            return launch_mlp_few<4>(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);
+        }
         const bool eight = mlp_eight_waves(D);
         switch (D.C / 64) {
         case 1: return launch_mlp_stream<1, 4>(D, hidden, w.x1, w.y, p, (bf16_t *)Xout, eps, st);

@@ -160,6 +160,9 @@ int generic_backward(const Dims &D, const void *X, const void *Wqkv, const void 
 
 // Whole block with the float32 kernels (bra_generic.hip): any dtype, C and hidden.
 size_t generic_block_workspace_bytes(const Dims &D, int hidden, size_t bra_bytes);
+// The float32 family's position or sum with LayerNorm on bf16 maps, up to 1024 channels.
+int token_ln_bf16(const Dims &D, bool pos, const bf16_t *A, const bf16_t *Badd, const bra_block_params &p, const float *gamma, const float *beta, bf16_t *Sum,
+                  bf16_t *Norm, float eps, hipStream_t st);
 int generic_block_forward(const Dims &D, int hidden, float eps, const void *X, const bra_block_params &p, void *Xout,
                           int32_t *Ir_out_opt, const int32_t *Ir_in_opt, void *ws, size_t bra_bytes, int path,
                           hipStream_t st);

@@ -973,6 +973,15 @@ int backward_t(const Dims &D, const T *X, const T *Wqkv, const T *Wo, const T *W
 
 }  // namespace
 
+int token_ln_bf16(const Dims &D, bool pos, const bf16_t *A, const bf16_t *Badd, const bra_block_params &p, const float *gamma, const float *beta, bf16_t *Sum,
+                  bf16_t *Norm, float eps, hipStream_t st)
+{
+    if (D.C % 4 != 0 || D.C > 1024) return BRA_ERR_UNSUPPORTED;
+    if (pos) launch_token_ln<bf16_t, true>(D, A, nullptr, (const bf16_t *)p.Wpos, p.bpos, gamma, beta, Sum, Norm, eps, st);
+    else launch_token_ln<bf16_t, false>(D, A, Badd, nullptr, nullptr, gamma, beta, Sum, Norm, eps, st);
+    return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
 size_t generic_block_workspace_bytes(const Dims &D, int hidden, size_t bra_bytes)
 {
     return carve_gen_block(D, hidden, bra_bytes, nullptr).bytes;
