@@ -21,6 +21,7 @@
 //            costs less than storing them; the workgroup finds its routed region itself)
 //   staged : k_pool -> k_route -> k_qkv -> k_attn_big                 (regions of 64 n tokens)
 //            k_qkv -> k_route_p -> small-region kernels (bra_mfma_small.hip)
+#include "bra_proj_dev.h"
 #include "bra_mfma_dev.h"
 
 #include <stdlib.h>
@@ -1711,6 +1712,59 @@ int launch_qkv(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const MfmaWs 
     return BRA_OK;
 }
 
+// Q, K, V at C = 64 with the routing from pooled X in the same launch, for the layers whose regions are pooled beforehand.  Wavefronts take 16 tokens at
+// a time on their own, all weights in LDS (proj_tile).  k_qkv, whose two tiles a workgroup are a chain of staging, products and stores on one and a half
+// wavefronts per SIMD, took 12.2 us for 32768 tokens however its tiles were dealt out, this 11.6, of which the routing by itself 6.2.  Layers before / now: 1 x 128 x 128,
+// k = 4 28.1 / 27.4 us, 8 x 128 x 128, k = 2 75.5 / 73.4, 33 x 64 x 64, k = 2 63.6 / 61.3, 2 x 128 x 128, k = 4 38.6 / 38.3.
+__global__ __launch_bounds__(256, 4) void k_proj_route(const bf16_t *__restrict__ X, long M, int per_group, GemmOut out, PrepArgs prep)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    // routing first: a long chain of dependent steps
+    if ((int)blockIdx.x < prep.route_items) {
+        route_body<64>(prep.Xr, prep.WT, prep.Ir, nullptr, prep.dims, smem, (int)blockIdx.x);
+        return;
+    }
+    constexpr int K = 64, N = 192, KS = K / 32;
+    bf16_t *Ws = (bf16_t *)smem;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, g = lane / 16, i = lane % 16;
+    const long tiles = (M + 15) / 16, first = ((long)blockIdx.x - prep.route_items) * per_group, last = min(tiles, first + per_group);
+    bf16x8 x[2][KS];
+    auto fetch = [&](long tile, int set) {
+        const size_t row = (size_t)min(min(tile, tiles - 1) * 16 + i, M - 1) * K + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) x[set][ks] = *(const bf16x8 *)(X + row + 32 * ks);
+    };
+    fetch(first + wave, 0);
+    proj_stage<K, N, false>(Ws, prep.Wqkv, N);
+    __syncthreads();
+    int again = 0;
+    auto work = [&](long t, int set) {
+        asm volatile("" : "+s"(again));
+        proj_tile<K, N, false>(Ws, again, x[set], t, M, out);
+    };
+    for (long t = first + wave; t < last; t += 8) {
+        if (t + 4 < last) fetch(t + 4, 1);
+        work(t, 0);
+        if (t + 4 >= last) break;
+        if (t + 8 < last) fetch(t + 8, 0);
+        work(t + 4, 1);
+    }
+}
+
+int launch_proj_route(const Dims &D, const bf16_t *X, const MfmaWs &w, const PrepArgs &prep, hipStream_t st, float qscale)
+{
+    const long M = (long)D.B * D.N, tiles = (M + 15) / 16;
+    // two workgroups per compute unit: layer of 4 x 128 x 128, k = 4 58.8 us, with four 61.0; 10 x 64 x 128, k = 2 44.7 / 46.1; 33 x 64 x 64, k = 2 61.3 / 60.3
+    const long slots = 512, per = 4 * ((tiles + 4 * slots - 1) / (4 * slots)), groups = (tiles + per - 1) / per;
+    const size_t smem = std::max(ProjLds<64, 192, false>::bytes, RouteSmem<64>::bytes);
+    static bool opted = false;
+    if (!lds_opt_in(k_proj_route, opted)) return BRA_ERR_LAUNCH;
+    const GemmOut out = {{w.q, w.k, w.v}, 64, {nullptr, nullptr}, nullptr, nullptr, 0, qscale};
+    ProfScope ps(st, K_MFMA_QKV);
+    hipLaunchKernelGGL(k_proj_route, dim3((unsigned)(prep.route_items + groups)), dim3(256), smem, st, X, M, (int)per, out, prep);
+    return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
+}
+
 // Y = O Wo (Eq. 2) as a plain projection of a token map: the projection kernel with Wo as
 // its only weight matrix.
 template <int C>
@@ -1782,7 +1836,8 @@ int forward_c(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const bf16_t *
             prep.route_items = D.B * ((D.R + 15) / 16);
             prep.dims = D;
         }
-        int rc = launch_qkv<C>(D, X, Wqkv, w, pooled, prep, st, q32 ? c_exp : 1.0f);
+        int rc = C == 64 && route_with_qkv ? launch_proj_route(D, X, w, prep, st, q32 ? c_exp : 1.0f)
+                                           : launch_qkv<C>(D, X, Wqkv, w, pooled, prep, st, q32 ? c_exp : 1.0f);
         if (rc != BRA_OK) return rc;
         if (pooled) {
             rc = launch_route_p<C>(D, w, Ir_dst, nullptr, st);
