@@ -1138,7 +1138,8 @@ int gemm_bt_tn(const GemmTn &J0, const GemmTn &J1, const GemmHalf &b, long M, in
     const int tokens = tn_share_tokens(M, J0.KA, J0.N, J1.KA, J1.N), shares = gemm_tn_shares(M, J0.KA, J0.N, J1.KA, J1.N);
     const long tn = tn_blocks(J0, J1, shares);
     ProfScope ps(st, kernel_id);
-    if (splits(M, K, b.Nout, b.out.cols)) return launch_bt_tn<0, 0>(J0, J1, tn, tokens, b, M, K, st);
+    // beside the contractions, with four wavefronts: up to half as many tiles unless they are long (2 x 14 x 14 x 256 (28) 29.1 / 28.0 us; 5 x 14 x 14 x 192 (48) 31.1 / 32.5)
+    if (splits(M, K, b.Nout, b.out.cols) && (K >= 1024 || (M + 63) / 64 * ((b.Nout + 63) / 64) <= 32)) return launch_bt_tn<0, 0>(J0, J1, tn, tokens, b, M, K, st);
     // that few tiles are never the wide ones
     if (pick_tile(M, K, b.Nout, 0, 0) == kNarrow) return launch_bt_tn<64, 64>(J0, J1, tn, tokens, b, M, K, st);
     return launch_bt_tn<64, 128>(J0, J1, tn, tokens, b, M, K, st);

@@ -169,10 +169,10 @@ long tile_blocks(long tiles) { return std::is_same<TB, float>::value ? tiles : (
 // which shows from 128 of the others on, and earlier where the contraction is short. Tiles of 64 / split (us, whole calls): 24 tiles, 1 x 7 x 7 x 512
 // 46.1 / 24.4; 72, 2 x 8 x 8 x 768 63.2 / 42.1; 112, 2 x 14 x 14 x 512's gradients 90.5 / 74.0; 80, 3 x 14 x 14 x 256 33.4 / 29.7; 12 rows of K = 3 C, gradients
 // of 1 x 7 x 7 x 768 131.5 / 83.8; beyond: 216, 7 x 7 x 7 x 768 67.7 / 79.1; 117 of K = 192, 1 x 28 x 28 x 192 26.7 / 27.9, 104 of K = 128, gradients of 1 x
-// 28 x 28 x 128 36.4 / 38.5.
+// 28 x 28 x 128 36.4 / 38.5, 60 of K = 128, 1 x 40 x 24 x 128 24.4 / 26.1 (36, 1 x 24 x 24 x 128 23.3 / 22.9).
 bool splits(long M, int N, int K, int N1 = 0)
 {
-    return K >= 64 && N % 32 == 0 && N1 % 32 == 0 && K % 16 == 0 && (M + 63) / 64 * ((N + 63) / 64 + (N1 + 63) / 64) <= (K >= 256 ? 128 : 64);
+    return K >= 64 && N % 32 == 0 && N1 % 32 == 0 && K % 16 == 0 && (M + 63) / 64 * ((N + 63) / 64 + (N1 + 63) / 64) <= (K >= 256 ? 128 : K > 128 ? 64 : 40);
 }
 
 // Rows of its tiles, 16 or 32: by the rounds of 256 workgroups (2 x 8 x 8 x 768 42.1 / 47.1 us), the larger where they take the same, which read less
