@@ -1138,8 +1138,10 @@ int gemm_bt_tn(const GemmTn &J0, const GemmTn &J1, const GemmHalf &b, long M, in
     const int tokens = tn_share_tokens(M, J0.KA, J0.N, J1.KA, J1.N), shares = gemm_tn_shares(M, J0.KA, J0.N, J1.KA, J1.N);
     const long tn = tn_blocks(J0, J1, shares);
     ProfScope ps(st, kernel_id);
-    // beside the contractions, with four wavefronts: up to half as many tiles unless they are long (2 x 14 x 14 x 256 (28) 29.1 / 28.0 us; 5 x 14 x 14 x 192 (48) 31.1 / 32.5)
-    if (splits(M, K, b.Nout, b.out.cols) && (K >= 1024 || (M + 63) / 64 * ((b.Nout + 63) / 64) <= 32)) return launch_bt_tn<0, 0>(J0, J1, tn, tokens, b, M, K, st);
+    // beside the contractions, with four wavefronts, up to half as many tiles unless the walk is long; then up to as many as it has steps of 16, or 112. Tiles, whole call with
+    // tiles of 64 / split (us): K = 768 (28) 29.1 / 28.0; K = 576 (48) 31.1 / 32.5; K = 1152 (60) 46.3 / 45.8, (72) 36.2 / 35.6 and 47.4 / 47.6, (96) 37.1 / 37.7, (114) 44.4 / 48.3;
+    // K = 1536 (96) 52.0 / 50.6, (104) 41.2 / 42.7, (112) 64.3 / 66.7; K = 2304 (84) 49.5 / 44.2, (108) 73.1 / 72.8, (120) 73.7 / 74.5.
+    if (splits(M, K, b.Nout, b.out.cols) && (M + 63) / 64 * ((b.Nout + 63) / 64) <= (K >= 1024 ? std::min(K / 16, 112) : 32)) return launch_bt_tn<0, 0>(J0, J1, tn, tokens, b, M, K, st);
     // that few tiles are never the wide ones
     if (pick_tile(M, K, b.Nout, 0, 0) == kNarrow) return launch_bt_tn<64, 64>(J0, J1, tn, tokens, b, M, K, st);
     return launch_bt_tn<64, 128>(J0, J1, tn, tokens, b, M, K, st);
