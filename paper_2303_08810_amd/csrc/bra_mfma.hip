@@ -1714,8 +1714,7 @@ int launch_qkv(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const MfmaWs 
 
 // Q, K, V at C = 64 with the routing from pooled X in the same launch, for the layers whose regions are pooled beforehand.  Wavefronts take 16 tokens at
 // a time on their own, all weights in LDS (proj_tile).  k_qkv, whose two tiles a workgroup are a chain of staging, products and stores on one and a half
-// wavefronts per SIMD, took 12.2 us for 32768 tokens however its tiles were dealt out, this 11.6, of which the routing by itself 6.2.  Layers before / now: 1 x 128 x 128,
-// k = 4 28.1 / 27.4 us, 8 x 128 x 128, k = 2 75.5 / 73.4, 33 x 64 x 64, k = 2 63.6 / 61.3, 2 x 128 x 128, k = 4 38.6 / 38.3.
+// wavefronts per SIMD, took 12.2 us for 32768 tokens however its tiles were dealt out, this 11.6, of which the routing by itself 6.2.
 __global__ __launch_bounds__(256, 4) void k_proj_route(const bf16_t *__restrict__ X, long M, int per_group, GemmOut out, PrepArgs prep)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1751,11 +1750,18 @@ __global__ __launch_bounds__(256, 4) void k_proj_route(const bf16_t *__restrict_
     }
 }
 
+// From more than one tile of 16 for each wavefront of the launch on: with one, nothing is requested ahead and all weights are staged for it.  Layers with
+// k_qkv / so (us): 1 x 128 x 128, k = 4 26.3 / 26.5, 2 images 34.6 / 35.0, 3 47.0 / 45.8, 4 57.5 / 55.4, 6 79.0 / 76.3; 2 x 112 x 112, S = 7, k = 4 34.2 / 34.0, 3 images, k = 1 31.6 / 29.9;
+// 10 x 64 x 64, k = 2 30.3 / 28.8, 24 images 47.4 / 45.1.
+constexpr long kProjSlots = 512;         // workgroups of four wavefronts, two per compute unit
+
+bool proj_route_pays(const Dims &D) { return (long)D.B * D.N > 16 * 4 * kProjSlots; }
+
 int launch_proj_route(const Dims &D, const bf16_t *X, const MfmaWs &w, const PrepArgs &prep, hipStream_t st, float qscale)
 {
     const long M = (long)D.B * D.N, tiles = (M + 15) / 16;
     // two workgroups per compute unit: layer of 4 x 128 x 128, k = 4 58.8 us, with four 61.0; 10 x 64 x 128, k = 2 44.7 / 46.1; 33 x 64 x 64, k = 2 61.3 / 60.3
-    const long slots = 512, per = 4 * ((tiles + 4 * slots - 1) / (4 * slots)), groups = (tiles + per - 1) / per;
+    const long per = 4 * ((tiles + 4 * kProjSlots - 1) / (4 * kProjSlots)), groups = (tiles + per - 1) / per;
     const size_t smem = std::max(ProjLds<64, 192, false>::bytes, RouteSmem<64>::bytes);
     static bool opted = false;
     if (!lds_opt_in(k_proj_route, opted)) return BRA_ERR_LAUNCH;
@@ -1836,7 +1842,7 @@ int forward_c(const Dims &D, const bf16_t *X, const bf16_t *Wqkv, const bf16_t *
             prep.route_items = D.B * ((D.R + 15) / 16);
             prep.dims = D;
         }
-        int rc = C == 64 && route_with_qkv ? launch_proj_route(D, X, w, prep, st, q32 ? c_exp : 1.0f)
+        int rc = C == 64 && route_with_qkv && proj_route_pays(D) ? launch_proj_route(D, X, w, prep, st, q32 ? c_exp : 1.0f)
                                            : launch_qkv<C>(D, X, Wqkv, w, pooled, prep, st, q32 ? c_exp : 1.0f);
         if (rc != BRA_OK) return rc;
         if (pooled) {
