@@ -140,5 +140,90 @@ __device__ __forceinline__ void park_sums(const RegionHalo &r, const Dims &D, fl
     }
 }
 
+// A slice of 32 channels of a whole image in LDS, `pitch` elements per token: items of 4 x 4 outputs of 16 channels on 16 lanes, a wavefront has two
+// items (`first`, the same for all its lanes, and the next one) of both halves of the channels.  Tokens outside the image read `zero` (16 bytes of zeros).
+// The last ones of a side of 4 or more end with the image: outputs that they share with the ones before come out twice, the same.
+struct SliceItem {
+    int y0, x0, at;                      // first output; this lane's column of the window's first row
+    int rows, columns;                   // how many of the first ones the items before have too
+    bool mine, left, right;              // there is such an item; the column lies in the image, the one 4 further does
+
+    __device__ __forceinline__ SliceItem(const Dims &D, int first, int items, int quads, float q_inv, int lane, int pitch)
+    {
+        const int s = lane % 16, m = first + lane / 32, item = min(m, items - 1), strip = mfma::fast_div(item, q_inv);
+        mine = m < items;
+        const int quad = item - strip * quads;
+        y0 = max(min(4 * strip, D.H - 4), 0);
+        x0 = max(min(4 * quad, D.W - 4), 0);
+        rows = 4 * strip - y0;
+        columns = 4 * quad - x0;
+        const int xl = x0 - 2 + s / 4;
+        left = xl >= 0 && xl < D.W;
+        right = xl + 4 < D.W;
+        at = ((y0 - 2) * D.W + xl) * pitch + 16 * (lane / 16 % 2) + 4 * (s % 4);
+    }
+    // Row y of the window (0 .. 7) as pairs of columns (j, j + 1) of the lane's channel.
+    __device__ __forceinline__ void pairs(const bf16_t *slice, const bf16_t *zero, int y, const Dims &D, int pitch, unsigned (&p)[7]) const
+    {
+        const bool in = (unsigned)(y0 + y - 2) < (unsigned)D.H;
+        const bf16_t *from = slice + at + y * D.W * pitch;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const mfma::u32x2 v = __builtin_bit_cast(mfma::u32x2, mfma::lds_read_tr16(in && (half ? right : left) ? from + 4 * half * pitch : zero));
+            p[4 * half] = v[0];
+            p[4 * half + 2] = v[1];
+        }
+#pragma unroll
+        for (int j = 1; j < 7; j += 2) p[j] = __builtin_amdgcn_alignbit(p[j + 1], p[j - 1], 16);
+    }
+    // The 16 sums of the lane's channel.
+    __device__ __forceinline__ void sums(const bf16_t *slice, const bf16_t *zero, const Dims &D, int pitch, const unsigned (&w)[5][3], float (&o)[4][4]) const
+    {
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[a][c] = 0.f;
+#pragma unroll
+        for (int y = 0; y < 8; ++y) {
+            unsigned p[7];
+            pairs(slice, zero, y, D, pitch, p);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                if (y < a || y > a + 4) continue;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    o[a][c] = dot2(w[y - a][0], p[c], o[a][c]);
+                    o[a][c] = dot2(w[y - a][1], p[c + 2], o[a][c]);
+                    o[a][c] = dot2(w[y - a][2], p[c + 3], o[a][c]);
+                }
+            }
+        }
+    }
+    // Tap gradients: the image's own V against the window in dO; acc[5 ky + kx] belongs to tap 24 - (5 ky + kx).  Tokens of V that the items before have are
+    // zeros here: they meet what those meet, so that an infinity of dO reaches no other taps.  Sides of at least 4.
+    __device__ __forceinline__ void taps(const bf16_t *dO, const bf16_t *V, const bf16_t *zero, const Dims &D, int pitch, float (&acc)[25]) const
+    {
+        const bool own = mine && (int)(threadIdx.x % 16 / 4) >= columns;
+        mfma::u32x2 v[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+            v[a] = __builtin_bit_cast(mfma::u32x2, mfma::lds_read_tr16(own && a >= rows ? V + at + (2 + (2 + a) * D.W) * pitch : zero));
+#pragma unroll
+        for (int y = 0; y < 8; ++y) {
+            unsigned p[7];
+            pairs(dO, zero, y, D, pitch, p);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                if (y < a || y > a + 4) continue;
+#pragma unroll
+                for (int j = 0; j < 5; ++j) {
+                    acc[5 * (y - a) + j] = dot2(v[a][0], p[j], acc[5 * (y - a) + j]);
+                    acc[5 * (y - a) + j] = dot2(v[a][1], p[j + 2], acc[5 * (y - a) + j]);
+                }
+            }
+        }
+    }
+};
+
 }  // namespace lce
 }  // namespace bra

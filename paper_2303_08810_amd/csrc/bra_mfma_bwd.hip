@@ -10,9 +10,9 @@
 //     dK = dS^T Q,  dV = P^T dO        key side: from the query regions routed to a KEY region, found in Ir, with P and
 //                                      dS recomputed from the statistics and sums in registers: no atomic adds
 //                                      (k_attn_bwd_map on small maps, else k_attn_bwd_q and k_attn_bwd_kv)
-//     O += LCE(V)                      in the query side, in the key side's launch, or k_lce_backward
-//     dV += LCE^T(dO) (the correlation with the taps reversed; also in the key side) and
-//     dWlce[c][ky][kx] = sum_t dO[t][c] V[t + (ky - 2, kx - 2)][c]       in the query side's launch, or k_lce_backward
+//     O += LCE(V)                      in the query side, in the key side's launch, at the end of k_attn_bwd_map, or k_lce_backward
+//     dV += LCE^T(dO) (the correlation with the taps reversed; also in the key side and k_attn_bwd_map) and
+//     dWlce[c][ky][kx] = sum_t dO[t][c] V[t + (ky - 2, kx - 2)][c]       in the query side's launch, k_attn_bwd_map, or k_lce_backward
 //     dX = [dQ | dK | dV] Wqkv^T,  dWqkv = X^T [dQ | dK | dV]      k_bwd_proj, one pass over the gradient map, or k_gemm_bt_tn
 //     dWo = O^T dY                     k_bwd_proj or k_gemm_tn (contraction over tokens)
 // All products take bf16 operands and accumulate in float32; dQ, dK, dV and dO are rounded to
@@ -216,6 +216,9 @@ bool fused_projection(int C) { return C == 64; }
 // Partial matrices of dWqkv and of dWo.
 int weight_parts(long M, int C) { return fused_projection(C) ? proj_plan(M).groups : gemm_tn_shares(M, C, 3 * C, C, C); }
 
+// Arrays of 25 C floats that the tap gradients come in.
+int tap_parts(const Dims &D) { return attn_bwd_map_ok(D) && attn_bwd_map_convolves(D) ? D.B : lce::lce_grad_groups_bf16(D, 3 * D.C); }
+
 struct BwdWs {
     bf16_t *q, *k, *v, *dO, *o, *dqkv;
     float *lse, *dsum, *part_qkv, *part_o, *part_lce;
@@ -245,7 +248,7 @@ BwdWs carve_bwd(const Dims &D, void *ws)
     const int parts = weight_parts(M, D.C);
     w.part_qkv = (float *)take((size_t)parts * 3 * C * C * 4);
     w.part_o = (float *)take((size_t)parts * C * C * 4);
-    w.part_lce = (float *)take((size_t)lce::lce_grad_groups_bf16(D, 3 * D.C) * 25 * C * 4);
+    w.part_lce = (float *)take((size_t)tap_parts(D) * 25 * C * 4);
     w.bytes = off;
     return w;
 }
@@ -259,8 +262,8 @@ int attention_and_lce(const Dims &D, const BwdWs &w, const int32_t *Ir, const bf
     const lce::BackwardJobs L = lce::backward_jobs(D, w.dO, w.v, Wlce, w.o, w.dqkv + 2 * D.C, w.dqkv + D.C, 3 * D.C, w.part_lce);
     const AttnBwdArgs A = {w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, w.lse, w.dsum};
     const bool map = attn_bwd_map_ok(D);
-    const int rc = map ? launch_attn_bwd_map(D, w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, K_GEN_BACKWARD, st) : launch_attn_bwd(D, A, L, K_GEN_BACKWARD, st);
-    if (rc != BRA_OK || (!map && (L.beside || attn_bwd_convolves(D, L)))) return rc;
+    const int rc = map ? launch_attn_bwd_map(D, w.q, w.k, w.v, w.dO, Ir, w.o, w.dqkv, Wlce, w.part_lce, K_GEN_BACKWARD, st) : launch_attn_bwd(D, A, L, K_GEN_BACKWARD, st);
+    if (rc != BRA_OK || (map ? attn_bwd_map_convolves(D) : L.beside || attn_bwd_convolves(D, L))) return rc;
     return lce::lce_backward_bf16(D, L, K_GEN_BACKWARD, st);
 }
 
@@ -319,7 +322,7 @@ int mfma_backward(const Dims &D, const void *X, const void *Wqkv, const void *Wo
         const int parts = weight_parts(M, C);
         const ReduceJob j0 = reduce_job(w.part_qkv, dWqkv, parts, 3 * C * C);
         const ReduceJob j1 = reduce_job(w.part_o, dWo, parts, C * C);
-        const ReduceJob j2 = reduce_job(w.part_lce, dWlce, lce::lce_grad_groups_bf16(D, 3 * D.C), 25 * C);
+        const ReduceJob j2 = reduce_job(w.part_lce, dWlce, tap_parts(D), 25 * C);
         ProfScope ps(st, K_GEN_BACKWARD);
         hipLaunchKernelGGL(k_reduce_parts, dim3(j0.blocks + j1.blocks + j2.blocks), dim3(256), 0, st, j0, j1, j2);
         if (!launched()) return BRA_ERR_LAUNCH;

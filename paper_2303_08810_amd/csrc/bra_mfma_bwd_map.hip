@@ -7,9 +7,14 @@
 // regions (O, dQ and the row statistics, which stay in LDS) and then over the key regions (dK, dV), all rows found by
 // index in LDS.  Arithmetic, operand layouts and rounding are those of the per-region kernels.
 // 67 us at that shape.  Bound by LDS reads: every row is read as an operand row and by the transposing read on each side.
+// The depth-wise parts come from the same slices at its end, in registers while other wavefronts still have key regions; they were a launch that read V, dO, O and
+// dV again.  Whole gradient (us) with that launch / now: 64 x 14 x 14 x 384, k = 16 168.4 / 167.3 (on another machine 158.8 / 156.2), 64 x 14 x 14 x 256 109.4 / 106.2,
+// 128 x 14 x 14 x 64 63.3 / 57.3, 32 x 14 x 28 x 256 105.6 / 99.8, 128 x 7 x 7 x 256, k = 9 109.8 / 102.8, 512 x 7 x 7 x 64 101.2 / 94.3.  At its head instead, parked in the places of O and
+// dV in 2-byte stores: 161 / 169 at the first shape; one after the other behind the barrier 166.
 // (Scores on 4x4x4 products, so that none of the 16 tile columns idles at 4 tokens per region, read the same bytes:
 // 67 us at 128 registers, 84 at 144.)
 #include "bra_bwd_dev.h"
+#include "bra_lce_region.h"
 #include "bra_mfma_bwd_map.h"
 
 namespace bra {
@@ -20,12 +25,14 @@ namespace {
 
 constexpr int kPitch = 40;       // 32 channels + 8: rows of 80 bytes
 constexpr int kWaveBytes = 768;  // of a wavefront's own: rows of a block, lse and D of its queries
+constexpr int kParkPitch = 36;   // floats per token of the depth-wise sums
+constexpr size_t kTapBytes = 25 * 32 * 4;   // tap gradients of a wavefront
 
 struct MapSmem {
-    size_t rows, first, list, start, count, lse, dsum, wave, bytes;
+    size_t rows, first, list, start, count, lse, dsum, wave, zero, bytes;
 };
 
-__host__ __device__ inline MapSmem map_smem(int N, int R, int k, int waves)
+__host__ __device__ inline MapSmem map_smem(int N, int R, int k, int waves, bool conv)
 {
     MapSmem m;
     size_t off = (size_t)4 * N * kPitch * 2;
@@ -38,7 +45,8 @@ __host__ __device__ inline MapSmem map_smem(int N, int R, int k, int waves)
     m.lse = take((size_t)N * 4);
     m.dsum = take((size_t)N * 4);
     m.wave = take((size_t)waves * kWaveBytes);
-    m.bytes = off;
+    m.zero = take(16);
+    m.bytes = conv && off < waves * kTapBytes ? waves * kTapBytes : off;
     return m;
 }
 
@@ -71,6 +79,7 @@ struct MapWork {
     int *start, *named;              // key region j is named by query regions named[start[j] .. start[j + 1])
     float *lse, *dsum;               // [N]: row statistics
     char *wave_mem;
+    bf16_t *zero;                    // 16 bytes of zeros
 };
 
 template <int NW>
@@ -84,7 +93,7 @@ __device__ __forceinline__ bool map_stage(MapWork &w, char *smem, const bf16_t *
     w.h = wid % D.heads;
     w.b = wid / D.heads;
     const int C = D.C, entries = D.R * D.k;
-    const MapSmem L = map_smem(D.N, D.R, D.k, NW);
+    const MapSmem L = map_smem(D.N, D.R, D.k, NW, false);
     w.Qs = (bf16_t *)smem;
     w.Ks = w.Qs + (size_t)D.N * kPitch;
     w.Vs = w.Ks + (size_t)D.N * kPitch;
@@ -98,6 +107,8 @@ __device__ __forceinline__ bool map_stage(MapWork &w, char *smem, const bf16_t *
     w.dsum = (float *)(smem + L.dsum);
     const int tid = threadIdx.x;
     w.wave_mem = smem + L.wave + (tid / kWave) * kWaveBytes;
+    w.zero = (bf16_t *)(smem + L.zero);
+    if (tid < 8) w.zero[tid] = 0;
     const size_t img = (size_t)w.b * D.N * C + 32 * w.h;
     const float s_inv = 1.0f / (float)D.S;
     // the head's slices of the four maps
@@ -155,11 +166,13 @@ __device__ __forceinline__ bool map_stage(MapWork &w, char *smem, const bf16_t *
     return true;      // the key side reads the list behind the next barrier
 }
 
-template <int NW>
+// CONV: with the depth-wise parts.
+template <int NW, bool CONV>
 __global__ __launch_bounds__(64 * NW, 4) void k_attn_bwd_map(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                           const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
                                                           const int32_t *__restrict__ Ir, bf16_t *__restrict__ O,
-                                                          bf16_t *__restrict__ dQKV, Dims D, int total)
+                                                          bf16_t *__restrict__ dQKV, const bf16_t *__restrict__ Wlce,
+                                                          float *__restrict__ PartLce, Dims D, int total)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     MapWork w;
@@ -319,27 +332,115 @@ __global__ __launch_bounds__(64 * NW, 4) void k_attn_bwd_map(const bf16_t *__res
             *(u32x2 *)(krow + C + 16) = pack4(av[1]);
         }
     }
+    if (!CONV) return;
+    // ---- the depth-wise parts of the head's channels, from the slices (SliceItem; a wavefront has one pair of items at most), in registers while
+    // others still have key regions
+    const int quads = (D.W + 3) / 4, items = quads * ((D.H + 3) / 4), pairs = (items + 1) / 2;
+    const int first_taps = 2 * pairs <= NW ? pairs : 0;      // with wavefronts to spare, others take the tap gradients
+    const float q_inv = 1.0f / (float)quads;
+    float o[2][4][4], acc[25];
+    if (wave < pairs) {
+        const lce::SliceItem item(D, 2 * wave, items, quads, q_inv, lane, kPitch);
+        const lce::LaneTaps<false> forward(Wlce, 32 * h + lane % 32);
+        const lce::LaneTaps<true> reversed(Wlce, 32 * h + lane % 32);
+        unsigned wt[5][3];
+        forward.operands(wt);
+        item.sums(Vs, w.zero, D, kPitch, wt, o[0]);
+        reversed.operands(wt);
+        item.sums(Gs, w.zero, D, kPitch, wt, o[1]);
+    }
+    const bool has_taps = wave >= first_taps && wave - first_taps < pairs;
+    if (has_taps) {
+#pragma unroll
+        for (int t = 0; t < 25; ++t) acc[t] = 0.f;
+        lce::SliceItem(D, 2 * (wave - first_taps), items, quads, q_inv, lane, kPitch).taps(Gs, Vs, w.zero, D, kPitch, acc);
+    }
+    __syncthreads();                             // the slices have been read; O and dV are there
+    float *parked = (float *)smem;               // [2][N][kParkPitch], where the slices were
+    constexpr int CHUNKS = 2;
+    u32x4 *to[CHUNKS][2], add[CHUNKS][2];
+    auto places = [&](int e, u32x4 *(&at)[2]) {
+        at[0] = (u32x4 *)(O + img + (size_t)(e / 4) * C + e % 4 * 8);
+        at[1] = (u32x4 *)(dQKV + ((size_t)b * D.N + e / 4) * 3 * C + 2 * C + 32 * h + e % 4 * 8);
+    };
+    const int chunks = 4 * D.N;
+#pragma unroll
+    for (int u = 0; u < CHUNKS; ++u) {
+        places(min((int)threadIdx.x + 64 * NW * u, chunks - 1), to[u]);
+        add[u][0] = *to[u][0];
+        add[u][1] = *to[u][1];
+    }
+    if (wave < pairs) {
+        const lce::SliceItem item(D, 2 * wave, items, quads, q_inv, lane, kPitch);
+        float *at = parked + (item.y0 * D.W + item.x0) * kParkPitch + lane % 32;
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (item.mine && item.y0 + a < D.H && item.x0 + c < D.W) {
+                    at[(a * D.W + c) * kParkPitch] = o[0][a][c];
+                    at[(D.N + a * D.W + c) * kParkPitch] = o[1][a][c];
+                }
+    }
+    __syncthreads();
+    auto sum = [&](int e, int which, u32x4 v) {
+        const f32x4 *f = (const f32x4 *)(parked + (which * D.N + e / 4) * kParkPitch + e % 4 * 8);
+        const f32x4 lo = f[0], hi = f[1];
+        const float r[8] = {bf16_lo(v[0]) + lo[0], bf16_hi(v[0]) + lo[1], bf16_lo(v[1]) + lo[2], bf16_hi(v[1]) + lo[3],
+                            bf16_lo(v[2]) + hi[0], bf16_hi(v[2]) + hi[1], bf16_lo(v[3]) + hi[2], bf16_hi(v[3]) + hi[3]};
+        return __builtin_bit_cast(u32x4, pack8(r));
+    };
+#pragma unroll
+    for (int u = 0; u < CHUNKS; ++u) {
+        const int e = threadIdx.x + 64 * NW * u;
+        if (e >= chunks) break;
+        *to[u][0] = sum(e, 0, add[u][0]);
+        *to[u][1] = sum(e, 1, add[u][1]);
+    }
+    for (int e = threadIdx.x + 64 * NW * CHUNKS; e < chunks; e += 64 * NW) {
+        u32x4 *at[2];
+        places(e, at);
+        *at[0] = sum(e, 0, *at[0]);
+        *at[1] = sum(e, 1, *at[1]);
+    }
+    // ---- the image's sums of the tap gradients
+    float *sums = (float *)smem;                 // [pair of items][tap][channel]
+    __syncthreads();
+    if (has_taps) {
+#pragma unroll
+        for (int t = 0; t < 25; ++t) {
+            const float v = acc[t] + __shfl_xor(acc[t], 32);
+            if (lane < 32) sums[((wave - first_taps) * 25 + t) * 32 + lane] = v;
+        }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 25 * 32; e += 64 * NW) {
+        const int c = e / 25, t = e - 25 * c;
+        float s = 0.f;
+        for (int u = 0; u < pairs; ++u) s += sums[(u * 25 + 24 - t) * 32 + c];
+        PartLce[((size_t)b * C + 32 * h) * 25 + e] = s;
+    }
 }
 
 int waves_of(const Dims &D)
 {
     // 16 wavefronts where only one workgroup fits a compute unit's LDS or there is at most one per unit; else two of 8
-    return map_smem(D.N, D.R, D.k, 8).bytes > (size_t)kMaxLds / 2 || (long)D.B * D.heads <= 256 ? 16 : 8;
+    return map_smem(D.N, D.R, D.k, 8, false).bytes > (size_t)kMaxLds / 2 || (long)D.B * D.heads <= 256 ? 16 : 8;
 }
 
-template <int NW>
+template <int NW, bool CONV>
 int launch(const Dims &D, const bf16_t *Q, const bf16_t *K, const bf16_t *V, const bf16_t *dO, const int32_t *Ir, bf16_t *O,
-           bf16_t *dQKV, hipStream_t st)
+           bf16_t *dQKV, const bf16_t *Wlce, float *PartLce, hipStream_t st)
 {
     static bool opted = false;
     if (!opted) {
-        if (hipFuncSetAttribute((const void *)k_attn_bwd_map<NW>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess)
+        if (hipFuncSetAttribute((const void *)k_attn_bwd_map<NW, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess)
             return BRA_ERR_LAUNCH;
         opted = true;
     }
     const int total = D.B * D.heads;
-    hipLaunchKernelGGL(k_attn_bwd_map<NW>, dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * NW), map_smem(D.N, D.R, D.k, NW).bytes,
-                       st, Q, K, V, dO, Ir, O, dQKV, D, total);
+    hipLaunchKernelGGL((k_attn_bwd_map<NW, CONV>), dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * NW), map_smem(D.N, D.R, D.k, NW, CONV).bytes,
+                       st, Q, K, V, dO, Ir, O, dQKV, Wlce, PartLce, D, total);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -351,15 +452,19 @@ bool attn_bwd_map_ok(const Dims &D)
     // and few workgroups leave the chip idle: by images / by regions, whole gradient (us), 128 of them: 64 x 7 x 7 x 64, k = 16
     // 42.0 / 37.1; 64 x 14 x 14 x 64, k = 44 88 / 78; 64 x 14 x 28 x 64, k = 16 80 / 73; 192: 24 x 14 x 14 x 256, k = 16 71.6 /
     // 76.9; 8 x 7 x 7 x 768, k = 44 70.8 / 81.2
-    return D.d == 32 && (long)D.B * D.heads >= 160 && D.n <= 8 && D.k > 1 && (long)D.B * D.heads < 0x7ffffff0L && map_smem(D.N, D.R, D.k, 16).bytes <= (size_t)kMaxLds;
+    return D.d == 32 && (long)D.B * D.heads >= 160 && D.n <= 8 && D.k > 1 && (long)D.B * D.heads < 0x7ffffff0L && map_smem(D.N, D.R, D.k, 16, false).bytes <= (size_t)kMaxLds;
 }
 
+// Wherever each pair of items has a wavefront, on sides that the items' tap gradients take.
+bool attn_bwd_map_convolves(const Dims &D) { return D.H >= 4 && D.W >= 4 && (D.W + 3) / 4 * ((D.H + 3) / 4) <= 2 * waves_of(D); }
+
 int launch_attn_bwd_map(const Dims &D, const bf16_t *Q, const bf16_t *K, const bf16_t *V, const bf16_t *dO, const int32_t *Ir,
-                        bf16_t *O, bf16_t *dQKV, int kernel_id, hipStream_t st)
+                        bf16_t *O, bf16_t *dQKV, const bf16_t *Wlce, float *PartLce, int kernel_id, hipStream_t st)
 {
     ProfScope ps(st, kernel_id);
-    if (waves_of(D) == 16) return launch<16>(D, Q, K, V, dO, Ir, O, dQKV, st);
-    return launch<8>(D, Q, K, V, dO, Ir, O, dQKV, st);
+    const bool conv = attn_bwd_map_convolves(D);
+    const auto run = waves_of(D) == 16 ? (conv ? launch<16, true> : launch<16, false>) : conv ? launch<8, true> : launch<8, false>;
+    return run(D, Q, K, V, dO, Ir, O, dQKV, Wlce, PartLce, st);
 }
 
 }  // namespace bra

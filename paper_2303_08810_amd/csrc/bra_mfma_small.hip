@@ -468,41 +468,15 @@ __device__ __forceinline__ void map_lce(const AttnArgs &A, const Dims &D, const 
     const int quads = (D.W + 3) / 4, items = quads * ((D.H + 3) / 4);
     const float q_inv = 1.0f / (float)quads;
     for (int first = 2 * (threadIdx.x / kWave); first < items; first += kMapThreads / 32) {      // the same for all lanes of a wavefront
-        const int mine = first + grp / 2 % 2, item = min(mine, items - 1);
-        const int strip = fast_div(item, q_inv), y0 = 4 * strip, x0 = 4 * (item - strip * quads);
-        const int xl = x0 - 2 + s / 4, col = 16 * (grp % 2) + 4 * (s % 4);
-        const bool left = xl >= 0 && xl < D.W, right = xl + 4 < D.W;
-        const bf16_t *at = w.Vs + ((y0 - 2) * D.W + xl) * kMapPitch + col;
+        const lce::SliceItem item(D, first, items, quads, q_inv, threadIdx.x % kWave, kMapPitch);
         float o[4][4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) o[a][c] = 0.f;
-#pragma unroll
-        for (int y = 0; y < 8; ++y, at += D.W * kMapPitch) {
-            const bool in = (unsigned)(y0 + y - 2) < (unsigned)D.H;
-            const u32x2 v0 = __builtin_bit_cast(u32x2, lds_read_tr16(in && left ? at : w.zero));
-            const u32x2 v1 = __builtin_bit_cast(u32x2, lds_read_tr16(in && right ? at + 4 * kMapPitch : w.zero));
-            unsigned p[7] = {v0[0], 0u, v0[1], 0u, v1[0], 0u, v1[1]};       // columns (j, j + 1)
-#pragma unroll
-            for (int j = 1; j < 7; j += 2) p[j] = __builtin_amdgcn_alignbit(p[j + 1], p[j - 1], 16);
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                if (y < a || y > a + 4) continue;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    o[a][c] = dot2(wt[y - a][0], p[c], o[a][c]);
-                    o[a][c] = dot2(wt[y - a][1], p[c + 2], o[a][c]);
-                    o[a][c] = dot2(wt[y - a][2], p[c + 3], o[a][c]);
-                }
-            }
-        }
-        float *to = w.Ls + (y0 * D.W + x0) * kMapLcePitch + ch;
+        item.sums(w.Vs, w.zero, D, kMapPitch, wt, o);
+        float *to = w.Ls + (item.y0 * D.W + item.x0) * kMapLcePitch + ch;
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                if (mine < items && y0 + a < D.H && x0 + c < D.W) to[(a * D.W + c) * kMapLcePitch] = o[a][c];
+                if (item.mine && item.y0 + a < D.H && item.x0 + c < D.W) to[(a * D.W + c) * kMapLcePitch] = o[a][c];
     }
     __syncthreads();
 }
