@@ -736,18 +736,17 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_gemm_pair_split(const bf16
     else split_tile<true, false, kSplitWaves>(In1, W1, ldw1, M, K, Nout1, out1, bi - blocks0, smem);
 }
 
-// Nout1: a second product over the same rows.  A round of workgroups, one per compute unit, holds as much as 64 tiles of 64 x 64 and takes about 4 us;
-// those take 0.5 us for 64 of the contraction, so that a short one leaves nothing to gain and a long one pays for a second round.  Tiles of 64 /
-// split (us, whole calls): 12 tiles, gradients of 1 x 7 x 7 x 512 34.1 / 27.0, of 2 x 7 x 7 x 768 46.8 / 38.1; 24, block of 2 x 8 x 8 x 768 73.7 / 60.3; block of
-// 1 x 14 x 14 x 384 45.9 / 40.7; two rounds: K = 2304, gradients of 2 x 14 x 14 x 768 (84) 49.1 / 44.0, but K = 256, 2 x 21 x 21 x 256 (112) 24.4 / 29.7, K = 384,
-// 1 x 28 x 28 x 384 (78) 27.4 / 28.3; K = 192, gradients of 2 x 24 x 24 x 192 29.8 / 31.9.
-bool splits(long M, int K, int Nout, int cols, int Nout1 = 0)
-{
-    const long tiles = (M + 63) / 64 * ((Nout + 63) / 64 + (Nout1 + 63) / 64);
-    return Nout % 32 == 0 && Nout1 % 32 == 0 && cols % 32 == 0 && tiles <= (K >= 1024 ? 128 : K >= 256 ? 64 : 0);
-}
-
 long split_blocks(long M, int Nout) { return (M + 31) / 32 * (Nout / 32); }
+
+// blocks: the workgroups it would take.  A round of them, one per compute unit (98 KB of LDS), takes about 4 us; tiles of 64 x 64 take 0.5 us for 64 of the
+// contraction, so that a short one leaves nothing to gain and only a long one pays for a second round.  Blocks, tiles of 64 / split (us, whole calls): gradients of
+// 1 x 7 x 7 x 512 34.1 / 27.0, of 2 x 7 x 7 x 768 46.8 / 38.1; block of 2 x 8 x 8 x 768 73.7 / 60.3, of 1 x 14 x 14 x 384 45.9 / 40.7; K = 256, forward of 6 x 7 x 7 x 256 (240) 19.9 / 18.8,
+// 8 x 7 x 7 x 256 (312) 20.1 / 20.6, 2 x 14 x 14 x 256 (312) 21.1 / 22.5, 2 x 16 x 16 x 256 (384) 19.4 / 22.5; K = 384, 4 x 7 x 7 x 384 (252) 23.2 / 20.3, 1 x 14 x 21 x 384 (360) 23.7 / 24.1;
+// K = 2304, gradients of 2 x 14 x 14 x 768 (312) 49.1 / 44.0; K = 192, gradients of 2 x 24 x 24 x 192 29.8 / 31.9.
+bool splits(long blocks, int K, int Nout, int cols)
+{
+    return Nout % 32 == 0 && cols % 32 == 0 && blocks <= (K >= 1024 ? 512 : K >= 256 ? 256 : 0);
+}
 
 template <bool BT>
 int launch_split(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, hipStream_t st)
@@ -1026,8 +1025,8 @@ int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, co
         return launch_proj(In, W, ldw, M, K, Nout, out, st);
     }
     ProfScope ps(st, kernel_id);
-    // float32 copies: by the columns that have them, as a product of those alone (bra_route decides on the same bits as bra_forward)
-    if (!regions && splits(M, K, out.f32[0] ? 2 * out.cols : Nout, out.cols)) return launch_split<false>(In, W, ldw, M, K, Nout, out, st);
+    // float32 copies: as with Q, K and V for all callers (bra_route decides on the same bits as bra_forward)
+    if (!regions && splits(split_blocks(M, out.f32[0] ? 3 * out.cols : Nout), K, Nout, out.cols)) return launch_split<false>(In, W, ldw, M, K, Nout, out, st);
     if (regions) return launch_big<true>(In, W, ldw, M, K, Nout, out, *regions, st);
     return launch_big<false>(In, W, ldw, M, K, Nout, out, GemmRegions{}, st);
 }
@@ -1037,12 +1036,12 @@ int gemm_means(const bf16_t *In, const bf16_t *W, int ldw, int K, int Nout, cons
     const long M = (long)means.regions * means.n;
     if (!sizes_ok(M, K, Nout) || out.cols % 32 || K > 4096 || means.n > kMeansMaxTokens) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);
-    // by the columns of Q and K for both callers: bra_route decides on the same bits as bra_forward
-    if (means.n <= 32 && splits(M, K, 2 * out.cols, out.cols)) {
+    // as with Q, K and V for both callers: bra_route decides on the same bits as bra_forward
+    const long each = means.n <= 32 ? 32 / means.n : 0, rows = each ? (means.regions + each - 1) / each : 0;
+    if (each && splits(rows * (3 * out.cols / 32), K, Nout, out.cols)) {
         static bool opted = false;
         if (!opt_in(k_gemm_means_split, opted)) return BRA_ERR_LAUNCH;
-        const long each = 32 / means.n, blocks = (means.regions + each - 1) / each * (Nout / 32);
-        hipLaunchKernelGGL(k_gemm_means_split, dim3((unsigned)blocks), dim3(64 * kSplitWaves), split_bytes<kSplitWaves>(), st, In, W, ldw, K, Nout, out, means);
+        hipLaunchKernelGGL(k_gemm_means_split, dim3((unsigned)(rows * (Nout / 32))), dim3(64 * kSplitWaves), split_bytes<kSplitWaves>(), st, In, W, ldw, K, Nout, out, means);
         return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
     }
     switch (pick_tile(M, K, Nout, 0, 0, means.n)) {
@@ -1058,7 +1057,7 @@ int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout
     if (!sizes_ok(M, K, Nout)) return BRA_ERR_UNSUPPORTED;
     const GemmOut out = {{Out, nullptr, nullptr}, Nout, {nullptr, nullptr}, nullptr, nullptr, 0};
     ProfScope ps(st, kernel_id);
-    if (splits(M, K, Nout, Nout)) return launch_split<true>(In, Wt, ldw, M, K, Nout, out, st);
+    if (splits(split_blocks(M, Nout), K, Nout, Nout)) return launch_split<true>(In, Wt, ldw, M, K, Nout, out, st);
     return launch_big<false, true>(In, Wt, ldw, M, K, Nout, out, GemmRegions{}, st);
 }
 
@@ -1068,7 +1067,7 @@ int gemm_pair(const GemmHalf &a, const GemmHalf &b, long M, int K, int kernel_id
     ProfScope ps(st, kernel_id);
     if (b.Nout == K && proj_ok(M, K, a.Nout, a.out, false) && a.Nout == 3 * K)
         return K == 64 ? launch_proj_t<64, 192, true>(a.In, a.W, a.ldw, M, a.out, st, b) : launch_proj_t<128, 384, true>(a.In, a.W, a.ldw, M, a.out, st, b);
-    if (splits(M, K, a.Nout, a.out.cols, b.Nout) && b.out.cols % 32 == 0) {
+    if (a.Nout % 32 == 0 && splits(split_blocks(M, a.Nout) + split_blocks(M, b.Nout), K, b.Nout, a.out.cols) && b.out.cols % 32 == 0) {
         static bool opted = false;
         if (!opt_in(k_gemm_pair_split, opted)) return BRA_ERR_LAUNCH;
         const long b0 = split_blocks(M, a.Nout), b1 = split_blocks(M, b.Nout);
@@ -1141,7 +1140,7 @@ int gemm_bt_tn(const GemmTn &J0, const GemmTn &J1, const GemmHalf &b, long M, in
     // beside the contractions, with four wavefronts, up to half as many tiles unless the walk is long; then up to as many as it has steps of 16, or 112. Tiles, whole call with
     // tiles of 64 / split (us): K = 768 (28) 29.1 / 28.0; K = 576 (48) 31.1 / 32.5; K = 1152 (60) 46.3 / 45.8, (72) 36.2 / 35.6 and 47.4 / 47.6, (96) 37.1 / 37.7, (114) 44.4 / 48.3;
     // K = 1536 (96) 52.0 / 50.6, (104) 41.2 / 42.7, (112) 64.3 / 66.7; K = 2304 (84) 49.5 / 44.2, (108) 73.1 / 72.8, (120) 73.7 / 74.5.
-    if (splits(M, K, b.Nout, b.out.cols) && (M + 63) / 64 * ((b.Nout + 63) / 64) <= (K >= 1024 ? std::min(K / 16, 112) : 32)) return launch_bt_tn<0, 0>(J0, J1, tn, tokens, b, M, K, st);
+    if (splits(split_blocks(M, b.Nout), K, b.Nout, b.out.cols) && (M + 63) / 64 * ((b.Nout + 63) / 64) <= (K >= 1024 ? std::min(K / 16, 112) : 32)) return launch_bt_tn<0, 0>(J0, J1, tn, tokens, b, M, K, st);
     // that few tiles are never the wide ones
     if (pick_tile(M, K, b.Nout, 0, 0) == kNarrow) return launch_bt_tn<64, 64>(J0, J1, tn, tokens, b, M, K, st);
     return launch_bt_tn<64, 128>(J0, J1, tn, tokens, b, M, K, st);

@@ -19,8 +19,10 @@ SHAPES = [  # (B, H, W, C, heads, S, k)
     (1, 16, 16, 768, 12, 4, 3),      # 16 tokens
     (1, 21, 12, 448, 7, 3, 2),       # 28
     (1, 32, 8, 256, 8, 4, 2),        # 16
-    (1, 32, 16, 256, 8, 4, 2),       # 32: 64 tiles
-    (1, 36, 16, 256, 8, 4, 2),       # 36: the other kernel
+    (1, 12, 24, 256, 8, 3, 2),       # 32: 216 workgroups
+    (1, 32, 16, 256, 8, 4, 2),       # 384: the other kernel
+    (1, 36, 16, 256, 8, 4, 2),       # 36 tokens: too
+    (4, 10, 10, 256, 8, 5, 2),       # 312 for Q, K and V, 208 for Q and K: the other kernel for both
     (1, 10, 10, 1088, 17, 5, 2),     # 34 steps
 ]
 
