@@ -111,6 +111,17 @@ __device__ __forceinline__ bool map_stage(MapWork &w, char *smem, const bf16_t *
     if (tid < 8) w.zero[tid] = 0;
     const size_t img = (size_t)w.b * D.N * C + 32 * w.h;
     const float s_inv = 1.0f / (float)D.S;
+    // f(entry, region it names) for this thread's routing entries; the first ones are requested ahead of the slices
+    const int32_t *irb = Ir + (size_t)w.b * entries;
+    int named[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) named[u] = irb[min(tid + T * u, entries - 1)];
+    auto each_entry = [&](auto f) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (tid + T * u < entries) f(tid + T * u, region_index(named[u], D.R));
+        for (int e = tid + 2 * T; e < entries; e += T) f(e, region_index(irb[e], D.R));
+    };
     // the head's slices of the four maps
     const int chunks = D.N * 4;
     for (int c0 = 0; c0 < chunks; c0 += 2 * T) {
@@ -142,27 +153,27 @@ __device__ __forceinline__ bool map_stage(MapWork &w, char *smem, const bf16_t *
     __syncthreads();
     // routing rows as token numbers, and per key region the query regions that name it, in the order of the entries:
     // arrival order through a counter, then a rank among the (few) entries of the same region
-    const int32_t *irb = Ir + (size_t)w.b * entries;
-    for (int e = tid; e < entries; e += T) {
-        const int j = region_index(irb[e], D.R);
+    each_entry([&](int e, int j) {
         w.rows[e] = w.first[j];
         arrived[e] = atomicAdd(&count[j], 1);
-    }
+    });
     __syncthreads();
     for (int j = tid; j <= D.R; j += T) {
         int s = 0;
+#pragma unroll 8
         for (int u = 0; u < j; ++u) s += count[u];
         w.start[j] = s;
     }
     __syncthreads();
-    for (int e = tid; e < entries; e += T) list[w.start[region_index(irb[e], D.R)] + arrived[e]] = e;
+    each_entry([&](int e, int j) { list[w.start[j] + arrived[e]] = e; });
     __syncthreads();
-    for (int e = tid; e < entries; e += T) {
-        const int j = region_index(irb[e], D.R), s0 = w.start[j], s1 = w.start[j + 1];
+    each_entry([&](int e, int j) {
+        const int s0 = w.start[j], s1 = w.start[j + 1];
         int rank = 0;
+#pragma unroll 8
         for (int u = s0; u < s1; ++u) rank += list[u] < e;
         arrived[s0 + rank] = e / D.k;            // `arrived` becomes the ordered list of query regions
-    }
+    });
     return true;      // the key side reads the list behind the next barrier
 }
 
