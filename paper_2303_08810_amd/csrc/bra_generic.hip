@@ -836,13 +836,15 @@ int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lc
 // a chain of rows, and the query side's sums meet twice, so that it turns earlier.  us, query side / key side with 1, 2, 4 per head:
 // 588 heads of regions (4 x 14 x 28 x 96, k = 16) 18.1, 15.7, 13.8 / 16.5, 14.1, 11.5; 1568 (8 x 28 x 28 x 128, k = 4) 18.1, 22.0, 25.4 / 21.1, 16.8, 20.8;
 // 3072 (3 x 32 x 32 x 128, S = 16, k = 11) 19.9, 23.3, 28.6 / 24.2, 29.6, 41.4.
+// No more than the query side has tiles of 16 routed keys (588 heads, 2 x 35 x 35 x 192, k = 1: two tiles, 16.3 us with 4).
 constexpr long kQueryShare = 2400, kKeyShare = 3200;
 
-int head_share(const Dims &D, long most)
+int head_share(const Dims &D, long most, int tiles)
 {
     const long heads = (long)D.B * D.R * D.heads;
     const int least = D.heads >= 3 ? 1 : D.heads == 2 ? 2 : 4;       // a workgroup has four wavefronts
-    return heads <= most / 4 ? 4 : heads <= most / 2 ? std::max(2, least) : least;
+    const int share = heads <= most / 4 ? 4 : heads <= most / 2 ? 2 : 1;
+    return std::max(least, std::min(share, tiles >= 4 ? 4 : tiles >= 2 ? 2 : 1));
 }
 
 template <int NT, bool VEC>
@@ -854,7 +856,7 @@ int launch_heads_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, const lce
     // workgroups of a side with `share` wavefronts per head
     auto groups = [&](int share) { return (D.heads + 4 / share - 1) / (4 / share); };
     auto blocks = [&](int share) { return ((long)D.B * D.R * groups(share) + 7) / 8 * 8; };
-    const int of_query = head_share(D, kQueryShare), of_key = head_share(D, kKeyShare);
+    const int of_query = head_share(D, kQueryShare, (D.kn + 15) / 16), of_key = head_share(D, kKeyShare, 4);
     if (blocks(std::max(of_query, of_key)) + std::max(grad.p.blocks(), add.blocks) > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     auto query_side = [&](auto share) {
         constexpr int W = decltype(share)::value;
@@ -926,7 +928,8 @@ int launch_gemm_end(const f32::TnJob<T, float> &J0, const f32::TnJob<float, T> &
     const int bn = narrow ? 64 : 128;
     const long tn = ((long)(J0.blocks() + J1.blocks()) * shares + 7) / 8 * 8;
     if constexpr (std::is_same<T, float>::value) {
-        if (splits(J.M, J.N, J.K)) {
+        // shorter contractions beside those of the weights up to 80 tiles (117 of K = 576, 2 x 35 x 35 x 192: kernel 25.0 us, 26.9 so)
+        if (splits(J.M, J.N, J.K) && (J.K >= 1024 || mt * ((J.N + 63) / 64) <= 80)) {
             const dim3 grid((unsigned)(tn + (J.M + 15) / 16 * (J.N / 32)));
             hipLaunchKernelGGL((f32::k_gemm_end<true, 64, T, true>), grid, dim3(256), 0, st, J0, J1, J.M, share_tokens, (int)tn, J);
             return launched() ? BRA_OK : BRA_ERR_LAUNCH;
