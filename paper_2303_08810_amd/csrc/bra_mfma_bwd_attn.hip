@@ -898,10 +898,12 @@ bool two_tiles(const Dims &D)
 }
 
 // A workgroup has its region whole and all routed keys in one block, and the key side's buffers hold the halo.
+// Regions that items of 4 x 4 fill badly only where there are many: whole gradient (us), passes / so, by regions: 6 x 6 tokens (42 x 42 x 64) 392 46.1 / 48.6, 784
+// 57.6 / 60.3, 1568 86.3 / 83.4; 3 x 16 784 62.0 / 65.1, 1568 95.5 / 91.3; 4 x 10 320 43.0 / 44.7, 2048 105.4 / 101.2; 8 x 8 392 57.4 / 56.8, 784 76.1 / 74.4.
 bool convolves(const Dims &D, const lce::BackwardJobs &L)
 {
     const lce::RegionHalo halo(D.rh, D.rw);
-    return L.fit && D.n <= 64 && D.kn <= Rows<kShared>::KB && walk_ok(D) && halo.items() <= 4 * kLceRounds &&
+    return L.fit && D.n <= 64 && (D.n > 56 || (long)D.B * D.R > 1024) && D.kn <= Rows<kShared>::KB && walk_ok(D) && halo.items() <= 4 * kLceRounds &&
            halo.bytes(D.n) <= 2 * Rows<kShared>::buf * (int)sizeof(bf16_t);
 }
 

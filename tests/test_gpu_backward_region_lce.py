@@ -22,6 +22,8 @@ SHAPES = [  # (B, H, W, C, heads, S, k)
     (1, 33, 2, 64, 2, 1, 1),         # 33 x 2 tokens, one region: too many for one tile
     (2, 33, 1, 64, 2, 1, 1),         # 33 x 1: nine items
     (2, 8, 7, 64, 2, 1, 1),          # one region, the whole map
+    (21, 42, 42, 64, 2, 7, 1),       # 6 x 6, many regions
+    (17, 24, 88, 64, 2, 8, 1),       # 3 x 11
     (1, 8, 16, 64, 2, 4, 4),         # 8 tokens, 32 keys
     (1, 8, 16, 64, 2, 4, 5),         # 40 keys
     (3, 16, 24, 128, 4, 4, 1),       # 24 tokens
