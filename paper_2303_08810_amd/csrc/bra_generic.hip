@@ -201,13 +201,14 @@ int launch_gemm_vec(const f32::GemmJob<TA, TB, TO> &J0, const f32::GemmJob<float
     return launched() ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
+// may_split: false for a product that is the second one of a launch elsewhere, where it is summed in one chain, and has to come out with the same bits.
 template <bool BT, typename TA, typename TB, typename TO>
-int launch_gemm(const f32::GemmJob<TA, TB, TO> &J0, const f32::GemmJob<float, TB, float> *J1, hipStream_t st)
+int launch_gemm(const f32::GemmJob<TA, TB, TO> &J0, const f32::GemmJob<float, TB, float> *J1, hipStream_t st, bool may_split = true)
 {
     auto quads = [](int a, int b, int c, int d, int e) { return (a | b | c | d | e) % 4 == 0; };
     const bool vec = quads(J0.lda, J0.ldb, J0.ldo, J0.N, J0.K) && (!J1 || quads(J1->lda, J1->ldb, J1->ldo, J1->N, J1->K));
     if constexpr (!BT && std::is_same<TA, float>::value && std::is_same<TB, float>::value && std::is_same<TO, float>::value) {
-        if (vec && !J1 && splits(J0.M, J0.N, J0.K)) {
+        if (vec && !J1 && may_split && splits(J0.M, J0.N, J0.K)) {
             const int rows = split_rows(J0.M, J0.N);
             const dim3 grid((unsigned)((J0.M + rows - 1) / rows * (J0.N / 32)));
             if (rows == 16) hipLaunchKernelGGL((f32::k_gemm_split<false, 1>), grid, dim3(512), 0, st, J0);
@@ -298,7 +299,8 @@ int launch_route(const Dims &D, const T *X, const T *Wqkv, int32_t *Ir, float *A
     launch_pool<T>(D, X, w.xr, st);
     {
         ProfScope ps(st, K_GEN_REGION_QK);
-        const int rc = launch_gemm<false>(region_job<T>(D, Wqkv, w), (const f32::GemmJob<float, T, float> *)nullptr, st);
+        // beside Q, K and V in forward_t
+        const int rc = launch_gemm<false>(region_job<T>(D, Wqkv, w), (const f32::GemmJob<float, T, float> *)nullptr, st, false);
         if (rc != BRA_OK) return rc;
     }
     return route_rows(D, w.qk, w.qk + D.C, 2 * D.C, Ir, Ar_opt, st);

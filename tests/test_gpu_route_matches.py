@@ -27,6 +27,24 @@ SHAPES = [  # (dtype, B, H, W, C, heads, S, k)
     ("bf16", 16, 28, 28, 96, 3, 7, 49),        # the float32 family
     ("f32", 16, 28, 28, 64, 2, 7, 4),
     ("f32", 16, 21, 14, 64, 2, 7, 49),
+    # float32, means of the tokens projected: bra_route's product on its own, bra_forward's beside Q, K and V
+    ("f32", 16, 56, 56, 64, 2, 7, 4),          # 64 tokens per region, more tiles than the means come out of
+    ("f32", 16, 56, 56, 64, 2, 7, 49),
+    ("f32", 1, 128, 128, 64, 2, 8, 4),         # more than 64 tokens
+    ("f32", 2, 63, 63, 128, 4, 7, 49),
+    ("f32", 2, 63, 63, 192, 6, 7, 49),
+    ("f32", 1, 63, 63, 256, 8, 7, 49),
+    ("f32", 2, 63, 63, 96, 3, 7, 49),
+    # few rows, whose contraction the wavefronts of a workgroup share: means out of the projection, one token per region
+    ("f32", 2, 16, 16, 256, 8, 4, 3),
+    ("f32", 1, 35, 28, 192, 6, 7, 49),
+    ("f32", 1, 7, 7, 512, 16, 7, 49),
+    ("bf16", 1, 7, 7, 512, 16, 7, 5),
+    ("bf16", 4, 7, 7, 384, 12, 7, 49),
+    ("bf16", 1, 14, 14, 384, 12, 7, 9),
+    ("bf16", 2, 14, 14, 1024, 32, 7, 49),
+    ("bf16", 3, 112, 112, 64, 2, 7, 2),        # 64 channels with all weights in LDS beside the routing
+    ("bf16", 10, 64, 64, 64, 2, 8, 64),
 ]
 
 
