@@ -12,6 +12,8 @@
 
 #include "bra_f32_dev.h"
 
+#include <cfloat>
+
 namespace bra {
 namespace f32 {
 
@@ -142,10 +144,10 @@ __global__ __launch_bounds__(256, NQ == 1 && VEC ? 4 : 3) void k_heads_bwd_q(con
                 for (int q = 0; q < NQ; ++q) acc[NS * q + dt] = mfma_f32(t, wt[q][e], acc[NS * q + dt]);
             }
     };
-    float m[NQ], l[NQ], dd[NQ];
+    float m[NQ], l[NQ], dd[NQ];                 // m begins at a finite value: a tile without a finite score leaves no weights, and no NaN
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        m[q] = -INFINITY;
+        m[q] = -FLT_MAX;
         l[q] = dd[q] = 0.f;
 #pragma unroll
         for (int dt = 0; dt < NS; ++dt) acc[NS * q + dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(256, NQ == 1 && VEC ? 4 : 3) void k_heads_bwd_q(con
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 f32x4 &x = st[u][q];
-                const float top = fmaxf(m[q], cross_row_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]))));     // finite: the tile's first key exists
+                const float top = fmaxf(m[q], cross_row_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]))));
                 const float alpha = __builtin_amdgcn_exp2f(m[q] - top);
                 m[q] = then[u][q] = top;
                 float ls = 0.f, ds = 0.f;
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(256, NQ == 1 && VEC ? 4 : 3) void k_heads_bwd_q(con
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            float top = -INFINITY;
+            float top = -FLT_MAX;
             const float *from = stats + (hl * W * NQ + q) * 48 + i;
 #pragma unroll
             for (int w = 0; w < W; ++w) top = fmaxf(top, from[w * NQ * 48]);
