@@ -43,7 +43,8 @@ __device__ __forceinline__ f32x4 total(const f32x4 *sums, int hl, int lane, int 
 }
 
 // Query side, see k_attn_bwd_q: O, lse, D and dQ of NQ tiles of 16 queries.  The weights and dP of up to kKept tiles of keys per
-// wavefront stay in registers; of more, they are formed twice.
+// wavefront stay in registers; of more, they are formed twice.  Scores are scaled behind their products, here and on the key side, and rounded once: the
+// statistics belong to the very scores that the key side forms, and terms that cancel do.
 template <int NQ>
 constexpr int kKeptTiles = NQ == 1 ? 4 : 2;
 
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(256, NQ == 1 && VEC ? 4 : 3) void k_heads_bwd_q(con
         qtok[q] = at.origin(reg) + at.slot(min(16 * q + i, D.n - 1));
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            qf[q][s] = blank(row_chunk(img + (size_t)qtok[q] * C3, s), s) * c_exp;       // scores as exponents of 2
+            qf[q][s] = blank(row_chunk(img + (size_t)qtok[q] * C3, s), s);
             gf[q][s] = blank(row_chunk(dO + (itok + qtok[q]) * D.C, s), s);
         }
     }
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(256, NQ == 1 && VEC ? 4 : 3) void k_heads_bwd_q(con
                 for (int q = 0; q < NQ; ++q) acc[NS * q + dt] = mfma_f32(t, wt[q][e], acc[NS * q + dt]);
             }
     };
-    float m[NQ], l[NQ], dd[NQ];                 // m begins at a finite value: a tile without a finite score leaves no weights, and no NaN
+    float m[NQ], l[NQ], dd[NQ];                 // m: an exponent of 2, at first a finite one: a tile without a finite score leaves no weights, and no NaN
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         m[q] = -FLT_MAX;
@@ -162,13 +163,13 @@ __global__ __launch_bounds__(256, NQ == 1 && VEC ? 4 : 3) void k_heads_bwd_q(con
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 f32x4 &x = st[u][q];
-                const float top = fmaxf(m[q], cross_row_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]))));
+                const float top = fmaxf(m[q], cross_row_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]))) * c_exp);
                 const float alpha = __builtin_amdgcn_exp2f(m[q] - top);
                 m[q] = then[u][q] = top;
                 float ls = 0.f, ds = 0.f;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    x[j] = __builtin_amdgcn_exp2f(x[j] - top);
+                    x[j] = __builtin_amdgcn_exp2f(fmaf(x[j], c_exp, -top));
                     ls += x[j];
                     ds = fmaf(x[j], dp[u][q][j], ds);
                 }
@@ -253,7 +254,7 @@ __global__ __launch_bounds__(256, NQ == 1 && VEC ? 4 : 3) void k_heads_bwd_q(con
             for (int q = 0; q < NQ; ++q) {
                 const float f = twice ? 1.0f : __builtin_amdgcn_exp2f(then[u][q] - m[q]);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) st[u][q][j] = (twice ? __builtin_amdgcn_exp2f(st[u][q][j] - m[q]) : st[u][q][j] * f) * inv[q] * (dp[u][q][j] - dd[q]);
+                for (int j = 0; j < 4; ++j) st[u][q][j] = (twice ? __builtin_amdgcn_exp2f(fmaf(st[u][q][j], c_exp, -m[q])) : st[u][q][j] * f) * inv[q] * (dp[u][q][j] - dd[q]);
             }
             contract(Kw, st[u]);
         }
@@ -306,7 +307,7 @@ __global__ __launch_bounds__(256, NK == 1 ? 4 : 3) void k_heads_bwd_kv(const flo
         const float *row = img + (size_t)ktok[q] * C3;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            kf[q][s] = blank(row_chunk(row + D.C, s), s) * c_exp;        // scores as exponents of 2
+            kf[q][s] = blank(row_chunk(row + D.C, s), s);
             vf[q][s] = blank(row_chunk(row + 2 * D.C, s), s);
         }
     }
@@ -363,7 +364,7 @@ __global__ __launch_bounds__(256, NK == 1 ? 4 : 3) void k_heads_bwd_kv(const flo
             for (int q = 0; q < NK; ++q)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    p[q][e] = __builtin_amdgcn_exp2f(st[q][e] - l4[e]);
+                    p[q][e] = __builtin_amdgcn_exp2f(fmaf(st[q][e], c_exp, -l4[e]));
                     ds[q][e] = p[q][e] * (dp[q][e] - d4[e]);
                 }
 #pragma unroll
