@@ -22,6 +22,10 @@ struct HeadShare {
     static constexpr int P = 32 + 4, HPG = 4 / W, kTile = 16 * P;      // heads of a workgroup; floats of a tile of rows in LDS
 };
 
+// Between what lanes of a wavefront write to its part of LDS and what others of it read there, both ways.  No instruction: the hardware keeps
+// the order of a wavefront's accesses, this asks the compiler to.
+__device__ __forceinline__ void lanes_meet() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 // Sums over the W wavefronts of a head: v of wavefront `part` goes to sums[..][part]; behind a barrier, total() adds them up in order.
 // N f32x4 per lane; entry c of all wavefronts is taken by wavefront c % W.
 template <int W, int N>
@@ -100,6 +104,7 @@ __global__ __launch_bounds__(256, NQ == 1 && VEC ? 4 : 3) void k_heads_bwd_q(con
         }
     };
     auto park_keys = [&](f32x4 (&k)[NS]) {
+        lanes_meet();                            // the tile before has been read
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             k[s] = blank(kr[s], s);
@@ -116,6 +121,7 @@ __global__ __launch_bounds__(256, NQ == 1 && VEC ? 4 : 3) void k_heads_bwd_q(con
             v[s] = blank(vr[s], s);
             if (both) *(f32x4 *)(Vw + i * P + 16 * s + 4 * g) = v[s];
         }
+        lanes_meet();
         if (tile + W < tiles) fetch(tile + W, true);
 #pragma unroll
         for (int q = 0; q < NQ; ++q) st[q] = dp[q] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -248,6 +254,7 @@ __global__ __launch_bounds__(256, NQ == 1 && VEC ? 4 : 3) void k_heads_bwd_q(con
             } else {
                 f32x4 k[NS];
                 park_keys(k);
+                lanes_meet();
                 if (tile + W < tiles) fetch(tile + W, false);
             }
 #pragma unroll
@@ -334,6 +341,7 @@ __global__ __launch_bounds__(256, NK == 1 ? 4 : 3) void k_heads_bwd_kv(const flo
         if (16 * part < rows) fetch(part);
         for (int tile = part; 16 * tile < rows; tile += W) {
             f32x4 qv[NS], gv[NS];
+            lanes_meet();                        // the tile before has been read
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 qv[s] = blank(qr[s], s);
@@ -345,6 +353,7 @@ __global__ __launch_bounds__(256, NK == 1 ? 4 : 3) void k_heads_bwd_kv(const flo
                 lw[i] = 16 * tile + i < rows ? row_lse : INFINITY;       // a missing row: P = exp2(-inf) = 0
                 lw[16 + i] = row_dd;
             }
+            lanes_meet();
             if (16 * (tile + W) < rows) fetch(tile + W);
             f32x4 st[NK], dp[NK];
 #pragma unroll
