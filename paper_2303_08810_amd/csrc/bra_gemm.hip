@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void k_gemm(GemmRegions J, const bf16_t *__res
 // chunk past the end was loaded once more).
 // BT: W is given transposed, [Nout][ldw] with the contraction axis contiguous; its chunk then lies like In's and needs no
 // transposing reads.
-__device__ bf16_t zero_row[4096];        // what missing rows of In read (never written)
+alignas(16) __device__ bf16_t zero_row[4096];        // what missing rows of In read (never written)
 
 // Row of the map in memory that row m of the padded map is, or -1.
 __device__ __forceinline__ long stored_row(const GemmRows &r, int m)

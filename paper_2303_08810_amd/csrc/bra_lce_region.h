@@ -28,7 +28,7 @@ struct RegionHalo {
 
 constexpr int kResultPitch = 68;         // floats per token of the results
 
-static __device__ bf16_t zero_piece[8];  // what tokens beyond the map read (never written)
+alignas(16) static __device__ bf16_t zero_piece[8];      // what tokens beyond the map read (never written)
 
 // Requests the halo of the region whose first token is (y0, x0).  map: the image's, at its first of 64 channels.  The caller waits.
 __device__ __forceinline__ void request_halo(const RegionHalo &r, const bf16_t *map, const Dims &D, int y0, int x0, unsigned at, int wave, int lane)
