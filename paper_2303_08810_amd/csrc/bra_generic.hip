@@ -781,7 +781,13 @@ SharePlan share_plan(long M, int C)
 // these, else two with 4-channel loads).  Two workgroups
 // per compute unit (29 x 28 x 28 x 96: whole gradient 176 us, 182 with three).
 bool by_heads(const Dims &D) { return D.n <= 32 && D.d <= 32; }
-lce::LcePlan lce_grad_plan(const Dims &D) { return lce::lce_plan(D, 512, D.d % 4 == 0 && !by_heads(D) ? 8 : 4); }
+
+// The query side of regions of 17 to 32 tokens that keeps all keys as one block of 64 instead of in tiles of 16 by wavefront: with two tiles of queries a wavefront of
+// k_heads_bwd_q keeps two tiles of keys.  Whole gradient (us), it / the block: 6 x 35 x 35 x 192, k = 2 154 / 140, 8 images 183 / 173, 2 images 74.0 / 68.1; 12 x 35 x 35 x 96 bf16, k = 2
+// 119 / 112; 24 x 21 x 42 x 64, k = 3 116 / 107; the other way round 7 x 21 x 42 x 64, k = 2 53.3 / 55.9; with more keys 10 x 35 x 35 x 96, k = 3 123 / 140; with one block of 32
+// mixed, 10 x 35 x 35 x 96, k = 1 99.6 / 105.0, 2 x 35 x 35 x 192 68.4 / 66.2, 14 x 28 x 56 x 64 90.5 / 87.3.
+bool query_by_heads(const Dims &D) { return by_heads(D) && !(D.n > 16 && D.heads >= 2 && D.kn > 32 && D.kn <= 64); }
+lce::LcePlan lce_grad_plan(const Dims &D) { return lce::lce_plan(D, 512, D.d % 4 == 0 && !query_by_heads(D) ? 8 : 4); }
 
 struct BwdWs {
     float *qkv, *o, *dO, *dqkv, *lse, *dsum, *part_qkv, *part_o, *part_lce;
@@ -813,7 +819,8 @@ BwdWs carve_bwd(const Dims &D, void *ws)
     return w;
 }
 
-template <int DP, int HPW, bool VEC>
+// The query side, or both, by workgroups of HPW heads.
+template <int DP, int HPW, bool VEC, bool KEYS = true>
 int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lce::Taps &taps, hipStream_t st)
 {
     const int hgroups = (D.heads + HPW - 1) / HPW, qt = f32::AttnShape<DP, HPW>::QT, tiles = (D.n + qt - 1) / qt;
@@ -824,11 +831,12 @@ int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lc
     // front of the query side it was slower (4 x 56 x 56 x 64, k = 2: 100.9 us behind, 105.6 in front).
     const float *V = w.qkv + 2 * D.C;
     const lce::GradJob<float> grad = {w.dO, V, taps, w.dqkv + 2 * D.C, w.part_lce, 3 * D.C, 3 * D.C, lce_grad_plan(D)};
-    const lce::AddJob<float> add = lce::add_job<float>(D, V, 3 * D.C, taps, w.o, D.C, VEC ? 2 : 1, 256);
+    const lce::AddJob<float> add = KEYS ? lce::add_job<float>(D, V, 3 * D.C, taps, w.o, D.C, VEC ? 2 : 1, 256) : lce::AddJob<float>{};
     if (blocks + std::max(grad.p.blocks(), add.blocks) > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     hipLaunchKernelGGL((f32::k_attn_bwd_q<DP, HPW, VEC>), dim3((unsigned)(blocks + grad.p.blocks())), dim3(256), 0, st, w.qkv, w.dO, Ir, w.o, w.dqkv, w.lse,
                        w.dsum, D, hgroups, tiles, by_image, grad, grad.p.blocks());
-    hipLaunchKernelGGL((f32::k_attn_bwd_kv<DP, HPW, VEC>), dim3((unsigned)(blocks + add.blocks)), dim3(256), 0, st, w.qkv, w.dO, Ir, w.lse,
+    if constexpr (!KEYS) return launched() ? BRA_OK : BRA_ERR_LAUNCH;
+    else hipLaunchKernelGGL((f32::k_attn_bwd_kv<DP, HPW, VEC>), dim3((unsigned)(blocks + add.blocks)), dim3(256), 0, st, w.qkv, w.dO, Ir, w.lse,
                        w.dsum, w.dqkv, D, hgroups, tiles, by_image, add, add.blocks);
     if (!launched()) return BRA_ERR_LAUNCH;
     return add.blocks ? BRA_OK : lce::launch_lce<float>(D, V, 3 * D.C, taps, w.o, D.C, K_GEN_BACKWARD, st);
@@ -875,7 +883,15 @@ int launch_heads_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, const lce
         else if (share == 2) side(std::integral_constant<int, 2>{});
         else side(std::integral_constant<int, 1>{});
     };
-    launch(of_query, query_side);
+    bool apart = false;
+    if constexpr (NT == 2) {
+        apart = !query_by_heads(D);
+        if (apart) {
+            const int rc = launch_attn_bwd_t<32, 2, VEC, false>(D, w, Ir, taps, st);
+            if (rc != BRA_OK) return rc;
+        }
+    }
+    if (!apart) launch(of_query, query_side);
     launch(of_key, key_side);
     if (!launched()) return BRA_ERR_LAUNCH;
     return add.blocks ? BRA_OK : lce::launch_lce<float>(D, V, 3 * D.C, taps, w.o, D.C, K_GEN_BACKWARD, st);

@@ -28,6 +28,14 @@ SHAPES = [  # (dtype, B, H, W, C, heads, S, k)
     ("f32", 70, 6, 9, 30, 5, 3, 2),        # of 6, one wavefront per head
     ("bf16", 2, 12, 20, 72, 3, 4, 5),      # of 24
     ("bf16", 5, 14, 28, 96, 3, 7, 12),
+    # 17 to 32 tokens: one block of 33 to 64 keys, of two heads to a workgroup; 32 keys and 66
+    ("f32", 2, 12, 10, 64, 2, 2, 2),       # 30 tokens, 60 keys
+    ("f32", 3, 16, 32, 160, 5, 4, 2),      # 64 keys, an odd number of heads
+    ("f32", 2, 15, 15, 60, 6, 3, 2),       # heads of 10 channels
+    ("f32", 2, 16, 32, 64, 2, 4, 1),
+    ("f32", 3, 24, 12, 96, 3, 4, 4),       # 72 keys
+    ("f32", 2, 12, 10, 32, 1, 2, 2),       # one head
+    ("bf16", 2, 35, 35, 96, 3, 7, 2),
 ]
 
 
