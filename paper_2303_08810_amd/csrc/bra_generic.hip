@@ -842,19 +842,30 @@ int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lc
     return add.blocks ? BRA_OK : lce::launch_lce<float>(D, V, 3 * D.C, taps, w.o, D.C, K_GEN_BACKWARD, st);
 }
 
-// Wavefronts that share a head of a region: four or two while there are at most `most` of them, else the fewest that fill a workgroup.  They hide
-// a chain of rows, and the query side's sums meet twice, so that it turns earlier.  us, query side / key side with 1, 2, 4 per head:
-// 588 heads of regions (4 x 14 x 28 x 96, k = 16) 18.1, 15.7, 13.8 / 16.5, 14.1, 11.5; 1568 (8 x 28 x 28 x 128, k = 4) 18.1, 22.0, 25.4 / 21.1, 16.8, 20.8;
-// 3072 (3 x 32 x 32 x 128, S = 16, k = 11) 19.9, 23.3, 28.6 / 24.2, 29.6, 41.4.
-// No more than the query side has tiles of 16 routed keys (588 heads, 2 x 35 x 35 x 192, k = 1: two tiles, 16.3 us with 4).
-constexpr long kQueryShare = 2400, kKeyShare = 3200;
+// Wavefronts that share a head of a region: a chain of rows is hidden by the other wavefronts of the unit or by more of them on it, and each reads the region's own rows.
+// us, query side / key side with 1, 2, 4 per head: 588 heads of regions (4 x 14 x 28 x 96, k = 16) 18.1, 15.7, 13.8 / 16.5, 14.1, 11.5; 1568 (8 x 28 x 28 x 128, k = 4)
+// 18.1, 22.0, 25.4 / 21.1, 16.8, 20.8; 3072 (3 x 32 x 32 x 128, S = 16, k = 11) 19.9, 23.3, 28.6 / 24.2, 29.6, 41.4.
+// A workgroup has four wavefronts: at least as many per head as leave none without one.
+int least_share(const Dims &D) { return D.heads >= 3 ? 1 : D.heads == 2 ? 2 : 4; }
 
-int head_share(const Dims &D, long most, int tiles)
+// Query side: no more than it has tiles of 16 routed keys.  Whole gradient of B x 28 x 28 x 128, us, 4, 2, 1: k = 4, 588 heads of regions 52.9, 53.1, 54.0; 784 58.5, 55.6, 56.8; 980 64.6, 61.5,
+// 61.4; 1176 70.7, 69.3, 69.0; 1372 74.9, 70.7, 71.0; 1568 79.3, 77.4, 74.5.
+int query_share(const Dims &D)
 {
     const long heads = (long)D.B * D.R * D.heads;
-    const int least = D.heads >= 3 ? 1 : D.heads == 2 ? 2 : 4;       // a workgroup has four wavefronts
-    const int share = heads <= most / 4 ? 4 : heads <= most / 2 ? 2 : 1;
-    return std::max(least, std::min(share, tiles >= 4 ? 4 : tiles >= 2 ? 2 : 1));
+    const int tiles = (D.kn + 15) / 16, share = heads <= 600 ? 4 : heads <= 1200 ? 2 : 1;
+    return std::max(least_share(D), std::min(share, tiles >= 4 ? 4 : tiles >= 2 ? 2 : 1));
+}
+
+// Key side: no more than the rows of an average list are worth, which has k n.  Whole gradient, us, 4, 2, 1: 784 heads of regions, 2 x 14 x 14 x 256, k = 1 (4 rows) 50.6, 46.8, 46.1; 4 x 14 x 28 x 128,
+// k = 2 (16) 45.9, 45.3, 45.1; 4 x 28 x 28 x 128, k = 2 (32) 53.6, 52.5, 54.8, k = 4 (64) 55.6, 54.9, 58.7, k = 8 62.7, 62.9, 68.4, k = 16 79.1, 81.0, 88.0; 588, k = 4 52.9, 53.4, 56.4.  One or two,
+// 64 rows: 1372 -, 70.8, 73.8; 1568 -, 74.5, 76.6; 1764 -, 82.9, 83.5; 2352 -, 102.6, 102.9; 2744 -, 109.1, 107.5; 4 tokens a region and 64 rows 1568 -, 64.8, 64.2, 1960 -, 69.9, 67.5.
+// With two tiles of keys a row is worth more: 7 x 35 x 35 x 64, k = 2 (50) 60.7, 64.1, -, k = 1 57.8, 59.1, -; 2 x 35 x 35 x 192, k = 1 68.0, 69.0, -; 5 x 21 x 42 x 96, k = 1 (18) 61.8, 59.5, 58.7.
+int key_share(const Dims &D)
+{
+    const long heads = (long)D.B * D.R * D.heads;
+    const int share = heads <= 800 ? 4 : heads <= 1600 ? 2 : 1, rows = D.n > 16 ? 3 * D.kn : D.kn;
+    return std::max(least_share(D), std::min(share, rows >= 64 ? 4 : rows >= 16 ? 2 : 1));
 }
 
 template <int NT, bool VEC>
@@ -866,7 +877,7 @@ int launch_heads_bwd(const Dims &D, const BwdWs &w, const int32_t *Ir, const lce
     // workgroups of a side with `share` wavefronts per head
     auto groups = [&](int share) { return (D.heads + 4 / share - 1) / (4 / share); };
     auto blocks = [&](int share) { return ((long)D.B * D.R * groups(share) + 7) / 8 * 8; };
-    const int of_query = head_share(D, kQueryShare, (D.kn + 15) / 16), of_key = head_share(D, kKeyShare, 4);
+    const int of_query = query_share(D), of_key = key_share(D);
     if (blocks(std::max(of_query, of_key)) + std::max(grad.p.blocks(), add.blocks) > 0x7fffffffL) return BRA_ERR_UNSUPPORTED;
     auto query_side = [&](auto share) {
         constexpr int W = decltype(share)::value;

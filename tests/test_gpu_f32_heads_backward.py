@@ -28,6 +28,11 @@ SHAPES = [  # (dtype, B, H, W, C, heads, S, k)
     ("f32", 70, 6, 9, 30, 5, 3, 2),        # of 6, one wavefront per head
     ("bf16", 2, 12, 20, 72, 3, 4, 5),      # of 24
     ("bf16", 5, 14, 28, 96, 3, 7, 12),
+    # lists of 4, 12, 16 and 64 rows on average: one, one, two and four wavefronts on the key side
+    ("f32", 2, 14, 14, 256, 8, 7, 1),
+    ("f32", 4, 14, 14, 96, 3, 7, 3),
+    ("f32", 4, 14, 14, 96, 3, 7, 4),
+    ("f32", 4, 14, 14, 96, 3, 7, 16),
     # 17 to 32 tokens: one block of 33 to 64 keys, of two heads to a workgroup; 32 keys and 66
     ("f32", 2, 12, 10, 64, 2, 2, 2),       # 30 tokens, 60 keys
     ("f32", 3, 16, 32, 160, 5, 4, 2),      # 64 keys, an odd number of heads
