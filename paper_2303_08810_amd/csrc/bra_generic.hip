@@ -849,22 +849,26 @@ int launch_attn_bwd_t(const Dims &D, const BwdWs &w, const int32_t *Ir, const lc
 int least_share(const Dims &D) { return D.heads >= 3 ? 1 : D.heads == 2 ? 2 : 4; }
 
 // Query side: no more than it has tiles of 16 routed keys.  Whole gradient of B x 28 x 28 x 128, us, 4, 2, 1: k = 4, 588 heads of regions 52.9, 53.1, 54.0; 784 58.5, 55.6, 56.8; 980 64.6, 61.5,
-// 61.4; 1176 70.7, 69.3, 69.0; 1372 74.9, 70.7, 71.0; 1568 79.3, 77.4, 74.5.
+// 61.4; 1176 70.7, 69.3, 69.0; 1372 74.9, 70.7, 71.0; 1568 79.3, 77.4, 74.5.  But as many as keep all weights in registers (kKeptTiles): k = 8 (8 tiles) 1372 84.6, 79.8, 87.0; 2744 134.7, 131.4, 132.1; k = 16
+// (16) 1372 102.0, 103.8, 114.9; 2744 167.8, 177.3, 175.6.  With two tiles of queries, which keep half, two up to 3200, where four heads at a time leave places empty or
+// there are many tiles: 8 x 35 x 35 x 192, k = 3 187, 184, 197, k = 5 205, 207, 234, k = 8
+// 254, 245, 289; 16 x 35 x 35 x 96, k = 3 174, 178, 180, k = 8 243, 257, 270; 8 x 28 x 56 x 192, k = 8 297, 296, 353; 12 x 35 x 35 x 128, k = 3 -, 164, 163, k = 5 -, 184, 198; 24 x 35 x 35 x 96, k = 4 (3528) -, 238, 230.
 int query_share(const Dims &D)
 {
     const long heads = (long)D.B * D.R * D.heads;
-    const int tiles = (D.kn + 15) / 16, share = heads <= 600 ? 4 : heads <= 1200 ? 2 : 1;
+    const int tiles = (D.kn + 15) / 16, keeps = D.n > 16 ? (heads <= 3200 && tiles > (D.heads % 4 ? 2 : 5) ? 2 : 1) : tiles <= 4 || tiles > 16 ? 1 : tiles <= 8 ? 2 : 4;
+    const int share = std::max(keeps, heads <= 600 ? 4 : heads <= 1200 ? 2 : 1);
     return std::max(least_share(D), std::min(share, tiles >= 4 ? 4 : tiles >= 2 ? 2 : 1));
 }
 
 // Key side: no more than the rows of an average list are worth, which has k n.  Whole gradient, us, 4, 2, 1: 784 heads of regions, 2 x 14 x 14 x 256, k = 1 (4 rows) 50.6, 46.8, 46.1; 4 x 14 x 28 x 128,
 // k = 2 (16) 45.9, 45.3, 45.1; 4 x 28 x 28 x 128, k = 2 (32) 53.6, 52.5, 54.8, k = 4 (64) 55.6, 54.9, 58.7, k = 8 62.7, 62.9, 68.4, k = 16 79.1, 81.0, 88.0; 588, k = 4 52.9, 53.4, 56.4.  One or two,
 // 64 rows: 1372 -, 70.8, 73.8; 1568 -, 74.5, 76.6; 1764 -, 82.9, 83.5; 2352 -, 102.6, 102.9; 2744 -, 109.1, 107.5; 4 tokens a region and 64 rows 1568 -, 64.8, 64.2, 1960 -, 69.9, 67.5.
-// With two tiles of keys a row is worth more: 7 x 35 x 35 x 64, k = 2 (50) 60.7, 64.1, -, k = 1 57.8, 59.1, -; 2 x 35 x 35 x 192, k = 1 68.0, 69.0, -; 5 x 21 x 42 x 96, k = 1 (18) 61.8, 59.5, 58.7.
+// With two tiles of keys, from 32 rows on, two up to twice as many: 8 x 35 x 35 x 192, k = 2 (2352) -, 170, 173, k = 5 211, 207, 228; 24 x 35 x 35 x 96, k = 2 (3528) 188, 184, 181.  And a row is worth more: 7 x 35 x 35 x 64, k = 2 (50) 60.7, 64.1, -, k = 1 57.8, 59.1, -; 2 x 35 x 35 x 192, k = 1 68.0, 69.0, -; 5 x 21 x 42 x 96, k = 1 (18) 61.8, 59.5, 58.7.
 int key_share(const Dims &D)
 {
     const long heads = (long)D.B * D.R * D.heads;
-    const int share = heads <= 800 ? 4 : heads <= 1600 ? 2 : 1, rows = D.n > 16 ? 3 * D.kn : D.kn;
+    const int share = heads <= 800 ? 4 : heads <= (D.n > 16 && D.kn >= 32 ? 3200 : 1600) ? 2 : 1, rows = D.n > 16 ? 3 * D.kn : D.kn;
     return std::max(least_share(D), std::min(share, rows >= 64 ? 4 : rows >= 16 ? 2 : 1));
 }
 

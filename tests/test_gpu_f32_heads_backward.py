@@ -33,6 +33,14 @@ SHAPES = [  # (dtype, B, H, W, C, heads, S, k)
     ("f32", 4, 14, 14, 96, 3, 7, 3),
     ("f32", 4, 14, 14, 96, 3, 7, 4),
     ("f32", 4, 14, 14, 96, 3, 7, 16),
+    # as many wavefronts as keep the weights: 4, 5, 8, 9, 16 and 17 tiles of keys at more than 1200 heads of regions
+    ("f32", 7, 14, 28, 128, 4, 7, 8),
+    ("f32", 7, 14, 28, 128, 4, 7, 9),
+    ("f32", 7, 14, 28, 128, 4, 7, 16),
+    ("f32", 7, 14, 28, 128, 4, 7, 17),
+    ("f32", 7, 14, 28, 128, 4, 7, 32),
+    ("f32", 7, 14, 28, 128, 4, 7, 33),
+    ("f32", 11, 21, 42, 96, 3, 7, 4),      # 18 tokens, 5 tiles: two
     # 17 to 32 tokens: one block of 33 to 64 keys, of two heads to a workgroup; 32 keys and 66
     ("f32", 2, 12, 10, 64, 2, 2, 2),       # 30 tokens, 60 keys
     ("f32", 3, 16, 32, 160, 5, 4, 2),      # 64 keys, an odd number of heads
