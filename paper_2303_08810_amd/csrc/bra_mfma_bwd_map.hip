@@ -466,8 +466,17 @@ bool attn_bwd_map_ok(const Dims &D)
     return D.d == 32 && (long)D.B * D.heads >= 160 && D.n <= 8 && D.k > 1 && (long)D.B * D.heads < 0x7ffffff0L && map_smem(D.N, D.R, D.k, 16, false).bytes <= (size_t)kMaxLds;
 }
 
-// Wherever each pair of items has a wavefront, on sides that the items' tap gradients take.
-bool attn_bwd_map_convolves(const Dims &D) { return D.H >= 4 && D.W >= 4 && (D.W + 3) / 4 * ((D.H + 3) / 4) <= 2 * waves_of(D); }
+// Wherever each pair of items has a wavefront, on sides that the items' tap gradients take, while there are few rounds of workgroups: in many, the
+// wavefronts without a pair hold their places until the others are done, and the tap gradients of every image are an array to be summed.  Whole gradient (us), here / with the
+// launch, by (image, head) pairs: 4 x 4 x 64 (1 pair of items) 1024 54 / 55, 1536 70 / 68, 4096 151 / 137; 7 x 7 x 64 (2) 1024 91 / 98, 4096 295 / 296, 8192 591 / 569; 7 x 14 x 64 (4) 1024
+// 106 / 109, 2048 189 / 184; 14 x 14 x 64 (8) 768 107 / 109, 1024 133 / 131, 2048 257 / 239; 16 x 16 x 512 (8) 512 145 / 150, 768 212 / 212, 1024 281 / 276; 14 x 28 x 256 (14), where a
+// compute unit holds one workgroup, 192 78 / 82, 320 124 / 120, 1024 312 / 298.
+bool attn_bwd_map_convolves(const Dims &D)
+{
+    const int items = (D.W + 3) / 4 * ((D.H + 3) / 4), waves = waves_of(D);
+    const long most = waves == 16 ? 256 : items > 8 ? 768 : items > 2 && items <= 4 && D.N > 32 ? 4096 : 1024;
+    return D.H >= 4 && D.W >= 4 && items <= 2 * waves && (long)D.B * D.heads <= most;
+}
 
 int launch_attn_bwd_map(const Dims &D, const bf16_t *Q, const bf16_t *K, const bf16_t *V, const bf16_t *dO, const int32_t *Ir,
                         bf16_t *O, bf16_t *dQKV, const bf16_t *Wlce, float *PartLce, int kernel_id, hipStream_t st)

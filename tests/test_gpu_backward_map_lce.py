@@ -25,6 +25,13 @@ SHAPES = [  # (B, H, W, C, heads, S, k)
     (80, 9, 36, 64, 2, 9, 2),        # 14 pairs of 27 items
     (80, 28, 14, 64, 2, 7, 2),       # 8 tokens per region
     (80, 9, 45, 64, 2, 9, 2),        # 36 items
+    # (image, head) pairs beyond which the passes are their own again: 768 with 9 items, 1024 with 4, 256 with 27 and a compute unit for each workgroup
+    (96, 12, 12, 256, 8, 6, 2),
+    (97, 12, 12, 256, 8, 6, 2),
+    (128, 5, 5, 256, 8, 5, 2),
+    (129, 5, 5, 256, 8, 5, 2),
+    (32, 9, 36, 256, 8, 9, 2),
+    (33, 9, 36, 256, 8, 9, 2),
 ]
 
 
