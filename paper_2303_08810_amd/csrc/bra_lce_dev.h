@@ -122,8 +122,8 @@ struct AddJob {
     int ldi, ldo, cblocks, blocks, groups;       // groups: of VW pairs of columns in a row
 };
 
-// Workgroup `block` of J, NT threads; table: [25][64].  ADDS = false: Out = LCE(In).
-template <int VW, bool ADDS, int NT, typename TM>
+// Workgroup `block` of J, NT threads; table: [25][64].  ADDS = false: Out = LCE(In).  AHEAD: rows requested a row ahead.
+template <int VW, bool ADDS, int NT, bool AHEAD = true, typename TM>
 __device__ __forceinline__ void lce_block(const AddJob<TM> &J, const Dims &D, int block, float *table)
 {
     constexpr int CPW = 64 / VW;
@@ -156,12 +156,13 @@ __device__ __forceinline__ void lce_block(const AddJob<TM> &J, const Dims &D, in
 #pragma unroll
         for (int j = 0; j < 6; ++j) raw[dy % 2][j] = load_channels<VW>((const TM *)(row + xo[j]));
     };
-    request(0);
+    if (AHEAD) request(0);
 #pragma unroll
     for (int dy = 0; dy < kLceRows + 4; ++dy) {
         const int y = y0 + dy - 2;
-        if (dy + 1 < kLceRows + 4) request(dy + 1);
+        if (AHEAD && dy + 1 < kLceRows + 4) request(dy + 1);
         if (y < 0 || y >= D.H) continue;
+        if (!AHEAD) request(dy);
         Channels<VW> in[6];
 #pragma unroll
         for (int j = 0; j < 6; ++j) in[j] = raw[dy % 2][j];
@@ -204,11 +205,13 @@ __device__ __forceinline__ void lce_block(const AddJob<TM> &J, const Dims &D, in
     }
 }
 
-template <typename TM, int VW>
-__global__ __launch_bounds__(256, 4) void k_lce(AddJob<TM> J, Dims D)
+// Not ahead with five workgroups per compute unit, by 13 registers: where four take a second round for what is left (layer with a given index, us, ahead / not: 32 x 28 x 28 x 160 bf16, 1176
+// workgroups 68.9 / 66.6, 27 x 35 x 35 x 96, 1094 108.4 / 107.0; against that 784: 32 x 28 x 28 x 128 float32 70.0 / 70.7; 1536: 4 x 64 x 128 x 160 96.8 / 99.1; 98: 1 x 56 x 56 x 64 22.8 / 24.4).
+template <typename TM, int VW, bool AHEAD>
+__global__ __launch_bounds__(256, AHEAD ? 4 : 5) void k_lce(AddJob<TM> J, Dims D)
 {
     __shared__ float table[25 * 64];
-    lce_block<VW, true, 256>(J, D, mfma::swizzled_block(), table);
+    lce_block<VW, true, 256, AHEAD>(J, D, mfma::swizzled_block(), table);
 }
 
 // The same for maps that k_lce's 32-bit offsets and numbers do not cover: a thread takes kLceRows rows of one column, all
@@ -292,8 +295,9 @@ int launch_lce(const Dims &D, const TM *In, int ldi, const Taps &taps, TM *Out, 
     if (!J.blocks && blocks > 0x7ffffff0L) return BRA_ERR_UNSUPPORTED;
     ProfScope ps(st, kernel_id);
     const dim3 far((unsigned)((blocks + 7) / 8 * 8)), near((unsigned)J.blocks);
-    if (J.blocks && two) hipLaunchKernelGGL((k_lce<TM, 2>), near, dim3(256), 0, st, J, D);
-    else if (J.blocks) hipLaunchKernelGGL((k_lce<TM, 1>), near, dim3(256), 0, st, J, D);
+    if (J.blocks && two && J.blocks > 4 * 256 && J.blocks <= 5 * 256) hipLaunchKernelGGL((k_lce<TM, 2, false>), near, dim3(256), 0, st, J, D);
+    else if (J.blocks && two) hipLaunchKernelGGL((k_lce<TM, 2, true>), near, dim3(256), 0, st, J, D);
+    else if (J.blocks) hipLaunchKernelGGL((k_lce<TM, 1, true>), near, dim3(256), 0, st, J, D);
     else if (two) hipLaunchKernelGGL((k_lce_far<TM, 2>), far, dim3(256), 0, st, In, ldi, taps, Out, ldo, D, J.cblocks);
     else hipLaunchKernelGGL((k_lce_far<TM, 1>), far, dim3(256), 0, st, In, ldi, taps, Out, ldo, D, J.cblocks);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;

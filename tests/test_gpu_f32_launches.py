@@ -31,7 +31,8 @@ def test_convolutions_beside(dtype, B, H, W, C, heads, S, k):
     compare_backward(X, Wqkv, Wo, Wlce, dtype, heads, S, k, path="generic")
 
 
-@pytest.mark.parametrize("dtype,B,H,W,C,heads,S,k", [SHAPES[1], SHAPES[3], SHAPES[5]])
+@pytest.mark.parametrize("dtype,B,H,W,C,heads,S,k", [SHAPES[1], SHAPES[3], SHAPES[5],
+    ("f32", 132, 30, 14, 64, 2, 2, 1)])      # 1056 workgroups: those that five to a compute unit take in one round
 def test_convolution_alone(dtype, B, H, W, C, heads, S, k):
     X, Wqkv, Wo, Wlce = make_inputs(B, H, W, C, seed=9560 + H * W + C, dtype=dtype)
     rng = np.random.Generator(np.random.PCG64(9561))
