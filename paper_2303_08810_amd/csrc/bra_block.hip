@@ -721,12 +721,10 @@ int launch_mlp_stream(const Dims &D, int hidden, const bf16_t *X1, const bf16_t 
                       bf16_t *Xout, float eps, hipStream_t st)
 {
     const size_t smem = MlpStreamSmem<CT>::bytes(hidden);
-    static size_t opted = 0;
-    if (smem > opted) {
-        if (hipFuncSetAttribute((const void *)k_mlp_stream<CT, NW>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)smem) != hipSuccess)
-            return BRA_ERR_LAUNCH;
-        opted = smem;
+    static bool opted = false;       // for all sizes at once: threads with different ones do not take it from each other
+    if (!opted) {
+        if (hipFuncSetAttribute((const void *)k_mlp_stream<CT, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess) return BRA_ERR_LAUNCH;
+        opted = true;
     }
     const long tokens = (long)D.B * D.N, grid = (tokens + 16 * NW - 1) / (16 * NW);
     ProfScope ps(st, K_BLK_MLP_FUSED);
@@ -888,10 +886,10 @@ template <int CT>
 int launch_mlp_few(const Dims &D, int hidden, const bf16_t *X1, const bf16_t *Y, const bra_block_params &p, bf16_t *Xout, float eps, hipStream_t st)
 {
     const size_t smem = MlpFewSmem<CT>::bytes(hidden);
-    static size_t opted = 0;
-    if (smem > opted) {
-        if (hipFuncSetAttribute((const void *)k_mlp_few<CT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) return BRA_ERR_LAUNCH;
-        opted = smem;
+    static bool opted = false;       // for all sizes at once: threads with different ones do not take it from each other
+    if (!opted) {
+        if (hipFuncSetAttribute((const void *)k_mlp_few<CT>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess) return BRA_ERR_LAUNCH;
+        opted = true;
     }
     const long tokens = (long)D.B * D.N;
     ProfScope ps(st, K_BLK_MLP_FUSED);
