@@ -6,7 +6,7 @@
 // whole workgroup: one wavefront per head with a chain of loads, barriers and products per block, and on the key side the most
 // popular region's list on one compute unit.  Whole gradient, us, with those and so: 8 x 28 x 28 x 128, k = 4 82.9 -> 74.4 (query side with the tap
 // gradients' pass 20.6 -> 18.1, key side 25.2 -> 16.8); 3 x 32 x 32 x 128, S = 16, k = 11 80.9 -> 73.6; 12 x 24 x 24 x 64, S = 8, k = 30 160 -> 95; bf16 4 x 14 x 28 x
-// 96, k = 16 66.9 -> 43.8; 60 x 28 x 28 x 96, k = 4 270 -> 252; 8 x 35 x 35 x 64, k = 2 65.3 -> 64.7.  A pass with two channels per thread would take 190
+// 96, k = 16 66.9 -> 43.8; 60 x 28 x 28 x 96, k = 4 270 -> 252; 16 x 35 x 35 x 96, k = 8 304 -> 257.  A pass with two channels per thread would take 190
 // registers and leave two wavefronts per SIMD.
 #pragma once
 
@@ -49,6 +49,8 @@ __device__ __forceinline__ f32x4 total(const f32x4 *sums, int hl, int lane, int 
 // Query side, see k_attn_bwd_q: O, lse, D and dQ of NQ tiles of 16 queries.  The weights and dP of up to kKept tiles of keys per
 // wavefront stay in registers; of more, they are formed twice.  Scores are scaled behind their products, here and on the key side, and rounded once: the
 // statistics belong to the very scores that the key side forms, and terms that cancel do.
+// Four wavefronts per SIMD, which spill 2 and 4 registers where two wavefronts or one have a head; three, which spill none: 8 x 28 x 28 x 128, k = 4 74.3 -> 73.9 us, 6 images 69.3 -> 70.2, 12 images
+// 102.9 -> 103.4.
 template <int NQ>
 constexpr int kKeptTiles = NQ == 1 ? 4 : 2;
 

@@ -377,7 +377,8 @@ bool attention_by_image(const Dims &D, int hgroups)
 // 89.4 / 84.8, bf16 64 x 28 x 28 x 96, k = 16 677 / 641, 1 x 192 x 192 x 96, S = 16, k = 4 790 / 767; against that bf16 1 x 56 x 84 x 96, k = 3 120.4 / 132.2, 1 x
 // 112 x 96 x 96, S = 16, k = 16 328.5 / 362.3, float32 1 x 48 x 48 x 192, S = 8, k = 2 82.6 / 88.7, 2 x 40 x 104 x 96, S = 8, k = 1 108.1 / 115.1.  Of one or
 // two head groups neither is the better one on average (0.90 to 1.05) until a region reads most of its image (2 x 21 x 21 x 256, k = 49
-// 156.8 / 164.0).
+// 156.8 / 164.0).  With a head for one, two or four wavefronts 0.96 to 1.02: bf16 4 x 28 x 28 x 96, k = 2 46.2 / 44.1, float32 14 x 28 x 28 x 128, k = 4 108.6 / 107.5, 4 x 35 x 35 x 192, k = 2
+// 104.5 / 102.5; against that 6 x 28 x 28 x 128, k = 12 89.1 / 90.9, 6 x 28 x 28 x 64, k = 4 47.0 / 47.7.
 bool gradients_by_image(const Dims &D, int hgroups, long workgroups)
 {
     return (long)D.B * hgroups >= 8 || workgroups >= 2048 || (hgroups <= 2 && 2L * D.k <= D.R);

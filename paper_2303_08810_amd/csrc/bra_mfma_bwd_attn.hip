@@ -32,7 +32,8 @@
 // float64 2.44e-3 -> 2.26e-3).  The tap gradients alone stay a pass.  Together with SINGLE, 64 x 56 x 56 x 64, k = 1: query side 71 -> 55 us,
 // key side 66 -> 58, whole gradient 209 -> 181; 16 images 79.3 -> 77.9, 2 images 40.0 -> 40.1.  Of the key side's 58 us the attention takes 43, the
 // products of the convolution 6, the halo's loads 5; the list of regions made while they arrive gave nothing, and the convolution
-// beside the first block costs 90 registers of scratch.  With more than one block (36 tokens, k = 6; 63 tokens, k = 4) it is 0 to 9 % slower than the passes.
+// beside the first block costs 90 registers of scratch.  Four
+// wavefronts per SIMD spill 6 registers of the key side; three, which spill none: 64 x 56 x 56 x 64 178.8 -> 180.5 us, 16 images 74.2 -> 74.5.  With more than one block (36 tokens, k = 6; 63 tokens, k = 4) it is 0 to 9 % slower than the passes.
 // SINGLE: all routed keys in one block: a head's scores and dP stay in registers from the weights to dS, which takes out the second sweep (a
 // third of the vector instructions) and 50 registers; 44 x 21 x 21 x 512, k = 2 281 -> 275 us.
 #include "bra_attn_dev.h"
