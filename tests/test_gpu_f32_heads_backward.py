@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [  # (dtype, B, H, W, C, heads, S, k)
     ("f32", 4, 28, 28, 96, 3, 7, 4),       # 588 heads of regions: four wavefronts each
-    ("f32", 25, 8, 16, 48, 3, 4, 3),       # 1200: two on the key side, one on the query side
+    ("f32", 25, 8, 16, 48, 3, 4, 3),       # 1200: two
+    ("f32", 26, 8, 16, 48, 3, 4, 3),       # 1248: one on the query side, two on the key side
     ("f32", 50, 8, 8, 32, 2, 4, 2),        # 1600: two heads, two wavefronts
     ("f32", 51, 8, 8, 32, 2, 4, 2),        # 1632
     ("f32", 40, 12, 12, 96, 3, 4, 5),      # 1920: one

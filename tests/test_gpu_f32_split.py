@@ -18,7 +18,8 @@ SHAPES = [  # (B, H, W, C, heads, S, k)
     (1, 14, 14, 160, 5, 7, 9),       # ten steps
     (2, 16, 16, 256, 8, 4, 3),       # 16 tokens: a tile
     (1, 21, 12, 192, 6, 3, 2),       # 28: 32 rows
-    (1, 32, 16, 128, 4, 4, 2),       # 32
+    (1, 8, 16, 256, 8, 2, 2),        # 32
+    (1, 32, 16, 128, 4, 4, 2),       # 32, 48 tiles of 64 x 64 at K = 128: the other kernel
     (1, 34, 4, 96, 3, 2, 1),         # 34: the other kernel
     (3, 14, 14, 256, 8, 7, 6),       # 32 rows, 588 of them
     (3, 14, 28, 256, 8, 7, 6),       # beyond
