@@ -711,12 +711,11 @@ __device__ __forceinline__ void split_tile(const bf16_t *__restrict__ In, const 
 
 constexpr int kSplitWaves = 8;
 
-template <bool BT>
 __global__ __launch_bounds__(64 * kSplitWaves) void k_gemm_split(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int M, int K, int Nout,
                                                                  GemmOut out)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    split_tile<BT, false, kSplitWaves>(In, W, ldw, M, K, Nout, out, blockIdx.x, smem);
+    split_tile<false, false, kSplitWaves>(In, W, ldw, M, K, Nout, out, blockIdx.x, smem);
 }
 
 __global__ __launch_bounds__(64 * kSplitWaves) void k_gemm_means_split(const bf16_t *__restrict__ In, const bf16_t *__restrict__ W, int ldw, int K, int Nout,
@@ -748,12 +747,11 @@ bool splits(long blocks, int K, int Nout, int cols)
     return Nout % 32 == 0 && cols % 32 == 0 && blocks <= (K >= 1024 ? 512 : K >= 256 ? 256 : 0);
 }
 
-template <bool BT>
 int launch_split(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, const GemmOut &out, hipStream_t st)
 {
     static bool opted = false;
-    if (!opt_in(k_gemm_split<BT>, opted)) return BRA_ERR_LAUNCH;
-    hipLaunchKernelGGL(k_gemm_split<BT>, dim3((unsigned)split_blocks(M, Nout)), dim3(64 * kSplitWaves), split_bytes<kSplitWaves>(), st, In, W, ldw, (int)M, K, Nout, out);
+    if (!opt_in(k_gemm_split, opted)) return BRA_ERR_LAUNCH;
+    hipLaunchKernelGGL(k_gemm_split, dim3((unsigned)split_blocks(M, Nout)), dim3(64 * kSplitWaves), split_bytes<kSplitWaves>(), st, In, W, ldw, (int)M, K, Nout, out);
     return hipGetLastError() == hipSuccess ? BRA_OK : BRA_ERR_LAUNCH;
 }
 
@@ -1026,7 +1024,7 @@ int gemm(const bf16_t *In, const bf16_t *W, int ldw, long M, int K, int Nout, co
     }
     ProfScope ps(st, kernel_id);
     // float32 copies: as with Q, K and V for all callers (bra_route decides on the same bits as bra_forward)
-    if (!regions && splits(split_blocks(M, out.f32[0] ? 3 * out.cols : Nout), K, Nout, out.cols)) return launch_split<false>(In, W, ldw, M, K, Nout, out, st);
+    if (!regions && splits(split_blocks(M, out.f32[0] ? 3 * out.cols : Nout), K, Nout, out.cols)) return launch_split(In, W, ldw, M, K, Nout, out, st);
     if (regions) return launch_big<true>(In, W, ldw, M, K, Nout, out, *regions, st);
     return launch_big<false>(In, W, ldw, M, K, Nout, out, GemmRegions{}, st);
 }
@@ -1057,7 +1055,6 @@ int gemm_bt(const bf16_t *In, const bf16_t *Wt, int ldw, long M, int K, int Nout
     if (!sizes_ok(M, K, Nout)) return BRA_ERR_UNSUPPORTED;
     const GemmOut out = {{Out, nullptr, nullptr}, Nout, {nullptr, nullptr}, nullptr, nullptr, 0};
     ProfScope ps(st, kernel_id);
-    if (splits(split_blocks(M, Nout), K, Nout, Nout)) return launch_split<true>(In, Wt, ldw, M, K, Nout, out, st);
     return launch_big<false, true>(In, Wt, ldw, M, K, Nout, out, GemmRegions{}, st);
 }
 

@@ -17,6 +17,7 @@ SHAPES = [  # (B, H, W, C, heads, S, k, hidden)
     (1, 3, 5, 256, 8, 1, 1, 320),
     (16, 16, 16, 256, 8, 4, 2, 256),     # 4096 tokens
     (1, 17, 241, 192, 6, 1, 1, 192),     # 4097: the other kernel
+    (1, 64, 66, 128, 4, 2, 1, 192),      # 4224: the other kernel, 4 wavefronts
     (1, 14, 14, 768, 24, 7, 4, 768),     # several chunks of channels per lane
     (1, 28, 28, 320, 10, 7, 4, 320),
     (1, 35, 28, 320, 10, 7, 4, 320),     # beyond that line

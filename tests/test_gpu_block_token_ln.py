@@ -15,6 +15,7 @@ SHAPES = [  # (dtype, B, H, W, C, heads, S, k)
     ("f32", 1, 4, 4, 1024, 16, 2, 1),    # four
     ("f32", 1, 2, 4, 1056, 33, 2, 1),    # five: the other kernel
     ("f32", 1, 4, 6, 30, 2, 2, 1),
+    ("bf16", 1, 4, 6, 30, 2, 2, 1),
     ("bf16", 42, 28, 28, 96, 3, 7, 1),   # two tokens per group
     ("f32", 42, 28, 28, 96, 3, 7, 1),
 ]

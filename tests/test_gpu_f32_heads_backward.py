@@ -42,6 +42,13 @@ SHAPES = [  # (dtype, B, H, W, C, heads, S, k)
     ("f32", 7, 14, 28, 128, 4, 7, 32),
     ("f32", 7, 14, 28, 128, 4, 7, 33),
     ("f32", 11, 21, 42, 96, 3, 7, 4),      # 18 tokens, 5 tiles: two
+    # heads of 10 channels, four wavefronts, with one and with two tiles of tokens; two on the query side and on both; one, in loads of four too
+    ("f32", 2, 12, 12, 30, 3, 3, 4),
+    ("f32", 2, 15, 15, 30, 3, 3, 3),
+    ("f32", 2, 15, 15, 30, 3, 3, 1),
+    ("f32", 2, 9, 18, 30, 3, 3, 1),
+    ("f32", 60, 9, 18, 30, 3, 3, 1),
+    ("f32", 60, 9, 18, 96, 3, 3, 1),
     # 17 to 32 tokens: one block of 33 to 64 keys, of two heads to a workgroup; 32 keys and 66
     ("f32", 2, 12, 10, 64, 2, 2, 2),       # 30 tokens, 60 keys
     ("f32", 3, 16, 32, 160, 5, 4, 2),      # 64 keys, an odd number of heads
