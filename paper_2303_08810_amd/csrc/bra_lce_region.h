@@ -78,6 +78,21 @@ struct LaneTaps {
     }
 };
 
+// Row y of an item's window (0 .. 7), as pairs of columns (j, j + 1), into the sums of the 4 x 4 outputs that it belongs to.
+__device__ __forceinline__ void add_row(int y, const unsigned (&p)[7], const unsigned (&w)[5][3], float (&o)[4][4])
+{
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        if (y < a || y > a + 4) continue;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            o[a][c] = dot2(w[y - a][0], p[c], o[a][c]);
+            o[a][c] = dot2(w[y - a][1], p[c + 2], o[a][c]);
+            o[a][c] = dot2(w[y - a][2], p[c + 3], o[a][c]);
+        }
+    }
+}
+
 // Sums of the lane's channel: lane group q has items q, q + 4, .. , ROUNDS of them; o[round][row][column].
 template <int ROUNDS>
 __device__ __forceinline__ void halo_sums(const RegionHalo &r, const bf16_t *halo, const unsigned (&w)[5][3], int wave, int lane, float (&o)[ROUNDS][4][4])
@@ -108,16 +123,7 @@ __device__ __forceinline__ void halo_sums(const RegionHalo &r, const bf16_t *hal
             }
 #pragma unroll
             for (int j = 1; j < 7; j += 2) p[j] = __builtin_amdgcn_alignbit(p[j + 1], p[j - 1], 16);
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                if (y < a || y > a + 4) continue;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    o[round][a][c] = dot2(w[y - a][0], p[c], o[round][a][c]);
-                    o[round][a][c] = dot2(w[y - a][1], p[c + 2], o[round][a][c]);
-                    o[round][a][c] = dot2(w[y - a][2], p[c + 3], o[round][a][c]);
-                }
-            }
+            add_row(y, p, w, o[round]);
         }
     }
 }
@@ -187,16 +193,7 @@ struct SliceItem {
         for (int y = 0; y < 8; ++y) {
             unsigned p[7];
             pairs(slice, zero, y, D, pitch, p);
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                if (y < a || y > a + 4) continue;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    o[a][c] = dot2(w[y - a][0], p[c], o[a][c]);
-                    o[a][c] = dot2(w[y - a][1], p[c + 2], o[a][c]);
-                    o[a][c] = dot2(w[y - a][2], p[c + 3], o[a][c]);
-                }
-            }
+            add_row(y, p, w, o);
         }
     }
     // Tap gradients: the image's own V against the window in dO; acc[5 ky + kx] belongs to tap 24 - (5 ky + kx).  Tokens of V that the items before have are
